@@ -8,12 +8,21 @@
 // copied transposed in memory.
 //
 // Tiling: 256 x 256 x 64 per workgroup of 4 wavefronts (2 x 2), each wavefront owning 128 x 128 =
-// 4 x 4 tiles of v_mfma_f32_32x32x16_bf16 with fp32 accumulators (256 accumulator registers per
+// 8 x 8 tiles of v_mfma_f32_16x16x32_bf16 with fp32 accumulators (256 accumulation registers per
 // lane, one wavefront per SIMD).  Operand tiles (32 KB each) live in a ring of five LDS slots
 // filled by direct global-to-LDS loads (no staging registers): two slots are being multiplied,
 // up to three are in flight, so the load path never drains at the per-step barrier.  Rows are
 // 128 B and the eight 16-byte pieces of a row are XOR-swizzled with the row index so that the
 // 16-byte fragment reads spread over all banks.
+//
+// What bounds it, and why this MFMA shape: at full load the board sits at its power cap and the clock gives way, so
+// energy per multiply-add is what counts.  From registers alone, on random operands, 32x32x16 MFMAs sustain 1.79 PFLOP/s
+// at 1.81 GHz and 16x16x32 ones 2.03 PFLOP/s at 2.07 GHz: per multiply-add they move half the accumulators.  They also
+// take twice the instructions, so the loop is scheduled by hand (see there).  Measured on one box against the
+// 32x32x16 loop it replaces: gate/up (43008 x 22016 x 4096) 5.40 -> 5.05 ms (1.44 -> 1.54 PFLOP/s), down
+// (43008 x 4096 x 11008) 2.59 -> 2.45 ms (1.50 -> 1.59), dWg (4096 x 11008 over 26112 rows) 1.73 -> 1.59 ms
+// (1.36 -> 1.48); with 16 workgroups on the chip, where the clock stays up and the step is issue-bound, 0.92 -> 0.94 us
+// per step.
 //
 // The MFMA is issued with the B fragment as the first operand, so the accumulator tile is the
 // transpose of the usual one: a lane holds, for one output row m, runs of 4 consecutive n.
@@ -27,8 +36,8 @@ namespace pcm {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // 16 bytes that only pass through registers
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 
@@ -45,7 +54,7 @@ constexpr int kRingSlots = 5;    // operand tiles resident or in flight in LDS
 // Epilogues pass their results through LDS so that global stores are whole 128-byte lines: each
 // wavefront owns a private staging area (no workgroup barrier needed; LDS operations of one
 // wavefront execute in order).
-constexpr int kWaveStageBytes = 33792;                       // 128 rows x (256 + 8) bytes
+constexpr int kWaveStageBytes = 34816;                       // 128 rows x (256 + 16) bytes
 constexpr int kSmemBytes = kRingSlots * kTileM * kTileK * 2;   // 160 KB: the whole LDS of a CU
 static_assert(4 * kWaveStageBytes <= kSmemBytes, "epilogue staging must fit in the operand ring");
 
@@ -74,15 +83,27 @@ struct GemmProblem {
 };
 enum RowsRole : int { kRowsUnused = 0, kRowsAreM = 1, kRowsAreK = 2 };
 
-// Accumulator coordinates.  For tile (i, j) of the wavefront and register e = 4 * q + t:
-//   row  m = m0 + wm * 128 + i * 32 + (lane & 31)
-//   col  n = n0 + wn * 128 + j * 32 + 8 * q + 4 * (lane >> 5) + t
+// Accumulators of a wavefront: 8 x 8 tiles of 16 x 16.  Tile (i, j), register t of a lane is
+//   row  m = m0 + wm * 128 + i * 16 + (lane & 15)
+//   col  n = n0 + wn * 128 + j * 16 + 4 * (lane >> 4) + t
+using Accumulators = f32x4[8][8];
 struct TileCoord {
     int m0, n0, wm, wn, lane;
     int split;   // which part of a split reduction this workgroup computed
-    __device__ int row(int i) const { return m0 + wm * 128 + i * 32 + (lane & 31); }
-    __device__ int col(int j, int q) const { return n0 + wn * 128 + j * 32 + 8 * q + 4 * (lane >> 5); }
+    __device__ int row(int i) const { return m0 + wm * 128 + i * 16 + (lane & 15); }
+    __device__ int col(int j) const { return n0 + wn * 128 + j * 16 + 4 * (lane >> 4); }
 };
+
+// f(0), f(1), .. f(kN - 1) with the number as a constant.
+template <int kI>
+struct Index { static constexpr int value = kI; };
+template <int kN, int kI = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (kI < kN) {
+        f(Index<kI>{});
+        static_for<kN, kI + 1>(f);
+    }
+}
 
 __device__ inline bf16x4 to_bf16x4(float a, float b, float c, float d) {
     bf16x4 r;
@@ -96,17 +117,10 @@ __device__ inline bf16x4 to_bf16x4(float a, float b, float c, float d) {
 // (bit 0 already selects the half window).
 __device__ inline int swizzle_piece(int row, int piece) { return piece ^ ((row >> 1) & 7); }
 // [K][rows] tiles (512-byte k-rows, read by transpose reads of four k-rows x 32 bytes per 16 lanes,
-// 32 lanes per cycle): within a 16-lane group the four k-rows are spread by XOR with k & 3; the two
-// groups served together read the same k-rows at adjacent 32-byte units, so bits 0 and 2 of the
-// unit index are exchanged to put them in different half windows.  Self-inverse for fixed k.
-__device__ inline int swizzle_unit(int unit, int k_low2) {
-    const int swapped = ((unit & 1) << 2) | (unit & 2) | ((unit >> 2) & 1) | (unit & 8);
-    return swapped ^ k_low2;
-}
-__device__ inline int unswizzle_unit(int phys, int k_low2) {
-    const int t = phys ^ k_low2;
-    return ((t & 1) << 2) | (t & 2) | ((t >> 2) & 1) | (t & 8);
-}
+// 32 lanes per cycle): a k-row spans all banks twice, so the 32-byte unit alone decides the banks.  The
+// four k-rows of a 16-lane group are spread by XOR with k & 3; the two groups served together read the
+// same unit eight k-rows apart, hence bit 3 of k on unit bit 2.  Self-inverse for fixed k.
+__device__ inline int swizzle_unit(int unit, int k) { return unit ^ (k & 3) ^ ((k >> 1) & 4); }
 
 // Workgroup id -> (tile_m, tile_n), or false if the workgroup has no tile.  Consecutive hardware
 // workgroup ids go to different XCDs (id mod 8), each with its own L2.  The live tiles are numbered
@@ -153,6 +167,24 @@ __device__ inline void direct_load_16B(const char* base, uint32_t lane_offset, u
                  : "s"(lds_addr), "v"(lane_offset), "s"(base)
                  : "memory");
 }
+// acc += B fragment x A fragment.  Inline assembly so that the accumulators stay in the accumulation registers: through
+// the builtin the register allocator moves them back and forth.  Operands of the next MFMAs come from LDS reads (the
+// compiler waits for those before it passes the registers on), never from a vector instruction right before.
+__device__ __forceinline__ void mfma_16x16x32(f32x4& acc, bf16x8 b, bf16x8 a) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
+}
+// The same around direct_load_16B to lds_addr + kLdsOffset: a load into LDS may not follow the write of m0 directly,
+// and the MFMA is the instruction in between.
+template <uint32_t kLdsOffset>
+__device__ __forceinline__ void mfma_16x16x32_and_load(f32x4& acc, bf16x8 b, bf16x8 a, const char* base, uint32_t lane_offset,
+                                                       uint32_t lds_addr) {
+    asm volatile("s_add_u32 m0, %1, %2\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %0, %3, %4, %0\n\t"
+                 "global_load_lds_dwordx4 %5, %6"
+                 : "+a"(acc)
+                 : "s"(lds_addr), "n"(kLdsOffset), "v"(b), "v"(a), "v"(lane_offset), "s"(base)
+                 : "memory", "scc");
+}
 // Direct loads retire in issue order, so waiting until at most `newest` remain outstanding
 // guarantees that all older ones have landed.
 template <int kNewest>
@@ -160,16 +192,26 @@ __device__ inline void wait_direct_loads() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kNewest) : "memory");
 }
 
-// 8 bf16 of one operand row at 8 consecutive k, from a [K][rows] tile: two transpose reads of 4 k
-// each.  Within a group of 16 lanes the instruction hands lane j the j-th 16-bit element of each of
-// the four 32-byte runs addressed by lanes 4 q .. 4 q + 3 (q = 0..3); the callers point run q at
-// k-row q, so lane j receives k = 0..3 of row j.
-__device__ inline bf16x8 read_transposed_fragment(const char* lds_ptr) {
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(lds_ptr));
-    const s16x4 hi =
-        __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(lds_ptr + 4 * 512));
-    const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, v);
+// 4 bf16 of one operand row at 4 consecutive k, from a [K][rows] tile: a transpose read.  Within a group of 16 lanes the
+// instruction hands lane j the j-th 16-bit element of each of the four 32-byte runs addressed by lanes
+// 4 q .. 4 q + 3 (q = 0..3); the callers point run q at k-row q, so lane j receives k = 0..3 of row j.
+__device__ inline s16x4 read_transposed(uint32_t lds_addr) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)lds_addr);
+}
+__device__ inline bf16x8 join_halves(s16x4 lo, s16x4 hi) {
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Addresses of LDS reads, written as assembly so that they stay where the main loop puts them, a gap before the read.
+__device__ __forceinline__ uint32_t fragment_address(uint32_t base, int xor_with) {
+    uint32_t at;
+    asm volatile("v_xor_b32 %0, %1, %2" : "=v"(at) : "i"(xor_with), "v"(base));
+    return at;
+}
+__device__ __forceinline__ uint32_t fragment_address_sum(uint32_t lane_base, uint32_t slot) {
+    uint32_t at;
+    asm volatile("v_add_u32 %0, %1, %2" : "=v"(at) : "s"(slot), "v"(lane_base));
+    return at;
 }
 
 // An epilogue may ask to run although the workgroup's reduction range is empty and skip_if_empty is set (it then
@@ -220,15 +262,15 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
     const uint32_t lds_base = (uint32_t)(uintptr_t)PCM_AS_LDS(smem);
     struct LoadCtx {
         const char* base;        // wave-uniform
-        uint32_t off[2];         // per-lane byte offset of an even / odd load before the per-load stride
+        uint32_t off[4];         // per-lane byte offset of a load before the per-load stride, by load_variant
         uint32_t stride;         // bytes between consecutive loads
         uint32_t dst;            // LDS byte address of this wave's part of the slot
     };
     // operand 0 = A rows m0.., operand 1 = B rows n0..  Per-lane offsets do not depend on the step; the
     // tile origin is a wave-uniform pointer that walks along k.
-    uint32_t lane_off[2][2], load_stride[2];
+    uint32_t lane_off[2][4], load_stride[2];
     const char* seg_origin[2][2];          // [operand][segment]: this tile's bytes at k = 0 of the segment
-    int64_t k_step_bytes[2];               // distance between consecutive steps
+    uint32_t k_step_bytes[2];              // distance between consecutive steps
 #pragma unroll
     for (int operand = 0; operand < 2; ++operand) {
         const uint32_t ld = (uint32_t)(operand == 0 ? p.lda : p.ldb);
@@ -240,9 +282,9 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
         if (layout == kRowsByK) {
             const uint32_t row = (uint32_t)wave * 64u + (uint32_t)(lane >> 3);      // + 8 r for load r
 #pragma unroll
-            for (uint32_t odd = 0; odd < 2; ++odd) {                                 // the swizzle may use row bit 3
-                const uint32_t piece = (uint32_t)swizzle_piece((lane >> 3) + 8 * odd, lane & 7);
-                lane_off[operand][odd] = (row * ld + piece * 8u) * 2u;
+            for (uint32_t var = 0; var < 4; ++var) {                                 // the swizzle uses row bit 3
+                const uint32_t piece = (uint32_t)swizzle_piece((lane >> 3) + 8 * (var & 1), lane & 7);
+                lane_off[operand][var] = (row * ld + piece * 8u) * 2u;
             }
             load_stride[operand] = 16u * ld;
             seg_origin[operand][0] = reinterpret_cast<const char*>(s1 + (int64_t)row0 * ld);
@@ -251,27 +293,27 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
         } else {
             const uint32_t krow = (uint32_t)wave * 16u + (uint32_t)(lane >> 5);      // + 2 r for load r
 #pragma unroll
-            for (uint32_t odd = 0; odd < 2; ++odd) {
-                const uint32_t k_low = 2u * odd + (uint32_t)(lane >> 5);             // (k-row of the load) & 3
-                const uint32_t piece = 2u * (uint32_t)unswizzle_unit((lane & 31) >> 1, (int)k_low) + (uint32_t)(lane & 1);
-                lane_off[operand][odd] = (krow * ld + piece * 8u) * 2u;
+            for (uint32_t var = 0; var < 4; ++var) {                                 // bits 0, 1 and 3 of the k-row
+                const int k = (int)(lane >> 5) + 2 * (int)(var & 1) + 8 * (int)(var >> 1);
+                const uint32_t piece = 2u * (uint32_t)swizzle_unit((lane & 31) >> 1, k) + (uint32_t)(lane & 1);
+                lane_off[operand][var] = (krow * ld + piece * 8u) * 2u;
             }
             load_stride[operand] = 4u * ld;
             seg_origin[operand][0] = reinterpret_cast<const char*>(s1 + row0);
             seg_origin[operand][1] = reinterpret_cast<const char*>(s2 + row0);
-            k_step_bytes[operand] = (int64_t)kTileK * ld * 2;
+            k_step_bytes[operand] = (uint32_t)kTileK * ld * 2u;
         }
     }
     auto tile_origin = [&](int operand, int step) {
         const bool seg1 = step < steps1;
-        return seg_origin[operand][seg1 ? 0 : 1] + (int64_t)(seg1 ? step : step - steps1) * k_step_bytes[operand];
+        return seg_origin[operand][seg1 ? 0 : 1] + (int64_t)(seg1 ? step : step - steps1) * (int64_t)k_step_bytes[operand];
     };
     // `slot` is the byte offset of a ring slot
     auto load_ctx_at = [&](int operand, uint32_t slot, const char* origin) {
         LoadCtx c;
         c.base = origin;
-        c.off[0] = lane_off[operand][0];
-        c.off[1] = lane_off[operand][1];
+#pragma unroll
+        for (int var = 0; var < 4; ++var) c.off[var] = lane_off[operand][var];
         c.stride = load_stride[operand];
         c.dst = lds_base + slot + (uint32_t)wave * 8192u;
         return c;
@@ -279,50 +321,39 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
     auto load_ctx = [&](int operand, uint32_t slot, int step) { return load_ctx_at(operand, slot, tile_origin(operand, step)); };
     auto issue_loads = [&](const LoadCtx& c, uint32_t r0, uint32_t n) {
 #pragma unroll
-        for (uint32_t r = r0; r < r0 + n; ++r) direct_load_16B(c.base, c.off[r & 1u] + r * c.stride, c.dst + r * 1024u);
+        for (uint32_t r = r0; r < r0 + n; ++r) direct_load_16B(c.base, c.off[(r & 1u) | ((r >> 1) & 2u)] + r * c.stride, c.dst + r * 1024u);
     };
 
-    f32x16 acc[4][4];
+    Accumulators acc;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Fragment registers are double-buffered: while the 16 MFMAs of one 16-wide k-slice run, the
-    // 8 fragment reads of the next slice are in flight.  Fragment pair i = rows 32 i .. 32 i + 31 of
-    // the wavefront's A and B sub-tiles.
-    bf16x8 fa[2][4], fb[2][4];
-    // byte offset inside a tile of this lane's fragment for row block i, slice ks
-    auto frag_offset = [&](int layout, int sub_row0, int ks, int i) -> uint32_t {
+    // Fragment registers are double-buffered: while the 64 MFMAs of one 32-wide k-slice run, the
+    // 16 fragment reads of the next slice are in flight.  Fragment i = rows 16 i .. 16 i + 15 of
+    // the wavefront's A or B sub-tile; lane l holds row l & 15, k = 8 (l >> 4) .. + 7 of the slice.
+    bf16x8 fa[2][8], fb[2][8];
+    // LDS address of this lane's fragment 0 of slice ks in a tile in ring slot 0.
+    //   [rows][K]: one 16-byte read; fragment i is 16 rows (2 KB) further.
+    //   [K][rows]: two transpose reads, the lane's run starting in k-row 8 (l >> 4) + ((l & 15) >> 2), the second four
+    //     k-rows further; fragment i is unit i of the wavefront's eight and the swizzle an XOR with a number below
+    //     eight, so it is at address ^ 32 i.
+    auto fragment_base = [&](int layout, int sub_row0, int ks) -> uint32_t {
         if (layout == kRowsByK) {
-            const int row = sub_row0 + i * 32 + (lane & 31);
-            const int piece = ks * 2 + (lane >> 5);
-            return (uint32_t)(row * (kTileK * 2) + swizzle_piece(row, piece) * 16);
+            const int row = sub_row0 + (lane & 15);
+            return lds_base + (uint32_t)(row * (kTileK * 2) + swizzle_piece(row, ks * 4 + (lane >> 4)) * 16);
         }
-        const int g = lane >> 4, j = lane & 15;                    // 16-lane group, lane in group
-        const int col0 = sub_row0 + i * 32 + (g & 1) * 16;         // this group's 16 rows of the operand
-        const int k = ks * 16 + (g >> 1) * 8 + (j >> 2);           // k-row this lane's run starts in
-        return (uint32_t)(k * 512 + (swizzle_unit(col0 >> 4, j >> 2) << 5) + ((j & 3) << 3));
+        const int k = (lane >> 4) * 8 + ((lane & 15) >> 2);
+        return lds_base + (uint32_t)((ks * 32 + k) * 512 + (swizzle_unit(sub_row0 >> 4, k) << 5) + ((lane & 3) << 3));
     };
-    auto read_frag_a = [&](int set, uint32_t slot_a, int ks, int i) {
-        const char* sa = reinterpret_cast<const char*>(smem) + slot_a + frag_offset(kLayA, wm * 128, ks, i);
-        if (kLayA == kRowsByK) fa[set][i] = *reinterpret_cast<const bf16x8*>(sa);
-        else fa[set][i] = read_transposed_fragment(sa);
-    };
-    auto read_frag_b = [&](int set, uint32_t slot_b, int ks, int j) {
-        const char* sb = reinterpret_cast<const char*>(smem) + slot_b + frag_offset(kLayB, wn * 128, ks, j);
-        if (kLayB == kRowsByK) fb[set][j] = *reinterpret_cast<const bf16x8*>(sb);
-        else fb[set][j] = read_transposed_fragment(sb);
-    };
-    auto read_frag_pair = [&](int set, uint32_t slot_a, uint32_t slot_b, int ks, int i) {
-        read_frag_a(set, slot_a, ks, i);
-        read_frag_b(set, slot_b, ks, i);
-    };
-    auto read_frags = [&](int set, uint32_t slot_a, uint32_t slot_b, int ks) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) read_frag_pair(set, slot_a, slot_b, ks, i);
+    const uint32_t base_a[2] = {fragment_base(kLayA, wm * 128, 0), fragment_base(kLayA, wm * 128, 1)};
+    const uint32_t base_b[2] = {fragment_base(kLayB, wn * 128, 0), fragment_base(kLayB, wn * 128, 1)};
+    constexpr uint32_t kHalfFragment = 4 * 512;
+    // `at`: the address of the fragment for [K][rows] tiles, of fragment 0 for [rows][K] tiles.
+    auto read_fragment = [](int layout, uint32_t at, int i) -> bf16x8 {
+        if (layout == kRowsByK) return *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)(at + (uint32_t)i * 2048u);
+        return join_halves(read_transposed(at), read_transposed(at + kHalfFragment));
     };
     // ring slots are named by their byte offset in LDS
     auto next_slot = [](uint32_t s) { return s + kTileBytes >= (uint32_t)kSmemBytes ? s + kTileBytes - kSmemBytes : s + kTileBytes; };
@@ -339,102 +370,111 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
         issue_loads(load_ctx(0, 4 * kTileBytes, min(step_begin + 2, last)), 0, 8);
         wait_direct_loads<3 * kLoadsPerTile>();
         __syncthreads();
-        read_frags(0, 0 * kTileBytes, 1 * kTileBytes, 0);
-        // One 64-wide step per trip.  `sa`, `sb` are the slots of this step's tiles; the next step's
-        // are the two after them in the ring.  Fragment set 0 holds slice 0 of this step on entry and
-        // slice 0 of the next step on exit.  The single barrier sits before the last slice: by then
-        // every wavefront has issued all its reads of `sa`, `sb`, so both slots can be refilled, `sa`
-        // with the B tile of step + 2 and `sb` with the A tile of step + 3.  At the barrier only the
-        // newest tile (the A tile) may still be in flight.  The body is branch-free: near the end it
-        // re-requests tiles that nobody reads.
-        //
-        // A wavefront issues in order and an MFMA keeps the matrix pipe busy for 32 cycles, so
-        // whatever is issued between two MFMAs must fit in about 28 cycles or the pipe idles.  The
-        // order is therefore fixed by hand, one memory instruction per gap: per MFMA row of a 16-wide
-        // slice, one refill load (16 per step, one per row: issued together they would hold the
-        // texture path for about 1000 cycles) and up to three fragment reads of the next slice.  The
-        // last row has no reads, so that the reads of a slot have long landed when the barrier that
-        // frees the slot waits for them; its gaps carry the scalar bookkeeping of the tile pointers.
-        auto one_mfma = [&](int set, int i, int j) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
-        };
-        // Reads of the next slice in the order its MFMAs need them: B0, B1, B2, A0, B3 for the first
-        // row, then A1..A3.
-        auto read_next = [&](int set, uint32_t rs_a, uint32_t rs_b, int ks, int n) {
-            if (n < 3) read_frag_b(set, rs_b, ks, n);
-            else if (n == 3) read_frag_a(set, rs_a, ks, 0);
-            else if (n == 4) read_frag_b(set, rs_b, ks, 3);
-            else if (n < 8) read_frag_a(set, rs_a, ks, n - 4);
-        };
-        // The 16 MFMAs of a slice walk the 4 x 4 tiles in serpentine order, so that consecutive
-        // instructions always share one operand fragment.
-        auto col = [](int g, int j) { return (g & 1) ? 3 - j : j; };
-        auto slice = [&](int set, const LoadCtx& c, uint32_t half, uint32_t rs_a, uint32_t rs_b, int ks, auto hook) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                one_mfma(set, g, col(g, 0));
-                __builtin_amdgcn_sched_barrier(0);
-                issue_loads(c, half * 4 + g, 1);
-                __builtin_amdgcn_sched_barrier(0);
-                one_mfma(set, g, col(g, 1));
-                __builtin_amdgcn_sched_barrier(0);
-                if (g < 3) read_next(set ^ 1, rs_a, rs_b, ks, 3 * g);
-                __builtin_amdgcn_sched_barrier(0);
-                one_mfma(set, g, col(g, 2));
-                __builtin_amdgcn_sched_barrier(0);
-                if (g < 3) read_next(set ^ 1, rs_a, rs_b, ks, 3 * g + 1);
-                else hook(0);
-                __builtin_amdgcn_sched_barrier(0);
-                one_mfma(set, g, col(g, 3));
-                __builtin_amdgcn_sched_barrier(0);
-                if (g < 3) read_next(set ^ 1, rs_a, rs_b, ks, 3 * g + 2);
-                else hook(1);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+        for (int i = 0; i < 8; ++i) {
+            fa[0][i] = read_fragment(kLayA, kLayA == kRowsByK ? base_a[0] : base_a[0] ^ (uint32_t)(32 * i), i);
+            const uint32_t at_b0 = base_b[0] + kTileBytes;
+            fb[0][i] = read_fragment(kLayB, kLayB == kRowsByK ? at_b0 : at_b0 ^ (uint32_t)(32 * i), i);
+        }
+        // One 64-wide step per trip.  `sa`, `sb` are the slots of this step's tiles, `na`, `nb` the next step's, the two
+        // after them in the ring.  Fragment set 0 holds slice 0 of this step on entry and slice 0 of the next step on
+        // exit.  The single barrier sits before the second slice: by then every wavefront has issued all its reads of
+        // `sa`, `sb`, so both slots can be refilled, `sa` with the B tile of step + 2 (during the second slice) and `sb`
+        // with the A tile of step + 3 (during the next step's first).  At the barrier only the newest tile (the A tile)
+        // may still be in flight.  The body is branch-free: near the end it re-requests tiles that nobody reads.
+        //
+        // A wavefront issues in order and an MFMA keeps the matrix pipe busy for 16 cycles.  Measured with one wavefront
+        // per SIMD: between two MFMAs one scalar instruction, two vector instructions or an LDS read cost nothing, three
+        // dependent scalar ones 4 cycles, an LDS read right behind the vector instruction that makes its address 8.  The
+        // order is therefore fixed by hand: per MFMA row of a slice (8 MFMAs) one refill load (16 per step: issued
+        // together they would hold the texture path for about 1000 cycles) and, in the first six rows, up to three
+        // fragment reads of the next slice, with their addresses made at least one MFMA earlier.  The last two rows have
+        // no reads, so that the reads of a slot have long landed when the barrier that frees the slot waits for them;
+        // they carry the scalar bookkeeping of the tile pointers, a few instructions per gap.
+        //
+        // Fragments of the next slice are read in the order its MFMAs need them: A0, B0..B7, A1..A7.
+        auto is_a = [](int n) { return n == 0 || n >= 9; };
+        auto fragment_of = [&](int n) { return n == 0 ? 0 : (n < 9 ? n - 1 : n - 8); };
+        // The 64 MFMAs of a slice walk the 8 x 8 tiles in serpentine order, so that consecutive
+        // instructions always share one operand fragment.
+        // c: the tile refilled meanwhile; rd_a, rd_b: bases of the fragments of the next slice.
+        auto slice = [&](int set, const LoadCtx& c, uint32_t rd_a, uint32_t rd_b, auto hook) {
+            uint32_t tr_at = rd_a;       // [K][rows]: address of the fragment being read
+            s16x4 tr_lo = {0, 0, 0, 0};  // [K][rows]: its first half
+            static_for<8>([&](auto row) __attribute__((always_inline)) {
+                constexpr int g = decltype(row)::value;
+                constexpr int j0 = (g & 1) ? 7 : 0;
+                mfma_16x16x32_and_load<g * 1024u>(acc[g][j0], fb[set][j0], fa[set][g], c.base,
+                                                  c.off[(g & 1) | ((g >> 1) & 2)] + g * c.stride, c.dst);
+#pragma unroll
+                for (int jj = 1; jj < 8; ++jj) {
+                    const int j = (g & 1) ? 7 - jj : jj;
+                    mfma_16x16x32(acc[g][j], fb[set][j], fa[set][g]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    // read n of the next slice: [rows][K] in gap jj, [K][rows] in halves in gaps jj and jj + 1 with the
+                    // address of the next one made behind the second (behind the last one of a row in gap 7)
+                    const int n = 3 * g + (jj - 1) / 2;
+                    if (g < 6 && jj < 7 && n < 16) {
+                        const int f = fragment_of(n);
+                        const bool transposed = is_a(n) ? kLayA == kKByRows : kLayB == kKByRows;
+                        if (jj & 1) {
+                            if (transposed) tr_lo = read_transposed(tr_at);
+                            else if (is_a(n)) fa[set ^ 1][f] = read_fragment(kLayA, rd_a, f);
+                            else fb[set ^ 1][f] = read_fragment(kLayB, rd_b, f);
+                        } else if (transposed) {
+                            (is_a(n) ? fa : fb)[set ^ 1][f] = join_halves(tr_lo, read_transposed(tr_at + kHalfFragment));
+                        }
+                    }
+                    if (g < 6 && (jj == 2 || jj == 4 || jj == 7) && 3 * g + jj / 2 < 16) {
+                        const int next = 3 * g + jj / 2, f = fragment_of(next);
+                        if (is_a(next) ? kLayA == kKByRows : kLayB == kKByRows) tr_at = fragment_address(is_a(next) ? rd_a : rd_b, 32 * f);
+                    }
+                    if (g >= 6 && !(jj & 1)) hook(3 * (g - 6) + jj / 2 - 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
         };
-        uint32_t sa = 0;
-        LoadCtx pend_b = load_ctx(0, 4 * kTileBytes, min(step_begin + 2, last));   // nothing pending yet: harmless re-request
-        LoadCtx pend_a = pend_b;
-        // tile streams: origin of the newest tile requested so far of each operand, and its step
-        int at_a = min(step_begin + 2, last), at_b = min(step_begin + 1, last);
-        const char* origin_a = tile_origin(0, at_a);
-        const char* origin_b = tile_origin(1, at_b);
-        auto no_hook = [](int) {};
-        // The step counters run on past `last` (the origin then stands still, or lands once on the
-        // start of the second segment, which is valid memory whether or not that segment is used).
-        auto advance = [&](int operand) {
-            if (operand == 0) {
-                at_a += 1;
-                origin_a += at_a <= last ? k_step_bytes[0] : (int64_t)0;
-                origin_a = at_a == steps1 ? seg_origin[0][1] : origin_a;
+        // Tile streams: origin of the newest tile requested so far of each operand.  On entry of a step the newest A
+        // tile is that of step + 2 (its loads are those of the first slice: on the first trip a harmless second request),
+        // the newest B tile that of step + 1; the first slice then moves each on by one step.  Past `last` an origin
+        // stands still, or lands once on the start of the second segment, which is valid memory whether or not that
+        // segment is used.
+        const char* origin_a = tile_origin(0, min(step_begin + 2, last));
+        const char* origin_b = tile_origin(1, min(step_begin + 1, last));
+        uint32_t sa = 0, sb = next_slot(sa), refill_a = 4 * kTileBytes, na = next_slot(sb), nb = next_slot(na);
+        uint32_t rd_a = base_a[1] + sa, rd_b = base_b[1] + sb, stride_now = 0;
+        // In six pieces of two or three scalar instructions; the A origin only after the last load from it.
+        auto between_a = [&](int step, int piece) {
+            const int operand = piece < 3 ? 1 : 0;
+            const int at = step + 2 + (operand == 0 ? 1 : 0);
+            const char*& origin = operand == 0 ? origin_a : origin_b;
+            if (piece % 3 == 0) {
+                stride_now = at <= last ? k_step_bytes[operand] : 0u;
+                if (piece == 0) rd_a = fragment_address_sum(base_a[0], na);
+                else rd_b = fragment_address_sum(base_b[0], nb);
+            } else if (piece % 3 == 1) {
+                origin += stride_now;
             } else {
-                at_b += 1;
-                origin_b += at_b <= last ? k_step_bytes[1] : (int64_t)0;
-                origin_b = at_b == steps1 ? seg_origin[1][1] : origin_b;
+                origin = at == steps1 ? seg_origin[operand][1] : origin;
             }
         };
-        // slots of this step's tiles and of the next step's; those of the step after are worked out in
-        // otherwise empty gaps of the second slice
-        uint32_t sb = next_slot(sa), na = next_slot(sb), nb = next_slot(na), after_a = 0, after_b = 0;
-        auto rotate = [&](int half) {
-            if (half == 0) after_a = next_slot(nb);
-            else after_b = next_slot(after_a);
+        auto between_b = [&](int piece) {
+            if (piece == 0) rd_a = fragment_address_sum(base_a[1], na);
+            else if (piece == 1) rd_b = fragment_address_sum(base_b[1], nb);
+            else if (piece == 2) refill_a = sb;
+            else if (piece == 3) sa = na;
+            else if (piece == 4) na = next_slot(sb = nb);
+            else nb = next_slot(na);
         };
         for (int step = step_begin; step < step_end; ++step) {
-            slice(0, pend_b, 1, sa, sb, 1, no_hook);
-            slice(1, pend_a, 0, sa, sb, 2, rotate);
-            slice(0, pend_a, 1, sa, sb, 3, advance);
+            slice(0, load_ctx_at(0, refill_a, origin_a), rd_a, rd_b, [&](int piece) { between_a(step, piece); });
             wait_direct_loads<kLoadsPerTile>();
             __syncthreads();
-            pend_b = load_ctx_at(1, sa, origin_b);   // tile 2 s + 5 -> slot of tile 2 s
-            pend_a = load_ctx_at(0, sb, origin_a);   // tile 2 s + 6 -> slot of tile 2 s + 1
-            slice(1, pend_b, 0, na, nb, 0, no_hook);
-            sa = na;
-            sb = nb;
-            na = after_a;
-            nb = after_b;
+            slice(1, load_ctx_at(1, sa, origin_b), rd_a, rd_b, between_b);   // tile 2 s + 5 -> slot of tile 2 s
         }
         wait_direct_loads<0>();
+        // the last MFMAs' results: the compiler does not know how long inline assembly takes to write them
+        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
         __syncthreads();
     }
 
@@ -453,27 +493,23 @@ __device__ inline char* wave_stage(const TileCoord& tc, char* lds) {
     return lds + (tc.wm * 2 + tc.wn) * kWaveStageBytes;
 }
 
-// Writes bf16(acc[i][j]) for j in [j0, j0 + nj) of tile row i into a staging area whose rows are
-// `stride` bytes apart: element (row, col) of the wavefront's sub-tile goes to
-// stage + (row - row0) * stride + col_off * 2 + (32 (j - j0) + 8 q + 4 (lane >> 5)) * 2.
+// Writes bf16 of four consecutive columns per lane for the 16-column tiles jj = 0 .. nj - 1 of one tile row into a
+// staging area whose rows are `stride` bytes apart, starting at column col_off.  The 32 lanes served together write
+// 16 rows x 16 bytes, so a stride of 16 bytes times an odd number spreads them over all banks.
 template <class F>
 __device__ inline void stage_tile_row(char* stage, int stride, int lane, int local_row, int col_off, int nj, F value) {
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
+    for (int jj = 0; jj < 8; ++jj) {
         if (jj >= nj) break;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int col = col_off + jj * 32 + 8 * q + 4 * (lane >> 5);
-            *reinterpret_cast<bf16x4*>(stage + local_row * stride + col * 2) =
-                to_bf16x4(value(jj, 4 * q), value(jj, 4 * q + 1), value(jj, 4 * q + 2), value(jj, 4 * q + 3));
-        }
+        const int col = col_off + jj * 16 + 4 * (lane >> 4);
+        const f32x4 v = value(jj);
+        *reinterpret_cast<bf16x4*>(stage + local_row * stride + col * 2) = to_bf16x4(v[0], v[1], v[2], v[3]);
     }
 }
 
 // Staging area -> global memory, 16 bytes per lane: kRowBytes / 16 lanes cover one row, so a pass moves
 // 1024 / kRowBytes rows and a 16-lane group writes whole 128-byte lines.  `dst` is this lane's address
-// in row 0; rows at and beyond n_rows (wave-uniform) are not written.  Staging rows are 8-byte aligned
-// only (their stride keeps the 8-byte writes of stage_tile_row conflict-free), hence two 8-byte reads.
+// in row 0; rows at and beyond n_rows (wave-uniform) are not written.
 template <int kRows, int kRowBytes>
 __device__ inline void copy_rows_out(const char* st, int stride, char* dst, int64_t ld_bytes, int n_rows, int lane) {
     constexpr int kLanesPerRow = kRowBytes / 16, kRowsPerPass = 64 / kLanesPerRow;
@@ -483,16 +519,14 @@ __device__ inline void copy_rows_out(const char* st, int stride, char* dst, int6
     if (n_rows >= kRows) {
 #pragma unroll 8
         for (int pass = 0; pass < kRows / kRowsPerPass; ++pass) {
-            const uint2 lo = *reinterpret_cast<const uint2*>(src), hi = *reinterpret_cast<const uint2*>(src + 8);
-            *reinterpret_cast<uint4*>(out) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            *reinterpret_cast<u32x4*>(out) = *reinterpret_cast<const u32x4*>(src);
             src += kRowsPerPass * stride;
             out += out_step;
         }
     } else {
         int r = lane / kLanesPerRow;
         for (int pass = 0; pass < kRows / kRowsPerPass && pass * kRowsPerPass < n_rows; ++pass) {
-            const uint2 lo = *reinterpret_cast<const uint2*>(src), hi = *reinterpret_cast<const uint2*>(src + 8);
-            if (r < n_rows) *reinterpret_cast<uint4*>(out) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            if (r < n_rows) *reinterpret_cast<u32x4*>(out) = *reinterpret_cast<const u32x4*>(src);
             src += kRowsPerPass * stride;
             out += out_step;
             r += kRowsPerPass;
@@ -538,28 +572,27 @@ __device__ inline double staged_sum_of_squares(const char* st, int stride, int l
 template <int kRows, int kRowBytes>
 struct RowFetch {
     static constexpr int kLanesPerRow = kRowBytes / 16, kRowsPerPass = 64 / kLanesPerRow, kPasses = kRows / kRowsPerPass;
-    uint4 r[kPasses];
-    __device__ void fetch_rows(const char* src_row0, int64_t ld_bytes, int lane) {
-        const char* in = src_row0 + (lane / kLanesPerRow) * ld_bytes + (lane % kLanesPerRow) * 16;
+    u32x4 r[kPasses];
+    __device__ __forceinline__ void fetch_rows(const char* src_row0, int64_t ld_bytes, int lane) {
+        // a wave-uniform row address plus a 32-bit lane offset: one address register for all passes
+        const uint32_t at = (uint32_t)(lane / kLanesPerRow) * (uint32_t)ld_bytes + (uint32_t)(lane % kLanesPerRow) * 16u;
 #pragma unroll
-        for (int pass = 0; pass < kPasses; ++pass) r[pass] = *reinterpret_cast<const uint4*>(in + pass * kRowsPerPass * ld_bytes);
+        for (int pass = 0; pass < kPasses; ++pass)
+            r[pass] = *reinterpret_cast<const u32x4*>(src_row0 + pass * kRowsPerPass * ld_bytes + at);
     }
     // The same with the rows given by number: rows[pass] is the row of a matrix (whose row 0, at this wavefront's
     // columns, is src_col0) that this lane fetches in that pass; a negative number stands for a row of zeros.
-    __device__ void fetch_rows_at(const char* src_col0, int64_t ld_bytes, const int (&rows)[kPasses], int lane) {
+    __device__ __forceinline__ void fetch_rows_at(const char* src_col0, int64_t ld_bytes, const int (&rows)[kPasses], int lane) {
         const char* in = src_col0 + (lane % kLanesPerRow) * 16;
 #pragma unroll
         for (int pass = 0; pass < kPasses; ++pass)
-            r[pass] = rows[pass] >= 0 ? *reinterpret_cast<const uint4*>(in + (int64_t)rows[pass] * ld_bytes)
-                                      : make_uint4(0, 0, 0, 0);
+            r[pass] = rows[pass] >= 0 ? *reinterpret_cast<const u32x4*>(in + (int64_t)rows[pass] * ld_bytes)
+                                      : u32x4{0, 0, 0, 0};
     }
-    __device__ void stash_rows(char* st, int stride, int lane) const {
+    __device__ __forceinline__ void stash_rows(char* st, int stride, int lane) const {
         char* dst = st + (lane / kLanesPerRow) * stride + (lane % kLanesPerRow) * 16;
 #pragma unroll
-        for (int pass = 0; pass < kPasses; ++pass) {
-            *reinterpret_cast<uint2*>(dst + pass * kRowsPerPass * stride) = make_uint2(r[pass].x, r[pass].y);
-            *reinterpret_cast<uint2*>(dst + pass * kRowsPerPass * stride + 8) = make_uint2(r[pass].z, r[pass].w);
-        }
+        for (int pass = 0; pass < kPasses; ++pass) *reinterpret_cast<u32x4*>(dst + pass * kRowsPerPass * stride) = r[pass];
     }
 };
 // copy_rows_out with the destination rows given by number (row i of the staging area goes to row rows[i] of the
@@ -573,8 +606,7 @@ __device__ inline void copy_rows_out_at(const char* st, int stride, char* dst_co
 #pragma unroll 8
     for (int pass = 0; pass < kRows / kRowsPerPass; ++pass) {
         const int row = rows[lane / kLanesPerRow + pass * kRowsPerPass];
-        const uint2 lo = *reinterpret_cast<const uint2*>(src), hi = *reinterpret_cast<const uint2*>(src + 8);
-        if (row >= 0) *reinterpret_cast<uint4*>(out + (int64_t)row * ld_bytes) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        if (row >= 0) *reinterpret_cast<u32x4*>(out + (int64_t)row * ld_bytes) = *reinterpret_cast<const u32x4*>(src);
         src += kRowsPerPass * stride;
     }
 }
@@ -584,13 +616,14 @@ struct EpiStoreBf16 {
     bf16* C;
     int64_t ldc;
     int row_limit;
-    __device__ void operator()(const TileCoord& tc, f32x16 (&acc)[4][4], char* lds) const {
-        constexpr int kStride = 264;                       // 128 bf16 + 8 bytes: conflict-free 8-byte accesses
+    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
+        constexpr int kStride = 272;                       // 128 bf16 + 16 bytes
         char* st = wave_stage(tc, lds);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            stage_tile_row(st, kStride, tc.lane, i * 32 + (tc.lane & 31), 0, 4,
-                           [&](int j, int e) { return acc[i][j][e]; });
+        for (int i = 0; i < 8; ++i) {
+            stage_tile_row(st, kStride, tc.lane, i * 16 + (tc.lane & 15), 0, 8, [&](int j) { return acc[i][j]; });
+            __builtin_amdgcn_sched_barrier(0);   // one tile row's conversions at a time: all at once spill
+        }
         __builtin_amdgcn_wave_barrier();
         const int row_base = tc.m0 + tc.wm * 128, col_base = tc.n0 + tc.wn * 128;
         copy_rows_out<128, 256>(st, kStride, reinterpret_cast<char*>(C + (int64_t)row_base * ldc + col_base), ldc * 2,
@@ -604,13 +637,14 @@ struct EpiScatterBf16 {
     bf16* C;
     int64_t ldc;
     const int32_t* row_idx;
-    __device__ void operator()(const TileCoord& tc, f32x16 (&acc)[4][4], char* lds) const {
-        constexpr int kStride = 264;
+    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
+        constexpr int kStride = 272;
         char* st = wave_stage(tc, lds);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            stage_tile_row(st, kStride, tc.lane, i * 32 + (tc.lane & 31), 0, 4,
-                           [&](int j, int e) { return acc[i][j][e]; });
+        for (int i = 0; i < 8; ++i) {
+            stage_tile_row(st, kStride, tc.lane, i * 16 + (tc.lane & 15), 0, 8, [&](int j) { return acc[i][j]; });
+            __builtin_amdgcn_sched_barrier(0);   // one tile row's conversions at a time: all at once spill
+        }
         __builtin_amdgcn_wave_barrier();
         const int row_base = tc.m0 + tc.wm * 128, col_base = tc.n0 + tc.wn * 128;
         copy_rows_out_at<128, 256>(st, kStride, reinterpret_cast<char*>(C + col_base), ldc * 2, row_idx + row_base, tc.lane);
@@ -624,32 +658,30 @@ struct EpiStoreBf16Split {
     bf16 *hi, *lo;
     int64_t ldc;
     int row_limit;
-    __device__ void operator()(const TileCoord& tc, f32x16 (&acc)[4][4], char* lds) const {
-        constexpr int kStride = 520;                       // [hi 128 | lo 128] bf16 + 8 bytes
+    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
+        constexpr int kStride = 528;                       // [hi 128 | lo 128] bf16 + 16 bytes
         char* st = wave_stage(tc, lds);
         const int col_base = tc.n0 + tc.wn * 128;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {             // 64 rows per pass
 #pragma unroll
-            for (int ii = 0; ii < 2; ++ii) {
-                const int i = half * 2 + ii;
-                char* row = st + (ii * 32 + (tc.lane & 31)) * kStride;
+            for (int ii = 0; ii < 4; ++ii) {
+                const int i = half * 4 + ii;
+                char* row = st + (ii * 16 + (tc.lane & 15)) * kStride;
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < 8; ++j) {
+                    float r[4];
+                    bf16x4 h;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float r[4];
-                        bf16x4 h;
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            const float x = acc[i][j][4 * q + t];
-                            h[t] = (__bf16)x;
-                            r[t] = x - (float)h[t];
-                        }
-                        char* at = row + (j * 32 + 8 * q + 4 * (tc.lane >> 5)) * 2;
-                        *reinterpret_cast<bf16x4*>(at) = h;
-                        *reinterpret_cast<bf16x4*>(at + 256) = to_bf16x4(r[0], r[1], r[2], r[3]);
+                    for (int t = 0; t < 4; ++t) {
+                        const float x = acc[i][j][t];
+                        h[t] = (__bf16)x;
+                        r[t] = x - (float)h[t];
                     }
+                    char* at = row + (j * 16 + 4 * (tc.lane >> 4)) * 2;
+                    *reinterpret_cast<bf16x4*>(at) = h;
+                    *reinterpret_cast<bf16x4*>(at + 256) = to_bf16x4(r[0], r[1], r[2], r[3]);
+                }
             }
             __builtin_amdgcn_wave_barrier();
             const int row_base = tc.m0 + tc.wm * 128 + half * 64;
@@ -687,7 +719,7 @@ struct EpiStoreF32 {
     double* sumsq_parts;
     FinalPanel final_panel;
     __device__ bool runs_when_empty() const { return sumsq_parts != nullptr && final_panel(); }
-    __device__ void operator()(const TileCoord& tc, f32x16 (&acc)[4][4], char* lds) const {
+    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
         float* const C = this->C + tc.split * split_stride;
         constexpr int kStride = 528;                       // 128 fp32 + 16 bytes: conflict-free 16-byte accesses
         char* st = wave_stage(tc, lds);
@@ -697,13 +729,11 @@ struct EpiStoreF32 {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {                      // 32 rows per pass
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x16& a = acc[i][j];
-                    f32x4 v = {a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
-                    *reinterpret_cast<f32x4*>(st + (tc.lane & 31) * kStride + (j * 32 + 8 * q + 4 * (tc.lane >> 5)) * 4) = v;
-                }
+                for (int j = 0; j < 8; ++j)
+                    *reinterpret_cast<f32x4*>(st + (ii * 16 + (tc.lane & 15)) * kStride + (j * 16 + 4 * (tc.lane >> 4)) * 4) =
+                        acc[2 * i + ii][j];
             __builtin_amdgcn_wave_barrier();
             const int row_base = tc.m0 + tc.wm * 128 + i * 32;
             char* const dst = reinterpret_cast<char*>(C + (int64_t)row_base * ldc + col_base);
@@ -722,8 +752,8 @@ struct EpiStoreF32 {
 };
 
 // Gate/up projection with the activation fused: the B operand holds, per 128 packed rows, 64 gate
-// columns followed by the 64 up columns of the same index range, so a wavefront's tiles j = 0, 1
-// are u (gate) and j = 2, 3 the matching v (up).  Writes a = silu(u) * v (bf16, [M, ff]) and, for
+// columns followed by the 64 up columns of the same index range, so a wavefront's tiles j = 0 .. 3
+// are u (gate) and j = 4 .. 7 the matching v (up).  Writes a = silu(u) * v (bf16, [M, ff]) and, for
 // a backward pass to come, the two factors it will need, computed here where the sigmoid is at
 // hand: fu = v * silu'(u) (so du = da * fu) and fv = silu(u) (so dv = da * fv).
 // With kKeepLow the rounding remainder of a is written as well (a_lo = bf16(a - bf16(a))), for products
@@ -732,43 +762,41 @@ template <bool kKeepFactors, bool kKeepLow = false>
 struct EpiSwigluForward {
     bf16 *fu, *fv, *a, *a_lo;
     int64_t ld;
-    __device__ void operator()(const TileCoord& tc, f32x16 (&acc)[4][4], char* lds) const {
-        // staged row: [a 64 | fu 64 | fv 64 | a_lo 64] bf16 (the parts that are kept) + 8 bytes
+    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
+        // staged row: [a 64 | fu 64 | fv 64 | a_lo 64] bf16 (the parts that are kept) + 16 bytes
         constexpr int kLowAt = kKeepFactors ? 384 : 128;
-        constexpr int kStride = 8 + 128 * (1 + (kKeepFactors ? 2 : 0) + (kKeepLow ? 1 : 0));
+        constexpr int kStride = 16 + 128 * (1 + (kKeepFactors ? 2 : 0) + (kKeepLow ? 1 : 0));
         char* st = wave_stage(tc, lds);
         const int col_base = ((tc.n0 + tc.wn * 128) / 128) * 64;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {             // 64 rows per pass
 #pragma unroll
-            for (int ii = 0; ii < 2; ++ii) {
-                const int i = half * 2 + ii;
-                char* row = st + (ii * 32 + (tc.lane & 31)) * kStride;
+            for (int ii = 0; ii < 4; ++ii) {
+                const int i = half * 4 + ii;
+                char* row = st + (ii * 16 + (tc.lane & 15)) * kStride;
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < 4; ++j) {
+                    float av[4], fuv[4], fvv[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float av[4], fuv[4], fvv[4];
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            const float x = acc[i][j][4 * q + t], y = acc[i][j + 2][4 * q + t];
-                            const float sg = kKeepLow ? 1.f / (1.f + expf(-x)) : fast_sigmoid(x);   // full accuracy where it is kept
-                            fvv[t] = x * sg;
-                            av[t] = fvv[t] * y;
-                            const float ys = y * sg;
-                            fuv[t] = __builtin_fmaf(ys, x - fvv[t], ys);     // y sg (1 + x (1 - sg))
-                        }
-                        char* at = row + (j * 32 + 8 * q + 4 * (tc.lane >> 5)) * 2;
-                        const bf16x4 a4 = to_bf16x4(av[0], av[1], av[2], av[3]);
-                        *reinterpret_cast<bf16x4*>(at) = a4;
-                        if (kKeepFactors) {
-                            *reinterpret_cast<bf16x4*>(at + 128) = to_bf16x4(fuv[0], fuv[1], fuv[2], fuv[3]);
-                            *reinterpret_cast<bf16x4*>(at + 256) = to_bf16x4(fvv[0], fvv[1], fvv[2], fvv[3]);
-                        }
-                        if (kKeepLow)
-                            *reinterpret_cast<bf16x4*>(at + kLowAt) = to_bf16x4(av[0] - (float)a4[0], av[1] - (float)a4[1],
-                                                                             av[2] - (float)a4[2], av[3] - (float)a4[3]);
+                    for (int t = 0; t < 4; ++t) {
+                        const float x = acc[i][j][t], y = acc[i][j + 4][t];
+                        const float sg = kKeepLow ? 1.f / (1.f + expf(-x)) : fast_sigmoid(x);   // full accuracy where it is kept
+                        fvv[t] = x * sg;
+                        av[t] = fvv[t] * y;
+                        const float ys = y * sg;
+                        fuv[t] = __builtin_fmaf(ys, x - fvv[t], ys);     // y sg (1 + x (1 - sg))
                     }
+                    char* at = row + (j * 16 + 4 * (tc.lane >> 4)) * 2;
+                    const bf16x4 a4 = to_bf16x4(av[0], av[1], av[2], av[3]);
+                    *reinterpret_cast<bf16x4*>(at) = a4;
+                    if (kKeepFactors) {
+                        *reinterpret_cast<bf16x4*>(at + 128) = to_bf16x4(fuv[0], fuv[1], fuv[2], fuv[3]);
+                        *reinterpret_cast<bf16x4*>(at + 256) = to_bf16x4(fvv[0], fvv[1], fvv[2], fvv[3]);
+                    }
+                    if (kKeepLow)
+                        *reinterpret_cast<bf16x4*>(at + kLowAt) = to_bf16x4(av[0] - (float)a4[0], av[1] - (float)a4[1],
+                                                                         av[2] - (float)a4[2], av[3] - (float)a4[3]);
+                }
             }
             __builtin_amdgcn_wave_barrier();
             const int row_base = tc.m0 + tc.wm * 128 + half * 64;
@@ -795,8 +823,8 @@ struct EpiSwigluBackward {
     int64_t ld;
     const int32_t* row_idx;
     bf16 *du, *dv;
-    __device__ void operator()(const TileCoord& tc, f32x16 (&acc)[4][4], char* lds) const {
-        constexpr int kStride = 520;                       // [du 128 | dv 128] bf16 + 8 bytes
+    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
+        constexpr int kStride = 528;                       // [du 128 | dv 128] bf16 + 16 bytes
         char* st = wave_stage(tc, lds);
         const int row_base = tc.m0 + tc.wm * 128, col_base = tc.n0 + tc.wn * 128;
         const int64_t ld_bytes = ld * 2;
@@ -812,7 +840,7 @@ struct EpiSwigluBackward {
             idx_hi = row_idx[row_base + 64 + tc.lane];
         }
         RowFetch<32, 256> ru, rv;
-        auto fetch = [&](int pass) {
+        auto fetch = [&](int pass) __attribute__((always_inline)) {
             if (kIndexed) {
                 int rows[RowFetch<32, 256>::kPasses];
 #pragma unroll
@@ -833,25 +861,25 @@ struct EpiSwigluBackward {
             rv.stash_rows(st + 256, kStride, tc.lane);
             if (i < 3) fetch(i + 1);
             __builtin_amdgcn_wave_barrier();
-            const int lr = tc.lane & 31;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int col = j * 32 + 8 * q + 4 * (tc.lane >> 5);
-                    char* pu = st + lr * kStride + col * 2;
+                for (int j = 0; j < 8; ++j) {
+                    const int col = j * 16 + 4 * (tc.lane >> 4);
+                    char* pu = st + (ii * 16 + (tc.lane & 15)) * kStride + col * 2;
                     char* pv = pu + 256;
                     const bf16x4 u4 = *reinterpret_cast<const bf16x4*>(pu);
                     const bf16x4 v4 = *reinterpret_cast<const bf16x4*>(pv);
+                    const f32x4 g = acc[2 * i + ii][j];
                     float gu[4], gv[4];
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
-                        const float g = acc[i][j][4 * q + t];
-                        gu[t] = g * (float)u4[t];
-                        gv[t] = g * (float)v4[t];
+                        gu[t] = g[t] * (float)u4[t];
+                        gv[t] = g[t] * (float)v4[t];
                     }
                     *reinterpret_cast<bf16x4*>(pu) = to_bf16x4(gu[0], gu[1], gu[2], gu[3]);
                     *reinterpret_cast<bf16x4*>(pv) = to_bf16x4(gv[0], gv[1], gv[2], gv[3]);
+                    if (j & 1) __builtin_amdgcn_sched_barrier(0);   // two tiles at a time: beside the fetched rows more spill
                 }
             __builtin_amdgcn_wave_barrier();
             copy_rows_out<32, 256>(st, kStride, du0 + i * 32 * ld_bytes, ld_bytes, 32, tc.lane);
@@ -878,7 +906,7 @@ struct EpiLogitsLoss {
     bf16* dz_extra;    // [M, 256]: entropy part, per-chunk ratio only
     float* logp_out;   // may be nullptr
     RowOut out;
-    __device__ void operator()(const TileCoord& tc, f32x16 (&acc)[4][4], char* lds) const {
+    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
         // exchange area (LDS, free after the main loop): [3 quantities][2 column halves][256 rows]
         float* ex_a = reinterpret_cast<float*>(lds);
         float* ex_b = ex_a + 512;
@@ -886,75 +914,81 @@ struct EpiLogitsLoss {
         const int64_t rows_batch = live_rows(n_kept, max_chunks, A);
         const float scale = objective_scale(opt, rows_batch);
         const int64_t rows_live = rows_batch - row_offset;          // live rows of this panel (may be <= 0)
-        const int lrow_base = tc.wm * 128 + (tc.lane & 31);
+        const int lrow_base = tc.wm * 128 + (tc.lane & 15);
+        const bool first_of_row = tc.lane < 16;                     // a row is held by the four lanes l, l + 16, l + 32, l + 48
 
-        float mx[4];
+        float mx[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 8; ++i) {
             float m = -INFINITY;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < 8; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) m = fmaxf(m, acc[i][j][e]);
+                for (int t = 0; t < 4; ++t) m = fmaxf(m, acc[i][j][t]);
+            m = fmaxf(m, __shfl_xor(m, 16, 64));
             m = fmaxf(m, __shfl_xor(m, 32, 64));
             mx[i] = m;
-            if (tc.lane < 32) ex_a[tc.wn * 256 + lrow_base + i * 32] = m;
+            if (first_of_row) ex_a[tc.wn * 256 + lrow_base + i * 16] = m;
         }
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) mx[i] = fmaxf(mx[i], ex_a[(tc.wn ^ 1) * 256 + lrow_base + i * 32]);
+        for (int i = 0; i < 8; ++i) mx[i] = fmaxf(mx[i], ex_a[(tc.wn ^ 1) * 256 + lrow_base + i * 16]);
         __syncthreads();
 
-        float lse[4], ztok[4], ent[4];
-        int tok[4];
+        float lse[8], ztok[8], ent[8];
+        int tok[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 8; ++i) {
             tok[i] = token[tc.row(i)];
             float se = 0.f, sz = 0.f, zt = 0.f;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < 8; ++j) {
+                const f32x4 z = acc[i][j];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int n = tc.col(j, q);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const float z = acc[i][j][4 * q + t];
-                        const float e = __expf(z - mx[i]);
-                        se += e;
-                        sz += e * z;
-                        zt += (n + t == tok[i]) ? z : 0.f;
-                    }
+                for (int t = 0; t < 4; ++t) {
+                    const float e = __expf(z[t] - mx[i]);
+                    se += e;
+                    sz += e * z[t];
                 }
-            se += __shfl_xor(se, 32, 64);
-            sz += __shfl_xor(sz, 32, 64);
-            zt += __shfl_xor(zt, 32, 64);
+                const int t0 = tok[i] & 3;               // the target is one of this lane's four columns, or none of them
+                const float at_t0 = t0 == 0 ? z[0] : (t0 == 1 ? z[1] : (t0 == 2 ? z[2] : z[3]));
+                zt += tc.col(j) == (tok[i] & ~3) ? at_t0 : 0.f;
+            }
+#pragma unroll
+            for (int o = 16; o < 64; o <<= 1) {
+                se += __shfl_xor(se, o, 64);
+                sz += __shfl_xor(sz, o, 64);
+                zt += __shfl_xor(zt, o, 64);
+            }
             lse[i] = se;
             ent[i] = sz;
             ztok[i] = zt;
-            if (tc.lane < 32) {
-                ex_a[tc.wn * 256 + lrow_base + i * 32] = se;
-                ex_b[tc.wn * 256 + lrow_base + i * 32] = zt;
-                ex_c[tc.wn * 256 + lrow_base + i * 32] = sz;
+            if (first_of_row) {
+                ex_a[tc.wn * 256 + lrow_base + i * 16] = se;
+                ex_b[tc.wn * 256 + lrow_base + i * 16] = zt;
+                ex_c[tc.wn * 256 + lrow_base + i * 16] = sz;
             }
         }
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int other = (tc.wn ^ 1) * 256 + lrow_base + i * 32;
+        for (int i = 0; i < 8; ++i) {
+            const int other = (tc.wn ^ 1) * 256 + lrow_base + i * 16;
             const float se = lse[i] + ex_a[other];
             lse[i] = mx[i] + __logf(se);
             ztok[i] += ex_b[other];
             ent[i] = lse[i] - (ent[i] + ex_c[other]) / se;      // H = -sum p log p
         }
 
+        float coef[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 8; ++i) {
             const int m = tc.row(i);
             const bool live = m < rows_live;
             const float lp = ztok[i] - lse[i];
             const float w = (opt.chunk_weight && live) ? opt.chunk_weight[(m + row_offset) / A] : 1.f;
             const LossRow lr = loss_row(lp, logp_old[m], adv_row[m], w, opt, scale);
-            if (tc.wn == 0 && tc.lane < 32) {
+            coef[i] = live ? (opt.chunk_ratio ? 1.f : lr.coef) : 0.f;
+            if (tc.wn == 0 && first_of_row) {
                 out.dlogp[m] = lr.dlogp;
                 out.entropy[m] = live ? ent[i] : 0.f;
                 if (!opt.chunk_ratio) {
@@ -964,32 +998,46 @@ struct EpiLogitsLoss {
                 }
                 if (logp_out && live) logp_out[m] = lp;
             }
-            if (dz) {
-                const float coef = opt.chunk_ratio ? (live ? 1.f : 0.f) : (live ? lr.coef : 0.f);
-                const float ec = live ? opt.entropy_coef * scale : 0.f;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int n = tc.col(j, q);
-                        float g[4], h[4];
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            const float lpj = acc[i][j][4 * q + t] - lse[i];
-                            const float pr = __expf(lpj);
-                            g[t] = coef * (((n + t == tok[i]) ? 1.f : 0.f) - pr);
-                            h[t] = ec * pr * (lpj + ent[i]);
-                        }
-                        if (opt.chunk_ratio) {
-                            *reinterpret_cast<bf16x4*>(dz + (int64_t)m * 256 + n) = to_bf16x4(g[0], g[1], g[2], g[3]);
-                            *reinterpret_cast<bf16x4*>(dz_extra + (int64_t)m * 256 + n) = to_bf16x4(h[0], h[1], h[2], h[3]);
-                        } else {
-                            *reinterpret_cast<bf16x4*>(dz + (int64_t)m * 256 + n) =
-                                to_bf16x4(g[0] + h[0], g[1] + h[1], g[2] + h[2], g[3] + h[3]);
-                        }
-                    }
-            }
         }
+        if (dz == nullptr) return;
+        // dz = -coef * softmax over the row, then the target's column, which has coef * (1 - softmax), again by the lane
+        // that wrote it: a store per row instead of a comparison and a selection per element.
+        const auto write_rows = [&](auto with_entropy) __attribute__((always_inline)) {
+            constexpr bool kEntropy = decltype(with_entropy)::value != 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int m = tc.row(i);
+                const float ec = m < rows_live ? opt.entropy_coef * scale : 0.f;
+                bf16* const dz_row = dz + (int64_t)m * 256;
+                bf16* const extra_row = dz_extra + (int64_t)m * 256;
+                const bool target_here = tok[i] >> 7 == tc.wn && ((tok[i] >> 2) & 3) == tc.lane >> 4;
+                const float lp = ztok[i] - lse[i], p_target = __expf(lp);
+                float g_target = coef[i] * (1.f - p_target);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int n = tc.col(j);
+                    float g[4], h[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const float lpj = acc[i][j][t] - lse[i];
+                        const float pr = __expf(lpj);
+                        g[t] = -(coef[i] * pr);
+                        if (kEntropy) h[t] = ec * pr * (lpj + ent[i]);
+                    }
+                    if (kEntropy && opt.chunk_ratio) {
+                        *reinterpret_cast<bf16x4*>(extra_row + n) = to_bf16x4(h[0], h[1], h[2], h[3]);
+                    } else if (kEntropy) {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) g[t] += h[t];
+                    }
+                    *reinterpret_cast<bf16x4*>(dz_row + n) = to_bf16x4(g[0], g[1], g[2], g[3]);
+                }
+                if (kEntropy && !opt.chunk_ratio) g_target += ec * p_target * (lp + ent[i]);
+                if (target_here) *reinterpret_cast<__bf16*>(dz_row + tok[i]) = (__bf16)g_target;
+            }
+        };
+        if (opt.entropy_coef != 0.f) write_rows(Index<1>{});     // uniform over the launch
+        else write_rows(Index<0>{});
     }
 };
 
