@@ -1,7 +1,7 @@
 // bf16 path of the masked GRPO actor step (Eq. 11): matrix-core GEMMs with fused epilogues.
 //
-// Forward:  X -> [gate|up] GEMM with silu(u)*v fused -> down GEMM -> logit GEMM with the
-//           log-softmax / ratio / clipped surrogate / dz fused.
+// Forward:  X -> [gate|up] GEMM with silu(u)*v fused -> down GEMM -> logit GEMM (fp32, split reduction) ->
+//           log-softmax / ratio / clipped surrogate / dz in one pass over the rows.
 // Backward: dy = dz Wo^T; da = dy Wd^T with the gated-activation derivative fused (du, dv
 //           overwrite the two factors the forward epilogue stored); weight gradients reduce over
 //           the row dimension (a small output, dWo, as partial products over slices of the rows,
@@ -135,6 +135,115 @@ __global__ void sum_parts_bf16(const float* parts, int n_parts, size_t n, bf16* 
     }
 }
 
+// The loss over the rows of a panel: log-softmax at the target bin, row entropy, ratio, clipped surrogate and
+// dz = coef * (onehot - softmax) + entropy_coef * scale * softmax * (log softmax + H) as bf16.  The logits arrive in fp32
+// as the partial products of a split reduction, parts[s][row][256], summed here.  With a per-chunk ratio the factor is
+// not known yet: dz <- onehot - softmax, the entropy part goes to dz_extra, and the rows are scaled once the chunk
+// ratios are known.
+//
+// A launch of its own and not an epilogue of the logit product: a product with a single column of tiles has few
+// workgroups (9 for 2072 rows), so its reduction has to be split, and as straight-line code over the accumulators the
+// loss was 64 KB of instructions that each of those workgroups fetched for one use.  16 lanes hold a row, 4 x 4
+// columns each (1 KB of a row per four loads), so that the reductions are four shuffles; bound by reading the logits,
+// which are still in the memory-side cache.  Logit product and loss together, before and after: 2072 rows at d = 512
+// 31.5 -> 20.9 us, 672 rows at d = 4096 83 -> 25 us, 5376 rows 109 -> 34 us.
+constexpr int kLossThreads = 256, kLossRows = kLossThreads / 16;   // rows per workgroup
+struct LossRowsArgs {
+    const float* parts;
+    int n_parts;
+    size_t part_stride;      // floats between two parts
+    const uint8_t* token;
+    const float* logp_old;
+    const float* adv_row;
+    const int32_t* n_kept;
+    int max_chunks, A;
+    int row_offset;          // batch row of the panel's row 0 (the per-row arrays are the panel's parts)
+    int rows_pad;            // rows of the panel
+    LossOptions opt;
+    bf16* dz;                // [rows_pad, 256] or nullptr
+    bf16* dz_extra;          // [rows_pad, 256]: entropy part, per-chunk ratio only
+    float* logp_out;         // may be nullptr
+    RowOut out;
+};
+__device__ inline float sum16(float x) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
+__global__ __launch_bounds__(kLossThreads) void loss_rows_bf16(LossRowsArgs p) {
+    const int64_t rows_batch = live_rows(p.n_kept, p.max_chunks, p.A);
+    const int64_t rows_live = rows_batch - p.row_offset;        // live rows of this panel (may be <= 0)
+    const int m = blockIdx.x * kLossRows + (int)(threadIdx.x >> 4), lane = threadIdx.x & 15;
+    // rows up to the end of the last live row tile are written (as rows without a gradient); nothing reads later ones
+    const int64_t limit = rows_live <= 0 ? 0 : (rows_live + kTileM - 1) / kTileM * kTileM;
+    if (m >= limit || m >= p.rows_pad) return;                  // uniform over the 16 lanes of a row
+    const float scale = objective_scale(p.opt, rows_batch);
+    const float* src = p.parts + (size_t)m * 256 + lane * 4;
+    f32x4 z[4];                                                 // z[q][t]: column 64 q + 4 lane + t
+#pragma unroll
+    for (int q = 0; q < 4; ++q) z[q] = *reinterpret_cast<const f32x4*>(src + q * 64);
+    for (int s = 1; s < p.n_parts; ++s) {
+        src += p.part_stride;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) z[q] += *reinterpret_cast<const f32x4*>(src + q * 64);
+    }
+    const int tok = p.token[m];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) mx = fmaxf(mx, z[q][t]);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    float se = 0.f, sz = 0.f, zt = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const float e = __expf(z[q][t] - mx);
+            se += e;
+            sz += e * z[q][t];
+            zt += (q * 64 + lane * 4 + t == tok) ? z[q][t] : 0.f;
+        }
+    se = sum16(se);
+    sz = sum16(sz);
+    zt = sum16(zt);
+    const float lse = mx + __logf(se), lp = zt - lse, ent = lse - sz / se;      // H = -sum p log p
+    const bool live = m < rows_live;
+    const float w = (p.opt.chunk_weight && live) ? p.opt.chunk_weight[(m + p.row_offset) / p.A] : 1.f;
+    const LossRow lr = loss_row(lp, p.logp_old[m], p.adv_row[m], w, p.opt, scale);
+    if (lane == 0) {
+        p.out.dlogp[m] = lr.dlogp;
+        p.out.entropy[m] = live ? ent : 0.f;
+        if (!p.opt.chunk_ratio) {
+            p.out.term[m] = live ? lr.term : 0.f;
+            p.out.ratio[m] = lr.ratio;
+            p.out.clipped[m] = lr.clipped;
+        }
+        if (p.logp_out && live) p.logp_out[m] = lp;
+    }
+    if (p.dz == nullptr) return;
+    const float coef = live ? (p.opt.chunk_ratio ? 1.f : lr.coef) : 0.f;
+    const float ec = live ? p.opt.entropy_coef * scale : 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float g[4], h[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const float lpj = z[q][t] - lse, pr = __expf(lpj);
+            g[t] = coef * ((q * 64 + lane * 4 + t == tok ? 1.f : 0.f) - pr);
+            h[t] = ec * pr * (lpj + ent);
+        }
+        const int64_t at = (int64_t)m * 256 + q * 64 + lane * 4;
+        if (p.opt.chunk_ratio) {
+            *reinterpret_cast<bf16x4*>(p.dz + at) = to_bf16x4(g[0], g[1], g[2], g[3]);
+            *reinterpret_cast<bf16x4*>(p.dz_extra + at) = to_bf16x4(h[0], h[1], h[2], h[3]);
+        } else {
+            *reinterpret_cast<bf16x4*>(p.dz + at) = to_bf16x4(g[0] + h[0], g[1] + h[1], g[2] + h[2], g[3] + h[3]);
+        }
+    }
+}
+
 // The forward products' operand layouts of the four weight matrices, in one buffer.
 struct PackedHead {
     bf16 *WguT, *WdT, *WoT;
@@ -178,7 +287,7 @@ struct Bf16Workspace {
     double* sumsq[4];      // sums of squares of the final dWg, dWu, dWd, dWo by workgroup (null: not asked for)
     int sumsq_count[4];
     bf16 *Wdo, *G;  // composed evaluation: Wd Wo and a^T dz, both [ff, V]
-    float* parts;   // partial products of split reductions
+    float* parts;   // partial products of split reductions; the logits
     RowMeta meta;   // whole batch
     RowOut out;     // whole batch
     int64_t Mp;     // padded rows of the batch
@@ -240,7 +349,9 @@ Bf16Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool grads, const 
     }
     w.Wdo = c.take<bf16>(ff * V);
     if (grads) w.G = c.take<bf16>(ff * V);
-    w.parts = c.take<float>(kMaxSplitTiles * (size_t)kTileM * kTileN);
+    // parts of split reductions; of the logits (one column of tiles) there is at least one part whatever the panel's height
+    const size_t row_tiles = Rp / kTileM;
+    w.parts = c.take<float>((row_tiles > kMaxSplitTiles ? row_tiles : kMaxSplitTiles) * (size_t)kTileM * kTileN);
     w.bytes = c.used();
     return w;
 }
@@ -401,15 +512,21 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
         }
         {
             StageTimer t(ST_GEMM_LOGITS_LOSS, s);
-            EpiLogitsLoss epi{meta.token, meta.logp_old, meta.adv, io.n_kept, sh.max_chunks, sh.A, (int)row0,
-                              io.opt, bwd ? w.dz : nullptr, w.dz_extra, io.logp_out ? io.logp_out + row0 : nullptr, out};
+            const size_t n_z = (size_t)Mp * V;                         // z in fp32, as parts of a split reduction
+            int n_parts;
             if (io.composed) {   // z = a W_do, W_do read as [K][rows]
-                launch_gemm<kRowsByK, kKByRows>(problem(w.a, ff, w.Wdo, V, Mp, V, ff, kr, kRowsAreM), epi, s);
+                GemmProblem p = problem(w.a, ff, w.Wdo, V, Mp, V, ff, kr, kRowsAreM);
+                n_parts = p.splits = pick_splits(Mp / kTileM, ff / kTileK);
+                launch_gemm<kRowsByK, kKByRows>(p, EpiStoreF32{w.parts, V, (int64_t)n_z, 0, nullptr, FinalPanel{}}, s);
             } else {
                 GemmProblem p = problem(w.y, d, w.WoT, d, Mp, V, d, kr, kRowsAreM);
                 if (split) { p.A2 = w.y_lo; p.B2 = w.WoT; p.K2 = d; }   // z = [y | y_lo] [Wo; Wo]
-                launch_gemm(p, epi, s);
+                n_parts = p.splits = pick_splits(Mp / kTileM, (p.K1 + p.K2) / kTileK);
+                launch_gemm(p, EpiStoreF32{w.parts, V, (int64_t)n_z, 0, nullptr, FinalPanel{}}, s);
             }
+            loss_rows_bf16<<<(unsigned)(Mp / kLossRows), kLossThreads, 0, s>>>(LossRowsArgs{
+                w.parts, n_parts, n_z, meta.token, meta.logp_old, meta.adv, io.n_kept, sh.max_chunks, sh.A, (int)row0, Mp,
+                io.opt, bwd ? w.dz : nullptr, w.dz_extra, io.logp_out ? io.logp_out + row0 : nullptr, out});
         }
         if (io.opt.chunk_ratio) {
             rc = launch_chunk_ratio(sh, io, meta, out, row0, Mp, s);

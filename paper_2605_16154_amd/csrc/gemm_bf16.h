@@ -889,158 +889,6 @@ struct EpiSwigluBackward {
     }
 };
 
-// Logit projection (N = V = 256 = one tile, so a workgroup holds whole rows) with the loss fused:
-// log-softmax at the target bin, row entropy, ratio, clipped surrogate and
-// dz = coef * (onehot - softmax) + entropy_coef * scale * softmax * (log softmax + H) as bf16.
-// With a per-chunk ratio the factor is not known yet: dz <- onehot - softmax, the entropy part goes
-// to dz_extra, and the rows are scaled once the chunk ratios are known.
-struct EpiLogitsLoss {
-    const uint8_t* token;
-    const float* logp_old;
-    const float* adv_row;
-    const int32_t* n_kept;
-    int max_chunks, A;
-    int row_offset;    // batch row of the panel's row 0 (the per-row arrays below are the panel's parts)
-    LossOptions opt;
-    bf16* dz;          // [M, 256] or nullptr
-    bf16* dz_extra;    // [M, 256]: entropy part, per-chunk ratio only
-    float* logp_out;   // may be nullptr
-    RowOut out;
-    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
-        // exchange area (LDS, free after the main loop): [3 quantities][2 column halves][256 rows]
-        float* ex_a = reinterpret_cast<float*>(lds);
-        float* ex_b = ex_a + 512;
-        float* ex_c = ex_b + 512;
-        const int64_t rows_batch = live_rows(n_kept, max_chunks, A);
-        const float scale = objective_scale(opt, rows_batch);
-        const int64_t rows_live = rows_batch - row_offset;          // live rows of this panel (may be <= 0)
-        const int lrow_base = tc.wm * 128 + (tc.lane & 15);
-        const bool first_of_row = tc.lane < 16;                     // a row is held by the four lanes l, l + 16, l + 32, l + 48
-
-        float mx[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            float m = -INFINITY;
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) m = fmaxf(m, acc[i][j][t]);
-            m = fmaxf(m, __shfl_xor(m, 16, 64));
-            m = fmaxf(m, __shfl_xor(m, 32, 64));
-            mx[i] = m;
-            if (first_of_row) ex_a[tc.wn * 256 + lrow_base + i * 16] = m;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 8; ++i) mx[i] = fmaxf(mx[i], ex_a[(tc.wn ^ 1) * 256 + lrow_base + i * 16]);
-        __syncthreads();
-
-        float lse[8], ztok[8], ent[8];
-        int tok[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            tok[i] = token[tc.row(i)];
-            float se = 0.f, sz = 0.f, zt = 0.f;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const f32x4 z = acc[i][j];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float e = __expf(z[t] - mx[i]);
-                    se += e;
-                    sz += e * z[t];
-                }
-                const int t0 = tok[i] & 3;               // the target is one of this lane's four columns, or none of them
-                const float at_t0 = t0 == 0 ? z[0] : (t0 == 1 ? z[1] : (t0 == 2 ? z[2] : z[3]));
-                zt += tc.col(j) == (tok[i] & ~3) ? at_t0 : 0.f;
-            }
-#pragma unroll
-            for (int o = 16; o < 64; o <<= 1) {
-                se += __shfl_xor(se, o, 64);
-                sz += __shfl_xor(sz, o, 64);
-                zt += __shfl_xor(zt, o, 64);
-            }
-            lse[i] = se;
-            ent[i] = sz;
-            ztok[i] = zt;
-            if (first_of_row) {
-                ex_a[tc.wn * 256 + lrow_base + i * 16] = se;
-                ex_b[tc.wn * 256 + lrow_base + i * 16] = zt;
-                ex_c[tc.wn * 256 + lrow_base + i * 16] = sz;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int other = (tc.wn ^ 1) * 256 + lrow_base + i * 16;
-            const float se = lse[i] + ex_a[other];
-            lse[i] = mx[i] + __logf(se);
-            ztok[i] += ex_b[other];
-            ent[i] = lse[i] - (ent[i] + ex_c[other]) / se;      // H = -sum p log p
-        }
-
-        float coef[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int m = tc.row(i);
-            const bool live = m < rows_live;
-            const float lp = ztok[i] - lse[i];
-            const float w = (opt.chunk_weight && live) ? opt.chunk_weight[(m + row_offset) / A] : 1.f;
-            const LossRow lr = loss_row(lp, logp_old[m], adv_row[m], w, opt, scale);
-            coef[i] = live ? (opt.chunk_ratio ? 1.f : lr.coef) : 0.f;
-            if (tc.wn == 0 && first_of_row) {
-                out.dlogp[m] = lr.dlogp;
-                out.entropy[m] = live ? ent[i] : 0.f;
-                if (!opt.chunk_ratio) {
-                    out.term[m] = live ? lr.term : 0.f;
-                    out.ratio[m] = lr.ratio;
-                    out.clipped[m] = lr.clipped;
-                }
-                if (logp_out && live) logp_out[m] = lp;
-            }
-        }
-        if (dz == nullptr) return;
-        // dz = -coef * softmax over the row, then the target's column, which has coef * (1 - softmax), again by the lane
-        // that wrote it: a store per row instead of a comparison and a selection per element.
-        const auto write_rows = [&](auto with_entropy) __attribute__((always_inline)) {
-            constexpr bool kEntropy = decltype(with_entropy)::value != 0;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int m = tc.row(i);
-                const float ec = m < rows_live ? opt.entropy_coef * scale : 0.f;
-                bf16* const dz_row = dz + (int64_t)m * 256;
-                bf16* const extra_row = dz_extra + (int64_t)m * 256;
-                const bool target_here = tok[i] >> 7 == tc.wn && ((tok[i] >> 2) & 3) == tc.lane >> 4;
-                const float lp = ztok[i] - lse[i], p_target = __expf(lp);
-                float g_target = coef[i] * (1.f - p_target);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int n = tc.col(j);
-                    float g[4], h[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const float lpj = acc[i][j][t] - lse[i];
-                        const float pr = __expf(lpj);
-                        g[t] = -(coef[i] * pr);
-                        if (kEntropy) h[t] = ec * pr * (lpj + ent[i]);
-                    }
-                    if (kEntropy && opt.chunk_ratio) {
-                        *reinterpret_cast<bf16x4*>(extra_row + n) = to_bf16x4(h[0], h[1], h[2], h[3]);
-                    } else if (kEntropy) {
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) g[t] += h[t];
-                    }
-                    *reinterpret_cast<bf16x4*>(dz_row + n) = to_bf16x4(g[0], g[1], g[2], g[3]);
-                }
-                if (kEntropy && !opt.chunk_ratio) g_target += ec * p_target * (lp + ent[i]);
-                if (target_here) *reinterpret_cast<__bf16*>(dz_row + tok[i]) = (__bf16)g_target;
-            }
-        };
-        if (opt.entropy_coef != 0.f) write_rows(Index<1>{});     // uniform over the launch
-        else write_rows(Index<0>{});
-    }
-};
-
 template <int kLayA = kRowsByK, int kLayB = kRowsByK, class Epilogue>
 inline void launch_gemm(const GemmProblem& p, const Epilogue& epi, hipStream_t s) {
     const unsigned grid = (unsigned)(p.M / kTileM) * (unsigned)(p.N / kTileN) * (unsigned)p.splits;

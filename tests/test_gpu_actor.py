@@ -241,6 +241,23 @@ def test_bf16_shape_sweep(pcm, d, ff, n_kept, A_dims, composed):
     check(ref, got, BF16_TOL, len(ref["rows"]), stats_tol=5e-2)
 
 
+@pytest.mark.parametrize("d,ff,n_kept", [
+    (1024, 256, 5),       # 280 rows: the logits' reduction in two parts, a ragged second row tile
+    (2304, 512, 9),       # 36 steps in four parts of nine
+    (256, 2560, 3),       # composed: the 40 steps over ff in five parts, a single row tile
+])
+def test_bf16_logits_as_parts_of_a_split_reduction(pcm, d, ff, n_kept, composed):
+    """Few row tiles and a long reduction: the logit product leaves several partial products that the loss kernel
+    adds.  Rows between the kept ones and the end of the last row tile must come out without a gradient."""
+    cfg = CONFIGS["cfg2"].with_(n_groups=1, G=4, N=8, K=4, B=4, d=d, ff=ff, seed=60 + n_kept)
+    ro = make_rollouts(cfg, 0)
+    _, active = O.advantages(ro["reward"], cfg.G)
+    kept, _, _ = O.sample_chunks(np.array([1.0, 0.3, 0.1, 0.6]), ro["phase"], None, active, cfg.B, cfg.seed, 0)
+    pr = make_problem(cfg, wstd=1.3 / np.sqrt(d), margin=0.08, kept=kept[:n_kept], old_rel=0.1, eps=(0.2, 0.4))
+    ref, got = run_both(pcm, pr, eps=(0.2, 0.4), torch_dtype=torch.bfloat16, max_kept=n_kept + 3, composed_head=composed)
+    check(ref, got, BF16_TOL, len(ref["rows"]), stats_tol=5e-2)
+
+
 def test_bf16_all_kept_and_forward_only(pcm, composed):
     cfg = CONFIGS["cfg2"].with_(n_groups=1, G=4, N=6, K=3, B=6, d=256, ff=256, seed=13)
     pr = make_problem(cfg, wstd=0.08, margin=0.08, kept=np.arange(cfg.T * cfg.N), old_rel=0.1)
