@@ -598,3 +598,25 @@ def test_bf16_large_configs_chained_selection_and_sampled_rows(pcm, name):
     got_np["logp"] = got["logp"][:n_rows].cpu().numpy()
     got_np["dX"] = got["dX"][:n_rows].float().cpu().numpy()
     check(ref, got_np, BF16_TOL, n_rows, stats_tol=5e-2)
+
+
+@pytest.mark.parametrize("d,ff,V,A_dims,n_kept,max_kept", [
+    (16, 16, 16, (1, 1), 1, 1),        # one row, a single reduction step
+    (33, 65, 17, (1, 7), 9, 12),       # odd everywhere: single-float loads, a partial last step, ragged tiles
+    (36, 132, 40, (3, 4), 11, 13),     # multiples of four but not of a step: 16-byte loads and a partial last step
+    (128, 64, 256, (8, 8), 8, 8),      # whole tiles
+    (260, 516, 300, (5, 7), 18, 24),   # one past a tile in every dimension, kept rows well below the capacity
+    (512, 1536, 256, (8, 7), 48, 56),  # 2688 rows: both tile sizes, split and unsplit reductions
+])
+def test_fp32_tiles_steps_and_edges(pcm, d, ff, V, A_dims, n_kept, max_kept, composed):
+    """The fp32 products at the edges of their tiles (64 and 128 wide) and of their 16-wide reduction steps.  The rows of
+    dX beyond the kept ones are zeros."""
+    cfg = CONFIGS["cfg1"].with_(n_groups=2, G=4, N=12, K=3, B=7, d=d, ff=ff, V=V, L=A_dims[0], D=A_dims[1], seed=70 + d)
+    ro = make_rollouts(cfg, 0)
+    _, active = O.advantages(ro["reward"], cfg.G)
+    kept, _, _ = O.sample_chunks(np.array([1.0, 0.3, 0.5]), ro["phase"], None, active, cfg.B, cfg.seed, 0)
+    assert len(kept) >= n_kept
+    pr = make_problem(cfg, wstd=1.2 / np.sqrt(d), margin=1e-3, kept=kept[:n_kept], old_rel=0.2, eps=(0.2, 0.4))
+    ref, got = run_both(pcm, pr, eps=(0.2, 0.4), max_kept=max_kept, composed_head=composed)
+    check(ref, got, 1e-5, len(ref["rows"]))
+    assert not got["dX"][len(ref["rows"]):].any()
