@@ -1,13 +1,15 @@
 // pcm_score_phases: group-relative advantages (Eq. 1) and the batch phase score C_c (Eq. 5).
 //
-// Four launches on the caller's stream:
-//   prepare     zero the integer accumulators; one thread per trajectory writes advantage/active
+// Two launches on the caller's stream (four launches of 2 - 3 us of work each were bound by the launches themselves):
+//   prepare     zero the integer accumulators and the arrival counters; one thread per trajectory writes
+//               advantage/active
 //   accumulate  streaming pass over the action tensor: every workgroup owns a slice of one
 //               trajectory's chunks, keeps per-phase 64-bit integer sums in LDS and adds the
-//               phases it met to the group's accumulators with 64-bit global atomics
-//   pairs       one wavefront per (group, phase): difference of pooled means, squared terms in
-//               parallel, added in index order by one lane, square root
-//   mean        one lane per phase: mean of the pair scores over contributing groups
+//               phases it met to the group's accumulators with 64-bit global atomics.  The last workgroup of a group
+//               to arrive forms the group's pair scores (difference of pooled means, squared terms in parallel, added
+//               in index order by one lane per phase, square root); the last group to arrive forms the mean of the pair
+//               scores over contributing groups, one lane per phase.  Nobody waits for anybody: a workgroup that is not
+//               the last one leaves.
 //
 // The action pass is bandwidth-bound (224 B per chunk plus one phase byte); everything after it
 // touches a few KB.  Integer accumulation makes the sums independent of slice and arrival order,
@@ -33,9 +35,10 @@ using ull = unsigned long long;
 struct ScoreWorkspace {
     ull* sums;            // [n_groups][2][K][A] integer sums of rint(a * 2^24); outcome 1 = success
     int* counts;          // [n_groups][2][K] chunks pooled
-    double* pair;         // [n_groups][K] per-(group, phase) score
-    uint8_t* pair_valid;  // [n_groups][K]
-    size_t zero_words;    // 32-bit words to clear at the start (sums + counts are contiguous)
+    double* pair;         // [n_groups][K] per-(group, phase) score, negative if the pair is skipped; until the group's
+                          // scores are written, the first word of its row counts the group's workgroups that are done
+    int* groups_done;     // groups whose pair scores are written
+    size_t zero_words;    // 32-bit words to clear at the start (everything up to groups_done is contiguous)
     size_t bytes;
 };
 
@@ -45,11 +48,11 @@ ScoreWorkspace carve(void* ws, int n_groups, int A, int K) {
     const size_t n_sum = (size_t)n_groups * 2 * K * A;
     const size_t n_cnt = (size_t)n_groups * 2 * K;
     w.sums = c.take<ull>(n_sum);
-    const size_t after_sums = c.used();
     w.counts = c.take<int>(n_cnt);
-    w.zero_words = (after_sums + n_cnt * sizeof(int) + 3) / 4;
     w.pair = c.take<double>((size_t)n_groups * K);
-    w.pair_valid = c.take<uint8_t>((size_t)n_groups * K);
+    const size_t after_pairs = c.used();
+    w.groups_done = reinterpret_cast<int*>(c.take<uint8_t>((size_t)n_groups * K));   // one int is used of it
+    w.zero_words = (after_pairs + sizeof(int)) / 4;
     w.bytes = c.used();
     return w;
 }
@@ -64,7 +67,12 @@ __global__ __launch_bounds__(kThreads) void score_prepare(uint32_t* zero, size_t
     for (size_t i = gid; i < (size_t)T; i += stride) {
         const int g = (int)(i / G);
         int s = 0;
-        for (int r = 0; r < G; ++r) s += reward[(size_t)g * G + r] != 0;
+        for (int r0 = 0; r0 < G; r0 += 8)             // eight loads under way together
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint8_t x = reward[(size_t)g * G + min(r0 + u, G - 1)];
+                s += r0 + u < G && x != 0;
+            }
         float a = 0.f;
         uint8_t act = 0;
         if (s != 0 && s != G) {
@@ -95,34 +103,36 @@ struct ActionVec<1> {
     __device__ void load(const float* p) { v[0] = *p; }
 };
 
-// grid = T * slices * phase_blocks workgroups; a workgroup pools the phases [c0, c0 + Kb) of its
-// chunks (phase_blocks is 1 unless K*A sums do not fit in LDS; then the chunks are read once per
-// block of phases).  LDS: Kb*A 64-bit sums followed by Kb chunk counts, indexed by phase - c0.
+// Values that workgroups hand to one another within the launch are written and read with device-scope atomic operations
+// only (adds to the accumulators, stores of the pair scores, the loads below): these go past the XCDs' own L2 caches, so
+// there is nothing to write back or to invalidate, and a fence, which would write back the whole L2 of the XCD (2048
+// workgroups doing so: 147 instead of 17 us), is not needed.  What is needed is that a workgroup's operations are
+// complete before it is counted: every thread waits for its own, then the barrier, then one thread adds.
+template <typename T>
+__device__ inline T load_shared(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ inline void store_shared(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ inline void add_shared(T* p, T v) { (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Whether this workgroup is the last of `expected` to arrive at *counter (every workgroup arrives once).
+__device__ inline bool arrive_last(int* counter, int expected) {
+    __shared__ int is_last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // this thread's adds and stores are complete
+    __syncthreads();
+    if (threadIdx.x == 0)
+        is_last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == expected - 1 ? 1 : 0;
+    __syncthreads();
+    const bool last = is_last != 0;
+    __syncthreads();                                              // is_last may be written again
+    return last;
+}
+
+// This workgroup's slice of a trajectory, its sums in LDS and from there to the group's accumulators.
 template <int VEC>
-__global__ __launch_bounds__(kThreads) void score_accumulate(
-    const float* __restrict__ actions, const uint8_t* __restrict__ phase,
-    const uint8_t* __restrict__ reward, const int32_t* __restrict__ n_chunks, int G, int N, int A,
-    int K, int Kb, int slices, ull* sums, int* counts) {
-    extern __shared__ ull lds_sum[];
-    int* lds_cnt = reinterpret_cast<int*>(lds_sum + (size_t)Kb * A);
-
-    const int phase_blocks = (K + Kb - 1) / Kb;
-    const int c0 = (blockIdx.x % phase_blocks) * Kb;
-    const int kb = min(Kb, K - c0);                     // phases of this workgroup
-    const int slice = (blockIdx.x / phase_blocks) % slices;
-    const int i = blockIdx.x / phase_blocks / slices;
-    const int g = i / G;
-    int s = 0;
-    for (int r = 0; r < G; ++r) s += reward[(size_t)g * G + r] != 0;
-    if (s == 0 || s == G) return;  // uniform rewards: the group has no score (whole workgroup exits)
-    const int outcome = reward[i] != 0;
-    int Ni = n_chunks ? n_chunks[i] : N;
-    Ni = Ni < 0 ? 0 : (Ni > N ? N : Ni);
-    const int per = (N + slices - 1) / slices;
-    const int k0 = slice * per;
-    const int k1 = min(Ni, k0 + per);
-    if (k0 >= k1) return;
-
+__device__ inline void accumulate_slice(const float* __restrict__ actions, const uint8_t* __restrict__ phase,
+                                        int i, int g, int outcome, int k0, int k1, int N, int A, int K, int c0, int kb,
+                                        ull* lds_sum, int* lds_cnt, ull* sums, int* counts) {
     const int tid = threadIdx.x;
     for (int e = tid; e < kb * A; e += kThreads) lds_sum[e] = 0;
     for (int c = tid; c < kb; c += kThreads) lds_cnt[c] = 0;
@@ -146,20 +156,31 @@ __global__ __launch_bounds__(kThreads) void score_accumulate(
         };
         const float* row = actions + (size_t)i * N * A + (size_t)jv * VEC;
         const uint8_t* ph = phase + (size_t)i * N;
-        for (int k = k0 + cs; k < k1; k += CPI) {
-            const int c = min((int)ph[k], K - 1) - c0;  // ids beyond the last phase count as the last; outside [0, kb): another block's
-            ActionVec<VEC> x;
-            x.load(row + (size_t)k * A);
-            if (c != cur) {
-                flush();
-                cur = c;
-                run = 0;
+        constexpr int kAhead = 4;      // chunks under way together: what a slice costs is mostly the latency of its loads
+        for (int kb0 = k0 + cs; kb0 < k1; kb0 += kAhead * CPI) {
+            int ph_id[kAhead];
+            ActionVec<VEC> x[kAhead];
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) acc[v] = 0;
+            for (int u = 0; u < kAhead; ++u) {
+                const int k = min(kb0 + u * CPI, k1 - 1);
+                ph_id[u] = ph[k];
+                x[u].load(row + (size_t)k * A);
             }
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[v] += __float2ll_rn(x.v[v] * kActionScale);
-            ++run;
+            for (int u = 0; u < kAhead; ++u) {
+                if (kb0 + u * CPI >= k1) break;
+                const int c = min(ph_id[u], K - 1) - c0;  // ids beyond the last phase count as the last; outside [0, kb): another block's
+                if (c != cur) {
+                    flush();
+                    cur = c;
+                    run = 0;
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) acc[v] = 0;
+                }
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[v] += __float2ll_rn(x[u].v[v] * kActionScale);
+                ++run;
+            }
         }
         flush();
     }
@@ -168,103 +189,134 @@ __global__ __launch_bounds__(kThreads) void score_accumulate(
     const size_t base = ((size_t)g * 2 + outcome) * K + c0;
     for (int e = tid; e < kb * A; e += kThreads) {
         const int c = e / A;
-        if (lds_cnt[c] > 0) atomicAdd(&sums[base * A + e], lds_sum[e]);
+        if (lds_cnt[c] > 0) add_shared(&sums[base * A + e], lds_sum[e]);
     }
     for (int c = tid; c < kb; c += kThreads)
-        if (lds_cnt[c] > 0) atomicAdd(&counts[base + c], lds_cnt[c]);
+        if (lds_cnt[c] > 0) add_shared(&counts[base + c], lds_cnt[c]);
 }
 
-// One wavefront per (group, phase).  All threads reach both barriers.
-__global__ __launch_bounds__(kThreads) void score_pairs(const ull* __restrict__ sums,
-                                                        const int* __restrict__ counts, int n_groups,
-                                                        int A, int K, double* pair,
-                                                        uint8_t* pair_valid) {
-    __shared__ double sq[kThreads / kWave][256];
-    const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int w = blockIdx.x * (kThreads / kWave) + wv;
-    const bool in_range = w < n_groups * K;
-    int n_pos = 0, n_neg = 0;
-    size_t pos_base = 0, neg_base = 0;
-    if (in_range) {
-        const int g = w / K, c = w % K;
-        pos_base = ((size_t)g * 2 + 1) * K + c;
-        neg_base = ((size_t)g * 2 + 0) * K + c;
-        n_pos = counts[pos_base];
-        n_neg = counts[neg_base];
-    }
-    const bool ok = in_range && n_pos > 0 && n_neg > 0;
-    if (ok) {
-        const double dp = (double)n_pos, dn = (double)n_neg;
-        for (int j = lane; j < A; j += kWave) {
-            const double mp = (double)(long long)sums[pos_base * A + j] / dp;
-            const double mn = (double)(long long)sums[neg_base * A + j] / dn;
-            const double diff = mp - mn;
-            sq[wv][j] = diff * diff;
+// Pair scores of group g for all phases, `block` phases at a time (as many as the squared terms in LDS allow).
+__device__ inline void score_pairs(int g, int A, int K, int block, const ull* sums, const int* counts, double* lds, double* pair) {
+    for (int c0 = 0; c0 < K; c0 += block) {
+        const int kb = min(block, K - c0);
+        const size_t pos = ((size_t)g * 2 + 1) * K + c0, neg = ((size_t)g * 2 + 0) * K + c0;
+        __syncthreads();
+        const int my_c = threadIdx.x < kb ? threadIdx.x : 0;      // the phase this thread adds up (kb <= 64)
+        const int my_pos = load_shared(&counts[pos + my_c]), my_neg = load_shared(&counts[neg + my_c]);
+        for (int e0 = threadIdx.x; e0 < kb * A; e0 += 4 * kThreads) {
+            int n_pos[4], n_neg[4];                               // all loads of four terms under way together
+            ull s_pos[4], s_neg[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int e = min(e0 + u * kThreads, kb * A - 1), c = e / A;
+                n_pos[u] = load_shared(&counts[pos + c]);
+                n_neg[u] = load_shared(&counts[neg + c]);
+                s_pos[u] = load_shared(&sums[pos * A + e]);
+                s_neg[u] = load_shared(&sums[neg * A + e]);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int e = e0 + u * kThreads;
+                if (e < kb * A && n_pos[u] > 0 && n_neg[u] > 0) {
+                    const double mp = (double)(long long)s_pos[u] / (double)n_pos[u];
+                    const double mn = (double)(long long)s_neg[u] / (double)n_neg[u];
+                    const double diff = mp - mn;
+                    lds[e] = diff * diff;
+                }
+            }
         }
-    }
-    __syncthreads();
-    if (in_range && lane == 0) {
-        if (ok) {
-            double acc = 0.0;
-            for (int j = 0; j < A; ++j) acc = acc + sq[wv][j];
-            pair[w] = sqrt(acc) * kActionUnscale;
-            pair_valid[w] = 1;
-        } else {
-            pair[w] = 0.0;
-            pair_valid[w] = 0;
+        __syncthreads();
+        if ((int)threadIdx.x < kb) {
+            const int c = threadIdx.x;
+            double score = -1.0;                                  // skipped: no chunks of one of the outcomes
+            if (my_pos > 0 && my_neg > 0) {
+                double acc = 0.0;
+#pragma unroll 8
+                for (int j = 0; j < A; ++j) acc = acc + lds[c * A + j];
+                score = sqrt(acc) * kActionUnscale;
+            }
+            store_shared(&pair[(size_t)g * K + c0 + c], score);
         }
     }
 }
 
 // Batch score of phase c = mean over the groups that contributed, added for g ascending (the order is
 // part of the definition: the result must not depend on the launch).  One workgroup: the per-group values
-// are brought into LDS a block of groups at a time (kMeanEntries values, so 4096 / K groups) with coalesced
-// loads, then lane c adds its column in order.
-constexpr int kMeanEntries = 4096;
-__global__ __launch_bounds__(256) void score_mean(const double* __restrict__ pair, const uint8_t* __restrict__ pair_valid,
-                                                  int n_groups, int K, double* C_out, uint8_t* valid_out) {
-    __shared__ double val[kMeanEntries];
-    __shared__ uint8_t ok[kMeanEntries];
+// are brought into LDS a block of groups at a time with coalesced loads, then lane c adds its column in order.
+__device__ inline void score_mean(const double* pair, int n_groups, int K, double* lds, int lds_entries, double* C_out,
+                                  uint8_t* valid_out) {
     const int c = threadIdx.x;
-    const int block_groups = kMeanEntries / K;          // K <= 64: at least 64 groups
+    const int block_groups = lds_entries / K;
     double tot = 0.0;
     int n = 0;
     for (int g0 = 0; g0 < n_groups; g0 += block_groups) {
         const int groups = min(block_groups, n_groups - g0);
-        // eight loads per thread in flight before the first is stored (a thread has at most 16 entries per block)
-        for (int i0 = threadIdx.x; i0 < groups * K; i0 += 8 * 256) {
+        __syncthreads();
+        // eight loads per thread in flight before the first is stored
+        for (int i0 = threadIdx.x; i0 < groups * K; i0 += 8 * kThreads) {
             double v[8];
-            uint8_t o[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u * 256;
-                v[u] = i < groups * K ? pair[(size_t)g0 * K + i] : 0.0;
-                o[u] = i < groups * K ? pair_valid[(size_t)g0 * K + i] : 0;
+                const int i = i0 + u * kThreads;
+                v[u] = i < groups * K ? load_shared(&pair[(size_t)g0 * K + i]) : 0.0;
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u * 256;
-                if (i < groups * K) {
-                    val[i] = o[u] ? v[u] : 0.0;   // a skipped pair adds +0.0, which leaves the non-negative sum as it is
-                    ok[i] = o[u];
-                }
-            }
+            for (int u = 0; u < 8; ++u)
+                if (i0 + u * kThreads < groups * K) lds[i0 + u * kThreads] = v[u];
         }
         __syncthreads();
         if (c < K) {
-            // branch-free, so that the LDS reads run ahead of the additions, which stay in group order
+            // branch-free, so that the LDS reads run ahead of the additions, which stay in group order; a skipped pair
+            // adds +0.0, which leaves the non-negative sum as it is
 #pragma unroll 8
             for (int g = 0; g < groups; ++g) {
-                tot = tot + val[g * K + c];
-                n += ok[g * K + c];
+                const double v = lds[g * K + c];
+                tot = tot + (v >= 0.0 ? v : 0.0);
+                n += v >= 0.0 ? 1 : 0;
             }
         }
-        __syncthreads();
     }
     if (c < K) {
         C_out[c] = n > 0 ? tot / (double)n : 0.0;
         valid_out[c] = n > 0 ? 1 : 0;
     }
+}
+
+// grid = T * slices * phase_blocks workgroups; a workgroup pools the phases [c0, c0 + Kb) of its
+// chunks (phase_blocks is 1 unless K*A sums do not fit in LDS; then the chunks are read once per
+// block of phases).  LDS: Kb*A 64-bit sums followed by Kb chunk counts, indexed by phase - c0; afterwards the squared
+// terms of a group's pairs, then the pair scores.
+template <int VEC>
+__global__ __launch_bounds__(kThreads) void score_accumulate(
+    const float* __restrict__ actions, const uint8_t* __restrict__ phase,
+    const uint8_t* __restrict__ reward, const int32_t* __restrict__ n_chunks, int n_groups, int G, int N, int A,
+    int K, int Kb, int slices, int lds_entries, ScoreWorkspace w, double* C_out, uint8_t* valid_out) {
+    extern __shared__ ull lds_sum[];
+    const int phase_blocks = (K + Kb - 1) / Kb;
+    const int c0 = (blockIdx.x % phase_blocks) * Kb;
+    const int kb = min(Kb, K - c0);                     // phases of this workgroup
+    const int slice = (blockIdx.x / phase_blocks) % slices;
+    const int i = blockIdx.x / phase_blocks / slices;
+    const int g = i / G;
+    int s = 0;                                          // successes of the group, 64 rollouts at a time
+    for (int r0 = 0; r0 < G; r0 += kWave) {
+        const int r = r0 + (int)(threadIdx.x % kWave);
+        const uint8_t x = reward[(size_t)g * G + min(r, G - 1)];
+        s += __popcll(__ballot(r < G && x != 0));
+    }
+    if (s != 0 && s != G) {      // with uniform rewards the group has no score; its counts stay zero
+        int Ni = n_chunks ? n_chunks[i] : N;
+        Ni = Ni < 0 ? 0 : (Ni > N ? N : Ni);
+        const int per = (N + slices - 1) / slices;
+        const int k0 = slice * per, k1 = min(Ni, k0 + per);
+        if (k0 < k1)
+            accumulate_slice<VEC>(actions, phase, i, g, reward[i] != 0, k0, k1, N, A, K, c0, kb, lds_sum,
+                                  reinterpret_cast<int*>(lds_sum + (size_t)Kb * A), w.sums, w.counts);
+    }
+    if (!arrive_last(reinterpret_cast<int*>(w.pair + (size_t)g * K), G * slices * phase_blocks)) return;
+    score_pairs(g, A, K, Kb, w.sums, w.counts, reinterpret_cast<double*>(lds_sum), w.pair);
+    if (!arrive_last(w.groups_done, n_groups)) return;
+    score_mean(w.pair, n_groups, K, reinterpret_cast<double*>(lds_sum), lds_entries, C_out, valid_out);
 }
 
 bool shape_ok(int n_groups, int G, int N, int A, int K) {
@@ -291,7 +343,7 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
 
-// Argument checks and the four launches shared by both entry points; `workspace` has been checked
+// Argument checks and the two launches shared by both entry points; `workspace` has been checked
 // to hold carve(...).bytes.
 int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward, const int32_t* n_chunks,
               int n_groups, int G, int N, int A, int K, double adv_eps, double* C_out, uint8_t* valid_out,
@@ -300,7 +352,9 @@ int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward,
     int Kb = (int)((size_t)64 * 1024 / ((size_t)A * sizeof(ull) + sizeof(int)));
     if (Kb > K) Kb = K;
     const int phase_blocks = ceil_div(K, Kb);
-    const size_t lds_bytes = (size_t)Kb * A * sizeof(ull) + (size_t)Kb * sizeof(int);
+    size_t lds_bytes = (size_t)Kb * A * sizeof(ull) + (size_t)Kb * sizeof(int);
+    if (lds_bytes < (size_t)PCM_MAX_PHASES * sizeof(double)) lds_bytes = (size_t)PCM_MAX_PHASES * sizeof(double);   // a row of pair scores
+    const int lds_entries = (int)(lds_bytes / sizeof(double));
     const int T = n_groups * G;
     {
         StageTimer t(ST_SCORE_PREPARE, s);
@@ -321,18 +375,11 @@ int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward,
         if (slices < 1) slices = 1;
         const unsigned grid = (unsigned)T * (unsigned)slices * (unsigned)phase_blocks;
         if (vec4)
-            score_accumulate<4><<<grid, kThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, G,
-                                                                N, A, K, Kb, slices, w.sums, w.counts);
+            score_accumulate<4><<<grid, kThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, n_groups, G, N, A, K, Kb,
+                                                                slices, lds_entries, w, C_out, valid_out);
         else
-            score_accumulate<1><<<grid, kThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, G,
-                                                                N, A, K, Kb, slices, w.sums, w.counts);
-    }
-    {
-        StageTimer t(ST_SCORE_FINALISE, s);
-        const int waves = n_groups * K;
-        score_pairs<<<ceil_div(waves, kThreads / kWave), kThreads, 0, s>>>(w.sums, w.counts, n_groups, A,
-                                                                         K, w.pair, w.pair_valid);
-        score_mean<<<1, 256, 0, s>>>(w.pair, w.pair_valid, n_groups, K, C_out, valid_out);
+            score_accumulate<1><<<grid, kThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, n_groups, G, N, A, K, Kb,
+                                                                slices, lds_entries, w, C_out, valid_out);
     }
     return launch_status();
 }
