@@ -7,7 +7,7 @@
 //            before its own to find where its output starts (a few KB of reads; for more than
 //            kFusedScanMax trajectories, and for the top-phase selector whose counts need a pass over
 //            the phases, a separate one-workgroup scan kernel writes the offsets first).  Lanes own
-//            contiguous runs of chunk slots with their integer weights in registers (in LDS when a
+//            contiguous runs of chunk slots with their running integer weights in registers (weights in LDS when a
 //            lane owns more than eight), an inclusive wave scan of lane sums is kept up to date
 //            across the min(B, N_i) successive draws, then kept slots are written in ascending order
 //            at the trajectory's offset (wave prefix of per-lane popcounts)
@@ -53,9 +53,9 @@ __device__ inline int top_phase(const double* keep_probs, int K) {
 // except under the top-phase selector, where only chunks of phase `only` (>= 0) are.
 __device__ inline int kept_count(const int32_t* n_chunks, const uint8_t* active, const uint8_t* phase, int i, int N,
                                  int K, int B, int only) {
-    if (active && !active[i]) return 0;
-    int Ni = n_chunks ? n_chunks[i] : N;
-    Ni = Ni < 0 ? 0 : (Ni > N ? N : Ni);
+    int Ni = n_chunks ? n_chunks[i] : N;              // both loads before either is looked at
+    const bool on = !active || active[i] != 0;
+    Ni = on ? (Ni < 0 ? 0 : (Ni > N ? N : Ni)) : 0;
     if (only >= 0) {
         const uint8_t* ph = phase + (size_t)i * N;
         int n = 0;
@@ -120,7 +120,8 @@ __global__ __launch_bounds__(kThreads) void sample_compact(
     int selector, uint64_t seed, uint64_t step, int32_t* kept_offsets, int32_t* n_kept, int32_t* kept_idx) {
     extern __shared__ uint32_t lds[];
     uint32_t* qtab = lds;
-    const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);      // what is the same for the whole wavefront stays scalar
     // This lane's phase bytes are requested first (their address depends on the launch geometry only), so that they
     // travel while the weights table and the output offset are worked out.
     uint8_t my_phase[kRegs > 0 ? kRegs : 1];
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(kThreads) void sample_compact(
     __syncthreads();
 
     const int i = blockIdx.x * waves_per_block + wv;
-    const int m = i < T ? kept_count(n_chunks, active, phase, i, N, K, B, only) : 0;
+    const int m = __builtin_amdgcn_readfirstlane(i < T ? kept_count(n_chunks, active, phase, i, N, K, B, only) : 0);
     int offset = 0;
     if (kFusedScan) {
         // kept chunks of all trajectories before this workgroup's first, then of the earlier wavefronts
@@ -164,7 +165,15 @@ __global__ __launch_bounds__(kThreads) void sample_compact(
             before = i0 * (N < B ? N : B);                                   // every trajectory keeps min(B, N)
         } else {
             int mine = 0;
-            for (int j = tid; j < i0; j += blockDim.x) mine += kept_count(n_chunks, active, phase, j, N, K, B, -1);
+            constexpr int kAhead = 4;                                        // counts under way together
+            for (int j0 = tid; j0 < i0; j0 += kAhead * blockDim.x) {
+                int count[kAhead];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u)
+                    count[u] = kept_count(n_chunks, active, phase, min(j0 + u * (int)blockDim.x, i0 - 1), N, K, B, -1);
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) mine += j0 + u * (int)blockDim.x < i0 ? count[u] : 0;
+            }
 #pragma unroll
             for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_xor(mine, off, kWave);
             if (lane == 0) part[0][wv] = mine;
@@ -253,13 +262,15 @@ __global__ __launch_bounds__(kThreads) void sample_compact(
     }
 
     uint64_t mask = 0;
-    uint32_t wreg[kRegs > 0 ? kRegs : 1];     // this lane's weights (kRegs > 0)
+    constexpr int kLast = kRegs > 0 ? kRegs - 1 : 0;
+    uint32_t cum[kLast + 1] = {}, excl = 0;   // kRegs > 0: running weight over all slots up to each of this lane's, and before them
+    uint32_t slots_picked = 0;                // kRegs > 0: this lane's picked slots
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
     const uint32_t s0 = (uint32_t)step, s1 = (uint32_t)(step >> 32);
     uint32_t x_lo = 0, x_hi = 0;              // lane l holds the random bits of round (r & ~63) + l
     int r = 0;                                // draw counter, running on across passes
     for (int pass = 0; pass < passes; ++pass) {
-        const int draws = selector == PCM_SELECT_STRATIFIED ? budget[pass] : m;
+        const int draws = selector == PCM_SELECT_STRATIFIED ? __builtin_amdgcn_readfirstlane(budget[pass]) : m;
         if (draws == 0) continue;
         uint32_t lane_sum = 0;
         auto weight_of_phase = [&](int k, int c) -> uint32_t {
@@ -271,8 +282,9 @@ __global__ __launch_bounds__(kThreads) void sample_compact(
         if (kRegs > 0) {
 #pragma unroll
             for (int j = 0; j < kRegs; ++j) {
-                wreg[j] = j < per_lane ? weight_of_phase(k_lo + j, my_phase[j]) : 0u;
-                lane_sum += wreg[j];
+                const bool picked = (slots_picked >> j) & 1u;     // (by an earlier pass: another phase, weight 0 in this one)
+                lane_sum += j < per_lane && !picked ? weight_of_phase(k_lo + j, my_phase[j]) : 0u;
+                cum[j] = lane_sum;
             }
         } else {
             for (int j = 0; j < per_lane; ++j) {
@@ -284,6 +296,11 @@ __global__ __launch_bounds__(kThreads) void sample_compact(
         }
         uint32_t incl = (uint32_t)wave_inclusive_scan((int)lane_sum, lane);
         uint32_t W_rem = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+        if (kRegs > 0) {
+            excl = incl - lane_sum;
+#pragma unroll
+            for (int j = 0; j < kRegs; ++j) cum[j] += excl;
+        }
         for (int d = 0; d < draws; ++d, ++r) {
             if ((r & (kWave - 1)) == 0) {     // the draws of the next 64 rounds, one per lane, in parallel
                 const uint64_t mine = philox_bits((uint32_t)i, (uint32_t)((r & ~(kWave - 1)) + lane), s0, s1, k0, k1);
@@ -291,27 +308,40 @@ __global__ __launch_bounds__(kThreads) void sample_compact(
                 x_hi = (uint32_t)(mine >> 32);
             }
             const int src = __builtin_amdgcn_readfirstlane(r & (kWave - 1));      // wave-uniform: a lane read, no shuffle
-            const uint64_t x = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)x_lo, src) |
-                               ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)x_hi, src) << 32);
-            const uint32_t t = (uint32_t)__umul64hi(x, (uint64_t)W_rem);   // in [0, W_rem)
-            const uint64_t over = __ballot(incl > t);
-            if (over == 0) break;             // cannot happen while W_rem > 0; keeps the loop total
-            const int L = __ffsll((long long)over) - 1;
-            uint32_t picked_w = 0;
-            if (lane == L) {
-                uint32_t run = incl - lane_sum;
-                if (kRegs > 0) {
+            const uint32_t xl = (uint32_t)__builtin_amdgcn_readlane((int)x_lo, src);
+            const uint32_t xh = (uint32_t)__builtin_amdgcn_readlane((int)x_hi, src);
+            // floor(x W_rem / 2^64), in [0, W_rem)
+            const uint32_t t = (uint32_t)(((uint64_t)xh * W_rem + (((uint64_t)xl * W_rem) >> 32)) >> 32);
+            if (kRegs > 0) {
+                // A draw is a chain of dependent instructions, so every lane works out beforehand which of its slots it
+                // would pick (the first whose running weight exceeds t) and of what weight; the first lane that has one
+                // is the one that does.  No branch, and one value passed between lanes.
+                const uint64_t over = __ballot(cum[kLast] > t);
+                if (over == 0) break;         // cannot happen while W_rem > 0; keeps the loop total
+                uint32_t before = excl, upto = cum[0];
+                int slot = 0;
 #pragma unroll
-                    for (int j = 0; j < kRegs; ++j) {
-                        const uint32_t wk = wreg[j];
-                        run += wk;
-                        if (picked_w == 0 && wk > 0 && run > t) {   // the first slot whose running weight exceeds t
-                            picked_w = wk;
-                            wreg[j] = 0;
-                            mask |= (uint64_t)1 << j;
-                        }
-                    }
-                } else {
+                for (int j = 1; j < kRegs; ++j) {
+                    const bool beyond = cum[j - 1] <= t;
+                    before = beyond ? cum[j - 1] : before;
+                    upto = beyond ? cum[j] : upto;
+                    slot += beyond ? 1 : 0;
+                }
+                const int L = __builtin_amdgcn_readfirstlane(__ffsll((long long)over) - 1);
+                const uint32_t picked_w = (uint32_t)__builtin_amdgcn_readlane((int)(upto - before), L);
+                const int first = lane < L ? kRegs : (lane == L ? slot : 0);      // this lane's slots from here on move down
+#pragma unroll
+                for (int j = 0; j < kRegs; ++j) cum[j] -= j >= first ? picked_w : 0u;
+                excl -= lane > L ? picked_w : 0u;
+                slots_picked |= lane == L ? 1u << slot : 0u;
+                W_rem -= picked_w;
+            } else {
+                const uint64_t over = __ballot(incl > t);
+                if (over == 0) break;
+                const int L = __ffsll((long long)over) - 1;
+                uint32_t picked_w = 0;
+                if (lane == L) {
+                    uint32_t run = incl - lane_sum;
                     for (int j = 0; j < per_lane; ++j) {
                         const int k = k_lo + j;
                         if (k >= N) break;
@@ -324,14 +354,15 @@ __global__ __launch_bounds__(kThreads) void sample_compact(
                             break;
                         }
                     }
+                    lane_sum -= picked_w;
                 }
-                lane_sum -= picked_w;
+                picked_w = (uint32_t)__builtin_amdgcn_readlane((int)picked_w, __builtin_amdgcn_readfirstlane(L));
+                if (lane >= L) incl -= picked_w;
+                W_rem -= picked_w;
             }
-            picked_w = (uint32_t)__builtin_amdgcn_readlane((int)picked_w, __builtin_amdgcn_readfirstlane(L));
-            if (lane >= L) incl -= picked_w;
-            W_rem -= picked_w;
         }
     }
+    if (kRegs > 0) mask = slots_picked;
 
     const int mine = __popcll(mask);
     int pos = offset + wave_inclusive_scan(mine, lane) - mine;
@@ -443,44 +474,77 @@ __global__ __launch_bounds__(kThreads) void importance_weights(const uint8_t* __
     }
 }
 
-// One workgroup: histograms in LDS of the kept chunks' phases and of the phases of all chunk slots the sampler
-// could have kept, written out as they are (nothing to clear, no atomics in memory).
+// hist[c] += 1 for every lane with c >= 0.  Neighbouring lanes mostly hold the same phase (a trajectory's phases are
+// contiguous), and as many LDS atomics on one address would be served one after the other: the first lane of every run
+// of equal values adds the length of the run.
+__device__ inline void wave_histogram(int* hist, int c, int lane) {
+    const int left = __shfl_up(c, 1, kWave);
+    const bool starts = lane == 0 || c != left;
+    const uint64_t starting = __ballot(starts);
+    if (starts && c >= 0) {
+        const uint64_t later = lane == kWave - 1 ? 0 : starting >> (lane + 1);
+        atomicAdd(&hist[c], later ? __ffsll((long long)later) : kWave - lane);
+    }
+}
+
+// Histograms in LDS of the kept chunks' phases (workgroup 0) and of the phases of all chunk slots the sampler could have
+// kept (workgroup 1), written out as they are (nothing to clear, no atomics in memory).  Bound by the latency of the loads
+// and by the instructions of one CU; each thread has sixteen slots under way.  32768 slots, 4096 kept: 22.7 -> 14 us
+// against one slot and one LDS atomic per thread at a time in a single workgroup.
+constexpr int kCountBatch = 16;
 __global__ __launch_bounds__(1024) void kept_phase_counts(const uint8_t* __restrict__ phase,
                                                           const int32_t* __restrict__ n_chunks,
                                                           const uint8_t* __restrict__ active,
                                                           const int32_t* __restrict__ kept_idx,
                                                           const int32_t* __restrict__ n_kept, int max_kept, int T, int N,
                                                           int K, int32_t* kept_out, int32_t* eligible_out) {
-    __shared__ int hist[2][PCM_MAX_PHASES];
-    const int tid = threadIdx.x;
-    if (tid < 2 * PCM_MAX_PHASES) hist[tid / PCM_MAX_PHASES][tid % PCM_MAX_PHASES] = 0;
+    __shared__ int hist[PCM_MAX_PHASES];
+    const int tid = threadIdx.x, lane = tid % kWave;
+    if (tid < PCM_MAX_PHASES) hist[tid] = 0;
     __syncthreads();
-    int nk = *n_kept;
-    nk = nk < 0 ? 0 : (nk > max_kept ? max_kept : nk);
     const int64_t slots = (int64_t)T * N;
-    for (int j = tid; j < nk; j += 1024) {
-        const int id = kept_idx[j];
-        if (id >= 0 && id < slots) {
-            const int c = phase[id];
-            atomicAdd(&hist[0][c < K ? c : K - 1], 1);
-        }
-    }
-    if (eligible_out) {
-        for (int64_t e = tid; e < slots; e += 1024) {
-            const int i = (int)(e / N), k = (int)(e % N);
-            int Ni = n_chunks ? n_chunks[i] : N;
-            Ni = Ni > N ? N : Ni;
-            if (k < Ni && (!active || active[i])) {
-                const int c = phase[e];
-                atomicAdd(&hist[1][c < K ? c : K - 1], 1);
+    if (blockIdx.x == 0) {
+        int nk = *n_kept;
+        nk = nk < 0 ? 0 : (nk > max_kept ? max_kept : nk);
+        constexpr int kBatch = 4;
+        for (int64_t j0 = 0; j0 < nk; j0 += 1024 * kBatch) {       // trips uniform over the workgroup
+            int id[kBatch], c[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int64_t j = j0 + u * 1024 + tid;
+                id[u] = j < nk ? kept_idx[j] : -1;
             }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) c[u] = id[u] >= 0 && id[u] < slots ? min((int)phase[id[u]], K - 1) : -1;
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) wave_histogram(hist, c[u], lane);
+        }
+    } else {
+        int i = tid / N, k = tid % N;                 // trajectory and slot of this thread's next entry, 1024 further each time
+        const int step_i = 1024 / N, step_k = 1024 % N;
+        for (int64_t e0 = 0; e0 < slots; e0 += 1024 * kCountBatch) {
+            int c[kCountBatch], Ni[kCountBatch], at[kCountBatch];
+            bool on[kCountBatch];
+#pragma unroll
+            for (int u = 0; u < kCountBatch; ++u) {
+                const bool in = i < T;
+                const int ii = in ? i : T - 1;
+                at[u] = in ? k : N;                   // beyond the last trajectory: no slot
+                c[u] = phase[in ? e0 + u * 1024 + tid : slots - 1];
+                Ni[u] = n_chunks ? n_chunks[ii] : N;
+                on[u] = !active || active[ii] != 0;
+                i += step_i;
+                k += step_k;
+                if (k >= N) { k -= N; ++i; }
+            }
+#pragma unroll
+            for (int u = 0; u < kCountBatch; ++u) c[u] = on[u] && at[u] < min(Ni[u], N) ? min(c[u], K - 1) : -1;
+#pragma unroll
+            for (int u = 0; u < kCountBatch; ++u) wave_histogram(hist, c[u], lane);
         }
     }
     __syncthreads();
-    if (tid < K) {
-        kept_out[tid] = hist[0][tid];
-        if (eligible_out) eligible_out[tid] = hist[1][tid];
-    }
+    if (tid < K) (blockIdx.x == 0 ? kept_out : eligible_out)[tid] = hist[tid];
 }
 
 }  // namespace
@@ -492,7 +556,7 @@ extern "C" int pcm_kept_phase_counts(const uint8_t* phase, const int32_t* n_chun
     if (!shape_ok(T, N, K, 1)) return PCM_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     StageTimer t(ST_SAMPLE_COMPACT, s);
-    kept_phase_counts<<<1, 1024, 0, s>>>(phase, n_chunks, active, kept_idx, n_kept, max_kept_chunks, T, N, K, kept_per_phase,
+    kept_phase_counts<<<chunks_per_phase ? 2 : 1, 1024, 0, s>>>(phase, n_chunks, active, kept_idx, n_kept, max_kept_chunks, T, N, K, kept_per_phase,
                                          chunks_per_phase);
     return launch_status();
 }

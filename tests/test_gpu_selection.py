@@ -276,3 +276,52 @@ def test_ten_chained_steps_bit_exact(pcm):
     assert all(np.array_equal(refreshed[t], refreshed[0]) for t in range(5))
     assert all(np.array_equal(refreshed[t], refreshed[5]) for t in range(5, 10))
     assert not np.array_equal(refreshed[0], refreshed[5])
+
+
+@pytest.mark.parametrize("N", [1, 63, 64, 65, 128, 129, 256, 257, 512, 513])
+def test_sampler_and_counts_at_the_edges_of_slots_per_lane(pcm, N):
+    """A lane keeps the running weights of up to 2, 4 or 8 chunk slots in registers, and of more in LDS: sizes on both
+    sides of each line, ragged trajectories, phases that do not come in runs; the allocation counts of the same batches."""
+    rng = np.random.default_rng(N)
+    T, K, B = 21, 7, min(N, 19)
+    phase = rng.integers(0, K + 1, size=(T, N)).astype(np.uint8)          # one id beyond the last phase
+    phase[::2] = np.sort(phase[::2], axis=1)
+    n_chunks = rng.integers(0, N + 1, size=T).astype(np.int32)
+    n_chunks[:2] = N
+    active = (rng.random(T) < 0.8).astype(np.uint8)
+    p = np.clip(rng.random(K) ** 3, 1e-3, 1.0)
+    p[0] = 1.0
+    for selector in ("pcm", "random", "top_phase", "stratified"):
+        kept_o, off_o, nk_o = O.sample_chunks(p, phase, n_chunks, active, B, 5, 9, selector=selector)
+        kept, off, nk = pcm.pcm_sample_chunks(dev(p), dev(phase), dev(n_chunks), dev(active), B, 5, 9, selector=selector)
+        assert np.array_equal(off.cpu().numpy(), off_o) and int(nk.item()) == nk_o
+        assert np.array_equal(kept.cpu().numpy()[:nk_o], kept_o), (N, selector)
+        got, eligible = pcm.pcm_kept_phase_counts(dev(phase), dev(n_chunks), dev(active), kept, nk, K)
+        want, want_eligible = O.kept_phase_counts(phase, n_chunks, active, kept_o, K)
+        assert np.array_equal(got.cpu().numpy(), want) and np.array_equal(eligible.cpu().numpy(), want_eligible)
+
+
+@pytest.mark.parametrize("n_groups,G,N,A,K", [
+    (1, 1, 3, 4, 2),        # a group of one: nothing to compare
+    (2, 65, 5, 8, 3),       # more rollouts than lanes in a wavefront
+    (300, 2, 4, 4, 5),      # more pair scores than fit in LDS at once, one chunk per workgroup
+    (3, 8, 256, 3, 64),     # the most phases, single-float loads, several slices per trajectory
+    (2, 4, 1100, 56, 12),   # more chunks per workgroup than are under way together
+])
+def test_score_in_two_launches(pcm, n_groups, G, N, A, K):
+    """The last workgroup of a group forms its pair scores, the last group the mean: called again and again on one
+    workspace, with other rewards in between, every call gives the checker's bits."""
+    rng = np.random.default_rng(n_groups + N)
+    T = n_groups * G
+    actions = rng.uniform(-1, 1, size=(T, N, A)).astype(np.float32)
+    phase = np.sort(rng.integers(0, K, size=(T, N)), axis=1).astype(np.uint8)
+    n_chunks = rng.integers(0, N + 1, size=T).astype(np.int32)
+    a, ph, n = dev(actions), dev(phase), dev(n_chunks)
+    for trip in range(4):
+        reward = (rng.random(T) < (0.5, 0.0, 0.9, 0.5)[trip]).astype(np.uint8)
+        C_o, valid_o = O.phase_scores(actions, phase, reward, n_chunks, n_groups, G, K)
+        adv_o, act_o = O.advantages(reward, G)
+        C, valid, adv, act = pcm.pcm_score_phases(a, ph, dev(reward), n, n_groups, G, K, 1e-6)
+        assert np.array_equal(bits(C.cpu().numpy()), bits(C_o)) and np.array_equal(valid.cpu().numpy(), valid_o), trip
+        assert np.array_equal(act.cpu().numpy(), act_o)
+        assert np.array_equal(adv.cpu().numpy().view(np.int32), adv_o.astype(np.float32).view(np.int32))
