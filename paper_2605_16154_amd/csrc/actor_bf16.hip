@@ -340,10 +340,11 @@ Bf16Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool grads, const 
         w.plan = c.take<LivePlan>(1);
     }
     if (grads && opt.grad_sumsq_out != nullptr) {
-        const size_t tiles[4] = {d / kTileM * (ff / kTileN), d / kTileM * (ff / kTileN), ff / kTileM * (d / kTileN),
-                                 d / kTileM * (V / kTileN)};
+        const size_t size[4][2] = {{d, ff}, {d, ff}, {ff, d}, {d, V}};
         for (int q = 0; q < 4; ++q) {
-            w.sumsq_count[q] = (int)(4 * tiles[q] > kSumBlocksMax ? 4 * tiles[q] : kSumBlocksMax);
+            const size_t tile = 32 * (size_t)tile_for((int64_t)size[q][0], (int64_t)size[q][1], 1);   // that of an unsplit product
+            const size_t waves = 4 * (size[q][0] / tile) * (size[q][1] / tile);
+            w.sumsq_count[q] = (int)(waves > kSumBlocksMax ? waves : kSumBlocksMax);
             w.sumsq[q] = c.take<double>((size_t)w.sumsq_count[q]);
         }
     }

@@ -47,16 +47,20 @@ enum OperandLayout : int {
     kKByRows = 1    // [K][rows]: element (row, k) at ptr[k * ld + row]
 };
 
-constexpr int kTileM = 256, kTileN = 256, kTileK = 64;
+constexpr int kTileM = 256, kTileN = 256, kTileK = 64;   // rows are padded to, and skipped in, units of kTileM whatever the tile
 constexpr int kGemmThreads = 256;
 constexpr int kNumXcd = 8;
 constexpr int kRingSlots = 5;    // operand tiles resident or in flight in LDS
+// Two tile sizes, 32 kW x 32 kW with kW x kW MFMA tiles per wavefront: 256 (kW = 8: one workgroup per CU, its operand
+// ring is the whole LDS) and 128 (kW = 4: two workgroups per CU) where the larger tile leaves CUs idle, see tile_for.
+constexpr int kLargeTile = 8, kSmallTile = 4;
+template <int kW> constexpr int kTile = 32 * kW;                     // rows and columns of a workgroup's tile
+template <int kW> constexpr int kWaveRows = 16 * kW;                 // rows and columns of a wavefront's part of it
+template <int kW> constexpr int kRingBytes = kRingSlots * kTile<kW> * kTileK * 2;   // 160 KB (the whole LDS) / 80 KB
 // Epilogues pass their results through LDS so that global stores are whole 128-byte lines: each
 // wavefront owns a private staging area (no workgroup barrier needed; LDS operations of one
 // wavefront execute in order).
-constexpr int kWaveStageBytes = 34816;                       // 128 rows x (256 + 16) bytes
-constexpr int kSmemBytes = kRingSlots * kTileM * kTileK * 2;   // 160 KB: the whole LDS of a CU
-static_assert(4 * kWaveStageBytes <= kSmemBytes, "epilogue staging must fit in the operand ring");
+template <int kW> constexpr int kWaveStageBytes = kRingBytes<kW> / 4;
 
 struct GemmProblem {
     const bf16* A;    // M x K1 operand, leading dimension lda (layout given by the kernel's template arguments)
@@ -83,15 +87,17 @@ struct GemmProblem {
 };
 enum RowsRole : int { kRowsUnused = 0, kRowsAreM = 1, kRowsAreK = 2 };
 
-// Accumulators of a wavefront: 8 x 8 tiles of 16 x 16.  Tile (i, j), register t of a lane is
-//   row  m = m0 + wm * 128 + i * 16 + (lane & 15)
-//   col  n = n0 + wn * 128 + j * 16 + 4 * (lane >> 4) + t
-using Accumulators = f32x4[8][8];
+// Accumulators of a wavefront: kW x kW tiles of 16 x 16.  Tile (i, j), register t of a lane is
+//   row  m = row0() + i * 16 + (lane & 15)
+//   col  n = col0() + j * 16 + 4 * (lane >> 4) + t
+template <int kW>
+using Accumulators = f32x4[kW][kW];
+template <int kW>
 struct TileCoord {
     int m0, n0, wm, wn, lane;
     int split;   // which part of a split reduction this workgroup computed
-    __device__ int row(int i) const { return m0 + wm * 128 + i * 16 + (lane & 15); }
-    __device__ int col(int j) const { return n0 + wn * 128 + j * 16 + 4 * (lane >> 4); }
+    __device__ int row0() const { return m0 + wm * kWaveRows<kW>; }
+    __device__ int col0() const { return n0 + wn * kWaveRows<kW>; }
 };
 
 // f(0), f(1), .. f(kN - 1) with the number as a constant.
@@ -133,17 +139,21 @@ __device__ inline int swizzle_unit(int unit, int k) { return unit ^ (k & 3) ^ ((
 // memory-side cache at once.)  Of the n_wg workgroups launched only tiles_m * tiles_n have a tile
 // (the row dimension may be cut short by a device-side count); only those are numbered, so a short
 // batch still spreads over all XCDs.
+template <int kW>
 __device__ inline bool tile_of_workgroup(int wg, int n_wg, int tiles_m, int tiles_n, int& tm, int& tn) {
     (void)n_wg;
-    constexpr int kBlock = 32;                      // tiles per XCD block = workgroups resident on one XCD
+    constexpr int kBlock = kW == kLargeTile ? 32 : 64;   // tiles per XCD block = workgroups resident on one XCD
     const int n_live = tiles_m * tiles_n;
     const int xcd = wg % kNumXcd, idx = wg / kNumXcd;
     const int full = n_live / (kBlock * kNumXcd);   // rounds in which every XCD gets a whole block
     int logical;
     if (idx < full * kBlock) logical = ((idx / kBlock) * kNumXcd + xcd) * kBlock + idx % kBlock;
-    else logical = full * kBlock * kNumXcd + (idx - full * kBlock) * kNumXcd + xcd;   // the rest, tile by tile
-    if (logical >= n_live) return false;
-    constexpr int kBand = 4;
+    else {                                          // the rest: neighbouring tiles to the same XCD, as evenly as they go
+        const int rest = n_live - full * kBlock * kNumXcd, at = idx - full * kBlock;
+        if (at >= rest / kNumXcd + (xcd < rest % kNumXcd ? 1 : 0)) return false;
+        logical = full * kBlock * kNumXcd + xcd * (rest / kNumXcd) + min(xcd, rest % kNumXcd) + at;
+    }
+    constexpr int kBand = kW == kLargeTile ? 4 : 8;
     const int band_size = kBand * tiles_n;
     const int band = logical / band_size;
     const int first = band * kBand;
@@ -221,17 +231,24 @@ __device__ inline auto runs_when_empty(const E& e, int) -> decltype(e.runs_when_
 template <class E>
 __device__ inline bool runs_when_empty(const E&, long) { return false; }
 
-template <class Epilogue, int kLayA, int kLayB>
-__global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epilogue epi) {
-    constexpr int kTileElems = kTileM * kTileK;                  // one operand tile
-    constexpr uint32_t kTileBytes = kTileElems * 2;
-    constexpr int kLoadsPerTile = 8;                             // wave-wide loads per wavefront per tile
+// An epilogue that combines columns 64 apart (of every 128) says so through a member kPairedColumns.
+template <class E>
+constexpr auto paired_columns(int) -> decltype(E::kPairedColumns) { return E::kPairedColumns; }
+template <class E>
+constexpr bool paired_columns(long) { return false; }
+
+template <class Epilogue, int kLayA, int kLayB, int kW>
+__global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_bf16(GemmProblem p, Epilogue epi) {
+    constexpr int TM = kTile<kW>, TN = kTile<kW>;
+    constexpr uint32_t kTileBytes = TM * kTileK * 2;             // one operand tile
+    constexpr int kLoadsPerTile = kW;                            // wave-wide loads per wavefront per tile
+    constexpr int kSmemBytes = kRingBytes<kW>;
     __shared__ __attribute__((aligned(1024))) __bf16 smem[kSmemBytes / 2];   // [slot][row][64]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
     const int wm = wave >> 1, wn = wave & 1;
-    const int tiles_m = p.M / kTileM, tiles_n = p.N / kTileN;
+    const int tiles_m = p.M / TM, tiles_n = p.N / TN;
     const int n_tiles = tiles_m * tiles_n;
     const int split = blockIdx.x / n_tiles;
     int k1 = p.K1, live_m = tiles_m;
@@ -239,12 +256,12 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
         int nk = *p.kept;
         nk = nk < 0 ? 0 : (nk > p.kept_max ? p.kept_max : nk);
         const int rows = max(0, nk * p.rows_per_kept - p.row_offset);
-        if (p.rows_role == kRowsAreM) live_m = min(tiles_m, (rows + kTileM - 1) / kTileM);
+        if (p.rows_role == kRowsAreM) live_m = min(tiles_m, (rows + kTileM - 1) / kTileM * (kTileM / TM));
         if (p.rows_role == kRowsAreK) k1 = min(k1, (rows + kTileK - 1) / kTileK * kTileK);
     }
     int tm, tn;
-    if (!tile_of_workgroup(blockIdx.x % n_tiles, n_tiles, live_m, tiles_n, tm, tn)) return;   // before any barrier
-    const int m0 = tm * kTileM, n0 = tn * kTileN;
+    if (!tile_of_workgroup<kW>(blockIdx.x % n_tiles, n_tiles, live_m, tiles_n, tm, tn)) return;   // before any barrier
+    const int m0 = tm * TM, n0 = tn * TN;
     // reduction range of this workgroup, in 64-wide steps over the concatenation of both segments
     const int steps1 = k1 / kTileK, steps_all = steps1 + p.K2 / kTileK;
     const int per_split = (steps_all + p.splits - 1) / p.splits;
@@ -255,14 +272,14 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
     // swizzle is therefore applied on the global side (the lane that lands in a slot fetches the
     // piece that belongs there).  Addresses are a wave-uniform base (tile origin + k offset) plus
     // a 32-bit per-lane byte offset.
-    //   [rows][K] operand: the tile is [256 rows][128 B]; wave w fills rows [64 w, 64 w + 64), 8 rows
+    //   [rows][K] operand: the tile is [32 kW rows][128 B]; wave w fills rows [8 kW w, 8 kW (w + 1)), 8 rows
     //     per load; piece p of row r sits in slot swizzle_piece(r, p).
-    //   [K][rows] operand: the tile is [64 k][512 B]; wave w fills k-rows [16 w, 16 w + 16), 2 per
-    //     load; the 32-byte unit u of k-row k sits in unit swizzle_unit(u, k & 3).
+    //   [K][rows] operand: the tile is [64 k][64 kW B]; wave w fills k-rows [16 w, 16 w + 16), 16 / kW per
+    //     load; the 32-byte unit u of k-row k sits in unit swizzle_unit(u, k).
     const uint32_t lds_base = (uint32_t)(uintptr_t)PCM_AS_LDS(smem);
     struct LoadCtx {
         const char* base;        // wave-uniform
-        uint32_t off[4];         // per-lane byte offset of a load before the per-load stride, by load_variant
+        uint32_t off[4];         // per-lane byte offset of a load before the per-load stride, by load_variant()
         uint32_t stride;         // bytes between consecutive loads
         uint32_t dst;            // LDS byte address of this wave's part of the slot
     };
@@ -280,7 +297,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
         const bf16* s1 = sel != nullptr ? *sel : (operand == 0 ? p.A : p.B);
         const bf16* s2 = sel != nullptr ? s1 : (operand == 0 ? p.A2 : p.B2);
         if (layout == kRowsByK) {
-            const uint32_t row = (uint32_t)wave * 64u + (uint32_t)(lane >> 3);      // + 8 r for load r
+            const uint32_t row = (uint32_t)wave * (8u * kW) + (uint32_t)(lane >> 3);   // + 8 r for load r
 #pragma unroll
             for (uint32_t var = 0; var < 4; ++var) {                                 // the swizzle uses row bit 3
                 const uint32_t piece = (uint32_t)swizzle_piece((lane >> 3) + 8 * (var & 1), lane & 7);
@@ -291,14 +308,15 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
             seg_origin[operand][1] = reinterpret_cast<const char*>(s2 + (int64_t)row0 * ld);
             k_step_bytes[operand] = kTileK * 2;
         } else {
-            const uint32_t krow = (uint32_t)wave * 16u + (uint32_t)(lane >> 5);      // + 2 r for load r
+            constexpr int kLanes = 4 * kW;                                            // lanes per k-row
+            const uint32_t krow = (uint32_t)wave * 16u + (uint32_t)(lane / kLanes);   // + (16 / kW) r for load r
 #pragma unroll
-            for (uint32_t var = 0; var < 4; ++var) {                                 // bits 0, 1 and 3 of the k-row
-                const int k = (int)(lane >> 5) + 2 * (int)(var & 1) + 8 * (int)(var >> 1);
-                const uint32_t piece = 2u * (uint32_t)swizzle_unit((lane & 31) >> 1, k) + (uint32_t)(lane & 1);
+            for (uint32_t var = 0; var < 4; ++var) {                                  // bits 0, 1 and 3 of the k-row
+                const int k = lane / kLanes + (kW == kLargeTile ? 2 * (int)(var & 1) + 8 * (int)(var >> 1) : 8 * (int)(var & 1));
+                const uint32_t piece = 2u * (uint32_t)swizzle_unit((lane % kLanes) >> 1, k) + (uint32_t)(lane & 1);
                 lane_off[operand][var] = (krow * ld + piece * 8u) * 2u;
             }
-            load_stride[operand] = 4u * ld;
+            load_stride[operand] = (32u / kW) * ld;
             seg_origin[operand][0] = reinterpret_cast<const char*>(s1 + row0);
             seg_origin[operand][1] = reinterpret_cast<const char*>(s2 + row0);
             k_step_bytes[operand] = (uint32_t)kTileK * ld * 2u;
@@ -315,25 +333,29 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
 #pragma unroll
         for (int var = 0; var < 4; ++var) c.off[var] = lane_off[operand][var];
         c.stride = load_stride[operand];
-        c.dst = lds_base + slot + (uint32_t)wave * 8192u;
+        c.dst = lds_base + slot + (uint32_t)wave * (kTileBytes / 4u);
         return c;
     };
     auto load_ctx = [&](int operand, uint32_t slot, int step) { return load_ctx_at(operand, slot, tile_origin(operand, step)); };
-    auto issue_loads = [&](const LoadCtx& c, uint32_t r0, uint32_t n) {
+    // which of the per-lane offsets load r takes
+    auto load_variant = [](int layout, int r) { return layout == kRowsByK ? r & 1 : (kW == kLargeTile ? (r & 1) | ((r >> 1) & 2) : r >> 1); };
+    auto issue_tile = [&](int operand, uint32_t slot, int step) {
+        const LoadCtx c = load_ctx(operand, slot, step);
 #pragma unroll
-        for (uint32_t r = r0; r < r0 + n; ++r) direct_load_16B(c.base, c.off[(r & 1u) | ((r >> 1) & 2u)] + r * c.stride, c.dst + r * 1024u);
+        for (uint32_t r = 0; r < (uint32_t)kLoadsPerTile; ++r)
+            direct_load_16B(c.base, c.off[load_variant(operand == 0 ? kLayA : kLayB, r)] + r * c.stride, c.dst + r * 1024u);
     };
 
-    Accumulators acc;
+    Accumulators<kW> acc;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < kW; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < kW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Fragment registers are double-buffered: while the 64 MFMAs of one 32-wide k-slice run, the
-    // 16 fragment reads of the next slice are in flight.  Fragment i = rows 16 i .. 16 i + 15 of
+    // Fragment registers are double-buffered: while the kW * kW MFMAs of one 32-wide k-slice run, the
+    // 2 kW fragment reads of the next slice are in flight.  Fragment i = rows 16 i .. 16 i + 15 of
     // the wavefront's A or B sub-tile; lane l holds row l & 15, k = 8 (l >> 4) .. + 7 of the slice.
-    bf16x8 fa[2][8], fb[2][8];
+    bf16x8 fa[2][kW], fb[2][kW];
     // LDS address of this lane's fragment 0 of slice ks in a tile in ring slot 0.
     //   [rows][K]: one 16-byte read; fragment i is 16 rows (2 KB) further.
     //   [K][rows]: two transpose reads, the lane's run starting in k-row 8 (l >> 4) + ((l & 15) >> 2), the second four
@@ -345,14 +367,20 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
             return lds_base + (uint32_t)(row * (kTileK * 2) + swizzle_piece(row, ks * 4 + (lane >> 4)) * 16);
         }
         const int k = (lane >> 4) * 8 + ((lane & 15) >> 2);
-        return lds_base + (uint32_t)((ks * 32 + k) * 512 + (swizzle_unit(sub_row0 >> 4, k) << 5) + ((lane & 3) << 3));
+        return lds_base + (uint32_t)((ks * 32 + k) * (64 * kW) + (swizzle_unit(sub_row0 >> 4, k) << 5) + ((lane & 3) << 3));
     };
-    const uint32_t base_a[2] = {fragment_base(kLayA, wm * 128, 0), fragment_base(kLayA, wm * 128, 1)};
-    const uint32_t base_b[2] = {fragment_base(kLayB, wn * 128, 0), fragment_base(kLayB, wn * 128, 1)};
-    constexpr uint32_t kHalfFragment = 4 * 512;
-    // `at`: the address of the fragment for [K][rows] tiles, of fragment 0 for [rows][K] tiles.
-    auto read_fragment = [](int layout, uint32_t at, int i) -> bf16x8 {
-        if (layout == kRowsByK) return *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)(at + (uint32_t)i * 2048u);
+    // B fragment j is rows 16 j .. of the wavefront's part; with paired columns (64 columns of one kind followed by the 64
+    // matching ones of another per 128, a wavefront needing both) and the small tile, half of its fragments come from each.
+    constexpr bool kPaired = paired_columns<Epilogue>(0) && kW == kSmallTile;
+    auto b_row = [](int j) { return kPaired ? j / (kW / 2) * 64 + j % (kW / 2) * 16 : j * 16; };
+    const int b_row0 = kPaired ? wn * (kWaveRows<kW> / 2) : wn * kWaveRows<kW>;
+    static_assert(!kPaired || kLayB == kRowsByK, "paired columns: rows by k only");
+    const uint32_t base_a[2] = {fragment_base(kLayA, wm * kWaveRows<kW>, 0), fragment_base(kLayA, wm * kWaveRows<kW>, 1)};
+    const uint32_t base_b[2] = {fragment_base(kLayB, b_row0, 0), fragment_base(kLayB, b_row0, 1)};
+    constexpr uint32_t kHalfFragment = 4 * 64 * kW;
+    // `at`: the address of the fragment for [K][rows] tiles; for [rows][K] tiles that of fragment 0, `row` rows before it.
+    auto read_fragment = [](int layout, uint32_t at, int row) -> bf16x8 {
+        if (layout == kRowsByK) return *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)(at + (uint32_t)row * 128u);
         return join_halves(read_transposed(at), read_transposed(at + kHalfFragment));
     };
     // ring slots are named by their byte offset in LDS
@@ -363,18 +391,18 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
         // slot t mod 5.  Prologue: tiles 0..4 (steps 0, 1 and the A tile of step 2) are requested;
         // steps past the end re-request the last step's tiles, which nobody reads.
         const int last = step_end - 1;
-        issue_loads(load_ctx(0, 0 * kTileBytes, step_begin), 0, 8);
-        issue_loads(load_ctx(1, 1 * kTileBytes, step_begin), 0, 8);
-        issue_loads(load_ctx(0, 2 * kTileBytes, min(step_begin + 1, last)), 0, 8);
-        issue_loads(load_ctx(1, 3 * kTileBytes, min(step_begin + 1, last)), 0, 8);
-        issue_loads(load_ctx(0, 4 * kTileBytes, min(step_begin + 2, last)), 0, 8);
+        issue_tile(0, 0 * kTileBytes, step_begin);
+        issue_tile(1, 1 * kTileBytes, step_begin);
+        issue_tile(0, 2 * kTileBytes, min(step_begin + 1, last));
+        issue_tile(1, 3 * kTileBytes, min(step_begin + 1, last));
+        issue_tile(0, 4 * kTileBytes, min(step_begin + 2, last));
         wait_direct_loads<3 * kLoadsPerTile>();
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            fa[0][i] = read_fragment(kLayA, kLayA == kRowsByK ? base_a[0] : base_a[0] ^ (uint32_t)(32 * i), i);
+        for (int i = 0; i < kW; ++i) {
+            fa[0][i] = read_fragment(kLayA, kLayA == kRowsByK ? base_a[0] : base_a[0] ^ (uint32_t)(32 * i), i * 16);
             const uint32_t at_b0 = base_b[0] + kTileBytes;
-            fb[0][i] = read_fragment(kLayB, kLayB == kRowsByK ? at_b0 : at_b0 ^ (uint32_t)(32 * i), i);
+            fb[0][i] = read_fragment(kLayB, kLayB == kRowsByK ? at_b0 : at_b0 ^ (uint32_t)(32 * i), b_row(i));
         }
         // One 64-wide step per trip.  `sa`, `sb` are the slots of this step's tiles, `na`, `nb` the next step's, the two
         // after them in the ring.  Fragment set 0 holds slice 0 of this step on entry and slice 0 of the next step on
@@ -392,44 +420,63 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
         // no reads, so that the reads of a slot have long landed when the barrier that frees the slot waits for them;
         // they carry the scalar bookkeeping of the tile pointers, a few instructions per gap.
         //
-        // Fragments of the next slice are read in the order its MFMAs need them: A0, B0..B7, A1..A7.
-        auto is_a = [](int n) { return n == 0 || n >= 9; };
-        auto fragment_of = [&](int n) { return n == 0 ? 0 : (n < 9 ? n - 1 : n - 8); };
-        // The 64 MFMAs of a slice walk the 8 x 8 tiles in serpentine order, so that consecutive
+        // (The small tile has two workgroups per CU to fill each other's gaps; its rows are 4 MFMAs, the first three carry
+        // a fragment read per gap.)
+        //
+        // Fragments of the next slice are read in the order its MFMAs need them: A0, B0, B1, .., A1, A2, ..
+        auto is_a = [](int n) { return n == 0 || n > kW; };
+        auto fragment_of = [&](int n) { return n == 0 ? 0 : (n <= kW ? n - 1 : n - kW); };
+        // The kW * kW MFMAs of a slice walk the tiles in serpentine order, so that consecutive
         // instructions always share one operand fragment.
-        // c: the tile refilled meanwhile; rd_a, rd_b: bases of the fragments of the next slice.
-        auto slice = [&](int set, const LoadCtx& c, uint32_t rd_a, uint32_t rd_b, auto hook) {
+        // refilled: the operand whose tile is refilled meanwhile, c: from and to where; rd_a, rd_b: bases of the fragments of
+        // the next slice.
+        auto slice = [&](int set, auto refilled, const LoadCtx& c, uint32_t rd_a, uint32_t rd_b, auto hook) {
             uint32_t tr_at = rd_a;       // [K][rows]: address of the fragment being read
             s16x4 tr_lo = {0, 0, 0, 0};  // [K][rows]: its first half
-            static_for<8>([&](auto row) __attribute__((always_inline)) {
+            auto transposed = [&](int n) { return is_a(n) ? kLayA == kKByRows : kLayB == kKByRows; };
+            auto read_rows = [&](int n) {                      // [rows][K]: read n
+                const int f = fragment_of(n);
+                if (is_a(n)) fa[set ^ 1][f] = read_fragment(kLayA, rd_a, f * 16);
+                else fb[set ^ 1][f] = read_fragment(kLayB, rd_b, b_row(f));
+            };
+            auto read_low = [&] { tr_lo = read_transposed(tr_at); };
+            auto read_high = [&](int n) {
+                (is_a(n) ? fa : fb)[set ^ 1][fragment_of(n)] = join_halves(tr_lo, read_transposed(tr_at + kHalfFragment));
+            };
+            auto next_address = [&](int n) {                   // [K][rows]: of read n
+                if (n < 2 * kW && transposed(n)) tr_at = fragment_address(is_a(n) ? rd_a : rd_b, 32 * fragment_of(n));
+            };
+            static_for<kW>([&](auto row) __attribute__((always_inline)) {
                 constexpr int g = decltype(row)::value;
-                constexpr int j0 = (g & 1) ? 7 : 0;
+                constexpr int j0 = (g & 1) ? kW - 1 : 0;
+                constexpr int layout = decltype(refilled)::value == 0 ? kLayA : kLayB;
                 mfma_16x16x32_and_load<g * 1024u>(acc[g][j0], fb[set][j0], fa[set][g], c.base,
-                                                  c.off[(g & 1) | ((g >> 1) & 2)] + g * c.stride, c.dst);
+                                                  c.off[load_variant(layout, g)] + g * c.stride, c.dst);
 #pragma unroll
-                for (int jj = 1; jj < 8; ++jj) {
-                    const int j = (g & 1) ? 7 - jj : jj;
+                for (int jj = 1; jj < kW; ++jj) {
+                    const int j = (g & 1) ? kW - 1 - jj : jj;
                     mfma_16x16x32(acc[g][j], fb[set][j], fa[set][g]);
                     __builtin_amdgcn_sched_barrier(0);
-                    // read n of the next slice: [rows][K] in gap jj, [K][rows] in halves in gaps jj and jj + 1 with the
-                    // address of the next one made behind the second (behind the last one of a row in gap 7)
-                    const int n = 3 * g + (jj - 1) / 2;
-                    if (g < 6 && jj < 7 && n < 16) {
-                        const int f = fragment_of(n);
-                        const bool transposed = is_a(n) ? kLayA == kKByRows : kLayB == kKByRows;
-                        if (jj & 1) {
-                            if (transposed) tr_lo = read_transposed(tr_at);
-                            else if (is_a(n)) fa[set ^ 1][f] = read_fragment(kLayA, rd_a, f);
-                            else fb[set ^ 1][f] = read_fragment(kLayB, rd_b, f);
-                        } else if (transposed) {
-                            (is_a(n) ? fa : fb)[set ^ 1][f] = join_halves(tr_lo, read_transposed(tr_at + kHalfFragment));
+                    if (kW == kLargeTile) {
+                        // read n of the next slice: [rows][K] in gap jj, [K][rows] in halves in gaps jj and jj + 1 with the
+                        // address of the next one made behind the second (behind the last one of a row in gap 7)
+                        const int n = 3 * g + (jj - 1) / 2;
+                        if (g < 6 && jj < 7 && n < 2 * kW) {
+                            if (!transposed(n)) { if (jj & 1) read_rows(n); }
+                            else if (jj & 1) read_low();
+                            else read_high(n);
                         }
+                        if (g < 6 && (jj == 2 || jj == 4 || jj == 7)) next_address(3 * g + jj / 2);
+                        if (g >= 6 && !(jj & 1)) hook(3 * (g - 6) + jj / 2 - 1);
+                    } else {
+                        const int n = 3 * g + jj - 1;
+                        if (g < 3 && n < 2 * kW) {
+                            if (!transposed(n)) read_rows(n);
+                            else { read_low(); read_high(n); }
+                            next_address(n + 1);
+                        }
+                        if (g == 3) { hook(2 * jj - 2); hook(2 * jj - 1); }
                     }
-                    if (g < 6 && (jj == 2 || jj == 4 || jj == 7) && 3 * g + jj / 2 < 16) {
-                        const int next = 3 * g + jj / 2, f = fragment_of(next);
-                        if (is_a(next) ? kLayA == kKByRows : kLayB == kKByRows) tr_at = fragment_address(is_a(next) ? rd_a : rd_b, 32 * f);
-                    }
-                    if (g >= 6 && !(jj & 1)) hook(3 * (g - 6) + jj / 2 - 1);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             });
@@ -467,10 +514,10 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
             else nb = next_slot(na);
         };
         for (int step = step_begin; step < step_end; ++step) {
-            slice(0, load_ctx_at(0, refill_a, origin_a), rd_a, rd_b, [&](int piece) { between_a(step, piece); });
+            slice(0, Index<0>{}, load_ctx_at(0, refill_a, origin_a), rd_a, rd_b, [&](int piece) { between_a(step, piece); });
             wait_direct_loads<kLoadsPerTile>();
             __syncthreads();
-            slice(1, load_ctx_at(1, sa, origin_b), rd_a, rd_b, between_b);   // tile 2 s + 5 -> slot of tile 2 s
+            slice(1, Index<1>{}, load_ctx_at(1, sa, origin_b), rd_a, rd_b, between_b);   // tile 2 s + 5 -> slot of tile 2 s
         }
         wait_direct_loads<0>();
         // the last MFMAs' results: the compiler does not know how long inline assembly takes to write them
@@ -479,7 +526,7 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
     }
 
     if (p.skip_if_empty && step_begin >= step_end && !runs_when_empty(epi, 0)) return;   // nothing to add (uniform over the workgroup)
-    TileCoord tc{m0, n0, wm, wn, lane, split};
+    const TileCoord<kW> tc{m0, n0, wm, wn, lane, split};
     epi(tc, acc, reinterpret_cast<char*>(smem));
 }
 
@@ -489,21 +536,20 @@ __global__ __launch_bounds__(kGemmThreads, 1) void gemm_bf16(GemmProblem p, Epil
 // rounded to bf16 afterwards).
 __device__ inline float fast_sigmoid(float x) { return __builtin_amdgcn_rcpf(1.f + __expf(-x)); }
 
-__device__ inline char* wave_stage(const TileCoord& tc, char* lds) {
-    return lds + (tc.wm * 2 + tc.wn) * kWaveStageBytes;
+template <int kW>
+__device__ inline char* wave_stage(const TileCoord<kW>& tc, char* lds) {
+    return lds + (tc.wm * 2 + tc.wn) * kWaveStageBytes<kW>;
 }
 
-// Writes bf16 of four consecutive columns per lane for the 16-column tiles jj = 0 .. nj - 1 of one tile row into a
-// staging area whose rows are `stride` bytes apart, starting at column col_off.  The 32 lanes served together write
+// Writes bf16 of four consecutive columns per lane for the 16-column tiles 0 .. kN - 1 of one tile row into a
+// staging area whose rows are `stride` bytes apart.  The 32 lanes served together write
 // 16 rows x 16 bytes, so a stride of 16 bytes times an odd number spreads them over all banks.
-template <class F>
-__device__ inline void stage_tile_row(char* stage, int stride, int lane, int local_row, int col_off, int nj, F value) {
+template <int kN, class F>
+__device__ inline void stage_tile_row(char* stage, int stride, int lane, int local_row, F value) {
 #pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-        if (jj >= nj) break;
-        const int col = col_off + jj * 16 + 4 * (lane >> 4);
+    for (int jj = 0; jj < kN; ++jj) {
         const f32x4 v = value(jj);
-        *reinterpret_cast<bf16x4*>(stage + local_row * stride + col * 2) = to_bf16x4(v[0], v[1], v[2], v[3]);
+        *reinterpret_cast<bf16x4*>(stage + local_row * stride + (jj * 16 + 4 * (lane >> 4)) * 2) = to_bf16x4(v[0], v[1], v[2], v[3]);
     }
 }
 
@@ -616,17 +662,19 @@ struct EpiStoreBf16 {
     bf16* C;
     int64_t ldc;
     int row_limit;
-    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
-        constexpr int kStride = 272;                       // 128 bf16 + 16 bytes
+    template <int kW>
+    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+        constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
+        constexpr int kStride = RW * 2 + 16;
         char* st = wave_stage(tc, lds);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            stage_tile_row(st, kStride, tc.lane, i * 16 + (tc.lane & 15), 0, 8, [&](int j) { return acc[i][j]; });
+        for (int i = 0; i < kW; ++i) {
+            stage_tile_row<kW>(st, kStride, tc.lane, i * 16 + (tc.lane & 15), [&](int j) { return acc[i][j]; });
             __builtin_amdgcn_sched_barrier(0);   // one tile row's conversions at a time: all at once spill
         }
         __builtin_amdgcn_wave_barrier();
-        const int row_base = tc.m0 + tc.wm * 128, col_base = tc.n0 + tc.wn * 128;
-        copy_rows_out<128, 256>(st, kStride, reinterpret_cast<char*>(C + (int64_t)row_base * ldc + col_base), ldc * 2,
+        const int row_base = tc.row0(), col_base = tc.col0();
+        copy_rows_out<RW, RW * 2>(st, kStride, reinterpret_cast<char*>(C + (int64_t)row_base * ldc + col_base), ldc * 2,
                                 row_limit - row_base, tc.lane);
     }
 };
@@ -637,17 +685,19 @@ struct EpiScatterBf16 {
     bf16* C;
     int64_t ldc;
     const int32_t* row_idx;
-    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
-        constexpr int kStride = 272;
+    template <int kW>
+    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+        constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
+        constexpr int kStride = RW * 2 + 16;
         char* st = wave_stage(tc, lds);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            stage_tile_row(st, kStride, tc.lane, i * 16 + (tc.lane & 15), 0, 8, [&](int j) { return acc[i][j]; });
+        for (int i = 0; i < kW; ++i) {
+            stage_tile_row<kW>(st, kStride, tc.lane, i * 16 + (tc.lane & 15), [&](int j) { return acc[i][j]; });
             __builtin_amdgcn_sched_barrier(0);   // one tile row's conversions at a time: all at once spill
         }
         __builtin_amdgcn_wave_barrier();
-        const int row_base = tc.m0 + tc.wm * 128, col_base = tc.n0 + tc.wn * 128;
-        copy_rows_out_at<128, 256>(st, kStride, reinterpret_cast<char*>(C + col_base), ldc * 2, row_idx + row_base, tc.lane);
+        const int row_base = tc.row0(), col_base = tc.col0();
+        copy_rows_out_at<RW, RW * 2>(st, kStride, reinterpret_cast<char*>(C + col_base), ldc * 2, row_idx + row_base, tc.lane);
     }
 };
 
@@ -658,18 +708,20 @@ struct EpiStoreBf16Split {
     bf16 *hi, *lo;
     int64_t ldc;
     int row_limit;
-    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
-        constexpr int kStride = 528;                       // [hi 128 | lo 128] bf16 + 16 bytes
+    template <int kW>
+    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+        constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
+        constexpr int kStride = RW * 4 + 16;               // [hi | lo] bf16 + 16 bytes
         char* st = wave_stage(tc, lds);
-        const int col_base = tc.n0 + tc.wn * 128;
+        const int col_base = tc.col0();
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {             // 64 rows per pass
+        for (int half = 0; half < RW / 64; ++half) {       // 64 rows per pass
 #pragma unroll
             for (int ii = 0; ii < 4; ++ii) {
                 const int i = half * 4 + ii;
                 char* row = st + (ii * 16 + (tc.lane & 15)) * kStride;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
+                for (int j = 0; j < kW; ++j) {
                     float r[4];
                     bf16x4 h;
 #pragma unroll
@@ -680,14 +732,14 @@ struct EpiStoreBf16Split {
                     }
                     char* at = row + (j * 16 + 4 * (tc.lane >> 4)) * 2;
                     *reinterpret_cast<bf16x4*>(at) = h;
-                    *reinterpret_cast<bf16x4*>(at + 256) = to_bf16x4(r[0], r[1], r[2], r[3]);
+                    *reinterpret_cast<bf16x4*>(at + RW * 2) = to_bf16x4(r[0], r[1], r[2], r[3]);
                 }
             }
             __builtin_amdgcn_wave_barrier();
-            const int row_base = tc.m0 + tc.wm * 128 + half * 64;
+            const int row_base = tc.row0() + half * 64;
             const int64_t at = (int64_t)row_base * ldc + col_base;
-            copy_rows_out<64, 256>(st, kStride, reinterpret_cast<char*>(hi + at), ldc * 2, row_limit - row_base, tc.lane);
-            copy_rows_out<64, 256>(st + 256, kStride, reinterpret_cast<char*>(lo + at), ldc * 2, row_limit - row_base, tc.lane);
+            copy_rows_out<64, RW * 2>(st, kStride, reinterpret_cast<char*>(hi + at), ldc * 2, row_limit - row_base, tc.lane);
+            copy_rows_out<64, RW * 2>(st + RW * 2, kStride, reinterpret_cast<char*>(lo + at), ldc * 2, row_limit - row_base, tc.lane);
             __builtin_amdgcn_wave_barrier();
         }
     }
@@ -719,67 +771,73 @@ struct EpiStoreF32 {
     double* sumsq_parts;
     FinalPanel final_panel;
     __device__ bool runs_when_empty() const { return sumsq_parts != nullptr && final_panel(); }
-    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
+    template <int kW>
+    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+        constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
         float* const C = this->C + tc.split * split_stride;
-        constexpr int kStride = 528;                       // 128 fp32 + 16 bytes: conflict-free 16-byte accesses
+        constexpr int kStride = RW * 4 + 16;               // conflict-free 16-byte accesses
         char* st = wave_stage(tc, lds);
-        const int col_base = tc.n0 + tc.wn * 128;
+        const int col_base = tc.col0();
         const bool want_sq = sumsq_parts != nullptr && final_panel();
         double sq = 0.0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {                      // 32 rows per pass
+        for (int i = 0; i < RW / 32; ++i) {                // 32 rows per pass
 #pragma unroll
             for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
+                for (int j = 0; j < kW; ++j)
                     *reinterpret_cast<f32x4*>(st + (ii * 16 + (tc.lane & 15)) * kStride + (j * 16 + 4 * (tc.lane >> 4)) * 4) =
                         acc[2 * i + ii][j];
             __builtin_amdgcn_wave_barrier();
-            const int row_base = tc.m0 + tc.wm * 128 + i * 32;
+            const int row_base = tc.row0() + i * 32;
             char* const dst = reinterpret_cast<char*>(C + (int64_t)row_base * ldc + col_base);
-            if (accumulate) add_rows_out<32, 512>(st, kStride, dst, ldc * 4, tc.lane);
-            else copy_rows_out<32, 512>(st, kStride, dst, ldc * 4, 32, tc.lane);
-            if (want_sq) sq += staged_sum_of_squares<32, 512>(st, kStride, tc.lane);
+            if (accumulate) add_rows_out<32, RW * 4>(st, kStride, dst, ldc * 4, tc.lane);
+            else copy_rows_out<32, RW * 4>(st, kStride, dst, ldc * 4, 32, tc.lane);
+            if (want_sq) sq += staged_sum_of_squares<32, RW * 4>(st, kStride, tc.lane);
             __builtin_amdgcn_wave_barrier();
         }
         if (want_sq) {
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
-            const int tile = (tc.m0 / kTileM) * (int)(ldc / kTileN) + tc.n0 / kTileN;
+            const int tile = (tc.m0 / kTile<kW>) * (int)(ldc / kTile<kW>) + tc.n0 / kTile<kW>;
             if (tc.lane == 0) sumsq_parts[tile * 4 + tc.wm * 2 + tc.wn] = sq;
         }
     }
 };
 
 // Gate/up projection with the activation fused: the B operand holds, per 128 packed rows, 64 gate
-// columns followed by the 64 up columns of the same index range, so a wavefront's tiles j = 0 .. 3
-// are u (gate) and j = 4 .. 7 the matching v (up).  Writes a = silu(u) * v (bf16, [M, ff]) and, for
+// columns followed by the 64 up columns of the same index range, and the first half of a wavefront's tiles j
+// are u (gate), the second half the matching v (up) (see paired_columns).  Writes a = silu(u) * v (bf16, [M, ff]) and, for
 // a backward pass to come, the two factors it will need, computed here where the sigmoid is at
 // hand: fu = v * silu'(u) (so du = da * fu) and fv = silu(u) (so dv = da * fv).
 // With kKeepLow the rounding remainder of a is written as well (a_lo = bf16(a - bf16(a))), for products
 // that need the activation to more than bf16 precision (they read [a | a_lo] as two reduction segments).
 template <bool kKeepFactors, bool kKeepLow = false>
 struct EpiSwigluForward {
+    static constexpr bool kPairedColumns = true;
     bf16 *fu, *fv, *a, *a_lo;
     int64_t ld;
-    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
-        // staged row: [a 64 | fu 64 | fv 64 | a_lo 64] bf16 (the parts that are kept) + 16 bytes
-        constexpr int kLowAt = kKeepFactors ? 384 : 128;
-        constexpr int kStride = 16 + 128 * (1 + (kKeepFactors ? 2 : 0) + (kKeepLow ? 1 : 0));
+    template <int kW>
+    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+        constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
+        constexpr int CW = RW / 2;                         // columns of the activation in this wavefront's block
+        // staged row: [a | fu | fv | a_lo] bf16 (the parts that are kept) + 16 bytes
+        constexpr int kPart = CW * 2, kLowAt = kKeepFactors ? 3 * kPart : kPart;
+        constexpr int kStride = 16 + kPart * (1 + (kKeepFactors ? 2 : 0) + (kKeepLow ? 1 : 0));
         char* st = wave_stage(tc, lds);
-        const int col_base = ((tc.n0 + tc.wn * 128) / 128) * 64;
+        const int col_base = tc.n0 / 2 + tc.wn * CW;
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {             // 64 rows per pass
+        for (int half = 0; half < RW / 64; ++half) {       // 64 rows per pass
 #pragma unroll
             for (int ii = 0; ii < 4; ++ii) {
                 const int i = half * 4 + ii;
                 char* row = st + (ii * 16 + (tc.lane & 15)) * kStride;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+                for (int j = 0; j < kW / 2; ++j) {
                     float av[4], fuv[4], fvv[4];
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
-                        const float x = acc[i][j][t], y = acc[i][j + 4][t];
+                        const float x = acc[i][j][t], y = acc[i][j + kW / 2][t];
                         const float sg = kKeepLow ? 1.f / (1.f + expf(-x)) : fast_sigmoid(x);   // full accuracy where it is kept
                         fvv[t] = x * sg;
                         av[t] = fvv[t] * y;
@@ -790,8 +848,8 @@ struct EpiSwigluForward {
                     const bf16x4 a4 = to_bf16x4(av[0], av[1], av[2], av[3]);
                     *reinterpret_cast<bf16x4*>(at) = a4;
                     if (kKeepFactors) {
-                        *reinterpret_cast<bf16x4*>(at + 128) = to_bf16x4(fuv[0], fuv[1], fuv[2], fuv[3]);
-                        *reinterpret_cast<bf16x4*>(at + 256) = to_bf16x4(fvv[0], fvv[1], fvv[2], fvv[3]);
+                        *reinterpret_cast<bf16x4*>(at + kPart) = to_bf16x4(fuv[0], fuv[1], fuv[2], fuv[3]);
+                        *reinterpret_cast<bf16x4*>(at + 2 * kPart) = to_bf16x4(fvv[0], fvv[1], fvv[2], fvv[3]);
                     }
                     if (kKeepLow)
                         *reinterpret_cast<bf16x4*>(at + kLowAt) = to_bf16x4(av[0] - (float)a4[0], av[1] - (float)a4[1],
@@ -799,14 +857,14 @@ struct EpiSwigluForward {
                 }
             }
             __builtin_amdgcn_wave_barrier();
-            const int row_base = tc.m0 + tc.wm * 128 + half * 64;
-            const int64_t at = (int64_t)row_base * ld + col_base;     // 64 rows x 128 bytes of each output
-            copy_rows_out<64, 128>(st, kStride, reinterpret_cast<char*>(a + at), ld * 2, 64, tc.lane);
+            const int row_base = tc.row0() + half * 64;
+            const int64_t at = (int64_t)row_base * ld + col_base;     // 64 rows x CW columns of each output
+            copy_rows_out<64, kPart>(st, kStride, reinterpret_cast<char*>(a + at), ld * 2, 64, tc.lane);
             if (kKeepFactors) {
-                copy_rows_out<64, 128>(st + 128, kStride, reinterpret_cast<char*>(fu + at), ld * 2, 64, tc.lane);
-                copy_rows_out<64, 128>(st + 256, kStride, reinterpret_cast<char*>(fv + at), ld * 2, 64, tc.lane);
+                copy_rows_out<64, kPart>(st + kPart, kStride, reinterpret_cast<char*>(fu + at), ld * 2, 64, tc.lane);
+                copy_rows_out<64, kPart>(st + 2 * kPart, kStride, reinterpret_cast<char*>(fv + at), ld * 2, 64, tc.lane);
             }
-            if (kKeepLow) copy_rows_out<64, 128>(st + kLowAt, kStride, reinterpret_cast<char*>(a_lo + at), ld * 2, 64, tc.lane);
+            if (kKeepLow) copy_rows_out<64, kPart>(st + kLowAt, kStride, reinterpret_cast<char*>(a_lo + at), ld * 2, 64, tc.lane);
             __builtin_amdgcn_wave_barrier();
         }
     }
@@ -815,7 +873,7 @@ struct EpiSwigluForward {
 // acc = da.  du = da * fu, dv = da * fv (bf16, [M, ff]; the factors are those written by the forward epilogue).
 // kIndexed = false: in place, fu <- du, fv <- dv.  kIndexed = true: the rows of the product are a selection of the
 // rows the forward pass ran over: product row m takes its factors from row row_idx[m] of fu, fv (negative: a row of
-// zeros) and writes row m of du, dv (other buffers).  Works through the wavefront's 128 x 128 block in four passes of
+// zeros) and writes row m of du, dv (other buffers).  Works through the wavefront's block in passes of
 // 32 rows; the rows of the next pass are fetched into registers while the current pass is computed.
 template <bool kIndexed>
 struct EpiSwigluBackward {
@@ -823,30 +881,33 @@ struct EpiSwigluBackward {
     int64_t ld;
     const int32_t* row_idx;
     bf16 *du, *dv;
-    __device__ __forceinline__ void operator()(const TileCoord& tc, const Accumulators& acc, char* lds) const {
-        constexpr int kStride = 528;                       // [du 128 | dv 128] bf16 + 16 bytes
+    template <int kW>
+    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+        constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
+        constexpr int kStride = RW * 4 + 16;               // [du | dv] bf16 + 16 bytes
         char* st = wave_stage(tc, lds);
-        const int row_base = tc.m0 + tc.wm * 128, col_base = tc.n0 + tc.wn * 128;
+        const int row_base = tc.row0(), col_base = tc.col0();
         const int64_t ld_bytes = ld * 2;
         const int64_t at = (kIndexed ? 0 : (int64_t)row_base * ld) + col_base;
         const char* const u0 = reinterpret_cast<const char*>(fu + at);
         const char* const v0 = reinterpret_cast<const char*>(fv + at);
         char* const du0 = reinterpret_cast<char*>((kIndexed ? du : fu) + (int64_t)row_base * ld + col_base);
         char* const dv0 = reinterpret_cast<char*>((kIndexed ? dv : fv) + (int64_t)row_base * ld + col_base);
-        // the 128 row numbers of this wavefront's block, two per lane; a pass hands them to the lanes that fetch the rows
+        // the row numbers of this wavefront's block, one or two per lane; a pass hands them to the lanes that fetch the rows
         int idx_lo = 0, idx_hi = 0;
         if (kIndexed) {
             idx_lo = row_idx[row_base + tc.lane];
-            idx_hi = row_idx[row_base + 64 + tc.lane];
+            if (RW > 64) idx_hi = row_idx[row_base + 64 + tc.lane];
         }
-        RowFetch<32, 256> ru, rv;
+        using Fetch = RowFetch<32, RW * 2>;
+        Fetch ru, rv;
         auto fetch = [&](int pass) __attribute__((always_inline)) {
             if (kIndexed) {
-                int rows[RowFetch<32, 256>::kPasses];
+                int rows[Fetch::kPasses];
 #pragma unroll
-                for (int q = 0; q < RowFetch<32, 256>::kPasses; ++q)
+                for (int q = 0; q < Fetch::kPasses; ++q)
                     rows[q] = __shfl(pass < 2 ? idx_lo : idx_hi,
-                                     (pass & 1) * 32 + tc.lane / RowFetch<32, 256>::kLanesPerRow + q * RowFetch<32, 256>::kRowsPerPass, 64);
+                                     (pass & 1) * 32 + tc.lane / Fetch::kLanesPerRow + q * Fetch::kRowsPerPass, 64);
                 ru.fetch_rows_at(u0, ld_bytes, rows, tc.lane);
                 rv.fetch_rows_at(v0, ld_bytes, rows, tc.lane);
             } else {
@@ -856,18 +917,18 @@ struct EpiSwigluBackward {
         };
         fetch(0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {                      // 32 rows per pass
+        for (int i = 0; i < RW / 32; ++i) {                // 32 rows per pass
             ru.stash_rows(st, kStride, tc.lane);
-            rv.stash_rows(st + 256, kStride, tc.lane);
-            if (i < 3) fetch(i + 1);
+            rv.stash_rows(st + RW * 2, kStride, tc.lane);
+            if (i < RW / 32 - 1) fetch(i + 1);
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
+                for (int j = 0; j < kW; ++j) {
                     const int col = j * 16 + 4 * (tc.lane >> 4);
                     char* pu = st + (ii * 16 + (tc.lane & 15)) * kStride + col * 2;
-                    char* pv = pu + 256;
+                    char* pv = pu + RW * 2;
                     const bf16x4 u4 = *reinterpret_cast<const bf16x4*>(pu);
                     const bf16x4 v4 = *reinterpret_cast<const bf16x4*>(pv);
                     const f32x4 g = acc[2 * i + ii][j];
@@ -882,17 +943,33 @@ struct EpiSwigluBackward {
                     if (j & 1) __builtin_amdgcn_sched_barrier(0);   // two tiles at a time: beside the fetched rows more spill
                 }
             __builtin_amdgcn_wave_barrier();
-            copy_rows_out<32, 256>(st, kStride, du0 + i * 32 * ld_bytes, ld_bytes, 32, tc.lane);
-            copy_rows_out<32, 256>(st + 256, kStride, dv0 + i * 32 * ld_bytes, ld_bytes, 32, tc.lane);
+            copy_rows_out<32, RW * 2>(st, kStride, du0 + i * 32 * ld_bytes, ld_bytes, 32, tc.lane);
+            copy_rows_out<32, RW * 2>(st + RW * 2, kStride, dv0 + i * 32 * ld_bytes, ld_bytes, 32, tc.lane);
             __builtin_amdgcn_wave_barrier();
         }
     }
 };
 
+// The tile for a product of M x N: a CU's time is the number of its tiles times what one takes.  A 64-wide step takes
+// 0.94 us with the large tile (the matrix pipe) and 0.46 us with the small one, not a quarter: it brings in 32 KB for a
+// quarter of the products, and the path from L2 into LDS carries about 70 GB/s per CU.  So the small tile pays where the
+// large ones are few: measured, large against small, 2072 rows at 512 -> 768 (54 tiles) 19.9 / 10.2 us, 672 x 4096 x 11008
+// (48 tiles) 181 / 116 us, 5376 x 4096 x 11008 (336 tiles) 261 / 416 us.
+inline int tile_for(int64_t M, int64_t N, int splits) {
+    const int64_t large = (M / kTileM) * (N / kTileN) * splits;
+    const double cost_large = 0.94 * (double)((large + 255) / 256), cost_small = 0.46 * (double)((4 * large + 255) / 256);
+    return cost_small < cost_large ? kSmallTile : kLargeTile;
+}
+
+template <int kLayA = kRowsByK, int kLayB = kRowsByK, int kW = kLargeTile, class Epilogue>
+inline void launch_gemm_tile(const GemmProblem& p, const Epilogue& epi, hipStream_t s) {
+    const unsigned grid = (unsigned)(p.M / kTile<kW>) * (unsigned)(p.N / kTile<kW>) * (unsigned)p.splits;
+    gemm_bf16<Epilogue, kLayA, kLayB, kW><<<grid, kGemmThreads, 0, s>>>(p, epi);
+}
 template <int kLayA = kRowsByK, int kLayB = kRowsByK, class Epilogue>
 inline void launch_gemm(const GemmProblem& p, const Epilogue& epi, hipStream_t s) {
-    const unsigned grid = (unsigned)(p.M / kTileM) * (unsigned)(p.N / kTileN) * (unsigned)p.splits;
-    gemm_bf16<Epilogue, kLayA, kLayB><<<grid, kGemmThreads, 0, s>>>(p, epi);
+    if (tile_for(p.M, p.N, p.splits) == kSmallTile) launch_gemm_tile<kLayA, kLayB, kSmallTile>(p, epi, s);
+    else launch_gemm_tile<kLayA, kLayB, kLargeTile>(p, epi, s);
 }
 
 }  // namespace pcm

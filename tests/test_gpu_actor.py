@@ -258,6 +258,33 @@ def test_bf16_logits_as_parts_of_a_split_reduction(pcm, d, ff, n_kept, composed)
     check(ref, got, BF16_TOL, len(ref["rows"]), stats_tol=5e-2)
 
 
+@pytest.mark.parametrize("d,ff,n_kept,max_kept", [
+    (256, 32768, 5, 9),       # wide: gate/up, da and dWg, dWu on 256-wide tiles, the narrow products on 128-wide ones
+    (256, 32768, 9, 9),
+    (1536, 2304, 11, 16),     # 616 rows: everything on 128-wide tiles, a live row tile of 256 only half covered by rows
+    (2048, 2048, 2, 3),       # 112 rows: fewer than one small tile
+])
+def test_bf16_both_tile_sizes(pcm, d, ff, n_kept, max_kept, composed):
+    """The rule takes 128-wide tiles where 256-wide ones would leave CUs idle; products of one step may differ in it.  Rows
+    of dX between the kept ones and the end of the last 256 rows come out as zeros with either."""
+    cfg = CONFIGS["cfg2"].with_(n_groups=1, G=4, N=8, K=4, B=4, d=d, ff=ff, seed=80 + n_kept)
+    ro = make_rollouts(cfg, 0)
+    _, active = O.advantages(ro["reward"], cfg.G)
+    kept, _, _ = O.sample_chunks(np.array([1.0, 0.3, 0.1, 0.6]), ro["phase"], None, active, cfg.B, cfg.seed, 0)
+    pr = make_problem(cfg, wstd=0.04 if d == 256 else 1.3 / np.sqrt(d), margin=0.08, kept=kept[:n_kept], old_rel=0.1, eps=(0.2, 0.4))
+    variants = [{}, dict(entropy_coef=1e-3, token_mean=True)]
+    for v in variants:
+        kw = {} if composed else dict(grad_sumsq=True)
+        ref, got = run_both(pcm, pr, eps=(0.2, 0.4), torch_dtype=torch.bfloat16, max_kept=max_kept, composed_head=composed, variants=v,
+                            scale=1.0 if v else None, **kw)
+        n = len(ref["rows"])
+        check(ref, got, BF16_TOL, n, stats_tol=5e-2)
+        assert not got["dX"][n:min(len(got["dX"]), -(-n // 256) * 256)].any()
+        if not composed:
+            sq = sum(float((got[k].astype(np.float64) ** 2).sum()) for k in GRADS)
+            assert abs(got["grad_sumsq"][0] - sq) <= 1e-6 * sq
+
+
 def test_bf16_all_kept_and_forward_only(pcm, composed):
     cfg = CONFIGS["cfg2"].with_(n_groups=1, G=4, N=6, K=3, B=6, d=256, ff=256, seed=13)
     pr = make_problem(cfg, wstd=0.08, margin=0.08, kept=np.arange(cfg.T * cfg.N), old_rel=0.1)
