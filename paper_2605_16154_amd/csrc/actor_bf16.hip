@@ -474,8 +474,10 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
     }
 
     const bool want_sumsq = grads && io.opt.grad_sumsq_out != nullptr && ws != nullptr && w.sumsq[0] != nullptr;
-    if (want_sumsq)   // slots no launch of this call writes must read as zero (a fill kernel: safe under graph capture)
-        for (int q = 0; q < 4; ++q) fill_zero_f64<<<(w.sumsq_count[q] + 255) / 256, 256, 0, s>>>(w.sumsq[q], w.sumsq_count[q]);
+    if (want_sumsq) {   // slots no launch of this call writes must read as zero (a fill kernel: safe under graph capture)
+        const int n = (int)(w.sumsq[3] - w.sumsq[0]) + w.sumsq_count[3];       // the four lists follow one another
+        fill_zero_f64<<<(n + 255) / 256, 256, 0, s>>>(w.sumsq[0], n);
+    }
 
     int rc = PCM_OK;
     for (int64_t row0 = 0; row0 < w.Mp; row0 += w.Rp) {
