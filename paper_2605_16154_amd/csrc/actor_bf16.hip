@@ -424,6 +424,28 @@ GemmProblem problem(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int 
     return p;
 }
 
+// C [M, N] bf16 = a product over the rows of the batch.  With few tiles and a long reduction it is computed as parts of a
+// split reduction (fp32) and summed: the operands then arrive over twice as many workgroups, and it is their latency and
+// not the products that such a launch waits for.  768 x 4096 x 11008 (192 small tiles): 124 us in one part, 97 us in two
+// with the sum.
+void launch_rows_bf16(GemmProblem p, bf16* C, float* parts, hipStream_t s) {
+    const int tiles = (p.M / kTileM) * (p.N / kTileN), steps = (p.K1 + p.K2) / kTileK;
+    if (tile_for(p.M, p.N, 1) == kSmallTile) {
+        int splits = 512 / (4 * tiles);                 // two small tiles per CU
+        if (splits > steps / 16) splits = steps / 16;
+        if (splits > 4) splits = 4;
+        if (splits > 1) {
+            p.splits = splits;
+            const size_t n = (size_t)p.M * p.N;
+            launch_gemm_tile<kRowsByK, kRowsByK, kSmallTile>(p, EpiStoreF32{parts, p.N, (int64_t)n, 0, nullptr, FinalPanel{}}, s);
+            const size_t blocks = (n / 4 + 255) / 256;
+            sum_parts_bf16<<<(unsigned)(blocks < kSumBlocksMax ? blocks : kSumBlocksMax), 256, 0, s>>>(parts, splits, n, C);
+            return;
+        }
+    }
+    launch_row_gemm(p, EpiStoreBf16{C, p.N, p.M}, s);
+}
+
 }  // namespace
 
 size_t packed_head_bytes(int d, int ff, int V) { return carve_packed(nullptr, d, ff, V).bytes; }
@@ -498,19 +520,19 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
         {
             StageTimer t(ST_GEMM_GATE_UP, s);
             const GemmProblem p = problem(w.X, d, w.WguT, d, Mp, 2 * ff, d, kr, kRowsAreM);
-            if (split && bwd) launch_gemm(p, EpiSwigluForward<true, true>{w.fu, w.fv, w.a, w.a_lo, ff}, s);
-            else if (split) launch_gemm(p, EpiSwigluForward<false, true>{nullptr, nullptr, w.a, w.a_lo, ff}, s);
-            else if (bwd) launch_gemm(p, EpiSwigluForward<true>{w.fu, w.fv, w.a, nullptr, ff}, s);
-            else launch_gemm(p, EpiSwigluForward<false>{nullptr, nullptr, w.a, nullptr, ff}, s);
+            if (split && bwd) launch_row_gemm(p, EpiSwigluForward<true, true>{w.fu, w.fv, w.a, w.a_lo, ff}, s);
+            else if (split) launch_row_gemm(p, EpiSwigluForward<false, true>{nullptr, nullptr, w.a, w.a_lo, ff}, s);
+            else if (bwd) launch_row_gemm(p, EpiSwigluForward<true>{w.fu, w.fv, w.a, nullptr, ff}, s);
+            else launch_row_gemm(p, EpiSwigluForward<false>{nullptr, nullptr, w.a, nullptr, ff}, s);
         }
         if (!io.composed) {
             StageTimer t(ST_GEMM_DOWN, s);
             GemmProblem p = problem(w.a, ff, w.WdT, ff, Mp, d, ff, kr, kRowsAreM);
             if (split) {                                       // y = [a | a_lo] [Wd; Wd], kept as y + y_lo
                 p.A2 = w.a_lo; p.B2 = w.WdT; p.K2 = ff;
-                launch_gemm(p, EpiStoreBf16Split{w.y, w.y_lo, d, Mp}, s);
+                launch_row_gemm(p, EpiStoreBf16Split{w.y, w.y_lo, d, Mp}, s);
             } else {
-                launch_gemm(p, EpiStoreBf16{w.y, d, Mp}, s);
+                launch_rows_bf16(p, w.y, w.parts, s);
             }
         }
         {
@@ -560,7 +582,7 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                 StageTimer t(ST_GEMM_DY, s);
                 GemmProblem p = problem(w.dz, V, Wo, V, Mp, d, V, lr, kRowsAreM);                                // dy = dz Wo^T
                 p.A_sel = src + LiveSources::kDz;
-                launch_gemm(p, EpiStoreBf16{w.dy, d, Mp}, s);
+                launch_row_gemm(p, EpiStoreBf16{w.dy, d, Mp}, s);
             }
             if (grads) {
                 GemmProblem p = problem(w.y, d, w.dz, V, d, V, Mp, lr, kRowsAreK);                               // dWo (+)= y^T dz
@@ -573,7 +595,7 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
             }
             {
                 StageTimer t(ST_GEMM_DA, s);                                                                     // du, dv from da = dy Wd^T
-                launch_gemm(problem(w.dy, d, Wd, d, Mp, ff, d, lr, kRowsAreM),
+                launch_row_gemm(problem(w.dy, d, Wd, d, Mp, ff, d, lr, kRowsAreM),
                             EpiSwigluBackward<true>{w.fu, w.fv, ff, w.live_idx, w.du, dv}, s);
             }
             if (grads) {
@@ -600,7 +622,7 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                 StageTimer t(ST_GEMM_DX, s);
                 GemmProblem p = problem(w.du, ff, Wg, ff, Mp, d, ff, lr, kRowsAreM);                             // dX = du Wg^T + dv Wu^T
                 p.A2 = dv; p.B2 = Wu; p.K2 = ff;
-                launch_gemm(p, EpiScatterBf16{dX, d, w.live_idx}, s);
+                launch_row_gemm(p, EpiScatterBf16{dX, d, w.live_idx}, s);
             }
             continue;
         }
@@ -618,11 +640,11 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                                    SumsqTarget{}, ST_GEMM_DWO, s);                                                               // dWo = Wd^T G
             }
             StageTimer t(ST_GEMM_DA, s);                                                                          // da = dz W_do^T
-            launch_gemm(problem(w.dz, V, w.Wdo, V, Mp, ff, V, kr, kRowsAreM), EpiSwigluBackward<false>{w.fu, w.fv, ff, nullptr, nullptr, nullptr}, s);
+            launch_row_gemm(problem(w.dz, V, w.Wdo, V, Mp, ff, V, kr, kRowsAreM), EpiSwigluBackward<false>{w.fu, w.fv, ff, nullptr, nullptr, nullptr}, s);
         } else {
             {
                 StageTimer t(ST_GEMM_DY, s);
-                launch_gemm(problem(w.dz, V, Wo, V, Mp, d, V, kr, kRowsAreM), EpiStoreBf16{w.dy, d, Mp}, s);          // dy = dz Wo^T
+                launch_row_gemm(problem(w.dz, V, Wo, V, Mp, d, V, kr, kRowsAreM), EpiStoreBf16{w.dy, d, Mp}, s);          // dy = dz Wo^T
             }
             if (grads) {
                 launch_weight_grad(problem(w.y, d, w.dz, V, d, V, Mp, kr, kRowsAreK), io.dWo, w.parts, !first, sq[3],
@@ -631,7 +653,7 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                                    ST_GEMM_DWD, s);                                                                            // dWd (+)= a^T dy
             }
             StageTimer t(ST_GEMM_DA, s);
-            launch_gemm(problem(w.dy, d, Wd, d, Mp, ff, d, kr, kRowsAreM), EpiSwigluBackward<false>{w.fu, w.fv, ff, nullptr, nullptr, nullptr}, s);   // fu <- du, fv <- dv
+            launch_row_gemm(problem(w.dy, d, Wd, d, Mp, ff, d, kr, kRowsAreM), EpiSwigluBackward<false>{w.fu, w.fv, ff, nullptr, nullptr, nullptr}, s);   // fu <- du, fv <- dv
         }
         if (grads) {
             launch_weight_grad(problem(w.X, d, w.fu, ff, d, ff, Mp, kr, kRowsAreK), io.dWg, w.parts, !first, sq[0],
@@ -644,7 +666,7 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
             GemmProblem p = problem(w.fu, ff, Wg, ff, Mp, d, ff, kr, kRowsAreM);                                 // dX = du Wg^T + dv Wu^T
             p.A2 = w.fv; p.B2 = Wu; p.K2 = ff;
             const int64_t rows_left = sh.rows_max() - row0;
-            launch_gemm(p, EpiStoreBf16{static_cast<bf16*>(io.dX) + row0 * d, d, (int)(rows_left < Mp ? rows_left : Mp)}, s);
+            launch_row_gemm(p, EpiStoreBf16{static_cast<bf16*>(io.dX) + row0 * d, d, (int)(rows_left < Mp ? rows_left : Mp)}, s);
         }
     }
     SumsqLists lists{};

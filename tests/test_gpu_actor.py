@@ -285,6 +285,29 @@ def test_bf16_both_tile_sizes(pcm, d, ff, n_kept, max_kept, composed):
             assert abs(got["grad_sumsq"][0] - sq) <= 1e-6 * sq
 
 
+@pytest.mark.parametrize("d,ff,n_kept,max_kept,chunk_ratio", [
+    (2048, 33024, 5, 9, False),   # 2 x 258 tiles of gate/up: 2 whole rounds, the last four tiles as small ones
+    (2048, 33024, 3, 3, True),    # 1 x 258 tiles, value and remainder of the activation kept
+])
+def test_bf16_last_columns_on_small_tiles_and_split_down(pcm, d, ff, n_kept, max_kept, chunk_ratio):
+    """gate/up with a few tiles beyond whole rounds (its last columns are a launch of their own) and a down projection whose
+    516-step reduction is split; and the same with everything forward only."""
+    cfg = CONFIGS["cfg2"].with_(n_groups=1, G=4, N=4, K=2, B=4, d=d, ff=ff, seed=90 + n_kept)
+    kept = np.arange(0, cfg.T * cfg.N, 3)[:n_kept]
+    pr = make_problem(cfg, wstd=0.02, margin=0.08, kept=kept, old_rel=0.05, eps=(0.2, 0.4))
+    variants = {}
+    if chunk_ratio:
+        from test_gpu_actor_variants import condition_chunks
+        pr = condition_chunks(pr, (0.2, 0.4), 0.02)
+        variants = dict(chunk_ratio=True)
+    ref, got = run_both(pcm, pr, eps=(0.2, 0.4), torch_dtype=torch.bfloat16, max_kept=max_kept, variants=variants)
+    n = len(ref["rows"])
+    check(ref, got, BF16_TOL, n, stats_tol=5e-2)
+    _, fwd = run_both(pcm, pr, eps=(0.2, 0.4), torch_dtype=torch.bfloat16, max_kept=max_kept, variants=variants,
+                      want_grads=False, want_dX=False)
+    assert fwd["loss"][0] == got["loss"][0] and np.array_equal(fwd["logp"][:n], got["logp"][:n])
+
+
 def test_bf16_all_kept_and_forward_only(pcm, composed):
     cfg = CONFIGS["cfg2"].with_(n_groups=1, G=4, N=6, K=3, B=6, d=256, ff=256, seed=13)
     pr = make_problem(cfg, wstd=0.08, margin=0.08, kept=np.arange(cfg.T * cfg.N), old_rel=0.1)
