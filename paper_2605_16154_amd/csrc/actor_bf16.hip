@@ -48,7 +48,10 @@ __device__ inline int packed_row(int c, int mode) {
     return (c / 64) * 128 + (c % 64) + (mode == kPackUp ? 64 : 0);
 }
 
-// dst[map(c), r] = src[r, c] for a [R, C] bf16 matrix (R, C multiples of 64); 64 x 64 tiles.
+// dst[map(c), r] = src[r, c] for a [R, C] bf16 matrix (R, C multiples of 64); 64 x 64 tiles.  kStream: the result is not
+// read again before the memory-side cache has turned over (the four re-layouts of a head of more than 256 MB, kept by the
+// caller: 112 -> 84 us at 272 MB); the stores then leave the cache to the sources.
+template <bool kStream>
 __global__ __launch_bounds__(256) void transpose_bf16(const uint16_t* __restrict__ src, int64_t ld_src,
                                                       uint16_t* __restrict__ dst, int64_t ld_dst, int mode) {
     __shared__ uint16_t tile[64][66];
@@ -70,15 +73,19 @@ __global__ __launch_bounds__(256) void transpose_bf16(const uint16_t* __restrict
         uint2 v;
         v.x = (uint32_t)tile[tv * 4 + 0][c] | ((uint32_t)tile[tv * 4 + 1][c] << 16);
         v.y = (uint32_t)tile[tv * 4 + 2][c] | ((uint32_t)tile[tv * 4 + 3][c] << 16);
-        *reinterpret_cast<uint2*>(dst + (int64_t)packed_row(c0 + c, mode) * ld_dst + r0 + tv * 4) = v;
+        uint16_t* const to = dst + (int64_t)packed_row(c0 + c, mode) * ld_dst + r0 + tv * 4;
+        if (kStream) __builtin_nontemporal_store((uint64_t)v.x | (uint64_t)v.y << 32, reinterpret_cast<uint64_t*>(to));
+        else *reinterpret_cast<uint2*>(to) = v;
     }
 }
 
-void transpose(hipStream_t s, const bf16* src, int R, int C, bf16* dst, int64_t ld_dst, int mode, int stage) {
+void transpose(hipStream_t s, const bf16* src, int R, int C, bf16* dst, int64_t ld_dst, int mode, int stage, bool stream = false) {
     StageTimer t(stage, s);
     dim3 grid(C / 64, R / 64);
-    transpose_bf16<<<grid, 256, 0, s>>>(reinterpret_cast<const uint16_t*>(src), C,
-                                        reinterpret_cast<uint16_t*>(dst), ld_dst, mode);
+    const uint16_t* const from = reinterpret_cast<const uint16_t*>(src);
+    uint16_t* const to = reinterpret_cast<uint16_t*>(dst);
+    if (stream) transpose_bf16<true><<<grid, 256, 0, s>>>(from, C, to, ld_dst, mode);
+    else transpose_bf16<false><<<grid, 256, 0, s>>>(from, C, to, ld_dst, mode);
 }
 
 __global__ void fill_zero_f64(double* p, int n) {
@@ -453,10 +460,11 @@ size_t packed_head_bytes(int d, int ff, int V) { return carve_packed(nullptr, d,
 int pack_head_weights(const void* Wg, const void* Wu, const void* Wd, const void* Wo, int d, int ff, int V, void* packed,
                       hipStream_t s) {
     const PackedHead p = carve_packed(packed, d, ff, V);
-    transpose(s, static_cast<const bf16*>(Wg), d, ff, p.WguT, d, kPackGate, ST_WEIGHT_LAYOUT);
-    transpose(s, static_cast<const bf16*>(Wu), d, ff, p.WguT, d, kPackUp, ST_WEIGHT_LAYOUT);
-    transpose(s, static_cast<const bf16*>(Wd), ff, d, p.WdT, ff, kPackNone, ST_WEIGHT_LAYOUT);
-    transpose(s, static_cast<const bf16*>(Wo), d, V, p.WoT, d, kPackNone, ST_WEIGHT_LAYOUT);
+    const bool stream = p.bytes > (size_t)256 << 20;
+    transpose(s, static_cast<const bf16*>(Wg), d, ff, p.WguT, d, kPackGate, ST_WEIGHT_LAYOUT, stream);
+    transpose(s, static_cast<const bf16*>(Wu), d, ff, p.WguT, d, kPackUp, ST_WEIGHT_LAYOUT, stream);
+    transpose(s, static_cast<const bf16*>(Wd), ff, d, p.WdT, ff, kPackNone, ST_WEIGHT_LAYOUT, stream);
+    transpose(s, static_cast<const bf16*>(Wo), d, V, p.WoT, d, kPackNone, ST_WEIGHT_LAYOUT, stream);
     return launch_status();
 }
 

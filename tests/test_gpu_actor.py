@@ -670,3 +670,16 @@ def test_fp32_tiles_steps_and_edges(pcm, d, ff, V, A_dims, n_kept, max_kept, com
     ref, got = run_both(pcm, pr, eps=(0.2, 0.4), max_kept=max_kept, composed_head=composed)
     check(ref, got, 1e-5, len(ref["rows"]))
     assert not got["dX"][len(ref["rows"]):].any()
+
+
+@pytest.mark.parametrize("d,ff", [(256, 512), (4096, 11008)])      # the larger one's 272 MB are stored past the caches
+def test_packed_head_weights_are_the_transposes(pcm, d, ff):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    rand = lambda *s: torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16)
+    Wg, Wu, Wd, Wo = rand(d, ff), rand(d, ff), rand(ff, d), rand(d, 256)
+    packed = pcm.pcm_pack_head_weights(Wg, Wu, Wd, Wo).view(torch.bfloat16)
+    gate_up = packed[:2 * ff * d].view(ff // 64, 2, 64, d)
+    assert torch.equal(gate_up[:, 0].reshape(ff, d), Wg.t()) and torch.equal(gate_up[:, 1].reshape(ff, d), Wu.t())
+    assert torch.equal(packed[2 * ff * d:3 * ff * d].view(d, ff), Wd.t())
+    assert torch.equal(packed[3 * ff * d:3 * ff * d + 256 * d].view(256, d), Wo.t())

@@ -152,3 +152,10 @@ def test_bad_arguments_are_rejected():
         pcm.pcm_adamw_clip_step(x, x, x, x, 1, beta1=1.0)
     with pytest.raises(pcm.PcmError):
         pcm.pcm_adamw_clip_step(x * 9, x * 9, x * 9, x * 9, 1)      # more than PCM_MAX_OPT_TENSORS
+
+
+@pytest.mark.parametrize("extra", [-1, 3])
+def test_both_sides_of_the_streaming_line(extra):
+    # up to 20 Mi elements the state is accessed through the caches, beyond with non-temporal accesses; a ragged second tensor
+    w, g, m, v = _case(9, ((20 * 2 ** 20 - 4097 + extra,), (4098,)), 1e-3)
+    _check(w, g, m, v, 5)
