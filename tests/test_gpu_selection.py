@@ -305,6 +305,7 @@ def test_sampler_and_counts_at_the_edges_of_slots_per_lane(pcm, N):
     (1, 1, 3, 4, 2),        # a group of one: nothing to compare
     (2, 65, 5, 8, 3),       # more rollouts than lanes in a wavefront
     (300, 2, 4, 4, 5),      # more pair scores than fit in LDS at once, one chunk per workgroup
+    (300, 3, 6, 2, 17),     # more pair scores than a workgroup's threads hold at once, LDS blocks that do not divide them
     (3, 8, 256, 3, 64),     # the most phases, single-float loads, several slices per trajectory
     (2, 4, 1100, 56, 12),   # more chunks per workgroup than are under way together
 ])
