@@ -23,7 +23,7 @@ if ROOT not in sys.path:
 import numpy as np
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0      # MI355X dense bf16 matrix peak
-ALU_FP32_PEAK_TFLOPS = 157.3
+FP32_PEAK_TFLOPS = 157.3
 HBM_PEAK_GBPS = 8000.0              # MI355X HBM3E peak
 GEMM_STAGES = ("gemm_gate_up", "gemm_down", "gemm_logits_loss", "gemm_dWo", "gemm_dy", "gemm_dWd", "gemm_da",
                "gemm_dWg_dWu", "gemm_dX")
@@ -509,12 +509,12 @@ def main():
                                        "ms_per_step": gemm_ms_step, "rows_forward": rows, "rows_backward_mean": rows_bwd,
                                        "tflops_if_all_rows_counted": total_flops_step / (gemm_ms_step * 1e-3) / 1e12}}
     else:
-        # fp32 correctness configuration: plain vector-ALU products (forward and backward stages of the fp32 path),
-        # against the fp32 vector peak 256 CU x 4 SIMD x 64 lanes x 2 flop x 2.4 GHz
+        # fp32 configuration: products on fp32 matrix cores (forward and backward stages of the fp32 path), against their
+        # peak, which is that of the vector ALUs: 256 CU x 4 SIMD x 64 lanes x 2 flop x 2.4 GHz
         alu_ms_step = (stages["f32_forward"][0] + stages["f32_backward"][0]) / stage_steps
         achieved = total_flops_step / (alu_ms_step * 1e-3) / 1e12
-        roofline = {"bound": "alu", "kernel": "sgemm (fp32 path, forward + backward)", "achieved": achieved,
-                    "peak": ALU_FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / ALU_FP32_PEAK_TFLOPS,
+        roofline = {"bound": "mfma", "kernel": "gemm_f32 (fp32 path, forward + backward)", "achieved": achieved,
+                    "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / FP32_PEAK_TFLOPS,
                     "traffic": None, "flops_per_step": total_flops_step, "ms_per_step": alu_ms_step}
 
     result = {"metric": "kept_action_tokens_per_sec_masked_grpo_actor_step", "value": value, "unit": "tokens/s",
