@@ -311,7 +311,7 @@ def test_sampler_and_counts_at_the_edges_of_slots_per_lane(pcm, N):
 ])
 def test_score_in_two_launches(pcm, n_groups, G, N, A, K):
     """The last workgroup of a group forms its pair scores, the last group the mean: called again and again on one
-    workspace, with other rewards in between, every call gives the checker's bits."""
+    workspace, with other rewards in between, every call gives the oracle's bits."""
     rng = np.random.default_rng(n_groups + N)
     T = n_groups * G
     actions = rng.uniform(-1, 1, size=(T, N, A)).astype(np.float32)
