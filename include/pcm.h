@@ -145,7 +145,9 @@ PCM_API int pcm_score_phases(const float* actions, const uint8_t* phase, const u
  * shape exceeds PCM_SCORE_STATIC_MAX_BYTES (about n_groups * K * A * 16 bytes: the paper-sized
  * batch needs 0.07 MB, 64 groups of 12 phases 0.7 MB).
  * All calls on one GPU share that GPU's array: two calls that may overlap (different streams
- * without an ordering between them, or different host threads) race; order them.
+ * without an ordering between them, or different host threads) race; order them.  The array holds
+ * the counters by which the last workgroups know that they are the last: overlapping calls can leave
+ * C_out and valid_out unwritten, that is with what the caller's buffers held before.
  * ------------------------------------------------------------------------------------------ */
 #define PCM_SCORE_STATIC_MAX_BYTES (4u << 20)   /* 4 MiB */
 PCM_API int pcm_score_phases_static(const float* actions, const uint8_t* phase, const uint8_t* reward,

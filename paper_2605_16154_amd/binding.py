@@ -110,18 +110,38 @@ def _stream() -> int:
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
-_workspaces: Dict[torch.device, torch.Tensor] = {}
+# Scratch of the calls, kept from one to the next by device and stream: calls that share scratch have to be ordered on one
+# stream.  A call takes its tensor out of the table while it enqueues its launches, so that threads that issue to one stream
+# at the same time have one each.  The table is bounded; a tensor that leaves it goes back to the caching allocator, which
+# hands it out on the same stream only.  Scratch used under graph capture stays for good: the graph holds its address.
+# (Plain dict operations, each atomic: a lock or a context manager costs a microsecond of the ten that a small call takes.)
+_KEPT_WORKSPACES = 8
+_workspaces: Dict[Tuple[Optional[int], int], torch.Tensor] = {}     # the one used longest ago first
+_captured_workspaces: Dict[int, torch.Tensor] = {}
 
 
-def _workspace(nbytes: int, device) -> Tuple[Optional[int], int]:
-    """One growing scratch tensor per device, shared by all calls (they are stream-ordered)."""
-    if nbytes == 0:
-        return None, 0
-    dev = torch.device(device)
-    ws = _workspaces.get(dev)
+def _take_workspace(nbytes: int, device: torch.device, stream: int) -> torch.Tensor:
+    """At least `nbytes` of scratch for one call on `stream`, to be handed to _give_workspace once it is enqueued."""
+    ws = _workspaces.pop((device.index, stream), None)
     if ws is None or ws.numel() < nbytes:
-        _workspaces[dev] = ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
-    return ws.data_ptr(), ws.numel()
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    return ws
+
+
+def _give_workspace(ws: torch.Tensor, device: torch.device, stream: int) -> None:
+    if _capturing():
+        _captured_workspaces[id(ws)] = ws
+    key = (device.index, stream)
+    kept = _workspaces.get(key)
+    if kept is None or kept.numel() < ws.numel():
+        _workspaces[key] = ws
+    if len(_workspaces) > _KEPT_WORKSPACES:
+        for oldest in list(_workspaces)[:-_KEPT_WORKSPACES]:
+            _workspaces.pop(oldest, None)
+
+
+def _capturing() -> bool:
+    return torch.cuda.is_current_stream_capturing()
 
 
 def pcm_version() -> str:
@@ -178,8 +198,12 @@ def pcm_score_phases(actions, phase, reward, n_chunks, n_groups: int, G: int, K:
         _check(lib().pcm_score_phases_static(*args, _stream()), "pcm_score_phases_static")
         return out
     need = lib().pcm_score_phases_workspace_bytes(n_groups, G, N, A, K)
-    ws, ws_bytes = _workspace(need, dev)
-    _check(lib().pcm_score_phases(*args, ws, ws_bytes, _stream()), "pcm_score_phases")
+    stream = _stream()
+    ws = _take_workspace(need, dev, stream)
+    try:
+        _check(lib().pcm_score_phases(*args, ws.data_ptr(), ws.numel(), stream), "pcm_score_phases")
+    finally:
+        _give_workspace(ws, dev, stream)
     return out
 
 
@@ -212,12 +236,11 @@ def pcm_sample_chunks(keep_probs, phase, n_chunks, active, B: int, seed: int, st
         out = (torch.empty(T * min(B, N), dtype=torch.int32, device=dev),
                torch.empty(T + 1, dtype=torch.int32, device=dev), torch.empty(1, dtype=torch.int32, device=dev))
     kept_idx, kept_offsets, n_kept = out
-    need = lib().pcm_sample_chunks_workspace_bytes(T, N, K, B)
-    ws, ws_bytes = _workspace(need, dev)
     head = (_ptr(keep_probs, torch.float64, "keep_probs"), _ptr(phase, torch.uint8, "phase"),
             _ptr(n_chunks, torch.int32, "n_chunks"), _ptr(active, torch.uint8, "active"), T, N, K, B)
     tail = (seed & 0xFFFFFFFFFFFFFFFF, step & 0xFFFFFFFFFFFFFFFF, _ptr(kept_idx, torch.int32, "kept_idx"),
-            _ptr(kept_offsets, torch.int32, "kept_offsets"), _ptr(n_kept, torch.int32, "n_kept"), ws, ws_bytes, _stream())
+            _ptr(kept_offsets, torch.int32, "kept_offsets"), _ptr(n_kept, torch.int32, "n_kept"),
+            None, 0, _stream())                                       # no workspace: none is needed
     if selector == "pcm":
         _check(lib().pcm_sample_chunks(*head, *tail), "pcm_sample_chunks")
     else:
@@ -348,20 +371,23 @@ def grpo_masked_actor_step(hidden, tokens, logp_old, adv, kept_idx, n_kept, T: i
         need = grpo_masked_actor_step_workspace_bytes(max_kept_chunks, A, d, ff, V, dtype, want_grads or want_dX)
     if need == 0:
         raise PcmError("grpo_masked_actor_step: unsupported shape or dtype for this path")
-    ws, ws_bytes = _workspace(need, dev)
+    stream = _stream()
     head = (_ptr(hidden, None, "hidden"), _ptr(tokens, torch.uint8, "tokens"), _ptr(logp_old, torch.float32, "logp_old"),
             _ptr(adv, torch.float32, "adv"), _ptr(kept_idx, torch.int32, "kept_idx"), _ptr(n_kept, torch.int32, "n_kept"),
             max_kept_chunks, T, N, A, d, ff, V, dtype, _ptr(Wg, None, "Wg"), _ptr(Wu, None, "Wu"), _ptr(Wd, None, "Wd"),
             _ptr(Wo, None, "Wo"))
     tail = (_ptr(loss, torch.float32, "loss"), _ptr(logp, torch.float32, "logp"),
-            *[_ptr(g, torch.float32, "dW") for g in grads], _ptr(dX, None, "dX"), _ptr(stats, torch.float32, "stats"),
-            ws, ws_bytes, _stream())
-    if extended:
-        rc = lib().grpo_masked_actor_step_ex(*head, C.byref(opt), *tail)
-        _check(rc, "grpo_masked_actor_step_ex")
-    else:
-        rc = lib().grpo_masked_actor_step(*head, eps_low, eps_high, loss_scale, *tail)
-        _check(rc, "grpo_masked_actor_step")
+            *[_ptr(g, torch.float32, "dW") for g in grads], _ptr(dX, None, "dX"), _ptr(stats, torch.float32, "stats"))
+    ws = _take_workspace(need, dev, stream)
+    try:
+        if extended:
+            rc = lib().grpo_masked_actor_step_ex(*head, C.byref(opt), *tail, ws.data_ptr(), ws.numel(), stream)
+            _check(rc, "grpo_masked_actor_step_ex")
+        else:
+            rc = lib().grpo_masked_actor_step(*head, eps_low, eps_high, loss_scale, *tail, ws.data_ptr(), ws.numel(), stream)
+            _check(rc, "grpo_masked_actor_step")
+    finally:
+        _give_workspace(ws, dev, stream)
     return out
 
 
@@ -395,16 +421,21 @@ def pcm_adamw_clip_step(grads, weights, m, v, step: int, lr: float = 1e-5, beta1
     need = lib().pcm_adamw_clip_step_workspace_bytes(n, numel)
     if need == 0:
         raise PcmError("pcm_adamw_clip_step: bad tensor list")
-    ws, ws_bytes = _workspace(need, dev)
+    stream = _stream()
     head = (n, numel, arr(grads, torch.float32, "grads"), arr(weights, torch.float32, "weights"),
             arr(m, torch.float32, "m"), arr(v, torch.float32, "v"), lowp, step, lr, beta1, beta2, eps, weight_decay,
             max_grad_norm)
-    tail = (_ptr(grad_norm_out, torch.float32, "norm"), ws, ws_bytes, _stream())
-    if grad_sumsq is not None:
-        rc = lib().pcm_adamw_clip_step_ex(*head, _ptr(grad_sumsq, torch.float64, "grad_sumsq"), *tail)
-    else:
-        rc = lib().pcm_adamw_clip_step(*head, *tail)
-    _check(rc, "pcm_adamw_clip_step")
+    norm = _ptr(grad_norm_out, torch.float32, "norm")
+    sumsq = _ptr(grad_sumsq, torch.float64, "grad_sumsq")
+    ws = _take_workspace(need, dev, stream)
+    try:
+        if grad_sumsq is not None:
+            rc = lib().pcm_adamw_clip_step_ex(*head, sumsq, norm, ws.data_ptr(), ws.numel(), stream)
+        else:
+            rc = lib().pcm_adamw_clip_step(*head, norm, ws.data_ptr(), ws.numel(), stream)
+        _check(rc, "pcm_adamw_clip_step")
+    finally:
+        _give_workspace(ws, dev, stream)
     return grad_norm_out
 
 

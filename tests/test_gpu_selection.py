@@ -326,3 +326,48 @@ def test_score_in_two_launches(pcm, n_groups, G, N, A, K):
         assert np.array_equal(bits(C.cpu().numpy()), bits(C_o)) and np.array_equal(valid.cpu().numpy(), valid_o), trip
         assert np.array_equal(act.cpu().numpy(), act_o)
         assert np.array_equal(adv.cpu().numpy().view(np.int32), adv_o.astype(np.float32).view(np.int32))
+
+
+def test_scores_of_streams_and_threads_that_overlap(pcm):
+    """Four host threads on two streams, calls that nothing orders: every call gives the oracle's bits (the counters by
+    which the last workgroups know that they are the last are in scratch, so calls that overlap must not share it)."""
+    import threading
+
+    n_groups, G, N, A, K, calls = 8, 6, 96, 24, 9, 40
+    T = n_groups * G
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    work = []
+    for i in range(4):
+        rng = np.random.default_rng(100 + i)
+        actions = rng.uniform(-1, 1, size=(T, N, A)).astype(np.float32)
+        phase = np.sort(rng.integers(0, K, size=(T, N)), axis=1).astype(np.uint8)
+        reward = (rng.random(T) < 0.5).astype(np.uint8)
+        n_chunks = rng.integers(1, N + 1, size=T).astype(np.int32)
+        d = torch.device("cuda:0")
+        outs = [(torch.full((K,), -7.0, dtype=torch.float64, device=d), torch.full((K,), 9, dtype=torch.uint8, device=d),
+                 torch.zeros(T, device=d), torch.zeros(T, dtype=torch.uint8, device=d)) for _ in range(calls)]
+        work.append((O.phase_scores(actions, phase, reward, n_chunks, n_groups, G, K),
+                     (dev(actions), dev(phase), dev(reward), dev(n_chunks)), outs))
+    torch.cuda.synchronize()
+    start, failed = threading.Barrier(4, timeout=60), []
+
+    def run(i):
+        try:
+            torch.cuda.set_device(0)
+            start.wait()
+            with torch.cuda.stream(streams[i % 2]):
+                for out in work[i][2]:
+                    pcm.pcm_score_phases(*work[i][1], n_groups, G, K, 1e-6, out=out)
+        except Exception as e:      # noqa: BLE001  (told to the main thread)
+            failed.append(e)
+
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed, failed
+    for (C_o, valid_o), _, outs in work:
+        for C, valid, _, _ in outs:
+            assert np.array_equal(bits(C.cpu().numpy()), bits(C_o)) and np.array_equal(valid.cpu().numpy(), valid_o)
