@@ -349,8 +349,9 @@ namespace {
 int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward, const int32_t* n_chunks,
               int n_groups, int G, int N, int A, int K, double adv_eps, double* C_out, uint8_t* valid_out,
               float* adv_out, uint8_t* active_out, const ScoreWorkspace& w, hipStream_t s) {
-    // phases per workgroup: all K if their sums fit in 64 KB of LDS (A <= 256: at least 31 do)
-    int Kb = (int)((size_t)64 * 1024 / ((size_t)A * sizeof(ull) + sizeof(int)));
+    // phases per workgroup: all K if their sums fit in the 64 KB of LDS that a workgroup may take by default, less the word
+    // of arrive_last with its padding (A <= 256: at least 31 do)
+    int Kb = (int)(((size_t)64 * 1024 - 16) / ((size_t)A * sizeof(ull) + sizeof(int)));
     if (Kb > K) Kb = K;
     const int phase_blocks = ceil_div(K, Kb);
     size_t lds_bytes = (size_t)Kb * A * sizeof(ull) + (size_t)Kb * sizeof(int);
