@@ -38,6 +38,7 @@ inline bool workspace_ok(const void* ws, size_t have, size_t need) {
 enum Stage : int {
     ST_SCORE_PREPARE = 0,
     ST_SCORE_ACCUMULATE,
+    ST_SCORE_FINALISE,
     ST_KEEP_PROBS,
     ST_SAMPLE_SCAN,
     ST_SAMPLE_COMPACT,

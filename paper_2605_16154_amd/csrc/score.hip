@@ -1,6 +1,6 @@
 // pcm_score_phases: group-relative advantages (Eq. 1) and the batch phase score C_c (Eq. 5).
 //
-// Two launches on the caller's stream (four launches of 2 - 3 us of work each were bound by the launches themselves):
+// Two launches on the caller's stream, four where the work behind the accumulation is long (see fuses_tail):
 //   prepare     zero the integer accumulators and the arrival counters; one thread per trajectory writes
 //               advantage/active
 //   accumulate  streaming pass over the action tensor: every workgroup owns a slice of one
@@ -10,6 +10,7 @@
 //               in index order by one lane per phase, square root); the last group to arrive forms the mean of the pair
 //               scores over contributing groups, one lane per phase.  Nobody waits for anybody: a workgroup that is not
 //               the last one leaves.
+//   pairs, mean   the same two steps as launches of their own: a wavefront per (group, phase), then one workgroup
 //
 // The action pass is bandwidth-bound (224 B per chunk plus one phase byte); everything after it
 // touches a few KB.  Integer accumulation makes the sums independent of slice and arrival order,
@@ -163,9 +164,11 @@ __device__ inline void accumulate_slice(const float* __restrict__ actions, const
             ActionVec<VEC> x[kAhead];
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
-                const int k = min(kb0 + u * CPI, k1 - 1);
-                ph_id[u] = ph[k];
-                x[u].load(row + (size_t)k * A);
+                const int k = kb0 + u * CPI;
+                if (k < k1) {
+                    ph_id[u] = ph[k];
+                    x[u].load(row + (size_t)k * A);
+                }
             }
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
@@ -196,8 +199,20 @@ __device__ inline void accumulate_slice(const float* __restrict__ actions, const
         if (lds_cnt[c] > 0) add_shared(&counts[base + c], lds_cnt[c]);
 }
 
-// Pair scores of group g for all phases, `block` phases at a time (as many as the squared terms in LDS allow).
-__device__ inline void score_pairs(int g, int A, int K, int block, const ull* sums, const int* counts, double* lds, double* pair) {
+__device__ inline double squared_difference(ull s_pos, int n_pos, ull s_neg, int n_neg) {
+    const double mp = (double)(long long)s_pos / (double)n_pos;
+    const double mn = (double)(long long)s_neg / (double)n_neg;
+    const double diff = mp - mn;
+    return diff * diff;
+}
+
+// Pair scores of group g for all phases by one workgroup, as many phases at a time as LDS holds.  Their rows of squared
+// terms are an odd number of doubles apart: a lane adds up a row, and with 256 between them all lanes met in one bank
+// (64 phases of 256 values: 41 -> 32 us).
+__host__ __device__ inline int pair_row(int A) { return A | 1; }
+__device__ inline void score_pairs_of_group(int g, int A, int K, const ull* sums, const int* counts, double* lds, int lds_entries,
+                                            double* pair) {
+    const int row = pair_row(A), block = min(K, lds_entries / row);
     for (int c0 = 0; c0 < K; c0 += block) {
         const int kb = min(block, K - c0);
         const size_t pos = ((size_t)g * 2 + 1) * K + c0, neg = ((size_t)g * 2 + 0) * K + c0;
@@ -205,25 +220,22 @@ __device__ inline void score_pairs(int g, int A, int K, int block, const ull* su
         const int my_c = threadIdx.x < kb ? threadIdx.x : 0;      // the phase this thread adds up (kb <= 64)
         const int my_pos = load_shared(&counts[pos + my_c]), my_neg = load_shared(&counts[neg + my_c]);
         for (int e0 = threadIdx.x; e0 < kb * A; e0 += 4 * kThreads) {
-            int n_pos[4], n_neg[4];                               // all loads of four terms under way together
+            int c[4], n_pos[4], n_neg[4];                         // all loads of four terms under way together
             ull s_pos[4], s_neg[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int e = min(e0 + u * kThreads, kb * A - 1), c = e / A;
-                n_pos[u] = load_shared(&counts[pos + c]);
-                n_neg[u] = load_shared(&counts[neg + c]);
+                const int e = min(e0 + u * kThreads, kb * A - 1);
+                c[u] = e / A;
+                n_pos[u] = load_shared(&counts[pos + c[u]]);
+                n_neg[u] = load_shared(&counts[neg + c[u]]);
                 s_pos[u] = load_shared(&sums[pos * A + e]);
                 s_neg[u] = load_shared(&sums[neg * A + e]);
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int e = e0 + u * kThreads;
-                if (e < kb * A && n_pos[u] > 0 && n_neg[u] > 0) {
-                    const double mp = (double)(long long)s_pos[u] / (double)n_pos[u];
-                    const double mn = (double)(long long)s_neg[u] / (double)n_neg[u];
-                    const double diff = mp - mn;
-                    lds[e] = diff * diff;
-                }
+                if (e < kb * A && n_pos[u] > 0 && n_neg[u] > 0)
+                    lds[c[u] * (row - A) + e] = squared_difference(s_pos[u], n_pos[u], s_neg[u], n_neg[u]);
             }
         }
         __syncthreads();
@@ -233,7 +245,7 @@ __device__ inline void score_pairs(int g, int A, int K, int block, const ull* su
             if (my_pos > 0 && my_neg > 0) {
                 double acc = 0.0;
 #pragma unroll 8
-                for (int j = 0; j < A; ++j) acc = acc + lds[c * A + j];
+                for (int j = 0; j < A; ++j) acc = acc + lds[c * row + j];
                 score = sqrt(acc) * kActionUnscale;
             }
             store_shared(&pair[(size_t)g * K + c0 + c], score);
@@ -241,12 +253,40 @@ __device__ inline void score_pairs(int g, int A, int K, int block, const ull* su
     }
 }
 
+// The same as a launch of its own: one wavefront per (group, phase).  All threads reach the barrier.
+__global__ __launch_bounds__(kThreads) void score_pairs(const ull* __restrict__ sums, const int* __restrict__ counts, int n_groups,
+                                                        int A, int K, double* pair) {
+    __shared__ double sq[kThreads / kWave][256];
+    const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int w = blockIdx.x * (kThreads / kWave) + wv;
+    const int at = min(w, n_groups * K - 1), g = at / K, c = at % K;
+    const size_t pos = ((size_t)g * 2 + 1) * K + c, neg = ((size_t)g * 2 + 0) * K + c;
+    const int n_pos = counts[pos], n_neg = counts[neg];
+    const bool ok = n_pos > 0 && n_neg > 0;
+    if (ok)
+        for (int j = lane; j < A; j += kWave) sq[wv][j] = squared_difference(sums[pos * A + j], n_pos, sums[neg * A + j], n_neg);
+    __syncthreads();
+    if (w < n_groups * K && lane == 0) {
+        double score = -1.0;
+        if (ok) {
+            double acc = 0.0;
+#pragma unroll 8
+            for (int j = 0; j < A; ++j) acc = acc + sq[wv][j];
+            score = sqrt(acc) * kActionUnscale;
+        }
+        pair[w] = score;
+    }
+}
+
 // Batch score of phase c = mean over the groups that contributed, added for g ascending (the order is
 // part of the definition: the result must not depend on the launch).  One workgroup: the per-group values
-// are brought into LDS a block of groups at a time with coalesced loads, then lane c adds its column in order.
-__device__ inline void score_mean(const double* pair, int n_groups, int K, double* lds, int lds_entries, double* C_out,
-                                  uint8_t* valid_out) {
-    const int c = threadIdx.x;
+// are brought into LDS a block of groups at a time with coalesced loads, then lane c of the first wavefront adds its
+// column in order while lane c of the second counts the groups in it.
+template <int kBlock, class Load>
+__device__ inline void mean_of_groups(const double* pair, int n_groups, int K, double* lds, int lds_entries, double* C_out,
+                                      uint8_t* valid_out, Load load) {
+    __shared__ int contributing[PCM_MAX_PHASES];
+    const int c = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const int block_groups = lds_entries / K;
     double tot = 0.0;
     int n = 0;
@@ -254,40 +294,50 @@ __device__ inline void score_mean(const double* pair, int n_groups, int K, doubl
         const int groups = min(block_groups, n_groups - g0);
         __syncthreads();
         // eight loads per thread in flight before the first is stored
-        for (int i0 = threadIdx.x; i0 < groups * K; i0 += 8 * kThreads) {
+        for (int i0 = threadIdx.x; i0 < groups * K; i0 += 8 * kBlock) {
             double v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u * kThreads;
-                v[u] = i < groups * K ? load_shared(&pair[(size_t)g0 * K + i]) : 0.0;
+                const int i = i0 + u * kBlock;
+                v[u] = i < groups * K ? load(&pair[(size_t)g0 * K + i]) : 0.0;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (i0 + u * kThreads < groups * K) lds[i0 + u * kThreads] = v[u];
+                if (i0 + u * kBlock < groups * K) lds[i0 + u * kBlock] = v[u];
         }
         __syncthreads();
-        if (c < K) {
-            // branch-free, so that the LDS reads run ahead of the additions, which stay in group order; a skipped pair
-            // adds +0.0, which leaves the non-negative sum as it is
+        if (c < K && wave == 0) {
+            // the additions stay in group order; a skipped pair adds +0.0, which leaves the non-negative sum as it is
 #pragma unroll 8
-            for (int g = 0; g < groups; ++g) {
-                const double v = lds[g * K + c];
-                tot = tot + (v >= 0.0 ? v : 0.0);
-                n += v >= 0.0 ? 1 : 0;
-            }
+            for (int g = 0; g < groups; ++g) tot = tot + fmax(lds[g * K + c], 0.0);
+        } else if (c < K && wave == 1) {
+#pragma unroll 8
+            for (int g = 0; g < groups; ++g) n += lds[g * K + c] >= 0.0 ? 1 : 0;
         }
     }
-    if (c < K) {
+    if (c < K && wave == 1) contributing[c] = n;
+    __syncthreads();
+    if (c < K && wave == 0) {
+        n = contributing[c];
         C_out[c] = n > 0 ? tot / (double)n : 0.0;
         valid_out[c] = n > 0 ? 1 : 0;
     }
 }
 
+// The mean as a launch of its own.  Bound by the loads of a block and by the additions behind them; with 1024 threads
+// instead of 256 a block is one round of loads (4096 groups of 64 phases: 284 -> 233 us for all four launches).
+constexpr int kMeanThreads = 1024, kMeanEntries = 4096;
+__global__ __launch_bounds__(kMeanThreads) void score_mean(const double* __restrict__ pair, int n_groups, int K, double* C_out,
+                                                       uint8_t* valid_out) {
+    __shared__ double val[kMeanEntries];
+    mean_of_groups<kMeanThreads>(pair, n_groups, K, val, kMeanEntries, C_out, valid_out, [](const double* p) { return *p; });
+}
+
 // grid = T * slices * phase_blocks workgroups; a workgroup pools the phases [c0, c0 + Kb) of its
 // chunks (phase_blocks is 1 unless K*A sums do not fit in LDS; then the chunks are read once per
-// block of phases).  LDS: Kb*A 64-bit sums followed by Kb chunk counts, indexed by phase - c0; afterwards the squared
-// terms of a group's pairs, then the pair scores.
-template <int VEC>
+// block of phases).  LDS: Kb*A 64-bit sums followed by Kb chunk counts, indexed by phase - c0; with kTail afterwards the
+// squared terms of a group's pairs, then the pair scores.
+template <int VEC, bool kTail>
 __global__ __launch_bounds__(kThreads) void score_accumulate(
     const float* __restrict__ actions, const uint8_t* __restrict__ phase,
     const uint8_t* __restrict__ reward, const int32_t* __restrict__ n_chunks, int n_groups, int G, int N, int A,
@@ -314,10 +364,26 @@ __global__ __launch_bounds__(kThreads) void score_accumulate(
             accumulate_slice<VEC>(actions, phase, i, g, reward[i] != 0, k0, k1, N, A, K, c0, kb, lds_sum,
                                   reinterpret_cast<int*>(lds_sum + (size_t)Kb * A), w.sums, w.counts);
     }
-    if (!arrive_last(reinterpret_cast<int*>(w.pair + (size_t)g * K), G * slices * phase_blocks)) return;
-    score_pairs(g, A, K, Kb, w.sums, w.counts, reinterpret_cast<double*>(lds_sum), w.pair);
-    if (!arrive_last(w.groups_done, n_groups)) return;
-    score_mean(w.pair, n_groups, K, reinterpret_cast<double*>(lds_sum), lds_entries, C_out, valid_out);
+    if (kTail) {
+        double* const lds = reinterpret_cast<double*>(lds_sum);
+        if (!arrive_last(reinterpret_cast<int*>(w.pair + (size_t)g * K), G * slices * phase_blocks)) return;
+        score_pairs_of_group(g, A, K, w.sums, w.counts, lds, lds_entries, w.pair);
+        if (!arrive_last(w.groups_done, n_groups)) return;
+        mean_of_groups<kThreads>(w.pair, n_groups, K, lds, lds_entries, C_out, valid_out, [](const double* p) { return load_shared(p); });
+    }
+}
+
+// Whether pair scores and mean are formed behind the accumulation (two launches in all) or by launches of their own (four).
+// Two launches save about 5 us, which count while the calls are bound by issuing them.  Behind the accumulation a group's
+// pair scores are the work of one workgroup and the mean waits for loads past the L2 caches, and every workgroup pays for
+// arriving.  Measured per call, two / four launches, the other bound held:
+//   by the pair terms of a group, one group:  12 phases of 56 values 12.8 / 17.4 us; 24 of 128 (3072 terms) 15.2 / 17.3,
+//   33 of 128 (4224) 16.8 / 17.4, 24 of 256 (6144) 20.3 / 18.7, 64 of 256 34.7 / 19.9
+//   by those of all groups:  32 groups of 5 x 56 (8960) 14.0 / 14.8 us, 8 of 24 x 128 (24576) 15.7 / 16.9, 8 of 33 x 128
+//   (33792) 17.2 / 17.5, 64 of 12 x 56 (43008, 256 chunks each) 19.3 / 18.6, 256 of 12 x 56 29.3 / 26.5, 1024 of 12 x 56
+//   85.6 / 75.5
+bool fuses_tail(int n_groups, int A, int K) {
+    return K * A <= 4096 && (int64_t)n_groups * K * A <= 32768;
 }
 
 bool shape_ok(int n_groups, int G, int N, int A, int K) {
@@ -344,20 +410,25 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
 
-// Argument checks and the two launches shared by both entry points; `workspace` has been checked
+// The launches shared by both entry points; `workspace` has been checked
 // to hold carve(...).bytes.
 int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward, const int32_t* n_chunks,
               int n_groups, int G, int N, int A, int K, double adv_eps, double* C_out, uint8_t* valid_out,
               float* adv_out, uint8_t* active_out, const ScoreWorkspace& w, hipStream_t s) {
     // phases per workgroup: all K if their sums fit in the 64 KB of LDS that a workgroup may take by default, less the word
     // of arrive_last with its padding (A <= 256: at least 31 do)
-    int Kb = (int)(((size_t)64 * 1024 - 16) / ((size_t)A * sizeof(ull) + sizeof(int)));
+    constexpr size_t kLdsMax = 64 * 1024 - 16;
+    int Kb = (int)(kLdsMax / ((size_t)A * sizeof(ull) + sizeof(int)));
     if (Kb > K) Kb = K;
     const int phase_blocks = ceil_div(K, Kb);
     size_t lds_bytes = (size_t)Kb * A * sizeof(ull) + (size_t)Kb * sizeof(int);
-    // all pair scores, but no more than lets eight workgroups share a CU (a group's scores fit, whatever K): the mean waits
-    // for loads once per block of groups that fits here (1024 groups of 12 phases: 119.7 -> 114.8 us in all)
-    lds_bytes = std::max(lds_bytes, std::min((size_t)n_groups * K * sizeof(double), (size_t)16 * 1024));
+    const bool tail = fuses_tail(n_groups, A, K);
+    if (tail) {
+        // all pair scores, but no more than lets eight workgroups share a CU (a group's scores fit, whatever K): the mean
+        // waits for loads once per block of groups that fits here; and all rows of squared terms
+        lds_bytes = std::max(lds_bytes, std::min((size_t)n_groups * K * sizeof(double), (size_t)16 * 1024));
+        lds_bytes = std::max(lds_bytes, std::min((size_t)K * pair_row(A) * sizeof(double), kLdsMax));
+    }
     const int lds_entries = (int)(lds_bytes / sizeof(double));
     const int T = n_groups * G;
     {
@@ -378,12 +449,19 @@ int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward,
         if (slices > max_slices) slices = max_slices;
         if (slices < 1) slices = 1;
         const unsigned grid = (unsigned)T * (unsigned)slices * (unsigned)phase_blocks;
-        if (vec4)
-            score_accumulate<4><<<grid, kThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, n_groups, G, N, A, K, Kb,
-                                                                slices, lds_entries, w, C_out, valid_out);
-        else
-            score_accumulate<1><<<grid, kThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, n_groups, G, N, A, K, Kb,
-                                                                slices, lds_entries, w, C_out, valid_out);
+#define PCM_ACCUMULATE(VEC, TAIL)                                                                                         \
+    score_accumulate<VEC, TAIL><<<grid, kThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, n_groups, G, N, A, K, Kb, \
+                                                                  slices, lds_entries, w, C_out, valid_out)
+        if (vec4 && tail) PCM_ACCUMULATE(4, true);
+        else if (vec4) PCM_ACCUMULATE(4, false);
+        else if (tail) PCM_ACCUMULATE(1, true);
+        else PCM_ACCUMULATE(1, false);
+#undef PCM_ACCUMULATE
+    }
+    if (!tail) {
+        StageTimer t(ST_SCORE_FINALISE, s);
+        score_pairs<<<ceil_div(n_groups * K, kThreads / kWave), kThreads, 0, s>>>(w.sums, w.counts, n_groups, A, K, w.pair);
+        score_mean<<<1, kMeanThreads, 0, s>>>(w.pair, n_groups, K, C_out, valid_out);
     }
     return launch_status();
 }

@@ -308,10 +308,15 @@ def test_sampler_and_counts_at_the_edges_of_slots_per_lane(pcm, N):
     (300, 3, 6, 2, 17),     # more pair scores than a workgroup's threads hold at once, LDS blocks that do not divide them
     (3, 8, 256, 3, 64),     # the most phases, single-float loads, several slices per trajectory
     (2, 4, 1100, 56, 12),   # more chunks per workgroup than are under way together
+    (8, 2, 9, 64, 64),      # the most pair terms, of a group and in all, that are formed behind the accumulation
+    (9, 2, 9, 64, 64),      # one group more: launches of their own from here on
+    (2, 3, 20, 241, 17),    # one term more in a group
+    (700, 2, 3, 8, 64),     # many blocks of groups in the mean's own launch, the last one partly filled
     (2, 3, 40, 190, 64),    # two blocks of phases; 43 phases' sums alone come within a word of 64 KB of LDS
 ])
 def test_score_in_two_launches(pcm, n_groups, G, N, A, K):
-    """The last workgroup of a group forms its pair scores, the last group the mean: called again and again on one
+    """The last workgroup of a group forms its pair scores, the last group the mean (or, where there are many pair terms,
+    launches of their own): called again and again on one
     workspace, with other rewards in between, every call gives the oracle's bits."""
     rng = np.random.default_rng(n_groups + N)
     T = n_groups * G
