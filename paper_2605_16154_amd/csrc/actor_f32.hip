@@ -384,7 +384,8 @@ __global__ __launch_bounds__(kThreads) void loss_rows(float* __restrict__ z, flo
 // its values is loaded for half as many products.  Measured on both sides of the line, 128-wide against 64-wide tiles:
 // 8192 x 1024 x 2816 (512 tiles of 128) 559 / 503 us, twice that 1112 / 981 us; 8192 x 5632 x 1024 (2816 tiles) 871 / 917 us;
 // a pair of 1024 x 2816 over 8192 rows 902 / 957 us.  Splits (if allowed) aim at two workgroups per CU, and at least at
-// 1024 tiles of 64 x 64 (shorter sums are also more accurate), and keep at least four steps each.
+// 1024 tiles of 64 x 64 (shorter sums are also more accurate), but not at slices of fewer than about four steps: as many
+// slices as that allows, rounded up, so that a sum over few rows is in slices of at most 64.
 struct TilePlan {
     int kI, kJ, splits, k_per_split;
 };
@@ -397,7 +398,7 @@ TilePlan plan_tiles(int M, int N, int K, int n_right, bool may_split, bool inter
         int64_t splits = 1;
         if (may_split) {
             splits = std::max(ceil_div64(512, tiles), ceil_div64(1024, (int64_t)ceil_div(M, 64) * ceil_div(N, 64)));
-            splits = std::max<int64_t>(1, std::min<int64_t>(splits, K / (4 * kStep)));
+            splits = std::max<int64_t>(1, std::min<int64_t>(splits, ceil_div(K, 4 * kStep)));
         }
         const int k_per = ceil_div(ceil_div(K, (int)splits), kStep) * kStep;
         splits = ceil_div(K, k_per);

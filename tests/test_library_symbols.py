@@ -115,3 +115,16 @@ def test_binding_fails_loudly_without_the_library(monkeypatch, tmp_path):
     monkeypatch.setattr(b, "_LIB_PATH", str(tmp_path / "absent.so"))
     with pytest.raises(b.PcmError):
         b.lib()
+
+
+@pytest.mark.parametrize("rows,slices", [(2000, 32), (125, 2), (564, 9), (64, 1), (65, 2)])
+def test_fp32_weight_gradient_sums_stay_short(cdll, rows, slices):
+    """A small weight gradient of the fp32 path is summed in slices of at most 64 rows (longer sums lose accuracy).  The
+    slices' buffer is what a call with gradients asks for beyond one without and its dz and dy buffers."""
+    d = ff = V = 64
+    q = cdll.grpo_masked_actor_step_workspace_bytes
+    q.restype = ctypes.c_size_t
+    align = lambda n: -(-n // 256) * 256
+    parts = q(rows, 1, d, ff, V, 0, 1) - q(rows, 1, d, ff, V, 0, 0) - align(rows * V * 4) - align(rows * d * 4)
+    pair = 2 * d * ff * 4                                                     # dWg and dWu in one launch
+    assert parts == (align(slices * pair) if slices > 1 else 0)
