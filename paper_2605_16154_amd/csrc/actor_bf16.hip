@@ -427,7 +427,7 @@ GemmProblem problem(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int 
     p.A2 = A; p.B2 = B;
     p.M = M; p.N = N; p.K1 = K; p.K2 = 0; p.splits = 1;
     p.kept = kr.kept; p.kept_max = kr.kept_max; p.rows_per_kept = kr.rows_per_kept; p.rows_role = rows_role;
-    p.row_offset = kr.row_offset; p.skip_if_empty = 0;
+    p.row_offset = kr.row_offset; p.skip_if_empty = 0; p.cut = kCutNone;
     return p;
 }
 

@@ -30,6 +30,8 @@
 // from which whole rows leave as 16-byte-per-lane stores).
 #pragma once
 
+#include <algorithm>
+
 #include "actor.h"
 
 namespace pcm {
@@ -84,7 +86,11 @@ struct GemmProblem {
     // (B); an earlier kernel of the same stream decides which buffer that is.  Single reduction segment only.
     const bf16* const* A_sel;
     const bf16* const* B_sel;
+    // A product whose last columns go to a second launch, on small tiles (launch_row_gemm): which of the two this is.  Both
+    // are given the whole product; how many columns that is (cut_columns) follows from the live rows.
+    int cut;
 };
+enum Cut : int { kCutNone = 0, kCutHead = 1, kCutTail = 2 };
 enum RowsRole : int { kRowsUnused = 0, kRowsAreM = 1, kRowsAreK = 2 };
 
 // Accumulators of a wavefront: kW x kW tiles of 16 x 16.  Tile (i, j), register t of a lane is
@@ -162,6 +168,15 @@ __device__ inline bool tile_of_workgroup(int wg, int n_wg, int tiles_m, int tile
     tm = first + in_band % rows;
     tn = in_band / rows;
     return true;
+}
+
+// How many 256-wide columns of a product of `live_tiles` x `tn` large tiles a launch of small tiles takes over: those that
+// leave whole rounds of large tiles on the 256 CUs, if one round of small tiles (256 run side by side at the rate this is
+// about) holds them.
+__host__ __device__ inline int cut_columns(int live_tiles, int tn) {
+    if (live_tiles <= 0) return 0;
+    const int rest = live_tiles * tn % 256, columns = (rest + live_tiles - 1) / live_tiles;
+    return columns < tn && 4 * live_tiles * columns <= 256 ? columns : 0;
 }
 
 #define PCM_AS_LDS(p) ((__attribute__((address_space(3))) void*)(p))
@@ -248,7 +263,8 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
     const int wm = wave >> 1, wn = wave & 1;
-    const int tiles_m = p.M / TM, tiles_n = p.N / TN;
+    const int tiles_m = p.M / TM;
+    int tiles_n = p.N / TN, n_first = 0;
     const int n_tiles = tiles_m * tiles_n;
     const int split = blockIdx.x / n_tiles;
     int k1 = p.K1, live_m = tiles_m;
@@ -259,9 +275,14 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
         if (p.rows_role == kRowsAreM) live_m = min(tiles_m, (rows + kTileM - 1) / kTileM * (kTileM / TM));
         if (p.rows_role == kRowsAreK) k1 = min(k1, (rows + kTileK - 1) / kTileK * kTileK);
     }
+    if (p.cut != kCutNone) {
+        const int columns = cut_columns(live_m / (kTileM / TM), p.N / kTileN);
+        n_first = p.cut == kCutTail ? p.N - columns * kTileN : 0;
+        tiles_n = (p.cut == kCutTail ? columns : p.N / kTileN - columns) * (kTileN / TN);
+    }
     int tm, tn;
     if (!tile_of_workgroup<kW>(blockIdx.x % n_tiles, n_tiles, live_m, tiles_n, tm, tn)) return;   // before any barrier
-    const int m0 = tm * TM, n0 = tn * TN;
+    const int m0 = tm * TM, n0 = n_first + tn * TN;
     // reduction range of this workgroup, in 64-wide steps over the concatenation of both segments
     const int steps1 = k1 / kTileK, steps_all = steps1 + p.K2 / kTileK;
     const int per_split = (steps_all + p.splits - 1) / p.splits;
@@ -662,7 +683,6 @@ struct EpiStoreBf16 {
     bf16* C;
     int64_t ldc;
     int row_limit;
-    EpiStoreBf16 columns_from(int64_t n) const { return {C + n, ldc, row_limit}; }   // the same for a product that starts at column n
     template <int kW>
     __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
         constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
@@ -686,7 +706,6 @@ struct EpiScatterBf16 {
     bf16* C;
     int64_t ldc;
     const int32_t* row_idx;
-    EpiScatterBf16 columns_from(int64_t n) const { return {C + n, ldc, row_idx}; }
     template <int kW>
     __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
         constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
@@ -710,7 +729,6 @@ struct EpiStoreBf16Split {
     bf16 *hi, *lo;
     int64_t ldc;
     int row_limit;
-    EpiStoreBf16Split columns_from(int64_t n) const { return {hi + n, lo + n, ldc, row_limit}; }
     template <int kW>
     __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
         constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
@@ -820,9 +838,6 @@ struct EpiSwigluForward {
     static constexpr bool kPairedColumns = true;
     bf16 *fu, *fv, *a, *a_lo;
     int64_t ld;
-    EpiSwigluForward columns_from(int64_t n) const {      // (of the packed columns)
-        return {fu ? fu + n / 2 : nullptr, fv ? fv + n / 2 : nullptr, a + n / 2, a_lo ? a_lo + n / 2 : nullptr, ld};
-    }
     template <int kW>
     __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
         constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
@@ -887,7 +902,6 @@ struct EpiSwigluBackward {
     int64_t ld;
     const int32_t* row_idx;
     bf16 *du, *dv;
-    EpiSwigluBackward columns_from(int64_t n) const { return {fu + n, fv + n, ld, row_idx, du ? du + n : nullptr, dv ? dv + n : nullptr}; }
     template <int kW>
     __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
         constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
@@ -979,27 +993,29 @@ inline void launch_gemm(const GemmProblem& p, const Epilogue& epi, hipStream_t s
     else launch_gemm_tile<kLayA, kLayB, kLargeTile>(p, epi, s);
 }
 
-// A product over the rows of a batch (columns: weights).  When whole rounds of large tiles leave a few over, the last
-// columns go to a launch of their own on small tiles, if one round of those holds them: it takes about 0.65 us per step
-// where one more round of large tiles takes 0.94.  Below 32 steps the launch costs more than that.  Measured: 768 x 22016 x
-// 4096 (258 large tiles) 157 -> 137 us, 5376 x 22016 x 4096 (1806) 615 -> 600 us; with two rounds of small tiles, 5376 x
-// 4096 x 22016 (336), 508 -> 706 us.
-template <int kLayA = kRowsByK, int kLayB = kRowsByK, class Epilogue>
+// A product over the rows of a batch (columns: weights), both operands [rows][K].  When whole rounds of large tiles leave a
+// few over, the last columns go to a launch of their own on small tiles, if one round of those holds them: it takes about
+// 0.65 us per step where one more round of large tiles takes 0.94.  Below 32 steps the launch costs more than that.
+// Measured: 768 x 22016 x 4096 (258 large tiles) 157 -> 137 us, 5376 x 22016 x 4096 (1806) 615 -> 600 us; with two rounds of
+// small tiles, 5376 x 4096 x 22016 (336), 508 -> 706 us.  Which columns, if any, the kernels work out from the live rows
+// (a list shorter than its buffer has other tiles left over); the second launch is made where a full list takes it, and
+// its workgroups leave at once where the live one does not.  One group's step in a buffer of 21 row tiles, columns chosen by
+// the buffer / none / by the live rows: 13 live row tiles 2254 / 2218 / 2221 us, 16 2552 / 2516 / 2522, 17 3162 / 3114 / 3117,
+// 21 3539 / 3555 / 3550.
+template <class Epilogue>
 inline void launch_row_gemm(const GemmProblem& p, const Epilogue& epi, hipStream_t s) {
-    const int64_t tm = p.M / kTileM, tn = p.N / kTileN, rest = tm * tn % 256, peel = (rest + tm - 1) / tm;
-    const int steps = (p.K1 + p.K2) / kTileK;
-    if (tile_for(p.M, p.N, 1) == kLargeTile && rest > 0 && peel < tn && 4 * tm * peel <= 256 && steps >= 32) {
-        const int64_t n = (tn - peel) * kTileN;
-        GemmProblem head = p, tail = p;
-        head.N = (int)n;
-        tail.N = (int)(p.N - n);
-        tail.B += kLayB == kRowsByK ? n * p.ldb : n;
-        tail.B2 += kLayB == kRowsByK ? n * p.ldb : n;
-        launch_gemm_tile<kLayA, kLayB, kLargeTile>(head, epi, s);
-        launch_gemm_tile<kLayA, kLayB, kSmallTile>(tail, epi.columns_from(n), s);
+    const int tm = p.M / kTileM, tn = p.N / kTileN, steps = (p.K1 + p.K2) / kTileK;
+    if (tile_for(p.M, p.N, 1) != kLargeTile || steps < 32 || tm > 64 || cut_columns(tm, tn) == 0) {
+        launch_gemm(p, epi, s);
         return;
     }
-    launch_gemm<kLayA, kLayB>(p, epi, s);
+    int most = 0;                                           // small tiles, over the lists that the buffer can hold
+    for (int live = 1; live <= tm; ++live) most = std::max(most, 4 * live * cut_columns(live, tn));
+    GemmProblem head = p, tail = p;
+    head.cut = kCutHead;
+    tail.cut = kCutTail;
+    launch_gemm_tile<kRowsByK, kRowsByK, kLargeTile>(head, epi, s);
+    gemm_bf16<Epilogue, kRowsByK, kRowsByK, kSmallTile><<<(unsigned)most, kGemmThreads, 0, s>>>(tail, epi);
 }
 
 }  // namespace pcm
