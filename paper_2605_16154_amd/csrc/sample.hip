@@ -478,7 +478,7 @@ __global__ __launch_bounds__(kThreads) void importance_weights(const uint8_t* __
 // contiguous), and as many LDS atomics on one address would be served one after the other: the first lane of every run
 // of equal values adds the length of the run.
 __device__ inline void wave_histogram(int* hist, int c, int lane) {
-    const int left = __shfl_up(c, 1, kWave);
+    const int left = __builtin_amdgcn_update_dpp(c, c, 0x138, 0xf, 0xf, false);       // the lane before (wave_shr:1), no LDS
     const bool starts = lane == 0 || c != left;
     const uint64_t starting = __ballot(starts);
     if (starts && c >= 0) {
