@@ -48,9 +48,8 @@ __device__ inline int packed_row(int c, int mode) {
     return (c / 64) * 128 + (c % 64) + (mode == kPackUp ? 64 : 0);
 }
 
-// dst[map(c), r] = src[r, c] for a [R, C] bf16 matrix (R, C multiples of 64); 64 x 64 tiles.  kStream: the result is not
-// read again before the memory-side cache has turned over (the four re-layouts of a head of more than 256 MB, kept by the
-// caller: 112 -> 84 us at 272 MB); the stores then leave the cache to the sources.
+// dst[map(c), r] = src[r, c] for a [R, C] bf16 matrix (R, C multiples of 64); 64 x 64 tiles.  kStream: non-temporal stores,
+// which leave the memory-side cache to the sources (see kStreamPackBytes).
 template <bool kStream>
 __global__ __launch_bounds__(256) void transpose_bf16(const uint16_t* __restrict__ src, int64_t ld_src,
                                                       uint16_t* __restrict__ dst, int64_t ld_dst, int mode) {
@@ -455,12 +454,19 @@ void launch_rows_bf16(GemmProblem p, bf16* C, float* parts, hipStream_t s) {
 
 }  // namespace
 
+// Packed weights of more than this are stored non-temporally.  The cache holds 256 MB: of a small head the next step finds
+// the result there, of a large one it does not, and the stores displace the bf16 weights that the optimizer has just
+// written and the re-layout reads.  Optimizer, re-layout and the step after them, ordinary / non-temporal stores:
+// log-probabilities of 672 rows 67 MB 324 / 330 us, 102 MB 457 / 464, 146 MB 632 / 621, 194 MB 837 / 818, 260 MB 1138 / 1112,
+// 338 MB 1464 / 1438; a training step of 1344 rows 67 MB 706 / 721, 146 MB 1263 / 1268, 194 MB 1599 / 1584, 260 MB 2195 / 2166.
+constexpr size_t kStreamPackBytes = (size_t)160 << 20;
+
 size_t packed_head_bytes(int d, int ff, int V) { return carve_packed(nullptr, d, ff, V).bytes; }
 
 int pack_head_weights(const void* Wg, const void* Wu, const void* Wd, const void* Wo, int d, int ff, int V, void* packed,
                       hipStream_t s) {
     const PackedHead p = carve_packed(packed, d, ff, V);
-    const bool stream = p.bytes > (size_t)256 << 20;
+    const bool stream = p.bytes > kStreamPackBytes;
     transpose(s, static_cast<const bf16*>(Wg), d, ff, p.WguT, d, kPackGate, ST_WEIGHT_LAYOUT, stream);
     transpose(s, static_cast<const bf16*>(Wu), d, ff, p.WguT, d, kPackUp, ST_WEIGHT_LAYOUT, stream);
     transpose(s, static_cast<const bf16*>(Wd), ff, d, p.WdT, ff, kPackNone, ST_WEIGHT_LAYOUT, stream);
