@@ -36,7 +36,7 @@ PCM_API int pcm_profile_collect(double* total_ms, int64_t* launches);
 
 /* ------------------------------------------------------------------------------------------
  * pcm_measure_mfma_rate (libpcm_measure.so).  Runs bf16 matrix instructions
- * (v_mfma_f32_32x32x16_bf16, fp32 accumulation) from registers on every CU of the current device
+ * (v_mfma_f32_16x16x32_bf16, the one the GEMMs issue, fp32 accumulation) from registers on every CU of the current device
  * for about `milliseconds`, with all-zero operands (random_operands = 0) or roughly normal random
  * operands, and reports the sustained rate in TFLOP/s and the mean shader clock in GHz (clock_ghz
  * may be NULL).  Allocates two small device buffers for its own use, frees them before it returns,
