@@ -129,7 +129,7 @@ def _take_workspace(nbytes: int, device: torch.device, stream: int) -> torch.Ten
 
 
 def _give_workspace(ws: torch.Tensor, device: torch.device, stream: int) -> None:
-    if _capturing():
+    if stream != 0 and _capturing():          # the default stream cannot be captured
         _captured_workspaces[id(ws)] = ws
     key = (device.index, stream)
     kept = _workspaces.get(key)

@@ -77,11 +77,11 @@ def test_table_is_bounded_and_drops_what_was_used_longest_ago():
 
 
 def test_scratch_of_a_capture_outlives_growth_and_the_bound(monkeypatch):
-    with take(100, 0) as w:
+    with take(100, 3) as w:
         captured = w
         monkeypatch.setattr(binding, "_capturing", lambda: True)
     monkeypatch.setattr(binding, "_capturing", lambda: False)
-    with take(200, 0):
+    with take(200, 3):
         pass
     assert not any(t is captured for t in binding._workspaces.values())
     assert [t is captured for t in binding._captured_workspaces.values()] == [True]
