@@ -19,7 +19,8 @@
 // energy per multiply-add is what counts.  From registers alone, on random operands, 32x32x16 MFMAs sustain 1.79 PFLOP/s
 // at 1.81 GHz and 16x16x32 ones 2.03 PFLOP/s at 2.07 GHz: per multiply-add they move half the accumulators.  They also
 // take twice the instructions, so the loop is scheduled by hand (see there).  Measured on one box against the
-// 32x32x16 loop it replaces: gate/up (43008 x 22016 x 4096) 5.40 -> 5.05 ms (1.44 -> 1.54 PFLOP/s), down
+// 32x32x16 loop it replaces: gate/up without the factors for a backward pass (43008 x 22016 x 4096) 5.40 -> 5.05 ms
+// (1.44 -> 1.54 PFLOP/s; the instance of a training step, which also writes those, 5.82 -> 5.42 on other boxes), down
 // (43008 x 4096 x 11008) 2.59 -> 2.45 ms (1.50 -> 1.59), dWg (4096 x 11008 over 26112 rows) 1.73 -> 1.59 ms
 // (1.36 -> 1.48); with 16 workgroups on the chip, where the clock stays up and the step is issue-bound, 0.92 -> 0.94 us
 // per step.

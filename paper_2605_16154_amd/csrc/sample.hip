@@ -489,7 +489,7 @@ __device__ inline void wave_histogram(int* hist, int c, int lane) {
 
 // Histograms in LDS of the kept chunks' phases (workgroup 0) and of the phases of all chunk slots the sampler could have
 // kept (workgroup 1), written out as they are (nothing to clear, no atomics in memory).  Bound by the latency of the loads
-// and by the instructions of one CU; each thread has sixteen slots under way.  32768 slots, 4096 kept: 22.7 -> 14 us
+// and by the instructions of one CU; each thread has sixteen slots under way.  32768 slots, 4096 kept: 22.7 -> 13.4 us
 // against one slot and one LDS atomic per thread at a time in a single workgroup.
 constexpr int kCountBatch = 16;
 __global__ __launch_bounds__(1024) void kept_phase_counts(const uint8_t* __restrict__ phase,
