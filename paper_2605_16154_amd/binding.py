@@ -6,7 +6,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
-from typing import Dict, Optional, Tuple
+from typing import Dict, List, Optional, Tuple
 
 import torch
 
@@ -113,25 +113,34 @@ def _stream() -> int:
 # Scratch of the calls, kept from one to the next by device and stream: calls that share scratch have to be ordered on one
 # stream.  A call takes its tensor out of the table while it enqueues its launches, so that threads that issue to one stream
 # at the same time have one each.  The table is bounded; a tensor that leaves it goes back to the caching allocator, which
-# hands it out on the same stream only.  Scratch used under graph capture stays for good: the graph holds its address.
+# hands it out on the same stream only.  A graph holds the address of the scratch it was captured with and may be replayed on
+# any stream: such scratch leaves the table for good, and only later captures on its stream use it again.
 # (Plain dict operations, each atomic: a lock or a context manager costs a microsecond of the ten that a small call takes.)
 _KEPT_WORKSPACES = 8
 _workspaces: Dict[Tuple[Optional[int], int], torch.Tensor] = {}     # the one used longest ago first
-_captured_workspaces: Dict[int, torch.Tensor] = {}
+_captured_workspaces: Dict[Tuple[Optional[int], int], List[torch.Tensor]] = {}     # the one in use last
 
 
 def _take_workspace(nbytes: int, device: torch.device, stream: int) -> torch.Tensor:
     """At least `nbytes` of scratch for one call on `stream`, to be handed to _give_workspace once it is enqueued."""
-    ws = _workspaces.pop((device.index, stream), None)
+    key = (device.index, stream)
+    captured = None
+    if stream != 0 and _capturing():          # the default stream cannot be captured
+        captured = _captured_workspaces.setdefault(key, [])
+        if captured and captured[-1].numel() >= nbytes:
+            return captured[-1]
+    ws = _workspaces.pop(key, None)
     if ws is None or ws.numel() < nbytes:
         ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    if captured is not None:
+        captured.append(ws)
     return ws
 
 
 def _give_workspace(ws: torch.Tensor, device: torch.device, stream: int) -> None:
-    if stream != 0 and _capturing():          # the default stream cannot be captured
-        _captured_workspaces[id(ws)] = ws
     key = (device.index, stream)
+    if any(c is ws for c in _captured_workspaces.get(key, ())):
+        return
     kept = _workspaces.get(key)
     if kept is None or kept.numel() < ws.numel():
         _workspaces[key] = ws

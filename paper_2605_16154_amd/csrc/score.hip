@@ -253,30 +253,35 @@ __device__ inline void score_pairs_of_group(int g, int A, int K, const ull* sums
     }
 }
 
-// The same as a launch of its own: one wavefront per (group, phase).  All threads reach the barrier.
+// The same as a launch of its own: one wavefront per (group, phase), striding by the grid.  All threads reach the barrier.
 __global__ __launch_bounds__(kThreads) void score_pairs(const ull* __restrict__ sums, const int* __restrict__ counts, int n_groups,
                                                         int A, int K, double* pair) {
     __shared__ double sq[kThreads / kWave][256];
     const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int w = blockIdx.x * (kThreads / kWave) + wv;
-    const int at = min(w, n_groups * K - 1), g = at / K, c = at % K;
-    const size_t pos = ((size_t)g * 2 + 1) * K + c, neg = ((size_t)g * 2 + 0) * K + c;
-    const int n_pos = counts[pos], n_neg = counts[neg];
-    const bool ok = n_pos > 0 && n_neg > 0;
-    if (ok)
-        for (int j = lane; j < A; j += kWave) sq[wv][j] = squared_difference(sums[pos * A + j], n_pos, sums[neg * A + j], n_neg);
-    __syncthreads();
-    if (w < n_groups * K && lane == 0) {
-        double score = -1.0;
-        if (ok) {
-            double acc = 0.0;
+    const int64_t n = (int64_t)n_groups * K, step = (int64_t)gridDim.x * (kThreads / kWave);
+    for (int64_t w0 = (int64_t)blockIdx.x * (kThreads / kWave); w0 < n; w0 += step) {
+        const int64_t w = w0 + wv, at = w < n ? w : n - 1;
+        const int64_t g = at / K, c = at % K;
+        const size_t pos = ((size_t)g * 2 + 1) * K + c, neg = ((size_t)g * 2 + 0) * K + c;
+        const int n_pos = counts[pos], n_neg = counts[neg];
+        const bool ok = n_pos > 0 && n_neg > 0;
+        if (ok)
+            for (int j = lane; j < A; j += kWave) sq[wv][j] = squared_difference(sums[pos * A + j], n_pos, sums[neg * A + j], n_neg);
+        __syncthreads();
+        if (w < n && lane == 0) {
+            double score = -1.0;
+            if (ok) {
+                double acc = 0.0;
 #pragma unroll 8
-            for (int j = 0; j < A; ++j) acc = acc + sq[wv][j];
-            score = sqrt(acc) * kActionUnscale;
+                for (int j = 0; j < A; ++j) acc = acc + sq[wv][j];
+                score = sqrt(acc) * kActionUnscale;
+            }
+            pair[w] = score;
         }
-        pair[w] = score;
     }
 }
+
+constexpr int64_t kPairBlocksMax = 1 << 16;   // workgroups of score_pairs at most
 
 // Batch score of phase c = mean over the groups that contributed, added for g ascending (the order is
 // part of the definition: the result must not depend on the launch).  One workgroup: the per-group values
@@ -460,7 +465,9 @@ int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward,
     }
     if (!tail) {
         StageTimer t(ST_SCORE_FINALISE, s);
-        score_pairs<<<ceil_div(n_groups * K, kThreads / kWave), kThreads, 0, s>>>(w.sums, w.counts, n_groups, A, K, w.pair);
+        const int64_t pair_blocks = ceil_div64((int64_t)n_groups * K, kThreads / kWave);
+        score_pairs<<<(unsigned)std::min<int64_t>(pair_blocks, kPairBlocksMax), kThreads, 0, s>>>(w.sums, w.counts, n_groups, A, K,
+                                                                                                w.pair);
         score_mean<<<1, kMeanThreads, 0, s>>>(w.pair, n_groups, K, C_out, valid_out);
     }
     return launch_status();

@@ -76,15 +76,28 @@ def test_table_is_bounded_and_drops_what_was_used_longest_ago():
     assert (None, 0) in binding._workspaces and (None, 1) not in binding._workspaces
 
 
-def test_scratch_of_a_capture_outlives_growth_and_the_bound(monkeypatch):
-    with take(100, 3) as w:
-        captured = w
-        monkeypatch.setattr(binding, "_capturing", lambda: True)
+def test_scratch_of_a_capture_is_the_graphs_from_then_on(monkeypatch):
+    """The graph may be replayed on any stream at any later time: neither eager calls on the capture's stream nor growth
+    nor the bound of the table may touch its scratch.  Later captures on the stream take it again, or a larger one."""
+    with take(300, 3) as w:                # warm-up: sizes the scratch before the capture
+        warm = w
+    monkeypatch.setattr(binding, "_capturing", lambda: True)
+    with take(0, 3) as v, take(100, 3) as w:
+        assert v is warm and w is warm     # calls of one capture are ordered: one tensor serves them
     monkeypatch.setattr(binding, "_capturing", lambda: False)
-    with take(200, 3):
-        pass
-    assert not any(t is captured for t in binding._workspaces.values())
-    assert [t is captured for t in binding._captured_workspaces.values()] == [True]
+    with take(100, 3) as w:
+        assert w is not warm
+    monkeypatch.setattr(binding, "_capturing", lambda: True)
+    with take(200, 3) as w:
+        assert w is warm
+    with take(400, 3) as w:
+        larger = w
+        assert w.numel() >= 400
+    with take(100, 3) as w:
+        assert w is larger
+    assert [c is t for c, t in zip(binding._captured_workspaces[(None, 3)], (warm, larger))] == [True, True]
+    monkeypatch.setattr(binding, "_capturing", lambda: False)
+    assert not any(t is c for t in binding._workspaces.values() for c in (warm, larger))
 
 
 def test_an_error_in_the_call_gives_the_scratch_back():

@@ -312,6 +312,7 @@ def test_sampler_and_counts_at_the_edges_of_slots_per_lane(pcm, N):
     (9, 2, 9, 64, 64),      # one group more: launches of their own from here on
     (2, 3, 20, 241, 17),    # one term more in a group
     (700, 2, 3, 8, 64),     # many blocks of groups in the mean's own launch, the last one partly filled
+    (4200, 2, 1, 5, 64),    # more (group, phase) pairs than the pair launch has wavefronts
     (2, 3, 40, 190, 64),    # two blocks of phases; 43 phases' sums alone come within a word of 64 KB of LDS
 ])
 def test_score_in_two_launches(pcm, n_groups, G, N, A, K):
