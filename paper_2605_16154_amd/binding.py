@@ -139,7 +139,8 @@ def _take_workspace(nbytes: int, device: torch.device, stream: int) -> torch.Ten
 
 def _give_workspace(ws: torch.Tensor, device: torch.device, stream: int) -> None:
     key = (device.index, stream)
-    if any(c is ws for c in _captured_workspaces.get(key, ())):
+    captured = _captured_workspaces.get(key)
+    if captured and any(c is ws for c in captured):
         return
     kept = _workspaces.get(key)
     if kept is None or kept.numel() < ws.numel():

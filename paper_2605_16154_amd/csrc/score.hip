@@ -29,6 +29,9 @@ namespace pcm {
 namespace {
 
 constexpr int kThreads = 256;
+// LDS for sums, squared terms and pair scores: the 64 KB that a workgroup may take by default, less the word of arrive_last
+// and the counts of the mean
+constexpr size_t kLdsMax = 64 * 1024 - (PCM_MAX_PHASES + 4) * sizeof(int);
 constexpr float kActionScale = 16777216.0f;                 // 2^24
 constexpr double kActionUnscale = 1.0 / 16777216.0;         // 2^-24
 
@@ -206,50 +209,40 @@ __device__ inline double squared_difference(ull s_pos, int n_pos, ull s_neg, int
     return diff * diff;
 }
 
-// Pair scores of group g for all phases by one workgroup, as many phases at a time as LDS holds.  Their rows of squared
-// terms are an odd number of doubles apart: a lane adds up a row, and with 256 between them all lanes met in one bank
-// (64 phases of 256 values: 41 -> 32 us).
-__host__ __device__ inline int pair_row(int A) { return A | 1; }
-__device__ inline void score_pairs_of_group(int g, int A, int K, const ull* sums, const int* counts, double* lds, int lds_entries,
-                                            double* pair) {
-    const int row = pair_row(A), block = min(K, lds_entries / row);
-    for (int c0 = 0; c0 < K; c0 += block) {
-        const int kb = min(block, K - c0);
-        const size_t pos = ((size_t)g * 2 + 1) * K + c0, neg = ((size_t)g * 2 + 0) * K + c0;
-        __syncthreads();
-        const int my_c = threadIdx.x < kb ? threadIdx.x : 0;      // the phase this thread adds up (kb <= 64)
-        const int my_pos = load_shared(&counts[pos + my_c]), my_neg = load_shared(&counts[neg + my_c]);
-        for (int e0 = threadIdx.x; e0 < kb * A; e0 += 4 * kThreads) {
-            int c[4], n_pos[4], n_neg[4];                         // all loads of four terms under way together
-            ull s_pos[4], s_neg[4];
+// Pair scores of group g for all phases by one workgroup; LDS holds the squared terms of all of them (see fuses_tail).
+__device__ inline void score_pairs_of_group(int g, int A, int K, const ull* sums, const int* counts, double* lds, double* pair) {
+    const size_t pos = ((size_t)g * 2 + 1) * K, neg = ((size_t)g * 2 + 0) * K;
+    __syncthreads();
+    const int my_c = (int)threadIdx.x < K ? threadIdx.x : 0;      // the phase this thread adds up (K <= 64)
+    const int my_pos = load_shared(&counts[pos + my_c]), my_neg = load_shared(&counts[neg + my_c]);
+    for (int e0 = threadIdx.x; e0 < K * A; e0 += 4 * kThreads) {
+        int n_pos[4], n_neg[4];                                   // all loads of four terms under way together
+        ull s_pos[4], s_neg[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int e = min(e0 + u * kThreads, kb * A - 1);
-                c[u] = e / A;
-                n_pos[u] = load_shared(&counts[pos + c[u]]);
-                n_neg[u] = load_shared(&counts[neg + c[u]]);
-                s_pos[u] = load_shared(&sums[pos * A + e]);
-                s_neg[u] = load_shared(&sums[neg * A + e]);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int e = e0 + u * kThreads;
-                if (e < kb * A && n_pos[u] > 0 && n_neg[u] > 0)
-                    lds[c[u] * (row - A) + e] = squared_difference(s_pos[u], n_pos[u], s_neg[u], n_neg[u]);
-            }
+        for (int u = 0; u < 4; ++u) {
+            const int e = min(e0 + u * kThreads, K * A - 1), c = e / A;
+            n_pos[u] = load_shared(&counts[pos + c]);
+            n_neg[u] = load_shared(&counts[neg + c]);
+            s_pos[u] = load_shared(&sums[pos * A + e]);
+            s_neg[u] = load_shared(&sums[neg * A + e]);
         }
-        __syncthreads();
-        if ((int)threadIdx.x < kb) {
-            const int c = threadIdx.x;
-            double score = -1.0;                                  // skipped: no chunks of one of the outcomes
-            if (my_pos > 0 && my_neg > 0) {
-                double acc = 0.0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * kThreads;
+            if (e < K * A && n_pos[u] > 0 && n_neg[u] > 0) lds[e] = squared_difference(s_pos[u], n_pos[u], s_neg[u], n_neg[u]);
+        }
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < K) {
+        const int c = threadIdx.x;
+        double score = -1.0;                                      // skipped: no chunks of one of the outcomes
+        if (my_pos > 0 && my_neg > 0) {
+            double acc = 0.0;
 #pragma unroll 8
-                for (int j = 0; j < A; ++j) acc = acc + lds[c * row + j];
-                score = sqrt(acc) * kActionUnscale;
-            }
-            store_shared(&pair[(size_t)g * K + c0 + c], score);
+            for (int j = 0; j < A; ++j) acc = acc + lds[c * A + j];
+            score = sqrt(acc) * kActionUnscale;
         }
+        store_shared(&pair[(size_t)g * K + c], score);
     }
 }
 
@@ -372,7 +365,7 @@ __global__ __launch_bounds__(kThreads) void score_accumulate(
     if (kTail) {
         double* const lds = reinterpret_cast<double*>(lds_sum);
         if (!arrive_last(reinterpret_cast<int*>(w.pair + (size_t)g * K), G * slices * phase_blocks)) return;
-        score_pairs_of_group(g, A, K, w.sums, w.counts, lds, lds_entries, w.pair);
+        score_pairs_of_group(g, A, K, w.sums, w.counts, lds, w.pair);
         if (!arrive_last(w.groups_done, n_groups)) return;
         mean_of_groups<kThreads>(w.pair, n_groups, K, lds, lds_entries, C_out, valid_out, [](const double* p) { return load_shared(p); });
     }
@@ -382,12 +375,13 @@ __global__ __launch_bounds__(kThreads) void score_accumulate(
 // Two launches save about 5 us, which count while the calls are bound by issuing them.  Behind the accumulation a group's
 // pair scores are the work of one workgroup and the mean waits for loads past the L2 caches, and every workgroup pays for
 // arriving.  Measured per call, two / four launches, the other bound held:
-//   by the pair terms of a group, one group:  12 phases of 56 values 12.8 / 17.4 us; 24 of 128 (3072 terms) 15.2 / 17.3,
-//   33 of 128 (4224) 16.8 / 17.4, 24 of 256 (6144) 20.3 / 18.7, 64 of 256 34.7 / 19.9
-//   by those of all groups:  32 groups of 5 x 56 (8960) 14.0 / 14.8 us, 8 of 24 x 128 (24576) 15.7 / 16.9, 8 of 33 x 128
-//   (33792) 17.2 / 17.5, 64 of 12 x 56 (43008, 256 chunks each) 19.3 / 18.6, 256 of 12 x 56 29.3 / 26.5, 1024 of 12 x 56
-//   85.6 / 75.5
+//   by the pair terms of a group, one group:  12 phases of 56 values 11.9 / 17.4 us; 24 of 128 (3072 terms) 15.0 / 17.3,
+//   33 of 128 (4224) 17.4 / 17.4, 24 of 256 (6144) 21.4 / 18.7, 64 of 256 40.6 / 19.9
+//   by those of all groups:  32 groups of 5 x 56 (8960) 14.0 / 14.8 us, 8 of 24 x 128 (24576) 15.8 / 16.9, 8 of 33 x 128
+//   (33792) 18.4 / 17.5, 64 of 12 x 56 (43008, 256 chunks each) 19.4 / 18.6, 256 of 12 x 56 29.6 / 26.5, 1024 of 12 x 56
+//   88.5 / 75.5
 bool fuses_tail(int n_groups, int A, int K) {
+    static_assert(4096 * sizeof(ull) + PCM_MAX_PHASES * sizeof(int) <= kLdsMax, "a group's sums and squared terms fit in LDS");
     return K * A <= 4096 && (int64_t)n_groups * K * A <= 32768;
 }
 
@@ -420,9 +414,7 @@ namespace {
 int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward, const int32_t* n_chunks,
               int n_groups, int G, int N, int A, int K, double adv_eps, double* C_out, uint8_t* valid_out,
               float* adv_out, uint8_t* active_out, const ScoreWorkspace& w, hipStream_t s) {
-    // phases per workgroup: all K if their sums fit in the 64 KB of LDS that a workgroup may take by default, less the word
-    // of arrive_last with its padding (A <= 256: at least 31 do)
-    constexpr size_t kLdsMax = 64 * 1024 - 16;
+    // phases per workgroup: all K if their sums fit in LDS (A <= 256: at least 31 do)
     int Kb = (int)(kLdsMax / ((size_t)A * sizeof(ull) + sizeof(int)));
     if (Kb > K) Kb = K;
     const int phase_blocks = ceil_div(K, Kb);
@@ -430,9 +422,8 @@ int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward,
     const bool tail = fuses_tail(n_groups, A, K);
     if (tail) {
         // all pair scores, but no more than lets eight workgroups share a CU (a group's scores fit, whatever K): the mean
-        // waits for loads once per block of groups that fits here; and all rows of squared terms
+        // waits for loads once per block of groups that fits here
         lds_bytes = std::max(lds_bytes, std::min((size_t)n_groups * K * sizeof(double), (size_t)16 * 1024));
-        lds_bytes = std::max(lds_bytes, std::min((size_t)K * pair_row(A) * sizeof(double), kLdsMax));
     }
     const int lds_entries = (int)(lds_bytes / sizeof(double));
     const int T = n_groups * G;
