@@ -69,13 +69,35 @@ struct RowOut {
 };
 
 // gather.hip ---------------------------------------------------------------------------------
+// Weights to be copied transposed: dst[map(c), r] = src[r, c], [R, C] bf16 row-major, R and C multiples of 64.
+enum PackMode : int { kPackNone = 0, kPackGate = 1, kPackUp = 2 };   // map: identity, or gate and up in blocks of 64 in turn
+struct TransposeJob {
+    const bf16* src;
+    bf16* dst;
+    int R, C, mode;
+};
+struct TransposeList {
+    static constexpr int kMax = 4;
+    TransposeJob job[kMax];
+    int first[kMax];      // workgroup of each one's first tile
+    int n, blocks;
+    void add(const bf16* src, int R, int C, bf16* dst, int mode) {
+        job[n] = TransposeJob{src, dst, R, C, mode};
+        first[n++] = blocks;
+        blocks += R / 64 * (C / 64);
+    }
+};
+// A launch of nothing but transposes; stream: non-temporal stores.
+void launch_transposes(const TransposeList& list, bool stream, hipStream_t s);
+
 // Copies the kept chunks' hidden rows into X [rows_pad, d] (rows at and beyond n_kept*A are
 // zero-filled) and fills the row metadata.  elem_bytes is 2 (bf16) or 4 (fp32).
 // With row_offset > 0 the rows are those of a panel of the batch that starts at that row: X and the metadata
 // arrays are the panel's own, `rows_pad` its height.  The same holds for the two per-chunk-ratio launches below
 // (row_offset a multiple of A, so no chunk straddles two panels).
+// In the same launch: the transposes of `layouts`, and zeros in zero[0 .. n_zero).
 int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void* X, int64_t row_offset, int64_t rows_pad,
-                  RowMeta meta, hipStream_t s);
+                  RowMeta meta, const TransposeList& layouts, double* zero, int n_zero, hipStream_t s);
 
 // Partial sums of squares of the four weight gradients, left by the launches that wrote their final values.
 struct SumsqLists {

@@ -39,58 +39,8 @@
 namespace pcm {
 namespace {
 
-constexpr int kPackNone = 0, kPackGate = 1, kPackUp = 2;
 constexpr size_t kMaxSplitTiles = 256;   // tiles x parts of a split reduction: one workgroup per CU
 constexpr size_t kSumBlocksMax = 2048;   // workgroups of sum_parts_f32 at most
-
-__device__ inline int packed_row(int c, int mode) {
-    if (mode == kPackNone) return c;
-    return (c / 64) * 128 + (c % 64) + (mode == kPackUp ? 64 : 0);
-}
-
-// dst[map(c), r] = src[r, c] for a [R, C] bf16 matrix (R, C multiples of 64); 64 x 64 tiles.  kStream: non-temporal stores,
-// which leave the memory-side cache to the sources (see kStreamPackBytes).
-template <bool kStream>
-__global__ __launch_bounds__(256) void transpose_bf16(const uint16_t* __restrict__ src, int64_t ld_src,
-                                                      uint16_t* __restrict__ dst, int64_t ld_dst, int mode) {
-    __shared__ uint16_t tile[64][66];
-    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-    const int t = threadIdx.x, tr = t >> 4, tv = t & 15;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int row = tr + 16 * q;
-        const uint2 v = *reinterpret_cast<const uint2*>(src + (int64_t)(r0 + row) * ld_src + c0 + tv * 4);
-        tile[row][tv * 4 + 0] = (uint16_t)(v.x & 0xFFFF);
-        tile[row][tv * 4 + 1] = (uint16_t)(v.x >> 16);
-        tile[row][tv * 4 + 2] = (uint16_t)(v.y & 0xFFFF);
-        tile[row][tv * 4 + 3] = (uint16_t)(v.y >> 16);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int c = tr + 16 * q;
-        uint2 v;
-        v.x = (uint32_t)tile[tv * 4 + 0][c] | ((uint32_t)tile[tv * 4 + 1][c] << 16);
-        v.y = (uint32_t)tile[tv * 4 + 2][c] | ((uint32_t)tile[tv * 4 + 3][c] << 16);
-        uint16_t* const to = dst + (int64_t)packed_row(c0 + c, mode) * ld_dst + r0 + tv * 4;
-        if (kStream) __builtin_nontemporal_store((uint64_t)v.x | (uint64_t)v.y << 32, reinterpret_cast<uint64_t*>(to));
-        else *reinterpret_cast<uint2*>(to) = v;
-    }
-}
-
-void transpose(hipStream_t s, const bf16* src, int R, int C, bf16* dst, int64_t ld_dst, int mode, int stage, bool stream = false) {
-    StageTimer t(stage, s);
-    dim3 grid(C / 64, R / 64);
-    const uint16_t* const from = reinterpret_cast<const uint16_t*>(src);
-    uint16_t* const to = reinterpret_cast<uint16_t*>(dst);
-    if (stream) transpose_bf16<true><<<grid, 256, 0, s>>>(from, C, to, ld_dst, mode);
-    else transpose_bf16<false><<<grid, 256, 0, s>>>(from, C, to, ld_dst, mode);
-}
-
-__global__ void fill_zero_f64(double* p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.0;
-}
 
 // Sum over a workgroup of 256 threads (every thread gets the result).
 __device__ inline double block_sum_256(double x) {
@@ -467,10 +417,12 @@ int pack_head_weights(const void* Wg, const void* Wu, const void* Wd, const void
                       hipStream_t s) {
     const PackedHead p = carve_packed(packed, d, ff, V);
     const bool stream = p.bytes > kStreamPackBytes;
-    transpose(s, static_cast<const bf16*>(Wg), d, ff, p.WguT, d, kPackGate, ST_WEIGHT_LAYOUT, stream);
-    transpose(s, static_cast<const bf16*>(Wu), d, ff, p.WguT, d, kPackUp, ST_WEIGHT_LAYOUT, stream);
-    transpose(s, static_cast<const bf16*>(Wd), ff, d, p.WdT, ff, kPackNone, ST_WEIGHT_LAYOUT, stream);
-    transpose(s, static_cast<const bf16*>(Wo), d, V, p.WoT, d, kPackNone, ST_WEIGHT_LAYOUT, stream);
+    TransposeList list{};
+    list.add(static_cast<const bf16*>(Wg), d, ff, p.WguT, kPackGate);
+    list.add(static_cast<const bf16*>(Wu), d, ff, p.WguT, kPackUp);
+    list.add(static_cast<const bf16*>(Wd), ff, d, p.WdT, kPackNone);
+    list.add(static_cast<const bf16*>(Wo), d, V, p.WoT, kPackNone);
+    launch_transposes(list, stream, s);
     return launch_status();
 }
 
@@ -493,27 +445,26 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
     const bf16* Wo = static_cast<const bf16*>(io.Wo);
 
     const KeptRows all_rows{nullptr, 0, 0, 0};
+    TransposeList layouts{};
     if (io.opt.packed_weights != nullptr) {               // layouts kept by the caller: nothing to re-lay-out
         const PackedHead ph = carve_packed(const_cast<void*>(io.opt.packed_weights), d, ff, V);
         w.WguT = ph.WguT; w.WdT = ph.WdT; w.WoT = ph.WoT;
     } else {
-        transpose(s, Wg, d, ff, w.WguT, d, kPackGate, ST_WEIGHT_LAYOUT);   // [d, ff] -> packed rows of [2 ff, d]
-        transpose(s, Wu, d, ff, w.WguT, d, kPackUp, ST_WEIGHT_LAYOUT);
+        layouts.add(Wg, d, ff, w.WguT, kPackGate);         // [d, ff] -> packed rows of [2 ff, d]
+        layouts.add(Wu, d, ff, w.WguT, kPackUp);
         if (io.composed) {
             // W_do = Wd Wo [ff, V], from the weights as given (Wd [rows][K], Wo [K][rows])
             launch_reduction_gemm<kRowsByK, kKByRows>(problem(Wd, d, Wo, V, ff, V, d, all_rows, kRowsUnused), nullptr, w.Wdo,
                                                       w.parts, false, SumsqTarget{}, ST_WEIGHT_LAYOUT, s);
         } else {
-            transpose(s, Wd, ff, d, w.WdT, ff, kPackNone, ST_WEIGHT_LAYOUT);   // [ff, d] -> [d, ff]
-            transpose(s, Wo, d, V, w.WoT, d, kPackNone, ST_WEIGHT_LAYOUT);     // [d, V]  -> [V, d]
+            layouts.add(Wd, ff, d, w.WdT, kPackNone);      // [ff, d] -> [d, ff]
+            layouts.add(Wo, d, V, w.WoT, kPackNone);       // [d, V]  -> [V, d]
         }
     }
 
+    // slots for sums of squares that no launch of this call writes must read as zero: cleared with the first gather
     const bool want_sumsq = grads && io.opt.grad_sumsq_out != nullptr && ws != nullptr && w.sumsq[0] != nullptr;
-    if (want_sumsq) {   // slots no launch of this call writes must read as zero (a fill kernel: safe under graph capture)
-        const int n = (int)(w.sumsq[3] - w.sumsq[0]) + w.sumsq_count[3];       // the four lists follow one another
-        fill_zero_f64<<<(n + 255) / 256, 256, 0, s>>>(w.sumsq[0], n);
-    }
+    const int n_zero = want_sumsq ? (int)(w.sumsq[3] - w.sumsq[0]) + w.sumsq_count[3] : 0;   // the four lists follow one another
 
     int rc = PCM_OK;
     for (int64_t row0 = 0; row0 < w.Mp; row0 += w.Rp) {
@@ -529,7 +480,7 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
         const RowMeta meta{w.meta.token + row0, w.meta.logp_old + row0, w.meta.adv + row0};
         const RowOut out{w.out.term + row0, w.out.ratio + row0, w.out.dlogp + row0, w.out.clipped + row0,
                          w.out.entropy + row0, w.out.coef + row0};
-        rc = launch_gather(sh, io, 2, w.X, row0, Mp, meta, s);
+        rc = launch_gather(sh, io, 2, w.X, row0, Mp, meta, first ? layouts : TransposeList{}, w.sumsq[0], first ? n_zero : 0, s);
         if (rc != PCM_OK) return rc;
         {
             StageTimer t(ST_GEMM_GATE_UP, s);

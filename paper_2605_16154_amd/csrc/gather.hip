@@ -24,36 +24,44 @@ template <>
 __device__ inline uint16_t zero_vec<uint16_t>() { return 0; }
 
 template <typename Vec>
-__global__ __launch_bounds__(kThreads) void gather_rows(
-    const Vec* __restrict__ hidden, const uint8_t* __restrict__ tokens, const float* __restrict__ logp_old,
-    const float* __restrict__ adv, const int32_t* __restrict__ kept_idx, const int32_t* __restrict__ n_kept,
-    int max_chunks, int T, int N, int A, int V, int vec_per_row, int64_t row_offset, int64_t rows_pad,
-    Vec* __restrict__ X, uint8_t* m_token, float* m_logp_old, float* m_adv) {
-    // rows are those of a panel that starts at batch row row_offset; X and the m_ arrays are the panel's
+struct GatherArgs {
+    const Vec* hidden;
+    const uint8_t* tokens;
+    const float *logp_old, *adv;
+    const int32_t *kept_idx, *n_kept;
+    int max_chunks, T, N, A, V, vec_per_row;
+    int64_t row_offset, rows_pad;   // rows are those of a panel that starts at batch row row_offset;
+    Vec* X;                         // X and the metadata arrays are the panel's
+    RowMeta meta;
+};
+
+// Rows [block * kRowsPerBlock, + kRowsPerBlock) of the panel.
+template <typename Vec>
+__device__ inline void gather_rows(const GatherArgs<Vec>& p, int block) {
     __shared__ int64_t src_row[kRowsPerBlock];
-    int nk = *n_kept;
-    nk = nk < 0 ? 0 : (nk > max_chunks ? max_chunks : nk);
-    const int64_t rows_valid = (int64_t)nk * A - row_offset;
-    const int64_t r0 = (int64_t)blockIdx.x * kRowsPerBlock;
-    const int tid = threadIdx.x;
+    const int A = p.A, vec_per_row = p.vec_per_row;
+    const int64_t rows_valid = live_rows(p.n_kept, p.max_chunks, A) - p.row_offset;
+    const int64_t r0 = (int64_t)block * kRowsPerBlock;
+    if (r0 >= (rows_valid + 255) / 256 * 256) return;   // beyond the last live row tile: read by nothing (a quarter of the
+    const int tid = threadIdx.x;                        // copy of a list three quarters full)
     if (tid < kRowsPerBlock) {
         const int64_t r = r0 + tid;
         int64_t src = -1;
         if (r < rows_valid) {
-            const int ci = (int)((r + row_offset) / A), tok = (int)((r + row_offset) % A);
-            int id = kept_idx[ci];
+            const int ci = (int)((r + p.row_offset) / A), tok = (int)((r + p.row_offset) % A);
+            int id = p.kept_idx[ci];
             float a = 0.f;
-            if (id >= 0 && (int64_t)id < (int64_t)T * N) a = adv[id / N];
+            if (id >= 0 && (int64_t)id < (int64_t)p.T * p.N) a = p.adv[id / p.N];
             else id = 0;
             src = (int64_t)id * A + tok;
-            int b = tokens[src];
-            m_token[r] = (uint8_t)(b < V ? b : V - 1);
-            m_logp_old[r] = logp_old[src];
-            m_adv[r] = a;
-        } else if (r < rows_pad) {
-            m_token[r] = 0;
-            m_logp_old[r] = 0.f;
-            m_adv[r] = 0.f;
+            int b = p.tokens[src];
+            p.meta.token[r] = (uint8_t)(b < p.V ? b : p.V - 1);
+            p.meta.logp_old[r] = p.logp_old[src];
+            p.meta.adv[r] = a;
+        } else if (r < p.rows_pad) {
+            p.meta.token[r] = 0;
+            p.meta.logp_old[r] = 0.f;
+            p.meta.adv[r] = 0.f;
         }
         src_row[tid] = src;
     }
@@ -68,7 +76,7 @@ __global__ __launch_bounds__(kThreads) void gather_rows(
             v[u] = zero_vec<Vec>();
             if (e < total) {
                 const int64_t src = src_row[e / vec_per_row];
-                if (src >= 0) v[u] = hidden[src * vec_per_row + e % vec_per_row];
+                if (src >= 0) v[u] = p.hidden[src * vec_per_row + e % vec_per_row];
             }
         }
 #pragma unroll
@@ -76,10 +84,74 @@ __global__ __launch_bounds__(kThreads) void gather_rows(
             const int e = base + u * kThreads;
             if (e < total) {
                 const int64_t r = r0 + e / vec_per_row;
-                if (r < rows_pad) X[r * vec_per_row + e % vec_per_row] = v[u];
+                if (r < p.rows_pad) p.X[r * vec_per_row + e % vec_per_row] = v[u];
             }
         }
     }
+}
+
+// Transposed copies of weights: dst[map(c), r] = src[r, c] for [R, C] bf16 matrices (R, C multiples of 64), a workgroup per
+// 64 x 64 tile.  kStream: non-temporal stores, which leave the memory-side cache to the sources.
+__device__ inline int packed_row(int c, int mode) {
+    if (mode == kPackNone) return c;
+    return (c / 64) * 128 + (c % 64) + (mode == kPackUp ? 64 : 0);
+}
+template <bool kStream>
+__device__ inline void transpose_tile(const TransposeList& list, int block) {
+    __shared__ uint16_t tile[64][66];
+    int which = 0;
+#pragma unroll
+    for (int q = 1; q < TransposeList::kMax; ++q) which += q < list.n && block >= list.first[q] ? 1 : 0;
+    const TransposeJob job = list.job[which];
+    block -= list.first[which];
+    const int tiles_c = job.C / 64;
+    const int r0 = block / tiles_c * 64, c0 = block % tiles_c * 64;
+    const uint16_t* const src = reinterpret_cast<const uint16_t*>(job.src);
+    uint16_t* const dst = reinterpret_cast<uint16_t*>(job.dst);
+    const int t = threadIdx.x, tr = t >> 4, tv = t & 15;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int row = tr + 16 * q;
+        const uint2 v = *reinterpret_cast<const uint2*>(src + (int64_t)(r0 + row) * job.C + c0 + tv * 4);
+        tile[row][tv * 4 + 0] = (uint16_t)(v.x & 0xFFFF);
+        tile[row][tv * 4 + 1] = (uint16_t)(v.x >> 16);
+        tile[row][tv * 4 + 2] = (uint16_t)(v.y & 0xFFFF);
+        tile[row][tv * 4 + 3] = (uint16_t)(v.y >> 16);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int c = tr + 16 * q;
+        uint2 v;
+        v.x = (uint32_t)tile[tv * 4 + 0][c] | ((uint32_t)tile[tv * 4 + 1][c] << 16);
+        v.y = (uint32_t)tile[tv * 4 + 2][c] | ((uint32_t)tile[tv * 4 + 3][c] << 16);
+        uint16_t* const to = dst + (int64_t)packed_row(c0 + c, job.mode) * job.R + r0 + tv * 4;
+        if (kStream) __builtin_nontemporal_store((uint64_t)v.x | (uint64_t)v.y << 32, reinterpret_cast<uint64_t*>(to));
+        else *reinterpret_cast<uint2*>(to) = v;
+    }
+}
+template <bool kStream>
+__global__ __launch_bounds__(kThreads) void transpose_weights(TransposeList list) { transpose_tile<kStream>(list, blockIdx.x); }
+
+// What a step does before its first product, in one launch: the weight layouts (if the caller keeps none), the gather of the
+// panel's rows, and zeros in a list of fp64 slots.  The three touch different memory, and of a small head each takes a few
+// microseconds, which is what a launch costs.  At 2072 rows of 512 -> 768 -> 512 -> 256: five launches of
+// 15.4 us -> one of 5.3.  The re-layout by itself 13.2 -> 6.4 us at 512 -> 3328, 98 -> 87 at 4096 -> 11008.
+struct ZeroSlots {
+    double* p;
+    int n;
+};
+template <typename Vec, bool kLayouts>
+__global__ __launch_bounds__(kThreads) void prepare_step(GatherArgs<Vec> gather, int gather_blocks, TransposeList list, ZeroSlots zero) {
+    int block = blockIdx.x;
+    if (block < gather_blocks) return gather_rows(gather, block);
+    block -= gather_blocks;
+    if (kLayouts) {
+        if (block < list.blocks) return transpose_tile<false>(list, block);
+        block -= list.blocks;
+    }
+    const int i = block * kThreads + (int)threadIdx.x;
+    if (i < zero.n) zero.p[i] = 0.0;
 }
 
 // One workgroup; lane-strided fp64 partials combined by a fixed tree, so the result does not
@@ -367,23 +439,31 @@ int launch_zero_unlisted(const ActorShape& sh, const ActorIO& io, const uint8_t*
 }
 
 int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void* X, int64_t row_offset, int64_t rows_pad,
-                  RowMeta meta, hipStream_t s) {
+                  RowMeta meta, const TransposeList& layouts, double* zero, int n_zero, hipStream_t s) {
     StageTimer t(ST_GATHER, s);
     const int64_t row_bytes = (int64_t)sh.d * elem_bytes;
     const unsigned blocks = (unsigned)ceil_div64(rows_pad, kRowsPerBlock);
+    const unsigned grid = (unsigned)layouts.blocks + blocks + (unsigned)ceil_div(n_zero, kThreads);
     const bool aligned16 = row_bytes % 16 == 0 && (reinterpret_cast<uintptr_t>(io.hidden) & 15u) == 0 &&
                            (reinterpret_cast<uintptr_t>(X) & 15u) == 0;
-#define PCM_GATHER(Vec, vpr)                                                                             \
-    gather_rows<Vec><<<blocks, kThreads, 0, s>>>(static_cast<const Vec*>(io.hidden), io.tokens,          \
-                                                 io.logp_old, io.adv, io.kept_idx, io.n_kept,            \
-                                                 sh.max_chunks, sh.T, sh.N, sh.A, sh.V, (int)(vpr),      \
-                                                 row_offset, rows_pad, static_cast<Vec*>(X), meta.token, \
-                                                 meta.logp_old, meta.adv)
-    if (aligned16) PCM_GATHER(uint4, row_bytes / 16);
-    else if (elem_bytes == 4) PCM_GATHER(uint32_t, sh.d);
-    else PCM_GATHER(uint16_t, sh.d);
-#undef PCM_GATHER
+    auto launch = [&](auto vec, int64_t vec_per_row) {
+        using Vec = decltype(vec);
+        const GatherArgs<Vec> args{static_cast<const Vec*>(io.hidden), io.tokens, io.logp_old, io.adv, io.kept_idx, io.n_kept,
+                                   sh.max_chunks, sh.T, sh.N, sh.A, sh.V, (int)vec_per_row, row_offset, rows_pad,
+                                   static_cast<Vec*>(X), meta};
+        if (layouts.n > 0) prepare_step<Vec, true><<<grid, kThreads, 0, s>>>(args, (int)blocks, layouts, ZeroSlots{zero, n_zero});
+        else prepare_step<Vec, false><<<grid, kThreads, 0, s>>>(args, (int)blocks, layouts, ZeroSlots{zero, n_zero});
+    };
+    if (aligned16) launch(uint4{}, row_bytes / 16);
+    else if (elem_bytes == 4) launch(uint32_t{}, sh.d);
+    else launch(uint16_t{}, sh.d);
     return launch_status();
+}
+
+void launch_transposes(const TransposeList& list, bool stream, hipStream_t s) {
+    StageTimer t(ST_WEIGHT_LAYOUT, s);
+    if (stream) transpose_weights<true><<<(unsigned)list.blocks, kThreads, 0, s>>>(list);
+    else transpose_weights<false><<<(unsigned)list.blocks, kThreads, 0, s>>>(list);
 }
 
 int launch_loss_reduce(const ActorShape& sh, const ActorIO& io, RowOut out, const SumsqLists& lists, hipStream_t s) {
