@@ -113,10 +113,9 @@ int launch_loss_reduce(const ActorShape& sh, const ActorIO& io, RowOut out, cons
 int launch_chunk_ratio(const ActorShape& sh, const ActorIO& io, RowMeta meta, RowOut out, int64_t row_offset,
                        int64_t rows_pad, hipStream_t s);
 
-// dz[r, :] = coef[r] * dz[r, :] (+ extra[r, :] if extra is given) for the live rows r (V columns each);
-// elem_bytes is 2 (bf16) or 4 (fp32).
-int launch_scale_rows(const ActorShape& sh, const ActorIO& io, void* dz, const void* extra, const float* coef,
-                      int64_t row_offset, int64_t rows_pad, int elem_bytes, hipStream_t s);
+// fp32 path: dz[r, :] = coef[r] * dz[r, :] (+ extra[r, :] if extra is given) for the live rows r (V columns each).
+int launch_scale_rows_f32(const ActorShape& sh, const ActorIO& io, float* dz, const float* extra, const float* coef,
+                          int64_t rows, hipStream_t s);
 
 // Backward pass over the rows that carry a gradient only (bf16 path).  A kernel lists the panel's rows whose factor
 // in dz is non-zero and writes, to device memory, what the backward products then read: their row count and which
@@ -132,17 +131,15 @@ struct LivePlan {
     int32_t listed;    // 1: the products run over the listed rows (operands copied), 0: over all live rows
 };
 // A row carries a gradient when the clip does not cut it (RowOut::clipped) and its advantage and chunk weight are
-// non-zero; clipped and adv are the panel's parts of those arrays.
-int launch_live_row_list(const ActorShape& sh, const ActorIO& io, const uint8_t* clipped, const float* adv,
-                         int64_t row_offset, int64_t rows_pad, const LiveSources& whole, const LiveSources& listed,
-                         int32_t* idx, LivePlan* plan, hipStream_t s);
-// dst[m] = src[idx[m]] (rows of row_bytes bytes, a multiple of 16) when the plan says listed; else nothing.
-int launch_gather_listed(const void* src, const int32_t* idx, const LivePlan* plan, int64_t rows_pad, int64_t row_bytes,
-                         void* dst, hipStream_t s);
-// Zero rows of the panel's part of dX (rows_in_dX rows exist) wherever the listed products write nothing.
-int launch_zero_unlisted(const ActorShape& sh, const ActorIO& io, const uint8_t* clipped, const float* adv,
-                         int64_t row_offset, int64_t rows_pad, int64_t rows_in_dX, int64_t row_bytes, void* dX,
-                         hipStream_t s);
+// non-zero; clipped and adv are the panel's parts of those arrays, counts the rows with a gradient in each of the panel's
+// blocks of kListBlock rows (up to the last live one).  Writes the plan, the list idx and, when the plan says listed, the
+// listed rows of the four sources (rows of row_bytes, a multiple of 16; 0: not wanted) with zero rows up to the end of the
+// last row tile.  Rows of dX (or null; rows_in_dX rows exist) that the listed products do not write are cleared.
+constexpr int kListBlock = 16;
+int launch_live_rows(const ActorShape& sh, const ActorIO& io, const uint8_t* clipped, const float* adv, const int32_t* counts,
+                     int64_t row_offset, int64_t rows_pad, const LiveSources& whole, const LiveSources& listed,
+                     const int64_t (&row_bytes)[LiveSources::kCount], void* dX, int64_t rows_in_dX, int32_t* idx, LivePlan* plan,
+                     hipStream_t s);
 
 // Number of live rows from the device-side kept count.
 __device__ inline int64_t live_rows(const int32_t* n_kept, int max_chunks, int A) {

@@ -120,7 +120,17 @@ struct LossRowsArgs {
     bf16* dz_extra;          // [rows_pad, 256]: entropy part, per-chunk ratio only
     float* logp_out;         // may be nullptr
     RowOut out;
+    int32_t* live_count;     // [rows_pad / kLossRows] rows with a gradient, or nullptr
 };
+static_assert(kLossRows == kListBlock, "a workgroup counts one block of the list");
+// The number of rows with a gradient among the workgroup's 16 (all of whose threads call this; `has`: of a thread's row).
+__device__ inline void count_live_rows(bool has, int32_t* to) {
+    __shared__ int32_t wave_count[kLossThreads / kWave];
+    const uint64_t votes = __ballot(has);
+    if (threadIdx.x % kWave == 0) wave_count[threadIdx.x / kWave] = __popcll(votes) / 16;
+    __syncthreads();
+    if (threadIdx.x == 0) *to = wave_count[0] + wave_count[1] + wave_count[2] + wave_count[3];
+}
 __device__ inline float sum16(float x) {
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
@@ -132,7 +142,7 @@ __global__ __launch_bounds__(kLossThreads) void loss_rows_bf16(LossRowsArgs p) {
     const int m = blockIdx.x * kLossRows + (int)(threadIdx.x >> 4), lane = threadIdx.x & 15;
     // rows up to the end of the last live row tile are written (as rows without a gradient); nothing reads later ones
     const int64_t limit = rows_live <= 0 ? 0 : (rows_live + kTileM - 1) / kTileM * kTileM;
-    if (m >= limit || m >= p.rows_pad) return;                  // uniform over the 16 lanes of a row
+    if (m >= limit || m >= p.rows_pad) return;                  // uniform over the workgroup: both are multiples of 16
     const float scale = objective_scale(p.opt, rows_batch);
     const float* src = p.parts + (size_t)m * 256 + lane * 4;
     f32x4 z[4];                                                 // z[q][t]: column 64 q + 4 lane + t
@@ -178,6 +188,8 @@ __global__ __launch_bounds__(kLossThreads) void loss_rows_bf16(LossRowsArgs p) {
         }
         if (p.logp_out && live) p.logp_out[m] = lp;
     }
+    if (p.live_count != nullptr)
+        count_live_rows(live && lr.clipped == 0 && p.adv_row[m] != 0.f && w != 0.f, p.live_count + blockIdx.x);
     if (p.dz == nullptr) return;
     const float coef = live ? (p.opt.chunk_ratio ? 1.f : lr.coef) : 0.f;
     const float ec = live ? p.opt.entropy_coef * scale : 0.f;
@@ -197,6 +209,43 @@ __global__ __launch_bounds__(kLossThreads) void loss_rows_bf16(LossRowsArgs p) {
         } else {
             *reinterpret_cast<bf16x4*>(p.dz + at) = to_bf16x4(g[0] + h[0], g[1] + h[1], g[2] + h[2], g[3] + h[3]);
         }
+    }
+}
+
+// Per-chunk ratio: dz[r, :] = coef[r] dz[r, :] (+ extra[r, :]) over the live rows of a panel, 16 lanes per row as above, and
+// the counts of rows with a gradient, which are known only now.
+struct ScaleRowsArgs {
+    bf16* dz;
+    const bf16* extra;               // or nullptr
+    const float *coef, *adv_row;
+    const uint8_t* clipped;
+    const float* chunk_weight;       // by chunk of the batch, or nullptr
+    const int32_t* n_kept;
+    int max_chunks, A, row_offset, rows_pad;
+    int32_t* live_count;             // or nullptr
+};
+__global__ __launch_bounds__(kLossThreads) void scale_rows_bf16(ScaleRowsArgs p) {
+    const int64_t rows = min(live_rows(p.n_kept, p.max_chunks, p.A) - p.row_offset, (int64_t)p.rows_pad);
+    if ((int64_t)blockIdx.x * kLossRows >= rows) return;        // uniform
+    const int m = blockIdx.x * kLossRows + (int)(threadIdx.x >> 4), lane = threadIdx.x & 15;
+    const bool live = m < rows;
+    if (p.live_count != nullptr) {
+        const int at = live ? m : blockIdx.x * kLossRows;
+        const float w = p.chunk_weight != nullptr ? p.chunk_weight[(at + p.row_offset) / p.A] : 1.f;
+        count_live_rows(live && p.clipped[at] == 0 && p.adv_row[at] != 0.f && w != 0.f, p.live_count + blockIdx.x);
+    }
+    if (!live) return;
+    const float coef = p.coef[m];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int64_t at = (int64_t)m * 256 + q * 128 + lane * 8;
+        const bf16x8 v = *reinterpret_cast<const bf16x8*>(p.dz + at);
+        bf16x8 e = {};
+        if (p.extra != nullptr) e = *reinterpret_cast<const bf16x8*>(p.extra + at);
+        bf16x8 r;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) r[t] = (__bf16)__builtin_fmaf(coef, (float)v[t], (float)e[t]);
+        *reinterpret_cast<bf16x8*>(p.dz + at) = r;
     }
 }
 
@@ -236,8 +285,9 @@ struct Bf16Workspace {
     bf16 *X, *fu, *fv, *a, *y, *dz, *dz_extra;   // one panel each; fu, fv: SwiGLU derivative factors, then du, dv
     bf16 *a_lo, *y_lo;                           // per-chunk ratio: rounding remainders of a and y
     bf16* dy;
-    bf16 *du, *xy, *dzc;   // backward over listed rows: du (before that the listed rows of a), the listed rows of y and
-                           // later of X, the listed rows of dz; dv takes the place of a
+    bf16 *du, *yc, *Xc, *dzc;   // backward over listed rows: du (before that the listed rows of a), the listed rows of y, X
+                                // and dz; dv takes the place of a
+    int32_t* live_count;   // [Rp / 16] rows with a gradient by block of 16
     int32_t* live_idx;     // [Rp] the listed rows
     LivePlan* plan;        // null: backward over all rows
     double* sumsq[4];      // sums of squares of the final dWg, dWu, dWd, dWo by workgroup (null: not asked for)
@@ -290,8 +340,10 @@ Bf16Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool grads, const 
     if (bwd) w.dy = c.take<bf16>(Rp * d);
     if (lists_live_rows(opt, bwd, composed)) {
         w.du = c.take<bf16>(Rp * ff);
-        w.xy = c.take<bf16>(Rp * d);
+        w.yc = c.take<bf16>(Rp * d);
+        w.Xc = c.take<bf16>(Rp * d);
         w.dzc = c.take<bf16>(Rp * V);
+        w.live_count = c.take<int32_t>(Rp / kListBlock);
         w.live_idx = c.take<int32_t>(Rp);
         w.plan = c.take<LivePlan>(1);
     }
@@ -516,15 +568,17 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
             }
             loss_rows_bf16<<<(unsigned)(Mp / kLossRows), kLossThreads, 0, s>>>(LossRowsArgs{
                 w.parts, n_parts, n_z, meta.token, meta.logp_old, meta.adv, io.n_kept, sh.max_chunks, sh.A, (int)row0, Mp,
-                io.opt, bwd ? w.dz : nullptr, w.dz_extra, io.logp_out ? io.logp_out + row0 : nullptr, out});
+                io.opt, bwd ? w.dz : nullptr, w.dz_extra, io.logp_out ? io.logp_out + row0 : nullptr, out,
+                io.opt.chunk_ratio ? nullptr : w.live_count});
         }
         if (io.opt.chunk_ratio) {
             rc = launch_chunk_ratio(sh, io, meta, out, row0, Mp, s);
             if (rc != PCM_OK) return rc;
             if (bwd) {
-                rc = launch_scale_rows(sh, io, w.dz, io.opt.entropy_coef != 0.f ? w.dz_extra : nullptr, out.coef, row0, Mp,
-                                       2, s);
-                if (rc != PCM_OK) return rc;
+                StageTimer t(ST_REDUCE, s);
+                scale_rows_bf16<<<(unsigned)(Mp / kLossRows), kLossThreads, 0, s>>>(
+                    ScaleRowsArgs{w.dz, io.opt.entropy_coef != 0.f ? w.dz_extra : nullptr, out.coef, meta.adv, out.clipped,
+                                  io.opt.chunk_weight, io.n_kept, sh.max_chunks, sh.A, (int)row0, Mp, w.live_count});
             }
         }
         if (!bwd) continue;
@@ -534,15 +588,13 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
             const bf16* const* const src = reinterpret_cast<const bf16* const*>(w.plan->src);
             const KeptRows lr{&w.plan->n_rows, Mp, 1, 0};
             bf16* const dv = w.a;                       // free once the listed rows of a are copied
-            {
-                StageTimer t(ST_LIVE_ROWS, s);
-                const LiveSources whole{{w.dz, w.y, w.a, w.X}}, listed{{w.dzc, w.xy, w.du, w.xy}};
-                rc = launch_live_row_list(sh, io, out.clipped, meta.adv, row0, Mp, whole, listed, w.live_idx, w.plan, s);
-                if (rc != PCM_OK) return rc;
-                launch_gather_listed(w.dz, w.live_idx, w.plan, Mp, (int64_t)V * 2, w.dzc, s);
-                if (grads) launch_gather_listed(w.y, w.live_idx, w.plan, Mp, (int64_t)d * 2, w.xy, s);
-                if (grads) launch_gather_listed(w.a, w.live_idx, w.plan, Mp, (int64_t)ff * 2, w.du, s);
-            }
+            const int64_t rows_left = sh.rows_max() - row0;
+            bf16* const dX = io.dX ? static_cast<bf16*>(io.dX) + row0 * d : nullptr;
+            const LiveSources whole{{w.dz, w.y, w.a, w.X}}, listed{{w.dzc, w.yc, w.du, w.Xc}};
+            const int64_t both = grads ? 2 : 0;         // without weight gradients only dz is read by row of the list
+            rc = launch_live_rows(sh, io, out.clipped, meta.adv, w.live_count, row0, Mp, whole, listed, {2 * V, both * d, both * ff, both * d},
+                                  dX, rows_left < Mp ? rows_left : Mp, w.live_idx, w.plan, s);
+            if (rc != PCM_OK) return rc;
             {
                 StageTimer t(ST_GEMM_DY, s);
                 GemmProblem p = problem(w.dz, V, Wo, V, Mp, d, V, lr, kRowsAreM);                                // dy = dz Wo^T
@@ -564,10 +616,6 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                             EpiSwigluBackward<true>{w.fu, w.fv, ff, w.live_idx, w.du, dv}, s);
             }
             if (grads) {
-                {
-                    StageTimer t(ST_LIVE_ROWS, s);
-                    launch_gather_listed(w.X, w.live_idx, w.plan, Mp, (int64_t)d * 2, w.xy, s);
-                }
                 GemmProblem p = problem(w.X, d, w.du, ff, d, ff, Mp, lr, kRowsAreK);                             // dWg (+)= X^T du
                 p.A_sel = src + LiveSources::kX;
                 launch_weight_grad(p, io.dWg, w.parts, !first, sq[0], ST_GEMM_DWG_DWU, s);
@@ -575,15 +623,7 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                 p.B2 = dv;
                 launch_weight_grad(p, io.dWu, w.parts, !first, sq[1], ST_GEMM_DWG_DWU, s);
             }
-            if (io.dX) {
-                const int64_t rows_left = sh.rows_max() - row0;
-                bf16* const dX = static_cast<bf16*>(io.dX) + row0 * d;
-                {
-                    StageTimer t(ST_LIVE_ROWS, s);
-                    rc = launch_zero_unlisted(sh, io, out.clipped, meta.adv, row0, Mp, rows_left < Mp ? rows_left : Mp, (int64_t)d * 2, dX,
-                                              s);
-                    if (rc != PCM_OK) return rc;
-                }
+            if (dX) {
                 StageTimer t(ST_GEMM_DX, s);
                 GemmProblem p = problem(w.du, ff, Wg, ff, Mp, d, ff, lr, kRowsAreM);                             // dX = du Wg^T + dv Wu^T
                 p.A2 = dv; p.B2 = Wu; p.K2 = ff;

@@ -566,7 +566,7 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t
         rc = launch_chunk_ratio(sh, io, w.meta, w.out, 0, M, s);
         if (rc != PCM_OK) return rc;
         if (bwd) {
-            rc = launch_scale_rows(sh, io, w.z, io.opt.entropy_coef != 0.f ? w.z_extra : nullptr, w.out.coef, 0, M, 4, s);
+            rc = launch_scale_rows_f32(sh, io, w.z, io.opt.entropy_coef != 0.f ? w.z_extra : nullptr, w.out.coef, M, s);
             if (rc != PCM_OK) return rc;
         }
     }

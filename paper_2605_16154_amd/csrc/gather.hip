@@ -240,201 +240,166 @@ __global__ __launch_bounds__(kRatioThreads) void chunk_ratio_rows(const float* _
     }
 }
 
-template <typename T>
-__device__ inline float to_f32(T x);
-template <>
-__device__ inline float to_f32<float>(float x) { return x; }
-template <>
-__device__ inline float to_f32<bf16>(bf16 x) { return __bfloat162float(x); }
-template <typename T>
-__device__ inline T from_f32(float x);
-template <>
-__device__ inline float from_f32<float>(float x) { return x; }
-template <>
-__device__ inline bf16 from_f32<bf16>(float x) { return __float2bfloat16(x); }
-
 // Rows [0, live rows) only: rows beyond them hold zeros (or, in row tiles that the logit product
 // skipped, nothing) and are not read by anything downstream.
-template <typename T>
-__global__ __launch_bounds__(256) void scale_rows(T* __restrict__ dz, const T* __restrict__ extra,
-                                                   const float* __restrict__ coef, const int32_t* __restrict__ n_kept,
-                                                   int max_chunks, int A, int64_t row_offset, int64_t rows_pad, int V) {
-    int64_t rows = live_rows(n_kept, max_chunks, A) - row_offset;
-    rows = rows < rows_pad ? rows : rows_pad;
+__global__ __launch_bounds__(256) void scale_rows_f32(float* __restrict__ dz, const float* __restrict__ extra,
+                                                      const float* __restrict__ coef, const int32_t* __restrict__ n_kept,
+                                                      int max_chunks, int A, int64_t rows_max, int V) {
+    const int64_t live = live_rows(n_kept, max_chunks, A), rows = live < rows_max ? live : rows_max;
     const int64_t n = rows * V;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        float x = coef[i / V] * to_f32<T>(dz[i]);
-        if (extra) x += to_f32<T>(extra[i]);
-        dz[i] = from_f32<T>(x);
+        float x = coef[i / V] * dz[i];
+        if (extra) x += extra[i];
+        dz[i] = x;
     }
 }
 
-// Whether panel row r (batch row r + row_offset) carries a gradient.
-struct RowGradient {
+// Rows whose gradient factor is zero (ratio cut by the clip, zero advantage, zero weight) have an all-zero row of dz and
+// add nothing to any gradient.  This launch lists the panel's other rows in order, decides whether the backward products run
+// over that list or over all live rows, copies the listed rows of up to four matrices into dense ones, and clears the rows of
+// dX that the products will not write.
+//
+// The kernels that know a row's factor leave the number of rows with a gradient in every block of kListBlock rows; a
+// workgroup here owns one such block, or a quarter of one where the blocks are few, and adds up the counts before it (and all
+// of them, for the decision) by itself, so there is no launch that only makes the list.  The copies are bound by memory: a
+// workgroup moves its listed rows as one contiguous stretch of the dense matrix, 16 bytes per thread and eight in flight.
+// (A wavefront per row instead: all of them start in the same column of rows a power of two apart, 430 -> 650 us.)  The list, four copies
+// and the zeros, six launches against this one: 2072 rows of 512 and 768 16.9 -> 3.5 us, 43,008 rows of 4096 and 11008
+// (24 thousand listed) 429 -> 422 us.
+constexpr int kListThreads = 256, kListWaves = kListThreads / kWave;
+constexpr int kListParts = 4;      // workgroups per block where the blocks are few
+struct ListArgs {
     const uint8_t* clipped;
     const float* adv;
-    const float* chunk_weight;   // by chunk of the batch, or null
+    const float* chunk_weight;      // by chunk of the batch, or null
+    const int32_t* counts;          // [rows_pad / kListBlock]
+    const int32_t* n_kept;
+    int max_chunks, A;
     int64_t row_offset;
-    int A;
-    __device__ bool operator()(int r) const {      // all loads unconditional, so that a loop of calls can overlap them
-        const uint8_t cut = clipped[r];
-        const float a = adv[r];
-        const float w = chunk_weight != nullptr ? chunk_weight[(r + row_offset) / A] : 1.f;
-        return cut == 0 && a != 0.f && w != 0.f;
-    }
+    int rows_pad, rows_in_dX, dX_vecs;
+    uint4* dX;                      // or null
+    LiveSources whole, listed;
+    int row_vecs[LiveSources::kCount];   // 16-byte units per row; 0: not copied
+    int32_t* idx;
+    LivePlan* plan;
+    int parts;                      // workgroups per block: 1 or kListParts
 };
-
-// Rows whose gradient factor is zero (ratio cut by the clip, zero advantage, zero weight) have an all-zero row of
-// dz and add nothing to any gradient.  One workgroup lists the panel's rows with a non-zero factor, in order, and
-// decides whether the backward products run over that list or over all live rows.
-// Rows are swept 1024 at a time (thread t looks at row 1024 q + t, so reads are contiguous); a sweep of kListRounds
-// such rounds first counts the rows with a gradient per round and wavefront, turns the counts into positions with
-// one scan, then writes the row numbers.
-constexpr int kListRounds = 64;   // one bit each in a 64-bit word per thread
-__global__ __launch_bounds__(1024) void live_row_list(RowGradient has_gradient, const int32_t* __restrict__ n_kept,
-                                                       int max_chunks, int A, int64_t row_offset, int rows_pad,
-                                                       LiveSources whole, LiveSources listed, int32_t* __restrict__ idx,
-                                                       LivePlan* __restrict__ plan) {
-    __shared__ int32_t count[kListRounds * 16];   // [round][wavefront], then the position of its first listed row
-    __shared__ int32_t wave_sum[16];
-    int64_t rows64 = live_rows(n_kept, max_chunks, A) - row_offset;
-    const int rows = (int)(rows64 < 0 ? 0 : (rows64 > rows_pad ? rows_pad : rows64));
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    int total = 0;
-    for (int sweep0 = 0; sweep0 < rows; sweep0 += kListRounds * 1024) {
-        // this thread's rows of the sweep, one bit per round; read first (independent loads, many in flight), the
-        // wavefront votes afterwards
-        uint64_t mine_bits = 0;
-        const int rounds = min(kListRounds, (rows - sweep0 + 1023) / 1024);     // (2072 rows: 16 -> 4.4 us against always all)
-        count[t] = 0;
-        __syncthreads();
-#pragma unroll 8
-        for (int q = 0; q < rounds; ++q) {
-            const int r = sweep0 + q * 1024 + t;
-            const bool g = has_gradient(r < rows ? r : rows - 1);
-            if (r < rows && g) mine_bits |= 1ull << q;
-        }
-        for (int q = 0; q < rounds; ++q) {
-            const uint64_t mask = __ballot((mine_bits >> q) & 1ull);
-            if (lane == 0) count[q * 16 + wave] = __popcll(mask);
-        }
-        __syncthreads();
-        const int mine = count[t];                       // entry t = (round t / 16, wavefront t % 16): row order
-        int incl = mine;
+// Rows from[0 .. n) of src -> dst[0 .. n) (dense), rows of `vecs` units, by the whole workgroup.
+__device__ __forceinline__ void copy_rows(const uint4* __restrict__ src, uint4* __restrict__ dst, int vecs, const int32_t* from, int n) {
+    constexpr int kUnroll = 8;
+    const int total = n * vecs;
+    for (int base = threadIdx.x; base < total; base += kListThreads * kUnroll) {
+        uint4 v[kUnroll];
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int up = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += up;
+        for (int u = 0; u < kUnroll; ++u) {
+            const int el = base + u * kListThreads;
+            v[u] = make_uint4(0, 0, 0, 0);
+            if (el < total) {
+                const int row = (uint32_t)el / (uint32_t)vecs;
+                v[u] = src[(int64_t)from[row] * vecs + (el - row * vecs)];
+            }
         }
-        if (lane == 63) wave_sum[wave] = incl;
-        __syncthreads();
-        int before = 0, sweep_total = 0;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int v = wave_sum[q];
-            before += q < wave ? v : 0;
-            sweep_total += v;
+        for (int u = 0; u < kUnroll; ++u) {
+            const int el = base + u * kListThreads;
+            if (el < total) dst[el] = v[u];
         }
-        count[t] = total + before + incl - mine;
-        __syncthreads();
-        for (int q = 0; q < rounds; ++q) {
-            const bool live = (mine_bits >> q) & 1ull;
-            const uint64_t mask = __ballot(live);
-            if (live) idx[count[q * 16 + wave] + __popcll(mask & ((1ull << lane) - 1ull))] = sweep0 + q * 1024 + t;
-        }
-        total += sweep_total;
-        __syncthreads();
+    }
+}
+__global__ __launch_bounds__(kListThreads) void list_live_rows(ListArgs p) {
+    __shared__ int part[2][kListWaves];
+    __shared__ int32_t from[kListBlock];
+    const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+    const int block = blockIdx.x / p.parts, of_block = blockIdx.x % p.parts;
+    const int64_t rows64 = live_rows(p.n_kept, p.max_chunks, p.A) - p.row_offset;
+    const int rows = (int)(rows64 < 0 ? 0 : (rows64 > p.rows_pad ? p.rows_pad : rows64));
+    const int blocks = (rows + kListBlock - 1) / kListBlock, tile_end = (rows + 255) / 256 * 256;
+    const int panel_blocks = p.rows_pad / kListBlock;
+    if (block > 0 && block < panel_blocks && block * kListBlock >= tile_end) return;   // uniform; the first one writes the plan
+    int all = 0, before = 0;
+#pragma unroll 4
+    for (int i = t; i < blocks; i += kListThreads) {
+        const int c = p.counts[i];
+        all += c;
+        before += i < block ? c : 0;
+    }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        all += __shfl_xor(all, o, kWave);
+        before += __shfl_xor(before, o, kWave);
+    }
+    if (lane == 0) {
+        part[0][wave] = all;
+        part[1][wave] = before;
+    }
+    __syncthreads();
+    all = before = 0;
+#pragma unroll
+    for (int q = 0; q < kListWaves; ++q) {
+        all += part[0][q];
+        before += part[1][q];
     }
     // the list pays once the rows it drops outweigh the copies it needs: at least one row in sixteen
-    const bool use_list = (int64_t)(rows - total) * 16 >= rows && rows > 0;
-    const int n = use_list ? total : rows;
-    if (!use_list)
-        for (int r = t; r < rows; r += 1024) idx[r] = r;
-    for (int m = n + t; m < (n + 255) / 256 * 256; m += 1024) idx[m] = -1;   // up to the end of the last row tile
-    if (t == 0) {
-        plan->n_rows = n;
-        plan->listed = use_list ? 1 : 0;
-        for (int q = 0; q < LiveSources::kCount; ++q) plan->src[q] = use_list ? listed.p[q] : whole.p[q];
+    const bool use_list = (int64_t)(rows - all) * 16 >= rows && rows > 0;
+    const int n = use_list ? all : rows;
+    if (blockIdx.x == 0 && t == 0) {
+        p.plan->n_rows = n;
+        p.plan->listed = use_list ? 1 : 0;
+        for (int q = 0; q < LiveSources::kCount; ++q) p.plan->src[q] = use_list ? p.listed.p[q] : p.whole.p[q];
     }
-}
-
-// dst[m] = src[idx[m]] for the listed rows, zero rows from there to the end of the last row tile; nothing when
-// the backward products run over all live rows.  Rows are row_vecs 16-byte units long; a workgroup moves blocks of
-// kRowsPerBlock rows, striding over the blocks by the grid.
-__global__ __launch_bounds__(kThreads) void gather_listed_rows(const uint4* __restrict__ src, const int32_t* __restrict__ idx,
-                                                               const LivePlan* __restrict__ plan, int row_vecs,
-                                                               uint4* __restrict__ dst) {
-    __shared__ int32_t src_row[kRowsPerBlock];
-    if (!plan->listed) return;
-    const int limit = (plan->n_rows + 255) / 256 * 256;
-    const int tid = threadIdx.x;
-    const int total = kRowsPerBlock * row_vecs;
-    constexpr int kUnroll = 8;
-    for (int r0 = blockIdx.x * kRowsPerBlock; r0 < limit; r0 += gridDim.x * kRowsPerBlock) {
-        __syncthreads();
-        if (tid < kRowsPerBlock) src_row[tid] = idx[r0 + tid];
-        __syncthreads();
-        for (int base = tid; base < total; base += kThreads * kUnroll) {
-            uint4 v[kUnroll];
+    if (block >= panel_blocks) {                        // zero rows from the end of the list to the end of its last row tile
+        const int m0 = n + (block - panel_blocks) * kListBlock + of_block * (kListBlock / p.parts);
+        const int pad = min((n + 255) / 256 * 256 - m0, kListBlock / p.parts);
+        if (t < pad) p.idx[m0 + t] = -1;
+        if (!use_list) return;
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                const int el = base + u * kThreads;
-                v[u] = make_uint4(0, 0, 0, 0);
-                if (el < total) {
-                    const int row = src_row[el / row_vecs];
-                    if (row >= 0) v[u] = src[(int64_t)row * row_vecs + el % row_vecs];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                const int el = base + u * kThreads;
-                if (el < total) dst[(int64_t)(r0 + el / row_vecs) * row_vecs + el % row_vecs] = v[u];
-            }
+        for (int q = 0; q < LiveSources::kCount; ++q) {
+            uint4* const dst = static_cast<uint4*>(const_cast<void*>(p.listed.p[q])) + (int64_t)m0 * p.row_vecs[q];
+            for (int at = t; at < pad * p.row_vecs[q]; at += kListThreads) dst[at] = make_uint4(0, 0, 0, 0);
         }
+        return;
     }
-}
-
-// Zero rows of dX for the panel rows the listed products do not write: rows without a gradient, and the rows
-// between the live rows and the end of their row tile (as far as dX has them).
-__global__ __launch_bounds__(kThreads) void zero_unlisted_rows(RowGradient has_gradient,
-                                                               const int32_t* __restrict__ n_kept, int max_chunks, int A,
-                                                               int64_t row_offset, int rows_pad, int rows_in_dX,
-                                                               int row_vecs, uint4* __restrict__ dX) {
-    int64_t rows64 = live_rows(n_kept, max_chunks, A) - row_offset;
-    const int rows = (int)(rows64 < 0 ? 0 : (rows64 > rows_pad ? rows_pad : rows64));
-    const int limit = min(rows_in_dX, (rows + 255) / 256 * 256);
-    for (int r = blockIdx.x; r < limit; r += gridDim.x) {
-        if (r < rows && has_gradient(r)) continue;
-        for (int c = threadIdx.x; c < row_vecs; c += kThreads) dX[(int64_t)r * row_vecs + c] = make_uint4(0, 0, 0, 0);
+    const int r0 = block * kListBlock, q = r0 + lane % kListBlock;     // the block's flags, by every wavefront alike
+    const bool in = q < rows;
+    const int at = in ? q : r0 < rows ? rows - 1 : 0;                  // all loads unconditional
+    const uint8_t cut = p.clipped[at];
+    const float a = p.adv[at];
+    const float w = p.chunk_weight != nullptr && rows > 0 ? p.chunk_weight[(at + p.row_offset) / p.A] : 1.f;
+    const uint32_t mask = (uint32_t)__ballot(in && cut == 0 && a != 0.f && w != 0.f) & ((1u << kListBlock) - 1u);
+    const int listed = __popc(mask), k0 = listed * of_block / p.parts, k1 = listed * (of_block + 1) / p.parts;
+    if (t < kListBlock) {
+        const int k = __popc(mask & ((1u << t) - 1u));
+        if (((mask >> t) & 1u) != 0) from[k] = r0 + t;
+        if (use_list && ((mask >> t) & 1u) != 0 && of_block == 0) p.idx[before + k] = r0 + t;
+        if (!use_list && r0 + t < rows && of_block == 0) p.idx[r0 + t] = r0 + t;
     }
+    __syncthreads();
+    if (use_list)
+#pragma unroll
+        for (int k = 0; k < LiveSources::kCount; ++k)
+            copy_rows(static_cast<const uint4*>(p.whole.p[k]),
+                      static_cast<uint4*>(const_cast<void*>(p.listed.p[k])) + (int64_t)(before + k0) * p.row_vecs[k], p.row_vecs[k], from + k0,
+                      k1 - k0);
+    if (p.dX == nullptr) return;
+    for (int r = r0 + of_block; r < min(r0 + kListBlock, min(tile_end, p.rows_in_dX)); r += p.parts)
+        if (((mask >> (r - r0)) & 1u) == 0)
+            for (int v = t; v < p.dX_vecs; v += kListThreads) p.dX[(int64_t)r * p.dX_vecs + v] = make_uint4(0, 0, 0, 0);
 }
 
 }  // namespace
 
-int launch_live_row_list(const ActorShape& sh, const ActorIO& io, const uint8_t* clipped, const float* adv,
-                         int64_t row_offset, int64_t rows_pad, const LiveSources& whole, const LiveSources& listed,
-                         int32_t* idx, LivePlan* plan, hipStream_t s) {
-    const RowGradient g{clipped, adv, io.opt.chunk_weight, row_offset, sh.A};
-    live_row_list<<<1, 1024, 0, s>>>(g, io.n_kept, sh.max_chunks, sh.A, row_offset, (int)rows_pad, whole, listed, idx, plan);
-    return launch_status();
-}
-
-int launch_gather_listed(const void* src, const int32_t* idx, const LivePlan* plan, int64_t rows_pad, int64_t row_bytes,
-                         void* dst, hipStream_t s) {
-    const int64_t blocks = ceil_div64(rows_pad, kRowsPerBlock);
-    gather_listed_rows<<<(unsigned)(blocks < 2048 ? blocks : 2048), kThreads, 0, s>>>(
-        static_cast<const uint4*>(src), idx, plan, (int)(row_bytes / 16), static_cast<uint4*>(dst));
-    return launch_status();
-}
-
-int launch_zero_unlisted(const ActorShape& sh, const ActorIO& io, const uint8_t* clipped, const float* adv,
-                         int64_t row_offset, int64_t rows_pad, int64_t rows_in_dX, int64_t row_bytes, void* dX,
-                         hipStream_t s) {
-    const RowGradient g{clipped, adv, io.opt.chunk_weight, row_offset, sh.A};
-    zero_unlisted_rows<<<(unsigned)(rows_pad < 2048 ? rows_pad : 2048), kThreads, 0, s>>>(
-        g, io.n_kept, sh.max_chunks, sh.A, row_offset, (int)rows_pad, (int)rows_in_dX, (int)(row_bytes / 16),
-        static_cast<uint4*>(dX));
+int launch_live_rows(const ActorShape& sh, const ActorIO& io, const uint8_t* clipped, const float* adv, const int32_t* counts,
+                     int64_t row_offset, int64_t rows_pad, const LiveSources& whole, const LiveSources& listed,
+                     const int64_t (&row_bytes)[LiveSources::kCount], void* dX, int64_t rows_in_dX, int32_t* idx, LivePlan* plan,
+                     hipStream_t s) {
+    StageTimer t(ST_LIVE_ROWS, s);
+    ListArgs p{clipped, adv, io.opt.chunk_weight, counts, io.n_kept, sh.max_chunks, sh.A, row_offset, (int)rows_pad, (int)rows_in_dX,
+               (int)((int64_t)sh.d * 2 / 16), static_cast<uint4*>(dX), whole, listed, {}, idx, plan, 1};
+    for (int q = 0; q < LiveSources::kCount; ++q) p.row_vecs[q] = (int)(row_bytes[q] / 16);
+    const int64_t blocks = (rows_pad + 256) / kListBlock;          // those of the panel, and a row tile behind the list
+    if (blocks <= 512) p.parts = kListParts;
+    list_live_rows<<<(unsigned)(blocks * p.parts), kListThreads, 0, s>>>(p);
     return launch_status();
 }
 
@@ -483,17 +448,11 @@ int launch_chunk_ratio(const ActorShape& sh, const ActorIO& io, RowMeta meta, Ro
     return launch_status();
 }
 
-int launch_scale_rows(const ActorShape& sh, const ActorIO& io, void* dz, const void* extra, const float* coef,
-                      int64_t row_offset, int64_t rows_pad, int elem_bytes, hipStream_t s) {
+int launch_scale_rows_f32(const ActorShape& sh, const ActorIO& io, float* dz, const float* extra, const float* coef,
+                          int64_t rows, hipStream_t s) {
     StageTimer t(ST_REDUCE, s);
-    const int64_t n = rows_pad * sh.V;
-    unsigned blocks = (unsigned)(ceil_div64(n, 256) < 4096 ? ceil_div64(n, 256) : 4096);
-    if (elem_bytes == 2)
-        scale_rows<bf16><<<blocks, 256, 0, s>>>(static_cast<bf16*>(dz), static_cast<const bf16*>(extra), coef, io.n_kept,
-                                                sh.max_chunks, sh.A, row_offset, rows_pad, sh.V);
-    else
-        scale_rows<float><<<blocks, 256, 0, s>>>(static_cast<float*>(dz), static_cast<const float*>(extra), coef,
-                                                 io.n_kept, sh.max_chunks, sh.A, row_offset, rows_pad, sh.V);
+    const int64_t blocks = ceil_div64(rows * sh.V, 256);
+    scale_rows_f32<<<(unsigned)(blocks < 4096 ? blocks : 4096), 256, 0, s>>>(dz, extra, coef, io.n_kept, sh.max_chunks, sh.A, rows, sh.V);
     return launch_status();
 }
 
