@@ -104,9 +104,33 @@ struct SumsqLists {
     const double* parts[4];
     int count[4];
 };
-// Sums the per-row loss terms and statistics in a fixed order (one workgroup, fp64 accumulators); with lists, also
-// the partial sums of squares into io.opt.grad_sumsq_out.
-int launch_loss_reduce(const ActorShape& sh, const ActorIO& io, RowOut out, const SumsqLists& lists, hipStream_t s);
+// Sums of partial products that split reductions left: out = (add: out +) parts[0] + parts[1] + .. in that order (fp32, n
+// floats, parts `stride` floats apart).  With live_row > 0 the sum is one over the rows of the batch, live_row floats each:
+// beyond the live rows rounded up to 128 the parts were not written and out is zero.  With sumsq, on the final panel every workgroup also leaves the sum of the squares of what it wrote in
+// sumsq[its number within the job].
+struct PartsSum {
+    const float* parts;
+    int n_parts, add;
+    size_t n, stride;
+    float* out;
+    double* sumsq;
+    int live_row;
+    int first, blocks, threads, vec;   // workgroups, their threads that take part; vec: 16-byte accesses
+};
+struct PartsSums {
+    static constexpr int kMax = 5, kBlocksMax = 2048;
+    PartsSum job[kMax];
+    int n, blocks;
+    static int blocks_for(size_t n_floats, int n_parts);      // workgroups of a sum at most
+    void add(const float* parts, int n_parts, size_t n_floats, size_t stride, float* out, bool add_to = false, double* sumsq = nullptr,
+             int live_row = 0);
+};
+// What a step does behind its last product, in one launch: sums of parts, and if asked for (with_loss) the per-row loss terms
+// and statistics of the whole batch, in a fixed order (one workgroup, fp64 accumulators).  With lists the partial sums of
+// squares of the weight gradients are added up behind it, into io.opt.grad_sumsq_out.
+struct FinalPanel;
+int launch_finish(const ActorShape& sh, const ActorIO& io, RowOut out, const PartsSums& sums, const FinalPanel& panel, bool with_loss,
+                  const SumsqLists& lists, hipStream_t s);
 
 // Per-chunk ratio: from the per-row dlogp, one ratio, one clipped term and one dz factor per kept chunk
 // (written to every row of the chunk; the term only to its first row).
@@ -152,6 +176,18 @@ __device__ inline float objective_scale(const LossOptions& o, int64_t rows_live)
     if (!o.token_mean) return o.loss_scale;
     return rows_live > 0 ? o.loss_scale / (float)rows_live : 0.f;
 }
+
+// Whether a row panel [row_begin, row_end) of a batch holds the batch's last live rows (panel 0 if there are none):
+// the weight gradients that panel leaves are the final ones.
+struct FinalPanel {
+    const int32_t* n_kept;
+    int max_chunks, A;
+    int64_t row_begin, row_end;
+    __device__ bool operator()() const {
+        const int64_t rows = live_rows(n_kept, max_chunks, A);
+        return rows <= row_end && (rows > row_begin || row_begin == 0);
+    }
+};
 
 // Clipped-surrogate math of one ratio (device), shared by both paths and both ratio levels.
 // term = weight * min(rho A, clip(rho) A); coef is the factor c in dz = c * (onehot - softmax):

@@ -40,42 +40,10 @@ namespace pcm {
 namespace {
 
 constexpr size_t kMaxSplitTiles = 256;   // tiles x parts of a split reduction: one workgroup per CU
-constexpr size_t kSumBlocksMax = 2048;   // workgroups of sum_parts_f32 at most
+constexpr size_t kSumBlocksMax = PartsSums::kBlocksMax;
 
-// Sum over a workgroup of 256 threads (every thread gets the result).
-__device__ inline double block_sum_256(double x) {
-    __shared__ double wave_part[4];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    if ((threadIdx.x & 63) == 0) wave_part[threadIdx.x >> 6] = x;
-    __syncthreads();
-    return wave_part[0] + wave_part[1] + wave_part[2] + wave_part[3];
-}
-
-// out[i] = sum over the parts of a split reduction (n is a multiple of 4; parts are n floats apart); kAdd: added
-// to what out holds.  With sumsq_parts, on the final panel, every workgroup also writes the sum of the squares of
-// the values it left in out to sumsq_parts[workgroup].
-template <bool kAdd>
-__global__ __launch_bounds__(256) void sum_parts_f32(const float* parts, int n_parts, size_t n, float* out, double* sumsq_parts,
-                                                     FinalPanel final_panel) {
-    const size_t stride = (size_t)gridDim.x * blockDim.x * 4;
-    double sq = 0.0;
-    for (size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < n; i += stride) {
-        float4 acc = kAdd ? *reinterpret_cast<const float4*>(out + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int s = 0; s < n_parts; ++s) {
-            const float4 v = *reinterpret_cast<const float4*>(parts + (size_t)s * n + i);
-            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-        }
-        *reinterpret_cast<float4*>(out + i) = acc;
-        sq += (double)acc.x * acc.x + (double)acc.y * acc.y + (double)acc.z * acc.z + (double)acc.w * acc.w;
-    }
-    if (sumsq_parts != nullptr && final_panel()) {
-        sq = block_sum_256(sq);
-        if (threadIdx.x == 0) sumsq_parts[blockIdx.x] = sq;
-    }
-}
-
-// The same sum, rounded once to bf16 (a product that the next GEMM takes as an operand).
+// out[i] = the sum over the parts of a split reduction (n is a multiple of 4; parts are n floats apart), rounded once to bf16: a
+// product that the next GEMM takes as an operand.
 __global__ void sum_parts_bf16(const float* parts, int n_parts, size_t n, bf16* out) {
     const size_t stride = (size_t)gridDim.x * blockDim.x * 4;
     for (size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < n; i += stride) {
@@ -89,6 +57,11 @@ __global__ void sum_parts_bf16(const float* parts, int n_parts, size_t n, bf16* 
         out[i + 2] = __float2bfloat16(acc.z);
         out[i + 3] = __float2bfloat16(acc.w);
     }
+}
+
+void launch_sum_bf16(const float* parts, int n_parts, size_t n, bf16* out, hipStream_t s) {
+    const size_t blocks = (n / 4 + 255) / 256;
+    sum_parts_bf16<<<(unsigned)(blocks < kSumBlocksMax ? blocks : kSumBlocksMax), 256, 0, s>>>(parts, n_parts, n, out);
 }
 
 // The loss over the rows of a panel: log-softmax at the target bin, row entropy, ratio, clipped surrogate and
@@ -280,13 +253,120 @@ int64_t panel_rows(const ActorShape& sh, bool composed, int target) {
     return Mp <= rp + rp / 4 ? Mp : rp;
 }
 
+// Reduction split for an output of `tiles` tiles and `steps` 64-wide reduction steps.  An output
+// that already covers the 256 CUs is not split; a small output is split so that tiles * splits
+// fills the chip (and never exceeds kMaxSplitTiles, which sizes the buffer of partial products),
+// keeping at least 8 steps per workgroup.
+int pick_splits(int tiles, int steps) {
+    if (tiles >= 256) return 1;
+    int s = (int)kMaxSplitTiles / tiles;
+    const int max_s = steps / 8 > 0 ? steps / 8 : 1;
+    if (s > max_s) s = max_s;
+    return s < 1 ? 1 : s;
+}
+
+// Tile and reduction splits of products that share a launch: those with the least estimated time.  A workgroup takes a few
+// microseconds to start and to write its tile, and per 64-wide step 0.94 us with the large tile (the matrix pipe) or 0.46 with
+// the small one (LDS, which two workgroups of a CU share; see tile_for).  The launch takes what its longest workgroup does, or
+// the work shared out over 256 CUs and about half a workgroup more at the end; parts are written, read back and added up at
+// about 4 TB/s.  Measured against every one of these choices forced on all three launches of a step (tile, and the longest
+// reduction from 6 steps to all of them): the estimate is within 1 % of the best, or better, at 14 of 16 sizes from 448 rows
+// of 3072 -> 768 to 5376 of 3328 -> 7168, and 2 to 3 % off at 9856 rows of 1792 -> 1792 and 2688 of 3072 -> 2560.
+struct GroupShape {
+    int64_t M, N;
+    int steps, count;      // `count` products of these sizes
+    bool split;            // whether the reduction may be split (fp32 parts, summed by a later launch)
+};
+struct GroupPlan {
+    static constexpr int kMax = 4;
+    int kW, splits[kMax];
+};
+template <int kN>
+GroupPlan plan_group(const GroupShape (&jobs)[kN]) {
+    GroupPlan best{};
+    double best_us = 0.0;
+    for (int kW : {kLargeTile, kSmallTile}) {
+        const double us_per_step = kW == kLargeTile ? 0.94 : 0.46, us_fixed = kW == kLargeTile ? 5.0 : 3.0;
+        for (int most : {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 1 << 20}) {     // longest reduction of a workgroup
+            GroupPlan plan{kW, {}};
+            double longest = 0.0, work = 0.0, sum_bytes = 0.0;
+            int64_t workgroups = 0;
+            for (int q = 0; q < kN; ++q) {
+                const GroupShape& j = jobs[q];
+                const int64_t tiles = j.M / (32 * kW) * (j.N / (32 * kW)), large = j.M / kTileM * (j.N / kTileN);
+                int s = 1;
+                if (j.split) s = (int)std::max<int64_t>(1, std::min({ceil_div64(j.steps, most), (int64_t)kMaxSplitTiles / large, (int64_t)64}));
+                plan.splits[q] = s;
+                const int len = ceil_div(j.steps, s);
+                longest = std::max(longest, us_fixed + us_per_step * len);
+                workgroups += tiles * s * j.count;
+                work += (double)(tiles * s * j.count) * (us_fixed + us_per_step * len);
+                if (s > 1) sum_bytes += (double)(2 * s + 1) * j.M * j.N * 4.0 * j.count;
+            }
+            const double us = std::max(longest, work / 256 + 0.5 * work / (double)workgroups) + sum_bytes / 4e6 + (sum_bytes > 0.0 ? 2.0 : 0.0);
+            if (best.kW == 0 || us < best_us) {
+                best = plan;
+                best_us = us;
+            }
+        }
+    }
+    return best;
+}
+
+// Launches shared by products of one dependency level, one launch per product / shared: 2072 rows of 512 -> 768 107 -> 79 us per
+// step, 448 of 3072 -> 768 156 -> 106; at 4096 -> 11008 with every row, 4086 rows (mean) 2667 -> 2513, 10,752 6340 -> 6240.
+//
+// Rows of a panel up to which the listed rows of a, du and dv have buffers of their own, so that dWd, which reads the first,
+// and da, which writes the others, may run side by side.
+constexpr int64_t kApartRows = 8192;
+
+// Large tiles of dX up to which it shares a launch with dWg and dWu.  What sharing saves is the part-filled last round of each;
+// with many rounds that is little, and where the products meet the workgroups of an XCD no longer walk through the same
+// panels in step.  Whole steps at 4096 -> 11008, every row, apart / shared: 672 tiles 6340 / 6240 us, 1344 12,625 / 12,380,
+// 2016 18,370 / 18,800, 2688 24,715 / 24,960; unmasked, panels of 3584, 129.4 / 130.9 ms.  (dWg and dWu in front where their
+// reductions are the longer: 133.5 ms.)
+constexpr int64_t kGroupTiles = 6 * 256;
+
+// How the backward products of a panel are launched.
+struct BackwardPlan {
+    // as written: {dy, dWo}, then {da, dWd}, then {dX, dWg and dWu}; composed: {da, G}, then {dX, dWg and dWu, dWo, dWd}
+    GroupPlan level[3];
+    bool group[3];
+    int split_o, split_d, split_gu, split_G;
+};
+BackwardPlan plan_backward(const ActorShape& sh, int64_t Rp, bool composed, bool listed) {
+    const int64_t d = sh.d, ff = sh.ff, V = sh.V;
+    const int rows = (int)(Rp / kTileK), by_d = sh.d / kTileK, by_ff = sh.ff / kTileK, by_V = sh.V / kTileK;
+    BackwardPlan b{};
+    if (composed) {
+        b.level[0] = plan_group<2>({{Rp, ff, by_V, 1, false}, {ff, V, rows, 1, true}});
+        b.level[2] = plan_group<4>({{Rp, d, 2 * by_ff, 1, false}, {d, ff, rows, 2, true}, {d, V, by_ff, 1, true}, {ff, d, by_V, 1, false}});
+        b.split_G = b.level[0].splits[1];
+        b.split_o = b.level[2].splits[2];
+        b.split_d = 1;
+        b.group[0] = b.group[2] = true;
+    } else {
+        b.level[0] = plan_group<2>({{Rp, d, by_V, 1, false}, {d, V, rows, 1, true}});
+        b.level[1] = plan_group<2>({{Rp, ff, by_d, 1, false}, {ff, d, rows, 1, true}});
+        b.level[2] = plan_group<2>({{Rp, d, 2 * by_ff, 1, false}, {d, ff, rows, 2, true}});
+        b.group[0] = true;
+        b.group[1] = !listed || Rp <= kApartRows;
+        b.group[2] = Rp / kTileM * (d / kTileN) <= kGroupTiles;
+        b.split_o = b.level[0].splits[1];
+        b.split_d = b.level[1].splits[1];
+        if (!b.group[1]) b.split_d = pick_splits((int)(ff / kTileM * (d / kTileN)), rows);
+    }
+    b.split_gu = b.level[2].splits[1];
+    if (!b.group[2]) b.split_gu = pick_splits((int)(d / kTileM * (ff / kTileN)), rows);
+    return b;
+}
 struct Bf16Workspace {
     bf16 *WguT, *WdT, *WoT;
     bf16 *X, *fu, *fv, *a, *y, *dz, *dz_extra;   // one panel each; fu, fv: SwiGLU derivative factors, then du, dv
     bf16 *a_lo, *y_lo;                           // per-chunk ratio: rounding remainders of a and y
     bf16* dy;
-    bf16 *du, *yc, *Xc, *dzc;   // backward over listed rows: du (before that the listed rows of a), the listed rows of y, X
-                                // and dz; dv takes the place of a
+    bf16 *yc, *Xc, *dzc, *ac;   // backward over listed rows: those of y, X, dz and a
+    bf16 *du, *dv;              // and du, dv, which in tall panels take the places of ac and a (see kApartRows)
     int32_t* live_count;   // [Rp / 16] rows with a gradient by block of 16
     int32_t* live_idx;     // [Rp] the listed rows
     LivePlan* plan;        // null: backward over all rows
@@ -294,6 +374,8 @@ struct Bf16Workspace {
     int sumsq_count[4];
     bf16 *Wdo, *G;  // composed evaluation: Wd Wo and a^T dz, both [ff, V]
     float* parts;   // partial products of split reductions; the logits
+    float *parts_o, *parts_d, *parts_g, *parts_u;   // those of dWo, dWd, dWg, dWu, which are added up at the end of a panel
+    BackwardPlan plan_b;
     RowMeta meta;   // whole batch
     RowOut out;     // whole batch
     int64_t Mp;     // padded rows of the batch
@@ -339,7 +421,9 @@ Bf16Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool grads, const 
     if (bwd) w.dz_extra = c.take<bf16>(Rp * V);
     if (bwd) w.dy = c.take<bf16>(Rp * d);
     if (lists_live_rows(opt, bwd, composed)) {
-        w.du = c.take<bf16>(Rp * ff);
+        w.ac = c.take<bf16>(Rp * ff);
+        w.du = (int64_t)Rp <= kApartRows ? c.take<bf16>(Rp * ff) : w.ac;
+        w.dv = (int64_t)Rp <= kApartRows ? c.take<bf16>(Rp * ff) : w.a;
         w.yc = c.take<bf16>(Rp * d);
         w.Xc = c.take<bf16>(Rp * d);
         w.dzc = c.take<bf16>(Rp * V);
@@ -347,12 +431,20 @@ Bf16Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool grads, const 
         w.live_idx = c.take<int32_t>(Rp);
         w.plan = c.take<LivePlan>(1);
     }
+    const BackwardPlan& plan = w.plan_b = plan_backward(sh, (int64_t)Rp, composed, lists_live_rows(opt, bwd, composed));
+    if (grads) {
+        if (plan.split_o > 1) w.parts_o = c.take<float>((size_t)plan.split_o * d * V);
+        if (plan.split_d > 1) w.parts_d = c.take<float>((size_t)plan.split_d * ff * d);
+        if (plan.split_gu > 1) w.parts_g = c.take<float>((size_t)plan.split_gu * d * ff);
+        if (plan.split_gu > 1) w.parts_u = c.take<float>((size_t)plan.split_gu * d * ff);
+    }
     if (grads && opt.grad_sumsq_out != nullptr) {
         const size_t size[4][2] = {{d, ff}, {d, ff}, {ff, d}, {d, V}};
-        for (int q = 0; q < 4; ++q) {
-            const size_t tile = 32 * (size_t)tile_for((int64_t)size[q][0], (int64_t)size[q][1], 1);   // that of an unsplit product
-            const size_t waves = 4 * (size[q][0] / tile) * (size[q][1] / tile);
-            w.sumsq_count[q] = (int)(waves > kSumBlocksMax ? waves : kSumBlocksMax);
+        const int level[4] = {2, 2, 1, 0}, splits[4] = {plan.split_gu, plan.split_gu, plan.split_d, plan.split_o};
+        for (int q = 0; q < 4; ++q) {       // unsplit: one per wavefront of the product; else one per workgroup of the sum
+            const int kW = plan.group[level[q]] ? plan.level[level[q]].kW : tile_for((int64_t)size[q][0], (int64_t)size[q][1], 1);
+            const size_t tile = 32 * (size_t)kW, waves = 4 * (size[q][0] / tile) * (size[q][1] / tile);
+            w.sumsq_count[q] = splits[q] == 1 ? (int)waves : PartsSums::blocks_for(size[q][0] * size[q][1], splits[q]);
             w.sumsq[q] = c.take<double>((size_t)w.sumsq_count[q]);
         }
     }
@@ -363,18 +455,6 @@ Bf16Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool grads, const 
     w.parts = c.take<float>((row_tiles > kMaxSplitTiles ? row_tiles : kMaxSplitTiles) * (size_t)kTileM * kTileN);
     w.bytes = c.used();
     return w;
-}
-
-// Reduction split for an output of `tiles` tiles and `steps` 64-wide reduction steps.  An output
-// that already covers the 256 CUs is not split; a small output is split so that tiles * splits
-// fills the chip (and never exceeds kMaxSplitTiles, which sizes the buffer of partial products),
-// keeping at least 8 steps per workgroup.
-int pick_splits(int tiles, int steps) {
-    if (tiles >= 256) return 1;
-    int s = (int)kMaxSplitTiles / tiles;
-    const int max_s = steps / 8 > 0 ? steps / 8 : 1;
-    if (s > max_s) s = max_s;
-    return s < 1 ? 1 : s;
 }
 
 // Which GEMM dimension runs over the kept rows, so that work beyond the device-side count is skipped; the rows
@@ -392,33 +472,26 @@ struct SumsqTarget {
     FinalPanel final_panel;
 };
 
-// C[M, N] = product of p with a long reduction and possibly a small output: fp32 (C32) or rounded to bf16
-// (C16), exactly one of the two given.  A small output is computed as several partial products over slices of
-// the reduction, summed by a second kernel (no atomics).  The weight gradients are the case
-// kLayA = kLayB = kKByRows: A^T B over the kept rows with both operands stored [rows][features].
-// accumulate (fp32 output only): the product is added to C.
+// A product with a long reduction whose fp32 result goes to C, or is added to it (accumulate), as one launch or as parts that
+// launch_finish adds up (no atomics): p.splits, the epilogue and, for parts, the entry in `sums`.  The weight gradients are the
+// case A^T B over the kept rows with both operands stored [rows][features].
+EpiStoreF32 reduction_epilogue(GemmProblem& p, int splits, float* C, float* parts, bool accumulate, const SumsqTarget& sq, PartsSums& sums) {
+    p.splits = splits;
+    p.skip_if_empty = splits == 1 && accumulate ? 1 : 0;
+    const size_t n = (size_t)p.M * p.N;
+    if (splits == 1) return EpiStoreF32{C, p.N, 0, accumulate ? 1 : 0, sq.parts, sq.final_panel};
+    sums.add(parts, splits, n, n, C, accumulate, sq.parts);
+    return EpiStoreF32{parts, p.N, (int64_t)n, 0, nullptr, FinalPanel{}};
+}
+// C = a product with a long reduction and a small output, as parts and rounded once to bf16.
 template <int kLayA, int kLayB>
-void launch_reduction_gemm(GemmProblem p, float* C32, bf16* C16, float* parts, bool accumulate, const SumsqTarget& sq, int stage,
-                           hipStream_t s) {
-    p.splits = pick_splits((p.M / kTileM) * (p.N / kTileN), p.K1 / kTileK);
+void launch_reduction_bf16(GemmProblem p, bf16* C, float* parts, int stage, hipStream_t s) {
     StageTimer t(stage, s);
-    if (p.splits == 1) {
-        p.skip_if_empty = accumulate ? 1 : 0;
-        if (C32) launch_gemm<kLayA, kLayB>(p, EpiStoreF32{C32, p.N, 0, accumulate ? 1 : 0, sq.parts, sq.final_panel}, s);
-        else launch_gemm<kLayA, kLayB>(p, EpiStoreBf16{C16, p.N, p.M}, s);
-        return;
-    }
+    p.splits = pick_splits((p.M / kTileM) * (p.N / kTileN), p.K1 / kTileK);
+    if (p.splits == 1) return launch_gemm<kLayA, kLayB>(p, EpiStoreBf16{C, p.N, p.M}, s);
     const size_t n = (size_t)p.M * p.N;
     launch_gemm<kLayA, kLayB>(p, EpiStoreF32{parts, p.N, (int64_t)n, 0, nullptr, FinalPanel{}}, s);
-    size_t blocks = (n / 4 + 255) / 256;
-    if (blocks > kSumBlocksMax) blocks = kSumBlocksMax;
-    if (C32 && accumulate) sum_parts_f32<true><<<(unsigned)blocks, 256, 0, s>>>(parts, p.splits, n, C32, sq.parts, sq.final_panel);
-    else if (C32) sum_parts_f32<false><<<(unsigned)blocks, 256, 0, s>>>(parts, p.splits, n, C32, sq.parts, sq.final_panel);
-    else sum_parts_bf16<<<(unsigned)blocks, 256, 0, s>>>(parts, p.splits, n, C16);
-}
-void launch_weight_grad(const GemmProblem& p, float* C, float* parts, bool accumulate, const SumsqTarget& sq, int stage,
-                        hipStream_t s) {
-    launch_reduction_gemm<kKByRows, kKByRows>(p, C, nullptr, parts, accumulate, sq, stage, s);
+    launch_sum_bf16(parts, p.splits, n, C, s);
 }
 
 GemmProblem problem(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
@@ -446,8 +519,7 @@ void launch_rows_bf16(GemmProblem p, bf16* C, float* parts, hipStream_t s) {
             p.splits = splits;
             const size_t n = (size_t)p.M * p.N;
             launch_gemm_tile<kRowsByK, kRowsByK, kSmallTile>(p, EpiStoreF32{parts, p.N, (int64_t)n, 0, nullptr, FinalPanel{}}, s);
-            const size_t blocks = (n / 4 + 255) / 256;
-            sum_parts_bf16<<<(unsigned)(blocks < kSumBlocksMax ? blocks : kSumBlocksMax), 256, 0, s>>>(parts, splits, n, C);
+            launch_sum_bf16(parts, splits, n, C, s);
             return;
         }
     }
@@ -506,8 +578,8 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
         layouts.add(Wu, d, ff, w.WguT, kPackUp);
         if (io.composed) {
             // W_do = Wd Wo [ff, V], from the weights as given (Wd [rows][K], Wo [K][rows])
-            launch_reduction_gemm<kRowsByK, kKByRows>(problem(Wd, d, Wo, V, ff, V, d, all_rows, kRowsUnused), nullptr, w.Wdo,
-                                                      w.parts, false, SumsqTarget{}, ST_WEIGHT_LAYOUT, s);
+            launch_reduction_bf16<kRowsByK, kKByRows>(problem(Wd, d, Wo, V, ff, V, d, all_rows, kRowsUnused), w.Wdo, w.parts,
+                                                      ST_WEIGHT_LAYOUT, s);
         } else {
             layouts.add(Wd, ff, d, w.WdT, kPackNone);      // [ff, d] -> [d, ff]
             layouts.add(Wo, d, V, w.WoT, kPackNone);       // [d, V]  -> [V, d]
@@ -519,6 +591,8 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
     const int n_zero = want_sumsq ? (int)(w.sumsq[3] - w.sumsq[0]) + w.sumsq_count[3] : 0;   // the four lists follow one another
 
     int rc = PCM_OK;
+    PartsSums last_sums{};
+    FinalPanel last_panel{};
     for (int64_t row0 = 0; row0 < w.Mp; row0 += w.Rp) {
         // this panel: batch rows [row0, row0 + Mp); all row-indexed arrays below are its parts
         const int Mp = (int)(w.Mp - row0 < w.Rp ? w.Mp - row0 : w.Rp);
@@ -583,103 +657,144 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
         }
         if (!bwd) continue;
 
-        if (w.plan != nullptr) {
-            // backward over the rows with a gradient; row counts and row-indexed operands come from the plan
-            const bf16* const* const src = reinterpret_cast<const bf16* const*>(w.plan->src);
-            const KeptRows lr{&w.plan->n_rows, Mp, 1, 0};
-            bf16* const dv = w.a;                       // free once the listed rows of a are copied
-            const int64_t rows_left = sh.rows_max() - row0;
-            bf16* const dX = io.dX ? static_cast<bf16*>(io.dX) + row0 * d : nullptr;
-            const LiveSources whole{{w.dz, w.y, w.a, w.X}}, listed{{w.dzc, w.yc, w.du, w.Xc}};
+        // Which rows the backward products run over, and where their row-indexed operands are: all live rows; or those with a
+        // gradient, where row count and operands come from the plan that a launch leaves in device memory.
+        const bool listed = w.plan != nullptr;
+        const BackwardPlan& plan = w.plan_b;
+        const int64_t rows_left = sh.rows_max() - row0;
+        bf16* const dX = io.dX ? static_cast<bf16*>(io.dX) + row0 * d : nullptr;
+        bf16* const du = listed ? w.du : w.fu;
+        bf16* const dv = listed ? w.dv : w.fv;
+        const KeptRows br = listed ? KeptRows{&w.plan->n_rows, Mp, 1, 0} : kr;
+        const bf16* const* const src = listed ? reinterpret_cast<const bf16* const*>(w.plan->src) : nullptr;
+        auto source = [&](int which) { return listed ? src + which : nullptr; };
+        if (listed) {
+            const LiveSources whole{{w.dz, w.y, w.a, w.X}}, rows{{w.dzc, w.yc, w.ac, w.Xc}};
             const int64_t both = grads ? 2 : 0;         // without weight gradients only dz is read by row of the list
-            rc = launch_live_rows(sh, io, out.clipped, meta.adv, w.live_count, row0, Mp, whole, listed, {2 * V, both * d, both * ff, both * d},
+            rc = launch_live_rows(sh, io, out.clipped, meta.adv, w.live_count, row0, Mp, whole, rows, {2 * V, both * d, both * ff, both * d},
                                   dX, rows_left < Mp ? rows_left : Mp, w.live_idx, w.plan, s);
             if (rc != PCM_OK) return rc;
-            {
-                StageTimer t(ST_GEMM_DY, s);
-                GemmProblem p = problem(w.dz, V, Wo, V, Mp, d, V, lr, kRowsAreM);                                // dy = dz Wo^T
-                p.A_sel = src + LiveSources::kDz;
-                launch_row_gemm(p, EpiStoreBf16{w.dy, d, Mp}, s);
-            }
-            if (grads) {
-                GemmProblem p = problem(w.y, d, w.dz, V, d, V, Mp, lr, kRowsAreK);                               // dWo (+)= y^T dz
-                p.A_sel = src + LiveSources::kY;
-                p.B_sel = src + LiveSources::kDz;
-                launch_weight_grad(p, io.dWo, w.parts, !first, sq[3], ST_GEMM_DWO, s);
-                p = problem(w.a, ff, w.dy, d, ff, d, Mp, lr, kRowsAreK);                                         // dWd (+)= a^T dy
-                p.A_sel = src + LiveSources::kA;
-                launch_weight_grad(p, io.dWd, w.parts, !first, sq[2], ST_GEMM_DWD, s);
-            }
-            {
-                StageTimer t(ST_GEMM_DA, s);                                                                     // du, dv from da = dy Wd^T
-                launch_row_gemm(problem(w.dy, d, Wd, d, Mp, ff, d, lr, kRowsAreM),
-                            EpiSwigluBackward<true>{w.fu, w.fv, ff, w.live_idx, w.du, dv}, s);
-            }
-            if (grads) {
-                GemmProblem p = problem(w.X, d, w.du, ff, d, ff, Mp, lr, kRowsAreK);                             // dWg (+)= X^T du
-                p.A_sel = src + LiveSources::kX;
-                launch_weight_grad(p, io.dWg, w.parts, !first, sq[0], ST_GEMM_DWG_DWU, s);
-                p.B = dv;                                                                                        // dWu (+)= X^T dv
-                p.B2 = dv;
-                launch_weight_grad(p, io.dWu, w.parts, !first, sq[1], ST_GEMM_DWG_DWU, s);
-            }
-            if (dX) {
-                StageTimer t(ST_GEMM_DX, s);
-                GemmProblem p = problem(w.du, ff, Wg, ff, Mp, d, ff, lr, kRowsAreM);                             // dX = du Wg^T + dv Wu^T
-                p.A2 = dv; p.B2 = Wu; p.K2 = ff;
-                launch_row_gemm(p, EpiScatterBf16{dX, d, w.live_idx}, s);
-            }
-            continue;
         }
+        PartsSums sums{};
+        // dWg (+)= X^T du, dWu (+)= X^T dv
+        GemmPairJob<kKByRows, kKByRows, EpiStoreF32> dWgu{problem(w.X, d, du, ff, d, ff, Mp, br, kRowsAreK), {du, dv}, {}, 0, 0};
+        dWgu.p.A_sel = source(LiveSources::kX);
+        // dX = du Wg^T + dv Wu^T
+        GemmProblem pX = problem(du, ff, Wg, ff, Mp, d, ff, br, kRowsAreM);
+        pX.A2 = dv; pX.B2 = Wu; pX.K2 = ff;
+        const EpiScatterBf16 scatter_X{dX, d, w.live_idx};
+        const EpiStoreBf16 store_X{dX, d, (int)(rows_left < Mp ? rows_left : Mp)};
+        const EpiSwigluBackward<true> swiglu_listed{w.fu, w.fv, ff, w.live_idx, du, dv};
+        const EpiSwigluBackward<false> swiglu{w.fu, w.fv, ff, nullptr, nullptr, nullptr};   // fu <- du, fv <- dv
         if (io.composed) {      // one panel: nothing to add to
+            // da = dz W_do^T, and G = a^T dz [ff, V] over the kept rows, rounded to bf16 as the operand of two products below
+            const GemmProblem pa = problem(w.dz, V, w.Wdo, V, Mp, ff, V, kr, kRowsAreM);
+            const GemmJob<kRowsByK, kRowsByK, EpiSwigluBackward<false>> da{pa, swiglu, 0};
             if (grads) {
-                // G = a^T dz [ff, V] over the kept rows, rounded to bf16 as the operand of the two products below
-                launch_reduction_gemm<kKByRows, kKByRows>(problem(w.a, ff, w.dz, V, ff, V, Mp, kr, kRowsAreK), nullptr, w.G,
-                                                          w.parts, false, SumsqTarget{}, ST_GEMM_DWD, s);
-                {
-                    StageTimer t(ST_GEMM_DWD, s);                                                                 // dWd = G Wo^T
-                    launch_gemm<kRowsByK, kRowsByK>(problem(w.G, V, Wo, V, ff, d, V, all_rows, kRowsUnused),
-                                                    EpiStoreF32{io.dWd, d, 0, 0, nullptr, FinalPanel{}}, s);
-                }
-                launch_weight_grad(problem(Wd, d, w.G, V, d, V, ff, all_rows, kRowsUnused), io.dWo, w.parts, false,
-                                   SumsqTarget{}, ST_GEMM_DWO, s);                                                               // dWo = Wd^T G
+                StageTimer t(ST_GEMM_DA, s);
+                GemmProblem p = problem(w.a, ff, w.dz, V, ff, V, Mp, kr, kRowsAreK);
+                p.splits = plan.split_G;
+                const size_t n = (size_t)ff * V;
+                launch_gemm_group(plan.level[0].kW, s, da,
+                                  GemmJob<kKByRows, kKByRows, EpiStoreF32>{p, EpiStoreF32{w.parts, V, (int64_t)n, 0, nullptr, FinalPanel{}}, 0});
+                launch_sum_bf16(w.parts, p.splits, n, w.G, s);
+            } else {
+                StageTimer t(ST_GEMM_DA, s);
+                launch_row_gemm(pa, swiglu, s);
             }
-            StageTimer t(ST_GEMM_DA, s);                                                                          // da = dz W_do^T
-            launch_row_gemm(problem(w.dz, V, w.Wdo, V, Mp, ff, V, kr, kRowsAreM), EpiSwigluBackward<false>{w.fu, w.fv, ff, nullptr, nullptr, nullptr}, s);
+            if (grads) {
+                StageTimer t(ST_GEMM_DX, s);
+                for (int q = 0; q < 2; ++q)
+                    dWgu.epi[q] = reduction_epilogue(dWgu.p, plan.split_gu, q ? io.dWu : io.dWg, q ? w.parts_u : w.parts_g, false, SumsqTarget{}, sums);
+                GemmProblem po = problem(Wd, d, w.G, V, d, V, ff, all_rows, kRowsUnused);                        // dWo = Wd^T G
+                const EpiStoreF32 eo = reduction_epilogue(po, plan.split_o, io.dWo, w.parts_o, false, SumsqTarget{}, sums);
+                const GemmJob<kKByRows, kKByRows, EpiStoreF32> dWo{po, eo, 0};
+                const GemmJob<kRowsByK, kRowsByK, EpiStoreF32> dWd{problem(w.G, V, Wo, V, ff, d, V, all_rows, kRowsUnused),   // dWd = G Wo^T
+                                                                   EpiStoreF32{io.dWd, d, 0, 0, nullptr, FinalPanel{}}, 0};
+                if (dX) launch_gemm_group(plan.level[2].kW, s, GemmJob<kRowsByK, kRowsByK, EpiStoreBf16>{pX, store_X, 0}, dWgu, dWo, dWd);
+                else launch_gemm_group(plan.level[2].kW, s, dWgu, dWo, dWd);
+            } else {
+                StageTimer t(ST_GEMM_DX, s);
+                launch_row_gemm(pX, store_X, s);
+            }
         } else {
+            GemmProblem py = problem(w.dz, V, Wo, V, Mp, d, V, br, kRowsAreM);                                   // dy = dz Wo^T
+            py.A_sel = source(LiveSources::kDz);
+            GemmProblem po = problem(w.y, d, w.dz, V, d, V, Mp, br, kRowsAreK);                                  // dWo (+)= y^T dz
+            po.A_sel = source(LiveSources::kY);
+            po.B_sel = source(LiveSources::kDz);
+            const GemmProblem pa = problem(w.dy, d, Wd, d, Mp, ff, d, br, kRowsAreM);                            // du, dv from da = dy Wd^T
+            GemmProblem pd = problem(w.a, ff, w.dy, d, ff, d, Mp, br, kRowsAreK);                                // dWd (+)= a^T dy
+            pd.A_sel = source(LiveSources::kA);
+            const EpiStoreBf16 store_y{w.dy, d, Mp};
+            if (!grads) {
+                {
+                    StageTimer t(ST_GEMM_DY, s);
+                    launch_row_gemm(py, store_y, s);
+                }
+                {
+                    StageTimer t(ST_GEMM_DA, s);
+                    if (listed) launch_row_gemm(pa, swiglu_listed, s);
+                    else launch_row_gemm(pa, swiglu, s);
+                }
+                StageTimer t(ST_GEMM_DX, s);
+                if (listed) launch_row_gemm(pX, scatter_X, s);
+                else launch_row_gemm(pX, store_X, s);
+                continue;
+            }
+            const EpiStoreF32 eo = reduction_epilogue(po, plan.split_o, io.dWo, w.parts_o, !first, sq[3], sums);
+            const EpiStoreF32 ed = reduction_epilogue(pd, plan.split_d, io.dWd, w.parts_d, !first, sq[2], sums);
+            const GemmJob<kKByRows, kKByRows, EpiStoreF32> dWo{po, eo, 0}, dWd{pd, ed, 0};
+            for (int q = 0; q < 2; ++q)
+                dWgu.epi[q] = reduction_epilogue(dWgu.p, plan.split_gu, q ? io.dWu : io.dWg, q ? w.parts_u : w.parts_g, !first, sq[q], sums);
             {
                 StageTimer t(ST_GEMM_DY, s);
-                launch_row_gemm(problem(w.dz, V, Wo, V, Mp, d, V, kr, kRowsAreM), EpiStoreBf16{w.dy, d, Mp}, s);          // dy = dz Wo^T
+                launch_gemm_group(plan.level[0].kW, s, dWo, GemmJob<kRowsByK, kRowsByK, EpiStoreBf16>{py, store_y, 0});
             }
-            if (grads) {
-                launch_weight_grad(problem(w.y, d, w.dz, V, d, V, Mp, kr, kRowsAreK), io.dWo, w.parts, !first, sq[3],
-                                   ST_GEMM_DWO, s);                                                                            // dWo (+)= y^T dz
-                launch_weight_grad(problem(w.a, ff, w.dy, d, ff, d, Mp, kr, kRowsAreK), io.dWd, w.parts, !first, sq[2],
-                                   ST_GEMM_DWD, s);                                                                            // dWd (+)= a^T dy
+            if (plan.group[1]) {
+                StageTimer t(ST_GEMM_DA, s);
+                if (listed) launch_gemm_group(plan.level[1].kW, s, GemmJob<kRowsByK, kRowsByK, EpiSwigluBackward<true>>{pa, swiglu_listed, 0}, dWd);
+                else launch_gemm_group(plan.level[1].kW, s, GemmJob<kRowsByK, kRowsByK, EpiSwigluBackward<false>>{pa, swiglu, 0}, dWd);
+            } else {
+                {
+                    StageTimer t(ST_GEMM_DWD, s);
+                    launch_gemm<kKByRows, kKByRows>(dWd.p, dWd.epi, s);
+                }
+                StageTimer t(ST_GEMM_DA, s);
+                if (listed) launch_row_gemm(pa, swiglu_listed, s);
+                else launch_row_gemm(pa, swiglu, s);
             }
-            StageTimer t(ST_GEMM_DA, s);
-            launch_row_gemm(problem(w.dy, d, Wd, d, Mp, ff, d, kr, kRowsAreM), EpiSwigluBackward<false>{w.fu, w.fv, ff, nullptr, nullptr, nullptr}, s);   // fu <- du, fv <- dv
+            if (plan.group[2]) {
+                StageTimer t(ST_GEMM_DX, s);
+                if (!dX) launch_gemm_group(plan.level[2].kW, s, dWgu);
+                else if (listed) launch_gemm_group(plan.level[2].kW, s, GemmJob<kRowsByK, kRowsByK, EpiScatterBf16>{pX, scatter_X, 0}, dWgu);
+                else launch_gemm_group(plan.level[2].kW, s, GemmJob<kRowsByK, kRowsByK, EpiStoreBf16>{pX, store_X, 0}, dWgu);
+            } else {
+                {
+                    StageTimer t(ST_GEMM_DWG_DWU, s);
+                    launch_gemm<kKByRows, kKByRows>(dWgu.p, dWgu.epi[0], s);
+                    dWgu.p.B = dWgu.p.B2 = dv;
+                    launch_gemm<kKByRows, kKByRows>(dWgu.p, dWgu.epi[1], s);
+                }
+                if (dX) {
+                    StageTimer t(ST_GEMM_DX, s);
+                    if (listed) launch_row_gemm(pX, scatter_X, s);
+                    else launch_row_gemm(pX, store_X, s);
+                }
+            }
         }
-        if (grads) {
-            launch_weight_grad(problem(w.X, d, w.fu, ff, d, ff, Mp, kr, kRowsAreK), io.dWg, w.parts, !first, sq[0],
-                               ST_GEMM_DWG_DWU, s);                                                                                // dWg (+)= X^T du
-            launch_weight_grad(problem(w.X, d, w.fv, ff, d, ff, Mp, kr, kRowsAreK), io.dWu, w.parts, !first, sq[1],
-                               ST_GEMM_DWG_DWU, s);                                                                                // dWu (+)= X^T dv
-        }
-        if (io.dX) {
-            StageTimer t(ST_GEMM_DX, s);
-            GemmProblem p = problem(w.fu, ff, Wg, ff, Mp, d, ff, kr, kRowsAreM);                                 // dX = du Wg^T + dv Wu^T
-            p.A2 = w.fv; p.B2 = Wu; p.K2 = ff;
-            const int64_t rows_left = sh.rows_max() - row0;
-            launch_row_gemm(p, EpiStoreBf16{static_cast<bf16*>(io.dX) + row0 * d, d, (int)(rows_left < Mp ? rows_left : Mp)}, s);
+        if (grads && row0 + w.Rp < w.Mp) {      // the last panel's sums go with the loss
+            rc = launch_finish(sh, io, w.out, sums, sq[0].final_panel, false, SumsqLists{}, s);
+            if (rc != PCM_OK) return rc;
+        } else {
+            last_sums = sums;
+            last_panel = sq[0].final_panel;
         }
     }
     SumsqLists lists{};
     if (want_sumsq)
         for (int q = 0; q < 4; ++q) { lists.parts[q] = w.sumsq[q]; lists.count[q] = w.sumsq_count[q]; }
-    rc = launch_loss_reduce(sh, io, w.out, lists, s);
-    if (rc != PCM_OK) return rc;
-    return launch_status();
+    return launch_finish(sh, io, w.out, last_sums, last_panel, true, lists, s);
 }
 
 }  // namespace pcm

@@ -287,23 +287,6 @@ struct F32SwigluBackward {
     }
 };
 
-// out[i] = parts[0][i] + parts[1][i] + ... in slice order (parts are n floats apart).
-__global__ void sum_slices(const float* __restrict__ parts, int n_parts, size_t n, float* __restrict__ out) {
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        float acc = parts[i];
-        for (int q = 1; q < n_parts; ++q) acc += parts[(size_t)q * n + i];
-        out[i] = acc;
-    }
-}
-// The sum of two slices over the rows of the batch; rows that no tile computed are zeros.
-__global__ void sum_live_rows(const float* __restrict__ first, const float* __restrict__ second, size_t n, int row_length,
-                              const int32_t* __restrict__ n_kept, int max_chunks, int A, float* __restrict__ out) {
-    const size_t limit = (size_t)((live_rows(n_kept, max_chunks, A) + kRowTile - 1) / kRowTile * kRowTile) * row_length;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) out[i] = i < limit ? first[i] + second[i] : 0.f;
-}
-
 __device__ inline float wave_max(float x) {
 #pragma unroll
     for (int d = kWave / 2; d > 0; d >>= 1) x = fmaxf(x, __shfl_xor(x, d, kWave));
@@ -419,7 +402,7 @@ size_t split_floats(int M, int N, int K, int n_right) {
 struct F32Workspace {
     float *X, *u, *v, *a, *y, *z, *z_extra, *dy;
     float *Wdo, *G;   // composed evaluation: Wd Wo and a^T dz, both [ff, V]
-    float* parts;     // partial products of the split reductions
+    float *parts, *parts_d;   // partial products of the split reductions; those of dWd
     RowMeta meta;
     RowOut out;
     size_t bytes;
@@ -450,12 +433,12 @@ F32Workspace carve(void* ws, const ActorShape& sh, bool grads) {
         w.z_extra = c.take<float>(M * sh.V);
         w.dy = c.take<float>(M * sh.d);
         const int rows = (int)M;
-        size_t parts = split_floats(sh.d, sh.V, rows, 1);                    // dWo = y^T dz
-        parts = std::max(parts, split_floats(sh.ff, sh.d, rows, 1));          // dWd = a^T dy
-        parts = std::max(parts, split_floats(sh.d, sh.ff, rows, 2));          // dWg, dWu
-        parts = std::max(parts, split_floats(sh.ff, sh.V, rows, 1));          // composed: G = a^T dz
-        parts = std::max(parts, split_floats(sh.d, sh.V, sh.ff, 1));          // composed: dWo = Wd^T G
-        w.parts = c.take<float>(parts);
+        // partial products: of dWo = y^T dz and dWd = a^T dy side by side (composed: of G = a^T dz, then of dWo = Wd^T G); once
+        // those are added up, of dWg and dWu
+        const size_t o = align_up(split_floats(sh.d, sh.V, rows, 1), 64), o_composed = split_floats(sh.d, sh.V, sh.ff, 1);
+        const size_t d = split_floats(sh.ff, sh.d, rows, 1);
+        w.parts = c.take<float>(std::max({o + d, o_composed, split_floats(sh.ff, sh.V, rows, 1), split_floats(sh.d, sh.ff, rows, 2)}));
+        w.parts_d = w.parts + o;
     }
     w.bytes = c.used();
     return w;
@@ -504,9 +487,9 @@ void gemm(hipStream_t s, const float* A, const float* B, bool b_t, float* C, int
 }
 
 // C[M, N] = A^T B with A [K, M], B [K, N] row-major: the weight-gradient shape (reduction over rows).  With B2 also
-// C2 = A^T B2 in the same launch.
+// C2 = A^T B2 in the same launch.  A reduction in slices leaves them in `parts`, and their sum in `sums` for a later launch.
 void gemm_reduce_rows(hipStream_t s, const float* A, const float* B, float* C, const float* B2, float* C2, int M, int N, int K,
-                      float* parts, const BatchRows& rows) {
+                      float* parts, PartsSums& sums, const BatchRows& rows) {
     const int n_right = B2 ? 2 : 1;
     F32Problem p = problem(A, M, B, N, M, N, K, rows, kLiveK);
     if (B2) p.B2 = B2;
@@ -517,10 +500,8 @@ void gemm_reduce_rows(hipStream_t s, const float* A, const float* B, float* C, c
     if (B2) launch<kKByRows, kKByRows, kPair>(p, t, epi, s);
     else launch<kKByRows, kKByRows, kNone>(p, t, epi, s);
     if (t.splits > 1) {
-        const size_t want = (n + 255) / 256;
-        const unsigned blocks = (unsigned)(want < 4096 ? want : 4096);
-        sum_slices<<<blocks, 256, 0, s>>>(parts, t.splits, n, C);
-        if (B2) sum_slices<<<blocks, 256, 0, s>>>(parts2, t.splits, n, C2);
+        sums.add(parts, t.splits, n, n, C);
+        if (B2) sums.add(parts2, t.splits, n, n, C2);
     }
 }
 
@@ -570,43 +551,47 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t
             if (rc != PCM_OK) return rc;
         }
     }
-    rc = launch_loss_reduce(sh, io, w.out, SumsqLists{}, s);
-    if (rc != PCM_OK) return rc;
-    if (!bwd) return launch_status();
+    if (!bwd) return launch_finish(sh, io, w.out, PartsSums{}, FinalPanel{}, true, SumsqLists{}, s);
+    PartsSums sums{};
     {
         StageTimer t(ST_F32_BACKWARD, s);
         float* dz = w.z;
         if (io.want_grads()) {
             if (io.composed) {
-                gemm_reduce_rows(s, w.a, dz, w.G, nullptr, nullptr, ff, V, M, w.parts, rows);          // G = a^T dz
+                PartsSums g{};
+                gemm_reduce_rows(s, w.a, dz, w.G, nullptr, nullptr, ff, V, M, w.parts, g, rows);     // G = a^T dz
+                launch_finish(sh, io, w.out, g, FinalPanel{}, false, SumsqLists{}, s);
                 gemm(s, w.G, Wo, true, io.dWd, ff, d, V, none);                                        // dWd = G Wo^T
-                gemm_reduce_rows(s, Wd, w.G, io.dWo, nullptr, nullptr, d, V, ff, w.parts, none);       // dWo = Wd^T G
+                gemm_reduce_rows(s, Wd, w.G, io.dWo, nullptr, nullptr, d, V, ff, w.parts, sums, none);   // dWo = Wd^T G
             } else {
-                gemm_reduce_rows(s, w.y, dz, io.dWo, nullptr, nullptr, d, V, M, w.parts, rows);        // dWo = y^T dz
+                gemm_reduce_rows(s, w.y, dz, io.dWo, nullptr, nullptr, d, V, M, w.parts, sums, rows);    // dWo = y^T dz
             }
         }
         if (!io.composed) {
             gemm(s, dz, Wo, true, w.dy, M, d, V, rows);                                                // dy = dz Wo^T
-            if (io.want_grads()) gemm_reduce_rows(s, w.a, w.dy, io.dWd, nullptr, nullptr, ff, d, M, w.parts, rows);   // dWd = a^T dy
+            if (io.want_grads()) gemm_reduce_rows(s, w.a, w.dy, io.dWd, nullptr, nullptr, ff, d, M, w.parts_d, sums, rows);   // dWd = a^T dy
         }
         {   // da = dy Wd^T (composed: dz W_do^T); u <- du, v <- dv
             const int k = io.composed ? V : d;
             const F32Problem p = io.composed ? problem(dz, V, w.Wdo, V, M, ff, k, rows, kLiveM) : problem(w.dy, d, Wd, d, M, ff, k, rows, kLiveM);
             launch<kRowsByK, kRowsByK, kNone>(p, plan_tiles(M, ff, k, 1, false, false), F32SwigluBackward{w.u, w.v}, s);
         }
-        if (io.want_grads()) gemm_reduce_rows(s, w.X, w.u, io.dWg, w.v, io.dWu, d, ff, M, w.parts, rows);     // dWg = X^T du, dWu = X^T dv
+        if (io.want_grads()) {
+            if (sums.n > 0 && split_floats(d, ff, M, 2) > 0) {                                         // the parts' memory is needed again
+                launch_finish(sh, io, w.out, sums, FinalPanel{}, false, SumsqLists{}, s);
+                sums = PartsSums{};
+            }
+            gemm_reduce_rows(s, w.X, w.u, io.dWg, w.v, io.dWu, d, ff, M, w.parts, sums, rows);     // dWg = X^T du, dWu = X^T dv
+        }
         if (io.dX) {                                                                                   // dX = du Wg^T + dv Wu^T
             // as two products, in place of y and dy (no longer needed), and their sum: twice the workgroups, sums half as long
             F32Problem p = problem(w.u, ff, Wg, ff, M, d, ff, rows, kLiveM);
             p.A2 = w.v; p.B2 = Wu;
-            const size_t n = (size_t)M * d;
             launch<kRowsByK, kRowsByK, kSum>(p, plan_tiles(M, d, ff, 2, false, false), F32Store{w.y, w.y, d, w.dy - w.y}, s);
-            const size_t want = (n + 255) / 256;
-            sum_live_rows<<<(unsigned)(want < 4096 ? want : 4096), 256, 0, s>>>(w.y, w.dy, n, d, io.n_kept, sh.max_chunks,
-                                                                                 sh.A, static_cast<float*>(io.dX));
+            sums.add(w.y, 2, (size_t)M * d, (size_t)(w.dy - w.y), static_cast<float*>(io.dX), false, nullptr, d);
         }
     }
-    return launch_status();
+    return launch_finish(sh, io, w.out, sums, FinalPanel{}, true, SumsqLists{}, s);
 }
 
 }  // namespace pcm

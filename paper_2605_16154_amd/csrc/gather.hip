@@ -6,6 +6,8 @@
 // kept_idx[r / A]); each workgroup moves a block of rows with 16-byte accesses, several loads in
 // flight per lane.  Rows at and beyond n_kept * A are zero-filled with advantage 0, so they add
 // nothing downstream.
+#include <algorithm>
+
 #include "actor.h"
 
 namespace pcm {
@@ -154,58 +156,117 @@ __global__ __launch_bounds__(kThreads) void prepare_step(GatherArgs<Vec> gather,
     if (i < zero.n) zero.p[i] = 0.0;
 }
 
+constexpr int kFinishThreads = 1024;
+// Sum over the workgroup by a fixed tree (thread 0 has the result).
+template <int kN>
+__device__ inline void tree_sum(double (&acc)[kN], double (&red)[kN][kFinishThreads]) {
+    for (int q = 0; q < kN; ++q) red[q][threadIdx.x] = acc[q];
+    __syncthreads();
+    for (int half = kFinishThreads / 2; half > 0; half >>= 1) {
+        if ((int)threadIdx.x < half)
+            for (int q = 0; q < kN; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + half];
+        __syncthreads();
+    }
+    for (int q = 0; q < kN; ++q) acc[q] = red[q][0];
+}
+__device__ inline void sum_lists(const SumsqLists& lists, double* out, double (&red)[1][kFinishThreads]) {
+    double sq[1] = {0.0};
+    for (int q = 0; q < 4; ++q)
+        for (int i = threadIdx.x; i < lists.count[q]; i += kFinishThreads) sq[0] += lists.parts[q][i];
+    tree_sum(sq, red);
+    if (threadIdx.x == 0) *out = sq[0];
+}
+__global__ __launch_bounds__(kFinishThreads) void sum_of_squares(SumsqLists lists, double* out) {
+    __shared__ double red[1][kFinishThreads];
+    sum_lists(lists, out, red);
+}
+
+struct LossReduceArgs {
+    RowOut row;
+    const int32_t* n_kept;
+    int max_chunks, A;
+    LossOptions opt;
+    float *loss_out, *stats_out;
+    int n_stats;
+};
 // One workgroup; lane-strided fp64 partials combined by a fixed tree, so the result does not
 // depend on anything but the row values.
-__global__ __launch_bounds__(1024) void loss_reduce(const float* __restrict__ term,
-                                                     const float* __restrict__ ratio,
-                                                     const float* __restrict__ dlogp,
-                                                     const uint8_t* __restrict__ clipped,
-                                                     const float* __restrict__ entropy,
-                                                     const int32_t* __restrict__ n_kept, int max_chunks, int A,
-                                                     LossOptions opt, float* loss_out, float* stats_out, int n_stats,
-                                                     SumsqLists lists) {
-    __shared__ double red[5][1024];
-    const int64_t rows = live_rows(n_kept, max_chunks, A);
+__device__ inline void reduce_loss(const LossReduceArgs& p) {
+    __shared__ double red[5][kFinishThreads];
+    const int64_t rows = live_rows(p.n_kept, p.max_chunks, p.A);
     double acc[5] = {0, 0, 0, 0, 0};
-    for (int64_t r = threadIdx.x; r < rows; r += 1024) {
-        acc[0] += (double)term[r];
-        acc[1] += (double)ratio[r];
-        acc[2] += (double)dlogp[r];
-        acc[3] += (double)clipped[r];
-        acc[4] += (double)entropy[r];
+    for (int64_t r = threadIdx.x; r < rows; r += kFinishThreads) {
+        acc[0] += (double)p.row.term[r];
+        acc[1] += (double)p.row.ratio[r];
+        acc[2] += (double)p.row.dlogp[r];
+        acc[3] += (double)p.row.clipped[r];
+        acc[4] += (double)p.row.entropy[r];
     }
-    for (int q = 0; q < 5; ++q) red[q][threadIdx.x] = acc[q];
+    tree_sum(acc, red);
+    if (threadIdx.x != 0) return;
+    const double scale = (double)objective_scale(p.opt, rows);
+    *p.loss_out = (float)(-scale * acc[0] - (double)p.opt.entropy_coef * scale * acc[4]);
+    if (p.stats_out) {
+        const double n = rows > 0 ? (double)rows : 1.0;
+        p.stats_out[0] = (float)(acc[3] / n);
+        p.stats_out[1] = (float)(acc[1] / n);
+        p.stats_out[2] = (float)(acc[2] / n);
+        p.stats_out[3] = (float)rows;
+        if (p.n_stats > 4) p.stats_out[4] = (float)(acc[4] / n);
+    }
+}
+
+// A workgroup's share of a sum of parts; returns the thread's sum of the squares of what it wrote.  Bound by memory: the
+// parts are read eight at a time, so that their loads are under way together (the five sums and the loss of a step of 5376 fp32 rows of
+// 256 -> 1024 -> 256: six launches of 46 us -> two of 20).
+template <class Vec>
+__device__ inline double sum_parts(const PartsSum& job, int block, int64_t live) {
+    constexpr int kPer = sizeof(Vec) / sizeof(float), kTogether = 8;
+    if ((int)threadIdx.x >= job.threads) return 0.0;
+    const size_t stride = (size_t)job.blocks * job.threads * kPer;
+    const size_t limit = job.live_row > 0 ? (size_t)((live + 127) / 128 * 128) * job.live_row : job.n;   // a multiple of 4, or n
+    double sq = 0.0;
+    for (size_t i = ((size_t)block * job.threads + threadIdx.x) * kPer; i < job.n; i += stride) {
+        auto part = [&](int s) { return *reinterpret_cast<const Vec*>(job.parts + (size_t)s * job.stride + i); };
+        Vec acc = {};
+        if (i < limit) {
+            acc = job.add ? *reinterpret_cast<const Vec*>(job.out + i) + part(0) : part(0);
+            for (int s0 = 1; s0 < job.n_parts; s0 += kTogether) {
+                Vec v[kTogether];
+#pragma unroll
+                for (int u = 0; u < kTogether; ++u) v[u] = part(min(s0 + u, job.n_parts - 1));
+#pragma unroll
+                for (int u = 0; u < kTogether; ++u)
+                    if (s0 + u < job.n_parts) acc = acc + v[u];
+            }
+        }
+        *reinterpret_cast<Vec*>(job.out + i) = acc;
+        if (job.sumsq != nullptr)
+            for (int e = 0; e < kPer; ++e) sq += (double)reinterpret_cast<const float*>(&acc)[e] * (double)reinterpret_cast<const float*>(&acc)[e];
+    }
+    return sq;
+}
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+__global__ __launch_bounds__(kFinishThreads) void finish_step(PartsSums sums, FinalPanel panel, LossReduceArgs loss, int with_loss) {
+    int block = blockIdx.x;
+    if (with_loss && block == 0) return reduce_loss(loss);       // first: it takes longest where the sums are small
+    block -= with_loss;
+    int which = 0;
+#pragma unroll
+    for (int q = 1; q < PartsSums::kMax; ++q) which += q < sums.n && block >= sums.job[q].first ? 1 : 0;
+    const PartsSum job = sums.job[which];
+    block -= job.first;
+    const int64_t live = job.live_row > 0 ? live_rows(loss.n_kept, loss.max_chunks, loss.A) : 0;
+    double sq = job.vec ? sum_parts<f32x4>(job, block, live) : sum_parts<float>(job, block, live);
+    if (job.sumsq == nullptr || !panel()) return;
+    __shared__ double wave_part[kFinishThreads / kWave];
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) sq += __shfl_xor(sq, o, kWave);
+    if (threadIdx.x % kWave == 0) wave_part[threadIdx.x / kWave] = sq;
     __syncthreads();
-    for (int half = 512; half > 0; half >>= 1) {
-        if ((int)threadIdx.x < half)
-            for (int q = 0; q < 5; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + half];
-        __syncthreads();
-    }
-    if (opt.grad_sumsq_out != nullptr && lists.parts[0] != nullptr) {   // uniform over the workgroup
-        __shared__ double red_sq[1024];
-        double sq = 0.0;
-        for (int q = 0; q < 4; ++q)
-            for (int i = threadIdx.x; i < lists.count[q]; i += 1024) sq += lists.parts[q][i];
-        red_sq[threadIdx.x] = sq;
-        __syncthreads();
-        for (int half = 512; half > 0; half >>= 1) {
-            if ((int)threadIdx.x < half) red_sq[threadIdx.x] += red_sq[threadIdx.x + half];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) *opt.grad_sumsq_out = red_sq[0];
-    }
-    if (threadIdx.x == 0) {
-        const double scale = (double)objective_scale(opt, rows);
-        *loss_out = (float)(-scale * red[0][0] - (double)opt.entropy_coef * scale * red[4][0]);
-        if (stats_out) {
-            const double n = rows > 0 ? (double)rows : 1.0;
-            stats_out[0] = (float)(red[3][0] / n);
-            stats_out[1] = (float)(red[1][0] / n);
-            stats_out[2] = (float)(red[2][0] / n);
-            stats_out[3] = (float)rows;
-            if (n_stats > 4) stats_out[4] = (float)(red[4][0] / n);
-        }
-    }
+    if (threadIdx.x != 0) return;
+    for (int q = 1; q < kFinishThreads / kWave; ++q) sq += wave_part[q];
+    job.sumsq[block] = sq;
 }
 
 // One wavefront per chunk slot.  rho_c = exp(sum over the chunk's tokens of (logp - logp_old)), the sum in fp64 (its terms
@@ -431,10 +492,46 @@ void launch_transposes(const TransposeList& list, bool stream, hipStream_t s) {
     else transpose_weights<false><<<(unsigned)list.blocks, kThreads, 0, s>>>(list);
 }
 
-int launch_loss_reduce(const ActorShape& sh, const ActorIO& io, RowOut out, const SumsqLists& lists, hipStream_t s) {
+// A CU reads about 70 GB/s, so a small sum of many parts wants many workgroups rather than full ones: the widest shape that
+// has 256 of them (56 parts of 65,536 floats in 16 / 256 workgroups 13 / 8 us; of few parts the thinner ones only take longer
+// to start).
+struct SumShape {
+    int blocks, threads, vec;
+};
+static SumShape sum_shape(size_t n_floats, bool may_vec, int n_parts) {
+    const SumShape shapes[4] = {{0, kFinishThreads, 1}, {0, kThreads, 1}, {0, kFinishThreads, 0}, {0, kThreads, 0}};
+    SumShape best{};
+    for (const SumShape& q : shapes) {
+        if (q.vec && !may_vec) continue;
+        best = q;
+        const int64_t want = ceil_div64((int64_t)n_floats, (int64_t)q.threads * (q.vec ? 4 : 1));
+        best.blocks = (int)std::min<int64_t>(want, PartsSums::kBlocksMax);
+        if (want >= 256 || n_parts < 16) break;
+    }
+    return best;
+}
+void PartsSums::add(const float* parts, int n_parts, size_t n_floats, size_t stride, float* out, bool add_to, double* sumsq, int live_row) {
+    PartsSum& p = job[n++];
+    p = PartsSum{parts, n_parts, add_to ? 1 : 0, n_floats, stride, out, sumsq, live_row, blocks, 0, 0, 0};
+    const bool may_vec = n_floats % 4 == 0 && stride % 4 == 0 && ((reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(parts)) & 15u) == 0;
+    const SumShape shape = sum_shape(n_floats, may_vec, n_parts);
+    p.blocks = shape.blocks;
+    p.threads = shape.threads;
+    p.vec = shape.vec;
+    blocks += p.blocks;
+}
+int PartsSums::blocks_for(size_t n_floats, int n_parts) {
+    return std::max(sum_shape(n_floats, true, n_parts).blocks, sum_shape(n_floats, false, n_parts).blocks);
+}
+
+int launch_finish(const ActorShape& sh, const ActorIO& io, RowOut out, const PartsSums& sums, const FinalPanel& panel, bool with_loss,
+                  const SumsqLists& lists, hipStream_t s) {
     StageTimer t(ST_REDUCE, s);
-    loss_reduce<<<1, 1024, 0, s>>>(out.term, out.ratio, out.dlogp, out.clipped, out.entropy, io.n_kept,
-                                   sh.max_chunks, sh.A, io.opt, io.loss_out, io.stats_out, io.n_stats, lists);
+    if (sums.blocks > 0 || with_loss)
+        finish_step<<<(unsigned)(sums.blocks + (with_loss ? 1 : 0)), kFinishThreads, 0, s>>>(
+            sums, panel, LossReduceArgs{out, io.n_kept, sh.max_chunks, sh.A, io.opt, io.loss_out, io.stats_out, io.n_stats},
+            with_loss ? 1 : 0);
+    if (lists.parts[0] != nullptr) sum_of_squares<<<1, kFinishThreads, 0, s>>>(lists, io.opt.grad_sumsq_out);
     return launch_status();
 }
 

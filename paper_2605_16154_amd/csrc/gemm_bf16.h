@@ -53,13 +53,14 @@ enum OperandLayout : int {
 constexpr int kTileM = 256, kTileN = 256, kTileK = 64;   // rows are padded to, and skipped in, units of kTileM whatever the tile
 constexpr int kGemmThreads = 256;
 constexpr int kNumXcd = 8;
-constexpr int kRingSlots = 5;    // operand tiles resident or in flight in LDS
 // Two tile sizes, 32 kW x 32 kW with kW x kW MFMA tiles per wavefront: 256 (kW = 8: one workgroup per CU, its operand
 // ring is the whole LDS) and 128 (kW = 4: two workgroups per CU) where the larger tile leaves CUs idle, see tile_for.
 constexpr int kLargeTile = 8, kSmallTile = 4;
 template <int kW> constexpr int kTile = 32 * kW;                     // rows and columns of a workgroup's tile
 template <int kW> constexpr int kWaveRows = 16 * kW;                 // rows and columns of a wavefront's part of it
-template <int kW> constexpr int kRingBytes = kRingSlots * kTile<kW> * kTileK * 2;   // 160 KB (the whole LDS) / 80 KB
+// Operand tiles resident or in flight in LDS: 160 KB, the whole LDS, or 80 KB.
+constexpr int kRingSlots = 5;
+template <int kW, int kSlots = kRingSlots> constexpr int kRingBytes = kSlots * kTile<kW> * kTileK * 2;
 // Epilogues pass their results through LDS so that global stores are whole 128-byte lines: each
 // wavefront owns a private staging area (no workgroup barrier needed; LDS operations of one
 // wavefront execute in order).
@@ -83,6 +84,11 @@ struct GemmProblem {
     const int32_t* kept;
     int kept_max, rows_per_kept, rows_role;
     int row_offset, skip_if_empty;
+    __device__ int live_rows() const {       // kept is set
+        int nk = *kept;
+        nk = nk < 0 ? 0 : (nk > kept_max ? kept_max : nk);
+        return max(0, nk * rows_per_kept - row_offset);
+    }
     // Operands chosen on the device: when set, the first-segment operand is read from *A_sel (*B_sel) instead of A
     // (B); an earlier kernel of the same stream decides which buffer that is.  Single reduction segment only.
     const bf16* const* A_sel;
@@ -228,6 +234,14 @@ __device__ inline bf16x8 join_halves(s16x4 lo, s16x4 hi) {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// A wave-uniform address as such: where bodies share a kernel the compiler may lose sight of it, and assembly takes it in
+// scalar registers.
+__device__ __forceinline__ const char* uniform_address(const void* p) {
+    const uint64_t at = (uint64_t)(uintptr_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)at), hi = __builtin_amdgcn_readfirstlane((uint32_t)(at >> 32));
+    return reinterpret_cast<const char*>((uintptr_t)((uint64_t)hi << 32 | lo));
+}
+
 // Addresses of LDS reads, written as assembly so that they stay where the main loop puts them, a gap before the read.
 __device__ __forceinline__ uint32_t fragment_address(uint32_t base, int xor_with) {
     uint32_t at;
@@ -253,13 +267,19 @@ constexpr auto paired_columns(int) -> decltype(E::kPairedColumns) { return E::kP
 template <class E>
 constexpr bool paired_columns(long) { return false; }
 
-template <class Epilogue, int kLayA, int kLayB, int kW>
-__global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_bf16(GemmProblem p, Epilogue epi) {
+template <int kW, int kSlots>
+struct OperandRing {
+    __attribute__((aligned(1024))) __bf16 data[kRingBytes<kW, kSlots> / 2];   // [slot][row][64]
+};
+
+// The work of workgroup `block` of a product; smem: the kernel's LDS.
+template <int kLayA, int kLayB, class Epilogue, int kW, int kSlots>
+__device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& epi, int block, OperandRing<kW, kSlots>& smem) {
     constexpr int TM = kTile<kW>, TN = kTile<kW>;
     constexpr uint32_t kTileBytes = TM * kTileK * 2;             // one operand tile
     constexpr int kLoadsPerTile = kW;                            // wave-wide loads per wavefront per tile
-    constexpr int kSmemBytes = kRingBytes<kW>;
-    __shared__ __attribute__((aligned(1024))) __bf16 smem[kSmemBytes / 2];   // [slot][row][64]
+    constexpr int kSmemBytes = kRingBytes<kW, kSlots>;
+    constexpr int kAhead = kSlots / 2;                           // steps requested ahead of the one being multiplied
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept in a scalar register
@@ -267,12 +287,11 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
     const int tiles_m = p.M / TM;
     int tiles_n = p.N / TN, n_first = 0;
     const int n_tiles = tiles_m * tiles_n;
-    const int split = blockIdx.x / n_tiles;
+    const int split = block / n_tiles;
+    if (split >= p.splits) return;                               // workgroups are launched in multiples of eight in a group
     int k1 = p.K1, live_m = tiles_m;
     if (p.kept != nullptr) {
-        int nk = *p.kept;
-        nk = nk < 0 ? 0 : (nk > p.kept_max ? p.kept_max : nk);
-        const int rows = max(0, nk * p.rows_per_kept - p.row_offset);
+        const int rows = p.live_rows();
         if (p.rows_role == kRowsAreM) live_m = min(tiles_m, (rows + kTileM - 1) / kTileM * (kTileM / TM));
         if (p.rows_role == kRowsAreK) k1 = min(k1, (rows + kTileK - 1) / kTileK * kTileK);
     }
@@ -282,7 +301,7 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
         tiles_n = (p.cut == kCutTail ? columns : p.N / kTileN - columns) * (kTileN / TN);
     }
     int tm, tn;
-    if (!tile_of_workgroup<kW>(blockIdx.x % n_tiles, n_tiles, live_m, tiles_n, tm, tn)) return;   // before any barrier
+    if (!tile_of_workgroup<kW>(block % n_tiles, n_tiles, live_m, tiles_n, tm, tn)) return;   // before any barrier
     const int m0 = tm * TM, n0 = n_first + tn * TN;
     // reduction range of this workgroup, in 64-wide steps over the concatenation of both segments
     const int steps1 = k1 / kTileK, steps_all = steps1 + p.K2 / kTileK;
@@ -298,7 +317,7 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
     //     per load; piece p of row r sits in slot swizzle_piece(r, p).
     //   [K][rows] operand: the tile is [64 k][64 kW B]; wave w fills k-rows [16 w, 16 w + 16), 16 / kW per
     //     load; the 32-byte unit u of k-row k sits in unit swizzle_unit(u, k).
-    const uint32_t lds_base = (uint32_t)(uintptr_t)PCM_AS_LDS(smem);
+    const uint32_t lds_base = (uint32_t)(uintptr_t)PCM_AS_LDS(smem.data);
     struct LoadCtx {
         const char* base;        // wave-uniform
         uint32_t off[4];         // per-lane byte offset of a load before the per-load stride, by load_variant()
@@ -326,8 +345,8 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
                 lane_off[operand][var] = (row * ld + piece * 8u) * 2u;
             }
             load_stride[operand] = 16u * ld;
-            seg_origin[operand][0] = reinterpret_cast<const char*>(s1 + (int64_t)row0 * ld);
-            seg_origin[operand][1] = reinterpret_cast<const char*>(s2 + (int64_t)row0 * ld);
+            seg_origin[operand][0] = uniform_address(s1 + (int64_t)row0 * ld);
+            seg_origin[operand][1] = uniform_address(s2 + (int64_t)row0 * ld);
             k_step_bytes[operand] = kTileK * 2;
         } else {
             constexpr int kLanes = 4 * kW;                                            // lanes per k-row
@@ -339,8 +358,8 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
                 lane_off[operand][var] = (krow * ld + piece * 8u) * 2u;
             }
             load_stride[operand] = (32u / kW) * ld;
-            seg_origin[operand][0] = reinterpret_cast<const char*>(s1 + row0);
-            seg_origin[operand][1] = reinterpret_cast<const char*>(s2 + row0);
+            seg_origin[operand][0] = uniform_address(s1 + row0);
+            seg_origin[operand][1] = uniform_address(s2 + row0);
             k_step_bytes[operand] = (uint32_t)kTileK * ld * 2u;
         }
     }
@@ -410,15 +429,12 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
 
     if (step_begin < step_end) {
         // Operand tiles are numbered 2 s + o (o = 0 for A, 1 for B of step s) and tile t lives in ring
-        // slot t mod 5.  Prologue: tiles 0..4 (steps 0, 1 and the A tile of step 2) are requested;
-        // steps past the end re-request the last step's tiles, which nobody reads.
+        // slot t mod kSlots.  Prologue: as many tiles as there are slots (five: steps 0, 1 and the A tile of step 2) are
+        // requested; steps past the end re-request the last step's tiles, which nobody reads.
         const int last = step_end - 1;
-        issue_tile(0, 0 * kTileBytes, step_begin);
-        issue_tile(1, 1 * kTileBytes, step_begin);
-        issue_tile(0, 2 * kTileBytes, min(step_begin + 1, last));
-        issue_tile(1, 3 * kTileBytes, min(step_begin + 1, last));
-        issue_tile(0, 4 * kTileBytes, min(step_begin + 2, last));
-        wait_direct_loads<3 * kLoadsPerTile>();
+#pragma unroll
+        for (int t = 0; t < kSlots; ++t) issue_tile(t & 1, (uint32_t)t * kTileBytes, min(step_begin + t / 2, last));
+        wait_direct_loads<(kSlots - 2) * kLoadsPerTile>();
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < kW; ++i) {
@@ -429,9 +445,9 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
         // One 64-wide step per trip.  `sa`, `sb` are the slots of this step's tiles, `na`, `nb` the next step's, the two
         // after them in the ring.  Fragment set 0 holds slice 0 of this step on entry and slice 0 of the next step on
         // exit.  The single barrier sits before the second slice: by then every wavefront has issued all its reads of
-        // `sa`, `sb`, so both slots can be refilled, `sa` with the B tile of step + 2 (during the second slice) and `sb`
-        // with the A tile of step + 3 (during the next step's first).  At the barrier only the newest tile (the A tile)
-        // may still be in flight.  The body is branch-free: near the end it re-requests tiles that nobody reads.
+        // `sa`, `sb`, so both slots can be refilled, `sa` with the B tile of step + kAhead (during the second slice) and `sb`
+        // with the A tile of step + kAhead + 1 (during the next step's first).  At the barrier the next step's tiles must have
+        // landed and only newer ones (of five slots, the newest A tile) may still be in flight.  The body is branch-free: near the end it re-requests tiles that nobody reads.
         //
         // A wavefront issues in order and an MFMA keeps the matrix pipe busy for 16 cycles.  Measured with one wavefront
         // per SIMD: between two MFMAs one scalar instruction, two vector instructions or an LDS read cost nothing, three
@@ -504,18 +520,18 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
             });
         };
         // Tile streams: origin of the newest tile requested so far of each operand.  On entry of a step the newest A
-        // tile is that of step + 2 (its loads are those of the first slice: on the first trip a harmless second request),
-        // the newest B tile that of step + 1; the first slice then moves each on by one step.  Past `last` an origin
+        // tile is that of step + kAhead (its loads are those of the first slice: on the first trip a harmless second request),
+        // the newest B tile one step before that; the first slice then moves each on by one step.  Past `last` an origin
         // stands still, or lands once on the start of the second segment, which is valid memory whether or not that
         // segment is used.
-        const char* origin_a = tile_origin(0, min(step_begin + 2, last));
-        const char* origin_b = tile_origin(1, min(step_begin + 1, last));
-        uint32_t sa = 0, sb = next_slot(sa), refill_a = 4 * kTileBytes, na = next_slot(sb), nb = next_slot(na);
+        const char* origin_a = tile_origin(0, min(step_begin + kAhead, last));
+        const char* origin_b = tile_origin(1, min(step_begin + kAhead - 1, last));
+        uint32_t sa = 0, sb = next_slot(sa), refill_a = (kSlots - 1) * kTileBytes, na = next_slot(sb), nb = next_slot(na);
         uint32_t rd_a = base_a[1] + sa, rd_b = base_b[1] + sb, stride_now = 0;
         // In six pieces of two or three scalar instructions; the A origin only after the last load from it.
         auto between_a = [&](int step, int piece) {
             const int operand = piece < 3 ? 1 : 0;
-            const int at = step + 2 + (operand == 0 ? 1 : 0);
+            const int at = step + kAhead + (operand == 0 ? 1 : 0);
             const char*& origin = operand == 0 ? origin_a : origin_b;
             if (piece % 3 == 0) {
                 stride_now = at <= last ? k_step_bytes[operand] : 0u;
@@ -537,9 +553,9 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
         };
         for (int step = step_begin; step < step_end; ++step) {
             slice(0, Index<0>{}, load_ctx_at(0, refill_a, origin_a), rd_a, rd_b, [&](int piece) { between_a(step, piece); });
-            wait_direct_loads<kLoadsPerTile>();
+            wait_direct_loads<(kSlots - 4) * kLoadsPerTile>();
             __syncthreads();
-            slice(1, Index<1>{}, load_ctx_at(1, sa, origin_b), rd_a, rd_b, between_b);   // tile 2 s + 5 -> slot of tile 2 s
+            slice(1, Index<1>{}, load_ctx_at(1, sa, origin_b), rd_a, rd_b, between_b);   // tile 2 s + kSlots -> slot of tile 2 s
         }
         wait_direct_loads<0>();
         // the last MFMAs' results: the compiler does not know how long inline assembly takes to write them
@@ -549,7 +565,61 @@ __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile ? 1 : 2) void gemm_b
 
     if (p.skip_if_empty && step_begin >= step_end && !runs_when_empty(epi, 0)) return;   // nothing to add (uniform over the workgroup)
     const TileCoord<kW> tc{m0, n0, wm, wn, lane, split};
-    epi(tc, acc, reinterpret_cast<char*>(smem));
+    epi(tc, acc, reinterpret_cast<char*>(smem.data));
+}
+
+template <class Epilogue, int kLayA, int kLayB, int kW, int kSlots = kRingSlots>
+__global__ __launch_bounds__(kGemmThreads, kW == kLargeTile || kSlots > kRingSlots ? 1 : 2) void gemm_bf16(GemmProblem p, Epilogue epi) {
+    __shared__ OperandRing<kW, kSlots> smem;
+    gemm_tile<kLayA, kLayB>(p, epi, blockIdx.x, smem);
+}
+
+// Products that depend on the same launches and not on one another, as one launch: the workgroups of one fill the CUs that
+// another leaves idle (its last, part-filled round, or all through where it has few tiles), its reductions need fewer parts to
+// fill the chip, and of a small head a launch takes as long to begin and end as its products do.  Figures at BackwardPlan.
+template <int kLayA, int kLayB, class Epilogue>
+struct GemmJob {
+    GemmProblem p;
+    Epilogue epi;
+    int first;                   // its first workgroup, a multiple of eight (see tile_of_workgroup)
+    int workgroups(int tile) const { return p.M / tile * (p.N / tile) * p.splits; }
+    template <int kW, int kSlots>
+    __device__ __forceinline__ void run(int block, OperandRing<kW, kSlots>& smem) const {
+        gemm_tile<kLayA, kLayB>(p, epi, block - first, smem);
+    }
+};
+// Two products of the same A and sizes with a right operand and a result each.
+template <int kLayA, int kLayB, class Epilogue>
+struct GemmPairJob {
+    GemmProblem p;
+    const bf16* B[2];
+    Epilogue epi[2];
+    int first, each;             // workgroups of one product, a multiple of eight
+    int workgroups(int tile) {
+        each = ceil_div(p.M / tile * (p.N / tile) * p.splits, kNumXcd) * kNumXcd;
+        return 2 * each;
+    }
+    template <int kW, int kSlots>
+    __device__ __forceinline__ void run(int block, OperandRing<kW, kSlots>& smem) const {
+        const bool second = block - first >= each;
+        GemmProblem q = p;
+        q.B = q.B2 = second ? B[1] : B[0];       // (an index instead of the choice would put the pair into scratch memory)
+        gemm_tile<kLayA, kLayB>(q, epi[0].or_second(second, epi[1]), block - first - (second ? each : 0), smem);
+    }
+};
+// The last job whose first workgroup is not beyond `block` runs it.
+template <class Ring, class Job>
+__device__ __forceinline__ void run_job(int block, Ring& smem, const Job& job) { job.run(block, smem); }
+template <class Ring, class Job, class Next, class... More>
+__device__ __forceinline__ void run_job(int block, Ring& smem, const Job& job, const Next& next, const More&... more) {
+    if (block < next.first) job.run(block, smem);
+    else run_job(block, smem, next, more...);
+}
+template <int kW, int kSlots, class... Jobs>
+__global__ __launch_bounds__(kGemmThreads, kW == kLargeTile || kSlots > kRingSlots ? 1 : 2) void gemm_group(Jobs... jobs) {
+    __shared__ OperandRing<kW, kSlots> smem;
+    const int block = blockIdx.x;
+    run_job(block, smem, jobs...);
 }
 
 // ---- epilogues -------------------------------------------------------------------------------
@@ -767,18 +837,6 @@ struct EpiStoreBf16Split {
     }
 };
 
-// Whether a row panel [row_begin, row_end) of a batch holds the batch's last live rows (panel 0 if there are none):
-// the weight gradients that panel leaves are the final ones.
-struct FinalPanel {
-    const int32_t* n_kept;
-    int max_chunks, A;
-    int64_t row_begin, row_end;
-    __device__ bool operator()() const {
-        const int64_t rows = live_rows(n_kept, max_chunks, A);
-        return rows <= row_end && (rows > row_begin || row_begin == 0);
-    }
-};
-
 // C (fp32, row-major) = acc.  With a split reduction, part s goes to C + s * split_stride (its own
 // M x N matrix; the caller sums the parts), so no atomics are needed and the sum is reproducible.
 // accumulate: C += acc instead (a batch processed in row panels adds every panel's weight gradient).
@@ -793,6 +851,10 @@ struct EpiStoreF32 {
     double* sumsq_parts;
     FinalPanel final_panel;
     __device__ bool runs_when_empty() const { return sumsq_parts != nullptr && final_panel(); }
+    // This one or `other`, which differs in where it stores.
+    __device__ EpiStoreF32 or_second(bool second, const EpiStoreF32& other) const {
+        return EpiStoreF32{second ? other.C : C, ldc, split_stride, accumulate, second ? other.sumsq_parts : sumsq_parts, final_panel};
+    }
     template <int kW>
     __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
         constexpr int RW = kWaveRows<kW>;                  // rows and columns of the wavefront's block
@@ -987,6 +1049,19 @@ template <int kLayA = kRowsByK, int kLayB = kRowsByK, int kW = kLargeTile, class
 inline void launch_gemm_tile(const GemmProblem& p, const Epilogue& epi, hipStream_t s) {
     const unsigned grid = (unsigned)(p.M / kTile<kW>) * (unsigned)(p.N / kTile<kW>) * (unsigned)p.splits;
     gemm_bf16<Epilogue, kLayA, kLayB, kW><<<grid, kGemmThreads, 0, s>>>(p, epi);
+}
+// The jobs of a group in one launch on tiles of kW; the longest reductions first.
+template <class Job>
+inline int place_job(Job& job, int tile, int first) {
+    job.first = first;
+    return first + ceil_div(job.workgroups(tile), kNumXcd) * kNumXcd;
+}
+template <class... Jobs>
+inline void launch_gemm_group(int kW, hipStream_t s, Jobs... jobs) {
+    int grid = 0;
+    ((grid = place_job(jobs, 32 * kW, grid)), ...);
+    if (kW == kLargeTile) gemm_group<kLargeTile, kRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
+    else gemm_group<kSmallTile, kRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
 }
 template <int kLayA = kRowsByK, int kLayB = kRowsByK, class Epilogue>
 inline void launch_gemm(const GemmProblem& p, const Epilogue& epi, hipStream_t s) {

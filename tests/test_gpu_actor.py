@@ -724,3 +724,51 @@ def test_packed_head_weights_are_the_transposes(pcm, d, ff):
     assert torch.equal(gate_up[:, 0].reshape(ff, d), Wg.t()) and torch.equal(gate_up[:, 1].reshape(ff, d), Wu.t())
     assert torch.equal(packed[2 * ff * d:3 * ff * d].view(d, ff), Wd.t())
     assert torch.equal(packed[3 * ff * d:3 * ff * d + 256 * d].view(256, d), Wo.t())
+
+
+@pytest.mark.parametrize("d,ff,V,n_kept,offset", [
+    (33, 65, 17, 46, 0),       # results of odd sizes: single floats, up to 41 slices per weight gradient
+    (36, 64, 20, 46, 1),       # sizes for 16-byte accesses, results one float off their alignment
+    (64, 64, 64, 46, 0),       # 16-byte accesses in thin workgroups
+    (40, 72, 24, 3, 0),        # fewer slices than the launch reads together
+])
+def test_fp32_sums_of_slices_at_odd_sizes_and_alignments(pcm, d, ff, V, n_kept, offset):
+    """Weight gradients and dX as sums of slices that one launch adds up; rows of dX beyond the kept ones are zeros."""
+    cfg = CONFIGS["cfg1"].with_(n_groups=2, G=4, N=12, K=3, B=7, d=d, ff=ff, V=V, seed=90 + d)
+    ro = make_rollouts(cfg, 0)
+    _, active = O.advantages(ro["reward"], cfg.G)
+    kept, _, _ = O.sample_chunks(np.array([1.0, 0.3, 0.5]), ro["phase"], None, active, cfg.B, cfg.seed, 0)
+    assert len(kept) >= n_kept
+    # logits of a half: dz = c (1 - p) loses relative accuracy as 2^-24 / (1 - p), and here 1 - p > 0.4 for every row
+    pr = make_problem(cfg, wstd=0.9 / np.sqrt(d), margin=1e-3, kept=kept[:n_kept], old_rel=0.2, eps=(0.2, 0.4))
+    shapes = {"dWg": (d, ff), "dWu": (d, ff), "dWd": (ff, d), "dWo": (d, V), "dX": ((n_kept + 3) * cfg.A, d)}
+    out = {k: torch.full((s[0] * s[1] + offset,), 7.0, device="cuda")[offset:].view(s) for k, s in shapes.items()}
+    ref, got = run_both(pcm, pr, eps=(0.2, 0.4), max_kept=n_kept + 3, out=out)
+    check(ref, got, 1e-5, len(ref["rows"]))
+    assert np.exp(ref["logp"]).max() < 0.6
+    assert not got["dX"][len(ref["rows"]):].any()
+
+
+@pytest.mark.parametrize("d,ff,n_kept,max_kept,options", [
+    (512, 768, 37, 40, dict(composed_head=True)),
+    (512, 768, 37, 40, {}),
+    (768, 2304, 3, 11, dict(dense_backward=True)),     # live rows well below the capacity that the launches are planned for
+    (256, 5120, 60, 60, {}),                           # wide: parts for dWo only
+])
+def test_bf16_products_that_share_a_launch(pcm, d, ff, n_kept, max_kept, options):
+    """Products of the backward pass share launches with whatever else is asked for: dX alone, the weight gradients alone and
+    both give the same bits, and both match the checker."""
+    cfg = CONFIGS["cfg2"].with_(n_groups=2, G=4, N=16, K=4, B=8, d=d, ff=ff, seed=95)
+    ro = make_rollouts(cfg, 0)
+    _, active = O.advantages(ro["reward"], cfg.G)
+    kept, _, _ = O.sample_chunks(np.array([1.0, 0.3, 0.1, 0.6]), ro["phase"], None, active, cfg.B, cfg.seed, 0)
+    pr = make_problem(cfg, wstd=1.1 / np.sqrt(d), margin=0.08, kept=kept[:n_kept], old_rel=0.1, eps=(0.2, 0.4))
+    kw = dict(eps=(0.2, 0.4), torch_dtype=torch.bfloat16, max_kept=max_kept, **options)
+    ref, both = run_both(pcm, pr, **kw)
+    n = len(ref["rows"])
+    check(ref, both, BF16_TOL, n, stats_tol=5e-2)
+    _, rows_only = run_both(pcm, pr, want_grads=False, **kw)
+    assert np.array_equal(rows_only["dX"][:n], both["dX"][:n])
+    _, weights_only = run_both(pcm, pr, want_dX=False, **kw)
+    for k in GRADS:
+        assert np.array_equal(weights_only[k], both[k]), k
