@@ -313,8 +313,9 @@ GroupPlan plan_group(const GroupShape (&jobs)[kN]) {
     return best;
 }
 
-// Launches shared by products of one dependency level, one launch per product / shared: 2072 rows of 512 -> 768 107 -> 79 us per
-// step, 448 of 3072 -> 768 156 -> 106; at 4096 -> 11008 with every row, 4086 rows (mean) 2667 -> 2513, 10,752 6340 -> 6240.
+// Whole steps with a launch per product / with launches shared by the products of a dependency level (and the sums at the
+// end): 2072 rows of 512 -> 768 121 / 79 us, 448 of 3072 -> 768 137 / 107, 512 of 3072 -> 1536 182 / 145, 5376 of 3328 -> 7168
+// 1578 / 1454; at 4096 -> 11008 4704 rows, three quarters live, 2679 / 2530, 10,752 with a chunk ratio 6758 / 6500.
 //
 // Rows of a panel up to which the listed rows of a, du and dv have buffers of their own, so that dWd, which reads the first,
 // and da, which writes the others, may run side by side.
