@@ -45,17 +45,19 @@ constexpr size_t kSumBlocksMax = PartsSums::kBlocksMax;
 // out[i] = the sum over the parts of a split reduction (n is a multiple of 4; parts are n floats apart), rounded once to bf16: a
 // product that the next GEMM takes as an operand.
 __global__ void sum_parts_bf16(const float* parts, int n_parts, size_t n, bf16* out) {
+    constexpr int kTogether = 4;      // loads under way together
     const size_t stride = (size_t)gridDim.x * blockDim.x * 4;
     for (size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < n; i += stride) {
-        float4 acc = *reinterpret_cast<const float4*>(parts + i);
-        for (int s = 1; s < n_parts; ++s) {
-            const float4 v = *reinterpret_cast<const float4*>(parts + (size_t)s * n + i);
-            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+        f32x4 acc = *reinterpret_cast<const f32x4*>(parts + i);
+        for (int s0 = 1; s0 < n_parts; s0 += kTogether) {
+            f32x4 v[kTogether];
+#pragma unroll
+            for (int u = 0; u < kTogether; ++u) v[u] = *reinterpret_cast<const f32x4*>(parts + (size_t)min(s0 + u, n_parts - 1) * n + i);
+#pragma unroll
+            for (int u = 0; u < kTogether; ++u)
+                if (s0 + u < n_parts) acc += v[u];
         }
-        out[i] = __float2bfloat16(acc.x);
-        out[i + 1] = __float2bfloat16(acc.y);
-        out[i + 2] = __float2bfloat16(acc.z);
-        out[i + 3] = __float2bfloat16(acc.w);
+        *reinterpret_cast<bf16x4*>(out + i) = to_bf16x4(acc[0], acc[1], acc[2], acc[3]);
     }
 }
 
@@ -276,38 +278,54 @@ struct GroupShape {
     int64_t M, N;
     int steps, count;      // `count` products of these sizes
     bool split;            // whether the reduction may be split (fp32 parts, summed by a later launch)
+    int shortest = 1;      // and into no fewer steps than these
 };
 struct GroupPlan {
     static constexpr int kMax = 4;
     int kW, splits[kMax];
 };
 template <int kN>
-GroupPlan plan_group(const GroupShape (&jobs)[kN]) {
+GroupPlan plan_group(const GroupShape (&jobs)[kN], float us_sum) {
+    // (little arithmetic: every call of a step comes through here, and a small one is bound by the host)
+    int large[kN], most_splits[kN], longest_split = 0;
+    float part_us[kN];                                   // writing or reading one part
+    for (int q = 0; q < kN; ++q) {
+        const GroupShape& j = jobs[q];
+        large[q] = (int)(j.M / kTileM) * (int)(j.N / kTileN);
+        most_splits[q] = j.split ? std::max(1, std::min({(int)kMaxSplitTiles / large[q], j.steps / j.shortest, 64})) : 1;
+        part_us[q] = (float)large[q] * (float)j.count * (kTileM * kTileN * 4 / 4e6f);
+        if (most_splits[q] > 1) longest_split = std::max(longest_split, j.steps);
+    }
     GroupPlan best{};
-    double best_us = 0.0;
+    float best_us = 0.f;
     for (int kW : {kLargeTile, kSmallTile}) {
-        const double us_per_step = kW == kLargeTile ? 0.94 : 0.46, us_fixed = kW == kLargeTile ? 5.0 : 3.0;
+        const float us_per_step = kW == kLargeTile ? 0.94f : 0.46f, us_fixed = kW == kLargeTile ? 5.f : 3.f;
+        const int tiles_per_large = kW == kLargeTile ? 1 : 4;
         for (int most : {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 1 << 20}) {     // longest reduction of a workgroup
-            GroupPlan plan{kW, {}};
-            double longest = 0.0, work = 0.0, sum_bytes = 0.0;
-            int64_t workgroups = 0;
-            for (int q = 0; q < kN; ++q) {
-                const GroupShape& j = jobs[q];
-                const int64_t tiles = j.M / (32 * kW) * (j.N / (32 * kW)), large = j.M / kTileM * (j.N / kTileN);
-                int s = 1;
-                if (j.split) s = (int)std::max<int64_t>(1, std::min({ceil_div64(j.steps, most), (int64_t)kMaxSplitTiles / large, (int64_t)64}));
-                plan.splits[q] = s;
-                const int len = ceil_div(j.steps, s);
-                longest = std::max(longest, us_fixed + us_per_step * len);
-                workgroups += tiles * s * j.count;
-                work += (double)(tiles * s * j.count) * (us_fixed + us_per_step * len);
-                if (s > 1) sum_bytes += (double)(2 * s + 1) * j.M * j.N * 4.0 * j.count;
+            if (most < longest_split || most == 1 << 20 || longest_split == 0) {
+                GroupPlan plan{kW, {}};
+                int steps = 0;                           // of the longest workgroup
+                int64_t workgroups = 0;
+                float work = 0.f, sum = 0.f;
+                for (int q = 0; q < kN; ++q) {
+                    const GroupShape& j = jobs[q];
+                    const int s = std::min(most_splits[q], ceil_div(j.steps, most)), len = s > 1 ? ceil_div(j.steps, s) : j.steps;
+                    plan.splits[q] = s;
+                    steps = std::max(steps, len);
+                    const int64_t n = (int64_t)large[q] * (tiles_per_large * s * j.count);
+                    workgroups += n;
+                    work += (float)n * (us_fixed + us_per_step * (float)len);
+                    if (s > 1) sum += (float)(2 * s + 1) * part_us[q];
+                }
+                float us = us_fixed + us_per_step * (float)steps;
+                if (workgroups > 256) us = std::max(us, work / 256 + 0.5f * work / (float)workgroups);
+                if (sum > 0.f) us += us_sum + sum;
+                if (best.kW == 0 || us < best_us) {
+                    best = plan;
+                    best_us = us;
+                }
             }
-            const double us = std::max(longest, work / 256 + 0.5 * work / (double)workgroups) + sum_bytes / 4e6 + (sum_bytes > 0.0 ? 2.0 : 0.0);
-            if (best.kW == 0 || us < best_us) {
-                best = plan;
-                best_us = us;
-            }
+            if (longest_split == 0) break;
         }
     }
     return best;
@@ -340,16 +358,16 @@ BackwardPlan plan_backward(const ActorShape& sh, int64_t Rp, bool composed, bool
     const int rows = (int)(Rp / kTileK), by_d = sh.d / kTileK, by_ff = sh.ff / kTileK, by_V = sh.V / kTileK;
     BackwardPlan b{};
     if (composed) {
-        b.level[0] = plan_group<2>({{Rp, ff, by_V, 1, false}, {ff, V, rows, 1, true}});
-        b.level[2] = plan_group<4>({{Rp, d, 2 * by_ff, 1, false}, {d, ff, rows, 2, true}, {d, V, by_ff, 1, true}, {ff, d, by_V, 1, false}});
+        b.level[0] = plan_group<2>({{Rp, ff, by_V, 1, false}, {ff, V, rows, 1, true}}, 2.f);
+        b.level[2] = plan_group<4>({{Rp, d, 2 * by_ff, 1, false}, {d, ff, rows, 2, true}, {d, V, by_ff, 1, true}, {ff, d, by_V, 1, false}}, 2.f);
         b.split_G = b.level[0].splits[1];
         b.split_o = b.level[2].splits[2];
         b.split_d = 1;
         b.group[0] = b.group[2] = true;
     } else {
-        b.level[0] = plan_group<2>({{Rp, d, by_V, 1, false}, {d, V, rows, 1, true}});
-        b.level[1] = plan_group<2>({{Rp, ff, by_d, 1, false}, {ff, d, rows, 1, true}});
-        b.level[2] = plan_group<2>({{Rp, d, 2 * by_ff, 1, false}, {d, ff, rows, 2, true}});
+        b.level[0] = plan_group<2>({{Rp, d, by_V, 1, false}, {d, V, rows, 1, true}}, 2.f);
+        b.level[1] = plan_group<2>({{Rp, ff, by_d, 1, false}, {ff, d, rows, 1, true}}, 2.f);
+        b.level[2] = plan_group<2>({{Rp, d, 2 * by_ff, 1, false}, {d, ff, rows, 2, true}}, 2.f);
         b.group[0] = true;
         b.group[1] = !listed || Rp <= kApartRows;
         b.group[2] = Rp / kTileM * (d / kTileN) <= kGroupTiles;
@@ -432,7 +450,8 @@ Bf16Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool grads, const 
         w.live_idx = c.take<int32_t>(Rp);
         w.plan = c.take<LivePlan>(1);
     }
-    const BackwardPlan& plan = w.plan_b = plan_backward(sh, (int64_t)Rp, composed, lists_live_rows(opt, bwd, composed));
+    if (bwd) w.plan_b = plan_backward(sh, (int64_t)Rp, composed, lists_live_rows(opt, bwd, composed));
+    const BackwardPlan& plan = w.plan_b;
     if (grads) {
         if (plan.split_o > 1) w.parts_o = c.take<float>((size_t)plan.split_o * d * V);
         if (plan.split_d > 1) w.parts_d = c.take<float>((size_t)plan.split_d * ff * d);
@@ -507,24 +526,19 @@ GemmProblem problem(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int 
 }
 
 // C [M, N] bf16 = a product over the rows of the batch.  With few tiles and a long reduction it is computed as parts of a
-// split reduction (fp32) and summed: the operands then arrive over twice as many workgroups, and it is their latency and
-// not the products that such a launch waits for.  768 x 4096 x 11008 (192 small tiles): 124 us in one part, 97 us in two
-// with the sum.
+// split reduction (fp32) and summed, if the estimate of plan_group says so; at least 16 steps a part.
+// Measured, whole passes without gradients, before (small tiles only, at most four parts) / now: 672 rows of 4096 -> 11008, five
+// parts on large tiles, 262 / 237 us (its down projection 96 -> 62, the sum 6 -> 10); 512 of 512 -> 9984 58.7 / 52.2; 896 of
+// 2304 -> 2560 86 / 79.
 void launch_rows_bf16(GemmProblem p, bf16* C, float* parts, hipStream_t s) {
-    const int tiles = (p.M / kTileM) * (p.N / kTileN), steps = (p.K1 + p.K2) / kTileK;
-    if (tile_for(p.M, p.N, 1) == kSmallTile) {
-        int splits = 512 / (4 * tiles);                 // two small tiles per CU
-        if (splits > steps / 16) splits = steps / 16;
-        if (splits > 4) splits = 4;
-        if (splits > 1) {
-            p.splits = splits;
-            const size_t n = (size_t)p.M * p.N;
-            launch_gemm_tile<kRowsByK, kRowsByK, kSmallTile>(p, EpiStoreF32{parts, p.N, (int64_t)n, 0, nullptr, FinalPanel{}}, s);
-            launch_sum_bf16(parts, splits, n, C, s);
-            return;
-        }
-    }
-    launch_row_gemm(p, EpiStoreBf16{C, p.N, p.M}, s);
+    const GroupPlan plan = plan_group<1>({{p.M, p.N, (p.K1 + p.K2) / kTileK, 1, true, 16}}, 5.f);
+    if (plan.splits[0] == 1) return launch_row_gemm(p, EpiStoreBf16{C, p.N, p.M}, s);
+    p.splits = plan.splits[0];
+    const size_t n = (size_t)p.M * p.N;
+    const EpiStoreF32 epi{parts, p.N, (int64_t)n, 0, nullptr, FinalPanel{}};
+    if (plan.kW == kSmallTile) launch_gemm_tile<kRowsByK, kRowsByK, kSmallTile>(p, epi, s);
+    else launch_gemm_tile<kRowsByK, kRowsByK, kLargeTile>(p, epi, s);
+    launch_sum_bf16(parts, p.splits, n, C, s);
 }
 
 }  // namespace

@@ -216,6 +216,8 @@ __device__ inline void reduce_loss(const LossReduceArgs& p) {
     }
 }
 
+__global__ __launch_bounds__(kFinishThreads) void finish_loss(LossReduceArgs loss) { reduce_loss(loss); }
+
 // A workgroup's share of a sum of parts; returns the thread's sum of the squares of what it wrote.  Bound by memory: the
 // parts are read eight at a time, so that their loads are under way together (the five sums and the loss of a step of 5376 fp32 rows of
 // 256 -> 1024 -> 256: six launches of 46 us -> two of 20).
@@ -527,10 +529,11 @@ int PartsSums::blocks_for(size_t n_floats, int n_parts) {
 int launch_finish(const ActorShape& sh, const ActorIO& io, RowOut out, const PartsSums& sums, const FinalPanel& panel, bool with_loss,
                   const SumsqLists& lists, hipStream_t s) {
     StageTimer t(ST_REDUCE, s);
-    if (sums.blocks > 0 || with_loss)
-        finish_step<<<(unsigned)(sums.blocks + (with_loss ? 1 : 0)), kFinishThreads, 0, s>>>(
-            sums, panel, LossReduceArgs{out, io.n_kept, sh.max_chunks, sh.A, io.opt, io.loss_out, io.stats_out, io.n_stats},
-            with_loss ? 1 : 0);
+    const LossReduceArgs loss{out, io.n_kept, sh.max_chunks, sh.A, io.opt, io.loss_out, io.stats_out, io.n_stats};
+    if (sums.blocks > 0)
+        finish_step<<<(unsigned)(sums.blocks + (with_loss ? 1 : 0)), kFinishThreads, 0, s>>>(sums, panel, loss, with_loss ? 1 : 0);
+    else if (with_loss)
+        finish_loss<<<1, kFinishThreads, 0, s>>>(loss);
     if (lists.parts[0] != nullptr) sum_of_squares<<<1, kFinishThreads, 0, s>>>(lists, io.opt.grad_sumsq_out);
     return launch_status();
 }

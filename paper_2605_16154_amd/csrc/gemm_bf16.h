@@ -238,9 +238,11 @@ __device__ inline bf16x8 join_halves(s16x4 lo, s16x4 hi) {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// A wave-uniform address as such: where bodies share a kernel the compiler may lose sight of it, and assembly takes it in
-// scalar registers.
-__device__ __forceinline__ const char* uniform_address(const void* p) {
+// A wave-uniform address: where several products share a kernel (kShared) the compiler may lose sight of that, and assembly
+// takes it in scalar registers.
+template <bool kShared>
+__device__ __forceinline__ const char* tile_address(const void* p) {
+    if (!kShared) return static_cast<const char*>(p);
     const uint64_t at = (uint64_t)(uintptr_t)p;
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)at), hi = __builtin_amdgcn_readfirstlane((uint32_t)(at >> 32));
     return reinterpret_cast<const char*>((uintptr_t)((uint64_t)hi << 32 | lo));
@@ -276,8 +278,8 @@ struct OperandRing {
     __attribute__((aligned(1024))) __bf16 data[kRingBytes<kW, kSlots> / 2];   // [slot][row][64]
 };
 
-// The work of workgroup `block` of a product; smem: the kernel's LDS.
-template <int kLayA, int kLayB, class Epilogue, int kW, int kSlots>
+// The work of workgroup `block` of a product; smem: the kernel's LDS.  kShared: one of several products of a launch.
+template <int kLayA, int kLayB, bool kShared, class Epilogue, int kW, int kSlots>
 __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& epi, int block, OperandRing<kW, kSlots>& smem) {
     constexpr int TM = kTile<kW>, TN = kTile<kW>;
     constexpr uint32_t kTileBytes = TM * kTileK * 2;             // one operand tile
@@ -292,7 +294,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& 
     int tiles_n = p.N / TN, n_first = 0;
     const int n_tiles = tiles_m * tiles_n;
     const int split = block / n_tiles;
-    if (split >= p.splits) return;                               // workgroups are launched in multiples of eight in a group
+    if (kShared && split >= p.splits) return;                    // their workgroups come in multiples of eight
     int k1 = p.K1, live_m = tiles_m;
     if (p.kept != nullptr) {
         const int rows = p.live_rows();
@@ -349,8 +351,8 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& 
                 lane_off[operand][var] = (row * ld + piece * 8u) * 2u;
             }
             load_stride[operand] = 16u * ld;
-            seg_origin[operand][0] = uniform_address(s1 + (int64_t)row0 * ld);
-            seg_origin[operand][1] = uniform_address(s2 + (int64_t)row0 * ld);
+            seg_origin[operand][0] = tile_address<kShared>(s1 + (int64_t)row0 * ld);
+            seg_origin[operand][1] = tile_address<kShared>(s2 + (int64_t)row0 * ld);
             k_step_bytes[operand] = kTileK * 2;
         } else {
             constexpr int kLanes = 4 * kW;                                            // lanes per k-row
@@ -362,8 +364,8 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& 
                 lane_off[operand][var] = (krow * ld + piece * 8u) * 2u;
             }
             load_stride[operand] = (32u / kW) * ld;
-            seg_origin[operand][0] = uniform_address(s1 + row0);
-            seg_origin[operand][1] = uniform_address(s2 + row0);
+            seg_origin[operand][0] = tile_address<kShared>(s1 + row0);
+            seg_origin[operand][1] = tile_address<kShared>(s2 + row0);
             k_step_bytes[operand] = (uint32_t)kTileK * ld * 2u;
         }
     }
@@ -575,7 +577,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& 
 template <class Epilogue, int kLayA, int kLayB, int kW, int kSlots = kRingSlots>
 __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile || kSlots > kRingSlots ? 1 : 2) void gemm_bf16(GemmProblem p, Epilogue epi) {
     __shared__ OperandRing<kW, kSlots> smem;
-    gemm_tile<kLayA, kLayB>(p, epi, blockIdx.x, smem);
+    gemm_tile<kLayA, kLayB, false>(p, epi, blockIdx.x, smem);
 }
 
 // Products that depend on the same launches and not on one another, as one launch: the workgroups of one fill the CUs that
@@ -589,7 +591,7 @@ struct GemmJob {
     int workgroups(int tile) const { return p.M / tile * (p.N / tile) * p.splits; }
     template <int kW, int kSlots>
     __device__ __forceinline__ void run(int block, OperandRing<kW, kSlots>& smem) const {
-        gemm_tile<kLayA, kLayB>(p, epi, block - first, smem);
+        gemm_tile<kLayA, kLayB, true>(p, epi, block - first, smem);
     }
 };
 // Two products of the same A and sizes with a right operand and a result each.
@@ -608,7 +610,7 @@ struct GemmPairJob {
         const bool second = block - first >= each;
         GemmProblem q = p;
         q.B = q.B2 = second ? B[1] : B[0];       // (an index instead of the choice would put the pair into scratch memory)
-        gemm_tile<kLayA, kLayB>(q, epi[0].or_second(second, epi[1]), block - first - (second ? each : 0), smem);
+        gemm_tile<kLayA, kLayB, true>(q, epi[0].or_second(second, epi[1]), block - first - (second ? each : 0), smem);
     }
 };
 // The last job whose first workgroup is not beyond `block` runs it.
@@ -1083,7 +1085,8 @@ inline void launch_gemm(const GemmProblem& p, const Epilogue& epi, hipStream_t s
 // (a list shorter than its buffer has other tiles left over); the second launch is made where a full list takes it, and
 // its workgroups leave at once where the live one does not.  One group's step in a buffer of 21 row tiles, columns chosen by
 // the buffer / none / by the live rows: 13 live row tiles 2254 / 2218 / 2221 us, 16 2552 / 2516 / 2522, 17 3162 / 3114 / 3117,
-// 21 3539 / 3555 / 3550.
+// 21 3539 / 3555 / 3550.  The second launch has at most one workgroup per CU and keeps the deep ring: 768 x 22016 x 4096, its twelve
+// tiles 45 -> 36 us.
 template <class Epilogue>
 inline void launch_row_gemm(const GemmProblem& p, const Epilogue& epi, hipStream_t s) {
     const int tm = p.M / kTileM, tn = p.N / kTileN, steps = (p.K1 + p.K2) / kTileK;
@@ -1097,7 +1100,7 @@ inline void launch_row_gemm(const GemmProblem& p, const Epilogue& epi, hipStream
     head.cut = kCutHead;
     tail.cut = kCutTail;
     launch_gemm_tile<kRowsByK, kRowsByK, kLargeTile>(head, epi, s);
-    gemm_bf16<Epilogue, kRowsByK, kRowsByK, kSmallTile><<<(unsigned)most, kGemmThreads, 0, s>>>(tail, epi);
+    gemm_bf16<Epilogue, kRowsByK, kRowsByK, kSmallTile, kDeepRingSlots><<<(unsigned)most, kGemmThreads, 0, s>>>(tail, epi);
 }
 
 }  // namespace pcm
