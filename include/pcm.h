@@ -243,7 +243,7 @@ PCM_API int pcm_importance_weights(const uint8_t* phase, const int32_t* n_chunks
  *   kept_per_phase    device i32 [K]: kept chunks of each phase (ids >= K count as K-1)
  *   chunks_per_phase  device i32 [K] or NULL: chunk slots the sampler could have kept (slots
  *                     k < n_chunks[i] of active trajectories) of each phase
- * One workgroup per output; meant for batches of up to a few million chunk slots.
+ * One workgroup per phase and output; meant for batches of up to a few million chunk slots.
  * ------------------------------------------------------------------------------------------ */
 PCM_API int pcm_kept_phase_counts(const uint8_t* phase, const int32_t* n_chunks, const uint8_t* active,
                           const int32_t* kept_idx, const int32_t* n_kept, int max_kept_chunks, int T, int N,

@@ -474,77 +474,69 @@ __global__ __launch_bounds__(kThreads) void importance_weights(const uint8_t* __
     }
 }
 
-// hist[c] += 1 for every lane with c >= 0.  Neighbouring lanes mostly hold the same phase (a trajectory's phases are
-// contiguous), and as many LDS atomics on one address would be served one after the other: the first lane of every run
-// of equal values adds the length of the run.
-__device__ inline void wave_histogram(int* hist, int c, int lane) {
-    const int left = __builtin_amdgcn_update_dpp(c, c, 0x138, 0xf, 0xf, false);       // the lane before (wave_shr:1), no LDS
-    const bool starts = lane == 0 || c != left;
-    const uint64_t starting = __ballot(starts);
-    if (starts && c >= 0) {
-        const uint64_t later = lane == kWave - 1 ? 0 : starting >> (lane + 1);
-        atomicAdd(&hist[c], later ? __ffsll((long long)later) : kWave - lane);
-    }
-}
-
-// Histograms in LDS of the kept chunks' phases (workgroup 0) and of the phases of all chunk slots the sampler could have
-// kept (workgroup 1), written out as they are (nothing to clear, no atomics in memory).  Bound by the latency of the loads
-// and by the instructions of one CU; each thread has sixteen slots under way.  32768 slots, 4096 kept: 22.7 -> 13.4 us
-// against one slot and one LDS atomic per thread at a time in a single workgroup.
-constexpr int kCountBatch = 16;
-__global__ __launch_bounds__(1024) void kept_phase_counts(const uint8_t* __restrict__ phase,
-                                                          const int32_t* __restrict__ n_chunks,
-                                                          const uint8_t* __restrict__ active,
-                                                          const int32_t* __restrict__ kept_idx,
-                                                          const int32_t* __restrict__ n_kept, int max_kept, int T, int N,
-                                                          int K, int32_t* kept_out, int32_t* eligible_out) {
-    __shared__ int hist[PCM_MAX_PHASES];
-    const int tid = threadIdx.x, lane = tid % kWave;
-    if (tid < PCM_MAX_PHASES) hist[tid] = 0;
-    __syncthreads();
-    const int64_t slots = (int64_t)T * N;
-    if (blockIdx.x == 0) {
+// Chunks of one phase: workgroup c counts the kept chunks of phase c, workgroup K + c the chunk slots of phase c that the
+// sampler could have kept.  Each output has one writer, so nothing is cleared and nothing added in memory; the phases are read
+// K times, by as many CUs (32 KB for 32768 slots).  What it waits for is three dependent loads: a wavefront takes kCountRows
+// trajectories at a time, 64 slots of each per trip.  A histogram of all phases by one workgroup was bound by the instructions of
+// its CU, histogram / this, per call: 256 trajectories of 128 slots, 5 phases 13.3 / 7.8 us; 512 of 256, 12 phases 47 / 17; 64 of
+// 4096, phases in random order 89 / 34; 8192 of 128 363 / 177; 300 of 77, 64 phases 12.7 / 10.4.
+constexpr int kCountThreads = 1024, kCountRows = 16;
+__global__ __launch_bounds__(kCountThreads) void kept_phase_counts(const uint8_t* __restrict__ phase,
+                                                                   const int32_t* __restrict__ n_chunks,
+                                                                   const uint8_t* __restrict__ active,
+                                                                   const int32_t* __restrict__ kept_idx,
+                                                                   const int32_t* __restrict__ n_kept, int max_kept, int T, int N,
+                                                                   int K, int32_t* kept_out, int32_t* eligible_out) {
+    __shared__ int wave_count[kCountThreads / kWave];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const bool eligible = (int)blockIdx.x >= K;
+    const int mine = (int)blockIdx.x % K;
+    auto is_mine = [&](int c) { return min(c, K - 1) == mine; };             // ids beyond the last phase count as the last
+    int count = 0;
+    if (!eligible) {
+        const int64_t slots = (int64_t)T * N;
         int nk = *n_kept;
         nk = nk < 0 ? 0 : (nk > max_kept ? max_kept : nk);
         constexpr int kBatch = 4;
-        for (int64_t j0 = 0; j0 < nk; j0 += 1024 * kBatch) {       // trips uniform over the workgroup
+        for (int64_t j0 = tid; j0 < nk; j0 += kCountThreads * kBatch) {
             int id[kBatch], c[kBatch];
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int64_t j = j0 + u * 1024 + tid;
-                id[u] = j < nk ? kept_idx[j] : -1;
-            }
+            for (int u = 0; u < kBatch; ++u) id[u] = j0 + u * kCountThreads < nk ? kept_idx[j0 + u * kCountThreads] : -1;
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) c[u] = id[u] >= 0 && id[u] < slots ? min((int)phase[id[u]], K - 1) : -1;
+            for (int u = 0; u < kBatch; ++u) c[u] = phase[id[u] >= 0 && id[u] < slots ? id[u] : 0];
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) wave_histogram(hist, c[u], lane);
+            for (int u = 0; u < kBatch; ++u) count += id[u] >= 0 && id[u] < slots && is_mine(c[u]) ? 1 : 0;
         }
     } else {
-        int i = tid / N, k = tid % N;                 // trajectory and slot of this thread's next entry, 1024 further each time
-        const int step_i = 1024 / N, step_k = 1024 % N;
-        for (int64_t e0 = 0; e0 < slots; e0 += 1024 * kCountBatch) {
-            int c[kCountBatch], Ni[kCountBatch], at[kCountBatch];
-            bool on[kCountBatch];
+        for (int64_t i0 = (int64_t)wave * kCountRows; i0 < T; i0 += kCountThreads / kWave * kCountRows) {
+            int live[kCountRows], longest = 0;                                // slots of each trajectory that may be kept
 #pragma unroll
-            for (int u = 0; u < kCountBatch; ++u) {
-                const bool in = i < T;
-                const int ii = in ? i : T - 1;
-                at[u] = in ? k : N;                   // beyond the last trajectory: no slot
-                c[u] = phase[in ? e0 + u * 1024 + tid : slots - 1];
-                Ni[u] = n_chunks ? n_chunks[ii] : N;
-                on[u] = !active || active[ii] != 0;
-                i += step_i;
-                k += step_k;
-                if (k >= N) { k -= N; ++i; }
+            for (int u = 0; u < kCountRows; ++u) {
+                const int i = (int)min(i0 + u, (int64_t)T - 1);
+                const int n = n_chunks ? n_chunks[i] : N;
+                const bool on = (!active || active[i] != 0) && i0 + u < T;
+                live[u] = on ? min(n, N) : 0;
             }
 #pragma unroll
-            for (int u = 0; u < kCountBatch; ++u) c[u] = on[u] && at[u] < min(Ni[u], N) ? min(c[u], K - 1) : -1;
+            for (int u = 0; u < kCountRows; ++u) longest = max(longest, live[u]);
+            for (int k = lane; k < longest; k += kWave) {
+                int c[kCountRows];
 #pragma unroll
-            for (int u = 0; u < kCountBatch; ++u) wave_histogram(hist, c[u], lane);
+                for (int u = 0; u < kCountRows; ++u) c[u] = phase[min(i0 + u, (int64_t)T - 1) * N + k];
+#pragma unroll
+                for (int u = 0; u < kCountRows; ++u) count += k < live[u] && is_mine(c[u]) ? 1 : 0;
+            }
         }
     }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) count += __shfl_xor(count, o, kWave);
+    if (lane == 0) wave_count[wave] = count;
     __syncthreads();
-    if (tid < K) (blockIdx.x == 0 ? kept_out : eligible_out)[tid] = hist[tid];
+    if (tid != 0) return;
+    count = 0;
+#pragma unroll
+    for (int q = 0; q < kCountThreads / kWave; ++q) count += wave_count[q];
+    (eligible ? eligible_out : kept_out)[mine] = count;
 }
 
 }  // namespace
@@ -556,8 +548,8 @@ extern "C" int pcm_kept_phase_counts(const uint8_t* phase, const int32_t* n_chun
     if (!shape_ok(T, N, K, 1)) return PCM_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     StageTimer t(ST_SAMPLE_COMPACT, s);
-    kept_phase_counts<<<chunks_per_phase ? 2 : 1, 1024, 0, s>>>(phase, n_chunks, active, kept_idx, n_kept, max_kept_chunks, T, N, K, kept_per_phase,
-                                         chunks_per_phase);
+    kept_phase_counts<<<(unsigned)(chunks_per_phase ? 2 * K : K), kCountThreads, 0, s>>>(phase, n_chunks, active, kept_idx, n_kept,
+                                                                                         max_kept_chunks, T, N, K, kept_per_phase, chunks_per_phase);
     return launch_status();
 }
 

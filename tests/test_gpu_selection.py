@@ -378,3 +378,33 @@ def test_scores_of_streams_and_threads_that_overlap(pcm):
     for (C_o, valid_o), _, outs in work:
         for C, valid, _, _ in outs:
             assert np.array_equal(bits(C.cpu().numpy()), bits(C_o)) and np.array_equal(valid.cpu().numpy(), valid_o)
+
+
+@pytest.mark.parametrize("T,N,K", [
+    (1, 1, 1),
+    (257, 64, 3),       # one trajectory more than a pass takes, whole wavefronts of slots
+    (300, 77, 64),      # a partial last trip, as many phases as there may be
+    (15, 200, 5),       # fewer trajectories than a wavefront takes
+])
+def test_allocation_counts_phase_by_phase(pcm, T, N, K):
+    """Counts against a plain histogram: ids beyond the last phase, chunk counts outside [0, N], inactive trajectories, kept
+    ids outside the batch, a kept count beyond its buffer, and with the second output left out."""
+    rng = np.random.default_rng(T)
+    phase = rng.integers(0, K + 2, size=(T, N)).astype(np.uint8)
+    n_chunks = rng.integers(-2, N + 3, size=T).astype(np.int32)
+    active = (rng.random(T) < 0.7).astype(np.uint8)
+    kept = rng.integers(-3, T * N + 3, size=5000).astype(np.int32)
+    n_kept = np.array([5003], np.int32)
+    ph = np.minimum(phase, K - 1).reshape(-1)
+    live = (np.arange(N)[None, :] < n_chunks[:, None]) & (active[:, None] != 0)
+    inside = kept[(kept >= 0) & (kept < T * N)]
+    want = np.bincount(ph[inside], minlength=K), np.bincount(ph[live.reshape(-1)], minlength=K)
+    got = pcm.pcm_kept_phase_counts(dev(phase), dev(n_chunks), dev(active), dev(kept), dev(n_kept), K)
+    assert np.array_equal(got[0].cpu().numpy(), want[0]) and np.array_equal(got[1].cpu().numpy(), want[1])
+    every = pcm.pcm_kept_phase_counts(dev(phase), None, None, dev(kept), dev(n_kept), K)
+    assert np.array_equal(every[0].cpu().numpy(), want[0]) and np.array_equal(every[1].cpu().numpy(), np.bincount(ph, minlength=K))
+    only = torch.full((K,), -1, dtype=torch.int32, device="cuda")
+    d_phase, d_kept, d_n = dev(phase), dev(kept), dev(n_kept)
+    assert pcm.lib().pcm_kept_phase_counts(d_phase.data_ptr(), None, None, d_kept.data_ptr(), d_n.data_ptr(), 5000, T, N, K,
+                                           only.data_ptr(), None, torch.cuda.current_stream().cuda_stream) == 0
+    assert np.array_equal(only.cpu().numpy(), want[0])
