@@ -4,7 +4,7 @@
 // every state element once.
 //
 //   pass 1  sumsq_chunks   one fp64 partial sum of g^2 per 4096-element chunk
-//   pass 2  finish_norm    one workgroup adds the partials in a fixed order -> norm, clip factor
+//   pass 2  finish_norm    one workgroup adds the partials in a fixed order -> norm, clip factor (few partials: part of pass 3)
 //   pass 3  adamw_chunks   m, v, theta updated in place, low-precision copy written
 //
 // The tensors are addressed as one list of chunks, so the whole head is one launch per pass.
@@ -28,8 +28,14 @@ struct TensorList {
     int n;
 };
 
+// Where the sum of squares comes from, and what to make of it.
+struct NormArgs {
+    const double* partial;      // n of them
+    int64_t n;
+    double max_norm, clip_eps;
+    float* norm_out;            // or null
+};
 struct NormResult {
-    double sumsq;
     float norm, scale;
 };
 
@@ -74,20 +80,40 @@ __global__ __launch_bounds__(kThreads) void sumsq_chunks(TensorList tl, double* 
     if (threadIdx.x == 0) partial[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(1024) void finish_norm(const double* partial, int64_t n_chunks, double max_norm,
-                                                    double clip_eps, NormResult* result, float* norm_out) {
+// Norm and clip factor from the partial sums, which 1024 threads take in turn, wavefront sums added in order; a workgroup of
+// 256 stands for four times as many threads, so that the result is the same bits whichever launch forms it.  Every thread
+// gets it.
+template <int kGroup>
+__device__ inline NormResult norm_of(const NormArgs& p) {
+    constexpr int kTurns = 1024 / kGroup;
     __shared__ double lds[16];
-    double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < n_chunks; i += blockDim.x) acc += partial[i];
-    const double total = block_sum(acc, lds);
-    if (threadIdx.x == 0) {
-        const double norm = sqrt(total);
-        const double scale = fmin(1.0, max_norm / (norm + clip_eps));
-        result->sumsq = total;
-        result->norm = (float)norm;
-        result->scale = (float)scale;
-        if (norm_out) *norm_out = (float)norm;
-    }
+    double acc[kTurns];
+#pragma unroll
+    for (int q = 0; q < kTurns; ++q) acc[q] = 0.0;
+    for (int64_t i = threadIdx.x; i < p.n; i += 1024)
+#pragma unroll
+        for (int q = 0; q < kTurns; ++q)
+            if (i + q * kGroup < p.n) acc[q] += p.partial[i + q * kGroup];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int q = 0; q < kTurns; ++q) acc[q] += __shfl_down(acc[q], off, 64);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int q = 0; q < kTurns; ++q) lds[q * (kGroup / 64) + (threadIdx.x >> 6)] = acc[q];
+    __syncthreads();
+    double total = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) total += lds[w];
+    const double norm = sqrt(total);
+    return NormResult{(float)norm, (float)fmin(1.0, p.max_norm / (norm + p.clip_eps))};
+}
+
+__global__ __launch_bounds__(1024) void finish_norm(NormArgs p, NormResult* result) {
+    const NormResult r = norm_of<1024>(p);
+    if (threadIdx.x != 0) return;
+    *result = r;
+    if (p.norm_out) *p.norm_out = r.norm;
 }
 
 struct AdamConst {
@@ -129,8 +155,14 @@ __device__ inline void store16(float* p, float4 x) {
 // 930.  Norm and update alone, ordinary / non-temporal accesses: 4 M parameters 26 / 33 us, 16 M 93 / 97, 32 M 216 / 179,
 // 64 M 440 / 360.
 constexpr int64_t kStreamElements = 20 << 20;
-template <bool kStream>
-__global__ __launch_bounds__(kThreads) void adamw_chunks(TensorList tl, const NormResult* result, AdamConst c) {
+// Partial sums up to which the update forms the norm.  Optimizer step and re-layout, norm by a launch of its own / by the update:
+// 64 partial sums 28.7 / 25.8 us, 416 28.0 / 25.2, 832 28.3 / 27.6, 1600 49.6 / 49.9, 3200 97 / 101, 6272 164 / 180; with the sum
+// given (one) 0.26 M parameters 25.3 / 22.5 us, 25 M 152.9 / 151.7, 136 M 814 / 813.
+constexpr int64_t kOwnNormPartials = 1024;
+// kOwnNorm: every workgroup forms the norm from the partial sums by itself, which saves the launch between the two passes: with
+// the sum of squares given, and else while the partial sums are few (see kOwnNormPartials).
+template <bool kStream, bool kOwnNorm>
+__global__ __launch_bounds__(kThreads) void adamw_chunks(TensorList tl, NormArgs norm, const NormResult* result, AdamConst c) {
     int t;
     int64_t begin;
     locate(tl, kStream ? (int64_t)gridDim.x - 1 - blockIdx.x : (int64_t)blockIdx.x, t, begin);
@@ -140,7 +172,14 @@ __global__ __launch_bounds__(kThreads) void adamw_chunks(TensorList tl, const No
     float* v = tl.v[t];
     uint16_t* lp = tl.lowp[t];
     const int64_t n = tl.numel[t];
-    const float scale = result->scale;
+    float scale;
+    if (kOwnNorm) {
+        const NormResult r = norm_of<kThreads>(norm);
+        scale = r.scale;
+        if (blockIdx.x == 0 && threadIdx.x == 0 && norm.norm_out) *norm.norm_out = r.norm;
+    } else {
+        scale = result->scale;
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int64_t i = begin + ((int64_t)r * kThreads + threadIdx.x) * 4;
@@ -248,19 +287,21 @@ PCM_API int pcm_adamw_clip_step_ex(int n_tensors, const int64_t* numel, const fl
     c.step_size = (float)(lr / (1.0 - pow(beta1, (double)step)));
     c.inv_sqrt_bc2 = (float)(1.0 / sqrt(1.0 - pow(beta2, (double)step)));
     c.eps = (float)eps;
-    {
+    const NormArgs norm = grad_sumsq != nullptr ? NormArgs{grad_sumsq, 1, max_grad_norm, 1e-6, grad_norm_out}
+                                                : NormArgs{w.partial, chunks, max_grad_norm, 1e-6, grad_norm_out};
+    const bool own = norm.n <= kOwnNormPartials;
+    if (grad_sumsq == nullptr || !own) {
         StageTimer t(ST_OPT_NORM, s);
-        if (grad_sumsq != nullptr) {      // the sum of squares is given: one "partial"
-            finish_norm<<<1, 1024, 0, s>>>(grad_sumsq, 1, max_grad_norm, 1e-6, w.result, grad_norm_out);
-        } else {
-            sumsq_chunks<<<(unsigned)chunks, kThreads, 0, s>>>(tl, w.partial);
-            finish_norm<<<1, 1024, 0, s>>>(w.partial, chunks, max_grad_norm, 1e-6, w.result, grad_norm_out);
-        }
+        if (grad_sumsq == nullptr) sumsq_chunks<<<(unsigned)chunks, kThreads, 0, s>>>(tl, w.partial);
+        if (!own) finish_norm<<<1, 1024, 0, s>>>(norm, w.result);
     }
     {
         StageTimer t(ST_OPT_ADAMW, s);
-        if (elements > kStreamElements) adamw_chunks<true><<<(unsigned)chunks, kThreads, 0, s>>>(tl, w.result, c);
-        else adamw_chunks<false><<<(unsigned)chunks, kThreads, 0, s>>>(tl, w.result, c);
+        const bool stream_past = elements > kStreamElements;
+        if (stream_past && own) adamw_chunks<true, true><<<(unsigned)chunks, kThreads, 0, s>>>(tl, norm, w.result, c);
+        else if (stream_past) adamw_chunks<true, false><<<(unsigned)chunks, kThreads, 0, s>>>(tl, norm, w.result, c);
+        else if (own) adamw_chunks<false, true><<<(unsigned)chunks, kThreads, 0, s>>>(tl, norm, w.result, c);
+        else adamw_chunks<false, false><<<(unsigned)chunks, kThreads, 0, s>>>(tl, norm, w.result, c);
     }
     return launch_status();
 }

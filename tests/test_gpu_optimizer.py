@@ -159,3 +159,18 @@ def test_both_sides_of_the_streaming_line(extra):
     # up to 20 Mi elements the state is accessed through the caches, beyond with non-temporal accesses; a ragged second tensor
     w, g, m, v = _case(9, ((20 * 2 ** 20 - 4097 + extra,), (4098,)), 1e-3)
     _check(w, g, m, v, 5)
+
+
+@pytest.mark.parametrize("chunks,extra", [(1, -4095), (3, 5), (1024, 0), (1024, 1)])
+def test_norm_formed_by_the_update_and_by_a_launch_of_its_own(chunks, extra):
+    """Up to 1024 partial sums every workgroup of the update forms the norm, beyond that a launch does: both sides of the line,
+    and the norm against the sum of the squares given."""
+    n = chunks * 4096 + extra
+    w, g, m, v = _case(11, [(n,)], 0.01)
+    _check(w, g, m, v, 7, max_grad_norm=0.5)
+    dev = torch.device("cuda:0")
+    sumsq = torch.tensor([float((g[0].astype(np.float64) ** 2).sum())], dtype=torch.float64, device=dev)
+    own = _run(w, g, m, v, 7, max_grad_norm=0.5)
+    given = _run(w, g, m, v, 7, max_grad_norm=0.5, grad_sumsq=sumsq)
+    assert abs(own[3] - given[3]) <= 1e-6 * own[3] and abs(own[3] - np.sqrt(float(sumsq.item()))) <= 1e-6 * own[3]
+    np.testing.assert_allclose(own[0][0], given[0][0], rtol=0, atol=1e-9 + 4e-7 * np.abs(w[0]).max())
