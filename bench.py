@@ -27,6 +27,7 @@ FP32_PEAK_TFLOPS = 157.3
 HBM_PEAK_GBPS = 8000.0              # MI355X HBM3E peak
 GEMM_STAGES = ("gemm_gate_up", "gemm_down", "gemm_logits_loss", "gemm_dWo", "gemm_dy", "gemm_dWd", "gemm_da",
                "gemm_dWg_dWu", "gemm_dX")
+SHARED_LAUNCHES = {"gemm_dWo": "gemm_dy", "gemm_dWd": "gemm_da", "gemm_dWg_dWu": "gemm_dX"}   # where products share one
 
 
 def stored_traffic(name):
@@ -482,6 +483,9 @@ def main():
                  "zero_operands": {"tflops": tf_zero, "clock_ghz": clk_zero}}
     rows_bwd = backward_rows(rows, wl.clip_fractions, args.dense_backward or cfg.dtype != "bf16")
     flops = gemm_flops_per_step(rows, cfg.d, cfg.ff, cfg.V, rows_bwd)
+    for stage, host in SHARED_LAUNCHES.items():          # no launch of its own: timed with the one it shares
+        if stages[stage][1] == 0 and stages[host][1] > 0:
+            flops[host] += flops.pop(stage)
     per_stage = {}
     for name, (ms, launches) in stages.items():
         if launches == 0:

@@ -1051,10 +1051,16 @@ inline int tile_for(int64_t M, int64_t N, int splits) {
     return cost_small < cost_large ? kSmallTile : kLargeTile;
 }
 
+// Steps of a part from which the deep ring pays: shorter ones are all requested at the start, and the first tile waits behind
+// nine.  Whole passes, always / from 9 steps / never: 32 rows of 512 -> 512 30.4 / 29.4 / 29.4 us, 2072 of 512 -> 768 78.6 / 78.3 /
+// 79.8, 1344 of 1024 -> 1024 39.4 / 39.6 / 42.0, 512 of 3072 -> 1536 145.7 / 145.4 / 150.7.
+constexpr int kDeepSteps = 9;
+inline int steps_per_part(const GemmProblem& p) { return ceil_div((p.K1 + p.K2) / kTileK, p.splits); }
+
 template <int kLayA = kRowsByK, int kLayB = kRowsByK, int kW = kLargeTile, class Epilogue>
 inline void launch_gemm_tile(const GemmProblem& p, const Epilogue& epi, hipStream_t s) {
     const unsigned grid = (unsigned)(p.M / kTile<kW>) * (unsigned)(p.N / kTile<kW>) * (unsigned)p.splits;
-    if (kW == kSmallTile && grid <= 256) gemm_bf16<Epilogue, kLayA, kLayB, kSmallTile, kDeepRingSlots><<<grid, kGemmThreads, 0, s>>>(p, epi);
+    if (kW == kSmallTile && grid <= 256 && steps_per_part(p) >= kDeepSteps) gemm_bf16<Epilogue, kLayA, kLayB, kSmallTile, kDeepRingSlots><<<grid, kGemmThreads, 0, s>>>(p, epi);
     else gemm_bf16<Epilogue, kLayA, kLayB, kW><<<grid, kGemmThreads, 0, s>>>(p, epi);
 }
 // The jobs of a group in one launch on tiles of kW; the longest reductions first.
@@ -1068,7 +1074,7 @@ inline void launch_gemm_group(int kW, hipStream_t s, Jobs... jobs) {
     int grid = 0;
     ((grid = place_job(jobs, 32 * kW, grid)), ...);
     if (kW == kLargeTile) gemm_group<kLargeTile, kRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
-    else if (grid <= 256) gemm_group<kSmallTile, kDeepRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
+    else if (grid <= 256 && std::max({steps_per_part(jobs.p)...}) >= kDeepSteps) gemm_group<kSmallTile, kDeepRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
     else gemm_group<kSmallTile, kRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
 }
 template <int kLayA = kRowsByK, int kLayB = kRowsByK, class Epilogue>
