@@ -300,7 +300,7 @@ def board_power_and_clock(work, seconds=2.0):
 
 def graph_replay_timing(wl, steps):
     """The same steps replayed from HIP graphs (one graph per resident batch, captured once): what is left when the
-    launch gaps between the ~30 kernels of a step are gone.  Reported beside `value`, which stays the eager figure."""
+    launch gaps between the kernels of a step are gone.  Reported beside `value`, which stays the eager figure."""
     torch, pcm, cfg = wl.torch, wl.pcm, wl.cfg
     n = len(wl.batches)
     wl.state = pcm.pcm_state_init(cfg.K, wl.dev)
