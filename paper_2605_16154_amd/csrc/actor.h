@@ -90,8 +90,8 @@ struct TransposeList {
 // A launch of nothing but transposes; stream: non-temporal stores.
 void launch_transposes(const TransposeList& list, bool stream, hipStream_t s);
 
-// Copies the kept chunks' hidden rows into X [rows_pad, d] (rows at and beyond n_kept*A are
-// zero-filled) and fills the row metadata.  elem_bytes is 2 (bf16) or 4 (fp32).
+// Copies the kept chunks' hidden rows into X [rows_pad, d] (rows from n_kept*A to the end of
+// their tile of 256 are zero-filled, later ones left as they are: nothing reads them) and fills the row metadata.  elem_bytes is 2 (bf16) or 4 (fp32).
 // With row_offset > 0 the rows are those of a panel of the batch that starts at that row: X and the metadata
 // arrays are the panel's own, `rows_pad` its height.  The same holds for the two per-chunk-ratio launches below
 // (row_offset a multiple of A, so no chunk straddles two panels).

@@ -4,9 +4,9 @@
 //           log-softmax / ratio / clipped surrogate / dz in one pass over the rows.
 // Backward: dy = dz Wo^T; da = dy Wd^T with the gated-activation derivative fused (du, dv
 //           overwrite the two factors the forward epilogue stored); weight gradients reduce over
-//           the row dimension (a small output, dWo, as partial products over slices of the rows,
-//           summed afterwards: no atomics); dX = du Wg^T + dv Wu^T as one GEMM over two
-//           reduction segments.
+//           the row dimension (small outputs as partial products over slices of the rows, summed at the
+//           end of the panel: no atomics); dX = du Wg^T + dv Wu^T as one GEMM over two
+//           reduction segments.  Products that do not depend on one another share a launch (see plan_backward).
 // Composed evaluation (an option): the down and the logit projection as the one matrix
 //           W_do = Wd Wo [ff, V] formed at the start of the call: z = a W_do; G = a^T dz,
 //           dWd = G Wo^T, dWo = Wd^T G, da = dz W_do^T.  y and dy are never formed; the three

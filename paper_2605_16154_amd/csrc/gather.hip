@@ -4,7 +4,7 @@
 //
 // The gather is a pure streaming copy (row r of the compacted batch is token r % A of chunk
 // kept_idx[r / A]); each workgroup moves a block of rows with 16-byte accesses, several loads in
-// flight per lane.  Rows at and beyond n_kept * A are zero-filled with advantage 0, so they add
+// flight per lane.  Rows from n_kept * A to the end of their tile of 256 are zero-filled with advantage 0, so they add
 // nothing downstream.
 #include <algorithm>
 
