@@ -379,6 +379,13 @@ BackwardPlan plan_backward(const ActorShape& sh, int64_t Rp, bool composed, bool
     if (!b.group[2]) b.split_gu = pick_splits((int)(d / kTileM * (ff / kTileN)), rows);
     return b;
 }
+// fp32 buffer that products use one after the other: the logits, and parts of split reductions that the next launch adds up
+// into a bf16 matrix.
+struct SharedParts {
+    float* at;
+    size_t floats;
+    bool hold(size_t n) const { return n <= floats; }
+};
 struct Bf16Workspace {
     bf16 *WguT, *WdT, *WoT;
     bf16 *X, *fu, *fv, *a, *y, *dz, *dz_extra;   // one panel each; fu, fv: SwiGLU derivative factors, then du, dv
@@ -392,7 +399,7 @@ struct Bf16Workspace {
     double* sumsq[4];      // sums of squares of the final dWg, dWu, dWd, dWo by workgroup (null: not asked for)
     int sumsq_count[4];
     bf16 *Wdo, *G;  // composed evaluation: Wd Wo and a^T dz, both [ff, V]
-    float* parts;   // partial products of split reductions; the logits
+    SharedParts parts;   // the logits; parts of the down projection, of W_do and of G
     float *parts_o, *parts_d, *parts_g, *parts_u;   // those of dWo, dWd, dWg, dWu, which are added up at the end of a panel
     BackwardPlan plan_b;
     RowMeta meta;   // whole batch
@@ -472,7 +479,8 @@ Bf16Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool grads, const 
     if (grads) w.G = c.take<bf16>(ff * V);
     // parts of split reductions; of the logits (one column of tiles) there is at least one part whatever the panel's height
     const size_t row_tiles = Rp / kTileM;
-    w.parts = c.take<float>((row_tiles > kMaxSplitTiles ? row_tiles : kMaxSplitTiles) * (size_t)kTileM * kTileN);
+    w.parts.floats = (row_tiles > kMaxSplitTiles ? row_tiles : kMaxSplitTiles) * (size_t)kTileM * kTileN;
+    w.parts.at = c.take<float>(w.parts.floats);
     w.bytes = c.used();
     return w;
 }
@@ -505,13 +513,18 @@ EpiStoreF32 reduction_epilogue(GemmProblem& p, int splits, float* C, float* part
 }
 // C = a product with a long reduction and a small output, as parts and rounded once to bf16.
 template <int kLayA, int kLayB>
-void launch_reduction_bf16(GemmProblem p, bf16* C, float* parts, int stage, hipStream_t s) {
+int launch_reduction_bf16(GemmProblem p, bf16* C, const SharedParts& parts, int stage, hipStream_t s) {
     StageTimer t(stage, s);
     p.splits = pick_splits((p.M / kTileM) * (p.N / kTileN), p.K1 / kTileK);
-    if (p.splits == 1) return launch_gemm<kLayA, kLayB>(p, EpiStoreBf16{C, p.N, p.M}, s);
     const size_t n = (size_t)p.M * p.N;
-    launch_gemm<kLayA, kLayB>(p, EpiStoreF32{parts, p.N, (int64_t)n, 0, nullptr, FinalPanel{}}, s);
-    launch_sum_bf16(parts, p.splits, n, C, s);
+    if (p.splits == 1) {
+        launch_gemm<kLayA, kLayB>(p, EpiStoreBf16{C, p.N, p.M}, s);
+        return PCM_OK;
+    }
+    if (!parts.hold(p.splits * n)) return PCM_EWORKSPACE;
+    launch_gemm<kLayA, kLayB>(p, EpiStoreF32{parts.at, p.N, (int64_t)n, 0, nullptr, FinalPanel{}}, s);
+    launch_sum_bf16(parts.at, p.splits, n, C, s);
+    return PCM_OK;
 }
 
 GemmProblem problem(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int M, int N, int K,
@@ -530,15 +543,20 @@ GemmProblem problem(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int 
 // Measured, whole passes without gradients, before (small tiles only, at most four parts) / now: 672 rows of 4096 -> 11008, five
 // parts on large tiles, 262 / 237 us (its down projection 96 -> 62, the sum 6 -> 10); 512 of 512 -> 9984 58.7 / 52.2; 896 of
 // 2304 -> 2560 86 / 79.
-void launch_rows_bf16(GemmProblem p, bf16* C, float* parts, hipStream_t s) {
+int launch_rows_bf16(GemmProblem p, bf16* C, const SharedParts& parts, hipStream_t s) {
     const GroupPlan plan = plan_group<1>({{p.M, p.N, (p.K1 + p.K2) / kTileK, 1, true, 16}}, 5.f);
-    if (plan.splits[0] == 1) return launch_row_gemm(p, EpiStoreBf16{C, p.N, p.M}, s);
+    if (plan.splits[0] == 1) {
+        launch_row_gemm(p, EpiStoreBf16{C, p.N, p.M}, s);
+        return PCM_OK;
+    }
     p.splits = plan.splits[0];
     const size_t n = (size_t)p.M * p.N;
-    const EpiStoreF32 epi{parts, p.N, (int64_t)n, 0, nullptr, FinalPanel{}};
+    if (!parts.hold(p.splits * n)) return PCM_EWORKSPACE;
+    const EpiStoreF32 epi{parts.at, p.N, (int64_t)n, 0, nullptr, FinalPanel{}};
     if (plan.kW == kSmallTile) launch_gemm_tile<kRowsByK, kRowsByK, kSmallTile>(p, epi, s);
     else launch_gemm_tile<kRowsByK, kRowsByK, kLargeTile>(p, epi, s);
-    launch_sum_bf16(parts, p.splits, n, C, s);
+    launch_sum_bf16(parts.at, p.splits, n, C, s);
+    return PCM_OK;
 }
 
 }  // namespace
@@ -584,6 +602,7 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
     const bf16* Wo = static_cast<const bf16*>(io.Wo);
 
     const KeptRows all_rows{nullptr, 0, 0, 0};
+    int rc = PCM_OK;
     TransposeList layouts{};
     if (io.opt.packed_weights != nullptr) {               // layouts kept by the caller: nothing to re-lay-out
         const PackedHead ph = carve_packed(const_cast<void*>(io.opt.packed_weights), d, ff, V);
@@ -593,8 +612,9 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
         layouts.add(Wu, d, ff, w.WguT, kPackUp);
         if (io.composed) {
             // W_do = Wd Wo [ff, V], from the weights as given (Wd [rows][K], Wo [K][rows])
-            launch_reduction_bf16<kRowsByK, kKByRows>(problem(Wd, d, Wo, V, ff, V, d, all_rows, kRowsUnused), w.Wdo, w.parts,
-                                                      ST_WEIGHT_LAYOUT, s);
+            rc = launch_reduction_bf16<kRowsByK, kKByRows>(problem(Wd, d, Wo, V, ff, V, d, all_rows, kRowsUnused), w.Wdo, w.parts,
+                                                           ST_WEIGHT_LAYOUT, s);
+            if (rc != PCM_OK) return rc;
         } else {
             layouts.add(Wd, ff, d, w.WdT, kPackNone);      // [ff, d] -> [d, ff]
             layouts.add(Wo, d, V, w.WoT, kPackNone);       // [d, V]  -> [V, d]
@@ -605,7 +625,6 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
     const bool want_sumsq = grads && io.opt.grad_sumsq_out != nullptr && ws != nullptr && w.sumsq[0] != nullptr;
     const int n_zero = want_sumsq ? (int)(w.sumsq[3] - w.sumsq[0]) + w.sumsq_count[3] : 0;   // the four lists follow one another
 
-    int rc = PCM_OK;
     PartsSums last_sums{};
     FinalPanel last_panel{};
     for (int64_t row0 = 0; row0 < w.Mp; row0 += w.Rp) {
@@ -638,7 +657,8 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                 p.A2 = w.a_lo; p.B2 = w.WdT; p.K2 = ff;
                 launch_row_gemm(p, EpiStoreBf16Split{w.y, w.y_lo, d, Mp}, s);
             } else {
-                launch_rows_bf16(p, w.y, w.parts, s);
+                rc = launch_rows_bf16(p, w.y, w.parts, s);
+                if (rc != PCM_OK) return rc;
             }
         }
         {
@@ -648,15 +668,17 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
             if (io.composed) {   // z = a W_do, W_do read as [K][rows]
                 GemmProblem p = problem(w.a, ff, w.Wdo, V, Mp, V, ff, kr, kRowsAreM);
                 n_parts = p.splits = pick_splits(Mp / kTileM, ff / kTileK);
-                launch_gemm<kRowsByK, kKByRows>(p, EpiStoreF32{w.parts, V, (int64_t)n_z, 0, nullptr, FinalPanel{}}, s);
+                if (!w.parts.hold(n_parts * n_z)) return PCM_EWORKSPACE;
+                launch_gemm<kRowsByK, kKByRows>(p, EpiStoreF32{w.parts.at, V, (int64_t)n_z, 0, nullptr, FinalPanel{}}, s);
             } else {
                 GemmProblem p = problem(w.y, d, w.WoT, d, Mp, V, d, kr, kRowsAreM);
                 if (split) { p.A2 = w.y_lo; p.B2 = w.WoT; p.K2 = d; }   // z = [y | y_lo] [Wo; Wo]
                 n_parts = p.splits = pick_splits(Mp / kTileM, (p.K1 + p.K2) / kTileK);
-                launch_gemm(p, EpiStoreF32{w.parts, V, (int64_t)n_z, 0, nullptr, FinalPanel{}}, s);
+                if (!w.parts.hold(n_parts * n_z)) return PCM_EWORKSPACE;
+                launch_gemm(p, EpiStoreF32{w.parts.at, V, (int64_t)n_z, 0, nullptr, FinalPanel{}}, s);
             }
             loss_rows_bf16<<<(unsigned)(Mp / kLossRows), kLossThreads, 0, s>>>(LossRowsArgs{
-                w.parts, n_parts, n_z, meta.token, meta.logp_old, meta.adv, io.n_kept, sh.max_chunks, sh.A, (int)row0, Mp,
+                w.parts.at, n_parts, n_z, meta.token, meta.logp_old, meta.adv, io.n_kept, sh.max_chunks, sh.A, (int)row0, Mp,
                 io.opt, bwd ? w.dz : nullptr, w.dz_extra, io.logp_out ? io.logp_out + row0 : nullptr, out,
                 io.opt.chunk_ratio ? nullptr : w.live_count});
         }
@@ -710,9 +732,14 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                 GemmProblem p = problem(w.a, ff, w.dz, V, ff, V, Mp, kr, kRowsAreK);
                 p.splits = plan.split_G;
                 const size_t n = (size_t)ff * V;
-                launch_gemm_group(plan.level[0].kW, s, da,
-                                  GemmJob<kKByRows, kKByRows, EpiStoreF32>{p, EpiStoreF32{w.parts, V, (int64_t)n, 0, nullptr, FinalPanel{}}, 0});
-                launch_sum_bf16(w.parts, p.splits, n, w.G, s);
+                if (p.splits == 1) {         // wide enough by itself (and wider than the parts that there is room for)
+                    launch_gemm_group(plan.level[0].kW, s, da, GemmJob<kKByRows, kKByRows, EpiStoreBf16>{p, EpiStoreBf16{w.G, V, ff}, 0});
+                } else {
+                    if (!w.parts.hold(p.splits * n)) return PCM_EWORKSPACE;
+                    launch_gemm_group(plan.level[0].kW, s, da,
+                                      GemmJob<kKByRows, kKByRows, EpiStoreF32>{p, EpiStoreF32{w.parts.at, V, (int64_t)n, 0, nullptr, FinalPanel{}}, 0});
+                    launch_sum_bf16(w.parts.at, p.splits, n, w.G, s);
+                }
             } else {
                 StageTimer t(ST_GEMM_DA, s);
                 launch_row_gemm(pa, swiglu, s);

@@ -1,0 +1,365 @@
+// Runs the host side of the actor step, as built in libpcm.so, on a HIP runtime of its own that launches nothing: the
+// functions below take the place of the runtime's, so no GPU is needed or touched.  Every launch of a matrix product and of
+// a sum of parts is looked at as the library issues it: each matrix that it reads or writes has to lie inside one of the
+// buffers that the call was given, the workspace being as long as the library's own query says.
+//
+//   host_path bounds   sweeps sizes and options and checks every launch
+#include <cxxabi.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "gemm_bf16.h"
+#include "pcm.h"
+
+using namespace pcm;
+
+namespace {
+
+struct Region {
+    const char* what;
+    uintptr_t begin, end;
+};
+std::vector<Region> regions;                      // what the call may touch
+std::map<const void*, std::string>& kernel_names() {   // by host stub; the library registers its kernels before main
+    static std::map<const void*, std::string> names;
+    return names;
+}
+std::string call;                                 // the call under way
+int failures = 0, products = 0, sums = 0;
+bool check_bounds = false;
+hipError_t last_error = hipSuccess;
+
+template <class T>
+T* buffer(const char* what, size_t count) {
+    const uintptr_t begin = regions.empty() ? (uintptr_t)1 << 40 : (regions.back().end + (1u << 20)) / 4096 * 4096;
+    regions.push_back(Region{what, begin, begin + count * sizeof(T)});
+    return reinterpret_cast<T*>(begin);
+}
+// `rows` rows of `columns` values, ld apart
+void touches(const char* kernel, const char* what, const void* p, int64_t rows, int64_t columns, int64_t ld, size_t size) {
+    if (rows <= 0) return;
+    const uintptr_t begin = (uintptr_t)p, end = begin + (uintptr_t)((rows - 1) * ld + columns) * size;
+    for (const Region& r : regions)
+        if (begin >= r.begin && end <= r.end) return;
+    if (++failures > 20) return;
+    const char* in = "no buffer";
+    long long beyond = 0;
+    for (const Region& r : regions)
+        if (begin >= r.begin && begin < r.end) { in = r.what; beyond = (long long)(end - r.end); }
+    printf("%s\n  %s: %s [%lld x %lld] starts in %s and ends %lld bytes beyond it\n", call.c_str(), kernel, what, (long long)rows,
+           (long long)columns, in, beyond);
+}
+
+// What the epilogues write; what they read of matrices is what they write, or as large.
+void writes(const char* k, const GemmProblem& p, const EpiStoreF32& e) {
+    for (int s = 0; s < p.splits; ++s) touches(k, "fp32 result", e.C + s * e.split_stride, p.M, p.N, e.ldc, 4);
+}
+void writes(const char* k, const GemmProblem& p, const EpiStoreBf16& e) {
+    touches(k, "bf16 result", e.C, p.M < e.row_limit ? p.M : e.row_limit, p.N, e.ldc, 2);
+}
+void writes(const char* k, const GemmProblem& p, const EpiStoreBf16Split& e) {
+    for (const bf16* q : {e.hi, e.lo}) touches(k, "bf16 pair", q, p.M < e.row_limit ? p.M : e.row_limit, p.N, e.ldc, 2);
+}
+void writes(const char* k, const GemmProblem& p, const EpiScatterBf16& e) { touches(k, "list", e.row_idx, 1, p.M, p.M, 4); }
+template <bool kFactors, bool kLow>
+void writes(const char* k, const GemmProblem& p, const EpiSwigluForward<kFactors, kLow>& e) {
+    touches(k, "a", e.a, p.M, p.N / 2, e.ld, 2);
+    if (kFactors) for (const bf16* q : {e.fu, e.fv}) touches(k, "factor", q, p.M, p.N / 2, e.ld, 2);
+    if (kLow) touches(k, "a_lo", e.a_lo, p.M, p.N / 2, e.ld, 2);
+}
+template <bool kIndexed>
+void writes(const char* k, const GemmProblem& p, const EpiSwigluBackward<kIndexed>& e) {
+    for (const bf16* q : {e.fu, e.fv}) touches(k, "factor", q, p.M, p.N, e.ld, 2);
+    if (kIndexed) for (const bf16* q : {e.du, e.dv}) touches(k, "du, dv", q, p.M, p.N, e.ld, 2);
+    if (kIndexed) touches(k, "list", e.row_idx, 1, p.M, p.M, 4);
+}
+template <int kLayA, int kLayB>
+void reads(const char* k, const GemmProblem& p) {
+    const bf16* const operand[2][2] = {{p.A, p.A2}, {p.B, p.B2}};
+    for (int segment = 0; segment < (p.K2 > 0 ? 2 : 1); ++segment) {
+        const int K = segment ? p.K2 : p.K1;
+        if (kLayA == kRowsByK) touches(k, "A", operand[0][segment], p.M, K, p.lda, 2);
+        else touches(k, "A", operand[0][segment], K, p.M, p.lda, 2);
+        if (kLayB == kRowsByK) touches(k, "B", operand[1][segment], p.N, K, p.ldb, 2);
+        else touches(k, "B", operand[1][segment], K, p.N, p.ldb, 2);
+    }
+}
+template <int kLayA, int kLayB, class Epilogue>
+void look(const char* k, const GemmProblem& p, const Epilogue& e) {
+    reads<kLayA, kLayB>(k, p);
+    writes(k, p, e);
+    ++products;
+}
+template <int kLayA, int kLayB, class Epilogue>
+void look_at_job(const char* k, const void* arg) {
+    const auto& j = *static_cast<const GemmJob<kLayA, kLayB, Epilogue>*>(arg);
+    look<kLayA, kLayB>(k, j.p, j.epi);
+}
+template <int kLayA, int kLayB, class Epilogue>
+void look_at_pair(const char* k, const void* arg) {
+    auto j = *static_cast<const GemmPairJob<kLayA, kLayB, Epilogue>*>(arg);
+    for (int q = 0; q < 2; ++q) {
+        j.p.B = j.p.B2 = j.B[q];
+        look<kLayA, kLayB>(k, j.p, j.epi[q]);
+    }
+}
+
+// The parts of a template argument list "A<..>, B, ..": split at the commas of the outermost level.
+std::vector<std::string> arguments(const std::string& text, size_t open) {
+    std::vector<std::string> parts(1);
+    int depth = 0;
+    for (size_t i = open + 1; i < text.size(); ++i) {
+        const char c = text[i];
+        if (c == '<') ++depth;
+        if (c == '>' && depth-- == 0) break;
+        if (c == ',' && depth == 0) parts.emplace_back();
+        else if (c != ' ') parts.back() += c;
+    }
+    return parts;
+}
+using Look = void (*)(const char*, const void*);
+// Job types by name, as the demangled kernel names write them without blanks.
+template <int kLayA, int kLayB, class Epilogue>
+void add_job(std::map<std::string, Look>& jobs, const char* epilogue) {
+    const std::string layouts = std::to_string(kLayA) + "," + std::to_string(kLayB) + ",";
+    jobs["pcm::GemmJob<" + layouts + epilogue + ">"] = look_at_job<kLayA, kLayB, Epilogue>;
+}
+template <class Epilogue>
+void add_jobs(std::map<std::string, Look>& jobs, const char* epilogue) {
+    add_job<0, 0, Epilogue>(jobs, epilogue);
+    add_job<0, 1, Epilogue>(jobs, epilogue);
+    add_job<1, 1, Epilogue>(jobs, epilogue);
+}
+const std::map<std::string, Look>& known_jobs() {
+    static std::map<std::string, Look> jobs;
+    if (jobs.empty()) {
+        add_jobs<EpiStoreF32>(jobs, "pcm::EpiStoreF32");
+        add_jobs<EpiStoreBf16>(jobs, "pcm::EpiStoreBf16");
+        add_jobs<EpiStoreBf16Split>(jobs, "pcm::EpiStoreBf16Split");
+        add_jobs<EpiScatterBf16>(jobs, "pcm::EpiScatterBf16");
+        add_jobs<EpiSwigluForward<false, false>>(jobs, "pcm::EpiSwigluForward<false,false>");
+        add_jobs<EpiSwigluForward<false, true>>(jobs, "pcm::EpiSwigluForward<false,true>");
+        add_jobs<EpiSwigluForward<true, false>>(jobs, "pcm::EpiSwigluForward<true,false>");
+        add_jobs<EpiSwigluForward<true, true>>(jobs, "pcm::EpiSwigluForward<true,true>");
+        add_jobs<EpiSwigluBackward<false>>(jobs, "pcm::EpiSwigluBackward<false>");
+        add_jobs<EpiSwigluBackward<true>>(jobs, "pcm::EpiSwigluBackward<true>");
+        jobs["pcm::GemmPairJob<1,1,pcm::EpiStoreF32>"] = look_at_pair<1, 1, EpiStoreF32>;
+    }
+    return jobs;
+}
+void unknown(const std::string& what) {
+    if (++failures <= 20) printf("%s\n  a launch that this program does not know: %s\n", call.c_str(), what.c_str());
+}
+// A product by itself has the arguments (GemmProblem, epilogue); a job holds the two side by side.
+void look_at_product(const char* k, const std::string& layouts_and_epilogue, void** args);
+
+void look_at_launch(const std::string& name, void** args) {
+    size_t at = name.find("gemm_group<");
+    if (at != std::string::npos) {
+        const auto parts = arguments(name, at + strlen("gemm_group<") - 1);
+        for (size_t q = 2; q < parts.size(); ++q) {
+            const auto job = known_jobs().find(parts[q]);
+            if (job == known_jobs().end()) unknown(parts[q]);
+            else job->second(parts[q].c_str(), args[q - 2]);
+        }
+        return;
+    }
+    at = name.find("gemm_bf16<");
+    if (at != std::string::npos) {
+        const auto parts = arguments(name, at + strlen("gemm_bf16<") - 1);      // epilogue, layout, layout, tile, ring
+        look_at_product(parts[0].c_str(), parts[1] + "," + parts[2] + "," + parts[0], args);
+        return;
+    }
+    if (name.find("sum_parts_bf16") != std::string::npos) {
+        const int n_parts = *static_cast<int*>(args[1]);
+        const size_t n = *static_cast<size_t*>(args[2]);
+        touches("sum_parts_bf16", "parts", *static_cast<void**>(args[0]), n_parts, (int64_t)n, (int64_t)n, 4);
+        touches("sum_parts_bf16", "result", *static_cast<void**>(args[3]), 1, (int64_t)n, (int64_t)n, 2);
+        ++sums;
+    }
+    if (name.find("finish_step") != std::string::npos) {
+        const PartsSums& s = *static_cast<PartsSums*>(args[0]);
+        for (int q = 0; q < s.n; ++q) {
+            touches("finish_step", "parts", s.job[q].parts, s.job[q].n_parts, (int64_t)s.job[q].n, (int64_t)s.job[q].stride, 4);
+            touches("finish_step", "result", s.job[q].out, 1, (int64_t)s.job[q].n, (int64_t)s.job[q].n, 4);
+            if (s.job[q].sumsq) touches("finish_step", "squares", s.job[q].sumsq, 1, s.job[q].blocks, s.job[q].blocks, 8);
+            ++sums;
+        }
+    }
+}
+template <class Epilogue, int kLayA, int kLayB>
+void look_at_args(const char* k, void** args) {
+    look<kLayA, kLayB>(k, *static_cast<GemmProblem*>(args[0]), *static_cast<Epilogue*>(args[1]));
+}
+template <class Epilogue>
+bool try_epilogue(const char* k, const std::string& want, const char* name, void** args) {
+    if (want == std::string("0,0,") + name) return look_at_args<Epilogue, 0, 0>(k, args), true;
+    if (want == std::string("0,1,") + name) return look_at_args<Epilogue, 0, 1>(k, args), true;
+    if (want == std::string("1,1,") + name) return look_at_args<Epilogue, 1, 1>(k, args), true;
+    return false;
+}
+void look_at_product(const char* k, const std::string& w, void** args) {
+    if (try_epilogue<EpiStoreF32>(k, w, "pcm::EpiStoreF32", args) || try_epilogue<EpiStoreBf16>(k, w, "pcm::EpiStoreBf16", args) ||
+        try_epilogue<EpiStoreBf16Split>(k, w, "pcm::EpiStoreBf16Split", args) ||
+        try_epilogue<EpiScatterBf16>(k, w, "pcm::EpiScatterBf16", args) ||
+        try_epilogue<EpiSwigluForward<false, false>>(k, w, "pcm::EpiSwigluForward<false,false>", args) ||
+        try_epilogue<EpiSwigluForward<false, true>>(k, w, "pcm::EpiSwigluForward<false,true>", args) ||
+        try_epilogue<EpiSwigluForward<true, false>>(k, w, "pcm::EpiSwigluForward<true,false>", args) ||
+        try_epilogue<EpiSwigluForward<true, true>>(k, w, "pcm::EpiSwigluForward<true,true>", args) ||
+        try_epilogue<EpiSwigluBackward<false>>(k, w, "pcm::EpiSwigluBackward<false>", args) ||
+        try_epilogue<EpiSwigluBackward<true>>(k, w, "pcm::EpiSwigluBackward<true>", args))
+        return;
+    unknown(w);
+}
+
+}  // namespace
+
+// ---- the runtime -------------------------------------------------------------------------------
+extern "C" {
+struct CallConfiguration { dim3 grid, block; size_t shared; hipStream_t stream; };
+static CallConfiguration configuration;
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shared, hipStream_t stream) {
+    configuration = CallConfiguration{grid, block, shared, stream};
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hipStream_t* stream) {
+    *grid = configuration.grid; *block = configuration.block; *shared = configuration.shared; *stream = configuration.stream;
+    return hipSuccess;
+}
+void** __hipRegisterFatBinary(const void*) { static void* handle; return &handle; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* stub, char*, const char* name, unsigned, void*, void*, dim3*, dim3*, int*) {
+    int status = 0;
+    char* const text = abi::__cxa_demangle(name, nullptr, nullptr, &status);
+    kernel_names()[stub] = text ? text : name;
+    free(text);
+}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+hipError_t hipLaunchKernel(const void* stub, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
+    if (check_bounds) {
+        if (grid.x == 0 || grid.y == 0 || grid.z == 0 || block.x * block.y * block.z > 1024) unknown("an empty or too large grid");
+        look_at_launch(kernel_names()[stub], args);
+    }
+    return hipSuccess;
+}
+hipError_t hipGetLastError() {
+    const hipError_t e = last_error;
+    last_error = hipSuccess;
+    return e;
+}
+hipError_t hipGetDevice(int* device) { *device = 0; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void**, const void*) { return hipErrorInvalidSymbol; }
+hipError_t hipEventCreate(hipEvent_t*) { return hipErrorInvalidValue; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipErrorInvalidValue; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipErrorInvalidValue; }
+hipError_t hipEventElapsedTime(float*, hipEvent_t, hipEvent_t) { return hipErrorInvalidValue; }
+}
+
+namespace {
+
+struct Step {
+    int dtype, chunks, A, d, ff, V;
+    bool weights, dX, composed, chunk_ratio, sumsq, packed, dense;
+    float entropy;
+    int panel_rows;
+};
+int run(const Step& c) {
+    char text[256];
+    snprintf(text, sizeof text, "dtype %d, %d chunks of %d rows, %d -> %d -> %d, weights %d dX %d composed %d chunk ratio %d squares %d "
+             "packed %d dense %d entropy %g panels %d", c.dtype, c.chunks, c.A, c.d, c.ff, c.V, c.weights, c.dX, c.composed, c.chunk_ratio,
+             c.sumsq, c.packed, c.dense, c.entropy, c.panel_rows);
+    call = text;
+    regions.clear();
+    const size_t d = c.d, ff = c.ff, V = c.V, rows = (size_t)c.chunks * c.A, size = c.dtype == PCM_BF16 ? 2 : 4;
+    pcm_loss_options o{};
+    o.eps_low = o.eps_high = 0.2f;
+    o.loss_scale = 1.f;
+    o.entropy_coef = c.entropy;
+    o.ratio_level = c.chunk_ratio ? PCM_RATIO_CHUNK : PCM_RATIO_TOKEN;
+    o.head_evaluation = c.composed ? PCM_HEAD_COMPOSED : PCM_HEAD_AS_WRITTEN;
+    o.panel_rows = c.panel_rows;
+    o.dense_backward = c.dense;
+    if (c.packed) o.packed_weights = buffer<char>("packed weights", pcm_packed_head_bytes(c.d, c.ff, c.V));
+    if (c.sumsq) o.grad_sumsq_out = buffer<double>("sum of squares", 1);
+    const char* const hidden = buffer<char>("hidden", rows * d * size);
+    const uint8_t* const tokens = buffer<uint8_t>("tokens", rows);
+    const float* const logp_old = buffer<float>("logp_old", rows);
+    const float* const adv = buffer<float>("adv", c.chunks);
+    const int32_t* const kept = buffer<int32_t>("kept_idx", c.chunks);
+    const int32_t* const n_kept = buffer<int32_t>("n_kept", 1);
+    const char *const Wg = buffer<char>("Wg", d * ff * size), *const Wu = buffer<char>("Wu", d * ff * size);
+    const char *const Wd = buffer<char>("Wd", ff * d * size), *const Wo = buffer<char>("Wo", d * V * size);
+    float* const loss = buffer<float>("loss", 1);
+    float *dW[4] = {};
+    if (c.weights) {
+        const size_t n[4] = {d * ff, d * ff, ff * d, d * V};
+        for (int q = 0; q < 4; ++q) dW[q] = buffer<float>("a weight gradient", n[q]);
+    }
+    char* const dX = c.dX ? buffer<char>("dX", rows * d * size) : nullptr;
+    const size_t bytes = grpo_masked_actor_step_ex_workspace_bytes(c.chunks, c.A, c.d, c.ff, c.V, c.dtype, c.weights || c.dX, &o);
+    if (bytes == 0) { unknown("the workspace query refuses the shape"); return PCM_EINVAL; }
+    char* const ws = buffer<char>("the workspace", bytes);
+    last_error = hipSuccess;
+    return grpo_masked_actor_step_ex(hidden, tokens, logp_old, adv, kept, n_kept, c.chunks, c.chunks, 1, c.A, c.d, c.ff, c.V, c.dtype, Wg, Wu,
+                                     Wd, Wo, &o, loss, nullptr, dW[0], dW[1], dW[2], dW[3], dX, nullptr, ws, bytes, nullptr);
+}
+void expect(int rc, int want) {
+    if (rc != want && ++failures <= 20) printf("%s\n  returned %d, not %d\n", call.c_str(), rc, want);
+}
+
+// f over the bf16 calls of one size
+template <class F>
+void bf16_calls(int chunks, int A, int d, int ff, int panel_rows, F f) {
+    Step s{PCM_BF16, chunks, A, d, ff, 256, false, false, false, false, false, false, false, 0.f, panel_rows};
+    for (int composed = 0; composed < 2; ++composed)
+        for (int grads = 0; grads < 4; ++grads)
+            for (int option = 0; option < 5; ++option) {
+                Step c = s;
+                c.composed = composed;
+                c.weights = grads & 1;
+                c.dX = grads & 2;
+                c.packed = option == 1 && !composed;
+                c.chunk_ratio = option == 2 && !composed;
+                c.sumsq = (option == 1 || option == 4) && c.weights && !composed;
+                c.dense = option == 3;
+                c.entropy = option == 4 ? 1e-3f : 0.f;
+                f(c);
+            }
+}
+void bounds() {
+    check_bounds = true;
+    const int heads[][2] = {{256, 256}, {512, 768}, {256, 5120}, {3072, 768}, {768, 2304}, {1024, 11008}, {4096, 11008}, {8192, 28672},
+                            {256, 32768}, {256, 33024}, {256, 65536}, {256, 65792}, {512, 131072}, {65792, 256}, {256, 1 << 20}};
+    const int rows[][2] = {{1, 1}, {1, 56}, {12, 56}, {37, 56}, {96, 56}, {147, 56}, {768, 56}, {2048, 56}, {4096, 16}, {5, 1000}, {65793, 1}};
+    for (const auto& h : heads)
+        for (const auto& r : rows)
+            for (int panel : {0, 1, 3000})
+                bf16_calls(r[0], r[1], h[0], h[1], panel, [&](const Step& c) { expect(run(c), PCM_OK); });
+    for (const auto& h : heads)                   // rows beyond the tiles of the widest of those heads
+        bf16_calls(1 << 20, 16, h[0], h[1], 0, [&](const Step& c) { expect(run(c), PCM_OK); });
+    for (int d : {1, 33, 64, 256, 1024})
+        for (int ff : {1, 65, 300, 2816})
+            for (int V : {1, 17, 256, 1024})
+                for (int chunks : {1, 9, 46, 500})
+                    for (int q = 0; q < 16; ++q) {
+                        const Step c{PCM_F32, chunks, 56, d, ff, V, (q & 1) != 0, (q & 2) != 0, (q & 4) != 0, (q & 8) != 0, false, false, false,
+                                     q % 3 == 0 ? 1e-3f : 0.f, 0};
+                        expect(run(c), PCM_OK);
+                    }
+    if (products < 10000 || sums < 1000) unknown("too few launches were looked at");
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+    if (argc != 2) return 2;
+    if (!strcmp(argv[1], "bounds")) bounds();
+    else return 2;
+    printf("%d products, %d sums, %d failures\n", products, sums, failures);
+    return failures != 0;
+}

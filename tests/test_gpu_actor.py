@@ -772,3 +772,14 @@ def test_bf16_products_that_share_a_launch(pcm, d, ff, n_kept, max_kept, options
     _, weights_only = run_both(pcm, pr, want_dX=False, **kw)
     for k in GRADS:
         assert np.array_equal(weights_only[k], both[k]), k
+
+
+@pytest.mark.parametrize("ff", [33024, 65792])
+def test_bf16_composed_head_too_wide_for_parts(pcm, ff):
+    """From 129 column tiles on a^T dz covers the chip by itself and is stored at once; from 257 on its parts would not fit
+    the buffer that the narrow heads' parts share."""
+    cfg = CONFIGS["cfg2"].with_(n_groups=1, G=4, N=16, K=4, B=4, d=256, ff=ff, seed=96)
+    kept = np.array([3, 17, 40], dtype=np.int32)
+    pr = make_problem(cfg, wstd=0.6 / np.sqrt(256), margin=0.08, kept=kept, old_rel=0.1, eps=(0.2, 0.4))
+    ref, got = run_both(pcm, pr, eps=(0.2, 0.4), torch_dtype=torch.bfloat16, max_kept=5, composed_head=True)
+    check(ref, got, BF16_TOL, len(ref["rows"]), stats_tol=5e-2)
