@@ -96,7 +96,7 @@ void launch_transposes(const TransposeList& list, bool stream, hipStream_t s);
 // arrays are the panel's own, `rows_pad` its height.  The same holds for the two per-chunk-ratio launches below
 // (row_offset a multiple of A, so no chunk straddles two panels).
 // In the same launch: the transposes of `layouts`, and zeros in zero[0 .. n_zero).
-int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void* X, int64_t row_offset, int64_t rows_pad,
+[[nodiscard]] int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void* X, int64_t row_offset, int64_t rows_pad,
                   RowMeta meta, const TransposeList& layouts, double* zero, int n_zero, hipStream_t s);
 
 // Partial sums of squares of the four weight gradients, left by the launches that wrote their final values.
@@ -129,16 +129,16 @@ struct PartsSums {
 // and statistics of the whole batch, in a fixed order (one workgroup, fp64 accumulators).  With lists the partial sums of
 // squares of the weight gradients are added up behind it, into io.opt.grad_sumsq_out.
 struct FinalPanel;
-int launch_finish(const ActorShape& sh, const ActorIO& io, RowOut out, const PartsSums& sums, const FinalPanel& panel, bool with_loss,
+[[nodiscard]] int launch_finish(const ActorShape& sh, const ActorIO& io, RowOut out, const PartsSums& sums, const FinalPanel& panel, bool with_loss,
                   const SumsqLists& lists, hipStream_t s);
 
 // Per-chunk ratio: from the per-row dlogp, one ratio, one clipped term and one dz factor per kept chunk
 // (written to every row of the chunk; the term only to its first row).
-int launch_chunk_ratio(const ActorShape& sh, const ActorIO& io, RowMeta meta, RowOut out, int64_t row_offset,
+[[nodiscard]] int launch_chunk_ratio(const ActorShape& sh, const ActorIO& io, RowMeta meta, RowOut out, int64_t row_offset,
                        int64_t rows_pad, hipStream_t s);
 
 // fp32 path: dz[r, :] = coef[r] * dz[r, :] (+ extra[r, :] if extra is given) for the live rows r (V columns each).
-int launch_scale_rows_f32(const ActorShape& sh, const ActorIO& io, float* dz, const float* extra, const float* coef,
+[[nodiscard]] int launch_scale_rows_f32(const ActorShape& sh, const ActorIO& io, float* dz, const float* extra, const float* coef,
                           int64_t rows, hipStream_t s);
 
 // Backward pass over the rows that carry a gradient only (bf16 path).  A kernel lists the panel's rows whose factor
@@ -160,7 +160,7 @@ struct LivePlan {
 // listed rows of the four sources (rows of row_bytes, a multiple of 16; 0: not wanted) with zero rows up to the end of the
 // last row tile.  Rows of dX (or null; rows_in_dX rows exist) that the listed products do not write are cleared.
 constexpr int kListBlock = 16;
-int launch_live_rows(const ActorShape& sh, const ActorIO& io, const uint8_t* clipped, const float* adv, const int32_t* counts,
+[[nodiscard]] int launch_live_rows(const ActorShape& sh, const ActorIO& io, const uint8_t* clipped, const float* adv, const int32_t* counts,
                      int64_t row_offset, int64_t rows_pad, const LiveSources& whole, const LiveSources& listed,
                      const int64_t (&row_bytes)[LiveSources::kCount], void* dX, int64_t rows_in_dX, int32_t* idx, LivePlan* plan,
                      hipStream_t s);

@@ -513,7 +513,7 @@ EpiStoreF32 reduction_epilogue(GemmProblem& p, int splits, float* C, float* part
 }
 // C = a product with a long reduction and a small output, as parts and rounded once to bf16.
 template <int kLayA, int kLayB>
-int launch_reduction_bf16(GemmProblem p, bf16* C, const SharedParts& parts, int stage, hipStream_t s) {
+[[nodiscard]] int launch_reduction_bf16(GemmProblem p, bf16* C, const SharedParts& parts, int stage, hipStream_t s) {
     StageTimer t(stage, s);
     p.splits = pick_splits((p.M / kTileM) * (p.N / kTileN), p.K1 / kTileK);
     const size_t n = (size_t)p.M * p.N;
@@ -543,7 +543,7 @@ GemmProblem problem(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int 
 // Measured, whole passes without gradients, before (small tiles only, at most four parts) / now: 672 rows of 4096 -> 11008, five
 // parts on large tiles, 262 / 237 us (its down projection 96 -> 62, the sum 6 -> 10); 512 of 512 -> 9984 58.7 / 52.2; 896 of
 // 2304 -> 2560 86 / 79.
-int launch_rows_bf16(GemmProblem p, bf16* C, const SharedParts& parts, hipStream_t s) {
+[[nodiscard]] int launch_rows_bf16(GemmProblem p, bf16* C, const SharedParts& parts, hipStream_t s) {
     const GroupPlan plan = plan_group<1>({{p.M, p.N, (p.K1 + p.K2) / kTileK, 1, true, 16}}, 5.f);
     if (plan.splits[0] == 1) {
         launch_row_gemm(p, EpiStoreBf16{C, p.N, p.M}, s);

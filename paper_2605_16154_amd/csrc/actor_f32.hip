@@ -553,14 +553,20 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t
     }
     if (!bwd) return launch_finish(sh, io, w.out, PartsSums{}, FinalPanel{}, true, SumsqLists{}, s);
     PartsSums sums{};
+    float* const dz = w.z;
+    if (io.want_grads() && io.composed) {
+        PartsSums g{};
+        {
+            StageTimer t(ST_F32_BACKWARD, s);
+            gemm_reduce_rows(s, w.a, dz, w.G, nullptr, nullptr, ff, V, M, w.parts, g, rows);               // G = a^T dz
+        }
+        rc = launch_finish(sh, io, w.out, g, FinalPanel{}, false, SumsqLists{}, s);
+        if (rc != PCM_OK) return rc;
+    }
     {
         StageTimer t(ST_F32_BACKWARD, s);
-        float* dz = w.z;
         if (io.want_grads()) {
             if (io.composed) {
-                PartsSums g{};
-                gemm_reduce_rows(s, w.a, dz, w.G, nullptr, nullptr, ff, V, M, w.parts, g, rows);     // G = a^T dz
-                launch_finish(sh, io, w.out, g, FinalPanel{}, false, SumsqLists{}, s);
                 gemm(s, w.G, Wo, true, io.dWd, ff, d, V, none);                                        // dWd = G Wo^T
                 gemm_reduce_rows(s, Wd, w.G, io.dWo, nullptr, nullptr, d, V, ff, w.parts, sums, none);   // dWo = Wd^T G
             } else {
@@ -571,18 +577,20 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t
             gemm(s, dz, Wo, true, w.dy, M, d, V, rows);                                                // dy = dz Wo^T
             if (io.want_grads()) gemm_reduce_rows(s, w.a, w.dy, io.dWd, nullptr, nullptr, ff, d, M, w.parts_d, sums, rows);   // dWd = a^T dy
         }
-        {   // da = dy Wd^T (composed: dz W_do^T); u <- du, v <- dv
-            const int k = io.composed ? V : d;
-            const F32Problem p = io.composed ? problem(dz, V, w.Wdo, V, M, ff, k, rows, kLiveM) : problem(w.dy, d, Wd, d, M, ff, k, rows, kLiveM);
-            launch<kRowsByK, kRowsByK, kNone>(p, plan_tiles(M, ff, k, 1, false, false), F32SwigluBackward{w.u, w.v}, s);
-        }
-        if (io.want_grads()) {
-            if (sums.n > 0 && split_floats(d, ff, M, 2) > 0) {                                         // the parts' memory is needed again
-                launch_finish(sh, io, w.out, sums, FinalPanel{}, false, SumsqLists{}, s);
-                sums = PartsSums{};
-            }
-            gemm_reduce_rows(s, w.X, w.u, io.dWg, w.v, io.dWu, d, ff, M, w.parts, sums, rows);     // dWg = X^T du, dWu = X^T dv
-        }
+        // da = dy Wd^T (composed: dz W_do^T); u <- du, v <- dv
+        const int k = io.composed ? V : d;
+        const F32Problem p = io.composed ? problem(dz, V, w.Wdo, V, M, ff, k, rows, kLiveM) : problem(w.dy, d, Wd, d, M, ff, k, rows, kLiveM);
+        launch<kRowsByK, kRowsByK, kNone>(p, plan_tiles(M, ff, k, 1, false, false), F32SwigluBackward{w.u, w.v}, s);
+    }
+    if (io.want_grads() && sums.n > 0 && split_floats(d, ff, M, 2) > 0) {                              // the parts' memory is needed again
+        rc = launch_finish(sh, io, w.out, sums, FinalPanel{}, false, SumsqLists{}, s);
+        if (rc != PCM_OK) return rc;
+        sums = PartsSums{};
+    }
+    {
+        StageTimer t(ST_F32_BACKWARD, s);
+        if (io.want_grads())
+            gemm_reduce_rows(s, w.X, w.u, io.dWg, w.v, io.dWu, d, ff, M, w.parts, sums, rows);         // dWg = X^T du, dWu = X^T dv
         if (io.dX) {                                                                                   // dX = du Wg^T + dv Wu^T
             // as two products, in place of y and dy (no longer needed), and their sum: twice the workgroups, sums half as long
             F32Problem p = problem(w.u, ff, Wg, ff, M, d, ff, rows, kLiveM);

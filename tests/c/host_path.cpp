@@ -4,6 +4,7 @@
 // buffers that the call was given, the workspace being as long as the library's own query says.
 //
 //   host_path bounds   sweeps sizes and options and checks every launch
+//   host_path errors   lets each launch of a call fail in turn: the call has to return PCM_EHIP
 #include <cxxabi.h>
 
 #include <cstdio>
@@ -30,7 +31,8 @@ std::map<const void*, std::string>& kernel_names() {   // by host stub; the libr
     return names;
 }
 std::string call;                                 // the call under way
-int failures = 0, products = 0, sums = 0;
+int failures = 0, launches = 0, products = 0, sums = 0;
+int fail_at = -1;                                 // the launch that fails, or -1
 bool check_bounds = false;
 hipError_t last_error = hipSuccess;
 
@@ -241,6 +243,8 @@ void __hipRegisterFunction(void**, const void* stub, char*, const char* name, un
 }
 void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 hipError_t hipLaunchKernel(const void* stub, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
+    const bool fails = launches++ == fail_at;
+    if (fails) return last_error = hipErrorLaunchFailure;
     if (check_bounds) {
         if (grid.x == 0 || grid.y == 0 || grid.z == 0 || block.x * block.y * block.z > 1024) unknown("an empty or too large grid");
         look_at_launch(kernel_names()[stub], args);
@@ -304,6 +308,7 @@ int run(const Step& c) {
     const size_t bytes = grpo_masked_actor_step_ex_workspace_bytes(c.chunks, c.A, c.d, c.ff, c.V, c.dtype, c.weights || c.dX, &o);
     if (bytes == 0) { unknown("the workspace query refuses the shape"); return PCM_EINVAL; }
     char* const ws = buffer<char>("the workspace", bytes);
+    launches = 0;
     last_error = hipSuccess;
     return grpo_masked_actor_step_ex(hidden, tokens, logp_old, adv, kept, n_kept, c.chunks, c.chunks, 1, c.A, c.d, c.ff, c.V, c.dtype, Wg, Wu,
                                      Wd, Wo, &o, loss, nullptr, dW[0], dW[1], dW[2], dW[3], dX, nullptr, ws, bytes, nullptr);
@@ -353,12 +358,29 @@ void bounds() {
                     }
     if (products < 10000 || sums < 1000) unknown("too few launches were looked at");
 }
+void errors() {
+    auto each_launch = [&](const Step& c) {
+        fail_at = -1;
+        expect(run(c), PCM_OK);
+        const int n = launches;
+        for (fail_at = 0; fail_at < n; ++fail_at) {
+            const int rc = run(c);
+            if (rc != PCM_EHIP) call += ", launch " + std::to_string(fail_at) + " of " + std::to_string(n) + " failed";
+            expect(rc, PCM_EHIP);
+        }
+    };
+    bf16_calls(37, 56, 512, 768, 0, each_launch);
+    bf16_calls(37, 56, 512, 768, 600, each_launch);
+    for (int q = 0; q < 16; ++q)
+        each_launch(Step{PCM_F32, 46, 56, 64, 96, 32, (q & 1) != 0, (q & 2) != 0, (q & 4) != 0, (q & 8) != 0, false, false, false, 0.f, 0});
+}
 
 }  // namespace
 
 int main(int argc, char** argv) {
     if (argc != 2) return 2;
     if (!strcmp(argv[1], "bounds")) bounds();
+    else if (!strcmp(argv[1], "errors")) errors();
     else return 2;
     printf("%d products, %d sums, %d failures\n", products, sums, failures);
     return failures != 0;

@@ -32,3 +32,8 @@ def test_every_product_stays_inside_the_buffers_of_the_call(host_path):
     its query says: over narrow and wide heads (up to a million columns, where a sum of parts no longer fits the buffer of the
     small ones), short and long batches, row panels, and every option."""
     _run(host_path, "bounds")
+
+
+def test_a_launch_that_fails_is_reported(host_path):
+    """Each launch of a call fails in turn, in the stub runtime: the call returns PCM_EHIP, whichever launch it was."""
+    _run(host_path, "errors")
