@@ -14,6 +14,8 @@
 //
 // All arithmetic after the weight quantisation is integer, and the random bits depend only on
 // (seed, step, trajectory, round), so the kept set is a pure function of the inputs.
+#include <type_traits>
+
 #include "common.h"
 
 namespace pcm {
@@ -476,25 +478,31 @@ __global__ __launch_bounds__(kThreads) void importance_weights(const uint8_t* __
 
 // Chunks of one phase: workgroup c counts the kept chunks of phase c, workgroup K + c the chunk slots of phase c that the
 // sampler could have kept.  Each output has one writer, so nothing is cleared and nothing added in memory; the phases are read
-// K times, by as many CUs (32 KB for 32768 slots).  What it waits for is three dependent loads: a wavefront takes kCountRows
-// trajectories at a time, 64 slots of each per trip.  A histogram of all phases by one workgroup was bound by the instructions of
-// its CU, histogram / this, per call: 256 trajectories of 128 slots, 5 phases 13.3 / 7.8 us; 512 of 256, 12 phases 47 / 17; 64 of
-// 4096, phases in random order 89 / 34; 8192 of 128 363 / 177; 300 of 77, 64 phases 12.7 / 10.4.
-constexpr int kCountThreads = 1024, kCountRows = 16;
+// K times, by as many CUs (32 KB for 32768 slots).  What it waits for is the latency of its loads, so they do not depend on one
+// another: the slots are dealt to the sixteen wavefronts in turn in units of one load each, kCountUnits under way together.
+// A unit is 64 slots of a trajectory, or 64 / L whole trajectories of up to L slots (L a power of two), so that neither a few
+// long trajectories nor many short ones leave wavefronts or lanes idle.
+// Per call, a histogram of all phases by one workgroup / whole trajectories, sixteen to a wavefront / this: 256 trajectories of 128
+// slots, 5 phases 13.3 / 7.9 / 6.1 us; 512 of 256, 12 phases 47 / 17 / 16; 64 of 4096 88 / 34 / 29; 4 of 4096 7.3 / 30 / 6.1;
+// 32768 of 8 96 / 602 / 32; 65536 of 16 380 / 1345 / 114; a million of one 673 / 21800 / 663; 300 of 77, 64 phases 12.7 / 10.4 / 7.4.
+constexpr int kCountThreads = 1024, kCountWaves = kCountThreads / kWave, kCountUnits = 16;
 __global__ __launch_bounds__(kCountThreads) void kept_phase_counts(const uint8_t* __restrict__ phase,
                                                                    const int32_t* __restrict__ n_chunks,
                                                                    const uint8_t* __restrict__ active,
                                                                    const int32_t* __restrict__ kept_idx,
                                                                    const int32_t* __restrict__ n_kept, int max_kept, int T, int N,
                                                                    int K, int32_t* kept_out, int32_t* eligible_out) {
-    __shared__ int wave_count[kCountThreads / kWave];
+    __shared__ int wave_count[kCountWaves];
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const bool eligible = (int)blockIdx.x >= K;
-    const int mine = (int)blockIdx.x % K;
+    const int mine = (int)blockIdx.x % K, slots = T * N;                     // fewer than 2^31
     auto is_mine = [&](int c) { return min(c, K - 1) == mine; };             // ids beyond the last phase count as the last
+    auto live_slots = [&](int i) {                                           // of trajectory i: those that may be kept
+        const int n = n_chunks ? n_chunks[i] : N;
+        return !active || active[i] != 0 ? min(n, N) : 0;
+    };
     int count = 0;
     if (!eligible) {
-        const int64_t slots = (int64_t)T * N;
         int nk = *n_kept;
         nk = nk < 0 ? 0 : (nk > max_kept ? max_kept : nk);
         constexpr int kBatch = 4;
@@ -508,25 +516,47 @@ __global__ __launch_bounds__(kCountThreads) void kept_phase_counts(const uint8_t
             for (int u = 0; u < kBatch; ++u) count += id[u] >= 0 && id[u] < slots && is_mine(c[u]) ? 1 : 0;
         }
     } else {
-        for (int64_t i0 = (int64_t)wave * kCountRows; i0 < T; i0 += kCountThreads / kWave * kCountRows) {
-            int live[kCountRows], longest = 0;                                // slots of each trajectory that may be kept
+        const int blocks = (N + kWave - 1) / kWave;                          // units of a trajectory
+        auto count_units = [&](auto trajectories) {
+            constexpr int kPer = decltype(trajectories)::value;              // of a unit; if several, blocks is 1
+            constexpr int kRounds = kPer > 4 ? kPer / 4 : 1;
+            const int64_t units = kPer > 1 ? (T + kPer - 1) / kPer : (int64_t)T * blocks;
+            const int k = lane % (kWave / kPer), row = lane / (kWave / kPer), at = kPer > 1 ? min(k, N - 1) : k;
+            for (int64_t u0 = 0; u0 < units; u0 += kCountWaves * kCountUnits) {
+                // trajectory r of the wavefront's unit q is looked after by lane (q kPer + r) modulo 64, once for all lanes of
+                // the unit: where its slots begin, and how many of them may be kept
+                int begin[kRounds], live[kRounds], c[kCountUnits];
 #pragma unroll
-            for (int u = 0; u < kCountRows; ++u) {
-                const int i = (int)min(i0 + u, (int64_t)T - 1);
-                const int n = n_chunks ? n_chunks[i] : N;
-                const bool on = (!active || active[i] != 0) && i0 + u < T;
-                live[u] = on ? min(n, N) : 0;
+                for (int m = 0; m < kRounds; ++m) {
+                    const int q = (m * kWave + lane) / kPer;
+                    const int64_t u = u0 + q * kCountWaves + wave;
+                    const int64_t i = kPer > 1 ? u * kPer + lane % kPer : (int64_t)((uint32_t)u / (uint32_t)blocks);
+                    const bool in = q < kCountUnits && u < units && i < T;
+                    const int k0 = in && kPer == 1 ? (int)(u - i * blocks) * kWave : 0;
+                    begin[m] = in ? (int)i * N + k0 : 0;
+                    live[m] = in ? live_slots((int)i) - k0 : 0;
+                }
+                auto of_unit = [&](const int (&x)[kRounds], int q) {
+                    const int from = x[q * kPer / kWave];
+                    if (kPer == kWave) return from;
+                    return kPer > 1 ? __shfl(from, q * kPer % kWave + row, kWave) : __builtin_amdgcn_readlane(from, q);
+                };
+#pragma unroll
+                for (int q = 0; q < kCountUnits; ++q) {
+                    const int from = of_unit(begin, q);
+                    c[q] = phase[from + min(at, slots - 1 - from)];
+                }
+#pragma unroll
+                for (int q = 0; q < kCountUnits; ++q) count += k < of_unit(live, q) && is_mine(c[q]) ? 1 : 0;
             }
-#pragma unroll
-            for (int u = 0; u < kCountRows; ++u) longest = max(longest, live[u]);
-            for (int k = lane; k < longest; k += kWave) {
-                int c[kCountRows];
-#pragma unroll
-                for (int u = 0; u < kCountRows; ++u) c[u] = phase[min(i0 + u, (int64_t)T - 1) * N + k];
-#pragma unroll
-                for (int u = 0; u < kCountRows; ++u) count += k < live[u] && is_mine(c[u]) ? 1 : 0;
-            }
-        }
+        };
+        if (N > 32) count_units(std::integral_constant<int, 1>{});
+        else if (N > 16) count_units(std::integral_constant<int, 2>{});
+        else if (N > 8) count_units(std::integral_constant<int, 4>{});
+        else if (N > 4) count_units(std::integral_constant<int, 8>{});
+        else if (N > 2) count_units(std::integral_constant<int, 16>{});
+        else if (N > 1) count_units(std::integral_constant<int, 32>{});
+        else count_units(std::integral_constant<int, 64>{});
     }
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) count += __shfl_xor(count, o, kWave);
@@ -535,7 +565,7 @@ __global__ __launch_bounds__(kCountThreads) void kept_phase_counts(const uint8_t
     if (tid != 0) return;
     count = 0;
 #pragma unroll
-    for (int q = 0; q < kCountThreads / kWave; ++q) count += wave_count[q];
+    for (int q = 0; q < kCountWaves; ++q) count += wave_count[q];
     (eligible ? eligible_out : kept_out)[mine] = count;
 }
 

@@ -408,3 +408,35 @@ def test_allocation_counts_phase_by_phase(pcm, T, N, K):
     assert pcm.lib().pcm_kept_phase_counts(d_phase.data_ptr(), None, None, d_kept.data_ptr(), d_n.data_ptr(), 5000, T, N, K,
                                            only.data_ptr(), None, torch.cuda.current_stream().cuda_stream) == 0
     assert np.array_equal(only.cpu().numpy(), want[0])
+
+
+@pytest.mark.parametrize("T,N,K", [
+    (3, 4096, 5),        # few long trajectories: every wavefront has slots of each
+    (5, 1000, 3),        # a last unit of a trajectory that is not full, fewer units than one trip takes
+    (70, 33, 4),         # a unit per trajectory, the shortest of them
+    (71, 32, 4),         # two trajectories per unit, the longest of them
+    (530, 17, 4),        # and the shortest, a second trip of a few units
+    (1027, 16, 4),       # four per unit, the longest, three trajectories behind a whole trip
+    (30, 9, 4),          # and the shortest
+    (3001, 5, 4),        # eight per unit, lanes beyond the trajectory's slots, a second trip that is not full
+    (2051, 8, 4),        # eight per unit, the longest, three trajectories behind a whole trip
+    (4099, 3, 4),        # sixteen
+    (8201, 2, 4),        # thirty-two
+    (16387, 1, 2),       # sixty-four per unit, three trajectories behind a whole trip
+])
+def test_allocation_counts_of_few_long_and_many_short_trajectories(pcm, T, N, K):
+    """Counts against a plain histogram on both sides of the line between the two ways the slots are dealt."""
+    rng = np.random.default_rng(T + N)
+    phase = rng.integers(0, K + 2, size=(T, N)).astype(np.uint8)
+    n_chunks = rng.integers(-2, N + 3, size=T).astype(np.int32)
+    active = (rng.random(T) < 0.7).astype(np.uint8)
+    kept = rng.integers(-3, T * N + 3, size=700).astype(np.int32)
+    n_kept = np.array([700], np.int32)
+    ph = np.minimum(phase, K - 1).reshape(-1)
+    live = (np.arange(N)[None, :] < n_chunks[:, None]) & (active[:, None] != 0)
+    inside = kept[(kept >= 0) & (kept < T * N)]
+    want = np.bincount(ph[inside], minlength=K), np.bincount(ph[live.reshape(-1)], minlength=K)
+    got = pcm.pcm_kept_phase_counts(dev(phase), dev(n_chunks), dev(active), dev(kept), dev(n_kept), K)
+    assert np.array_equal(got[0].cpu().numpy(), want[0]) and np.array_equal(got[1].cpu().numpy(), want[1])
+    every = pcm.pcm_kept_phase_counts(dev(phase), None, None, dev(kept), dev(n_kept), K)
+    assert np.array_equal(every[0].cpu().numpy(), want[0]) and np.array_equal(every[1].cpu().numpy(), np.bincount(ph, minlength=K))
