@@ -42,12 +42,25 @@ namespace {
 constexpr size_t kMaxSplitTiles = 256;   // tiles x parts of a split reduction: one workgroup per CU
 constexpr size_t kSumBlocksMax = PartsSums::kBlocksMax;
 
+// Rows of a product over a panel of the batch that its row tiles cover, from the device-side count (kept as in GemmProblem).
+struct LiveTiles {
+    const int32_t* kept;
+    int kept_max, rows_per_kept, row_offset, row_length;
+    __device__ size_t rows() const {
+        const int64_t rows = live_rows(kept, kept_max, rows_per_kept) - row_offset;
+        return rows <= 0 ? 0 : (size_t)((rows + kTileM - 1) / kTileM * kTileM);
+    }
+};
+
 // out[i] = the sum over the parts of a split reduction (n is a multiple of 4; parts are n floats apart), rounded once to bf16: a
-// product that the next GEMM takes as an operand.
-__global__ void sum_parts_bf16(const float* parts, int n_parts, size_t n, bf16* out) {
+// product that the next GEMM takes as an operand.  Of a product over the rows of the batch (live.kept is set) only the row tiles
+// that it computed: of a list far shorter than its buffer the rest are parts that nobody wrote.  Log-probabilities, all rows of
+// the buffer / live tiles: 112 rows in a buffer of 2296, 1024 -> 11008, six parts 87.0 / 80.1 us; 448 in one of 5376, 1024 -> 8192,
+// three parts 101.8 / 93.1; 56 in one of 672, 4096 -> 11008, five parts 175.1 / 166.3.
+__global__ void sum_parts_bf16(const float* parts, int n_parts, size_t n, bf16* out, LiveTiles live) {
     constexpr int kTogether = 4;      // loads under way together
-    const size_t stride = (size_t)gridDim.x * blockDim.x * 4;
-    for (size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < n; i += stride) {
+    const size_t stride = (size_t)gridDim.x * blockDim.x * 4, limit = live.kept != nullptr ? min(n, live.rows() * live.row_length) : n;
+    for (size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < limit; i += stride) {
         f32x4 acc = *reinterpret_cast<const f32x4*>(parts + i);
         for (int s0 = 1; s0 < n_parts; s0 += kTogether) {
             f32x4 v[kTogether];
@@ -61,9 +74,9 @@ __global__ void sum_parts_bf16(const float* parts, int n_parts, size_t n, bf16* 
     }
 }
 
-void launch_sum_bf16(const float* parts, int n_parts, size_t n, bf16* out, hipStream_t s) {
+void launch_sum_bf16(const float* parts, int n_parts, size_t n, bf16* out, const LiveTiles& live, hipStream_t s) {
     const size_t blocks = (n / 4 + 255) / 256;
-    sum_parts_bf16<<<(unsigned)(blocks < kSumBlocksMax ? blocks : kSumBlocksMax), 256, 0, s>>>(parts, n_parts, n, out);
+    sum_parts_bf16<<<(unsigned)(blocks < kSumBlocksMax ? blocks : kSumBlocksMax), 256, 0, s>>>(parts, n_parts, n, out, live);
 }
 
 // The loss over the rows of a panel: log-softmax at the target bin, row entropy, ratio, clipped surrogate and
@@ -523,7 +536,7 @@ template <int kLayA, int kLayB>
     }
     if (!parts.hold(p.splits * n)) return PCM_EWORKSPACE;
     launch_gemm<kLayA, kLayB>(p, EpiStoreF32{parts.at, p.N, (int64_t)n, 0, nullptr, FinalPanel{}}, s);
-    launch_sum_bf16(parts.at, p.splits, n, C, s);
+    launch_sum_bf16(parts.at, p.splits, n, C, LiveTiles{}, s);
     return PCM_OK;
 }
 
@@ -543,6 +556,9 @@ GemmProblem problem(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int 
 // Measured, whole passes without gradients, before (small tiles only, at most four parts) / now: 672 rows of 4096 -> 11008, five
 // parts on large tiles, 262 / 237 us (its down projection 96 -> 62, the sum 6 -> 10); 512 of 512 -> 9984 58.7 / 52.2; 896 of
 // 2304 -> 2560 86 / 79.
+// The plan is made for a full buffer, so that a row's bits do not depend on how many others are in the list.  Lists up to a quarter
+// of the buffer would like more parts: plan / that rule before, full and with a quarter of the list: 2296 rows of 1024 -> 11008
+// 194.7 and 108.4 / 199.9 and 120.2 us, 1344 of 2048 -> 5632 124 and 94 / 135 and 88, 5376 of 512 -> 5632 137 and 86 / 145 and 74.
 [[nodiscard]] int launch_rows_bf16(GemmProblem p, bf16* C, const SharedParts& parts, hipStream_t s) {
     const GroupPlan plan = plan_group<1>({{p.M, p.N, (p.K1 + p.K2) / kTileK, 1, true, 16}}, 5.f);
     if (plan.splits[0] == 1) {
@@ -555,7 +571,7 @@ GemmProblem problem(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int 
     const EpiStoreF32 epi{parts.at, p.N, (int64_t)n, 0, nullptr, FinalPanel{}};
     if (plan.kW == kSmallTile) launch_gemm_tile<kRowsByK, kRowsByK, kSmallTile>(p, epi, s);
     else launch_gemm_tile<kRowsByK, kRowsByK, kLargeTile>(p, epi, s);
-    launch_sum_bf16(parts.at, p.splits, n, C, s);
+    launch_sum_bf16(parts.at, p.splits, n, C, LiveTiles{p.kept, p.kept_max, p.rows_per_kept, p.row_offset, p.N}, s);
     return PCM_OK;
 }
 
@@ -738,7 +754,7 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                     if (!w.parts.hold(p.splits * n)) return PCM_EWORKSPACE;
                     launch_gemm_group(plan.level[0].kW, s, da,
                                       GemmJob<kKByRows, kKByRows, EpiStoreF32>{p, EpiStoreF32{w.parts.at, V, (int64_t)n, 0, nullptr, FinalPanel{}}, 0});
-                    launch_sum_bf16(w.parts.at, p.splits, n, w.G, s);
+                    launch_sum_bf16(w.parts.at, p.splits, n, w.G, LiveTiles{}, s);
                 }
             } else {
                 StageTimer t(ST_GEMM_DA, s);

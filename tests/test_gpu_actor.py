@@ -783,3 +783,31 @@ def test_bf16_composed_head_too_wide_for_parts(pcm, ff):
     pr = make_problem(cfg, wstd=0.6 / np.sqrt(256), margin=0.08, kept=kept, old_rel=0.1, eps=(0.2, 0.4))
     ref, got = run_both(pcm, pr, eps=(0.2, 0.4), torch_dtype=torch.bfloat16, max_kept=5, composed_head=True)
     check(ref, got, BF16_TOL, len(ref["rows"]), stats_tol=5e-2)
+
+
+@pytest.mark.parametrize("d,ff,n_kept,max_kept,options", [
+    (256, 2560, 2, 60, {}),                               # down projection in parts, one live row tile of fourteen
+    (256, 2560, 2, 60, dict(composed_head=True)),
+    (512, 768, 6, 30, dict(dense_backward=True)),         # two of seven, no parts
+    (256, 2560, 9, 60, dict(panel_rows=1792)),            # both of them, the second panel without a live row
+])
+def test_bf16_rows_behind_the_list_are_read_by_nothing(pcm, d, ff, n_kept, max_kept, options):
+    """Rows of the buffers behind the list's last row tile are neither written nor read: with scratch that holds NaN everywhere
+    a list far shorter than its buffer gives the results of the checker, and the bits of a call on clean scratch."""
+    from paper_2605_16154_amd import binding
+    cfg = CONFIGS["cfg2"].with_(n_groups=1, G=4, N=16, K=4, B=4, d=d, ff=ff, seed=97)
+    kept = np.arange(1, 60, 6, dtype=np.int32)[:n_kept]
+    pr = make_problem(cfg, wstd=1.1 / np.sqrt(d), margin=0.08, kept=kept, old_rel=0.1, eps=(0.2, 0.4))
+    kw = dict(eps=(0.2, 0.4), torch_dtype=torch.bfloat16, max_kept=max_kept, **options)
+    ref, clean = run_both(pcm, pr, **kw)
+    n = len(ref["rows"])
+    for want in (dict(), dict(want_grads=False, want_dX=False)):
+        assert binding._workspaces
+        for ws in binding._workspaces.values():
+            ws.fill_(0xFF)                                # NaN as bf16, fp32 and fp64
+        _, got = run_both(pcm, pr, **kw, **want)
+        if not want:
+            check(ref, got, BF16_TOL, n, stats_tol=5e-2)
+            for k in GRADS:
+                assert np.array_equal(got[k], clean[k]), k
+        assert np.array_equal(got["logp"][:n], clean["logp"][:n]) and got["loss"][0] == clean["loss"][0]
