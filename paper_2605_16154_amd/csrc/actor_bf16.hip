@@ -356,12 +356,15 @@ constexpr int64_t kApartRows = 8192;
 // with many rounds that is little, and where the products meet the workgroups of an XCD no longer walk through the same
 // panels in step.  Whole steps at 4096 -> 11008, every row, apart / shared: 672 tiles 6340 / 6240 us, 1344 12,625 / 12,380,
 // 2016 18,370 / 18,800, 2688 24,715 / 24,960; unmasked, panels of 3584, 129.4 / 130.9 ms.  (dWg and dWu in front where their
-// reductions are the longer: 133.5 ms.)
+// reductions are the longer: 133.5 ms.)  The composed evaluation, one panel whatever the batch, all products
+// of the levels shared / apart beyond the line: 2688 tiles 17,760 / 17,520 us, 5376 35,510 / 34,550; at 2048 -> 5632 2688 tiles
+// 10,710 / 10,415, 5376 21,260 / 20,485.
 constexpr int64_t kGroupTiles = 6 * 256;
 
 // How the backward products of a panel are launched.
 struct BackwardPlan {
-    // as written: {dy, dWo}, then {da, dWd}, then {dX, dWg and dWu}; composed: {da, G}, then {dX, dWg and dWu, dWo, dWd}
+    // as written: {dy, dWo}, then {da, dWd}, then {dX, dWg and dWu}; composed: {da, G}, then {dX, dWg and dWu, dWo, dWd}, where not
+    // grouped dWg, dWu, {dWo, dWd}, dX
     GroupPlan level[3];
     bool group[3];
     int split_o, split_d, split_gu, split_G;
@@ -371,12 +374,17 @@ BackwardPlan plan_backward(const ActorShape& sh, int64_t Rp, bool composed, bool
     const int rows = (int)(Rp / kTileK), by_d = sh.d / kTileK, by_ff = sh.ff / kTileK, by_V = sh.V / kTileK;
     BackwardPlan b{};
     if (composed) {
+        b.group[0] = b.group[2] = Rp / kTileM * (d / kTileN) <= kGroupTiles;
         b.level[0] = plan_group<2>({{Rp, ff, by_V, 1, false}, {ff, V, rows, 1, true}}, 2.f);
-        b.level[2] = plan_group<4>({{Rp, d, 2 * by_ff, 1, false}, {d, ff, rows, 2, true}, {d, V, by_ff, 1, true}, {ff, d, by_V, 1, false}}, 2.f);
-        b.split_G = b.level[0].splits[1];
-        b.split_o = b.level[2].splits[2];
+        if (b.group[2]) {
+            b.level[2] = plan_group<4>({{d, V, by_ff, 1, true}, {ff, d, by_V, 1, false}, {Rp, d, 2 * by_ff, 1, false}, {d, ff, rows, 2, true}}, 2.f);
+            b.split_gu = b.level[2].splits[3];
+        } else {
+            b.level[2] = plan_group<2>({{d, V, by_ff, 1, true}, {ff, d, by_V, 1, false}}, 2.f);
+        }
+        b.split_G = b.group[0] ? b.level[0].splits[1] : pick_splits((int)(ff / kTileM), rows);
+        b.split_o = b.level[2].splits[0];
         b.split_d = 1;
-        b.group[0] = b.group[2] = true;
     } else {
         b.level[0] = plan_group<2>({{Rp, d, by_V, 1, false}, {d, V, rows, 1, true}}, 2.f);
         b.level[1] = plan_group<2>({{Rp, ff, by_d, 1, false}, {ff, d, rows, 1, true}}, 2.f);
@@ -386,9 +394,9 @@ BackwardPlan plan_backward(const ActorShape& sh, int64_t Rp, bool composed, bool
         b.group[2] = Rp / kTileM * (d / kTileN) <= kGroupTiles;
         b.split_o = b.level[0].splits[1];
         b.split_d = b.level[1].splits[1];
+        b.split_gu = b.level[2].splits[1];
         if (!b.group[1]) b.split_d = pick_splits((int)(ff / kTileM * (d / kTileN)), rows);
     }
-    b.split_gu = b.level[2].splits[1];
     if (!b.group[2]) b.split_gu = pick_splits((int)(d / kTileM * (ff / kTileN)), rows);
     return b;
 }
@@ -739,29 +747,40 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
         const EpiStoreBf16 store_X{dX, d, (int)(rows_left < Mp ? rows_left : Mp)};
         const EpiSwigluBackward<true> swiglu_listed{w.fu, w.fv, ff, w.live_idx, du, dv};
         const EpiSwigluBackward<false> swiglu{w.fu, w.fv, ff, nullptr, nullptr, nullptr};   // fu <- du, fv <- dv
+        auto weights_apart = [&] {
+            StageTimer t(ST_GEMM_DWG_DWU, s);
+            launch_gemm<kKByRows, kKByRows>(dWgu.p, dWgu.epi[0], s);
+            dWgu.p.B = dWgu.p.B2 = dv;
+            launch_gemm<kKByRows, kKByRows>(dWgu.p, dWgu.epi[1], s);
+        };
+        auto rows_apart = [&] {
+            StageTimer t(ST_GEMM_DX, s);
+            if (listed) launch_row_gemm(pX, scatter_X, s);
+            else launch_row_gemm(pX, store_X, s);
+        };
         if (io.composed) {      // one panel: nothing to add to
             // da = dz W_do^T, and G = a^T dz [ff, V] over the kept rows, rounded to bf16 as the operand of two products below
             const GemmProblem pa = problem(w.dz, V, w.Wdo, V, Mp, ff, V, kr, kRowsAreM);
             const GemmJob<kRowsByK, kRowsByK, EpiSwigluBackward<false>> da{pa, swiglu, 0};
             if (grads) {
-                StageTimer t(ST_GEMM_DA, s);
                 GemmProblem p = problem(w.a, ff, w.dz, V, ff, V, Mp, kr, kRowsAreK);
-                p.splits = plan.split_G;
                 const size_t n = (size_t)ff * V;
-                if (p.splits == 1) {         // wide enough by itself (and wider than the parts that there is room for)
+                if (!plan.group[0]) {
+                    rc = launch_reduction_bf16<kKByRows, kKByRows>(p, w.G, w.parts, ST_GEMM_DWD, s);
+                    if (rc != PCM_OK) return rc;
+                    StageTimer t(ST_GEMM_DA, s);
+                    launch_row_gemm(pa, swiglu, s);
+                } else if (plan.split_G == 1) {   // wide enough by itself (and wider than the parts that there is room for)
+                    StageTimer t(ST_GEMM_DA, s);
                     launch_gemm_group(plan.level[0].kW, s, da, GemmJob<kKByRows, kKByRows, EpiStoreBf16>{p, EpiStoreBf16{w.G, V, ff}, 0});
                 } else {
+                    StageTimer t(ST_GEMM_DA, s);
+                    p.splits = plan.split_G;
                     if (!w.parts.hold(p.splits * n)) return PCM_EWORKSPACE;
                     launch_gemm_group(plan.level[0].kW, s, da,
                                       GemmJob<kKByRows, kKByRows, EpiStoreF32>{p, EpiStoreF32{w.parts.at, V, (int64_t)n, 0, nullptr, FinalPanel{}}, 0});
                     launch_sum_bf16(w.parts.at, p.splits, n, w.G, LiveTiles{}, s);
                 }
-            } else {
-                StageTimer t(ST_GEMM_DA, s);
-                launch_row_gemm(pa, swiglu, s);
-            }
-            if (grads) {
-                StageTimer t(ST_GEMM_DX, s);
                 for (int q = 0; q < 2; ++q)
                     dWgu.epi[q] = reduction_epilogue(dWgu.p, plan.split_gu, q ? io.dWu : io.dWg, q ? w.parts_u : w.parts_g, false, SumsqTarget{}, sums);
                 GemmProblem po = problem(Wd, d, w.G, V, d, V, ff, all_rows, kRowsUnused);                        // dWo = Wd^T G
@@ -769,11 +788,24 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                 const GemmJob<kKByRows, kKByRows, EpiStoreF32> dWo{po, eo, 0};
                 const GemmJob<kRowsByK, kRowsByK, EpiStoreF32> dWd{problem(w.G, V, Wo, V, ff, d, V, all_rows, kRowsUnused),   // dWd = G Wo^T
                                                                    EpiStoreF32{io.dWd, d, 0, 0, nullptr, FinalPanel{}}, 0};
-                if (dX) launch_gemm_group(plan.level[2].kW, s, GemmJob<kRowsByK, kRowsByK, EpiStoreBf16>{pX, store_X, 0}, dWgu, dWo, dWd);
-                else launch_gemm_group(plan.level[2].kW, s, dWgu, dWo, dWd);
+                if (!plan.group[2]) {
+                    weights_apart();
+                    {
+                        StageTimer t(ST_GEMM_DWD, s);
+                        launch_gemm_group(plan.level[2].kW, s, dWo, dWd);
+                    }
+                    if (dX) rows_apart();
+                } else {
+                    StageTimer t(ST_GEMM_DX, s);
+                    if (dX) launch_gemm_group(plan.level[2].kW, s, GemmJob<kRowsByK, kRowsByK, EpiStoreBf16>{pX, store_X, 0}, dWgu, dWo, dWd);
+                    else launch_gemm_group(plan.level[2].kW, s, dWgu, dWo, dWd);
+                }
             } else {
-                StageTimer t(ST_GEMM_DX, s);
-                launch_row_gemm(pX, store_X, s);
+                {
+                    StageTimer t(ST_GEMM_DA, s);
+                    launch_row_gemm(pa, swiglu, s);
+                }
+                rows_apart();
             }
         } else {
             GemmProblem py = problem(w.dz, V, Wo, V, Mp, d, V, br, kRowsAreM);                                   // dy = dz Wo^T
@@ -795,9 +827,7 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                     if (listed) launch_row_gemm(pa, swiglu_listed, s);
                     else launch_row_gemm(pa, swiglu, s);
                 }
-                StageTimer t(ST_GEMM_DX, s);
-                if (listed) launch_row_gemm(pX, scatter_X, s);
-                else launch_row_gemm(pX, store_X, s);
+                rows_apart();
                 continue;
             }
             const EpiStoreF32 eo = reduction_epilogue(po, plan.split_o, io.dWo, w.parts_o, !first, sq[3], sums);
@@ -828,17 +858,8 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
                 else if (listed) launch_gemm_group(plan.level[2].kW, s, GemmJob<kRowsByK, kRowsByK, EpiScatterBf16>{pX, scatter_X, 0}, dWgu);
                 else launch_gemm_group(plan.level[2].kW, s, GemmJob<kRowsByK, kRowsByK, EpiStoreBf16>{pX, store_X, 0}, dWgu);
             } else {
-                {
-                    StageTimer t(ST_GEMM_DWG_DWU, s);
-                    launch_gemm<kKByRows, kKByRows>(dWgu.p, dWgu.epi[0], s);
-                    dWgu.p.B = dWgu.p.B2 = dv;
-                    launch_gemm<kKByRows, kKByRows>(dWgu.p, dWgu.epi[1], s);
-                }
-                if (dX) {
-                    StageTimer t(ST_GEMM_DX, s);
-                    if (listed) launch_row_gemm(pX, scatter_X, s);
-                    else launch_row_gemm(pX, store_X, s);
-                }
+                weights_apart();
+                if (dX) rows_apart();
             }
         }
         if (grads && row0 + w.Rp < w.Mp) {      // the last panel's sums go with the loss

@@ -811,3 +811,21 @@ def test_bf16_rows_behind_the_list_are_read_by_nothing(pcm, d, ff, n_kept, max_k
             for k in GRADS:
                 assert np.array_equal(got[k], clean[k]), k
         assert np.array_equal(got["logp"][:n], clean["logp"][:n]) and got["loss"][0] == clean["loss"][0]
+
+
+@pytest.mark.parametrize("max_kept", [436, 441])
+def test_bf16_composed_head_over_a_tall_buffer(pcm, max_kept):
+    """Up to 1536 tiles of dX the products of a level share a launch (96 row tiles at this width), beyond that they have their
+    own; the list covers two row tiles."""
+    cfg = CONFIGS["cfg2"].with_(n_groups=1, G=4, N=16, K=4, B=4, d=4096, ff=256, seed=98)
+    kept = np.arange(2, 60, 6, dtype=np.int32)[:9]
+    pr = make_problem(cfg, wstd=0.02, margin=0.08, kept=kept, old_rel=0.1, eps=(0.2, 0.4))
+    kw = dict(eps=(0.2, 0.4), torch_dtype=torch.bfloat16, max_kept=max_kept, composed_head=True)
+    ref, got = run_both(pcm, pr, **kw)
+    n = len(ref["rows"])
+    check(ref, got, BF16_TOL, n, stats_tol=5e-2)
+    _, rows_only = run_both(pcm, pr, want_grads=False, **kw)
+    assert np.array_equal(rows_only["dX"][:n], got["dX"][:n])
+    _, weights_only = run_both(pcm, pr, want_dX=False, **kw)
+    for k in GRADS:
+        assert np.array_equal(weights_only[k], got[k]), k
