@@ -55,12 +55,13 @@ struct ActorIO {
 struct RowMeta {
     uint8_t* token;    // [rows_pad] target bin (clamped to V-1)
     float* logp_old;   // [rows_pad]
-    float* adv;        // [rows_pad] advantage of the row's trajectory; 0 for padding rows
+    float* adv;        // [rows_pad] advantage of the row's trajectory; 0 from the last live row to the end of its tile of 256
 };
 
-// Per-row results of the loss stage, reduced in a fixed order afterwards.
+// Per-row results of the loss stage, reduced in a fixed order afterwards.  Like the arrays above they are written up to the end
+// of the last live row's tile; what lies behind it is neither written nor read.
 struct RowOut {
-    float* term;       // [rows_pad] min(rho A, clip(rho) A); 0 for padding rows
+    float* term;       // [rows_pad] min(rho A, clip(rho) A); 0 behind the last live row
     float* ratio;      // [rows_pad]
     float* dlogp;      // [rows_pad] logp_old - logp
     uint8_t* clipped;  // [rows_pad] 1 if the row's gradient is cut by the clip

@@ -17,8 +17,9 @@
 // columns so that the activation can be fused).  The weight-gradient products reduce over the row
 // dimension and read the activations as they are, through the GEMM's LDS transpose reads.
 //
-// Rows are padded to a multiple of 256; padding rows are zero with zero advantage, so they
-// contribute nothing to any output.
+// Buffers are padded to a multiple of 256 rows.  The rows from the last live one to the end of its
+// row tile are zero with zero advantage, so they contribute nothing to any output; rows behind that
+// tile are neither written nor read, by any launch.
 //
 // Backward over the rows that carry a gradient: a row whose ratio the clip cuts (or whose advantage or weight is
 // zero) has an all-zero row of dz, hence of dy, du, dv and dX, and adds nothing to a weight gradient.  After the loss
@@ -349,16 +350,23 @@ GroupPlan plan_group(const GroupShape (&jobs)[kN], float us_sum) {
 // 1578 / 1454; at 4096 -> 11008 4704 rows, three quarters live, 2679 / 2530, 10,752 with a chunk ratio 6758 / 6500.
 //
 // Rows of a panel up to which the listed rows of a, du and dv have buffers of their own, so that dWd, which reads the first,
-// and da, which writes the others, may run side by side.
+// and da, which writes the others, may run side by side.  What that saves shrinks as the launches grow, while the two further
+// buffers of ff columns grow with them.  Whole steps, half to two thirds of the rows listed, apart / side by side: 2296 rows of
+// 512 -> 768 88.8 / 81.0 us, of 1024 -> 2816 219.6 / 186.7, of 4096 -> 11008 1401 / 1332; 4480 105 / 98.9, 344 / 318, 2227 / 2225;
+// 8064 152 / 144, 449 / 454, 3702 / 3717; 8960 162 / 158, 493 / 501, 4176 / 4154; 16,128 253 / 234, 739 / 744, 7115 / 7162; 32,256
+// 397 / 394, 1372 / 1365, 14,210 / 14,080.
 constexpr int64_t kApartRows = 8192;
 
 // Large tiles of dX up to which it shares a launch with dWg and dWu.  What sharing saves is the part-filled last round of each;
 // with many rounds that is little, and where the products meet the workgroups of an XCD no longer walk through the same
-// panels in step.  Whole steps at 4096 -> 11008, every row, apart / shared: 672 tiles 6340 / 6240 us, 1344 12,625 / 12,380,
-// 2016 18,370 / 18,800, 2688 24,715 / 24,960; unmasked, panels of 3584, 129.4 / 130.9 ms.  (dWg and dWu in front where their
-// reductions are the longer: 133.5 ms.)  The composed evaluation, one panel whatever the batch, all products
-// of the levels shared / apart beyond the line: 2688 tiles 17,760 / 17,520 us, 5376 35,510 / 34,550; at 2048 -> 5632 2688 tiles
-// 10,710 / 10,415, 5376 21,260 / 20,485.
+// panels in step.  Whole steps, every row, apart / shared, us:
+//   4096 -> 11008:  672 tiles 6340 / 6240, 1344 12,625 / 12,380, 2016 18,370 / 18,800, 2688 24,715 / 24,960; unmasked, panels of
+//                   3584, 129.4 / 130.9 ms (dWg and dWu in front where their reductions are the longer: 133.5 ms)
+//   4096 -> 2048:   672 1423 / 1369, 1344 2792 / 2750, 1792 3549 / 3488
+//   2048 -> 5632:   672 3635 / 3540, 1344 7206 / 7174, 1568 8389 / 8438, 1792 9407 / 9585
+//   8192 -> 8192:   672 4781 / 4748, 1344 9288 / 9425, 1696 11,461 / 11,544, 2016 13,494 / 13,584, 2688 17,988 / 18,144
+// The composed evaluation, one panel whatever the batch, all its levels: 4096 -> 11008 2688 17,520 / 17,760, 5376 34,550 / 35,510;
+// 2048 -> 5632 2688 10,415 / 10,710, 5376 20,485 / 21,260.
 constexpr int64_t kGroupTiles = 6 * 256;
 
 // How the backward products of a panel are launched.

@@ -331,7 +331,10 @@ __global__ __launch_bounds__(256) void scale_rows_f32(float* __restrict__ dz, co
 // and the zeros, six launches against this one: 2072 rows of 512 and 768 16.9 -> 3.5 us, 43,008 rows of 4096 and 11008
 // (24 thousand listed) 429 -> 422 us.
 constexpr int kListThreads = 256, kListWaves = kListThreads / kWave;
-constexpr int kListParts = 4;      // workgroups per block where the blocks are few
+// Workgroups per block where there are no more than two blocks to a CU: the copies of a block are then spread over four.  Whole
+// steps, one / four to a block: 672 rows of 512 -> 768 76.0 / 74.8 us, of 1024 -> 2816 133.9 / 130.5; 2072 of 512 -> 768 81.3 / 80.1,
+// 7616 143.8 / 143.1; beyond the line (about 8000 rows) 8960 161 / 163, 14,336 238 / 239.
+constexpr int kListParts = 4;
 struct ListArgs {
     const uint8_t* clipped;
     const float* adv;
@@ -461,7 +464,7 @@ int launch_live_rows(const ActorShape& sh, const ActorIO& io, const uint8_t* cli
                (int)((int64_t)sh.d * 2 / 16), static_cast<uint4*>(dX), whole, listed, {}, idx, plan, 1};
     for (int q = 0; q < LiveSources::kCount; ++q) p.row_vecs[q] = (int)(row_bytes[q] / 16);
     const int64_t blocks = (rows_pad + 256) / kListBlock;          // those of the panel, and a row tile behind the list
-    if (blocks <= 512) p.parts = kListParts;
+    if (blocks <= 512) p.parts = kListParts;                        // see kListParts
     list_live_rows<<<(unsigned)(blocks * p.parts), kListThreads, 0, s>>>(p);
     return launch_status();
 }

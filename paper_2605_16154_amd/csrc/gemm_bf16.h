@@ -59,8 +59,8 @@ constexpr int kLargeTile = 8, kSmallTile = 4;
 template <int kW> constexpr int kTile = 32 * kW;                     // rows and columns of a workgroup's tile
 template <int kW> constexpr int kWaveRows = 16 * kW;                 // rows and columns of a wavefront's part of it
 // Operand tiles resident or in flight in LDS: five (160 KB, the whole LDS, or 80 KB).  Launches of small tiles with at most one
-// workgroup per CU have the LDS of a second one to spare and keep nine, four steps ahead instead of two: their steps wait for
-// loads that no neighbour covers.  Whole steps with five / nine: 2072 rows of 512 -> 768 80.0 / 78.7 us, composed 1152 of
+// workgroup per CU have the LDS of a second one to spare and, if a workgroup has kDeepSteps steps or more, keep nine, four steps
+// ahead instead of two: their steps wait for loads that no neighbour covers.  Whole steps with five / nine: 2072 rows of 512 -> 768 80.0 / 78.7 us, composed 1152 of
 // 3584 -> 1024 125.5 / 121.2, 1344 of 1024 -> 1024 without gradients 42.3 / 40.2; where more than 256 workgroups run the
 // neighbour is worth more and they keep five.
 constexpr int kRingSlots = 5, kDeepRingSlots = 9;
@@ -453,7 +453,8 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& 
         // exit.  The single barrier sits before the second slice: by then every wavefront has issued all its reads of
         // `sa`, `sb`, so both slots can be refilled, `sa` with the B tile of step + kAhead (during the second slice) and `sb`
         // with the A tile of step + kAhead + 1 (during the next step's first).  At the barrier the next step's tiles must have
-        // landed and only newer ones (of five slots, the newest A tile) may still be in flight.  The body is branch-free: near the end it re-requests tiles that nobody reads.
+        // landed and only newer ones (of five slots, the newest A tile) may still be in flight.  The body is branch-free: near the
+        // end it re-requests tiles that nobody reads.
         //
         // A wavefront issues in order and an MFMA keeps the matrix pipe busy for 16 cycles.  Measured with one wavefront
         // per SIMD: between two MFMAs one scalar instruction, two vector instructions or an LDS read cost nothing, three
@@ -1063,7 +1064,7 @@ inline void launch_gemm_tile(const GemmProblem& p, const Epilogue& epi, hipStrea
     if (kW == kSmallTile && grid <= 256 && steps_per_part(p) >= kDeepSteps) gemm_bf16<Epilogue, kLayA, kLayB, kSmallTile, kDeepRingSlots><<<grid, kGemmThreads, 0, s>>>(p, epi);
     else gemm_bf16<Epilogue, kLayA, kLayB, kW><<<grid, kGemmThreads, 0, s>>>(p, epi);
 }
-// The jobs of a group in one launch on tiles of kW; the longest reductions first.
+// The jobs of a group in one launch on tiles of kW, their workgroups in the order given.
 template <class Job>
 inline int place_job(Job& job, int tile, int first) {
     job.first = first;
