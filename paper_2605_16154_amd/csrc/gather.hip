@@ -56,9 +56,10 @@ __device__ inline void gather_rows(const GatherArgs<Vec>& p, int block) {
             if (id >= 0 && (int64_t)id < (int64_t)p.T * p.N) a = p.adv[id / p.N];
             else id = 0;
             src = (int64_t)id * A + tok;
-            int b = p.tokens[src];
+            const int b = p.tokens[src];                 // all loads before the first store, which might alias them
+            const float logp_old = p.logp_old[src];
             p.meta.token[r] = (uint8_t)(b < p.V ? b : p.V - 1);
-            p.meta.logp_old[r] = p.logp_old[src];
+            p.meta.logp_old[r] = logp_old;
             p.meta.adv[r] = a;
         } else if (r < p.rows_pad) {
             p.meta.token[r] = 0;
