@@ -574,7 +574,8 @@ GemmProblem problem(const bf16* A, int64_t lda, const bf16* B, int64_t ldb, int 
 // 2304 -> 2560 86 / 79.
 // The plan is made for a full buffer, so that a row's bits do not depend on how many others are in the list.  Lists up to a quarter
 // of the buffer would like more parts: plan / that rule before, full and with a quarter of the list: 2296 rows of 1024 -> 11008
-// 194.7 and 108.4 / 199.9 and 120.2 us, 1344 of 2048 -> 5632 124 and 94 / 135 and 88, 5376 of 512 -> 5632 137 and 86 / 145 and 74.
+// 194.7 and 108.4 / 199.9 and 120.2 us, 1344 of 2048 -> 5632 124 and 94 / 135 and 88, 5376 of 512 -> 5632 137 and 86 / 145 and 74
+// (112 rows of those 68 / 54).
 [[nodiscard]] int launch_rows_bf16(GemmProblem p, bf16* C, const SharedParts& parts, hipStream_t s) {
     const GroupPlan plan = plan_group<1>({{p.M, p.N, (p.K1 + p.K2) / kTileK, 1, true, 16}}, 5.f);
     if (plan.splits[0] == 1) {
