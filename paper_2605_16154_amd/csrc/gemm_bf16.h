@@ -60,9 +60,9 @@ template <int kW> constexpr int kTile = 32 * kW;                     // rows and
 template <int kW> constexpr int kWaveRows = 16 * kW;                 // rows and columns of a wavefront's part of it
 // Operand tiles resident or in flight in LDS: five (160 KB, the whole LDS, or 80 KB).  Launches of small tiles with at most one
 // workgroup per CU have the LDS of a second one to spare and, if a workgroup has kDeepSteps steps or more, keep nine, four steps
-// ahead instead of two: their steps wait for loads that no neighbour covers.  Whole steps with five / nine: 2072 rows of 512 -> 768 80.0 / 78.7 us, composed 1152 of
-// 3584 -> 1024 125.5 / 121.2, 1344 of 1024 -> 1024 without gradients 42.3 / 40.2; where more than 256 workgroups run the
-// neighbour is worth more and they keep five.
+// ahead instead of two: their steps wait for loads that no neighbour covers.  Whole steps with five / nine: 2072 rows of
+// 512 -> 768 80.0 / 78.7 us, composed 1152 of 3584 -> 1024 125.5 / 121.2, 1344 of 1024 -> 1024 without gradients 42.3 / 40.2; where
+// more than 256 workgroups run the neighbour is worth more and they keep five.
 constexpr int kRingSlots = 5, kDeepRingSlots = 9;
 template <int kW, int kSlots = kRingSlots> constexpr int kRingBytes = kSlots * kTile<kW> * kTileK * 2;
 // Epilogues pass their results through LDS so that global stores are whole 128-byte lines: each

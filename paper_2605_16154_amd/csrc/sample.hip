@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kCountThreads) void kept_phase_counts(const uint8_t
         auto count_units = [&](auto trajectories) {
             constexpr int kPer = decltype(trajectories)::value;              // of a unit; if several, blocks is 1
             constexpr int kRounds = kPer > 4 ? kPer / 4 : 1;
-            const int64_t units = kPer > 1 ? (T + kPer - 1) / kPer : (int64_t)T * blocks;
+            const int64_t units = kPer > 1 ? ((int64_t)T + kPer - 1) / kPer : (int64_t)T * blocks;
             const int k = lane % (kWave / kPer), row = lane / (kWave / kPer), at = kPer > 1 ? min(k, N - 1) : k;
             for (int64_t u0 = 0; u0 < units; u0 += kCountWaves * kCountUnits) {
                 // trajectory r of the wavefront's unit q is looked after by lane (q kPer + r) modulo 64, once for all lanes of

@@ -793,7 +793,7 @@ def test_bf16_composed_head_too_wide_for_parts(pcm, ff):
 ])
 def test_bf16_rows_behind_the_list_are_read_by_nothing(pcm, d, ff, n_kept, max_kept, options):
     """Rows of the buffers behind the list's last row tile are neither written nor read: with scratch that holds NaN everywhere
-    a list far shorter than its buffer gives the results of the checker, and the bits of a call on clean scratch."""
+    a list far shorter than its buffer gives the results of the oracle, and the bits of a call on clean scratch."""
     from paper_2605_16154_amd import binding
     cfg = CONFIGS["cfg2"].with_(n_groups=1, G=4, N=16, K=4, B=4, d=d, ff=ff, seed=97)
     kept = np.arange(1, 60, 6, dtype=np.int32)[:n_kept]
