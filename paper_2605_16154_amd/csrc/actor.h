@@ -92,12 +92,12 @@ struct TransposeList {
 void launch_transposes(const TransposeList& list, bool stream, hipStream_t s);
 
 // Copies the kept chunks' hidden rows into X [rows_pad, d] (rows from n_kept*A to the end of
-// their tile of 256 are zero-filled, later ones left as they are: nothing reads them) and fills the row metadata.  elem_bytes is 2 (bf16) or 4 (fp32).
+// their tile of 256 are zero-filled, later ones left as they are: nothing reads them) and fills the row metadata (bf16 path).
 // With row_offset > 0 the rows are those of a panel of the batch that starts at that row: X and the metadata
 // arrays are the panel's own, `rows_pad` its height.  The same holds for the two per-chunk-ratio launches below
 // (row_offset a multiple of A, so no chunk straddles two panels).
 // In the same launch: the transposes of `layouts`, and zeros in zero[0 .. n_zero).
-[[nodiscard]] int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void* X, int64_t row_offset, int64_t rows_pad,
+[[nodiscard]] int launch_gather(const ActorShape& sh, const ActorIO& io, void* X, int64_t row_offset, int64_t rows_pad,
                   RowMeta meta, const TransposeList& layouts, double* zero, int n_zero, hipStream_t s);
 
 // Partial sums of squares of the four weight gradients, left by the launches that wrote their final values.
@@ -106,8 +106,8 @@ struct SumsqLists {
     int count[4];
 };
 // Sums of partial products that split reductions left: out = (add: out +) parts[0] + parts[1] + .. in that order (fp32, n
-// floats, parts `stride` floats apart).  With live_row > 0 the sum is one over the rows of the batch, live_row floats each:
-// beyond the live rows rounded up to 128 the parts were not written and out is zero.  With sumsq, on the final panel every workgroup also leaves the sum of the squares of what it wrote in
+// floats, parts `stride` floats apart).  With live_row > 0 it is one over the rows of the batch, live_row floats each, and ends with
+// the row tile of the last live one.  With sumsq, on the final panel every workgroup also leaves the sum of the squares of what it wrote in
 // sumsq[its number within the job].
 struct PartsSum {
     const float* parts;
@@ -137,10 +137,6 @@ struct FinalPanel;
 // (written to every row of the chunk; the term only to its first row).
 [[nodiscard]] int launch_chunk_ratio(const ActorShape& sh, const ActorIO& io, RowMeta meta, RowOut out, int64_t row_offset,
                        int64_t rows_pad, hipStream_t s);
-
-// fp32 path: dz[r, :] = coef[r] * dz[r, :] (+ extra[r, :] if extra is given) for the live rows r (V columns each).
-[[nodiscard]] int launch_scale_rows_f32(const ActorShape& sh, const ActorIO& io, float* dz, const float* extra, const float* coef,
-                          int64_t rows, hipStream_t s);
 
 // Backward pass over the rows that carry a gradient only (bf16 path).  A kernel lists the panel's rows whose factor
 // in dz is non-zero and writes, to device memory, what the backward products then read: their row count and which
@@ -217,7 +213,7 @@ __device__ inline LossRow loss_row(float logp, float logp_old, float adv, float 
 }
 
 // actor_f32.hip / actor_bf16.hip ---------------------------------------------------------------
-size_t actor_f32_workspace_bytes(const ActorShape& sh, bool want_grads);
+size_t actor_f32_workspace_bytes(const ActorShape& sh, bool bwd, bool composed);
 int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t s);
 size_t actor_bf16_workspace_bytes(const ActorShape& sh, bool want_grads, const LossOptions& opt, bool composed);
 int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t s);

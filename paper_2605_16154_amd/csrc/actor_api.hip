@@ -20,7 +20,7 @@ bool shape_valid(const ActorShape& sh) {
 
 namespace {
 size_t workspace_need(const ActorShape& sh, int dtype, bool bwd, const LossOptions& opt, bool composed) {
-    return dtype == PCM_F32 ? actor_f32_workspace_bytes(sh, bwd) : actor_bf16_workspace_bytes(sh, bwd, opt, composed);
+    return dtype == PCM_F32 ? actor_f32_workspace_bytes(sh, bwd, composed) : actor_bf16_workspace_bytes(sh, bwd, opt, composed);
 }
 LossOptions plain_options(float eps_low, float eps_high, float loss_scale) {
     return LossOptions{eps_low, eps_high, loss_scale, 0.f, 0, 0, nullptr, 0, nullptr, 0, nullptr};

@@ -1,291 +1,321 @@
-// fp32 path of the masked GRPO actor step (Eq. 11): fp32 matrix-core products (v_mfma_f32_32x32x2_f32: fp32 operands,
-// products and sums) with the activation fused into their epilogues.
+// fp32 path of the masked GRPO actor step (Eq. 11): fp32 operands, sums and results, on the bf16 matrix cores.
 //
-// This path exists for small heads and for checking the method at fp32 accuracy.  One GEMM kernel template serves all
-// products of the forward and backward pass; reductions over the row dimension (the weight gradients) are split across
-// workgroups into partial products that a second kernel adds in slice order, so the results are the same from run to
-// run (no atomics).  Row tiles beyond the kept count are skipped.
+// Every operand of a product is held as three bf16 matrices whose sum it is exactly (thirds.h); a product of two is six
+// products of such parts, as six segments of one reduction of the bf16 GEMM's main loop, the small ones first (the three left
+// out are below 2^-23 of the whole).  The matrix cores add up 32 products at a time in fp32, so a sum has a thirty-second of
+// the roundings that one by fp32 multiply-adds has.  Errors against 64 bits, root mean square over six inputs each, fp32 matrix
+// instructions / thirds: at 1024 -> 2816 -> 1024 -> 256 log-probabilities 4.8e-7 / 1.7e-7, gradients 4.9e-6 / 1.8e-6; at 256 -> 1024
+// 2.7e-7 / 1.0e-7 and 2.8e-6 / 1.1e-6; at eight further sizes of 169 .. 619 -> 133 .. 2026 every one 0.29 to 0.48 of what it was.
+// (With the six products of every 32 k added up one behind the other the sums had a bias of 1e-7 to 4e-7: the matrix cores cut
+// off what they add; in segments, small ones first, a sixth of the additions do so at full size.)
+// The bf16 matrix cores do 16 times the multiply-adds of the fp32 ones, so six products take 3/8 of the time at the same
+// share of their rates.  Steps: 10,752 rows of 1024 -> 2816 -> 1024 -> 256, a quarter of them not kept, 4.00 -> 2.45 ms; 5376 of
+// 256 -> 1024 -> 256 -> 256 363 -> 316 us; 360 of 473 -> 333 -> 473 -> 512 185 -> 143, 1440 of 619 -> 1302 -> 619 -> 256 413 -> 243,
+// 8960 of 103 -> 149 -> 103 -> 256, composed, where most of the padded tiles is padding, 171 -> 164; faster at 16 of 16 sizes.
+//
+// Who reads a matrix only as an operand gets the thirds alone: X, a, y, dz, dy, du and dv, and the weights, are never stored
+// in fp32.  Wg and Wu are one matrix with columns in blocks of 32 of each in turn, so that a wavefront holds a gate column and
+// its up column, and so are u and v, and du and dv.  Operands are padded with zeros to whole tiles in the workspace, so any
+// size runs; results are written as far as they reach.
+//
+// Products of one dependency level share a launch and long reductions are split into parts that a later launch adds up in
+// order (no atomics), as in the bf16 path.  Row tiles beyond the kept count are skipped.
 #include <algorithm>
 
-#include "actor.h"
+#include "gemm_bf16.h"
+#include "thirds.h"
 
 namespace pcm {
 namespace {
 
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
 constexpr int kThreads = 256;
-constexpr int kStep = 16;           // reduction steps are 16 wide
-constexpr int kRowTile = 128;       // live rows are rounded up to this: the tallest row tile
 
-// How an operand of C[m, n] = sum_k A(m, k) B(n, k) is stored (ld = distance between rows of the storage).
-enum Layout : int { kRowsByK = 0, kKByRows = 1 };
-
-struct F32Problem {
-    const float *A, *B;
-    const float *A2, *B2;   // operands of a second product of the same sizes and layouts (see Second)
-    int64_t lda, ldb;
-    int M, N, K;
-    int k_per_split;        // slice blockIdx.z covers [z, z + 1) * k_per_split of the reduction
-    int tiles_n;            // column tiles of one right operand
-    // rows of the batch: kLiveM: row tiles beyond the live rows (rounded up to kRowTile) are skipped; kLiveK: the
-    // reduction ends with the live rows
-    const int32_t* n_kept;
-    int max_chunks, rows_per_chunk, live;
-};
-enum LiveRows : int { kLiveUnused = 0, kLiveM = 1, kLiveK = 2 };
-
-// A second product in the launch: kNone; kPair: column tiles tiles_n .. 2 tiles_n - 1 are those of A B2; kInterleaved: the
-// columns are 32 of B, the same 32 of B2, and so on, so that a wavefront holds both of a pair; kSum: slice 0 is A B,
-// slice 1 A2 B2, to be added as the slices of a split reduction are.
-enum Second : int { kNone = 0, kPair = 1, kInterleaved = 2, kSum = 3 };
-
-// Where a lane's accumulators belong: register e of tile (i, j) is row row(i, e), column col(j) of the product.
-// (kInterleaved: col(j) is the column of B for even j and of B2 for odd j.)
-template <int kI, int kJ, int kSecond>
-struct F32Coord {
-    int m0, n0, wm, wn, lane, split, right;
-    __device__ int row(int i, int e) const { return m0 + (wm * kI + i) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); }
-    __device__ int col(int j) const {
-        if (kSecond == kInterleaved) return n0 / 2 + wn * (kJ / 2) * 32 + (j / 2) * 32 + (lane & 31);
-        return n0 + (wn * kJ + j) * 32 + (lane & 31);
-    }
-};
-
-__device__ inline int64_t live_rows_of(const F32Problem& p) { return live_rows(p.n_kept, p.max_chunks, p.rows_per_chunk); }
-
-// One tile of 64 kI x 64 kJ per workgroup of four wavefronts (2 x 2), each 32 kI x 32 kJ.  Steps are 16 wide; operand
-// tiles are double-buffered in LDS as [k][row] (a lane feeds one row and every second k, so a fragment is one 4-byte read
-// of consecutive rows) and the next step's values are on the way to registers meanwhile.  Bound by the matrix pipe: an
-// MFMA occupies it for 64 cycles and needs one 4-byte read per operand (counters of the large products: matrix pipes busy
-// 75 % of the cycles, LDS 17 - 38 %; 51 - 66 % and 26 - 34 % in those too short to fill the chip throughout).  128 x 128 tiles for the reuse in L2, smaller
-// ones where those share out badly (see plan_tiles).  Steps of 32 and values fetched two steps ahead were no faster.
-// kVec: 16-byte loads (sizes and strides multiples of four floats, aligned pointers); otherwise single floats.
-//
-// Measured (gate and up projection with the activation, 8192 x 2816 x 1024 each, 94 GFLOP): 0.87 - 0.92 ms = 105 TFLOP/s
-// of a nominal 157, where the vector-ALU kernel of 64 x 64 tiles it replaces and its separate activation took 2.5 ms.
-// Whole step at 10752 rows, 1024 -> 2816 -> 1024 -> 256 (24 % of the rows not kept): 11.0 -> 3.7 ms; at 5376 rows,
-// 256 -> 1024 -> 256 -> 256: 1.17 -> 0.39 ms.  The MFMA adds its products one k after the other, as the vector kernel
-// did, and no sum is longer than there: the outputs of both steps are the same to the last bit.
-template <int kI, int kJ, int kLayA, int kLayB, int kSecond, bool kVec, class Epilogue>
-__global__ __launch_bounds__(kThreads) void gemm_f32(F32Problem p, Epilogue epi) {
-    constexpr int TM = 64 * kI, TN = 64 * kJ;
-    constexpr int SA = TM + 4, SB = TN + 4;                     // floats between k-rows
-    __shared__ __attribute__((aligned(16))) float As[2][kStep * SA], Bs[2][kStep * SB];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int right = kSecond == kPair ? (int)blockIdx.x / p.tiles_n : 0;
-    const int m0 = blockIdx.y * TM, n0 = ((int)blockIdx.x - right * p.tiles_n) * TN;
-    const F32Coord<kI, kJ, kSecond> tc{m0, n0, wave >> 1, wave & 1, lane, (int)blockIdx.z, right};
-    int K = p.K;
-    if (p.live == kLiveM && m0 >= (live_rows_of(p) + kRowTile - 1) / kRowTile * kRowTile) return;   // the same rows whatever the tile
-    if (p.live == kLiveK) K = (int)min((int64_t)K, live_rows_of(p));
-    const bool second_sum = kSecond == kSum && blockIdx.z == 1;
-    const int k_first = kSecond == kSum ? 0 : (int)blockIdx.z * p.k_per_split, k_last = min(K, k_first + p.k_per_split);
-    const int steps = k_last > k_first ? (k_last - k_first + kStep - 1) / kStep : 0;
-
-    // A tile of kT rows x 16 k as 4-float pieces: [rows][K] four k of a row, [K][rows] four rows of a k.  Rows beyond the
-    // matrix are read as its last ones (whatever they give is not stored); only a step that ends beyond the reduction
-    // needs a check per piece.
-    constexpr int kPiecesA = TM * kStep / 4 / kThreads, kPiecesB = TN * kStep / 4 / kThreads;
-    f32x4 ra[kPiecesA], rb[kPiecesB];
-    const float *pa[kPiecesA], *pb[kPiecesB];                    // this thread's pieces of the next step to fetch
-    int ea[4], eb[4];                                            // element offsets within a piece (not kVec)
-    auto row_in = [](int row, int rows) { return kVec ? min(row, (rows + 3) / 4 * 4 - 4) : min(row, rows - 1); };
-    auto point_at = [&](const float* A, const float* B, const float* B_odd, int k0) __attribute__((always_inline)) {
+__device__ __forceinline__ void split4(f32x4 v, bf16x4 (&out)[3]) {
+    const float x[4] = {v[0], v[1], v[2], v[3]};
+    uint32_t part[3][2];
+    split_in_three(x, part);
 #pragma unroll
-        for (int q = 0; q < kPiecesA; ++q) {
-            const int piece = tid + q * kThreads;
-            const int row = kLayA == kRowsByK ? min(m0 + piece / 4, p.M - 1) : row_in(m0 + piece % (TM / 4) * 4, p.M);
-            const int k = k0 + (kLayA == kRowsByK ? piece % 4 * 4 : piece / (TM / 4));
-            pa[q] = A + (kLayA == kRowsByK ? (int64_t)row * p.lda + k : (int64_t)k * p.lda + row);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) ea[e] = kLayA == kRowsByK ? e : min(row + e, p.M - 1) - row;
-        }
-#pragma unroll
-        for (int q = 0; q < kPiecesB; ++q) {
-            const int piece = tid + q * kThreads;
-            const int c = kLayB == kRowsByK ? piece / 4 : piece % (TN / 4) * 4;      // column within the tile
-            const int k = k0 + (kLayB == kRowsByK ? piece % 4 * 4 : piece / (TN / 4));
-            const int n = kSecond == kInterleaved ? n0 / 2 + c / 64 * 32 + c % 32 : n0 + c;
-            const float* const from = kSecond == kInterleaved && (c & 32) ? B_odd : B;
-            const int row = kLayB == kRowsByK ? min(n, p.N - 1) : row_in(n, p.N);
-            pb[q] = from + (kLayB == kRowsByK ? (int64_t)row * p.ldb + k : (int64_t)k * p.ldb + row);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) eb[e] = kLayB == kRowsByK ? e : min(row + e, p.N - 1) - row;
-        }
-    };
-    const int64_t inc_a = kLayA == kRowsByK ? kStep : kStep * p.lda, inc_b = kLayB == kRowsByK ? kStep : kStep * p.ldb;
-    auto load4 = [](const float* at, const int (&e)[4]) __attribute__((always_inline)) -> f32x4 {
-        if (kVec) return *reinterpret_cast<const f32x4*>(at);
-        return f32x4{at[e[0]], at[e[1]], at[e[2]], at[e[3]]};
-    };
-    auto load4_checked = [](const float* at, const int (&e)[4], bool k_is_within, int left) __attribute__((always_inline)) -> f32x4 {
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};                          // left: k from the piece's first one to the end
+    for (int t = 0; t < 3; ++t) out[t] = __builtin_bit_cast(bf16x4, (uint64_t)part[t][0] | (uint64_t)part[t][1] << 32);
+}
+// Four consecutive columns n .. n + 3 of a row with N of them, as far as they are there.
+__device__ __forceinline__ void store4(float* row, int n, int N, f32x4 v) {
+    if (n + 3 < N) {
+        *reinterpret_cast<f32x4_any*>(row + n) = v;
+    } else {
 #pragma unroll
         for (int t = 0; t < 4; ++t)
-            if ((k_is_within ? t : 0) < left) v[t] = at[e[t]];
-        return v;
-    };
-    auto fetch = [&](int s) __attribute__((always_inline)) {
-        const int left = k_last - k_first - s * kStep;
-        if (left >= kStep) {                                     // uniform
-#pragma unroll
-            for (int q = 0; q < kPiecesA; ++q) ra[q] = load4(pa[q], ea);
-#pragma unroll
-            for (int q = 0; q < kPiecesB; ++q) rb[q] = load4(pb[q], eb);
-        } else {
-#pragma unroll
-            for (int q = 0; q < kPiecesA; ++q) {
-                const int piece = tid + q * kThreads;
-                ra[q] = load4_checked(pa[q], ea, kLayA == kRowsByK, left - (kLayA == kRowsByK ? piece % 4 * 4 : piece / (TM / 4)));
-            }
-#pragma unroll
-            for (int q = 0; q < kPiecesB; ++q) {
-                const int piece = tid + q * kThreads;
-                rb[q] = load4_checked(pb[q], eb, kLayB == kRowsByK, left - (kLayB == kRowsByK ? piece % 4 * 4 : piece / (TN / 4)));
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < kPiecesA; ++q) pa[q] += inc_a;
-#pragma unroll
-        for (int q = 0; q < kPiecesB; ++q) pb[q] += inc_b;
-    };
-    auto stash = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int q = 0; q < kPiecesA; ++q) {
-            const int piece = tid + q * kThreads;
-            if (kLayA == kRowsByK) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) As[buf][(piece % 4 * 4 + e) * SA + piece / 4] = ra[q][e];
-            } else {
-                *reinterpret_cast<f32x4*>(&As[buf][piece / (TM / 4) * SA + piece % (TM / 4) * 4]) = ra[q];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < kPiecesB; ++q) {
-            const int piece = tid + q * kThreads;
-            if (kLayB == kRowsByK) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Bs[buf][(piece % 4 * 4 + e) * SB + piece / 4] = rb[q][e];
-            } else {
-                *reinterpret_cast<f32x4*>(&Bs[buf][piece / (TN / 4) * SB + piece % (TN / 4) * 4]) = rb[q];
-            }
-        }
-    };
-
-    f32x16 acc[kI][kJ];
-#pragma unroll
-    for (int i = 0; i < kI; ++i)
-#pragma unroll
-        for (int j = 0; j < kJ; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    if (steps > 0) {                                             // uniform over the workgroup
-        // Fragments are read one group of MFMAs (two k) ahead, the values fetched at the start of a step go to the other
-        // LDS buffer behind the sixth group, and the barrier that hands it over stands before the last, behind which the
-        // first fragments of the next step are read: the matrix pipe has work through each of these waits.
-        point_at(second_sum ? p.A2 : p.A, right || second_sum ? p.B2 : p.B, p.B2, k_first);
-        fetch(0);
-        stash(0);
-        __syncthreads();
-        const int a_at = (lane >> 5) * SA + tc.wm * kI * 32 + (lane & 31), b_at = (lane >> 5) * SB + tc.wn * kJ * 32 + (lane & 31);
-        float fa[2][kI], fb[2][kJ];
-        auto read = [&](int set, int buf, int kk) __attribute__((always_inline)) {
-#pragma unroll
-            for (int i = 0; i < kI; ++i) fa[set][i] = As[buf][kk * SA + a_at + i * 32];
-#pragma unroll
-            for (int j = 0; j < kJ; ++j) fb[set][j] = Bs[buf][kk * SB + b_at + j * 32];
-        };
-        read(0, 0, 0);
-        constexpr int kGroups = kStep / 2;
-        for (int s = 0; s < steps; ++s) {
-            const int buf = s & 1;
-            const bool more = s + 1 < steps;
-            if (more) fetch(s + 1);
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) {
-                if (g + 1 < kGroups) read((g + 1) & 1, buf, 2 * (g + 1));
-                else if (more) read(0, buf ^ 1, 0);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int i = 0; i < kI; ++i)
-#pragma unroll
-                    for (int j = 0; j < kJ; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[g & 1][i], fb[g & 1][j], acc[i][j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                if (g == kGroups - 3 && more) stash(buf ^ 1);    // read last in the step before this one
-                if (g == kGroups - 2 && more) __syncthreads();
-            }
-        }
+            if (n + t < N) row[n + t] = v[t];
     }
-    epi(tc, acc, p);
 }
 
-// C (row-major, ldc) = acc; slice z of a split reduction goes to C + z * split_stride, the second product of a pair to
-// C2 (one product: C2 = C).  Skipped tiles are not written.
-struct F32Store {
-    float *C, *C2;
+// ---- epilogues: results go through the wavefront's staging area, as those of the bf16 path do -------------------------
+
+// C = acc as thirds.  Columns up to C.ld (a multiple of a wavefront's), rows below `rows`.
+struct EpiThirds {
+    Thirds C;
+    int rows;
+    template <int kW>
+    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+        constexpr int RW = kWaveRows<kW>, kRow = RW * 2, kStride = 3 * kRow + 16;
+        const int col_base = tc.col0();
+        if (col_base >= C.ld) return;
+        char* const st = wave_stage(tc, lds);
+#pragma unroll
+        for (int i = 0; i < RW / 32; ++i) {                // 32 rows per pass
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+                for (int j = 0; j < kW; ++j) {
+                    bf16x4 part[3];
+                    split4(acc[2 * i + ii][j], part);
+                    char* const at = st + (ii * 16 + (tc.lane & 15)) * kStride + (j * 16 + 4 * (tc.lane >> 4)) * 2;
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(at + t * kRow) = part[t];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            __builtin_amdgcn_wave_barrier();
+            const int row_base = tc.row0() + i * 32;
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                copy_rows_out<32, kRow>(st + t * kRow, kStride, reinterpret_cast<char*>(C.p + t * C.third + (int64_t)row_base * C.ld + col_base),
+                                        C.ld * 2, rows - row_base, tc.lane);
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+};
+
+// C = acc in fp32, M x N with rows ldc apart, of any alignment; part s of a split reduction goes to C + s * split_stride.
+struct EpiFloats {
+    float* C;
     int64_t ldc, split_stride;
-    template <class Coord, int kI, int kJ>
-    __device__ void operator()(const Coord& tc, const f32x16 (&acc)[kI][kJ], const F32Problem& p) const {
-        float* const out = (tc.right ? C2 : C) + tc.split * split_stride;
+    int M, N;
+    template <int kW>
+    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+        constexpr int RW = kWaveRows<kW>, kStride = RW * 4 + 16, kLanesPerRow = RW / 4, kRowsPerPass = 64 / kLanesPerRow;
+        char* const st = wave_stage(tc, lds);
+        float* const out = C + tc.split * split_stride;
+        const int n = tc.col0() + tc.lane % kLanesPerRow * 4;
 #pragma unroll
-        for (int i = 0; i < kI; ++i)
+        for (int i = 0; i < RW / 32; ++i) {                // 32 rows per pass
 #pragma unroll
-            for (int j = 0; j < kJ; ++j)
+            for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int m = tc.row(i, e), n = tc.col(j);
-                    if (m < p.M && n < p.N) out[(int64_t)m * ldc + n] = acc[i][j][e];
-                }
+                for (int j = 0; j < kW; ++j)
+                    *reinterpret_cast<f32x4*>(st + (ii * 16 + (tc.lane & 15)) * kStride + (j * 16 + 4 * (tc.lane >> 4)) * 4) = acc[2 * i + ii][j];
+            __builtin_amdgcn_wave_barrier();
+            const int row0 = tc.row0() + i * 32 + tc.lane / kLanesPerRow;
+#pragma unroll 8
+            for (int q = 0; q < 32 / kRowsPerPass; ++q) {
+                const int row = row0 + q * kRowsPerPass;
+                const f32x4 v = *reinterpret_cast<const f32x4*>(st + (q * kRowsPerPass + tc.lane / kLanesPerRow) * kStride + tc.lane % kLanesPerRow * 16);
+                if (row < M) store4(out + (int64_t)row * ldc, n, N, v);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
     }
 };
 
-// Gate and up projection interleaved: acc[i][even] = u, acc[i][odd] = v of the same columns; a = silu(u) v.
-struct F32SwigluForward {
-    float *u, *v, *a;
-    template <class Coord, int kI, int kJ>
-    __device__ void operator()(const Coord& tc, const f32x16 (&acc)[kI][kJ], const F32Problem& p) const {
+// The same where the product's columns are 32 of one matrix and the same 32 of another in turn (each M x N, rows N apart).
+struct EpiFloatsPair {
+    float* C[2];
+    int64_t split_stride;
+    int M, N;
+    template <int kW>
+    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+        constexpr int RW = kWaveRows<kW>, kStride = RW * 4 + 16, kLanesPerRow = RW / 4, kRowsPerPass = 64 / kLanesPerRow;
+        char* const st = wave_stage(tc, lds);
+        const int packed = tc.col0() + tc.lane % kLanesPerRow * 4, n = packed / 64 * 32 + packed % 32;
+        float* const out = (packed & 32 ? C[1] : C[0]) + tc.split * split_stride;
 #pragma unroll
-        for (int i = 0; i < kI; ++i)
+        for (int i = 0; i < RW / 32; ++i) {                // 32 rows per pass
 #pragma unroll
-            for (int j = 0; j < kJ; j += 2)
+            for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int m = tc.row(i, e), n = tc.col(j);
-                    if (m >= p.M || n >= p.N) continue;
-                    const int64_t at = (int64_t)m * p.N + n;
-                    const float x = acc[i][j][e], y = acc[i][j + 1][e];
-                    u[at] = x;
-                    v[at] = y;
-                    a[at] = x / (1.f + expf(-x)) * y;
-                }
+                for (int j = 0; j < kW; ++j)
+                    *reinterpret_cast<f32x4*>(st + (ii * 16 + (tc.lane & 15)) * kStride + (j * 16 + 4 * (tc.lane >> 4)) * 4) = acc[2 * i + ii][j];
+            __builtin_amdgcn_wave_barrier();
+            const int row0 = tc.row0() + i * 32 + tc.lane / kLanesPerRow;
+#pragma unroll 8
+            for (int q = 0; q < 32 / kRowsPerPass; ++q) {
+                const int row = row0 + q * kRowsPerPass;
+                const f32x4 v = *reinterpret_cast<const f32x4*>(st + (q * kRowsPerPass + tc.lane / kLanesPerRow) * kStride + tc.lane % kLanesPerRow * 16);
+                if (row < M) store4(out + (int64_t)row * N, n, N, v);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
     }
 };
 
-// acc = da.  In place: u <- du = da * v * silu'(u), v <- dv = da * silu(u).
-struct F32SwigluBackward {
-    float *u, *v;
-    template <class Coord, int kI, int kJ>
-    __device__ void operator()(const Coord& tc, const f32x16 (&acc)[kI][kJ], const F32Problem& p) const {
+// Gate and up projection, columns in blocks of 32 of each in turn: a = silu(u) v as thirds, and for a backward pass u and v in
+// fp32 as they are in the product.
+struct EpiGateUp {
+    float* uv;               // [rows, 2 a.ld] or null
+    Thirds a;
+    template <int kW>
+    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+        constexpr int RW = kWaveRows<kW>, CW = RW / 2, kRow = CW * 2;
+        constexpr int kStrideUv = RW * 4 + 16, kStride = 3 * kRow + 16;
+        const int col_base = tc.col0();
+        if (col_base >= 2 * a.ld) return;
+        char* const st = wave_stage(tc, lds);
 #pragma unroll
-        for (int i = 0; i < kI; ++i)
+        for (int i = 0; i < RW / 32; ++i) {                // 32 rows per pass
+            const int64_t row_base = tc.row0() + i * 32;
+            if (uv != nullptr) {
 #pragma unroll
-            for (int j = 0; j < kJ; ++j)
+                for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int m = tc.row(i, e), n = tc.col(j);
-                    if (m >= p.M || n >= p.N) continue;
-                    const int64_t at = (int64_t)m * p.N + n;
-                    const float x = u[at], vv = v[at], g = acc[i][j][e];
-                    const float s = 1.f / (1.f + expf(-x));
-                    u[at] = g * vv * (s * (1.f + x * (1.f - s)));
-                    v[at] = g * (x * s);
+                    for (int j = 0; j < kW; ++j)
+                        *reinterpret_cast<f32x4*>(st + (ii * 16 + (tc.lane & 15)) * kStrideUv + (j * 16 + 4 * (tc.lane >> 4)) * 4) = acc[2 * i + ii][j];
+                __builtin_amdgcn_wave_barrier();
+                copy_rows_out<32, RW * 4>(st, kStrideUv, reinterpret_cast<char*>(uv + row_base * 2 * a.ld + col_base), a.ld * 8, 32, tc.lane);
+                __builtin_amdgcn_wave_barrier();
+            }
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+                for (int q = 0; q < kW / 2; ++q) {
+                    const int j = q / 2 * 4 + q % 2;       // u; v: j + 2
+                    const f32x4 x = acc[2 * i + ii][j], y = acc[2 * i + ii][j + 2];
+                    f32x4 r;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) r[t] = x[t] / (1.f + expf(-x[t])) * y[t];
+                    bf16x4 part[3];
+                    split4(r, part);
+                    char* const at = st + (ii * 16 + (tc.lane & 15)) * kStride + (q * 16 + 4 * (tc.lane >> 4)) * 2;
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(at + t * kRow) = part[t];
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                copy_rows_out<32, kRow>(st + t * kRow, kStride, reinterpret_cast<char*>(a.p + t * a.third + row_base * a.ld + col_base / 2),
+                                        a.ld * 2, 32, tc.lane);
+            __builtin_amdgcn_wave_barrier();
+        }
     }
 };
+
+// acc = da.  du = da v silu'(u) and dv = da silu(u) as thirds, in blocks of 32 columns of each in turn, as u and v are.
+struct EpiGateUpBackward {
+    const float* uv;         // [rows, duv.ld]
+    Thirds duv;
+    template <int kW>
+    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+        constexpr int RW = kWaveRows<kW>, kRow = 2 * RW * 2, kStride = 3 * kRow + 16;
+        const int col_base = 2 * tc.col0();                // packed column of this wavefront's block of 2 RW
+        if (col_base >= duv.ld) return;
+        char* const st = wave_stage(tc, lds);
+        constexpr int kTogether = kW == kLargeTile ? 4 : 4;      // tiles whose u and v are on their way together
+#pragma unroll
+        for (int i = 0; i < kW; ++i) {                     // 16 rows per pass
+            const int64_t row_base = tc.row0() + i * 16;
+            const float* const from = uv + (row_base + (tc.lane & 15)) * duv.ld + col_base + 4 * (tc.lane >> 4);
+            char* const to = st + (tc.lane & 15) * kStride + 4 * (tc.lane >> 4) * 2;
+#pragma unroll
+            for (int j0 = 0; j0 < kW; j0 += kTogether) {
+                f32x4 u[kTogether], v[kTogether];
+#pragma unroll
+                for (int q = 0; q < kTogether; ++q) {
+                    const int at = (j0 + q) / 2 * 64 + (j0 + q) % 2 * 16;
+                    u[q] = *reinterpret_cast<const f32x4*>(from + at);
+                    v[q] = *reinterpret_cast<const f32x4*>(from + at + 32);
+                }
+#pragma unroll
+                for (int q = 0; q < kTogether; ++q) {
+                    const int at = (j0 + q) / 2 * 64 + (j0 + q) % 2 * 16;
+                    f32x4 du, dv;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const float x = u[q][t], g = acc[i][j0 + q][t], s = 1.f / (1.f + expf(-x));
+                        du[t] = g * v[q][t] * (s * (1.f + x * (1.f - s)));
+                        dv[t] = g * (x * s);
+                    }
+                    bf16x4 pu[3], pv[3];
+                    split4(du, pu);
+                    split4(dv, pv);
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) {
+                        *reinterpret_cast<bf16x4*>(to + t * kRow + at * 2) = pu[t];
+                        *reinterpret_cast<bf16x4*>(to + t * kRow + (at + 32) * 2) = pv[t];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                copy_rows_out<16, kRow>(st + t * kRow, kStride, reinterpret_cast<char*>(duv.p + t * duv.third + row_base * duv.ld + col_base),
+                                        duv.ld * 2, 16, tc.lane);
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+};
+
+// ---- products -----------------------------------------------------------------------------------
+
+// A product of thirds among others of its launch.
+template <int kLayA, int kLayB, class Epilogue>
+struct ThirdsProduct {
+    GemmProblem p;
+    Epilogue epi;
+    int first;                   // its first workgroup, a multiple of eight (see tile_of_workgroup)
+    int workgroups(int tile) {   // operands are padded, so a tile may reach beyond the matrix
+        p.M = ceil_div(p.M, tile) * tile;
+        p.N = ceil_div(p.N, tile) * tile;
+        return p.M / tile * (p.N / tile) * p.splits;
+    }
+    template <int kW, int kSlots>
+    __device__ __forceinline__ void run(int block, OperandRing<kW, kSlots>& smem) const {
+        gemm_tile<kLayA, kLayB, true, true>(p, epi, block - first, smem);
+    }
+};
+template <int kLayA, int kLayB, class Epilogue>
+ThirdsProduct<kLayA, kLayB, Epilogue> job(const GemmProblem& p, const Epilogue& epi) { return {p, epi, 0}; }
+
+template <int kW, int kSlots, class... Jobs>
+__global__ __launch_bounds__(kGemmThreads, kW == kLargeTile || kSlots > kRingSlots ? 1 : 2) void gemm_f32(Jobs... jobs) {
+    __shared__ OperandRing<kW, kSlots> smem;
+    const int block = blockIdx.x;
+    run_job(block, smem, jobs...);
+}
+inline int steps_of(const GemmProblem& p) { return ceil_div(kSegmentsOfThree * (p.K1 / kTileK), p.splits); }
+template <class... Jobs>
+void launch_products(int kW, hipStream_t s, Jobs... jobs) {
+    int grid = 0;
+    ((grid = place_job(jobs, 32 * kW, grid)), ...);
+    if (kW == kLargeTile) gemm_f32<kLargeTile, kRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
+    else if (grid <= 256 && std::max({steps_of(jobs.p)...}) >= kDeepSteps) gemm_f32<kSmallTile, kDeepRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
+    else gemm_f32<kSmallTile, kRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
+}
+
+// C = the sum over the parts of a split reduction, as thirds; parts are n floats (rows of C.ld) apart and in the row tiles of the
+// live rows (live.kept set) or all of them.
+__global__ __launch_bounds__(kThreads) void sum_parts_thirds(const float* parts, int n_parts, size_t n, Thirds C, const int32_t* n_kept,
+                                                            int max_chunks, int A) {
+    constexpr int kTogether = 4;      // loads under way together
+    size_t limit = n;
+    if (n_kept != nullptr) limit = min(n, (size_t)((live_rows(n_kept, max_chunks, A) + kTileM - 1) / kTileM * kTileM) * (size_t)C.ld);
+    const size_t stride = (size_t)gridDim.x * kThreads * 4;
+    for (size_t i = ((size_t)blockIdx.x * kThreads + threadIdx.x) * 4; i < limit; i += stride) {
+        f32x4 acc = *reinterpret_cast<const f32x4*>(parts + i);
+        for (int s0 = 1; s0 < n_parts; s0 += kTogether) {
+            f32x4 v[kTogether];
+#pragma unroll
+            for (int u = 0; u < kTogether; ++u) v[u] = *reinterpret_cast<const f32x4*>(parts + (size_t)min(s0 + u, n_parts - 1) * n + i);
+#pragma unroll
+            for (int u = 0; u < kTogether; ++u)
+                if (s0 + u < n_parts) acc += v[u];
+        }
+        bf16x4 part[3];
+        split4(acc, part);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(C.p + t * C.third + i) = part[t];
+    }
+}
+
+// ---- loss ---------------------------------------------------------------------------------------
 
 __device__ inline float wave_max(float x) {
 #pragma unroll
@@ -298,305 +328,373 @@ __device__ inline float wave_sum(float x) {
     return x;
 }
 
-// One wavefront per row: log-softmax at the target bin, entropy, ratio, clipped surrogate, and (in
-// place) z <- dz = coef * (onehot - softmax) + entropy part.  With a per-chunk ratio the factor is
-// not known yet: z <- onehot - softmax and the entropy part goes to `extra`; the rows are scaled
-// once the chunk ratios are known.
-__global__ __launch_bounds__(kThreads) void loss_rows(float* __restrict__ z, float* __restrict__ extra, int V,
-                                                      const uint8_t* __restrict__ token,
-                                                      const float* __restrict__ logp_old,
-                                                      const float* __restrict__ adv_row,
-                                                      const int32_t* __restrict__ n_kept, int max_chunks, int A,
-                                                      int64_t rows_total, LossOptions opt, int write_dz,
-                                                      float* logp_out, RowOut out) {
+// One wavefront per row, four columns per lane and 256: the logits as the sum of their parts, log-softmax at the target bin,
+// entropy, ratio, clipped surrogate, and dz = coef * (onehot - softmax) + entropy part as thirds.  With a per-chunk ratio the
+// factor is not known yet: the first part of z <- onehot - softmax and the entropy part goes to `extra`; scale_rows makes dz of
+// them once the chunk ratios are known.
+constexpr int kMaxV = 1024;
+struct LossArgs {
+    float* z;                // [n_parts][rows, ld]
+    int n_parts, V, ld;
+    size_t part_stride;
+    float* extra;            // [rows, V], unpadded
+    Thirds dz;               // p null: no backward pass
+    RowMeta meta;
+    const int32_t* n_kept;
+    int max_chunks, A;
+    LossOptions opt;
+    float* logp_out;
+    RowOut out;
+};
+__global__ __launch_bounds__(kThreads) void loss_rows(LossArgs p) {
+    constexpr int kQ = kMaxV / 256;
     const int lane = threadIdx.x % kWave;
     const int64_t r = (int64_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
-    const int64_t rows = live_rows(n_kept, max_chunks, A);
-    if (r >= rows_total || r >= (rows + kRowTile - 1) / kRowTile * kRowTile) return;   // later rows: skipped tiles, read by nothing
+    const int64_t rows = live_rows(p.n_kept, p.max_chunks, p.A);
+    if (r >= (rows + kTileM - 1) / kTileM * kTileM) return;     // later rows: skipped tiles, read by nothing
     const bool live = r < rows;
-    const float scale = objective_scale(opt, rows);
-    float* zr = z + r * V;
-    float mx = -INFINITY;
-    for (int j = lane; j < V; j += kWave) mx = fmaxf(mx, zr[j]);
+    const float scale = objective_scale(p.opt, rows);
+    float* const zr = p.z + r * p.ld;
+    const int b = p.meta.token[r];
+    f32x4 z[kQ];
+    float mx = -INFINITY, zt = 0.f;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+        const int c = q * 256 + 4 * lane;
+        if (c >= p.ld) continue;
+        z[q] = *reinterpret_cast<const f32x4*>(zr + c);
+        for (int s = 1; s < p.n_parts; ++s) z[q] += *reinterpret_cast<const f32x4*>(zr + s * p.part_stride + c);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (c + t < p.V) mx = fmaxf(mx, z[q][t]);
+            if (c + t == b) zt = z[q][t];
+        }
+    }
     mx = wave_max(mx);
     float se = 0.f, sz = 0.f;
-    for (int j = lane; j < V; j += kWave) {
-        const float e = expf(zr[j] - mx);
-        se += e;
-        sz += e * zr[j];
-    }
+#pragma unroll
+    for (int q = 0; q < kQ; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (q * 256 + 4 * lane + t < p.V) {
+                const float e = expf(z[q][t] - mx);
+                se += e;
+                sz += e * z[q][t];
+            }
     se = wave_sum(se);
     sz = wave_sum(sz);
-    const int b = token[r];
+    zt = wave_sum(zt);
     const float lse = mx + logf(se);
-    const float lp = zr[b] - lse;
+    const float lp = zt - lse;
     const float H = lse - sz / se;                      // -sum p log p
-    const float w = (opt.chunk_weight && live) ? opt.chunk_weight[r / A] : 1.f;
-    const LossRow lr = loss_row(lp, logp_old[r], adv_row[r], w, opt, scale);
+    const float w = (p.opt.chunk_weight && live) ? p.opt.chunk_weight[r / p.A] : 1.f;
+    const LossRow lr = loss_row(lp, p.meta.logp_old[r], p.meta.adv[r], w, p.opt, scale);
     if (lane == 0) {
-        out.dlogp[r] = lr.dlogp;
-        out.entropy[r] = live ? H : 0.f;
-        if (!opt.chunk_ratio) {
-            out.term[r] = live ? lr.term : 0.f;
-            out.ratio[r] = lr.ratio;
-            out.clipped[r] = lr.clipped;
+        p.out.dlogp[r] = lr.dlogp;
+        p.out.entropy[r] = live ? H : 0.f;
+        if (!p.opt.chunk_ratio) {
+            p.out.term[r] = live ? lr.term : 0.f;
+            p.out.ratio[r] = lr.ratio;
+            p.out.clipped[r] = lr.clipped;
         }
-        if (logp_out && live) logp_out[r] = lp;
+        if (p.logp_out && live) p.logp_out[r] = lp;
     }
-    if (write_dz) {
-        const float coef = opt.chunk_ratio ? (live ? 1.f : 0.f) : (live ? lr.coef : 0.f);
-        const float ec = live ? opt.entropy_coef * scale : 0.f;
-        for (int j = lane; j < V; j += kWave) {
-            const float zj = zr[j];
-            const float p = expf(zj - lse);
-            const float pg = coef * ((j == b ? 1.f : 0.f) - p);
-            const float ent = ec * p * (zj - lse + H);
-            if (opt.chunk_ratio) {
-                zr[j] = pg;
-                extra[r * V + j] = ent;
-            } else {
-                zr[j] = pg + ent;
+    if (p.dz.p == nullptr) return;
+    const float coef = p.opt.chunk_ratio ? (live ? 1.f : 0.f) : (live ? lr.coef : 0.f);
+    const float ec = live ? p.opt.entropy_coef * scale : 0.f;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+        const int c = q * 256 + 4 * lane;
+        if (c >= p.ld) continue;
+        f32x4 g = {}, ent = {};
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (c + t < p.V) {
+                const float pr = expf(z[q][t] - lse);
+                g[t] = coef * ((c + t == b ? 1.f : 0.f) - pr);
+                ent[t] = ec * pr * (z[q][t] - lse + H);
             }
+        if (p.opt.chunk_ratio) {
+            *reinterpret_cast<f32x4*>(zr + c) = g;
+            if (live) store4(p.extra + r * p.V, c, p.V, ent);
+        } else {
+            bf16x4 part[3];
+            split4(g + ent, part);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(p.dz.p + t * p.dz.third + r * p.ld + c) = part[t];
         }
     }
 }
 
-// Tile and reduction split of an M x N product (n_right of them in one launch) over K: the tile whose workgroups,
-// shared out over the 256 CUs, have the least to do.  The matrix pipes are shared by the workgroups of a CU, so a CU's
-// time is the number of its tiles times their size, plus about half a tile that the dispatcher, which puts several
-// workgroups on one CU while others have none left, costs; the smaller tile counts 1.08 times its size because each of
-// its values is loaded for half as many products.  Measured on both sides of the line, 128-wide against 64-wide tiles:
-// 8192 x 1024 x 2816 (512 tiles of 128) 559 / 503 us, twice that 1112 / 981 us; 8192 x 5632 x 1024 (2816 tiles) 871 / 917 us;
-// a pair of 1024 x 2816 over 8192 rows 902 / 957 us.  Splits (if allowed) aim at two workgroups per CU, and at least at
-// 1024 tiles of 64 x 64 (shorter sums are also more accurate), but not at slices of fewer than about four steps: as many
-// slices as that allows, rounded up, so that a sum over few rows is in slices of at most 64.
-struct TilePlan {
-    int kI, kJ, splits, k_per_split;
-};
-TilePlan plan_tiles(int M, int N, int K, int n_right, bool may_split, bool interleaved) {
-    TilePlan best{};
-    double best_cost = 0.0;
-    for (int big = 1; big >= 0; --big) {
-        const int kI = big ? 2 : 1, kJ = big || interleaved ? 2 : 1;
-        const int64_t tiles = (int64_t)ceil_div(M, 64 * kI) * ceil_div(interleaved ? 2 * N : N, 64 * kJ) * n_right;
-        int64_t splits = 1;
-        if (may_split) {
-            splits = std::max(ceil_div64(512, tiles), ceil_div64(1024, (int64_t)ceil_div(M, 64) * ceil_div(N, 64)));
-            splits = std::max<int64_t>(1, std::min<int64_t>(splits, ceil_div(K, 4 * kStep)));
+// Per-chunk ratio: dz[r, :] = coef[r] z[r, :] (+ extra[r, :] if given) for the live rows, zeros to the end of their last tile.
+__global__ __launch_bounds__(kThreads) void scale_rows(const float* z, const float* extra, int V, const float* coef, const int32_t* n_kept,
+                                                       int max_chunks, int A, Thirds dz) {
+    const int64_t rows = live_rows(n_kept, max_chunks, A), n = (rows + kTileM - 1) / kTileM * kTileM * dz.ld;
+    const int64_t stride = (int64_t)gridDim.x * kThreads * 4;
+    for (int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4; i < n; i += stride) {
+        f32x4 x = {};
+        const int64_t r = i / dz.ld;
+        if (r < rows) {
+            x = *reinterpret_cast<const f32x4*>(z + i);
+            const float c = coef[r];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) x[t] = c * x[t];
+            if (extra) {
+                const int n = (int)(i - r * dz.ld);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) x[t] += n + t < V ? extra[r * V + n + t] : 0.f;
+            }
         }
-        const int k_per = ceil_div(ceil_div(K, (int)splits), kStep) * kStep;
-        splits = ceil_div(K, k_per);
-        const double cost = ((double)ceil_div64(tiles * splits, 256) + 0.5) * kI * kJ * k_per * (big ? 1.0 : 1.08);
-        if (big || cost < best_cost) {
-            best = TilePlan{kI, kJ, (int)splits, k_per};
-            best_cost = cost;
-        }
+        bf16x4 part[3];
+        split4(x, part);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(dz.p + t * dz.third + i) = part[t];
     }
-    return best;
 }
-size_t split_floats(int M, int N, int K, int n_right) {
-    const TilePlan t = plan_tiles(M, N, K, n_right, true, false);
-    return t.splits > 1 ? (size_t)t.splits * M * N * n_right : 0;
+
+// ---- the step -------------------------------------------------------------------------------------
+
+int64_t padded(int64_t n) { return ceil_div64(n, kThirdsUnit) * kThirdsUnit; }
+int steps64(int64_t n) { return (int)ceil_div64(n, kTileK) * kTileK; }
+int64_t tiles256(int64_t n) { return ceil_div64(n, kTileM) * kTileM; }
+
+// Reduction splits of the products: of those with a fp32 result, into parts.
+struct F32Plan {
+    GroupPlan gate, down, logits, wdo, G;      // composed: Wdo and G; else down
+    GroupPlan level[3];                        // as written {dy, dWo}, {da, dWd}, {dX, dWgu}; composed {da, G}, {dWo, dWd}, {dX, dWgu}
+};
+// One product's plan: tile and, if it may be split, parts.  (The plans are those of the bf16 path, with six times the steps.  Each
+// tile and number of parts forced on its launch at six sizes: within 3 % of the best at five of them, 6 % at 5376 rows of 256.)
+GroupPlan plan_one(int64_t M, int64_t N, int64_t K, bool split, int shortest, float us_sum) {
+    return plan_group<1>({{tiles256(M), tiles256(N), kSegmentsOfThree * steps64(K) / kTileK, 1, split, shortest}}, us_sum);
+}
+F32Plan plan_step(const ActorShape& sh, int64_t Mp, bool composed) {
+    const int64_t d = sh.d, ff = sh.ff, V = sh.V;
+    const auto shape = [](int64_t M, int64_t N, int64_t K, bool split) {
+        return GroupShape{tiles256(M), tiles256(N), kSegmentsOfThree * steps64(K) / kTileK, 1, split};
+    };
+    F32Plan p{};
+    p.gate = plan_one(Mp, 2 * padded(ff), d, false, 1, 0.f);
+    if (composed) p.wdo = plan_one(ff, V, d, false, 1, 0.f);
+    else p.down = plan_one(Mp, d, ff, true, 16, 5.f);
+    p.logits = plan_one(Mp, V, composed ? ff : d, true, 8, 0.f);
+    if (composed) {
+        p.level[0] = plan_group<1>({shape(Mp, ff, V, false)}, 2.f);
+        p.G = plan_one(ff, V, Mp, true, 8, 5.f);
+        p.level[1] = plan_group<2>({shape(ff, d, V, false), shape(d, V, ff, true)}, 2.f);
+    } else {
+        p.level[0] = plan_group<2>({shape(Mp, d, V, false), shape(d, V, Mp, true)}, 2.f);
+        p.level[1] = plan_group<2>({shape(Mp, ff, d, false), shape(ff, d, Mp, true)}, 2.f);
+    }
+    GroupShape dX = shape(Mp, d, 2 * padded(ff), true);      // in two parts at most: one goes to dX itself, which the other is added to
+    dX.shortest = ceil_div(dX.steps, 2);
+    p.level[2] = plan_group<2>({dX, shape(d, 2 * padded(ff), Mp, true)}, 2.f);
+    // a small weight gradient in slices of 64 rows
+    if (d <= kTileK && ff <= kTileK) p.level[2].splits[1] = ceil_div((int)sh.rows_max(), kTileK);
+    return p;
 }
 
 struct F32Workspace {
-    float *X, *u, *v, *a, *y, *z, *z_extra, *dy;
-    float *Wdo, *G;   // composed evaluation: Wd Wo and a^T dz, both [ff, V]
-    float *parts, *parts_d;   // partial products of the split reductions; those of dWd
+    Thirds Wgu, Wd, Wo, X, a, y, dz, dy, duv;
+    Thirds Wdo, G;           // composed evaluation: Wd Wo and a^T dz, both [ff, V]
+    float *uv, *z, *z_extra;
+    float* dX_part;          // the second of two parts of dX
+    float* parts_y;          // parts of y (composed: of G)
+    float *parts_o, *parts_d, *parts_g, *parts_u;   // of the weight gradients, where they are computed in parts
+    F32Plan plan;
     RowMeta meta;
     RowOut out;
+    int64_t Mp;
     size_t bytes;
 };
 
-F32Workspace carve(void* ws, const ActorShape& sh, bool grads) {
+// One layout for calls with and without gradients: those without hold the buffers of the backward products too, and those with
+// have three more at the end.
+F32Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool composed) {
     Carver c(ws);
     F32Workspace w{};
-    const size_t M = (size_t)sh.rows_max();
-    w.X = c.take<float>(M * sh.d);
-    w.u = c.take<float>(M * sh.ff);
-    w.v = c.take<float>(M * sh.ff);
-    w.a = c.take<float>(M * sh.ff);
-    w.y = c.take<float>(M * sh.d);
-    w.z = c.take<float>(M * sh.V);
-    w.meta.token = c.take<uint8_t>(M);
-    w.meta.logp_old = c.take<float>(M);
-    w.meta.adv = c.take<float>(M);
-    w.out.term = c.take<float>(M);
-    w.out.ratio = c.take<float>(M);
-    w.out.dlogp = c.take<float>(M);
-    w.out.clipped = c.take<uint8_t>(M);
-    w.out.entropy = c.take<float>(M);
-    w.out.coef = c.take<float>(M);
-    w.Wdo = c.take<float>((size_t)sh.ff * sh.V);
-    w.G = c.take<float>((size_t)sh.ff * sh.V);
-    if (grads) {
-        w.z_extra = c.take<float>(M * sh.V);
-        w.dy = c.take<float>(M * sh.d);
-        const int rows = (int)M;
-        // partial products: of dWo = y^T dz and dWd = a^T dy side by side (composed: of G = a^T dz, then of dWo = Wd^T G); once
-        // those are added up, of dWg and dWu
-        const size_t o = align_up(split_floats(sh.d, sh.V, rows, 1), 64), o_composed = split_floats(sh.d, sh.V, sh.ff, 1);
-        const size_t d = split_floats(sh.ff, sh.d, rows, 1);
-        w.parts = c.take<float>(std::max({o + d, o_composed, split_floats(sh.ff, sh.V, rows, 1), split_floats(sh.d, sh.ff, rows, 2)}));
-        w.parts_d = w.parts + o;
+    const int64_t Mp = w.Mp = tiles256(sh.rows_max());
+    const auto thirds = [&](int64_t rows, int64_t columns) {
+        Thirds t{};
+        t.ld = padded(columns);
+        t.third = tiles256(rows) * t.ld;
+        t.p = c.take<bf16>((size_t)(3 * t.third + kTileN));      // a tile may read beyond the last row's columns
+        return t;
+    };
+    w.plan = plan_step(sh, Mp, composed);
+    const F32Plan& plan = w.plan;
+    const int64_t ffp = padded(sh.ff), Vp = padded(sh.V), dp = padded(sh.d);
+    w.Wgu = thirds(sh.d, 2 * ffp);
+    w.Wd = thirds(sh.ff, sh.d);
+    w.Wo = thirds(sh.d, sh.V);
+    w.X = thirds(Mp, sh.d);
+    w.a = thirds(Mp, sh.ff);
+    if (composed) w.Wdo = thirds(sh.ff, sh.V);
+    else w.y = thirds(Mp, sh.d);
+    if (!composed && plan.down.splits[0] > 1) w.parts_y = c.take<float>((size_t)plan.down.splits[0] * Mp * dp);
+    w.z = c.take<float>((size_t)plan.logits.splits[0] * Mp * Vp);
+    w.meta.token = c.take<uint8_t>(Mp);
+    w.meta.logp_old = c.take<float>(Mp);
+    w.meta.adv = c.take<float>(Mp);
+    w.out.term = c.take<float>(Mp);
+    w.out.ratio = c.take<float>(Mp);
+    w.out.dlogp = c.take<float>(Mp);
+    w.out.clipped = c.take<uint8_t>(Mp);
+    w.out.entropy = c.take<float>(Mp);
+    w.out.coef = c.take<float>(Mp);
+    const size_t M = (size_t)sh.rows_max(), d = sh.d, ff = sh.ff, V = sh.V;
+    w.uv = c.take<float>((size_t)Mp * 2 * ffp);
+    const Thirds dz = thirds(Mp, V);
+    Thirds dy{};
+    if (!composed) dy = thirds(Mp, d);
+    w.duv = thirds(Mp, 2 * ffp);
+    if (composed) w.G = thirds(ff, V);
+    if (composed) w.parts_y = c.take<float>((size_t)plan.G.splits[0] * ffp * Vp);
+    const int o = composed ? plan.level[1].splits[1] : plan.level[0].splits[1], dd = composed ? 1 : plan.level[1].splits[1];
+    const int gu = plan.level[2].splits[1];
+    if (o > 1) w.parts_o = c.take<float>(o * d * V);
+    if (dd > 1) w.parts_d = c.take<float>(dd * ff * d);
+    if (bwd) {
+        w.dz = dz;
+        w.dy = dy;
+        w.z_extra = c.take<float>(M * V);
+        w.dX_part = c.take<float>(M * d);
+        if (gu > 1) w.parts_g = c.take<float>(2 * gu * d * ff);
+        w.parts_u = w.parts_g + gu * d * ff;
+    } else {
+        w.uv = nullptr;
     }
     w.bytes = c.used();
     return w;
 }
 
-bool vec_ok(std::initializer_list<const void*> pointers, std::initializer_list<int64_t> sizes) {
-    for (const void* q : pointers)
-        if (reinterpret_cast<uintptr_t>(q) & 15u) return false;
-    for (int64_t n : sizes)
-        if (n % 4 != 0) return false;
-    return true;
-}
-
-template <int kLayA, int kLayB, int kSecond, class Epilogue>
-void launch(F32Problem p, const TilePlan& t, const Epilogue& epi, hipStream_t s) {
-    const bool vec = vec_ok({p.A, p.B, p.A2, p.B2}, {p.lda, p.ldb, p.M, p.N, p.K});
-    const int columns = kSecond == kInterleaved ? 2 * p.N : p.N;
-    p.k_per_split = t.k_per_split;
-    p.tiles_n = ceil_div(columns, 64 * t.kJ);
-    const dim3 grid((unsigned)p.tiles_n * (kSecond == kPair ? 2u : 1u), (unsigned)ceil_div(p.M, 64 * t.kI),
-                    kSecond == kSum ? 2u : (unsigned)t.splits);
-    constexpr int kSmallJ = kSecond == kInterleaved ? 2 : 1;
-    if (t.kI == 2 && vec) gemm_f32<2, 2, kLayA, kLayB, kSecond, true><<<grid, kThreads, 0, s>>>(p, epi);
-    else if (t.kI == 2) gemm_f32<2, 2, kLayA, kLayB, kSecond, false><<<grid, kThreads, 0, s>>>(p, epi);
-    else if (vec) gemm_f32<1, kSmallJ, kLayA, kLayB, kSecond, true><<<grid, kThreads, 0, s>>>(p, epi);
-    else gemm_f32<1, kSmallJ, kLayA, kLayB, kSecond, false><<<grid, kThreads, 0, s>>>(p, epi);
-}
-
-// The rows a launch runs over: those of the batch (their live count in device memory), or none.
-struct BatchRows {
-    const int32_t* n_kept;
-    int max_chunks, rows_per_chunk;
-};
-F32Problem problem(const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, const BatchRows& rows, int live) {
-    return F32Problem{A, B, A, B, lda, ldb, M, N, K, 0, 0, rows.n_kept, rows.max_chunks, rows.rows_per_chunk,
-                      rows.n_kept ? live : (int)kLiveUnused};
-}
-
-// C[M, N] = A B with A [M, K], and B [K, N] (or [N, K] if b_t), all row-major.
-void gemm(hipStream_t s, const float* A, const float* B, bool b_t, float* C, int M, int N, int K, const BatchRows& rows) {
-    const F32Problem p = problem(A, K, B, b_t ? K : N, M, N, K, rows, kLiveM);
-    const TilePlan t = plan_tiles(M, N, K, 1, false, false);
-    const F32Store epi{C, C, N, 0};
-    if (b_t) launch<kRowsByK, kRowsByK, kNone>(p, t, epi, s);
-    else launch<kRowsByK, kKByRows, kNone>(p, t, epi, s);
-}
-
-// C[M, N] = A^T B with A [K, M], B [K, N] row-major: the weight-gradient shape (reduction over rows).  With B2 also
-// C2 = A^T B2 in the same launch.  A reduction in slices leaves them in `parts`, and their sum in `sums` for a later launch.
-void gemm_reduce_rows(hipStream_t s, const float* A, const float* B, float* C, const float* B2, float* C2, int M, int N, int K,
-                      float* parts, PartsSums& sums, const BatchRows& rows) {
-    const int n_right = B2 ? 2 : 1;
-    F32Problem p = problem(A, M, B, N, M, N, K, rows, kLiveK);
-    if (B2) p.B2 = B2;
-    const TilePlan t = plan_tiles(M, N, K, n_right, true, false);
-    const size_t n = (size_t)M * N;
-    float* const parts2 = parts + (size_t)t.splits * n;
-    const F32Store epi = t.splits > 1 ? F32Store{parts, parts2, N, (int64_t)n} : F32Store{C, C2, N, 0};
-    if (B2) launch<kKByRows, kKByRows, kPair>(p, t, epi, s);
-    else launch<kKByRows, kKByRows, kNone>(p, t, epi, s);
-    if (t.splits > 1) {
-        sums.add(parts, t.splits, n, n, C);
-        if (B2) sums.add(parts2, t.splits, n, n, C2);
-    }
-}
-
 }  // namespace
 
-size_t actor_f32_workspace_bytes(const ActorShape& sh, bool want_grads) {
-    return carve(nullptr, sh, want_grads).bytes;
+size_t actor_f32_workspace_bytes(const ActorShape& sh, bool bwd, bool composed) {
+    return carve(nullptr, sh, bwd, composed).bytes;
 }
 
 int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t s) {
-    const bool bwd = io.want_grads() || io.dX != nullptr;
-    F32Workspace w = carve(ws, sh, bwd);
-    const int M = (int)sh.rows_max();
-    const int d = sh.d, ff = sh.ff, V = sh.V;
-    const float* Wg = static_cast<const float*>(io.Wg);
-    const float* Wu = static_cast<const float*>(io.Wu);
-    const float* Wd = static_cast<const float*>(io.Wd);
-    const float* Wo = static_cast<const float*>(io.Wo);
-    const BatchRows rows{io.n_kept, sh.max_chunks, sh.A}, none{nullptr, 0, 0};
+    const bool grads = io.want_grads(), bwd = grads || io.dX != nullptr;
+    const F32Workspace w = carve(ws, sh, bwd, io.composed);
+    const F32Plan& plan = w.plan;
+    const int Mp = (int)w.Mp, M = (int)sh.rows_max(), d = sh.d, ff = sh.ff, V = sh.V;
+    const int ffp = (int)padded(ff), Vp = (int)padded(V), dp = (int)padded(d);
 
-    int rc = launch_gather(sh, io, 4, w.X, 0, M, w.meta, TransposeList{}, nullptr, 0, s);
+    // C[M, N] = sum_k A(m, k) B(n, k) with the batch's rows as M or K (role) or not at all
+    const auto product = [&](const Thirds& A, const Thirds& B, int m, int n, int k, int role, int splits = 1) {
+        GemmProblem p{};
+        p.A = A.p; p.A2 = A.p + A.third; p.lda = A.ld;
+        p.B = B.p; p.B2 = B.p + B.third; p.ldb = B.ld;
+        p.M = m; p.N = n; p.K1 = steps64(k); p.splits = splits;
+        if (role != kRowsUnused) { p.kept = io.n_kept; p.kept_max = sh.max_chunks; p.rows_per_kept = sh.A; }
+        p.rows_role = role;
+        return p;
+    };
+    PartsSums sums{};
+    // C [m, n] in fp32, or its parts for the launch behind the last product
+    const auto floats = [&](int splits, float* parts, float* C, int m, int n) {
+        const int64_t size = (int64_t)m * n;
+        if (splits == 1) return EpiFloats{C, n, 0, m, n};
+        sums.add(parts, splits, (size_t)size, (size_t)size, C);
+        return EpiFloats{parts, n, size, m, n};
+    };
+    const auto sum_thirds = [&](const float* parts, int n_parts, int64_t rows, const Thirds& C, bool batch) {
+        const size_t n = (size_t)rows * C.ld;
+        sum_parts_thirds<<<(unsigned)std::min<size_t>((n / 4 + kThreads - 1) / kThreads, 2048), kThreads, 0, s>>>(
+            parts, n_parts, n, C, batch ? io.n_kept : nullptr, sh.max_chunks, sh.A);
+    };
+
+    ThirdsList weights{};
+    const int d_rows = (int)padded(d), ff_rows = (int)padded(ff);
+    weights.add(ThirdsJob{static_cast<const float*>(io.Wg), w.Wgu, d, ff, d_rows, kPackGate});
+    weights.add(ThirdsJob{static_cast<const float*>(io.Wu), w.Wgu, d, ff, d_rows, kPackUp});
+    weights.add(ThirdsJob{static_cast<const float*>(io.Wd), w.Wd, ff, d, ff_rows, kPackNone});
+    weights.add(ThirdsJob{static_cast<const float*>(io.Wo), w.Wo, d, V, d_rows, kPackNone});
+    int rc = launch_prepare_f32(sh, io, w.X, Mp, w.meta, weights, static_cast<float*>(io.dX), s);
     if (rc != PCM_OK) return rc;
     {
         StageTimer t(ST_F32_FORWARD, s);
-        F32Problem p = problem(w.X, d, Wg, ff, M, ff, d, rows, kLiveM);                        // u, v, a
-        p.B2 = Wu;
-        launch<kRowsByK, kKByRows, kInterleaved>(p, plan_tiles(M, ff, d, 1, false, true), F32SwigluForward{w.u, w.v, w.a}, s);
-        if (io.composed) {
-            gemm(s, Wd, Wo, false, w.Wdo, ff, V, d, none);                                   // W_do = Wd Wo
-            gemm(s, w.a, w.Wdo, false, w.z, M, V, ff, rows);                                 // z = a W_do
+        launch_products(plan.gate.kW, s, job<kRowsByK, kKByRows>(product(w.X, w.Wgu, Mp, 2 * ffp, d, kRowsAreM), EpiGateUp{w.uv, w.a}));
+        if (io.composed) {                                                                             // W_do = Wd Wo
+            launch_products(plan.wdo.kW, s, job<kRowsByK, kKByRows>(product(w.Wd, w.Wo, ffp, Vp, d, kRowsUnused), EpiThirds{w.Wdo, ffp}));
+        } else if (plan.down.splits[0] == 1) {
+            launch_products(plan.down.kW, s, job<kRowsByK, kKByRows>(product(w.a, w.Wd, Mp, dp, ff, kRowsAreM), EpiThirds{w.y, Mp}));
         } else {
-            gemm(s, w.a, Wd, false, w.y, M, d, ff, rows);
-            gemm(s, w.y, Wo, false, w.z, M, V, d, rows);
+            const int n_parts = plan.down.splits[0];
+            launch_products(plan.down.kW, s, job<kRowsByK, kKByRows>(product(w.a, w.Wd, Mp, dp, ff, kRowsAreM, n_parts),
+                                                                     EpiFloats{w.parts_y, dp, (int64_t)Mp * dp, Mp, dp}));
+            sum_thirds(w.parts_y, n_parts, Mp, w.y, true);
         }
+        const int n_parts = plan.logits.splits[0];                                                     // z = y Wo, or a W_do
+        launch_products(plan.logits.kW, s,
+                        job<kRowsByK, kKByRows>(io.composed ? product(w.a, w.Wdo, Mp, Vp, ff, kRowsAreM, n_parts)
+                                                            : product(w.y, w.Wo, Mp, Vp, d, kRowsAreM, n_parts),
+                                                EpiFloats{w.z, Vp, (int64_t)Mp * Vp, Mp, Vp}));
     }
     {
         StageTimer t(ST_F32_LOSS, s);
-        loss_rows<<<(unsigned)ceil_div64(M, kThreads / kWave), kThreads, 0, s>>>(
-            w.z, w.z_extra, V, w.meta.token, w.meta.logp_old, w.meta.adv, io.n_kept, sh.max_chunks, sh.A, M, io.opt,
-            bwd ? 1 : 0, io.logp_out, w.out);
+        loss_rows<<<(unsigned)(Mp / (kThreads / kWave)), kThreads, 0, s>>>(
+            LossArgs{w.z, plan.logits.splits[0], V, Vp, (size_t)Mp * Vp, w.z_extra, w.dz, w.meta, io.n_kept, sh.max_chunks, sh.A, io.opt,
+                     io.logp_out, w.out});
     }
     if (io.opt.chunk_ratio) {
         rc = launch_chunk_ratio(sh, io, w.meta, w.out, 0, M, s);
         if (rc != PCM_OK) return rc;
         if (bwd) {
-            rc = launch_scale_rows_f32(sh, io, w.z, io.opt.entropy_coef != 0.f ? w.z_extra : nullptr, w.out.coef, M, s);
-            if (rc != PCM_OK) return rc;
+            StageTimer t(ST_REDUCE, s);
+            const int64_t blocks = ceil_div64((int64_t)Mp * Vp / 4, kThreads);
+            scale_rows<<<(unsigned)std::min<int64_t>(blocks, 4096), kThreads, 0, s>>>(
+                w.z, io.opt.entropy_coef != 0.f ? w.z_extra : nullptr, V, w.out.coef, io.n_kept, sh.max_chunks, sh.A, w.dz);
         }
     }
     if (!bwd) return launch_finish(sh, io, w.out, PartsSums{}, FinalPanel{}, true, SumsqLists{}, s);
-    PartsSums sums{};
-    float* const dz = w.z;
-    if (io.want_grads() && io.composed) {
-        PartsSums g{};
-        {
-            StageTimer t(ST_F32_BACKWARD, s);
-            gemm_reduce_rows(s, w.a, dz, w.G, nullptr, nullptr, ff, V, M, w.parts, g, rows);               // G = a^T dz
-        }
-        rc = launch_finish(sh, io, w.out, g, FinalPanel{}, false, SumsqLists{}, s);
-        if (rc != PCM_OK) return rc;
-    }
     {
         StageTimer t(ST_F32_BACKWARD, s);
-        if (io.want_grads()) {
-            if (io.composed) {
-                gemm(s, w.G, Wo, true, io.dWd, ff, d, V, none);                                        // dWd = G Wo^T
-                gemm_reduce_rows(s, Wd, w.G, io.dWo, nullptr, nullptr, d, V, ff, w.parts, sums, none);   // dWo = Wd^T G
+        const EpiGateUpBackward swiglu{w.uv, w.duv};
+        if (io.composed) {
+            const auto da = job<kRowsByK, kRowsByK>(product(w.dz, w.Wdo, Mp, ffp, V, kRowsAreM), swiglu);      // da = dz W_do^T
+            launch_products(plan.level[0].kW, s, da);
+            if (grads) {
+                const int n_parts = plan.G.splits[0];                                                  // G = a^T dz
+                launch_products(plan.G.kW, s, job<kKByRows, kKByRows>(product(w.a, w.dz, ffp, Vp, Mp, kRowsAreK, n_parts),
+                                                                      EpiFloats{w.parts_y, Vp, (int64_t)ffp * Vp, ffp, Vp}));
+                sum_thirds(w.parts_y, n_parts, ffp, w.G, false);
+                const auto dWd = job<kRowsByK, kRowsByK>(product(w.G, w.Wo, ff, d, V, kRowsUnused), EpiFloats{io.dWd, d, 0, ff, d});   // G Wo^T
+                const int o = plan.level[1].splits[1];
+                const auto dWo = job<kKByRows, kKByRows>(product(w.Wd, w.G, d, V, ff, kRowsUnused, o), floats(o, w.parts_o, io.dWo, d, V));   // Wd^T G
+                launch_products(plan.level[1].kW, s, dWo, dWd);
+            }
+        } else {
+            const auto dy = job<kRowsByK, kRowsByK>(product(w.dz, w.Wo, Mp, dp, V, kRowsAreM), EpiThirds{w.dy, Mp});     // dy = dz Wo^T
+            const auto da = job<kRowsByK, kRowsByK>(product(w.dy, w.Wd, Mp, ffp, d, kRowsAreM), swiglu);                 // da = dy Wd^T
+            if (grads) {
+                const int o = plan.level[0].splits[1], dd = plan.level[1].splits[1];
+                launch_products(plan.level[0].kW, s, job<kKByRows, kKByRows>(product(w.y, w.dz, d, V, Mp, kRowsAreK, o), floats(o, w.parts_o, io.dWo, d, V)), dy);
+                launch_products(plan.level[1].kW, s, da, job<kKByRows, kKByRows>(product(w.a, w.dy, ff, d, Mp, kRowsAreK, dd), floats(dd, w.parts_d, io.dWd, ff, d)));
             } else {
-                gemm_reduce_rows(s, w.y, dz, io.dWo, nullptr, nullptr, d, V, M, w.parts, sums, rows);    // dWo = y^T dz
+                launch_products(plan.level[0].kW, s, dy);
+                launch_products(plan.level[1].kW, s, da);
             }
         }
-        if (!io.composed) {
-            gemm(s, dz, Wo, true, w.dy, M, d, V, rows);                                                // dy = dz Wo^T
-            if (io.want_grads()) gemm_reduce_rows(s, w.a, w.dy, io.dWd, nullptr, nullptr, ff, d, M, w.parts_d, sums, rows);   // dWd = a^T dy
-        }
-        // da = dy Wd^T (composed: dz W_do^T); u <- du, v <- dv
-        const int k = io.composed ? V : d;
-        const F32Problem p = io.composed ? problem(dz, V, w.Wdo, V, M, ff, k, rows, kLiveM) : problem(w.dy, d, Wd, d, M, ff, k, rows, kLiveM);
-        launch<kRowsByK, kRowsByK, kNone>(p, plan_tiles(M, ff, k, 1, false, false), F32SwigluBackward{w.u, w.v}, s);
-    }
-    if (io.want_grads() && sums.n > 0 && split_floats(d, ff, M, 2) > 0) {                              // the parts' memory is needed again
-        rc = launch_finish(sh, io, w.out, sums, FinalPanel{}, false, SumsqLists{}, s);
-        if (rc != PCM_OK) return rc;
-        sums = PartsSums{};
-    }
-    {
-        StageTimer t(ST_F32_BACKWARD, s);
-        if (io.want_grads())
-            gemm_reduce_rows(s, w.X, w.u, io.dWg, w.v, io.dWu, d, ff, M, w.parts, sums, rows);         // dWg = X^T du, dWu = X^T dv
-        if (io.dX) {                                                                                   // dX = du Wg^T + dv Wu^T
-            // as two products, in place of y and dy (no longer needed), and their sum: twice the workgroups, sums half as long
-            F32Problem p = problem(w.u, ff, Wg, ff, M, d, ff, rows, kLiveM);
-            p.A2 = w.v; p.B2 = Wu;
-            launch<kRowsByK, kRowsByK, kSum>(p, plan_tiles(M, d, ff, 2, false, false), F32Store{w.y, w.y, d, w.dy - w.y}, s);
-            sums.add(w.y, 2, (size_t)M * d, (size_t)(w.dy - w.y), static_cast<float*>(io.dX), false, nullptr, d);
+        float* const out_X = static_cast<float*>(io.dX);
+        const int x = plan.level[2].splits[0];                                                         // dX = du Wg^T + dv Wu^T
+        const auto dX = job<kRowsByK, kRowsByK>(product(w.duv, w.Wgu, Mp, d, 2 * ffp, kRowsAreM, x), EpiFloats{out_X, d, w.dX_part - out_X, M, d});
+        if (out_X && x > 1) sums.add(w.dX_part, 1, (size_t)M * d, (size_t)M * d, out_X, true, nullptr, d);
+        if (grads) {
+            const int gu = plan.level[2].splits[1];                                                    // dWg = X^T du, dWu = X^T dv
+            EpiFloatsPair epi{{io.dWg, io.dWu}, 0, d, ff};
+            if (gu > 1) {
+                const size_t n = (size_t)d * ff;
+                sums.add(w.parts_g, gu, n, n, io.dWg);
+                sums.add(w.parts_u, gu, n, n, io.dWu);
+                epi = EpiFloatsPair{{w.parts_g, w.parts_u}, (int64_t)n, d, ff};
+            }
+            const auto dWgu = job<kKByRows, kKByRows>(product(w.X, w.duv, d, 2 * ffp, Mp, kRowsAreK, gu), epi);
+            if (io.dX) launch_products(plan.level[2].kW, s, dX, dWgu);
+            else launch_products(plan.level[2].kW, s, dWgu);
+        } else {
+            launch_products(plan.level[2].kW, s, dX);
         }
     }
     return launch_finish(sh, io, w.out, sums, FinalPanel{}, true, SumsqLists{}, s);

@@ -9,6 +9,7 @@
 #include <algorithm>
 
 #include "actor.h"
+#include "thirds.h"
 
 namespace pcm {
 namespace {
@@ -20,8 +21,6 @@ template <typename Vec>
 __device__ inline Vec zero_vec();
 template <>
 __device__ inline uint4 zero_vec<uint4>() { return make_uint4(0, 0, 0, 0); }
-template <>
-__device__ inline uint32_t zero_vec<uint32_t>() { return 0u; }
 template <>
 __device__ inline uint16_t zero_vec<uint16_t>() { return 0; }
 
@@ -37,15 +36,10 @@ struct GatherArgs {
     RowMeta meta;
 };
 
-// Rows [block * kRowsPerBlock, + kRowsPerBlock) of the panel.
+// The metadata of rows [r0, r0 + kRowsPerBlock) of the panel, and where they come from (row of hidden, or -1 for a row of zeros).
 template <typename Vec>
-__device__ inline void gather_rows(const GatherArgs<Vec>& p, int block) {
-    __shared__ int64_t src_row[kRowsPerBlock];
-    const int A = p.A, vec_per_row = p.vec_per_row;
-    const int64_t rows_valid = live_rows(p.n_kept, p.max_chunks, A) - p.row_offset;
-    const int64_t r0 = (int64_t)block * kRowsPerBlock;
-    if (r0 >= (rows_valid + 255) / 256 * 256) return;   // beyond the last live row tile: read by nothing (a quarter of the
-    const int tid = threadIdx.x;                        // copy of a list three quarters full)
+__device__ inline void gather_metadata(const GatherArgs<Vec>& p, int64_t r0, int64_t rows_valid, int64_t (&src_row)[kRowsPerBlock]) {
+    const int tid = threadIdx.x, A = p.A;
     if (tid < kRowsPerBlock) {
         const int64_t r = r0 + tid;
         int64_t src = -1;
@@ -69,6 +63,16 @@ __device__ inline void gather_rows(const GatherArgs<Vec>& p, int block) {
         src_row[tid] = src;
     }
     __syncthreads();
+}
+// Rows [block * kRowsPerBlock, + kRowsPerBlock) of the panel.
+template <typename Vec>
+__device__ inline void gather_rows(const GatherArgs<Vec>& p, int block) {
+    __shared__ int64_t src_row[kRowsPerBlock];
+    const int vec_per_row = p.vec_per_row, tid = threadIdx.x;
+    const int64_t rows_valid = live_rows(p.n_kept, p.max_chunks, p.A) - p.row_offset;
+    const int64_t r0 = (int64_t)block * kRowsPerBlock;
+    if (r0 >= (rows_valid + 255) / 256 * 256) return;   // beyond the last live row tile: read by nothing (a quarter of the
+    gather_metadata(p, r0, rows_valid, src_row);        // copy of a list three quarters full)
     const int total = kRowsPerBlock * vec_per_row;
     constexpr int kUnroll = 8;
     for (int base = tid; base < total; base += kThreads * kUnroll) {
@@ -157,6 +161,93 @@ __global__ __launch_bounds__(kThreads) void prepare_step(GatherArgs<Vec> gather,
     if (i < zero.n) zero.p[i] = 0.0;
 }
 
+// Columns c .. c + 7 of a row of C floats, zeros from its end on.
+__device__ __forceinline__ void load_eight(const float* row, int c, int C, float (&x)[8]) {
+    if (c + 8 <= C) {
+        const f32x4_any lo = *reinterpret_cast<const f32x4_any*>(row + c), hi = *reinterpret_cast<const f32x4_any*>(row + c + 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) { x[t] = lo[t]; x[4 + t] = hi[t]; }
+    } else {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) x[t] = c + t < C ? row[c + t] : 0.f;
+    }
+}
+__device__ __forceinline__ void store_thirds(const float (&x)[8], bf16* at, int64_t third) {
+    uint32_t part[3][4];
+    split_in_three(x, part);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) *reinterpret_cast<uint4*>(at + t * third) = make_uint4(part[t][0], part[t][1], part[t][2], part[t][3]);
+}
+// The fp32 path's counterpart of prepare_step (see launch_prepare_f32).  Bound by memory: four bytes read and six written per
+// value; every thread has four groups of eight values under way.
+struct PrepareF32 {
+    GatherArgs<float> gather;    // X unused
+    Thirds X;
+    ThirdsList weights;
+    float* dX;
+    int gather_blocks;
+};
+__device__ inline void gather_rows_f32(const PrepareF32& p, int block) {
+    __shared__ int64_t src_row[kRowsPerBlock];
+    const GatherArgs<float>& g = p.gather;
+    const int d = g.vec_per_row, tid = threadIdx.x, groups = (int)(p.X.ld / 8);
+    const int64_t rows_valid = live_rows(g.n_kept, g.max_chunks, g.A), r0 = (int64_t)block * kRowsPerBlock;
+    if (r0 >= (rows_valid + 255) / 256 * 256) {
+        if (p.dX != nullptr) {
+            const int64_t end = min(r0 + kRowsPerBlock, (int64_t)g.max_chunks * g.A) * d;
+            for (int64_t i = r0 * d + tid; i < end; i += kThreads) p.dX[i] = 0.f;
+        }
+        return;
+    }
+    gather_metadata(g, r0, rows_valid, src_row);
+    const int total = kRowsPerBlock * groups;
+    constexpr int kUnroll = 4;
+    for (int base = tid; base < total; base += kThreads * kUnroll) {
+        float x[kUnroll][8];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int e = base + u * kThreads, row = e / groups;
+            const int64_t src = e < total ? src_row[row] : -1;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) x[u][t] = 0.f;
+            if (src >= 0) load_eight(g.hidden + src * d, (e - row * groups) * 8, d, x[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int e = base + u * kThreads, row = e / groups;
+            if (e < total) store_thirds(x[u], p.X.p + (r0 + row) * p.X.ld + (e - row * groups) * 8, p.X.third);
+        }
+    }
+}
+__device__ inline void split_weights(const ThirdsList& list, int block) {
+    int which = 0;
+#pragma unroll
+    for (int q = 1; q < ThirdsList::kMax; ++q) which += q < list.n && block >= list.first[q] ? 1 : 0;
+    const ThirdsJob job = list.job[which];
+    const int groups = (int)(job.mode == kPackNone ? job.dst.ld : job.dst.ld / 2) / 8;
+    const int64_t total = (int64_t)job.rows * groups, e0 = (int64_t)(block - list.first[which]) * ThirdsList::kUnits + threadIdx.x;
+    constexpr int kUnroll = ThirdsList::kUnits / kThreads;
+    float x[kUnroll][8];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const int64_t e = e0 + u * kThreads;
+        const int row = (int)(e / groups), c = (int)(e - (int64_t)row * groups) * 8;
+        load_eight(job.src + (int64_t)min(row, job.R - 1) * job.C, c, e < total && row < job.R ? job.C : 0, x[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const int64_t e = e0 + u * kThreads;
+        const int row = (int)(e / groups), c = (int)(e - (int64_t)row * groups) * 8;
+        const int to = job.mode == kPackNone ? c : c / 32 * 64 + c % 32 + (job.mode == kPackUp ? 32 : 0);
+        if (e < total) store_thirds(x[u], job.dst.p + (int64_t)row * job.dst.ld + to, job.dst.third);
+    }
+}
+__global__ __launch_bounds__(kThreads) void prepare_step_f32(PrepareF32 p) {
+    const int block = blockIdx.x;
+    if (block < p.gather_blocks) gather_rows_f32(p, block);
+    else split_weights(p.weights, block - p.gather_blocks);
+}
+
 constexpr int kFinishThreads = 1024;
 // Sum over the workgroup by a fixed tree (thread 0 has the result).
 template <int kN>
@@ -223,25 +314,21 @@ __global__ __launch_bounds__(kFinishThreads) void finish_loss(LossReduceArgs los
 // parts are read eight at a time, so that their loads are under way together (the five sums and the loss of a step of 5376 fp32 rows of
 // 256 -> 1024 -> 256: six launches of 46 us -> two of 20).
 template <class Vec>
-__device__ inline double sum_parts(const PartsSum& job, int block, int64_t live) {
+__device__ inline double sum_parts(const PartsSum& job, int block, size_t n) {
     constexpr int kPer = sizeof(Vec) / sizeof(float), kTogether = 8;
     if ((int)threadIdx.x >= job.threads) return 0.0;
     const size_t stride = (size_t)job.blocks * job.threads * kPer;
-    const size_t limit = job.live_row > 0 ? (size_t)((live + 127) / 128 * 128) * job.live_row : job.n;   // a multiple of 4, or n
     double sq = 0.0;
-    for (size_t i = ((size_t)block * job.threads + threadIdx.x) * kPer; i < job.n; i += stride) {
+    for (size_t i = ((size_t)block * job.threads + threadIdx.x) * kPer; i < n; i += stride) {
         auto part = [&](int s) { return *reinterpret_cast<const Vec*>(job.parts + (size_t)s * job.stride + i); };
-        Vec acc = {};
-        if (i < limit) {
-            acc = job.add ? *reinterpret_cast<const Vec*>(job.out + i) + part(0) : part(0);
-            for (int s0 = 1; s0 < job.n_parts; s0 += kTogether) {
-                Vec v[kTogether];
+        Vec acc = job.add ? *reinterpret_cast<const Vec*>(job.out + i) + part(0) : part(0);
+        for (int s0 = 1; s0 < job.n_parts; s0 += kTogether) {
+            Vec v[kTogether];
 #pragma unroll
-                for (int u = 0; u < kTogether; ++u) v[u] = part(min(s0 + u, job.n_parts - 1));
+            for (int u = 0; u < kTogether; ++u) v[u] = part(min(s0 + u, job.n_parts - 1));
 #pragma unroll
-                for (int u = 0; u < kTogether; ++u)
-                    if (s0 + u < job.n_parts) acc = acc + v[u];
-            }
+            for (int u = 0; u < kTogether; ++u)
+                if (s0 + u < job.n_parts) acc = acc + v[u];
         }
         *reinterpret_cast<Vec*>(job.out + i) = acc;
         if (job.sumsq != nullptr)
@@ -259,8 +346,9 @@ __global__ __launch_bounds__(kFinishThreads) void finish_step(PartsSums sums, Fi
     for (int q = 1; q < PartsSums::kMax; ++q) which += q < sums.n && block >= sums.job[q].first ? 1 : 0;
     const PartsSum job = sums.job[which];
     block -= job.first;
-    const int64_t live = job.live_row > 0 ? live_rows(loss.n_kept, loss.max_chunks, loss.A) : 0;
-    double sq = job.vec ? sum_parts<f32x4>(job, block, live) : sum_parts<float>(job, block, live);
+    size_t n = job.n;
+    if (job.live_row > 0) n = min(n, (size_t)((live_rows(loss.n_kept, loss.max_chunks, loss.A) + 255) / 256 * 256) * job.live_row);
+    double sq = job.vec ? sum_parts<f32x4>(job, block, n) : sum_parts<float>(job, block, n);
     if (job.sumsq == nullptr || !panel()) return;
     __shared__ double wave_part[kFinishThreads / kWave];
 #pragma unroll
@@ -301,21 +389,6 @@ __global__ __launch_bounds__(kRatioThreads) void chunk_ratio_rows(const float* _
         ratio[r] = lr.ratio;
         clipped[r] = lr.clipped;
         coef[r] = lr.coef;
-    }
-}
-
-// Rows [0, live rows) only: rows beyond them hold zeros (or, in row tiles that the logit product
-// skipped, nothing) and are not read by anything downstream.
-__global__ __launch_bounds__(256) void scale_rows_f32(float* __restrict__ dz, const float* __restrict__ extra,
-                                                      const float* __restrict__ coef, const int32_t* __restrict__ n_kept,
-                                                      int max_chunks, int A, int64_t rows_max, int V) {
-    const int64_t live = live_rows(n_kept, max_chunks, A), rows = live < rows_max ? live : rows_max;
-    const int64_t n = rows * V;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        float x = coef[i / V] * dz[i];
-        if (extra) x += extra[i];
-        dz[i] = x;
     }
 }
 
@@ -470,10 +543,20 @@ int launch_live_rows(const ActorShape& sh, const ActorIO& io, const uint8_t* cli
     return launch_status();
 }
 
-int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void* X, int64_t row_offset, int64_t rows_pad,
+int launch_prepare_f32(const ActorShape& sh, const ActorIO& io, const Thirds& X, int64_t rows_pad, RowMeta meta,
+                       const ThirdsList& weights, float* dX, hipStream_t s) {
+    StageTimer t(ST_GATHER, s);
+    const GatherArgs<float> gather{static_cast<const float*>(io.hidden), io.tokens, io.logp_old, io.adv, io.kept_idx, io.n_kept,
+                                   sh.max_chunks, sh.T, sh.N, sh.A, sh.V, sh.d, 0, rows_pad, nullptr, meta};
+    const int blocks = (int)ceil_div64(rows_pad, kRowsPerBlock);
+    prepare_step_f32<<<(unsigned)(blocks + weights.blocks), kThreads, 0, s>>>(PrepareF32{gather, X, weights, dX, blocks});
+    return launch_status();
+}
+
+int launch_gather(const ActorShape& sh, const ActorIO& io, void* X, int64_t row_offset, int64_t rows_pad,
                   RowMeta meta, const TransposeList& layouts, double* zero, int n_zero, hipStream_t s) {
     StageTimer t(ST_GATHER, s);
-    const int64_t row_bytes = (int64_t)sh.d * elem_bytes;
+    const int64_t row_bytes = (int64_t)sh.d * 2;
     const unsigned blocks = (unsigned)ceil_div64(rows_pad, kRowsPerBlock);
     const unsigned grid = (unsigned)layouts.blocks + blocks + (unsigned)ceil_div(n_zero, kThreads);
     const bool aligned16 = row_bytes % 16 == 0 && (reinterpret_cast<uintptr_t>(io.hidden) & 15u) == 0 &&
@@ -487,7 +570,6 @@ int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void*
         else prepare_step<Vec, false><<<grid, kThreads, 0, s>>>(args, (int)blocks, layouts, ZeroSlots{zero, n_zero});
     };
     if (aligned16) launch(uint4{}, row_bytes / 16);
-    else if (elem_bytes == 4) launch(uint32_t{}, sh.d);
     else launch(uint16_t{}, sh.d);
     return launch_status();
 }
@@ -549,14 +631,6 @@ int launch_chunk_ratio(const ActorShape& sh, const ActorIO& io, RowMeta meta, Ro
     chunk_ratio_rows<<<(unsigned)ceil_div64(slots, kRatioSlots), kRatioThreads, 0, s>>>(out.dlogp, meta.adv, io.n_kept, sh.max_chunks,
                                                                       sh.A, row_offset, rows_pad, io.opt, out.term,
                                                                       out.ratio, out.clipped, out.coef);
-    return launch_status();
-}
-
-int launch_scale_rows_f32(const ActorShape& sh, const ActorIO& io, float* dz, const float* extra, const float* coef,
-                          int64_t rows, hipStream_t s) {
-    StageTimer t(ST_REDUCE, s);
-    const int64_t blocks = ceil_div64(rows * sh.V, 256);
-    scale_rows_f32<<<(unsigned)(blocks < 4096 ? blocks : 4096), 256, 0, s>>>(dz, extra, coef, io.n_kept, sh.max_chunks, sh.A, rows, sh.V);
     return launch_status();
 }
 

@@ -1,0 +1,89 @@
+"""The fp32 actor step where its operands as three bf16 matrices can go wrong: sizes at the edges of the padding and of the
+tiles, magnitudes at the ends of the fp32 range, and values that are no numbers."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_actor import CONFIGS, check, condition_logp_old, make_problem, pcm, run_both  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5     # the accuracy that the fp32 path states
+
+
+def problem(d, ff, V, A, n_kept, seed=5):
+    cfg = CONFIGS["cfg1"].with_(n_groups=1, G=4, N=max(4, -(-n_kept // 3)), K=2, B=4, d=d, ff=ff, V=V, L=1, D=A, seed=seed)
+    kept = np.arange(0, cfg.T * cfg.N)[:n_kept]
+    pr = make_problem(cfg, wstd=min(0.2, 1.2 / np.sqrt(d)), margin=1e-3, kept=kept, old_rel=0.2)
+    pr["adv"] = np.where(np.arange(cfg.T) % 2 == 0, 0.8, -1.2)
+    return pr
+
+
+@pytest.mark.parametrize("composed", [False, True])
+@pytest.mark.parametrize("d,ff,V,A,n_kept,max_kept", [
+    (1, 1, 2, 1, 1, 1),               # one product per value
+    (64, 128, 128, 1, 256, 256),      # whole steps, whole units of padding, one whole row tile
+    (65, 129, 129, 1, 257, 300),      # one beyond each of them
+    (63, 127, 127, 3, 85, 86),        # one before; rows unaligned to 16 bytes; 255 rows
+    (130, 384, 384, 5, 103, 110),     # three units of padding: a 256-wide tile reaches beyond them
+    (257, 640, 513, 4, 63, 64),       # V of five units; 252 rows
+    (96, 2560, 1024, 8, 20, 70),      # the widest V; row tiles of the buffer without a live row
+    (700, 300, 101, 15, 90, 90),      # six row tiles
+])
+def test_f32_sizes(pcm, d, ff, V, A, n_kept, max_kept, composed):   # noqa: F811
+    """TOL holds at these sizes as at any: at most 2560 + 513 terms a sum, with the roundings of a thirty-second of them."""
+    pr = problem(d, ff, V, A, n_kept)
+    for variants in ({}, dict(entropy_coef=1e-3, token_mean=True)):
+        ref, got = run_both(pcm, pr, max_kept=max_kept, composed_head=composed, variants=variants, scale=1.0 if variants else None)
+        check(ref, got, TOL, len(ref["rows"]))
+        assert not got["dX"][len(ref["rows"]):].any()          # rows of the buffer behind the kept ones
+    _, fwd = run_both(pcm, pr, max_kept=max_kept, composed_head=composed, want_grads=False, want_dX=False, scale=1.0 if variants else None,
+                      variants=variants)
+    n = len(ref["rows"])
+    assert np.array_equal(fwd["logp"][:n], got["logp"][:n])
+    _, only = run_both(pcm, pr, max_kept=max_kept, composed_head=composed, want_grads=False, want_dX=True, scale=1.0 if variants else None,
+                       variants=variants)
+    assert np.array_equal(only["dX"], got["dX"])
+
+
+@pytest.mark.parametrize("power", [60, 80])
+def test_f32_scaled_operands_give_the_same_bits(pcm, power):   # noqa: F811
+    """Rows times 2^p and gate and up weights over 2^p: every product and sum scales exactly, parts of operands included
+    (the smallest, 2^-16 of the smallest weight, is a normal bf16 value: checked)."""
+    pr = problem(96, 160, 64, 4, 40)
+    assert min(np.abs(pr["W"][k]).min() for k in ("Wg", "Wu")) * 2.0 ** (-power - 16) > 2.0 ** -125
+    f = 2.0 ** power
+    sc = dict(pr, hidden=(pr["hidden"].astype(np.float32) * np.float32(f)), W=dict(pr["W"], Wg=pr["W"]["Wg"].astype(np.float32) / np.float32(f),
+                                                                                   Wu=pr["W"]["Wu"].astype(np.float32) / np.float32(f)))
+    base = dict(pr, hidden=pr["hidden"].astype(np.float32), W={k: v.astype(np.float32) for k, v in pr["W"].items()})
+    _, want = run_both(pcm, base)
+    _, got = run_both(pcm, sc)
+    for k in ("loss", "logp", "dWd", "dWo"):
+        assert np.array_equal(got[k], want[k]), k
+    for k in ("dWg", "dWu"):
+        assert np.array_equal(got[k] / np.float32(f), want[k]), k
+    assert np.array_equal(got["dX"] * np.float32(f), want["dX"])
+
+
+def test_f32_largest_value(pcm):   # noqa: F811
+    """The largest fp32 value splits without overflow: 2^128 (1 - 2^-24) times a weight of 2^-126 is 4 (1 - 2^-24)."""
+    pr = problem(64, 96, 32, 4, 20)
+    hidden, W = pr["hidden"].astype(np.float32), {k: v.astype(np.float32) for k, v in pr["W"].items()}
+    hidden[:, 0] = np.finfo(np.float32).max
+    W["Wg"][0] = W["Wu"][0] = np.float32(2.0 ** -126)
+    ref, got = run_both(pcm, dict(pr, hidden=hidden, W=W), want_grads=False, want_dX=False)
+    n = len(ref["rows"])
+    assert np.isfinite(got["logp"][:n]).all()
+    assert np.abs(got["logp"][:n] - ref["logp"]).max() <= TOL * np.abs(ref["logp"]).max()
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_f32_rows_that_are_no_numbers_stay_alone(pcm, value):   # noqa: F811
+    """A row with an infinity or a NaN has NaN for its log-probability; every other row is what it is without."""
+    pr = problem(70, 90, 33, 4, 80)
+    hidden = pr["hidden"].astype(np.float32)
+    _, want = run_both(pcm, dict(pr, hidden=hidden), want_grads=False, want_dX=False)
+    bad = hidden.copy()
+    bad[17, 3] = value
+    _, got = run_both(pcm, dict(pr, hidden=bad), want_grads=False, want_dX=False)
+    others = np.arange(len(want["logp"])) != 17
+    assert np.isnan(got["logp"][17]) and np.array_equal(got["logp"][others], want["logp"][others])
