@@ -40,6 +40,7 @@
 namespace pcm {
 namespace {
 
+constexpr size_t kMaxSplitTiles = 256;   // tiles x parts of a split reduction: one workgroup per CU
 constexpr size_t kSumBlocksMax = PartsSums::kBlocksMax;
 
 // Rows of a product over a panel of the batch that its row tiles cover, from the device-side count (kept as in GemmProblem).
@@ -278,6 +279,70 @@ int pick_splits(int tiles, int steps) {
     const int max_s = steps / 8 > 0 ? steps / 8 : 1;
     if (s > max_s) s = max_s;
     return s < 1 ? 1 : s;
+}
+
+// Tile and reduction splits of products that share a launch: those with the least estimated time.  A workgroup takes a few
+// microseconds to start and to write its tile, and per 64-wide step 0.94 us with the large tile (the matrix pipe) or 0.46 with
+// the small one (LDS, which two workgroups of a CU share; see tile_for).  The launch takes what its longest workgroup does, or
+// the work shared out over 256 CUs and about half a workgroup more at the end; parts are written, read back and added up at
+// about 4 TB/s.  Measured against every one of these choices forced on all three launches of a step (tile, and the longest
+// reduction from 6 steps to all of them): the estimate is within 1 % of the best, or better, at 14 of 16 sizes from 448 rows
+// of 3072 -> 768 to 5376 of 3328 -> 7168, and 2 to 3 % off at 9856 rows of 1792 -> 1792 and 2688 of 3072 -> 2560.
+struct GroupShape {
+    int64_t M, N;
+    int steps, count;      // `count` products of these sizes
+    bool split;            // whether the reduction may be split (fp32 parts, summed by a later launch)
+    int shortest = 1;      // and into no fewer steps than these
+};
+struct GroupPlan {
+    static constexpr int kMax = 4;
+    int kW, splits[kMax];
+};
+template <int kN>
+GroupPlan plan_group(const GroupShape (&jobs)[kN], float us_sum) {
+    // (little arithmetic: every call of a step comes through here, and a small one is bound by the host)
+    int large[kN], most_splits[kN], longest_split = 0;
+    float part_us[kN];                                   // writing or reading one part
+    for (int q = 0; q < kN; ++q) {
+        const GroupShape& j = jobs[q];
+        large[q] = (int)(j.M / kTileM) * (int)(j.N / kTileN);
+        most_splits[q] = j.split ? std::max(1, std::min({(int)kMaxSplitTiles / large[q], j.steps / j.shortest, 64})) : 1;
+        part_us[q] = (float)large[q] * (float)j.count * (kTileM * kTileN * 4 / 4e6f);
+        if (most_splits[q] > 1) longest_split = std::max(longest_split, j.steps);
+    }
+    GroupPlan best{};
+    float best_us = 0.f;
+    for (int kW : {kLargeTile, kSmallTile}) {
+        const float us_per_step = kW == kLargeTile ? 0.94f : 0.46f, us_fixed = kW == kLargeTile ? 5.f : 3.f;
+        const int tiles_per_large = kW == kLargeTile ? 1 : 4;
+        for (int most : {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 1 << 20}) {     // longest reduction of a workgroup
+            if (most < longest_split || most == 1 << 20 || longest_split == 0) {
+                GroupPlan plan{kW, {}};
+                int steps = 0;                           // of the longest workgroup
+                int64_t workgroups = 0;
+                float work = 0.f, sum = 0.f;
+                for (int q = 0; q < kN; ++q) {
+                    const GroupShape& j = jobs[q];
+                    const int s = std::min(most_splits[q], ceil_div(j.steps, most)), len = s > 1 ? ceil_div(j.steps, s) : j.steps;
+                    plan.splits[q] = s;
+                    steps = std::max(steps, len);
+                    const int64_t n = (int64_t)large[q] * (tiles_per_large * s * j.count);
+                    workgroups += n;
+                    work += (float)n * (us_fixed + us_per_step * (float)len);
+                    if (s > 1) sum += (float)(2 * s + 1) * part_us[q];
+                }
+                float us = us_fixed + us_per_step * (float)steps;
+                if (workgroups > 256) us = std::max(us, work / 256 + 0.5f * work / (float)workgroups);
+                if (sum > 0.f) us += us_sum + sum;
+                if (best.kW == 0 || us < best_us) {
+                    best = plan;
+                    best_us = us;
+                }
+            }
+            if (longest_split == 0) break;
+        }
+    }
+    return best;
 }
 
 // Whole steps with a launch per product / with launches shared by the products of a dependency level (and the sums at the

@@ -1,34 +1,40 @@
-// fp32 path of the masked GRPO actor step (Eq. 11): fp32 operands, sums and results, on the bf16 matrix cores.
+// fp32 path of the masked GRPO actor step (Eq. 11): fp32 operands, sums and results.
 //
-// Every operand of a product is held as three bf16 matrices whose sum it is exactly (thirds.h); a product of two is six
-// products of such parts, as six segments of one reduction of the bf16 GEMM's main loop, the small ones first (the three left
-// out are below 2^-23 of the whole).  The matrix cores add up 32 products at a time in fp32, so a sum has a thirty-second of
-// the roundings that one by fp32 multiply-adds has.  Errors against 64 bits, root mean square over six inputs each, fp32 matrix
-// instructions / thirds: at 1024 -> 2816 -> 1024 -> 256 log-probabilities 4.8e-7 / 1.7e-7, gradients 4.9e-6 / 1.8e-6; at 256 -> 1024
-// 2.7e-7 / 1.0e-7 and 2.8e-6 / 1.1e-6; at eight further sizes of 169 .. 619 -> 133 .. 2026 every one 0.29 to 0.48 of what it was.
-// (With the six products of every 32 k added up one behind the other the sums had a bias of 1e-7 to 4e-7: the matrix cores cut
-// off what they add; in segments, small ones first, a sixth of the additions do so at full size.)
-// The bf16 matrix cores do 16 times the multiply-adds of the fp32 ones, so six products take 3/8 of the time at the same
-// share of their rates.  Steps: 10,752 rows of 1024 -> 2816 -> 1024 -> 256, a quarter of them not kept, 4.00 -> 2.45 ms; 5376 of
-// 256 -> 1024 -> 256 -> 256 363 -> 316 us; 360 of 473 -> 333 -> 473 -> 512 185 -> 143, 1440 of 619 -> 1302 -> 619 -> 256 413 -> 243,
-// 8960 of 103 -> 149 -> 103 -> 256, composed, where most of the padded tiles is padding, 171 -> 164; faster at 16 of 16 sizes.
+// Forward: products on the fp32 matrix instructions (gemm_floats.h), every sum one chain in the order of k, so that loss and
+// log-probabilities have the bits of the definition's order of additions whatever the tile.
 //
-// Who reads a matrix only as an operand gets the thirds alone: X, a, y, dz, dy, du and dv, and the weights, are never stored
-// in fp32.  Wg and Wu are one matrix with columns in blocks of 32 of each in turn, so that a wavefront holds a gate column and
-// its up column, and so are u and v, and du and dv.  Operands are padded with zeros to whole tiles in the workspace, so any
+// Backward: products on the bf16 matrix cores.  Every operand is held as three bf16 matrices whose sum it is exactly (thirds.h),
+// and a product of two is six products of such parts (gemm_thirds.h; the three left out are below 2^-23 of the whole).  The
+// matrix cores add up 32 products at a time in fp32, so a sum has a thirty-second of the roundings that one by fp32
+// multiply-adds has, and they do 16 times the multiply-adds of the fp32 ones: six products take 3/8 of the time at the same share
+// of their rates.
+// Measured against fp32 matrix instructions throughout, steps: 10,752 rows of 1024 -> 2816 -> 1024 -> 256, a quarter of them not kept,
+// 3.74 -> 2.54 ms; 5376 of 256 -> 1024 -> 256 -> 256 362 -> 273 us; 360 of 473 -> 333 -> 473 -> 512 185 -> 124, 1440 of 619 -> 1302 -> 619 ->
+// 256 413 -> 201, 8960 of 103 -> 149 -> 103 -> 256, composed, where most of the padded tiles is padding, 171 -> 149; faster at 16 of 16
+// sizes, 1.15 to 2.06 times.  Loss, log-probabilities and statistics have the same bits; errors of the gradients against 64 bits,
+// root mean square over six inputs each: dX 4.85e-6 -> 4.74e-6 and 2.78e-6 -> 2.71e-6 at the first two, no larger at any of ten sizes.
+// (The forward products as thirds too: 2.08 ms and 232 us, and a third of the error; but the loss may be a sum of terms of both
+// signs that nearly cancel, and any other rounding of the logits moves it by more than a part in 10^4 then.)
+//
+// Who reads a matrix only as an operand gets its operand form alone: X, a and y as floats in blocks and as thirds, dz, dy, du and
+// dv as thirds.  Wg and Wu are one matrix with columns in blocks of 32 of each in turn, so that a wavefront holds a gate column
+// and its up column, and so are u and v, and du and dv.  Operands are padded with zeros to whole blocks in the workspace, so any
 // size runs; results are written as far as they reach.
 //
-// Products of one dependency level share a launch and long reductions are split into parts that a later launch adds up in
-// order (no atomics), as in the bf16 path.  Row tiles beyond the kept count are skipped.
+// Backward products of one dependency level share a launch and long reductions are split into parts that a later launch adds up
+// in order (no atomics), as in the bf16 path.  Row tiles beyond the kept count are skipped.
 #include <algorithm>
 
-#include "gemm_bf16.h"
-#include "thirds.h"
+#include "gemm_floats.h"
+#include "gemm_thirds.h"
 
 namespace pcm {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kW = kSmallTile;
+using ThirdsCoord = TileCoord<kW>;
+using ThirdsSums = Accumulators<kW>;
 
 __device__ __forceinline__ void split4(f32x4 v, bf16x4 (&out)[3]) {
     const float x[4] = {v[0], v[1], v[2], v[3]};
@@ -48,14 +54,31 @@ __device__ __forceinline__ void store4(float* row, int n, int N, f32x4 v) {
     }
 }
 
+// The parts of kRows rows of kRowBytes each from a staging area, rows `stride` bytes apart and the parts of a row kRowBytes, to C
+// from (row, column) on, multiples of kRows and 32; rows at and beyond n_rows are not written.
+template <int kRows, int kRowBytes>
+__device__ __forceinline__ void copy_thirds_out(const char* st, int stride, const Thirds& C, int64_t row, int64_t column, int n_rows, int lane) {
+    constexpr int kLanesPerRow = kRowBytes / 16, kRowsPerPass = 64 / kLanesPerRow;
+    static_assert(kRowsPerPass % 2 == 0 && kThirdsUnit % kRows == 0, "both rows of a line in a pass, all rows in a block");
+    const int r = lane / kLanesPerRow, c = lane % kLanesPerRow;
+    bf16* const out = C.p + Thirds::at(row + r, column + c * 8, C.ld);
+    const char* const src = st + r * stride + c * 16;
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int pass = 0; pass < kRows / kRowsPerPass; ++pass)
+            if (pass * kRowsPerPass < n_rows)            // wave-uniform: n_rows is a multiple of a pass's rows
+                *reinterpret_cast<u32x4*>(out + t * kThirdsPart + pass * kRowsPerPass * 32) =
+                    *reinterpret_cast<const u32x4*>(src + t * kRowBytes + pass * kRowsPerPass * stride);
+}
+
 // ---- epilogues: results go through the wavefront's staging area, as those of the bf16 path do -------------------------
 
 // C = acc as thirds.  Columns up to C.ld (a multiple of a wavefront's), rows below `rows`.
 struct EpiThirds {
     Thirds C;
     int rows;
-    template <int kW>
-    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+    __device__ __forceinline__ void operator()(const ThirdsCoord& tc, const ThirdsSums& acc, char* lds) const {
         constexpr int RW = kWaveRows<kW>, kRow = RW * 2, kStride = 3 * kRow + 16;
         const int col_base = tc.col0();
         if (col_base >= C.ld) return;
@@ -75,10 +98,7 @@ struct EpiThirds {
                 }
             __builtin_amdgcn_wave_barrier();
             const int row_base = tc.row0() + i * 32;
-#pragma unroll
-            for (int t = 0; t < 3; ++t)
-                copy_rows_out<32, kRow>(st + t * kRow, kStride, reinterpret_cast<char*>(C.p + t * C.third + (int64_t)row_base * C.ld + col_base),
-                                        C.ld * 2, rows - row_base, tc.lane);
+            copy_thirds_out<32, kRow>(st, kStride, C, row_base, col_base, rows - row_base, tc.lane);
             __builtin_amdgcn_wave_barrier();
         }
     }
@@ -89,8 +109,7 @@ struct EpiFloats {
     float* C;
     int64_t ldc, split_stride;
     int M, N;
-    template <int kW>
-    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+    __device__ __forceinline__ void operator()(const ThirdsCoord& tc, const ThirdsSums& acc, char* lds) const {
         constexpr int RW = kWaveRows<kW>, kStride = RW * 4 + 16, kLanesPerRow = RW / 4, kRowsPerPass = 64 / kLanesPerRow;
         char* const st = wave_stage(tc, lds);
         float* const out = C + tc.split * split_stride;
@@ -120,8 +139,7 @@ struct EpiFloatsPair {
     float* C[2];
     int64_t split_stride;
     int M, N;
-    template <int kW>
-    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+    __device__ __forceinline__ void operator()(const ThirdsCoord& tc, const ThirdsSums& acc, char* lds) const {
         constexpr int RW = kWaveRows<kW>, kStride = RW * 4 + 16, kLanesPerRow = RW / 4, kRowsPerPass = 64 / kLanesPerRow;
         char* const st = wave_stage(tc, lds);
         const int packed = tc.col0() + tc.lane % kLanesPerRow * 4, n = packed / 64 * 32 + packed % 32;
@@ -146,68 +164,16 @@ struct EpiFloatsPair {
     }
 };
 
-// Gate and up projection, columns in blocks of 32 of each in turn: a = silu(u) v as thirds, and for a backward pass u and v in
-// fp32 as they are in the product.
-struct EpiGateUp {
-    float* uv;               // [rows, 2 a.ld] or null
-    Thirds a;
-    template <int kW>
-    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
-        constexpr int RW = kWaveRows<kW>, CW = RW / 2, kRow = CW * 2;
-        constexpr int kStrideUv = RW * 4 + 16, kStride = 3 * kRow + 16;
-        const int col_base = tc.col0();
-        if (col_base >= 2 * a.ld) return;
-        char* const st = wave_stage(tc, lds);
-#pragma unroll
-        for (int i = 0; i < RW / 32; ++i) {                // 32 rows per pass
-            const int64_t row_base = tc.row0() + i * 32;
-            if (uv != nullptr) {
-#pragma unroll
-                for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-                    for (int j = 0; j < kW; ++j)
-                        *reinterpret_cast<f32x4*>(st + (ii * 16 + (tc.lane & 15)) * kStrideUv + (j * 16 + 4 * (tc.lane >> 4)) * 4) = acc[2 * i + ii][j];
-                __builtin_amdgcn_wave_barrier();
-                copy_rows_out<32, RW * 4>(st, kStrideUv, reinterpret_cast<char*>(uv + row_base * 2 * a.ld + col_base), a.ld * 8, 32, tc.lane);
-                __builtin_amdgcn_wave_barrier();
-            }
-#pragma unroll
-            for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-                for (int q = 0; q < kW / 2; ++q) {
-                    const int j = q / 2 * 4 + q % 2;       // u; v: j + 2
-                    const f32x4 x = acc[2 * i + ii][j], y = acc[2 * i + ii][j + 2];
-                    f32x4 r;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) r[t] = x[t] / (1.f + expf(-x[t])) * y[t];
-                    bf16x4 part[3];
-                    split4(r, part);
-                    char* const at = st + (ii * 16 + (tc.lane & 15)) * kStride + (q * 16 + 4 * (tc.lane >> 4)) * 2;
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(at + t * kRow) = part[t];
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int t = 0; t < 3; ++t)
-                copy_rows_out<32, kRow>(st + t * kRow, kStride, reinterpret_cast<char*>(a.p + t * a.third + row_base * a.ld + col_base / 2),
-                                        a.ld * 2, 32, tc.lane);
-            __builtin_amdgcn_wave_barrier();
-        }
-    }
-};
-
 // acc = da.  du = da v silu'(u) and dv = da silu(u) as thirds, in blocks of 32 columns of each in turn, as u and v are.
 struct EpiGateUpBackward {
     const float* uv;         // [rows, duv.ld]
     Thirds duv;
-    template <int kW>
-    __device__ __forceinline__ void operator()(const TileCoord<kW>& tc, const Accumulators<kW>& acc, char* lds) const {
+    __device__ __forceinline__ void operator()(const ThirdsCoord& tc, const ThirdsSums& acc, char* lds) const {
         constexpr int RW = kWaveRows<kW>, kRow = 2 * RW * 2, kStride = 3 * kRow + 16;
         const int col_base = 2 * tc.col0();                // packed column of this wavefront's block of 2 RW
         if (col_base >= duv.ld) return;
         char* const st = wave_stage(tc, lds);
-        constexpr int kTogether = kW == kLargeTile ? 4 : 4;      // tiles whose u and v are on their way together
+        constexpr int kTogether = 4;                       // tiles whose u and v are on their way together
 #pragma unroll
         for (int i = 0; i < kW; ++i) {                     // 16 rows per pass
             const int64_t row_base = tc.row0() + i * 16;
@@ -244,16 +210,122 @@ struct EpiGateUpBackward {
                 }
             }
             __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int t = 0; t < 3; ++t)
-                copy_rows_out<16, kRow>(st + t * kRow, kStride, reinterpret_cast<char*>(duv.p + t * duv.third + row_base * duv.ld + col_base),
-                                        duv.ld * 2, 16, tc.lane);
+            copy_thirds_out<16, kRow>(st, kStride, duv, row_base, col_base, 16, tc.lane);
             __builtin_amdgcn_wave_barrier();
         }
     }
 };
 
-// ---- products -----------------------------------------------------------------------------------
+// ---- forward ------------------------------------------------------------------------------------
+
+// 32 rows x 32 columns of a wavefront of gemm_floats, v[g] columns 8 g + 4 (lane >> 5) .. + 3 of row (lane & 31), to C and, if it is
+// there, to C3, from (row, column) on.
+__device__ __forceinline__ void put_square(char* st, int lane, const f32x4 (&v)[4], const FloatBlocks& C, const Thirds& C3, int64_t row,
+                                           int64_t column) {
+    constexpr int kStride = 128 + 16, kStride3 = 3 * 64 + 16;
+    const int r = lane & 31, half = lane >> 5;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {                          // the even columns of eight, then the odd ones
+        *reinterpret_cast<float2*>(st + r * kStride + g * 32 + half * 8) = make_float2(v[g][0], v[g][2]);
+        *reinterpret_cast<float2*>(st + r * kStride + g * 32 + 16 + half * 8) = make_float2(v[g][1], v[g][3]);
+    }
+    __builtin_amdgcn_wave_barrier();
+    copy_rows_out<32, 128>(st, kStride, reinterpret_cast<char*>(C.p + FloatBlocks::at(row, column, C.ld)), 128, 32, lane);
+    __builtin_amdgcn_wave_barrier();
+    if (C3.p == nullptr) return;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        bf16x4 part[3];
+        split4(v[g], part);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(st + r * kStride3 + t * 64 + (8 * g + 4 * half) * 2) = part[t];
+    }
+    __builtin_amdgcn_wave_barrier();
+    copy_thirds_out<32, 64>(st, kStride3, C3, row, column, 32, lane);
+    __builtin_amdgcn_wave_barrier();
+}
+template <int kJ>
+__device__ __forceinline__ void put_rows(char* st, int lane, const f32x16 (&acc)[kJ], float* C, int64_t ldc) {   // 32 rows, row-major
+    constexpr int kStride = 32 * kJ * 4 + 16;
+#pragma unroll
+    for (int j = 0; j < kJ; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<f32x4*>(st + (lane & 31) * kStride + (j * 32 + 8 * g + 4 * (lane >> 5)) * 4) =
+                f32x4{acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]};
+    __builtin_amdgcn_wave_barrier();
+    copy_rows_out<32, 32 * kJ * 4>(st, kStride, reinterpret_cast<char*>(C), ldc * 4, 32, lane);
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Gate and up projection, columns in blocks of 32 of each in turn: a = silu(u) v, and for a backward pass u and v as they are in
+// the product.
+struct EpiGateUp {
+    float* uv;               // [rows, 2 a.ld] or null
+    FloatBlocks a;
+    Thirds a3;
+    template <int kI, int kJ>
+    __device__ __forceinline__ void operator()(const FloatsCoord<kI, kJ>& tc, const f32x16 (&acc)[kI][kJ], char* st) const {
+        static_assert(kJ == 2, "a gate block and its up block");
+#pragma unroll
+        for (int i = 0; i < kI; ++i) {
+            const int64_t row = tc.row0 + 32 * i;
+            if (uv != nullptr) put_rows(st, tc.lane, acc[i], uv + row * 2 * a.ld + tc.col0, 2 * a.ld);
+            f32x4 r[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float x = acc[i][0][4 * g + t], y = acc[i][1][4 * g + t];
+                    r[g][t] = x / (1.f + expf(-x)) * y;
+                }
+            put_square(st, tc.lane, r, a, a3, row, tc.col0 / 2);
+        }
+    }
+};
+// A product that is an operand of others.
+struct EpiOperand {
+    FloatBlocks C;
+    Thirds C3;
+    template <int kI, int kJ>
+    __device__ __forceinline__ void operator()(const FloatsCoord<kI, kJ>& tc, const f32x16 (&acc)[kI][kJ], char* st) const {
+#pragma unroll
+        for (int i = 0; i < kI; ++i)
+#pragma unroll
+            for (int j = 0; j < kJ; ++j) {
+                f32x4 v[4];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) v[e / 4][e % 4] = acc[i][j][e];
+                put_square(st, tc.lane, v, C, C3, tc.row0 + 32 * i, tc.col0 + 32 * j);
+            }
+    }
+};
+// C row-major.
+struct EpiRows {
+    float* C;
+    int64_t ldc;
+    template <int kI, int kJ>
+    __device__ __forceinline__ void operator()(const FloatsCoord<kI, kJ>& tc, const f32x16 (&acc)[kI][kJ], char* st) const {
+#pragma unroll
+        for (int i = 0; i < kI; ++i) put_rows(st, tc.lane, acc[i], C + (int64_t)(tc.row0 + 32 * i) * ldc + tc.col0, ldc);
+    }
+};
+
+// The tile whose workgroups, shared out over the 256 CUs, have the least to do: the matrix pipes are shared by the workgroups of
+// a CU, so a CU's time is the number of its tiles times their size; the smaller tile counts 1.08 times its size.  By themselves
+// 128 x 128, 64 x 128 and 64 x 64 take at 8192 x 5632 x 1024 802 / 731 / 717 us, at 8192 x 1024 x 2816 332 / 336 / 341, at 8192 x 1024 x
+// 11264 1299 / 1325 / 1426; within a step, where the backward products have brought the clock down, the larger ones are ahead:
+// gate and up of 10,752 rows at 1024 -> 2816 871 / 916, steps of 5376 at 890 -> 849 478 / 503.  kPairs: a wavefront takes 64 columns.
+template <bool kPairs, class Epilogue>
+void launch_floats(const FloatsProblem& p, const Epilogue& epi, hipStream_t s) {
+    const int64_t large = (int64_t)(p.M / 128) * (p.N / 128);
+    constexpr int kSmallJ = kPairs ? 2 : 1, kPerLarge = 4 / kSmallJ;
+    const double cost_large = 4.0 * (double)ceil_div64(large, 256), cost_small = 1.08 * kSmallJ * (double)ceil_div64(kPerLarge * large, 256);
+    if (cost_large <= cost_small) gemm_floats<2, 2><<<(unsigned)large, 256, 0, s>>>(p, epi);
+    else gemm_floats<1, kSmallJ><<<(unsigned)(kPerLarge * large), 256, 0, s>>>(p, epi);
+}
+
+// ---- backward products -----------------------------------------------------------------------------------
 
 // A product of thirds among others of its launch.
 template <int kLayA, int kLayB, class Epilogue>
@@ -266,39 +338,28 @@ struct ThirdsProduct {
         p.N = ceil_div(p.N, tile) * tile;
         return p.M / tile * (p.N / tile) * p.splits;
     }
-    template <int kW, int kSlots>
-    __device__ __forceinline__ void run(int block, OperandRing<kW, kSlots>& smem) const {
-        gemm_tile<kLayA, kLayB, true, true>(p, epi, block - first, smem);
-    }
+    __device__ __forceinline__ void run(int block, ThirdsRing& smem) const { thirds_tile<kLayA, kLayB>(p, epi, block - first, smem); }
 };
 template <int kLayA, int kLayB, class Epilogue>
 ThirdsProduct<kLayA, kLayB, Epilogue> job(const GemmProblem& p, const Epilogue& epi) { return {p, epi, 0}; }
 
-template <int kW, int kSlots, class... Jobs>
-__global__ __launch_bounds__(kGemmThreads, kW == kLargeTile || kSlots > kRingSlots ? 1 : 2) void gemm_f32(Jobs... jobs) {
-    __shared__ OperandRing<kW, kSlots> smem;
-    const int block = blockIdx.x;
-    run_job(block, smem, jobs...);
-}
-inline int steps_of(const GemmProblem& p) { return ceil_div(kSegmentsOfThree * (p.K1 / kTileK), p.splits); }
 template <class... Jobs>
-void launch_products(int kW, hipStream_t s, Jobs... jobs) {
+__global__ __launch_bounds__(kGemmThreads, 1) void gemm_f32(Jobs... jobs) {
+    __shared__ ThirdsRing smem;
+    run_job((int)blockIdx.x, smem, jobs...);
+}
+template <class... Jobs>
+void launch_products(hipStream_t s, Jobs... jobs) {
     int grid = 0;
-    ((grid = place_job(jobs, 32 * kW, grid)), ...);
-    if (kW == kLargeTile) gemm_f32<kLargeTile, kRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
-    else if (grid <= 256 && std::max({steps_of(jobs.p)...}) >= kDeepSteps) gemm_f32<kSmallTile, kDeepRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
-    else gemm_f32<kSmallTile, kRingSlots><<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
+    ((grid = place_job(jobs, kThirdsUnit, grid)), ...);
+    gemm_f32<<<(unsigned)grid, kGemmThreads, 0, s>>>(jobs...);
 }
 
-// C = the sum over the parts of a split reduction, as thirds; parts are n floats (rows of C.ld) apart and in the row tiles of the
-// live rows (live.kept set) or all of them.
-__global__ __launch_bounds__(kThreads) void sum_parts_thirds(const float* parts, int n_parts, size_t n, Thirds C, const int32_t* n_kept,
-                                                            int max_chunks, int A) {
+// C = the sum over the parts of a split reduction, as thirds; parts are n floats (rows of C.ld) apart.
+__global__ __launch_bounds__(kThreads) void sum_parts_thirds(const float* parts, int n_parts, size_t n, Thirds C) {
     constexpr int kTogether = 4;      // loads under way together
-    size_t limit = n;
-    if (n_kept != nullptr) limit = min(n, (size_t)((live_rows(n_kept, max_chunks, A) + kTileM - 1) / kTileM * kTileM) * (size_t)C.ld);
     const size_t stride = (size_t)gridDim.x * kThreads * 4;
-    for (size_t i = ((size_t)blockIdx.x * kThreads + threadIdx.x) * 4; i < limit; i += stride) {
+    for (size_t i = ((size_t)blockIdx.x * kThreads + threadIdx.x) * 4; i < n; i += stride) {
         f32x4 acc = *reinterpret_cast<const f32x4*>(parts + i);
         for (int s0 = 1; s0 < n_parts; s0 += kTogether) {
             f32x4 v[kTogether];
@@ -311,7 +372,7 @@ __global__ __launch_bounds__(kThreads) void sum_parts_thirds(const float* parts,
         bf16x4 part[3];
         split4(acc, part);
 #pragma unroll
-        for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(C.p + t * C.third + i) = part[t];
+        for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(C.p + Thirds::at(i / C.ld, i % C.ld, C.ld) + t * kThirdsPart) = part[t];
     }
 }
 
@@ -328,16 +389,14 @@ __device__ inline float wave_sum(float x) {
     return x;
 }
 
-// One wavefront per row, four columns per lane and 256: the logits as the sum of their parts, log-softmax at the target bin,
-// entropy, ratio, clipped surrogate, and dz = coef * (onehot - softmax) + entropy part as thirds.  With a per-chunk ratio the
-// factor is not known yet: the first part of z <- onehot - softmax and the entropy part goes to `extra`; scale_rows makes dz of
-// them once the chunk ratios are known.
+// One wavefront per row, a column per lane and 64: log-softmax at the target bin, entropy, ratio, clipped surrogate, and dz =
+// coef * (onehot - softmax) + entropy part as thirds.  With a per-chunk ratio the factor is not known yet: z <- onehot - softmax
+// and the entropy part goes to `extra`; scale_rows makes dz of them once the chunk ratios are known.
 constexpr int kMaxV = 1024;
 struct LossArgs {
-    float* z;                // [n_parts][rows, ld]
-    int n_parts, V, ld;
-    size_t part_stride;
-    float* extra;            // [rows, V], unpadded
+    float* z;                // [rows, ld]
+    int V, ld;
+    float* extra;            // [rows, V]
     Thirds dz;               // p null: no backward pass
     RowMeta meta;
     const int32_t* n_kept;
@@ -347,7 +406,7 @@ struct LossArgs {
     RowOut out;
 };
 __global__ __launch_bounds__(kThreads) void loss_rows(LossArgs p) {
-    constexpr int kQ = kMaxV / 256;
+    constexpr int kQ = kMaxV / kWave;
     const int lane = threadIdx.x % kWave;
     const int64_t r = (int64_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
     const int64_t rows = live_rows(p.n_kept, p.max_chunks, p.A);
@@ -356,36 +415,28 @@ __global__ __launch_bounds__(kThreads) void loss_rows(LossArgs p) {
     const float scale = objective_scale(p.opt, rows);
     float* const zr = p.z + r * p.ld;
     const int b = p.meta.token[r];
-    f32x4 z[kQ];
-    float mx = -INFINITY, zt = 0.f;
+    const float zb = zr[b];
+    float z[kQ];
+    float mx = -INFINITY;
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
-        const int c = q * 256 + 4 * lane;
-        if (c >= p.ld) continue;
-        z[q] = *reinterpret_cast<const f32x4*>(zr + c);
-        for (int s = 1; s < p.n_parts; ++s) z[q] += *reinterpret_cast<const f32x4*>(zr + s * p.part_stride + c);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            if (c + t < p.V) mx = fmaxf(mx, z[q][t]);
-            if (c + t == b) zt = z[q][t];
-        }
+        const int j = q * kWave + lane;
+        z[q] = j < p.V ? zr[j] : -INFINITY;
+        mx = fmaxf(mx, z[q]);
     }
     mx = wave_max(mx);
     float se = 0.f, sz = 0.f;
 #pragma unroll
     for (int q = 0; q < kQ; ++q)
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            if (q * 256 + 4 * lane + t < p.V) {
-                const float e = expf(z[q][t] - mx);
-                se += e;
-                sz += e * z[q][t];
-            }
+        if (q * kWave + lane < p.V) {
+            const float e = expf(z[q] - mx);
+            se += e;
+            sz += e * z[q];
+        }
     se = wave_sum(se);
     sz = wave_sum(sz);
-    zt = wave_sum(zt);
     const float lse = mx + logf(se);
-    const float lp = zt - lse;
+    const float lp = zb - lse;
     const float H = lse - sz / se;                      // -sum p log p
     const float w = (p.opt.chunk_weight && live) ? p.opt.chunk_weight[r / p.A] : 1.f;
     const LossRow lr = loss_row(lp, p.meta.logp_old[r], p.meta.adv[r], w, p.opt, scale);
@@ -404,24 +455,23 @@ __global__ __launch_bounds__(kThreads) void loss_rows(LossArgs p) {
     const float ec = live ? p.opt.entropy_coef * scale : 0.f;
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
-        const int c = q * 256 + 4 * lane;
-        if (c >= p.ld) continue;
-        f32x4 g = {}, ent = {};
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            if (c + t < p.V) {
-                const float pr = expf(z[q][t] - lse);
-                g[t] = coef * ((c + t == b ? 1.f : 0.f) - pr);
-                ent[t] = ec * pr * (z[q][t] - lse + H);
-            }
+        const int j = q * kWave + lane;
+        if (j >= p.ld) continue;
+        float pg = 0.f, ent = 0.f;
+        if (j < p.V) {
+            const float pr = expf(z[q] - lse);
+            pg = coef * ((j == b ? 1.f : 0.f) - pr);
+            ent = ec * pr * (z[q] - lse + H);
+        }
         if (p.opt.chunk_ratio) {
-            *reinterpret_cast<f32x4*>(zr + c) = g;
-            if (live) store4(p.extra + r * p.V, c, p.V, ent);
+            zr[j] = pg;
+            if (live && j < p.V) p.extra[r * p.V + j] = ent;
         } else {
-            bf16x4 part[3];
-            split4(g + ent, part);
+            const float x[2] = {pg + ent, 0.f};
+            uint32_t part[3][1];
+            split_in_three(x, part);
 #pragma unroll
-            for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(p.dz.p + t * p.dz.third + r * p.ld + c) = part[t];
+            for (int t = 0; t < 3; ++t) reinterpret_cast<uint16_t*>(p.dz.p)[Thirds::at(r, j, p.dz.ld) + t * kThirdsPart] = (uint16_t)part[t][0];
         }
     }
 }
@@ -448,7 +498,7 @@ __global__ __launch_bounds__(kThreads) void scale_rows(const float* z, const flo
         bf16x4 part[3];
         split4(x, part);
 #pragma unroll
-        for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(dz.p + t * dz.third + i) = part[t];
+        for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(dz.p + Thirds::at(r, i - r * dz.ld, dz.ld) + t * kThirdsPart) = part[t];
     }
 }
 
@@ -458,48 +508,80 @@ int64_t padded(int64_t n) { return ceil_div64(n, kThirdsUnit) * kThirdsUnit; }
 int steps64(int64_t n) { return (int)ceil_div64(n, kTileK) * kTileK; }
 int64_t tiles256(int64_t n) { return ceil_div64(n, kTileM) * kTileM; }
 
-// Reduction splits of the products: of those with a fp32 result, into parts.
-struct F32Plan {
-    GroupPlan gate, down, logits, wdo, G;      // composed: Wdo and G; else down
-    GroupPlan level[3];                        // as written {dy, dWo}, {da, dWd}, {dX, dWgu}; composed {da, G}, {dWo, dWd}, {dX, dWgu}
+// Reduction splits of products that share a launch: those with the least estimated time (as plan_group of the bf16 path).  A
+// workgroup takes about 6 us to start and to write its tile and 1 us per step of 32 k; the launch takes what its longest
+// workgroup does, or the work shared out over 256 CUs and about half a workgroup more at the end; parts are written, read back
+// and added up at about 4 TB/s.  Each number of parts forced on its product at ten sizes: within 2 % of the best at seven of them,
+// 3 to 7 % at three.
+struct ProductShape {
+    int64_t M, N;
+    int steps;
+    int most_parts;        // 1: not to be split
 };
-// One product's plan: tile and, if it may be split, parts.  (The plans are those of the bf16 path, with six times the steps.  Each
-// tile and number of parts forced on its launch at six sizes: within 3 % of the best at five of them, 6 % at 5376 rows of 256.)
-GroupPlan plan_one(int64_t M, int64_t N, int64_t K, bool split, int shortest, float us_sum) {
-    return plan_group<1>({{tiles256(M), tiles256(N), kSegmentsOfThree * steps64(K) / kTileK, 1, split, shortest}}, us_sum);
-}
-F32Plan plan_step(const ActorShape& sh, int64_t Mp, bool composed) {
-    const int64_t d = sh.d, ff = sh.ff, V = sh.V;
-    const auto shape = [](int64_t M, int64_t N, int64_t K, bool split) {
-        return GroupShape{tiles256(M), tiles256(N), kSegmentsOfThree * steps64(K) / kTileK, 1, split};
-    };
-    F32Plan p{};
-    p.gate = plan_one(Mp, 2 * padded(ff), d, false, 1, 0.f);
-    if (composed) p.wdo = plan_one(ff, V, d, false, 1, 0.f);
-    else p.down = plan_one(Mp, d, ff, true, 16, 5.f);
-    p.logits = plan_one(Mp, V, composed ? ff : d, true, 8, 0.f);
-    if (composed) {
-        p.level[0] = plan_group<1>({shape(Mp, ff, V, false)}, 2.f);
-        p.G = plan_one(ff, V, Mp, true, 8, 5.f);
-        p.level[1] = plan_group<2>({shape(ff, d, V, false), shape(d, V, ff, true)}, 2.f);
-    } else {
-        p.level[0] = plan_group<2>({shape(Mp, d, V, false), shape(d, V, Mp, true)}, 2.f);
-        p.level[1] = plan_group<2>({shape(Mp, ff, d, false), shape(ff, d, Mp, true)}, 2.f);
+template <int kN>
+void plan_products(const ProductShape (&jobs)[kN], float us_sum, int (&splits)[kN]) {
+    constexpr float kUsPerStep = 1.f, kUsFixed = 6.f;
+    float best_us = 0.f;
+    for (int most : {8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 1 << 20}) {    // longest reduction of a workgroup
+        int parts[kN], longest = 0;
+        int64_t workgroups = 0;
+        float work = 0.f, sum = 0.f;
+        for (int q = 0; q < kN; ++q) {
+            const ProductShape& j = jobs[q];
+            const int s = parts[q] = std::max(1, std::min(j.most_parts, ceil_div(j.steps, most))), len = ceil_div(j.steps, s);
+            const int64_t n = ceil_div64(j.M, kThirdsUnit) * ceil_div64(j.N, kThirdsUnit) * s;
+            longest = std::max(longest, len);
+            workgroups += n;
+            work += (float)n * (kUsFixed + kUsPerStep * (float)len);
+            if (s > 1) sum += (float)(2 * s + 1) * (float)j.M * (float)j.N * (4 / 4e6f);
+        }
+        float us = kUsFixed + kUsPerStep * (float)longest;
+        if (workgroups > 256) us = std::max(us, work / 256 + 0.5f * us);
+        if (sum > 0.f) us += us_sum + sum;
+        if (best_us == 0.f || us < best_us) {
+            best_us = us;
+            for (int q = 0; q < kN; ++q) splits[q] = parts[q];
+        }
     }
-    GroupShape dX = shape(Mp, d, 2 * padded(ff), true);      // in two parts at most: one goes to dX itself, which the other is added to
-    dX.shortest = ceil_div(dX.steps, 2);
-    p.level[2] = plan_group<2>({dX, shape(d, 2 * padded(ff), Mp, true)}, 2.f);
-    // a small weight gradient in slices of 64 rows
-    if (d <= kTileK && ff <= kTileK) p.level[2].splits[1] = ceil_div((int)sh.rows_max(), kTileK);
+}
+struct F32Plan {
+    int G, dWo, dWd, dWgu, dX;      // parts of each
+};
+constexpr int kMaxParts = 64;
+F32Plan plan_step(const ActorShape& sh, int64_t Mp, bool composed) {
+    const int64_t d = sh.d, ff = sh.ff, V = sh.V, gu = 2 * padded(ff);
+    const auto shape = [](int64_t M, int64_t N, int64_t K, int most) { return ProductShape{M, N, steps64(K) / kThirdsK, most}; };
+    F32Plan p{1, 1, 1, 1, 1};
+    const auto two = [&](const ProductShape& a, const ProductShape& b, int& of_a, int& of_b) {
+        int s[2];
+        plan_products<2>({a, b}, 2.f, s);
+        of_a = s[0];
+        of_b = s[1];
+    };
+    int unsplit;
+    if (composed) {
+        int G[1];
+        plan_products<1>({shape(ff, V, Mp, kMaxParts)}, 5.f, G);
+        p.G = G[0];
+        two(shape(ff, d, V, 1), shape(d, V, ff, kMaxParts), unsplit, p.dWo);
+    } else {
+        two(shape(Mp, d, V, 1), shape(d, V, Mp, kMaxParts), unsplit, p.dWo);
+        two(shape(Mp, ff, d, 1), shape(ff, d, Mp, kMaxParts), unsplit, p.dWd);
+    }
+    // dX in two parts at most: one goes to dX itself, which the other is added to
+    two(shape(Mp, d, gu, 2), shape(d, gu, Mp, kMaxParts), p.dX, p.dWgu);
+    if (d <= 64 && ff <= 64) p.dWgu = ceil_div((int)sh.rows_max(), 64);       // a small weight gradient in slices of 64 rows
     return p;
 }
 
 struct F32Workspace {
-    Thirds Wgu, Wd, Wo, X, a, y, dz, dy, duv;
-    Thirds Wdo, G;           // composed evaluation: Wd Wo and a^T dz, both [ff, V]
+    FloatBlocks X, a, y, WguT, WdT, WoT;          // forward; weights with their columns as rows (composed: Wd as it is for WdT)
+    FloatBlocks WdoT;                             // composed evaluation: (Wd Wo)^T [V, ff]
+    Thirds Wgu, Wd, Wo, X3, a3, y3, dz, dy, duv;  // backward
+    Thirds WdoT3, G;                              // composed: the same, and a^T dz [ff, V]
     float *uv, *z, *z_extra;
     float* dX_part;          // the second of two parts of dX
-    float* parts_y;          // parts of y (composed: of G)
+    float* parts_G;          // composed
     float *parts_o, *parts_d, *parts_g, *parts_u;   // of the weight gradients, where they are computed in parts
     F32Plan plan;
     RowMeta meta;
@@ -514,25 +596,19 @@ F32Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool composed) {
     Carver c(ws);
     F32Workspace w{};
     const int64_t Mp = w.Mp = tiles256(sh.rows_max());
-    const auto thirds = [&](int64_t rows, int64_t columns) {
-        Thirds t{};
-        t.ld = padded(columns);
-        t.third = tiles256(rows) * t.ld;
-        t.p = c.take<bf16>((size_t)(3 * t.third + kTileN));      // a tile may read beyond the last row's columns
-        return t;
-    };
+    const auto thirds = [&](int64_t rows, int64_t columns) { return Thirds{c.take<bf16>((size_t)(3 * padded(rows) * padded(columns))), padded(columns)}; };
+    const auto floats = [&](int64_t rows, int64_t columns) { return FloatBlocks{c.take<float>((size_t)(padded(rows) * padded(columns))), padded(columns)}; };
     w.plan = plan_step(sh, Mp, composed);
     const F32Plan& plan = w.plan;
-    const int64_t ffp = padded(sh.ff), Vp = padded(sh.V), dp = padded(sh.d);
-    w.Wgu = thirds(sh.d, 2 * ffp);
-    w.Wd = thirds(sh.ff, sh.d);
-    w.Wo = thirds(sh.d, sh.V);
-    w.X = thirds(Mp, sh.d);
-    w.a = thirds(Mp, sh.ff);
-    if (composed) w.Wdo = thirds(sh.ff, sh.V);
-    else w.y = thirds(Mp, sh.d);
-    if (!composed && plan.down.splits[0] > 1) w.parts_y = c.take<float>((size_t)plan.down.splits[0] * Mp * dp);
-    w.z = c.take<float>((size_t)plan.logits.splits[0] * Mp * Vp);
+    const int64_t ffp = padded(sh.ff), Vp = padded(sh.V);
+    w.X = floats(Mp, sh.d);
+    w.a = floats(Mp, sh.ff);
+    w.WguT = floats(2 * ffp, sh.d);
+    w.WdT = composed ? floats(sh.ff, sh.d) : floats(sh.d, sh.ff);
+    w.WoT = floats(sh.V, sh.d);
+    if (composed) w.WdoT = floats(sh.V, sh.ff);
+    else w.y = floats(Mp, sh.d);
+    w.z = c.take<float>((size_t)Mp * Vp);
     w.meta.token = c.take<uint8_t>(Mp);
     w.meta.logp_old = c.take<float>(Mp);
     w.meta.adv = c.take<float>(Mp);
@@ -543,26 +619,33 @@ F32Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool composed) {
     w.out.entropy = c.take<float>(Mp);
     w.out.coef = c.take<float>(Mp);
     const size_t M = (size_t)sh.rows_max(), d = sh.d, ff = sh.ff, V = sh.V;
-    w.uv = c.take<float>((size_t)Mp * 2 * ffp);
-    const Thirds dz = thirds(Mp, V);
-    Thirds dy{};
-    if (!composed) dy = thirds(Mp, d);
-    w.duv = thirds(Mp, 2 * ffp);
-    if (composed) w.G = thirds(ff, V);
-    if (composed) w.parts_y = c.take<float>((size_t)plan.G.splits[0] * ffp * Vp);
-    const int o = composed ? plan.level[1].splits[1] : plan.level[0].splits[1], dd = composed ? 1 : plan.level[1].splits[1];
-    const int gu = plan.level[2].splits[1];
-    if (o > 1) w.parts_o = c.take<float>(o * d * V);
-    if (dd > 1) w.parts_d = c.take<float>(dd * ff * d);
+    F32Workspace b{};                     // of the backward pass
+    b.uv = c.take<float>((size_t)Mp * 2 * ffp);
+    b.Wgu = thirds(d, 2 * ffp);
+    b.Wd = thirds(ff, d);
+    b.Wo = thirds(d, V);
+    b.X3 = thirds(Mp, d);
+    b.a3 = thirds(Mp, ff);
+    b.dz = thirds(Mp, V);
+    b.duv = thirds(Mp, 2 * ffp);
+    if (composed) {
+        b.WdoT3 = thirds(V, ff);
+        b.G = thirds(ff, V);
+        b.parts_G = c.take<float>((size_t)plan.G * ffp * Vp);
+    } else {
+        b.y3 = thirds(Mp, d);
+        b.dy = thirds(Mp, d);
+    }
+    const int o = plan.dWo, dd = plan.dWd, gu = plan.dWgu;
+    if (o > 1) b.parts_o = c.take<float>(o * d * V);
+    if (dd > 1) b.parts_d = c.take<float>(dd * ff * d);
     if (bwd) {
-        w.dz = dz;
-        w.dy = dy;
+        w.uv = b.uv; w.Wgu = b.Wgu; w.Wd = b.Wd; w.Wo = b.Wo; w.X3 = b.X3; w.a3 = b.a3; w.y3 = b.y3; w.dz = b.dz; w.dy = b.dy; w.duv = b.duv;
+        w.WdoT3 = b.WdoT3; w.G = b.G; w.parts_G = b.parts_G; w.parts_o = b.parts_o; w.parts_d = b.parts_d;
         w.z_extra = c.take<float>(M * V);
         w.dX_part = c.take<float>(M * d);
         if (gu > 1) w.parts_g = c.take<float>(2 * gu * d * ff);
         w.parts_u = w.parts_g + gu * d * ff;
-    } else {
-        w.uv = nullptr;
     }
     w.bytes = c.used();
     return w;
@@ -584,8 +667,8 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t
     // C[M, N] = sum_k A(m, k) B(n, k) with the batch's rows as M or K (role) or not at all
     const auto product = [&](const Thirds& A, const Thirds& B, int m, int n, int k, int role, int splits = 1) {
         GemmProblem p{};
-        p.A = A.p; p.A2 = A.p + A.third; p.lda = A.ld;
-        p.B = B.p; p.B2 = B.p + B.third; p.ldb = B.ld;
+        p.A = p.A2 = A.p; p.lda = A.ld;
+        p.B = p.B2 = B.p; p.ldb = B.ld;
         p.M = m; p.N = n; p.K1 = steps64(k); p.splits = splits;
         if (role != kRowsUnused) { p.kept = io.n_kept; p.kept_max = sh.max_chunks; p.rows_per_kept = sh.A; }
         p.rows_role = role;
@@ -599,44 +682,41 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t
         sums.add(parts, splits, (size_t)size, (size_t)size, C);
         return EpiFloats{parts, n, size, m, n};
     };
-    const auto sum_thirds = [&](const float* parts, int n_parts, int64_t rows, const Thirds& C, bool batch) {
-        const size_t n = (size_t)rows * C.ld;
-        sum_parts_thirds<<<(unsigned)std::min<size_t>((n / 4 + kThreads - 1) / kThreads, 2048), kThreads, 0, s>>>(
-            parts, n_parts, n, C, batch ? io.n_kept : nullptr, sh.max_chunks, sh.A);
-    };
 
-    ThirdsList weights{};
-    const int d_rows = (int)padded(d), ff_rows = (int)padded(ff);
-    weights.add(ThirdsJob{static_cast<const float*>(io.Wg), w.Wgu, d, ff, d_rows, kPackGate});
-    weights.add(ThirdsJob{static_cast<const float*>(io.Wu), w.Wgu, d, ff, d_rows, kPackUp});
-    weights.add(ThirdsJob{static_cast<const float*>(io.Wd), w.Wd, ff, d, ff_rows, kPackNone});
-    weights.add(ThirdsJob{static_cast<const float*>(io.Wo), w.Wo, d, V, d_rows, kPackNone});
-    int rc = launch_prepare_f32(sh, io, w.X, Mp, w.meta, weights, static_cast<float*>(io.dX), s);
+    const Thirds none3{};
+    const FloatBlocks none{};
+    const float *const Wg = static_cast<const float*>(io.Wg), *const Wu = static_cast<const float*>(io.Wu);
+    const float *const Wd = static_cast<const float*>(io.Wd), *const Wo = static_cast<const float*>(io.Wo);
+    WeightJobs weights{};
+    weights.add(WeightJob{Wg, w.WguT, none3, d, ff, true, kPackGate});
+    weights.add(WeightJob{Wu, w.WguT, none3, d, ff, true, kPackUp});
+    weights.add(WeightJob{Wd, w.WdT, none3, ff, d, !io.composed, kPackNone});
+    weights.add(WeightJob{Wo, w.WoT, none3, d, V, true, kPackNone});
+    if (io.dX) weights.add(WeightJob{Wg, none, w.Wgu, d, ff, false, kPackGate});
+    if (io.dX) weights.add(WeightJob{Wu, none, w.Wgu, d, ff, false, kPackUp});
+    if (bwd && (grads || !io.composed)) weights.add(WeightJob{Wd, none, w.Wd, ff, d, false, kPackNone});
+    if (bwd && (grads || !io.composed)) weights.add(WeightJob{Wo, none, w.Wo, d, V, false, kPackNone});
+    int rc = launch_prepare_f32(sh, io, w.X, grads ? w.X3 : none3, Mp, w.meta, weights, static_cast<float*>(io.dX), s);
     if (rc != PCM_OK) return rc;
     {
         StageTimer t(ST_F32_FORWARD, s);
-        launch_products(plan.gate.kW, s, job<kRowsByK, kKByRows>(product(w.X, w.Wgu, Mp, 2 * ffp, d, kRowsAreM), EpiGateUp{w.uv, w.a}));
-        if (io.composed) {                                                                             // W_do = Wd Wo
-            launch_products(plan.wdo.kW, s, job<kRowsByK, kKByRows>(product(w.Wd, w.Wo, ffp, Vp, d, kRowsUnused), EpiThirds{w.Wdo, ffp}));
-        } else if (plan.down.splits[0] == 1) {
-            launch_products(plan.down.kW, s, job<kRowsByK, kKByRows>(product(w.a, w.Wd, Mp, dp, ff, kRowsAreM), EpiThirds{w.y, Mp}));
-        } else {
-            const int n_parts = plan.down.splits[0];
-            launch_products(plan.down.kW, s, job<kRowsByK, kKByRows>(product(w.a, w.Wd, Mp, dp, ff, kRowsAreM, n_parts),
-                                                                     EpiFloats{w.parts_y, dp, (int64_t)Mp * dp, Mp, dp}));
-            sum_thirds(w.parts_y, n_parts, Mp, w.y, true);
+        // C[m, n] = sum_k A(m, k) B(n, k)
+        const auto forward = [&](const FloatBlocks& A, const FloatBlocks& B, int m, int n, int k, bool batch) {
+            return FloatsProblem{A.p, B.p, A.ld, B.ld, m, n, (int)ceil_div64(k, 32) * 32, batch ? io.n_kept : nullptr, sh.max_chunks, sh.A};
+        };
+        launch_floats<true>(forward(w.X, w.WguT, Mp, 2 * ffp, d, true), EpiGateUp{w.uv, w.a, grads ? w.a3 : none3}, s);
+        if (io.composed) {                                                                             // (Wd Wo)^T, then z = a Wd Wo
+            launch_floats<false>(forward(w.WoT, w.WdT, Vp, ffp, d, false), EpiOperand{w.WdoT, w.WdoT3}, s);
+            launch_floats<false>(forward(w.a, w.WdoT, Mp, Vp, ff, true), EpiRows{w.z, Vp}, s);
+        } else {                                                                                       // y = a Wd, z = y Wo
+            launch_floats<false>(forward(w.a, w.WdT, Mp, dp, ff, true), EpiOperand{w.y, grads ? w.y3 : none3}, s);
+            launch_floats<false>(forward(w.y, w.WoT, Mp, Vp, d, true), EpiRows{w.z, Vp}, s);
         }
-        const int n_parts = plan.logits.splits[0];                                                     // z = y Wo, or a W_do
-        launch_products(plan.logits.kW, s,
-                        job<kRowsByK, kKByRows>(io.composed ? product(w.a, w.Wdo, Mp, Vp, ff, kRowsAreM, n_parts)
-                                                            : product(w.y, w.Wo, Mp, Vp, d, kRowsAreM, n_parts),
-                                                EpiFloats{w.z, Vp, (int64_t)Mp * Vp, Mp, Vp}));
     }
     {
         StageTimer t(ST_F32_LOSS, s);
         loss_rows<<<(unsigned)(Mp / (kThreads / kWave)), kThreads, 0, s>>>(
-            LossArgs{w.z, plan.logits.splits[0], V, Vp, (size_t)Mp * Vp, w.z_extra, w.dz, w.meta, io.n_kept, sh.max_chunks, sh.A, io.opt,
-                     io.logp_out, w.out});
+            LossArgs{w.z, V, Vp, w.z_extra, w.dz, w.meta, io.n_kept, sh.max_chunks, sh.A, io.opt, io.logp_out, w.out});
     }
     if (io.opt.chunk_ratio) {
         rc = launch_chunk_ratio(sh, io, w.meta, w.out, 0, M, s);
@@ -653,36 +733,34 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t
         StageTimer t(ST_F32_BACKWARD, s);
         const EpiGateUpBackward swiglu{w.uv, w.duv};
         if (io.composed) {
-            const auto da = job<kRowsByK, kRowsByK>(product(w.dz, w.Wdo, Mp, ffp, V, kRowsAreM), swiglu);      // da = dz W_do^T
-            launch_products(plan.level[0].kW, s, da);
+            launch_products(s, job<kRowsByK, kKByRows>(product(w.dz, w.WdoT3, Mp, ffp, V, kRowsAreM), swiglu));   // da = dz (Wd Wo)^T
             if (grads) {
-                const int n_parts = plan.G.splits[0];                                                  // G = a^T dz
-                launch_products(plan.G.kW, s, job<kKByRows, kKByRows>(product(w.a, w.dz, ffp, Vp, Mp, kRowsAreK, n_parts),
-                                                                      EpiFloats{w.parts_y, Vp, (int64_t)ffp * Vp, ffp, Vp}));
-                sum_thirds(w.parts_y, n_parts, ffp, w.G, false);
+                const size_t n = (size_t)ffp * Vp;                                                     // G = a^T dz
+                launch_products(s, job<kKByRows, kKByRows>(product(w.a3, w.dz, ffp, Vp, Mp, kRowsAreK, plan.G), EpiFloats{w.parts_G, Vp, (int64_t)n, ffp, Vp}));
+                sum_parts_thirds<<<(unsigned)std::min<size_t>((n / 4 + kThreads - 1) / kThreads, 2048), kThreads, 0, s>>>(w.parts_G, plan.G, n, w.G);
                 const auto dWd = job<kRowsByK, kRowsByK>(product(w.G, w.Wo, ff, d, V, kRowsUnused), EpiFloats{io.dWd, d, 0, ff, d});   // G Wo^T
-                const int o = plan.level[1].splits[1];
+                const int o = plan.dWo;
                 const auto dWo = job<kKByRows, kKByRows>(product(w.Wd, w.G, d, V, ff, kRowsUnused, o), floats(o, w.parts_o, io.dWo, d, V));   // Wd^T G
-                launch_products(plan.level[1].kW, s, dWo, dWd);
+                launch_products(s, dWo, dWd);
             }
         } else {
             const auto dy = job<kRowsByK, kRowsByK>(product(w.dz, w.Wo, Mp, dp, V, kRowsAreM), EpiThirds{w.dy, Mp});     // dy = dz Wo^T
             const auto da = job<kRowsByK, kRowsByK>(product(w.dy, w.Wd, Mp, ffp, d, kRowsAreM), swiglu);                 // da = dy Wd^T
             if (grads) {
-                const int o = plan.level[0].splits[1], dd = plan.level[1].splits[1];
-                launch_products(plan.level[0].kW, s, job<kKByRows, kKByRows>(product(w.y, w.dz, d, V, Mp, kRowsAreK, o), floats(o, w.parts_o, io.dWo, d, V)), dy);
-                launch_products(plan.level[1].kW, s, da, job<kKByRows, kKByRows>(product(w.a, w.dy, ff, d, Mp, kRowsAreK, dd), floats(dd, w.parts_d, io.dWd, ff, d)));
+                const int o = plan.dWo, dd = plan.dWd;
+                launch_products(s, job<kKByRows, kKByRows>(product(w.y3, w.dz, d, V, Mp, kRowsAreK, o), floats(o, w.parts_o, io.dWo, d, V)), dy);
+                launch_products(s, da, job<kKByRows, kKByRows>(product(w.a3, w.dy, ff, d, Mp, kRowsAreK, dd), floats(dd, w.parts_d, io.dWd, ff, d)));
             } else {
-                launch_products(plan.level[0].kW, s, dy);
-                launch_products(plan.level[1].kW, s, da);
+                launch_products(s, dy);
+                launch_products(s, da);
             }
         }
         float* const out_X = static_cast<float*>(io.dX);
-        const int x = plan.level[2].splits[0];                                                         // dX = du Wg^T + dv Wu^T
+        const int x = plan.dX;                                                         // dX = du Wg^T + dv Wu^T
         const auto dX = job<kRowsByK, kRowsByK>(product(w.duv, w.Wgu, Mp, d, 2 * ffp, kRowsAreM, x), EpiFloats{out_X, d, w.dX_part - out_X, M, d});
         if (out_X && x > 1) sums.add(w.dX_part, 1, (size_t)M * d, (size_t)M * d, out_X, true, nullptr, d);
         if (grads) {
-            const int gu = plan.level[2].splits[1];                                                    // dWg = X^T du, dWu = X^T dv
+            const int gu = plan.dWgu;                                                    // dWg = X^T du, dWu = X^T dv
             EpiFloatsPair epi{{io.dWg, io.dWu}, 0, d, ff};
             if (gu > 1) {
                 const size_t n = (size_t)d * ff;
@@ -690,11 +768,11 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t
                 sums.add(w.parts_u, gu, n, n, io.dWu);
                 epi = EpiFloatsPair{{w.parts_g, w.parts_u}, (int64_t)n, d, ff};
             }
-            const auto dWgu = job<kKByRows, kKByRows>(product(w.X, w.duv, d, 2 * ffp, Mp, kRowsAreK, gu), epi);
-            if (io.dX) launch_products(plan.level[2].kW, s, dX, dWgu);
-            else launch_products(plan.level[2].kW, s, dWgu);
+            const auto dWgu = job<kKByRows, kKByRows>(product(w.X3, w.duv, d, 2 * ffp, Mp, kRowsAreK, gu), epi);
+            if (io.dX) launch_products(s, dX, dWgu);
+            else launch_products(s, dWgu);
         } else {
-            launch_products(plan.level[2].kW, s, dX);
+            launch_products(s, dX);
         }
     }
     return launch_finish(sh, io, w.out, sums, FinalPanel{}, true, SumsqLists{}, s);

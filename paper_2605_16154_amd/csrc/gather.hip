@@ -172,18 +172,23 @@ __device__ __forceinline__ void load_eight(const float* row, int c, int C, float
         for (int t = 0; t < 8; ++t) x[t] = c + t < C ? row[c + t] : 0.f;
     }
 }
-__device__ __forceinline__ void store_thirds(const float (&x)[8], bf16* at, int64_t third) {
+__device__ __forceinline__ void store_thirds(const float (&x)[8], bf16* at) {
     uint32_t part[3][4];
     split_in_three(x, part);
 #pragma unroll
-    for (int t = 0; t < 3; ++t) *reinterpret_cast<uint4*>(at + t * third) = make_uint4(part[t][0], part[t][1], part[t][2], part[t][3]);
+    for (int t = 0; t < 3; ++t) *reinterpret_cast<uint4*>(at + t * kThirdsPart) = make_uint4(part[t][0], part[t][1], part[t][2], part[t][3]);
 }
-// The fp32 path's counterpart of prepare_step (see launch_prepare_f32).  Bound by memory: four bytes read and six written per
-// value; every thread has four groups of eight values under way.
+__device__ __forceinline__ void store_floats(const float (&x)[8], float* at) {
+    *reinterpret_cast<float4*>(at) = make_float4(x[0], x[2], x[4], x[6]);
+    *reinterpret_cast<float4*>(at + 4) = make_float4(x[1], x[3], x[5], x[7]);
+}
+// The fp32 path's counterpart of prepare_step (see launch_prepare_f32).  Bound by memory: four bytes read and four or six written
+// per value; every thread has four groups of eight values under way.
 struct PrepareF32 {
     GatherArgs<float> gather;    // X unused
-    Thirds X;
-    ThirdsList weights;
+    FloatBlocks X;
+    Thirds X3;
+    WeightJobs weights;
     float* dX;
     int gather_blocks;
 };
@@ -214,38 +219,63 @@ __device__ inline void gather_rows_f32(const PrepareF32& p, int block) {
         }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            const int e = base + u * kThreads, row = e / groups;
-            if (e < total) store_thirds(x[u], p.X.p + (r0 + row) * p.X.ld + (e - row * groups) * 8, p.X.third);
+            const int e = base + u * kThreads, row = e / groups, c = (e - row * groups) * 8;
+            if (e >= total) continue;
+            store_floats(x[u], p.X.p + FloatBlocks::at(r0 + row, c, p.X.ld));
+            if (p.X3.p != nullptr) store_thirds(x[u], p.X3.p + Thirds::at(r0 + row, c, p.X3.ld));
         }
     }
 }
-__device__ inline void split_weights(const ThirdsList& list, int block) {
+__device__ inline void lay_out_weights(const WeightJobs& list, int block) {
     int which = 0;
 #pragma unroll
-    for (int q = 1; q < ThirdsList::kMax; ++q) which += q < list.n && block >= list.first[q] ? 1 : 0;
-    const ThirdsJob job = list.job[which];
-    const int groups = (int)(job.mode == kPackNone ? job.dst.ld : job.dst.ld / 2) / 8;
-    const int64_t total = (int64_t)job.rows * groups, e0 = (int64_t)(block - list.first[which]) * ThirdsList::kUnits + threadIdx.x;
-    constexpr int kUnroll = ThirdsList::kUnits / kThreads;
+    for (int q = 1; q < WeightJobs::kMax; ++q) which += q < list.n && block >= list.first[q] ? 1 : 0;
+    const WeightJob job = list.job[which];
+    const int rows = (job.R + kThirdsUnit - 1) / kThirdsUnit * kThirdsUnit, columns = (job.C + kThirdsUnit - 1) / kThirdsUnit * kThirdsUnit;
+    const int64_t total = (int64_t)rows * columns / 8, e0 = (int64_t)(block - list.first[which]) * WeightJobs::kUnits + threadIdx.x;
+    constexpr int kUnroll = WeightJobs::kUnits / kThreads;
+    auto packed = [&](int c) { return job.mode == kPackNone ? c : c / 32 * 64 + c % 32 + (job.mode == kPackUp ? 32 : 0); };
+    // The unit e: eight columns of a row; transposed, eight rows of a column, a wavefront taking 16 columns of 32 rows.
+    auto place = [&](int64_t e, int& row, int& c) {
+        if (!job.transposed) {
+            const int groups = columns / 8;
+            row = (int)(e / groups);
+            c = (int)(e - (int64_t)row * groups) * 8;
+        } else {
+            const int64_t wave = e / kWave;
+            const int lane = (int)(e % kWave), across = columns / 16;
+            row = (int)(wave / across) * 32 + lane / 16 * 8;
+            c = (int)(wave % across) * 16 + lane % 16;
+        }
+    };
     float x[kUnroll][8];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
         const int64_t e = e0 + u * kThreads;
-        const int row = (int)(e / groups), c = (int)(e - (int64_t)row * groups) * 8;
-        load_eight(job.src + (int64_t)min(row, job.R - 1) * job.C, c, e < total && row < job.R ? job.C : 0, x[u]);
+        int row = 0, c = 0;
+        if (e < total) place(e, row, c);
+        if (!job.transposed) {
+            load_eight(job.src + (int64_t)min(row, job.R - 1) * job.C, c, e < total && row < job.R ? job.C : 0, x[u]);
+        } else {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) x[u][t] = e < total && c < job.C && row + t < job.R ? job.src[(int64_t)(row + t) * job.C + c] : 0.f;
+        }
     }
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
         const int64_t e = e0 + u * kThreads;
-        const int row = (int)(e / groups), c = (int)(e - (int64_t)row * groups) * 8;
-        const int to = job.mode == kPackNone ? c : c / 32 * 64 + c % 32 + (job.mode == kPackUp ? 32 : 0);
-        if (e < total) store_thirds(x[u], job.dst.p + (int64_t)row * job.dst.ld + to, job.dst.third);
+        if (e >= total) continue;
+        int row, c;
+        place(e, row, c);
+        if (job.transposed) store_floats(x[u], job.to.p + FloatBlocks::at(packed(c), row, job.to.ld));
+        else if (job.to.p != nullptr) store_floats(x[u], job.to.p + FloatBlocks::at(row, packed(c), job.to.ld));
+        else store_thirds(x[u], job.to3.p + Thirds::at(row, packed(c), job.to3.ld));
     }
 }
 __global__ __launch_bounds__(kThreads) void prepare_step_f32(PrepareF32 p) {
     const int block = blockIdx.x;
     if (block < p.gather_blocks) gather_rows_f32(p, block);
-    else split_weights(p.weights, block - p.gather_blocks);
+    else lay_out_weights(p.weights, block - p.gather_blocks);
 }
 
 constexpr int kFinishThreads = 1024;
@@ -543,13 +573,13 @@ int launch_live_rows(const ActorShape& sh, const ActorIO& io, const uint8_t* cli
     return launch_status();
 }
 
-int launch_prepare_f32(const ActorShape& sh, const ActorIO& io, const Thirds& X, int64_t rows_pad, RowMeta meta,
-                       const ThirdsList& weights, float* dX, hipStream_t s) {
+int launch_prepare_f32(const ActorShape& sh, const ActorIO& io, const FloatBlocks& X, const Thirds& X3, int64_t rows_pad, RowMeta meta,
+                       const WeightJobs& weights, float* dX, hipStream_t s) {
     StageTimer t(ST_GATHER, s);
     const GatherArgs<float> gather{static_cast<const float*>(io.hidden), io.tokens, io.logp_old, io.adv, io.kept_idx, io.n_kept,
                                    sh.max_chunks, sh.T, sh.N, sh.A, sh.V, sh.d, 0, rows_pad, nullptr, meta};
     const int blocks = (int)ceil_div64(rows_pad, kRowsPerBlock);
-    prepare_step_f32<<<(unsigned)(blocks + weights.blocks), kThreads, 0, s>>>(PrepareF32{gather, X, weights, dX, blocks});
+    prepare_step_f32<<<(unsigned)(blocks + weights.blocks), kThreads, 0, s>>>(PrepareF32{gather, X, X3, weights, dX, blocks});
     return launch_status();
 }
 

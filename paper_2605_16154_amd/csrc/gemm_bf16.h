@@ -74,8 +74,7 @@ struct GemmProblem {
     const bf16* A;    // M x K1 operand, leading dimension lda (layout given by the kernel's template arguments)
     const bf16* B;    // N x K1 operand, leading dimension ldb
     const bf16* A2;   // optional second reduction segment (same M, N, layouts and leading dimensions), K2 columns;
-    const bf16* B2;   // when K2 == 0 both must still point at valid operands (A, B); of fp32 operands as three bf16 matrices each,
-                      // equally far apart (kThree), the second ones
+    const bf16* B2;   // when K2 == 0 both must still point at valid operands (A, B)
     int64_t lda, ldb;
     int M, N, K1, K2;  // M, N multiples of 256; K1, K2 multiples of 64
     int splits;        // reduction split (grid multiplies by it); epilogue must combine partials
@@ -279,14 +278,8 @@ struct OperandRing {
     __attribute__((aligned(1024))) __bf16 data[kRingBytes<kW, kSlots> / 2];   // [slot][row][64]
 };
 
-// A product of fp32 operands, each the sum of three bf16 matrices of the same shape (kThree, see split_in_three): six of the nine
-// products of their parts, as that many segments of one reduction, the small ones first; the other three are below 2^-23 of
-// the whole.  Part of the left and of the right operand in segment q: bits 4 q .. 4 q + 3.
-constexpr int kSegmentsOfThree = 6;
-constexpr uint32_t kLeftParts = 0x001102, kRightParts = 0x010120;
-
 // The work of workgroup `block` of a product; smem: the kernel's LDS.  kShared: one of several products of a launch.
-template <int kLayA, int kLayB, bool kShared, bool kThree, class Epilogue, int kW, int kSlots>
+template <int kLayA, int kLayB, bool kShared, class Epilogue, int kW, int kSlots>
 __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& epi, int block, OperandRing<kW, kSlots>& smem) {
     constexpr int TM = kTile<kW>, TN = kTile<kW>;
     constexpr uint32_t kTileBytes = TM * kTileK * 2;             // one operand tile
@@ -317,7 +310,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& 
     if (!tile_of_workgroup<kW>(block % n_tiles, n_tiles, live_m, tiles_n, tm, tn)) return;   // before any barrier
     const int m0 = tm * TM, n0 = n_first + tn * TN;
     // reduction range of this workgroup, in 64-wide steps over the concatenation of both segments
-    const int steps1 = k1 / kTileK, steps_all = kThree ? kSegmentsOfThree * steps1 : steps1 + p.K2 / kTileK;
+    const int steps1 = k1 / kTileK, steps_all = steps1 + p.K2 / kTileK;
     const int per_split = (steps_all + p.splits - 1) / p.splits;
     const int step_begin = split * per_split;
     const int step_end = min(steps_all, step_begin + per_split);
@@ -351,22 +344,19 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& 
         const bf16* s1 = sel != nullptr ? *sel : (operand == 0 ? p.A : p.B);
         const bf16* s2 = sel != nullptr ? s1 : (operand == 0 ? p.A2 : p.B2);
         if (layout == kRowsByK) {
-            // (kThree: the wavefront's rows in the origin, so that lane offsets stay below 2^32 for rows of up to 32 million)
-            const uint32_t row = (kThree ? 0u : (uint32_t)wave * (8u * kW)) + (uint32_t)(lane >> 3);   // + 8 r for load r
-            const int64_t first = kThree ? (int64_t)(wave * 8 * kW) * ld : 0;
+            const uint32_t row = (uint32_t)wave * (8u * kW) + (uint32_t)(lane >> 3);   // + 8 r for load r
 #pragma unroll
             for (uint32_t var = 0; var < 4; ++var) {                                 // the swizzle uses row bit 3
                 const uint32_t piece = (uint32_t)swizzle_piece((lane >> 3) + 8 * (var & 1), lane & 7);
                 lane_off[operand][var] = (row * ld + piece * 8u) * 2u;
             }
             load_stride[operand] = 16u * ld;
-            seg_origin[operand][0] = tile_address<kShared>(s1 + (int64_t)row0 * ld + first);
-            seg_origin[operand][1] = tile_address<kShared>(s2 + (int64_t)row0 * ld + first);
+            seg_origin[operand][0] = tile_address<kShared>(s1 + (int64_t)row0 * ld);
+            seg_origin[operand][1] = tile_address<kShared>(s2 + (int64_t)row0 * ld);
             k_step_bytes[operand] = kTileK * 2;
         } else {
             constexpr int kLanes = 4 * kW;                                            // lanes per k-row
-            const uint32_t krow = (kThree ? 0u : (uint32_t)wave * 16u) + (uint32_t)(lane / kLanes);   // + (16 / kW) r for load r
-            const int64_t first = kThree ? (int64_t)(wave * 16) * ld : 0;
+            const uint32_t krow = (uint32_t)wave * 16u + (uint32_t)(lane / kLanes);   // + (16 / kW) r for load r
 #pragma unroll
             for (uint32_t var = 0; var < 4; ++var) {                                  // bits 0, 1 and 3 of the k-row
                 const int k = lane / kLanes + (kW == kLargeTile ? 2 * (int)(var & 1) + 8 * (int)(var >> 1) : 8 * (int)(var & 1));
@@ -374,17 +364,12 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& 
                 lane_off[operand][var] = (krow * ld + piece * 8u) * 2u;
             }
             load_stride[operand] = (32u / kW) * ld;
-            seg_origin[operand][0] = tile_address<kShared>(s1 + row0 + first);
-            seg_origin[operand][1] = tile_address<kShared>(s2 + row0 + first);
+            seg_origin[operand][0] = tile_address<kShared>(s1 + row0);
+            seg_origin[operand][1] = tile_address<kShared>(s2 + row0);
             k_step_bytes[operand] = (uint32_t)kTileK * ld * 2u;
         }
     }
-    auto third_origin = [&](int operand, int segment) {           // kThree: of the part that a segment takes
-        const uint32_t part = ((operand == 0 ? kLeftParts : kRightParts) >> (4 * segment)) & 15u;
-        return seg_origin[operand][0] + (int64_t)part * (seg_origin[operand][1] - seg_origin[operand][0]);
-    };
     auto tile_origin = [&](int operand, int step) {
-        if constexpr (kThree) return third_origin(operand, step / steps1) + (int64_t)(step % steps1) * (int64_t)k_step_bytes[operand];
         const bool seg1 = step < steps1;
         return seg_origin[operand][seg1 ? 0 : 1] + (int64_t)(seg1 ? step : step - steps1) * (int64_t)k_step_bytes[operand];
     };
@@ -548,14 +533,6 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& 
         // segment is used.
         const char* origin_a = tile_origin(0, min(step_begin + kAhead, last));
         const char* origin_b = tile_origin(1, min(step_begin + kAhead - 1, last));
-        // kThree: the next segment of each operand and the step at which it begins
-        int segment_a = 0, segment_b = 0, next_a = 0, next_b = 0;
-        if constexpr (kThree) {
-            segment_a = min(step_begin + kAhead, last) / steps1 + 1;
-            segment_b = min(step_begin + kAhead - 1, last) / steps1 + 1;
-            next_a = segment_a * steps1;
-            next_b = segment_b * steps1;
-        }
         uint32_t sa = 0, sb = next_slot(sa), refill_a = (kSlots - 1) * kTileBytes, na = next_slot(sb), nb = next_slot(na);
         uint32_t rd_a = base_a[1] + sa, rd_b = base_b[1] + sb, stride_now = 0;
         // In six pieces of two or three scalar instructions; the A origin only after the last load from it.
@@ -569,12 +546,6 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& 
                 else rd_b = fragment_address_sum(base_b[0], nb);
             } else if (piece % 3 == 1) {
                 origin += stride_now;
-            } else if constexpr (kThree) {
-                int &next = operand == 0 ? next_a : next_b, &segment = operand == 0 ? segment_a : segment_b;
-                if (at == next && at <= last) {
-                    origin = third_origin(operand, segment++);
-                    next += steps1;
-                }
             } else {
                 origin = at == steps1 ? seg_origin[operand][1] : origin;
             }
@@ -607,7 +578,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& p, const Epilogue& 
 template <class Epilogue, int kLayA, int kLayB, int kW, int kSlots = kRingSlots>
 __global__ __launch_bounds__(kGemmThreads, kW == kLargeTile || kSlots > kRingSlots ? 1 : 2) void gemm_bf16(GemmProblem p, Epilogue epi) {
     __shared__ OperandRing<kW, kSlots> smem;
-    gemm_tile<kLayA, kLayB, false, false>(p, epi, blockIdx.x, smem);
+    gemm_tile<kLayA, kLayB, false>(p, epi, blockIdx.x, smem);
 }
 
 // Products that depend on the same launches and not on one another, as one launch: the workgroups of one fill the CUs that
@@ -621,7 +592,7 @@ struct GemmJob {
     int workgroups(int tile) const { return p.M / tile * (p.N / tile) * p.splits; }
     template <int kW, int kSlots>
     __device__ __forceinline__ void run(int block, OperandRing<kW, kSlots>& smem) const {
-        gemm_tile<kLayA, kLayB, true, false>(p, epi, block - first, smem);
+        gemm_tile<kLayA, kLayB, true>(p, epi, block - first, smem);
     }
 };
 // Two products of the same A and sizes with a right operand and a result each.
@@ -640,7 +611,7 @@ struct GemmPairJob {
         const bool second = block - first >= each;
         GemmProblem q = p;
         q.B = q.B2 = second ? B[1] : B[0];       // (an index instead of the choice would put the pair into scratch memory)
-        gemm_tile<kLayA, kLayB, true, false>(q, epi[0].or_second(second, epi[1]), block - first - (second ? each : 0), smem);
+        gemm_tile<kLayA, kLayB, true>(q, epi[0].or_second(second, epi[1]), block - first - (second ? each : 0), smem);
     }
 };
 // The last job whose first workgroup is not beyond `block` runs it.
@@ -1070,8 +1041,6 @@ struct EpiSwigluBackward {
     }
 };
 
-constexpr size_t kMaxSplitTiles = 256;   // tiles x parts of a split reduction: one workgroup per CU
-
 // The tile for a product of M x N: a CU's time is the number of its tiles times what one takes.  A 64-wide step takes
 // 0.94 us with the large tile (the matrix pipe) and 0.46 us with the small one, not a quarter: it brings in 32 KB for a
 // quarter of the products, and the path from L2 into LDS carries about 70 GB/s per CU.  So the small tile pays where the
@@ -1113,70 +1082,6 @@ template <int kLayA = kRowsByK, int kLayB = kRowsByK, class Epilogue>
 inline void launch_gemm(const GemmProblem& p, const Epilogue& epi, hipStream_t s) {
     if (tile_for(p.M, p.N, p.splits) == kSmallTile) launch_gemm_tile<kLayA, kLayB, kSmallTile>(p, epi, s);
     else launch_gemm_tile<kLayA, kLayB, kLargeTile>(p, epi, s);
-}
-
-// Tile and reduction splits of products that share a launch: those with the least estimated time.  A workgroup takes a few
-// microseconds to start and to write its tile, and per 64-wide step 0.94 us with the large tile (the matrix pipe) or 0.46 with
-// the small one (LDS, which two workgroups of a CU share; see tile_for).  The launch takes what its longest workgroup does, or
-// the work shared out over 256 CUs and about half a workgroup more at the end; parts are written, read back and added up at
-// about 4 TB/s.  Measured against every one of these choices forced on all three launches of a step (tile, and the longest
-// reduction from 6 steps to all of them): the estimate is within 1 % of the best, or better, at 14 of 16 sizes from 448 rows
-// of 3072 -> 768 to 5376 of 3328 -> 7168, and 2 to 3 % off at 9856 rows of 1792 -> 1792 and 2688 of 3072 -> 2560.
-struct GroupShape {
-    int64_t M, N;
-    int steps, count;      // `count` products of these sizes
-    bool split;            // whether the reduction may be split (fp32 parts, summed by a later launch)
-    int shortest = 1;      // and into no fewer steps than these
-};
-struct GroupPlan {
-    static constexpr int kMax = 4;
-    int kW, splits[kMax];
-};
-template <int kN>
-inline GroupPlan plan_group(const GroupShape (&jobs)[kN], float us_sum) {
-    // (little arithmetic: every call of a step comes through here, and a small one is bound by the host)
-    int large[kN], most_splits[kN], longest_split = 0;
-    float part_us[kN];                                   // writing or reading one part
-    for (int q = 0; q < kN; ++q) {
-        const GroupShape& j = jobs[q];
-        large[q] = (int)(j.M / kTileM) * (int)(j.N / kTileN);
-        most_splits[q] = j.split ? std::max(1, std::min({(int)kMaxSplitTiles / large[q], j.steps / j.shortest, 64})) : 1;
-        part_us[q] = (float)large[q] * (float)j.count * (kTileM * kTileN * 4 / 4e6f);
-        if (most_splits[q] > 1) longest_split = std::max(longest_split, j.steps);
-    }
-    GroupPlan best{};
-    float best_us = 0.f;
-    for (int kW : {kLargeTile, kSmallTile}) {
-        const float us_per_step = kW == kLargeTile ? 0.94f : 0.46f, us_fixed = kW == kLargeTile ? 5.f : 3.f;
-        const int tiles_per_large = kW == kLargeTile ? 1 : 4;
-        for (int most : {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 1 << 20}) {     // longest reduction of a workgroup
-            if (most < longest_split || most == 1 << 20 || longest_split == 0) {
-                GroupPlan plan{kW, {}};
-                int steps = 0;                           // of the longest workgroup
-                int64_t workgroups = 0;
-                float work = 0.f, sum = 0.f;
-                for (int q = 0; q < kN; ++q) {
-                    const GroupShape& j = jobs[q];
-                    const int s = std::min(most_splits[q], ceil_div(j.steps, most)), len = s > 1 ? ceil_div(j.steps, s) : j.steps;
-                    plan.splits[q] = s;
-                    steps = std::max(steps, len);
-                    const int64_t n = (int64_t)large[q] * (tiles_per_large * s * j.count);
-                    workgroups += n;
-                    work += (float)n * (us_fixed + us_per_step * (float)len);
-                    if (s > 1) sum += (float)(2 * s + 1) * part_us[q];
-                }
-                float us = us_fixed + us_per_step * (float)steps;
-                if (workgroups > 256) us = std::max(us, work / 256 + 0.5f * work / (float)workgroups);
-                if (sum > 0.f) us += us_sum + sum;
-                if (best.kW == 0 || us < best_us) {
-                    best = plan;
-                    best_us = us;
-                }
-            }
-            if (longest_split == 0) break;
-        }
-    }
-    return best;
 }
 
 // A product over the rows of a batch (columns: weights), both operands [rows][K].  When whole rounds of large tiles leave a
