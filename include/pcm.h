@@ -126,6 +126,9 @@ PCM_API int pcm_label_phases(const float* actions, const int32_t* n_chunks, int 
  *   C_out     device f64 [K];  valid_out device u8 [K]
  *   adv_out   device f32 [T] or NULL;  active_out device u8 [T] or NULL
  * Limits: 1 <= K <= PCM_MAX_PHASES, 1 <= A <= 256, G >= 1, n_groups >= 1, N >= 1.
+ * Workspace: the query names the bytes with which the call is fastest.  The accumulators, about
+ * n_groups * K * A * 16 bytes whatever G and N, are enough for every call of those n_groups, K and A;
+ * PCM_EWORKSPACE below that.
  * ------------------------------------------------------------------------------------------ */
 PCM_API size_t pcm_score_phases_workspace_bytes(int n_groups, int G, int N, int A, int K);
 PCM_API int pcm_score_phases(const float* actions, const uint8_t* phase, const uint8_t* reward,
@@ -142,8 +145,8 @@ PCM_API int pcm_score_phases(const float* actions, const uint8_t* phase, const u
  * and frees nothing (its first call on a device looks up that device's copy of the array).
  *
  * Errors: as pcm_score_phases; PCM_EWORKSPACE when pcm_score_phases_workspace_bytes(...) of the
- * shape exceeds PCM_SCORE_STATIC_MAX_BYTES (about n_groups * K * A * 16 bytes: the paper-sized
- * batch needs 0.07 MB, 64 groups of 12 phases 0.7 MB).
+ * shape exceeds PCM_SCORE_STATIC_MAX_BYTES (when the accumulators do, about n_groups * K * A * 16
+ * bytes: the paper-sized batch needs 0.07 MB of them, 64 groups of 12 phases 0.7 MB).
  * All calls on one GPU share that GPU's array: two calls that may overlap (different streams
  * without an ordering between them, or different host threads) race; order them.  The array holds
  * the counters by which the last workgroups know that they are the last: overlapping calls can leave

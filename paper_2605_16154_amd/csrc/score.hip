@@ -1,18 +1,22 @@
 // pcm_score_phases: group-relative advantages (Eq. 1) and the batch phase score C_c (Eq. 5).
 //
-// Two launches on the caller's stream, four where the work behind the accumulation is long (see fuses_tail):
-//   prepare     zero the integer accumulators and the arrival counters; one thread per trajectory writes
-//               advantage/active
-//   accumulate  streaming pass over the action tensor: every workgroup owns a slice of one
-//               trajectory's chunks, keeps per-phase 64-bit integer sums in LDS and adds the
-//               phases it met to the group's accumulators with 64-bit global atomics.  The last workgroup of a group
-//               to arrive forms the group's pair scores (difference of pooled means, squared terms in parallel, added
-//               in index order by one lane per phase, square root); the last group to arrive forms the mean of the pair
-//               scores over contributing groups, one lane per phase.  Nobody waits for anybody: a workgroup that is not
-//               the last one leaves.
-//   pairs, mean   the same two steps as launches of their own: a wavefront per (group, phase), then one workgroup
+// Three routes on the caller's stream, with the same results bit for bit (the rules and what they measured stand at is_small,
+// table_slices and fuses_tail):
+//   small         one launch of one workgroup: all sums in LDS, pair scores and mean behind them
+//   tables        two launches: a table of sums per trajectory or slice of one; tables to pair scores, last workgroup to mean
+//   accumulators  two launches, four where the work behind the accumulation is long:
+//     prepare     zero the integer accumulators and the arrival counters; one thread per trajectory writes
+//                 advantage/active
+//     accumulate  streaming pass over the action tensor: every workgroup owns a slice of one
+//                 trajectory's chunks, keeps per-phase integer sums in LDS and adds the
+//                 phases it met to the group's accumulators with 64-bit global atomics.  The last workgroup of a group
+//                 to arrive forms the group's pair scores (difference of pooled means, squared terms in parallel, added
+//                 in index order by one lane per phase, square root); the last group to arrive forms the mean of the pair
+//                 scores over contributing groups, one lane per phase.  Nobody waits for anybody: a workgroup that is not
+//                 the last one leaves.
+//     pairs, mean the same two steps as launches of their own: a wavefront per (group, phase), then one workgroup
 //
-// The action pass is bandwidth-bound (224 B per chunk plus one phase byte); everything after it
+// The action pass of large batches is bandwidth-bound (224 B per chunk plus one phase byte); everything after it
 // touches a few KB.  Integer accumulation makes the sums independent of slice and arrival order,
 // which is what lets the sampler downstream be reproduced bit for bit.
 //
@@ -92,6 +96,13 @@ __global__ __launch_bounds__(kThreads) void score_prepare(uint32_t* zero, size_t
     }
 }
 
+// rint(a 2^24) as a double, and sums of up to kExactRun of them, are exact: |a| <= 2^20, so they stay below 2^53.  Four
+// instructions a value where the conversion to a 64-bit integer and its addition take fourteen: the small
+// route at 16 trajectories of 32 chunks of 56 values 10.8 -> 7.6 us, the tables of 512 trajectories of up to
+// 256 chunks 9.3 -> 8.7, of 256 of up to 128 6.4 -> 6.1 us.
+__device__ inline double to_fixed(float a) { return (double)rintf(a * kActionScale); }
+constexpr int kExactRun = 256;
+
 template <int VEC>
 struct ActionVec;
 template <>
@@ -133,29 +144,28 @@ __device__ inline bool arrive_last(int* counter, int expected) {
     return last;
 }
 
-// This workgroup's slice of a trajectory, its sums in LDS and from there to the group's accumulators.
-template <int VEC>
+// Sums and counts by phase of a workgroup's slice of a trajectory, in LDS.
+template <int VEC, int kT>
 __device__ inline void accumulate_slice(const float* __restrict__ actions, const uint8_t* __restrict__ phase,
-                                        int i, int g, int outcome, int k0, int k1, int N, int A, int K, int c0, int kb,
-                                        ull* lds_sum, int* lds_cnt, ull* sums, int* counts) {
+                                        int i, int k0, int k1, int N, int A, int K, int c0, int kb, ull* lds_sum, int* lds_cnt) {
     const int tid = threadIdx.x;
-    for (int e = tid; e < kb * A; e += kThreads) lds_sum[e] = 0;
-    for (int c = tid; c < kb; c += kThreads) lds_cnt[c] = 0;
+    for (int e = tid; e < kb * A; e += kT) lds_sum[e] = 0;
+    for (int c = tid; c < kb; c += kT) lds_cnt[c] = 0;
     __syncthreads();
 
     const int AV = A / VEC;            // vectors per chunk
-    const int CPI = kThreads / AV;     // chunks per pass of the workgroup
+    const int CPI = kT / AV;           // chunks per pass of the workgroup
     const int jv = tid % AV, cs = tid / AV;
     if (cs < CPI) {
-        long long acc[VEC];
+        double acc[VEC];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[v] = 0;
+        for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
         int cur = -1, run = 0;
         auto flush = [&]() {
             if (cur >= 0 && cur < kb && run > 0) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v)
-                    atomicAdd(&lds_sum[(size_t)cur * A + jv * VEC + v], (ull)acc[v]);
+                    atomicAdd(&lds_sum[(size_t)cur * A + jv * VEC + v], (ull)__double2ll_rn(acc[v]));
                 if (jv == 0) atomicAdd(&lds_cnt[cur], run);
             }
         };
@@ -177,29 +187,21 @@ __device__ inline void accumulate_slice(const float* __restrict__ actions, const
             for (int u = 0; u < kAhead; ++u) {
                 if (kb0 + u * CPI >= k1) break;
                 const int c = min(ph_id[u], K - 1) - c0;  // ids beyond the last phase count as the last; outside [0, kb): another block's
-                if (c != cur) {
+                if (c != cur || run == kExactRun) {
                     flush();
                     cur = c;
                     run = 0;
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[v] = 0;
+                    for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
                 }
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) acc[v] += __float2ll_rn(x[u].v[v] * kActionScale);
+                for (int v = 0; v < VEC; ++v) acc[v] += to_fixed(x[u].v[v]);
                 ++run;
             }
         }
         flush();
     }
     __syncthreads();
-
-    const size_t base = ((size_t)g * 2 + outcome) * K + c0;
-    for (int e = tid; e < kb * A; e += kThreads) {
-        const int c = e / A;
-        if (lds_cnt[c] > 0) add_shared(&sums[base * A + e], lds_sum[e]);
-    }
-    for (int c = tid; c < kb; c += kThreads)
-        if (lds_cnt[c] > 0) add_shared(&counts[base + c], lds_cnt[c]);
 }
 
 __device__ inline double squared_difference(ull s_pos, int n_pos, ull s_neg, int n_neg) {
@@ -358,9 +360,15 @@ __global__ __launch_bounds__(kThreads) void score_accumulate(
         Ni = Ni < 0 ? 0 : (Ni > N ? N : Ni);
         const int per = (N + slices - 1) / slices;
         const int k0 = slice * per, k1 = min(Ni, k0 + per);
-        if (k0 < k1)
-            accumulate_slice<VEC>(actions, phase, i, g, reward[i] != 0, k0, k1, N, A, K, c0, kb, lds_sum,
-                                  reinterpret_cast<int*>(lds_sum + (size_t)Kb * A), w.sums, w.counts);
+        if (k0 < k1) {
+            int* const lds_cnt = reinterpret_cast<int*>(lds_sum + (size_t)Kb * A);
+            accumulate_slice<VEC, kThreads>(actions, phase, i, k0, k1, N, A, K, c0, kb, lds_sum, lds_cnt);
+            const size_t base = ((size_t)g * 2 + (reward[i] != 0)) * K + c0;
+            for (int e = threadIdx.x; e < kb * A; e += kThreads)
+                if (lds_cnt[e / A] > 0) add_shared(&w.sums[base * A + e], lds_sum[e]);
+            for (int c = threadIdx.x; c < kb; c += kThreads)
+                if (lds_cnt[c] > 0) add_shared(&w.counts[base + c], lds_cnt[c]);
+        }
     }
     if (kTail) {
         double* const lds = reinterpret_cast<double*>(lds_sum);
@@ -368,6 +376,291 @@ __global__ __launch_bounds__(kThreads) void score_accumulate(
         score_pairs_of_group(g, A, K, w.sums, w.counts, lds, w.pair);
         if (!arrive_last(w.groups_done, n_groups)) return;
         mean_of_groups<kThreads>(w.pair, n_groups, K, lds, lds_entries, C_out, valid_out, [](const double* p) { return load_shared(p); });
+    }
+}
+
+// ---- small and ordinary batches: a table per trajectory ------------------------------------------
+//
+// Two launches and no accumulators to clear.  The first gives every trajectory, or slice of one, a workgroup and a table of its
+// own: sums and counts by phase from LDS, written as they are.  The second adds up the tables of a group (1024 sums a workgroup),
+// forms the pair scores, and its last workgroup the mean.  Bound by latency: two loads deep in the first, three in the second.
+// Kernel times, 256 trajectories of up to 128 chunks of 56 values, 5 phases: 2.1 + 11.6 us with accumulators (the additions to them and the
+// hand-over to the last workgroup are the longer part), 6.1 + 7.5 with tables; 512 of up to 256 with 12 phases
+// 2.2 + 10.5 + 3.8 + 2.9 against 8.7 + 7.6.
+constexpr int kTableThreads = 1024;
+constexpr int kTableMeanEntries = 2048;                  // pair scores in LDS at a time
+constexpr size_t kTableBytesMax = PCM_SCORE_STATIC_MAX_BYTES;
+
+struct TableWorkspace {
+    ull* sums;            // [T * slices][K][A]; of phases without a chunk unwritten
+    int* counts;          // [T * slices][K]
+    double* pair;         // [n_groups][K]
+    int* done;            // workgroups of the second launch that are done
+    size_t bytes;
+};
+TableWorkspace carve_tables(void* ws, int n_groups, int G, int A, int K, int slices) {
+    Carver c(ws);
+    TableWorkspace w;
+    const size_t tables = (size_t)n_groups * G * slices;
+    w.sums = c.take<ull>(tables * K * A);
+    w.counts = c.take<int>(tables * K);
+    w.pair = c.take<double>((size_t)n_groups * K);
+    w.done = c.take<int>(1);
+    w.bytes = c.used();
+    return w;
+}
+int phases_per_pair_block(int A) { return kTableThreads / A; }        // A <= 256
+
+// Slices per trajectory, or 0 where the batch takes the accumulators: the tables have to fit in 4 MiB, so that a shape fits the
+// library's own array if it did with those, and in the workspace that the caller brings (one that holds the accumulators is enough
+// for any call), and what the second launch adds up per sum has to stay short.  A slice is at least one chunk per thread, and no more
+// are made than two workgroups per CU want.
+int table_slices(int n_groups, int G, int N, int A, int K, size_t bytes_max) {
+    if ((size_t)K * A * sizeof(ull) + (size_t)K * sizeof(int) > kLdsMax || G > kWave) return 0;
+    if ((int64_t)n_groups * ceil_div(K, phases_per_pair_block(A)) > 1024) return 0;       // workgroups of the second launch
+    const int T = n_groups * G, per_pass = kTableThreads / (A % 4 == 0 ? A / 4 : A);
+    int slices = std::min({ceil_div(512, T), ceil_div(N, per_pass), kWave / G});
+    for (; slices > 0; --slices)
+        if (carve_tables(nullptr, n_groups, G, A, K, slices).bytes <= std::min(bytes_max, kTableBytesMax)) break;
+    return slices;
+}
+
+// Successes of the group (a bit per trajectory, G <= 64), the same in every wavefront.
+__device__ inline uint64_t successes_of(const uint8_t* reward, int g, int G) {
+    const int r = threadIdx.x % kWave;
+    const uint8_t x = reward[(size_t)g * G + min(r, G - 1)];
+    return __ballot(r < G && x != 0);
+}
+
+template <int VEC>
+__global__ __launch_bounds__(kTableThreads) void score_tables(const float* __restrict__ actions, const uint8_t* __restrict__ phase,
+                                                              const uint8_t* __restrict__ reward, const int32_t* __restrict__ n_chunks, int G,
+                                                              int N, int A, int K, int slices, double adv_eps, float* adv_out,
+                                                              uint8_t* active_out, TableWorkspace w) {
+    extern __shared__ ull lds_sum[];
+    int* const lds_cnt = reinterpret_cast<int*>(lds_sum + (size_t)K * A);
+    const int i = blockIdx.x / slices, slice = blockIdx.x % slices, g = i / G, tid = threadIdx.x;
+    int Ni = n_chunks ? n_chunks[i] : N;
+    const uint64_t won = successes_of(reward, g, G);
+    const int s = __popcll(won);
+    const bool mixed = s != 0 && s != G;
+    Ni = Ni < 0 ? 0 : (Ni > N ? N : Ni);
+    if (mixed) {                                  // with uniform rewards the group has no score; nobody reads its tables
+        const int per = (N + slices - 1) / slices, k0 = slice * per, k1 = min(Ni, k0 + per);
+        accumulate_slice<VEC, kTableThreads>(actions, phase, i, k0, k1, N, A, K, 0, K, lds_sum, lds_cnt);
+        ull* const sums = w.sums + (size_t)blockIdx.x * K * A;
+        for (int e = tid; e < K * A; e += kTableThreads)
+            if (lds_cnt[e / A] > 0) sums[e] = lds_sum[e];
+        if (tid < K) w.counts[(size_t)blockIdx.x * K + tid] = lds_cnt[tid];
+    }
+    if (tid != kTableThreads - 1) return;         // a thread that has had little to do
+    if (blockIdx.x == 0) *w.done = 0;
+    if (slice != 0) return;
+    float a = 0.f;
+    if (mixed) {
+        const double mu = (double)s / (double)G;
+        const double sigma = sqrt(mu * (1.0 - mu));
+        const double r = (won >> (i - g * G)) & 1u ? 1.0 : 0.0;
+        a = (float)((r - mu) / (sigma + adv_eps));
+    }
+    if (adv_out) adv_out[i] = a;
+    if (active_out) active_out[i] = mixed ? 1 : 0;
+}
+
+__global__ __launch_bounds__(kTableThreads) void score_of_tables(const uint8_t* __restrict__ reward, int n_groups, int G, int A, int K, int slices,
+                                                                 int phases, TableWorkspace w, double* C_out, uint8_t* valid_out) {
+    __shared__ double lds[kTableMeanEntries];
+    __shared__ int n_of[2][PCM_MAX_PHASES];
+    const int blocks = (K + phases - 1) / phases, g = blockIdx.x / blocks, c0 = blockIdx.x % blocks * phases, kb = min(phases, K - c0);
+    const int tid = threadIdx.x;
+    const uint64_t won = successes_of(reward, g, G);
+    const int s = __popcll(won);
+    const bool mixed = s != 0 && s != G;
+    if (mixed && tid < kb * A) {
+        const int c = tid / A, tables = G * slices;
+        const size_t first = (size_t)g * tables;
+        const int* const counts = w.counts + first * K + c0 + c;
+        const ull* const sums = w.sums + first * K * A + (size_t)c0 * A + tid;
+        int n_pos = 0, n_neg = 0;
+        ull s_pos = 0, s_neg = 0;
+        constexpr int kTogether = 8;              // tables whose loads are under way together
+        for (int t0 = 0; t0 < tables; t0 += kTogether) {
+            int n[kTogether];
+            ull v[kTogether];
+#pragma unroll
+            for (int u = 0; u < kTogether; ++u) {
+                const int t = min(t0 + u, tables - 1);
+                n[u] = counts[(size_t)t * K];
+                v[u] = sums[(size_t)t * K * A];
+            }
+#pragma unroll
+            for (int u = 0; u < kTogether; ++u) {
+                if (t0 + u >= tables || n[u] == 0) continue;       // (a sum without a chunk was not written)
+                if ((won >> ((t0 + u) / slices)) & 1u) { n_pos += n[u]; s_pos += v[u]; }
+                else { n_neg += n[u]; s_neg += v[u]; }
+            }
+        }
+        if (n_pos > 0 && n_neg > 0) lds[tid] = squared_difference(s_pos, n_pos, s_neg, n_neg);
+        if (tid == c * A) {
+            n_of[0][c] = n_neg;
+            n_of[1][c] = n_pos;
+        }
+    }
+    __syncthreads();
+    if (tid < kb) {
+        double score = -1.0;                      // skipped: uniform rewards, or no chunks of one of the outcomes
+        if (mixed && n_of[0][tid] > 0 && n_of[1][tid] > 0) {
+            double acc = 0.0;
+#pragma unroll 8
+            for (int j = 0; j < A; ++j) acc = acc + lds[tid * A + j];
+            score = sqrt(acc) * kActionUnscale;
+        }
+        store_shared(&w.pair[(size_t)g * K + c0 + tid], score);
+    }
+    if (!arrive_last(w.done, (int)gridDim.x)) return;
+    mean_of_groups<kTableThreads>(w.pair, n_groups, K, lds, kTableMeanEntries, C_out, valid_out, [](const double* p) { return load_shared(p); });
+}
+
+// ---- the smallest batches: one workgroup, one launch ---------------------------------------------
+//
+// Bound by latency alone, so nothing is handed from one workgroup to another: all sums in LDS, every thread a run of
+// consecutive chunks (one or two flushes), pair scores and mean behind it.
+// 16 trajectories of 32 chunks of 56 values, 4 phases: one launch of 7.6 us against 2.0 + 7.6 with
+// accumulators.  The line: calls one after another, this route / tables, 16 trajectories of 4 chunks 4.8 / 8.9 us,
+// of 18 6.4 / 9.0, of 36 (eight chunks a thread, sixteen spill: 15.7) 8.0 / 9.1; 72 chunks each in one group of 12 phases 8.4 / 9.8;
+// 4 groups of 8 trajectories of 18 chunks 8.8 / 9.0, 18 groups of 8 of 4 chunks 9.4 / 9.4 (4032 pair terms: no gain beyond 4096).
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallPerThread = 8;            // chunks per thread at most
+struct SmallShape {
+    int n_groups, G, N, A, K;
+    __host__ __device__ int sums() const { return n_groups * 2 * K * A; }
+    // LDS: the sums; chunks pooled [n_groups][2][K]; squared terms [n_groups][K][A]; pair scores [n_groups][K]
+    __host__ __device__ size_t lds_bytes() const {
+        return (size_t)sums() * 8 + (size_t)n_groups * K * A * 8 + (size_t)n_groups * K * 8 + (size_t)n_groups * 2 * K * 4;
+    }
+};
+bool is_vec4(const float* actions, int A) { return A % 4 == 0 && (reinterpret_cast<uintptr_t>(actions) & 15u) == 0; }
+bool is_small(const SmallShape& p, bool vec4) {
+    const int chunks_at_once = kSmallThreads / (vec4 ? p.A / 4 : p.A);
+    return (int64_t)p.n_groups * p.G * p.N <= (int64_t)chunks_at_once * kSmallPerThread && (int64_t)p.n_groups * p.G <= kSmallThreads &&
+           p.G <= kWave && (int64_t)p.n_groups * p.K * p.A <= 4096 && p.lds_bytes() <= kLdsMax - 2 * kSmallThreads * sizeof(int);
+}
+template <int VEC>
+__global__ __launch_bounds__(kSmallThreads) void score_small(const float* __restrict__ actions, const uint8_t* __restrict__ phase,
+                                                             const uint8_t* __restrict__ reward, const int32_t* __restrict__ n_chunks, SmallShape p,
+                                                             double adv_eps, double* C_out, uint8_t* valid_out, float* adv_out,
+                                                             uint8_t* active_out) {
+    extern __shared__ ull lds_sum[];
+    const int G = p.G, N = p.N, A = p.A, K = p.K, T = p.n_groups * G, tid = threadIdx.x;
+    double* const sq = reinterpret_cast<double*>(lds_sum + p.sums());
+    double* const pair = sq + (size_t)p.n_groups * K * A;
+    int* const counts = reinterpret_cast<int*>(pair + (size_t)p.n_groups * K);
+    __shared__ int table_of[kSmallThreads];       // of each trajectory: its (group, outcome), or -1 in a group of uniform rewards
+    __shared__ int valid_of[kSmallThreads];       // and how many of its chunks are there
+    const int AV = A / VEC, CPI = kSmallThreads / AV;             // vectors per chunk; threads per vector
+    const int jv = tid % AV, cs = tid / AV;
+    const int per = (T * N + CPI - 1) / CPI, q0 = cs * per, q1 = cs < CPI ? min(q0 + per, T * N) : q0;
+    int ph[kSmallPerThread];
+    ActionVec<VEC> x[kSmallPerThread];
+#pragma unroll
+    for (int u = 0; u < kSmallPerThread; ++u)                     // all loads of a thread under way together
+        if (q0 + u < q1) {
+            ph[u] = phase[q0 + u];
+            x[u].load(actions + (size_t)(q0 + u) * A + (size_t)jv * VEC);
+        }
+    for (int e = tid; e < p.sums(); e += kSmallThreads) lds_sum[e] = 0;
+    for (int e = tid; e < p.n_groups * 2 * K; e += kSmallThreads) counts[e] = 0;
+    if (tid < T) {
+        const int g = tid / G;
+        int s = 0;
+        for (int r0 = 0; r0 < G; r0 += 8)             // eight loads under way together
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint8_t x = reward[(size_t)g * G + min(r0 + u, G - 1)];
+                s += r0 + u < G && x != 0;
+            }
+        const bool won = reward[tid] != 0, mixed = s != 0 && s != G;
+        int Ni = n_chunks ? n_chunks[tid] : N;
+        valid_of[tid] = Ni < 0 ? 0 : (Ni > N ? N : Ni);
+        table_of[tid] = mixed ? g * 2 + (won ? 1 : 0) : -1;
+    }
+    __syncthreads();
+    double acc[VEC];
+    int i = q0 / N, k = q0 - i * N;                               // trajectory and slot
+    int cur = -1, run = 0;                                        // the sums under way: (table, phase)
+    auto flush = [&]() {
+        if (run == 0) return;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) atomicAdd(&lds_sum[(size_t)cur * A + jv * VEC + v], (ull)__double2ll_rn(acc[v]));
+        if (jv == 0) atomicAdd(&counts[cur], run);
+    };
+#pragma unroll
+    for (int u = 0; u < kSmallPerThread; ++u) {
+        if (q0 + u >= q1) break;
+        const int table = table_of[i], slot = k++;
+        const bool in = table >= 0 && slot < valid_of[i];
+        if (k == N) {
+            k = 0;
+            ++i;
+        }
+        if (!in) continue;
+        const int to = table * K + min(ph[u], K - 1);             // ids beyond the last phase count as the last
+        if (to != cur) {
+            flush();
+            cur = to;
+            run = 0;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
+        }
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[v] += to_fixed(x[u].v[v]);
+        ++run;
+    }
+    flush();
+    __syncthreads();
+    for (int e = tid; e < p.n_groups * K * A; e += kSmallThreads) {
+        const int g = e / (K * A), r = e - g * K * A, c = r / A;
+        const int n_neg = counts[(g * 2) * K + c], n_pos = counts[(g * 2 + 1) * K + c];
+        if (n_pos > 0 && n_neg > 0)
+            sq[e] = squared_difference(lds_sum[(size_t)(g * 2 + 1) * K * A + r], n_pos, lds_sum[(size_t)(g * 2) * K * A + r], n_neg);
+    }
+    __syncthreads();
+    if (tid >= kSmallThreads - T) {                               // advantages, by the last threads: the first ones add up the pairs
+        const int t = tid - (kSmallThreads - T), table = table_of[t];
+        float a = 0.f;
+        if (table >= 0) {
+            int s = 0;
+            for (int r = t / G * G; r < t / G * G + G; ++r) s += table_of[r] & 1;
+            const double mu = (double)s / (double)G;
+            const double sigma = sqrt(mu * (1.0 - mu));
+            a = (float)(((double)(table & 1) - mu) / (sigma + adv_eps));
+        }
+        if (adv_out) adv_out[t] = a;
+        if (active_out) active_out[t] = table >= 0 ? 1 : 0;
+    }
+    for (int e = tid; e < p.n_groups * K; e += kSmallThreads) {
+        const int g = e / K, c = e - g * K;
+        double score = -1.0;                                      // skipped: no chunks of one of the outcomes
+        if (counts[(g * 2) * K + c] > 0 && counts[(g * 2 + 1) * K + c] > 0) {
+            double sum = 0.0;
+#pragma unroll 8
+            for (int j = 0; j < A; ++j) sum = sum + sq[(size_t)e * A + j];
+            score = sqrt(sum) * kActionUnscale;
+        }
+        pair[e] = score;
+    }
+    __syncthreads();
+    if (tid < K) {                                                // the mean over contributing groups, added for g ascending
+        double tot = 0.0;
+        int n = 0;
+#pragma unroll 8
+        for (int g = 0; g < p.n_groups; ++g) {
+            const double v = pair[g * K + tid];
+            tot = tot + fmax(v, 0.0);                             // a skipped pair adds +0.0, which leaves the non-negative sum as it is
+            n += v >= 0.0 ? 1 : 0;
+        }
+        C_out[tid] = n > 0 ? tot / (double)n : 0.0;
+        valid_out[tid] = n > 0 ? 1 : 0;
     }
 }
 
@@ -397,7 +690,8 @@ using namespace pcm;
 
 extern "C" size_t pcm_score_phases_workspace_bytes(int n_groups, int G, int N, int A, int K) {
     if (!shape_ok(n_groups, G, N, A, K)) return 0;
-    return carve(nullptr, n_groups, A, K).bytes;
+    const int slices = table_slices(n_groups, G, N, A, K, kTableBytesMax);
+    return std::max(carve(nullptr, n_groups, A, K).bytes, slices > 0 ? carve_tables(nullptr, n_groups, G, A, K, slices).bytes : 0);
 }
 
 // ---- scratch memory owned by the library, for the entry point that takes no workspace -------------
@@ -409,8 +703,32 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
 
-// The launches shared by both entry points; `workspace` has been checked
-// to hold carve(...).bytes.
+int run_small(const float* actions, const uint8_t* phase, const uint8_t* reward, const int32_t* n_chunks, const SmallShape& p, double adv_eps,
+              double* C_out, uint8_t* valid_out, float* adv_out, uint8_t* active_out, hipStream_t s) {
+    StageTimer t(ST_SCORE_ACCUMULATE, s);
+    if (is_vec4(actions, p.A))
+        score_small<4><<<1, kSmallThreads, p.lds_bytes(), s>>>(actions, phase, reward, n_chunks, p, adv_eps, C_out, valid_out, adv_out, active_out);
+    else
+        score_small<1><<<1, kSmallThreads, p.lds_bytes(), s>>>(actions, phase, reward, n_chunks, p, adv_eps, C_out, valid_out, adv_out, active_out);
+    return launch_status();
+}
+int run_tables(const float* actions, const uint8_t* phase, const uint8_t* reward, const int32_t* n_chunks, int n_groups, int G, int N, int A,
+               int K, double adv_eps, double* C_out, uint8_t* valid_out, float* adv_out, uint8_t* active_out, int slices,
+               const TableWorkspace& w, hipStream_t s) {
+    {
+        StageTimer t(ST_SCORE_ACCUMULATE, s);
+        const bool vec4 = is_vec4(actions, A);
+        const unsigned grid = (unsigned)(n_groups * G) * (unsigned)slices;
+        const size_t lds_bytes = (size_t)K * A * sizeof(ull) + (size_t)K * sizeof(int);
+        if (vec4) score_tables<4><<<grid, kTableThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, G, N, A, K, slices, adv_eps, adv_out, active_out, w);
+        else score_tables<1><<<grid, kTableThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, G, N, A, K, slices, adv_eps, adv_out, active_out, w);
+    }
+    StageTimer t(ST_SCORE_FINALISE, s);
+    const int phases = phases_per_pair_block(A);
+    score_of_tables<<<(unsigned)n_groups * (unsigned)ceil_div(K, phases), kTableThreads, 0, s>>>(reward, n_groups, G, A, K, slices, phases, w, C_out, valid_out);
+    return launch_status();
+}
+
 int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward, const int32_t* n_chunks,
               int n_groups, int G, int N, int A, int K, double adv_eps, double* C_out, uint8_t* valid_out,
               float* adv_out, uint8_t* active_out, const ScoreWorkspace& w, hipStream_t s) {
@@ -437,7 +755,7 @@ int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward,
     }
     {
         StageTimer t(ST_SCORE_ACCUMULATE, s);
-        const bool vec4 = (A % 4 == 0) && ((reinterpret_cast<uintptr_t>(actions) & 15u) == 0);
+        const bool vec4 = is_vec4(actions, A);
         const int chunks_per_pass = kThreads / (vec4 ? A / 4 : A);
         // enough workgroups to cover the chip several times over, but at least two passes each
         int slices = ceil_div(2048, T);
@@ -462,6 +780,19 @@ int run_score(const float* actions, const uint8_t* phase, const uint8_t* reward,
         score_mean<<<1, kMeanThreads, 0, s>>>(w.pair, n_groups, K, C_out, valid_out);
     }
     return launch_status();
+}
+
+// The launches of either entry point; the workspace holds the accumulators at least.
+int run_in(void* workspace, size_t workspace_bytes, const float* actions, const uint8_t* phase, const uint8_t* reward, const int32_t* n_chunks, int n_groups, int G,
+           int N, int A, int K, double adv_eps, double* C_out, uint8_t* valid_out, float* adv_out, uint8_t* active_out, hipStream_t s) {
+    const SmallShape small{n_groups, G, N, A, K};
+    if (is_small(small, is_vec4(actions, A)))
+        return run_small(actions, phase, reward, n_chunks, small, adv_eps, C_out, valid_out, adv_out, active_out, s);
+    if (const int slices = table_slices(n_groups, G, N, A, K, workspace_bytes); slices > 0)
+        return run_tables(actions, phase, reward, n_chunks, n_groups, G, N, A, K, adv_eps, C_out, valid_out, adv_out, active_out, slices,
+                          carve_tables(workspace, n_groups, G, A, K, slices), s);
+    return run_score(actions, phase, reward, n_chunks, n_groups, G, N, A, K, adv_eps, C_out, valid_out, adv_out, active_out,
+                     carve(workspace, n_groups, A, K), s);
 }
 
 bool args_ok(const float* actions, const uint8_t* phase, const uint8_t* reward, int n_groups, int G, int N, int A,
@@ -498,10 +829,9 @@ extern "C" int pcm_score_phases(const float* actions, const uint8_t* phase, cons
                                 uint8_t* active_out, void* workspace, size_t workspace_bytes,
                                 void* stream) {
     if (!args_ok(actions, phase, reward, n_groups, G, N, A, K, adv_eps, C_out, valid_out)) return PCM_EINVAL;
-    ScoreWorkspace w = carve(workspace, n_groups, A, K);
-    if (!workspace_ok(workspace, workspace_bytes, w.bytes)) return PCM_EWORKSPACE;
-    return run_score(actions, phase, reward, n_chunks, n_groups, G, N, A, K, adv_eps, C_out, valid_out, adv_out,
-                     active_out, w, static_cast<hipStream_t>(stream));
+    if (!workspace_ok(workspace, workspace_bytes, carve(nullptr, n_groups, A, K).bytes)) return PCM_EWORKSPACE;
+    return run_in(workspace, workspace_bytes, actions, phase, reward, n_chunks, n_groups, G, N, A, K, adv_eps, C_out, valid_out, adv_out, active_out,
+                  static_cast<hipStream_t>(stream));
 }
 
 extern "C" int pcm_score_phases_static(const float* actions, const uint8_t* phase, const uint8_t* reward,
@@ -513,7 +843,6 @@ extern "C" int pcm_score_phases_static(const float* actions, const uint8_t* phas
     void* base = nullptr;
     const int rc = static_scratch(&base);
     if (rc != PCM_OK) return rc;
-    const ScoreWorkspace w = carve(base, n_groups, A, K);
-    return run_score(actions, phase, reward, n_chunks, n_groups, G, N, A, K, adv_eps, C_out, valid_out, adv_out,
-                     active_out, w, static_cast<hipStream_t>(stream));
+    return run_in(base, kStaticScratchBytes, actions, phase, reward, n_chunks, n_groups, G, N, A, K, adv_eps, C_out, valid_out, adv_out, active_out,
+                  static_cast<hipStream_t>(stream));
 }
