@@ -382,13 +382,15 @@ __global__ __launch_bounds__(kThreads) void score_accumulate(
 // ---- small and ordinary batches: a table per trajectory ------------------------------------------
 //
 // Two launches and no accumulators to clear.  The first gives every trajectory, or slice of one, a workgroup and a table of its
-// own: sums and counts by phase from LDS, written as they are.  The second adds up the tables of a group (1024 sums a workgroup),
-// forms the pair scores, and its last workgroup the mean.  Bound by latency: two loads deep in the first, three in the second.
-// Kernel times, 256 trajectories of up to 128 chunks of 56 values, 5 phases: 2.1 + 11.6 us with accumulators (the additions to them and the
-// hand-over to the last workgroup are the longer part), 6.1 + 7.5 with tables; 512 of up to 256 with 12 phases
+// own: sums and counts by phase from LDS, written as they are.  The second adds up the tables of a group, a thread per sum, or
+// several where a group has more than eight tables (1 x 8 x 1024 chunks: 15.0 -> 11.1 us a call), forms the pair scores, and its
+// last workgroup the mean.  Bound by latency: two loads deep in the first, three in the second.
+// Kernel times, 256 trajectories of up to 128 chunks of 56 values, 5 phases: 2.1 + 11.6 us with accumulators (the additions to
+// them and the hand-over to the last workgroup are the longer part), 6.1 + 7.5 with tables; 512 of up to 256 with 12 phases
 // 2.2 + 10.5 + 3.8 + 2.9 against 8.7 + 7.6.
 constexpr int kTableThreads = 1024;
 constexpr int kTableMeanEntries = 2048;                  // pair scores in LDS at a time
+constexpr int kTableTrajectoriesMax = 512, kTableGroupsMax = 128;
 constexpr size_t kTableBytesMax = PCM_SCORE_STATIC_MAX_BYTES;
 
 struct TableWorkspace {
@@ -409,15 +411,27 @@ TableWorkspace carve_tables(void* ws, int n_groups, int G, int A, int K, int sli
     w.bytes = c.used();
     return w;
 }
-int phases_per_pair_block(int A) { return kTableThreads / A; }        // A <= 256
+constexpr int kTablesTogether = 8;                       // tables that a thread of the second launch loads at once
+// Threads of the second launch that share a sum, each a part of the group's tables, and phases per workgroup (A <= 256)
+struct PairBlock {
+    int parts, phases;
+};
+PairBlock pair_block(int A, int tables) {
+    const int parts = std::min(ceil_div(tables, kTablesTogether), kTableThreads / A);
+    return {parts, kTableThreads / (A * parts)};
+}
 
 // Slices per trajectory, or 0 where the batch takes the accumulators: the tables have to fit in 4 MiB, so that a shape fits the
 // library's own array if it did with those, and in the workspace that the caller brings (one that holds the accumulators is enough
-// for any call), and what the second launch adds up per sum has to stay short.  A slice is at least one chunk per thread, and no more
-// are made than two workgroups per CU want.
+// for any call).  A slice is at least one chunk per thread, and no more are made than two workgroups per compute unit want, or 64
+// tables per group.  Calls one after another, tables / accumulators, 56 values and 5 phases if not said (groups x trajectories x
+// chunks): 8 x 8 x 64 10.1 / 10.1 us; 32 x 8 x 128 12.6 / 13.2; 64 x 8 x 256, 12 phases 16.9 / 18.4; 1 x 8 x 1024 11.1 / 11.6;
+// 8 x 4 x 4096 14.2 / 21.6; 4 x 64 x 64 12.0 / 15.7; 4 x 32 x 256 of 256 values, 8 phases 19.9 / 30.2; 20 x 25 x 100 15.8 / 16.4.
+// Beyond 512 trajectories, more than two workgroups per compute unit, nothing is gained (128 x 8 x 128 18.8 / 18.8, 16 x 64 x 32
+// 16.6 / 16.8), and beyond 128 groups the mean is too long for the last workgroup (128 x 4 x 64 15.2 / 15.5, 170 x 3 x 100 18.9 / 17.4).
 int table_slices(int n_groups, int G, int N, int A, int K, size_t bytes_max) {
     if ((size_t)K * A * sizeof(ull) + (size_t)K * sizeof(int) > kLdsMax || G > kWave) return 0;
-    if ((int64_t)n_groups * ceil_div(K, phases_per_pair_block(A)) > 1024) return 0;       // workgroups of the second launch
+    if (n_groups > kTableGroupsMax || (int64_t)n_groups * G > kTableTrajectoriesMax) return 0;
     const int T = n_groups * G, per_pass = kTableThreads / (A % 4 == 0 ? A / 4 : A);
     int slices = std::min({ceil_div(512, T), ceil_div(N, per_pass), kWave / G});
     for (; slices > 0; --slices)
@@ -467,45 +481,69 @@ __global__ __launch_bounds__(kTableThreads) void score_tables(const float* __res
     if (active_out) active_out[i] = mixed ? 1 : 0;
 }
 
+template <bool kParts>
 __global__ __launch_bounds__(kTableThreads) void score_of_tables(const uint8_t* __restrict__ reward, int n_groups, int G, int A, int K, int slices,
-                                                                 int phases, TableWorkspace w, double* C_out, uint8_t* valid_out) {
+                                                                 int parts, int phases, TableWorkspace w, double* C_out, uint8_t* valid_out) {
     __shared__ double lds[kTableMeanEntries];
+    __shared__ int part_n[2][kTableThreads];
+    static_assert(kTableMeanEntries >= 2 * kTableThreads, "the parts of the sums fit");
     __shared__ int n_of[2][PCM_MAX_PHASES];
     const int blocks = (K + phases - 1) / phases, g = blockIdx.x / blocks, c0 = blockIdx.x % blocks * phases, kb = min(phases, K - c0);
     const int tid = threadIdx.x;
     const uint64_t won = successes_of(reward, g, G);
     const int s = __popcll(won);
     const bool mixed = s != 0 && s != G;
-    if (mixed && tid < kb * A) {
-        const int c = tid / A, tables = G * slices;
+    const int sums = kb * A, tables = G * slices;
+    int n_pos = 0, n_neg = 0;
+    ull s_pos = 0, s_neg = 0;
+    const int step = kParts ? parts * kTablesTogether : kTablesTogether;
+    if (mixed && tid < (kParts ? sums * parts : sums)) {
+        const int part = kParts ? tid / sums : 0, e = tid - part * sums, c = e / A;
         const size_t first = (size_t)g * tables;
         const int* const counts = w.counts + first * K + c0 + c;
-        const ull* const sums = w.sums + first * K * A + (size_t)c0 * A + tid;
-        int n_pos = 0, n_neg = 0;
-        ull s_pos = 0, s_neg = 0;
-        constexpr int kTogether = 8;              // tables whose loads are under way together
-        for (int t0 = 0; t0 < tables; t0 += kTogether) {
-            int n[kTogether];
-            ull v[kTogether];
+        const ull* const table_sums = w.sums + first * K * A + (size_t)c0 * A + e;
+        for (int t0 = part * kTablesTogether; t0 < tables; t0 += step) {
+            int n[kTablesTogether];
+            ull v[kTablesTogether];
 #pragma unroll
-            for (int u = 0; u < kTogether; ++u) {
+            for (int u = 0; u < kTablesTogether; ++u) {
                 const int t = min(t0 + u, tables - 1);
                 n[u] = counts[(size_t)t * K];
-                v[u] = sums[(size_t)t * K * A];
+                v[u] = table_sums[(size_t)t * K * A];
             }
 #pragma unroll
-            for (int u = 0; u < kTogether; ++u) {
+            for (int u = 0; u < kTablesTogether; ++u) {
                 if (t0 + u >= tables || n[u] == 0) continue;       // (a sum without a chunk was not written)
                 if ((won >> ((t0 + u) / slices)) & 1u) { n_pos += n[u]; s_pos += v[u]; }
                 else { n_neg += n[u]; s_neg += v[u]; }
             }
         }
-        if (n_pos > 0 && n_neg > 0) lds[tid] = squared_difference(s_pos, n_pos, s_neg, n_neg);
-        if (tid == c * A) {
+        if (!kParts && e == c * A) {
             n_of[0][c] = n_neg;
             n_of[1][c] = n_pos;
         }
     }
+    if (kParts && mixed) {                        // uniform
+        ull* const part_sum = reinterpret_cast<ull*>(lds);         // [2][kTableThreads]
+        part_sum[tid] = s_neg;
+        part_sum[kTableThreads + tid] = s_pos;
+        part_n[0][tid] = n_neg;
+        part_n[1][tid] = n_pos;
+        __syncthreads();
+        if (tid < sums)
+            for (int q = 1; q < parts; ++q) {
+                s_neg += part_sum[q * sums + tid];
+                s_pos += part_sum[kTableThreads + q * sums + tid];
+                n_neg += part_n[0][q * sums + tid];
+                n_pos += part_n[1][q * sums + tid];
+            }
+        if (tid < sums && tid % A == 0) {
+            n_of[0][tid / A] = n_neg;
+            n_of[1][tid / A] = n_pos;
+        }
+        __syncthreads();
+    }
+    if (mixed && tid < sums && n_pos > 0 && n_neg > 0) lds[tid] = squared_difference(s_pos, n_pos, s_neg, n_neg);
     __syncthreads();
     if (tid < kb) {
         double score = -1.0;                      // skipped: uniform rewards, or no chunks of one of the outcomes
@@ -724,8 +762,10 @@ int run_tables(const float* actions, const uint8_t* phase, const uint8_t* reward
         else score_tables<1><<<grid, kTableThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, G, N, A, K, slices, adv_eps, adv_out, active_out, w);
     }
     StageTimer t(ST_SCORE_FINALISE, s);
-    const int phases = phases_per_pair_block(A);
-    score_of_tables<<<(unsigned)n_groups * (unsigned)ceil_div(K, phases), kTableThreads, 0, s>>>(reward, n_groups, G, A, K, slices, phases, w, C_out, valid_out);
+    const PairBlock block = pair_block(A, G * slices);
+    const unsigned grid = (unsigned)n_groups * (unsigned)ceil_div(K, block.phases);
+    if (block.parts > 1) score_of_tables<true><<<grid, kTableThreads, 0, s>>>(reward, n_groups, G, A, K, slices, block.parts, block.phases, w, C_out, valid_out);
+    else score_of_tables<false><<<grid, kTableThreads, 0, s>>>(reward, n_groups, G, A, K, slices, block.parts, block.phases, w, C_out, valid_out);
     return launch_status();
 }
 

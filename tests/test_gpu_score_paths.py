@@ -39,6 +39,12 @@ def batch(n_groups, G, N, A, K, seed, ragged=True):
     (64, 8, 20, 56, 18),        # 4.0 MB of tables
     (64, 8, 20, 56, 19),        # and 4.2: accumulators
     (90, 3, 5, 3, 64),          # pair scores of several rounds through LDS in the mean
+    (3, 32, 40, 200, 9),        # five threads a sum for 64 tables, a phase per workgroup
+    (2, 9, 20, 75, 5),    # two threads a sum for nine tables
+    (8, 64, 3, 8, 3),           # 512 trajectories
+    (27, 19, 3, 8, 3),          # and 513: accumulators
+    (128, 4, 6, 5, 3),          # as many groups as tables take
+    (129, 3, 6, 5, 3),          # and one more: accumulators
 ])
 @pytest.mark.parametrize("largest", [1.0, 2.0 ** 20])       # the limit of the definition: sums of whole numbers up to 2^44
 def test_score_routes(n_groups, G, N, A, K, largest):
