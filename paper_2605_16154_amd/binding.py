@@ -5,6 +5,7 @@ PyTorch provides device memory (tensors) and the stream; nothing is computed her
 from __future__ import annotations
 
 import ctypes as C
+import importlib
 import os
 from typing import Dict, List, Optional, Tuple
 
@@ -41,7 +42,7 @@ def _sig(fn, res, args):
 
 def lib() -> C.CDLL:
     """The loaded C library.  Raises if it has not been built (no fallback exists)."""
-    global _lib
+    global _lib, _ptrs
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -84,6 +85,13 @@ def lib() -> C.CDLL:
     _sig(L.pcm_profile_stage_count, i32, [])
     _sig(L.pcm_profile_stage_name, C.c_char_p, [i32])
     _sig(L.pcm_profile_collect, i32, [C.POINTER(f64), C.POINTER(i64)])
+    try:
+        native = importlib.import_module("._pointers", __package__)
+    except ImportError as e:
+        raise PcmError(f"{os.path.join(_HERE, '_pointers.so')} is missing or does not load ({e}): build it with "
+                       "`python -m paper_2605_16154_amd.build`") from e
+    native.set_python_check(_ptr)
+    _ptrs = native.pointers
     _lib = L
     return L
 
@@ -103,6 +111,27 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, name: str = "tensor") -> Optiona
     if dtype is not None and t.dtype != dtype:
         raise PcmError(f"{name} must be {dtype}, got {t.dtype}")
     return t.data_ptr()
+
+
+def _ptrs(rules, *tensors):
+    """_ptr of each tensor by its rule (dtype or None, name).  Once the library is loaded the same in native code
+    (csrc/pointers.cpp), which calls _ptr for what it does not accept."""
+    return tuple(_ptr(t, dtype, name) for t, (dtype, name) in zip(tensors, rules))
+
+
+_F32, _F64, _U8, _I32, _I64, _BF16 = torch.float32, torch.float64, torch.uint8, torch.int32, torch.int64, torch.bfloat16
+_LABEL = ((_F32, "actions"), (_I32, "n_chunks"), (_U8, "phase"))
+_SCORE = ((_F32, "actions"), (_U8, "phase"), (_U8, "reward"), (_I32, "n_chunks"), (_F64, "C_out"), (_U8, "valid_out"),
+          (_F32, "adv_out"), (_U8, "active_out"))
+_KEEP = ((_I64, "state"), (_F64, "C"), (_U8, "valid"), (_F64, "keep_probs_out"))
+_SAMPLE = ((_F64, "keep_probs"), (_U8, "phase"), (_I32, "n_chunks"), (_U8, "active"), (_I32, "kept_idx"),
+           (_I32, "kept_offsets"), (_I32, "n_kept"))
+_IMPORTANCE = ((_U8, "phase"), (_I32, "n_chunks"), (_I32, "kept_idx"), (_I32, "kept_offsets"), (_F32, "weights"))
+_COUNTS = ((_U8, "phase"), (_I32, "n_chunks"), (_U8, "active"), (_I32, "kept_idx"), (_I32, "n_kept"),
+           (_I32, "kept_per_phase"), (_I32, "chunks_per_phase"))
+_STEP = ((None, "hidden"), (_U8, "tokens"), (_F32, "logp_old"), (_F32, "adv"), (_I32, "kept_idx"), (_I32, "n_kept"),
+         (None, "Wg"), (None, "Wu"), (None, "Wd"), (None, "Wo"), (_F32, "loss"), (_F32, "logp"), (_F32, "dW"), (_F32, "dW"),
+         (_F32, "dW"), (_F32, "dW"), (None, "dX"), (_F32, "stats"))
 
 
 def _stream() -> int:
@@ -181,9 +210,9 @@ def pcm_label_phases(actions, n_chunks, L: int, D: int, gripper_dim: Optional[in
     if out is None:
         out = torch.empty((T, N), dtype=torch.uint8, device=actions.device)
     g = D - 1 if gripper_dim is None else gripper_dim
-    rc = lib().pcm_label_phases(_ptr(actions, torch.float32, "actions"), _ptr(n_chunks, torch.int32, "n_chunks"), T, N,
-                                L, D, g, close_threshold, _ptr(out, torch.uint8, "phase"), _stream())
-    _check(rc, "pcm_label_phases")
+    entry = lib().pcm_label_phases
+    p_actions, p_chunks, p_out = _ptrs(_LABEL, actions, n_chunks, out)
+    _check(entry(p_actions, p_chunks, T, N, L, D, g, close_threshold, p_out, _stream()), "pcm_label_phases")
     return out
 
 
@@ -199,11 +228,8 @@ def pcm_score_phases(actions, phase, reward, n_chunks, n_groups: int, G: int, K:
         out = (torch.empty(K, dtype=torch.float64, device=dev), torch.empty(K, dtype=torch.uint8, device=dev),
                torch.empty(T, dtype=torch.float32, device=dev), torch.empty(T, dtype=torch.uint8, device=dev))
     Cc, valid, adv, active = out
-    args = (_ptr(actions, torch.float32, "actions"), _ptr(phase, torch.uint8, "phase"),
-            _ptr(reward, torch.uint8, "reward"), _ptr(n_chunks, torch.int32, "n_chunks"),
-            n_groups, G, N, A, K, adv_eps, _ptr(Cc, torch.float64, "C_out"),
-            _ptr(valid, torch.uint8, "valid_out"), _ptr(adv, torch.float32, "adv_out"),
-            _ptr(active, torch.uint8, "active_out"))
+    p = _ptrs(_SCORE, actions, phase, reward, n_chunks, Cc, valid, adv, active)
+    args = (*p[:4], n_groups, G, N, A, K, adv_eps, *p[4:])
     if static_scratch:
         _check(lib().pcm_score_phases_static(*args, _stream()), "pcm_score_phases_static")
         return out
@@ -221,10 +247,9 @@ def pcm_update_keep_probs(state, Cc, valid, p_min: float = 0.1, T_rc: int = 5, k
     K = Cc.shape[0]
     if keep_probs_out is None:
         keep_probs_out = torch.empty(K, dtype=torch.float64, device=Cc.device)
-    rc = lib().pcm_update_keep_probs(_ptr(state, torch.int64, "state"), _ptr(Cc, torch.float64, "C"),
-                                     _ptr(valid, torch.uint8, "valid"), K, p_min, T_rc,
-                                     _ptr(keep_probs_out, torch.float64, "keep_probs_out"), _stream())
-    _check(rc, "pcm_update_keep_probs")
+    entry = lib().pcm_update_keep_probs
+    p_state, p_C, p_valid, p_out = _ptrs(_KEEP, state, Cc, valid, keep_probs_out)
+    _check(entry(p_state, p_C, p_valid, K, p_min, T_rc, p_out, _stream()), "pcm_update_keep_probs")
     return keep_probs_out
 
 
@@ -246,11 +271,9 @@ def pcm_sample_chunks(keep_probs, phase, n_chunks, active, B: int, seed: int, st
         out = (torch.empty(T * min(B, N), dtype=torch.int32, device=dev),
                torch.empty(T + 1, dtype=torch.int32, device=dev), torch.empty(1, dtype=torch.int32, device=dev))
     kept_idx, kept_offsets, n_kept = out
-    head = (_ptr(keep_probs, torch.float64, "keep_probs"), _ptr(phase, torch.uint8, "phase"),
-            _ptr(n_chunks, torch.int32, "n_chunks"), _ptr(active, torch.uint8, "active"), T, N, K, B)
-    tail = (seed & 0xFFFFFFFFFFFFFFFF, step & 0xFFFFFFFFFFFFFFFF, _ptr(kept_idx, torch.int32, "kept_idx"),
-            _ptr(kept_offsets, torch.int32, "kept_offsets"), _ptr(n_kept, torch.int32, "n_kept"),
-            None, 0, _stream())                                       # no workspace: none is needed
+    p = _ptrs(_SAMPLE, keep_probs, phase, n_chunks, active, kept_idx, kept_offsets, n_kept)
+    head = (*p[:4], T, N, K, B)
+    tail = (seed & 0xFFFFFFFFFFFFFFFF, step & 0xFFFFFFFFFFFFFFFF, *p[4:], None, 0, _stream())      # no workspace: none is needed
     if selector == "pcm":
         _check(lib().pcm_sample_chunks(*head, *tail), "pcm_sample_chunks")
     else:
@@ -263,11 +286,9 @@ def pcm_importance_weights(phase, n_chunks, kept_idx, kept_offsets, K: int, out=
     T, N = phase.shape
     if out is None:
         out = torch.zeros(kept_idx.shape[0], dtype=torch.float32, device=phase.device)
-    rc = lib().pcm_importance_weights(_ptr(phase, torch.uint8, "phase"), _ptr(n_chunks, torch.int32, "n_chunks"),
-                                      _ptr(kept_idx, torch.int32, "kept_idx"),
-                                      _ptr(kept_offsets, torch.int32, "kept_offsets"), T, N, K,
-                                      _ptr(out, torch.float32, "weights"), _stream())
-    _check(rc, "pcm_importance_weights")
+    entry = lib().pcm_importance_weights
+    *p, p_out = _ptrs(_IMPORTANCE, phase, n_chunks, kept_idx, kept_offsets, out)
+    _check(entry(*p, T, N, K, p_out, _stream()), "pcm_importance_weights")
     return out
 
 
@@ -276,12 +297,9 @@ def pcm_kept_phase_counts(phase, n_chunks, active, kept_idx, n_kept, K: int, out
     T, N = phase.shape
     if out is None:
         out = (torch.empty(K, dtype=torch.int32, device=phase.device), torch.empty(K, dtype=torch.int32, device=phase.device))
-    rc = lib().pcm_kept_phase_counts(_ptr(phase, torch.uint8, "phase"), _ptr(n_chunks, torch.int32, "n_chunks"),
-                                     _ptr(active, torch.uint8, "active"), _ptr(kept_idx, torch.int32, "kept_idx"),
-                                     _ptr(n_kept, torch.int32, "n_kept"), kept_idx.shape[0], T, N, K,
-                                     _ptr(out[0], torch.int32, "kept_per_phase"), _ptr(out[1], torch.int32, "chunks_per_phase"),
-                                     _stream())
-    _check(rc, "pcm_kept_phase_counts")
+    entry = lib().pcm_kept_phase_counts
+    p = _ptrs(_COUNTS, phase, n_chunks, active, kept_idx, n_kept, out[0], out[1])
+    _check(entry(*p[:5], kept_idx.shape[0], T, N, K, *p[5:], _stream()), "pcm_kept_phase_counts")
     return out
 
 
@@ -382,12 +400,9 @@ def grpo_masked_actor_step(hidden, tokens, logp_old, adv, kept_idx, n_kept, T: i
     if need == 0:
         raise PcmError("grpo_masked_actor_step: unsupported shape or dtype for this path")
     stream = _stream()
-    head = (_ptr(hidden, None, "hidden"), _ptr(tokens, torch.uint8, "tokens"), _ptr(logp_old, torch.float32, "logp_old"),
-            _ptr(adv, torch.float32, "adv"), _ptr(kept_idx, torch.int32, "kept_idx"), _ptr(n_kept, torch.int32, "n_kept"),
-            max_kept_chunks, T, N, A, d, ff, V, dtype, _ptr(Wg, None, "Wg"), _ptr(Wu, None, "Wu"), _ptr(Wd, None, "Wd"),
-            _ptr(Wo, None, "Wo"))
-    tail = (_ptr(loss, torch.float32, "loss"), _ptr(logp, torch.float32, "logp"),
-            *[_ptr(g, torch.float32, "dW") for g in grads], _ptr(dX, None, "dX"), _ptr(stats, torch.float32, "stats"))
+    p = _ptrs(_STEP, hidden, tokens, logp_old, adv, kept_idx, n_kept, Wg, Wu, Wd, Wo, loss, logp, *grads, dX, stats)
+    head = (*p[:6], max_kept_chunks, T, N, A, d, ff, V, dtype, *p[6:10])
+    tail = p[10:]
     ws = _take_workspace(need, dev, stream)
     try:
         if extended:

@@ -1,10 +1,12 @@
 """Builds libpcm.so (the C-ABI library of include/pcm.h) and libpcm_measure.so (the stand-alone
-matrix-core rate probe of include/pcm_measure.h) for gfx950 with hipcc, in-tree."""
+matrix-core rate probe of include/pcm_measure.h) for gfx950 with hipcc, and the binding's argument checks
+(_pointers.so, host code against torch) with the host compiler, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -12,6 +14,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libpcm.so")
 MEASURE_LIB = os.path.join(PKG, "libpcm_measure.so")
+POINTERS = os.path.join(PKG, "_pointers.so")
 OBJ_DIR = os.path.join(PKG, "_build")
 
 SOURCES = ["runtime.hip", "score.hip", "keep_probs.hip", "sample.hip", "gather.hip",
@@ -47,10 +50,25 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_pointers() -> None:
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", sysconfig.get_paths()["include"],
+           *(x for path in include_paths() for x in ("-isystem", path)), os.path.join(CSRC, "pointers.cpp"), "-o", POINTERS,
+           "-L", torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{torch_lib}"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("building pointers.cpp failed:\n" + r.stderr)
+
+
 def build_library(jobs: int = 8) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        pointers = ex.submit(_build_pointers)
         objs = list(ex.map(_compile, SOURCES + MEASURE_SOURCES))
+        pointers.result()
     for lib, part in ((LIB, objs[:len(SOURCES)]), (MEASURE_LIB, objs[len(SOURCES):])):
         cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *part]
         r = subprocess.run(cmd, capture_output=True, text=True)
