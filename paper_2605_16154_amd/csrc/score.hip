@@ -389,6 +389,11 @@ __global__ __launch_bounds__(kThreads) void score_accumulate(
 // them and the hand-over to the last workgroup are the longer part), 6.1 + 7.5 with tables; 512 of up to 256 with 12 phases
 // 2.2 + 10.5 + 3.8 + 2.9 against 8.7 + 7.6.
 constexpr int kTableThreads = 1024;
+// Workgroups of 256 threads where these load a slice in one go (four vectors each), and where there are no more sums than that: the
+// wavefronts of a workgroup wait for each other several times.  Calls one after another, 1024 / 256 threads (groups x trajectories
+// x chunks, values, phases): 40 x 8 x 100, 14, 5 12.9 / 10.6 us; 54 x 5 x 47, 12, 12 11.2 / 9.9; 32 x 8 x 128 in two slices, 56, 5
+// 12.7 / 11.7; 32 x 8 x 64, 56, 5 10.8 / 10.9.
+constexpr int kNarrowThreads = 256, kNarrowLoads = 4 * kNarrowThreads;
 constexpr int kTableMeanEntries = 2048;                  // pair scores in LDS at a time
 constexpr int kTableTrajectoriesMax = 512, kTableGroupsMax = 128;
 constexpr size_t kTableBytesMax = PCM_SCORE_STATIC_MAX_BYTES;
@@ -425,7 +430,7 @@ PairBlock pair_block(int A, int tables) {
 // library's own array if it did with those, and in the workspace that the caller brings (one that holds the accumulators is enough
 // for any call).  A slice is at least one chunk per thread, and no more are made than two workgroups per compute unit want, or 64
 // tables per group.  Calls one after another, tables / accumulators, 56 values and 5 phases if not said (groups x trajectories x
-// chunks): 8 x 8 x 64 10.1 / 10.1 us; 32 x 8 x 128 12.6 / 13.2; 64 x 8 x 256, 12 phases 16.9 / 18.4; 1 x 8 x 1024 11.1 / 11.6;
+// chunks): 8 x 8 x 64 10.2 / 10.0 us; 32 x 8 x 128 11.7 / 13.2; 64 x 8 x 256, 12 phases 16.9 / 18.4; 1 x 8 x 1024 11.1 / 11.6;
 // 8 x 4 x 4096 14.2 / 21.6; 4 x 64 x 64 12.0 / 15.7; 4 x 32 x 256 of 256 values, 8 phases 19.9 / 30.2; 20 x 25 x 100 15.8 / 16.4.
 // Beyond 512 trajectories, more than two workgroups per compute unit, nothing is gained (128 x 8 x 128 18.8 / 18.8, 16 x 64 x 32
 // 16.6 / 16.8), and beyond 128 groups the mean is too long for the last workgroup (128 x 4 x 64 15.2 / 15.5, 170 x 3 x 100 18.9 / 17.4).
@@ -446,11 +451,11 @@ __device__ inline uint64_t successes_of(const uint8_t* reward, int g, int G) {
     return __ballot(r < G && x != 0);
 }
 
-template <int VEC>
-__global__ __launch_bounds__(kTableThreads) void score_tables(const float* __restrict__ actions, const uint8_t* __restrict__ phase,
-                                                              const uint8_t* __restrict__ reward, const int32_t* __restrict__ n_chunks, int G,
-                                                              int N, int A, int K, int slices, double adv_eps, float* adv_out,
-                                                              uint8_t* active_out, TableWorkspace w) {
+template <int VEC, int kT>
+__global__ __launch_bounds__(kT) void score_tables(const float* __restrict__ actions, const uint8_t* __restrict__ phase,
+                                                   const uint8_t* __restrict__ reward, const int32_t* __restrict__ n_chunks, int G, int N,
+                                                   int A, int K, int slices, double adv_eps, float* adv_out, uint8_t* active_out,
+                                                   TableWorkspace w) {
     extern __shared__ ull lds_sum[];
     int* const lds_cnt = reinterpret_cast<int*>(lds_sum + (size_t)K * A);
     const int i = blockIdx.x / slices, slice = blockIdx.x % slices, g = i / G, tid = threadIdx.x;
@@ -461,13 +466,13 @@ __global__ __launch_bounds__(kTableThreads) void score_tables(const float* __res
     Ni = Ni < 0 ? 0 : (Ni > N ? N : Ni);
     if (mixed) {                                  // with uniform rewards the group has no score; nobody reads its tables
         const int per = (N + slices - 1) / slices, k0 = slice * per, k1 = min(Ni, k0 + per);
-        accumulate_slice<VEC, kTableThreads>(actions, phase, i, k0, k1, N, A, K, 0, K, lds_sum, lds_cnt);
+        accumulate_slice<VEC, kT>(actions, phase, i, k0, k1, N, A, K, 0, K, lds_sum, lds_cnt);
         ull* const sums = w.sums + (size_t)blockIdx.x * K * A;
-        for (int e = tid; e < K * A; e += kTableThreads)
+        for (int e = tid; e < K * A; e += kT)
             if (lds_cnt[e / A] > 0) sums[e] = lds_sum[e];
         if (tid < K) w.counts[(size_t)blockIdx.x * K + tid] = lds_cnt[tid];
     }
-    if (tid != kTableThreads - 1) return;         // a thread that has had little to do
+    if (tid != kT - 1) return;         // a thread that has had little to do
     if (blockIdx.x == 0) *w.done = 0;
     if (slice != 0) return;
     float a = 0.f;
@@ -481,11 +486,12 @@ __global__ __launch_bounds__(kTableThreads) void score_tables(const float* __res
     if (active_out) active_out[i] = mixed ? 1 : 0;
 }
 
-template <bool kParts>
-__global__ __launch_bounds__(kTableThreads) void score_of_tables(const uint8_t* __restrict__ reward, int n_groups, int G, int A, int K, int slices,
+template <bool kParts, int kT>
+__global__ __launch_bounds__(kT) void score_of_tables(const uint8_t* __restrict__ reward, int n_groups, int G, int A, int K, int slices,
                                                                  int parts, int phases, TableWorkspace w, double* C_out, uint8_t* valid_out) {
     __shared__ double lds[kTableMeanEntries];
-    __shared__ int part_n[2][kTableThreads];
+    __shared__ int part_n[2][kParts ? kTableThreads : 1];
+    static_assert(!kParts || kT == kTableThreads);
     static_assert(kTableMeanEntries >= 2 * kTableThreads, "the parts of the sums fit");
     __shared__ int n_of[2][PCM_MAX_PHASES];
     const int blocks = (K + phases - 1) / phases, g = blockIdx.x / blocks, c0 = blockIdx.x % blocks * phases, kb = min(phases, K - c0);
@@ -556,7 +562,7 @@ __global__ __launch_bounds__(kTableThreads) void score_of_tables(const uint8_t* 
         store_shared(&w.pair[(size_t)g * K + c0 + tid], score);
     }
     if (!arrive_last(w.done, (int)gridDim.x)) return;
-    mean_of_groups<kTableThreads>(w.pair, n_groups, K, lds, kTableMeanEntries, C_out, valid_out, [](const double* p) { return load_shared(p); });
+    mean_of_groups<kT>(w.pair, n_groups, K, lds, kTableMeanEntries, C_out, valid_out, [](const double* p) { return load_shared(p); });
 }
 
 // ---- the smallest batches: one workgroup, one launch ---------------------------------------------
@@ -758,14 +764,25 @@ int run_tables(const float* actions, const uint8_t* phase, const uint8_t* reward
         const bool vec4 = is_vec4(actions, A);
         const unsigned grid = (unsigned)(n_groups * G) * (unsigned)slices;
         const size_t lds_bytes = (size_t)K * A * sizeof(ull) + (size_t)K * sizeof(int);
-        if (vec4) score_tables<4><<<grid, kTableThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, G, N, A, K, slices, adv_eps, adv_out, active_out, w);
-        else score_tables<1><<<grid, kTableThreads, lds_bytes, s>>>(actions, phase, reward, n_chunks, G, N, A, K, slices, adv_eps, adv_out, active_out, w);
+        const bool narrow = (int64_t)ceil_div(N, slices) * (vec4 ? A / 4 : A) <= kNarrowLoads;
+#define PCM_TABLES(VEC, THREADS)                                                                                               \
+    score_tables<VEC, THREADS><<<grid, THREADS, lds_bytes, s>>>(actions, phase, reward, n_chunks, G, N, A, K, slices, adv_eps, \
+                                                                adv_out, active_out, w)
+        if (vec4 && narrow) PCM_TABLES(4, kNarrowThreads);
+        else if (vec4) PCM_TABLES(4, kTableThreads);
+        else if (narrow) PCM_TABLES(1, kNarrowThreads);
+        else PCM_TABLES(1, kTableThreads);
+#undef PCM_TABLES
     }
     StageTimer t(ST_SCORE_FINALISE, s);
     const PairBlock block = pair_block(A, G * slices);
     const unsigned grid = (unsigned)n_groups * (unsigned)ceil_div(K, block.phases);
-    if (block.parts > 1) score_of_tables<true><<<grid, kTableThreads, 0, s>>>(reward, n_groups, G, A, K, slices, block.parts, block.phases, w, C_out, valid_out);
-    else score_of_tables<false><<<grid, kTableThreads, 0, s>>>(reward, n_groups, G, A, K, slices, block.parts, block.phases, w, C_out, valid_out);
+#define PCM_OF_TABLES(PARTS, THREADS)                                                                                       \
+    score_of_tables<PARTS, THREADS><<<grid, THREADS, 0, s>>>(reward, n_groups, G, A, K, slices, block.parts, block.phases, w, C_out, valid_out)
+    if (block.parts > 1) PCM_OF_TABLES(true, kTableThreads);
+    else if (K * A <= kNarrowThreads) PCM_OF_TABLES(false, kNarrowThreads);
+    else PCM_OF_TABLES(false, kTableThreads);
+#undef PCM_OF_TABLES
     return launch_status();
 }
 

@@ -41,6 +41,12 @@ def batch(n_groups, G, N, A, K, seed, ragged=True):
     (90, 3, 5, 3, 64),          # pair scores of several rounds through LDS in the mean
     (3, 32, 40, 200, 9),        # five threads a sum for 64 tables, a phase per workgroup
     (2, 9, 20, 75, 5),    # two threads a sum for nine tables
+    (8, 8, 73, 56, 5),          # narrow workgroups for the slices: 1022 vectors (wide ones for single floats)
+    (2, 8, 128, 32, 8),         # 1024 vectors, and as many sums as narrow workgroups form
+    (2, 8, 129, 32, 9),         # one slot more in two slices, more sums
+    (3, 4, 60, 68, 3),          # 1020 vectors
+    (3, 4, 61, 68, 3),          # 1037 in slices of 31 slots
+    (2, 2, 4, 256, 31),     # wide workgroups for the sums, narrow ones for the slices
     (8, 64, 3, 8, 3),           # 512 trajectories
     (27, 19, 3, 8, 3),          # and 513: accumulators
     (128, 4, 6, 5, 3),          # as many groups as tables take
