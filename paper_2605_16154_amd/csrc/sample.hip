@@ -73,9 +73,7 @@ __device__ inline int kept_count(const int32_t* n_chunks, const uint8_t* active,
 
 // `yes` in the lanes of `mask` (the same in every lane), else `no`: one instruction that takes the mask as it is.
 __device__ inline uint32_t select_by_lane(uint64_t mask, uint32_t yes, uint32_t no) {
-    uint32_t r;
-    asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(r) : "v"(no), "v"(yes), "s"(mask));
-    return r;
+    return __builtin_amdgcn_inverse_ballot_w64(mask) ? yes : no;
 }
 
 __device__ inline int wave_inclusive_scan(int v, int lane) {

@@ -128,3 +128,10 @@ def test_fp32_weight_gradient_sums_stay_short(cdll, rows, slices):
     parts = q(rows, 1, d, ff, V, 0, 1) - q(rows, 1, d, ff, V, 0, 0) - align(rows * V * 4) - align(rows * d * 4)
     pair = 2 * d * ff * 4                                                     # dWg and dWu in one launch
     assert parts == (align(slices * pair) if slices > 1 else 0)
+
+
+def test_sampler_leaves_waits_to_the_compiler():
+    """A vector register that inline assembly writes may be read by v_readlane one wait state later at the earliest, and the compiler
+    does not insert that wait behind inline assembly: the draws of the sampler use none."""
+    text = open(os.path.join(ROOT, "paper_2605_16154_amd", "csrc", "sample.hip")).read()
+    assert not re.search(r"\basm\b", text)
