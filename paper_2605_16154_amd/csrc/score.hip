@@ -96,12 +96,16 @@ __global__ __launch_bounds__(kThreads) void score_prepare(uint32_t* zero, size_t
     }
 }
 
-// rint(a 2^24) as a double, and sums of up to kExactRun of them, are exact: |a| <= 2^20, so they stay below 2^53.  Four
+// rint(a 2^24) as a double, and sums of up to kExactRun of them, are exact while |a| <= 2^20: they stay below 2^53.  Four
 // instructions a value where the conversion to a 64-bit integer and its addition take fourteen: the small
 // route at 16 trajectories of 32 chunks of 56 values 10.8 -> 7.6 us, the tables of 512 trajectories of up to
 // 256 chunks 9.3 -> 8.7, of 256 of up to 128 6.4 -> 6.1 us.
 __device__ inline double to_fixed(float a) { return (double)rintf(a * kActionScale); }
 constexpr int kExactRun = 256;
+// Values beyond that, infinities and NaN among them, are converted one by one and added as integers, so that they leave the
+// other chunks of a run as they are and the sums do not depend on the route.
+constexpr float kExactMax = 1048576.0f;                     // 2^20
+__device__ inline ull to_integer(float a) { return (ull)__float2ll_rn(a * kActionScale); }
 
 template <int VEC>
 struct ActionVec;
@@ -112,11 +116,15 @@ struct ActionVec<4> {
         const float4 t = *reinterpret_cast<const float4*>(p);
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     }
+    __device__ bool exact() const {
+        return fabsf(v[0]) <= kExactMax && fabsf(v[1]) <= kExactMax && fabsf(v[2]) <= kExactMax && fabsf(v[3]) <= kExactMax;
+    }
 };
 template <>
 struct ActionVec<1> {
     float v[1];
     __device__ void load(const float* p) { v[0] = *p; }
+    __device__ bool exact() const { return fabsf(v[0]) <= kExactMax; }
 };
 
 // Values that workgroups hand to one another within the launch are written and read with device-scope atomic operations
@@ -194,9 +202,14 @@ __device__ inline void accumulate_slice(const float* __restrict__ actions, const
 #pragma unroll
                     for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
                 }
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) acc[v] += to_fixed(x[u].v[v]);
                 ++run;
+                if (__ballot(!x[u].exact()) == 0) {
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) acc[v] += to_fixed(x[u].v[v]);
+                } else if (c >= 0 && c < kb) {
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) atomicAdd(&lds_sum[(size_t)c * A + jv * VEC + v], to_integer(x[u].v[v]));
+                }
             }
         }
         flush();
@@ -656,9 +669,14 @@ __global__ __launch_bounds__(kSmallThreads) void score_small(const float* __rest
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
         }
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[v] += to_fixed(x[u].v[v]);
         ++run;
+        if (__ballot(!x[u].exact()) == 0) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[v] += to_fixed(x[u].v[v]);
+        } else {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) atomicAdd(&lds_sum[(size_t)to * A + jv * VEC + v], to_integer(x[u].v[v]));
+        }
     }
     flush();
     __syncthreads();

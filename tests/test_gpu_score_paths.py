@@ -96,3 +96,21 @@ def test_the_accumulators_bound_the_workspace_on_every_route(shape):
     assert L.pcm_score_phases(*args, ws.data_ptr(), enough, stream) == 0
     assert np.array_equal(C.cpu().numpy().view(np.int64), C_o.view(np.int64))
     assert np.array_equal(valid.cpu().numpy(), valid_o)
+
+
+@pytest.mark.parametrize("n_groups,G,N,A,K", [(2, 8, 32, 56, 4), (3, 5, 12, 7, 3), (32, 8, 64, 56, 5), (3, 5, 50, 7, 9), (2, 4, 30, 256, 32)])
+def test_values_beyond_the_required_range(n_groups, G, N, A, K):
+    """|a| <= 2^20 is what the definition asks for.  Larger values still add up exactly, as integers, whichever route a batch takes, and
+    a NaN counts as 0 without touching the values around it."""
+    import paper_2605_16154_amd as pcm
+    actions, phase, reward, n_chunks = batch(n_groups, G, N, A, K, seed=N)
+    dev = lambda x: torch.from_numpy(x).cuda()
+    score = lambda a: [t.cpu().numpy() for t in pcm.pcm_score_phases(dev(a), dev(phase), dev(reward), dev(n_chunks), n_groups, G, K, 1e-6)[:2]]
+    where = np.random.default_rng(K).random(actions.shape)
+    large = np.where(where < 0.05, actions * np.float32(2.0 ** 30), actions).astype(np.float32)      # sums below 2^63
+    C, valid = score(large)
+    C_o, valid_o = O.phase_scores(large, phase, reward, np.minimum(n_chunks, N), n_groups, G, K)
+    assert np.array_equal(C.view(np.int64), C_o.view(np.int64)) and np.array_equal(valid, valid_o)
+    C, valid = score(np.where(where < 0.02, np.float32(np.nan), actions))
+    C_0, valid_0 = score(np.where(where < 0.02, np.float32(0.0), actions))
+    assert np.array_equal(C.view(np.int64), C_0.view(np.int64)) and np.array_equal(valid, valid_0)
