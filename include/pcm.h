@@ -44,7 +44,8 @@ extern "C" {
 typedef enum {
     PCM_OK = 0,
     PCM_EINVAL = -1,       /* null pointer, non-positive size, value out of the stated range */
-    PCM_EWORKSPACE = -2,   /* workspace missing, misaligned or smaller than the query says */
+    PCM_EWORKSPACE = -2,   /* workspace missing, misaligned or smaller than the query says (or, where an entry
+                              point names a smaller size that is enough, than that) */
     PCM_EHIP = -3,         /* a HIP call (kernel launch, event) reported an error */
     PCM_EUNSUPPORTED = -4  /* shape or dtype outside what the kernels implement */
 } pcm_status;
@@ -280,6 +281,10 @@ PCM_API int pcm_kept_phase_counts(const uint8_t* phase, const int32_t* n_chunks,
  * dtype PCM_BF16: bf16 storage, MFMA with fp32 accumulation, bf16 intermediates;
  *             requires d % 256 == 0, ff % 256 == 0, V == 256.
  * ------------------------------------------------------------------------------------------ */
+/* fp32: the query names the bytes with which the call is fastest.  A call takes any workspace that holds its
+ * matrices as they are, about rows * (12 d + 12 ff + 8 V) + 8 ff V bytes and the parts of the weight gradients
+ * (rows * (8 d + 12 ff + 4 V) + 8 ff V without gradients); loss and log-probabilities have the same bits either way,
+ * gradients differ by the rounding of their sums. */
 PCM_API size_t grpo_masked_actor_step_workspace_bytes(int max_kept_chunks, int A, int d, int ff, int V,
                                               int dtype, int want_grads);
 PCM_API int grpo_masked_actor_step(const void* hidden, const uint8_t* tokens, const float* logp_old,

@@ -18,7 +18,7 @@ POINTERS = os.path.join(PKG, "_pointers.so")
 OBJ_DIR = os.path.join(PKG, "_build")
 
 SOURCES = ["runtime.hip", "score.hip", "keep_probs.hip", "sample.hip", "gather.hip",
-           "actor_f32.hip", "actor_bf16.hip", "actor_api.hip", "optimizer.hip", "labeler.hip"]
+           "actor_f32.hip", "actor_f32_direct.hip", "actor_bf16.hip", "actor_api.hip", "optimizer.hip", "labeler.hip"]
 MEASURE_SOURCES = ["measure/mfma_rate.hip"]
 # the fp64 tails of the selection stage are specified without fused multiply-add
 NO_CONTRACT = {"score.hip", "keep_probs.hip"}

@@ -91,13 +91,25 @@ struct TransposeList {
 // A launch of nothing but transposes; stream: non-temporal stores.
 void launch_transposes(const TransposeList& list, bool stream, hipStream_t s);
 
+// What the copy of the kept chunks' rows reads and writes, in units of Vec.
+template <typename Vec>
+struct GatherArgs {
+    const Vec* hidden;
+    const uint8_t* tokens;
+    const float *logp_old, *adv;
+    const int32_t *kept_idx, *n_kept;
+    int max_chunks, T, N, A, V, vec_per_row;
+    int64_t row_offset, rows_pad;   // rows are those of a panel that starts at batch row row_offset;
+    Vec* X;                         // X and the metadata arrays are the panel's
+    RowMeta meta;
+};
 // Copies the kept chunks' hidden rows into X [rows_pad, d] (rows from n_kept*A to the end of
-// their tile of 256 are zero-filled, later ones left as they are: nothing reads them) and fills the row metadata (bf16 path).
+// their tile of 256 are zero-filled, later ones left as they are: nothing reads them) and fills the row metadata.  elem_bytes is 2 (bf16) or 4 (fp32).
 // With row_offset > 0 the rows are those of a panel of the batch that starts at that row: X and the metadata
 // arrays are the panel's own, `rows_pad` its height.  The same holds for the two per-chunk-ratio launches below
 // (row_offset a multiple of A, so no chunk straddles two panels).
 // In the same launch: the transposes of `layouts`, and zeros in zero[0 .. n_zero).
-[[nodiscard]] int launch_gather(const ActorShape& sh, const ActorIO& io, void* X, int64_t row_offset, int64_t rows_pad,
+[[nodiscard]] int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void* X, int64_t row_offset, int64_t rows_pad,
                   RowMeta meta, const TransposeList& layouts, double* zero, int n_zero, hipStream_t s);
 
 // Partial sums of squares of the four weight gradients, left by the launches that wrote their final values.
@@ -106,8 +118,8 @@ struct SumsqLists {
     int count[4];
 };
 // Sums of partial products that split reductions left: out = (add: out +) parts[0] + parts[1] + .. in that order (fp32, n
-// floats, parts `stride` floats apart).  With live_row > 0 it is one over the rows of the batch, live_row floats each, and ends with
-// the row tile of the last live one.  With sumsq, on the final panel every workgroup also leaves the sum of the squares of what it wrote in
+// floats, parts `stride` floats apart).  With live_row > 0 it is one over the rows of the batch, live_row floats each, the parts of which end
+// with the last live one's tile of live_tile rows; behind it `out` is left as it is if added to, and zero otherwise.  With sumsq, on the final panel every workgroup also leaves the sum of the squares of what it wrote in
 // sumsq[its number within the job].
 struct PartsSum {
     const float* parts;
@@ -115,7 +127,7 @@ struct PartsSum {
     size_t n, stride;
     float* out;
     double* sumsq;
-    int live_row;
+    int live_row, live_tile;
     int first, blocks, threads, vec;   // workgroups, their threads that take part; vec: 16-byte accesses
 };
 struct PartsSums {
@@ -124,7 +136,7 @@ struct PartsSums {
     int n, blocks;
     static int blocks_for(size_t n_floats, int n_parts);      // workgroups of a sum at most
     void add(const float* parts, int n_parts, size_t n_floats, size_t stride, float* out, bool add_to = false, double* sumsq = nullptr,
-             int live_row = 0);
+             int live_row = 0, int live_tile = 256);
 };
 // What a step does behind its last product, in one launch: sums of parts, and if asked for (with_loss) the per-row loss terms
 // and statistics of the whole batch, in a fixed order (one workgroup, fp64 accumulators).  With lists the partial sums of
@@ -137,6 +149,10 @@ struct FinalPanel;
 // (written to every row of the chunk; the term only to its first row).
 [[nodiscard]] int launch_chunk_ratio(const ActorShape& sh, const ActorIO& io, RowMeta meta, RowOut out, int64_t row_offset,
                        int64_t rows_pad, hipStream_t s);
+
+// fp32 path, direct route: dz[r, :] = coef[r] * dz[r, :] (+ extra[r, :] if extra is given) for the live rows r (V columns each).
+[[nodiscard]] int launch_scale_rows_f32(const ActorShape& sh, const ActorIO& io, float* dz, const float* extra, const float* coef,
+                          int64_t rows, hipStream_t s);
 
 // Backward pass over the rows that carry a gradient only (bf16 path).  A kernel lists the panel's rows whose factor
 // in dz is non-zero and writes, to device memory, what the backward products then read: their row count and which
@@ -213,8 +229,10 @@ __device__ inline LossRow loss_row(float logp, float logp_old, float adv, float 
 }
 
 // actor_f32.hip / actor_bf16.hip ---------------------------------------------------------------
-size_t actor_f32_workspace_bytes(const ActorShape& sh, bool bwd, bool composed);
-int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t s);
+// fp32: bytes with which a call is fastest, and those that are enough for any call of the shape.
+size_t actor_f32_workspace_bytes(const ActorShape& sh, bool bwd, const LossOptions& opt, bool composed);
+size_t actor_f32_least_bytes(const ActorShape& sh, bool bwd);
+int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, size_t ws_bytes, hipStream_t s);
 size_t actor_bf16_workspace_bytes(const ActorShape& sh, bool want_grads, const LossOptions& opt, bool composed);
 int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t s);
 size_t packed_head_bytes(int d, int ff, int V);

@@ -20,7 +20,7 @@ bool shape_valid(const ActorShape& sh) {
 
 namespace {
 size_t workspace_need(const ActorShape& sh, int dtype, bool bwd, const LossOptions& opt, bool composed) {
-    return dtype == PCM_F32 ? actor_f32_workspace_bytes(sh, bwd, composed) : actor_bf16_workspace_bytes(sh, bwd, opt, composed);
+    return dtype == PCM_F32 ? actor_f32_workspace_bytes(sh, bwd, opt, composed) : actor_bf16_workspace_bytes(sh, bwd, opt, composed);
 }
 LossOptions plain_options(float eps_low, float eps_high, float loss_scale) {
     return LossOptions{eps_low, eps_high, loss_scale, 0.f, 0, 0, nullptr, 0, nullptr, 0, nullptr};
@@ -77,13 +77,13 @@ int run_actor_step(const void* hidden, const uint8_t* tokens, const float* logp_
     }
     // the split-precision forward pass of the per-chunk ratio exists for the evaluation as written only
     if (dtype == PCM_BF16 && opt.chunk_ratio && composed) return PCM_EUNSUPPORTED;
-    const size_t need = workspace_need(sh, dtype, bwd, opt, composed);
+    const size_t need = dtype == PCM_F32 ? actor_f32_least_bytes(sh, bwd) : workspace_need(sh, dtype, bwd, opt, composed);
     if (!workspace_ok(workspace, workspace_bytes, need)) return PCM_EWORKSPACE;
 
     ActorIO io{hidden, tokens, logp_old, adv, kept_idx, n_kept, Wg, Wu, Wd, Wo, opt,
                loss_out, logp_out, dWg, dWu, dWd, dWo, dX, stats_out, n_stats, composed};
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return dtype == PCM_F32 ? actor_f32_run(sh, io, workspace, s) : actor_bf16_run(sh, io, workspace, s);
+    return dtype == PCM_F32 ? actor_f32_run(sh, io, workspace, workspace_bytes, s) : actor_bf16_run(sh, io, workspace, s);
 }
 
 }  // namespace

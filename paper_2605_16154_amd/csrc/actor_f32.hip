@@ -9,7 +9,7 @@
 // multiply-adds has, and they do 16 times the multiply-adds of the fp32 ones: six products take 3/8 of the time at the same share
 // of their rates.
 // Measured against fp32 matrix instructions throughout, steps: 10,752 rows of 1024 -> 2816 -> 1024 -> 256, a quarter of them not kept,
-// 3.74 -> 2.54 ms; 5376 of 256 -> 1024 -> 256 -> 256 362 -> 273 us; 360 of 473 -> 333 -> 473 -> 512 185 -> 124, 1440 of 619 -> 1302 -> 619 ->
+// 3.74 -> 2.54 ms; 5376 of 256 -> 1024 -> 256 -> 256 362 -> 262 to 287 us, by the box; 360 of 473 -> 333 -> 473 -> 512 185 -> 124, 1440 of 619 -> 1302 -> 619 ->
 // 256 413 -> 201, 8960 of 103 -> 149 -> 103 -> 256, composed, where most of the padded tiles is padding, 171 -> 149; faster at 16 of 16
 // sizes, 1.15 to 2.06 times.  Loss, log-probabilities and statistics have the same bits; errors of the gradients against 64 bits,
 // root mean square over six inputs each: dX 4.85e-6 -> 4.74e-6 and 2.78e-6 -> 2.71e-6 at the first two, no larger at any of ten sizes.
@@ -21,296 +21,20 @@
 // and its up column, and so are u and v, and du and dv.  Operands are padded with zeros to whole blocks in the workspace, so any
 // size runs; results are written as far as they reach.
 //
+// Heads and batches for which that does not pay, and calls whose workspace is too short for it, take their matrices as they are
+// (actor_f32_direct.hip; uses_blocks).
+//
 // Backward products of one dependency level share a launch and long reductions are split into parts that a later launch adds up
 // in order (no atomics), as in the bf16 path.  Row tiles beyond the kept count are skipped.
 #include <algorithm>
 
-#include "gemm_floats.h"
-#include "gemm_thirds.h"
+#include "actor_f32.h"
+#include "epilogues_f32.h"
 
 namespace pcm {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kW = kSmallTile;
-using ThirdsCoord = TileCoord<kW>;
-using ThirdsSums = Accumulators<kW>;
-
-__device__ __forceinline__ void split4(f32x4 v, bf16x4 (&out)[3]) {
-    const float x[4] = {v[0], v[1], v[2], v[3]};
-    uint32_t part[3][2];
-    split_in_three(x, part);
-#pragma unroll
-    for (int t = 0; t < 3; ++t) out[t] = __builtin_bit_cast(bf16x4, (uint64_t)part[t][0] | (uint64_t)part[t][1] << 32);
-}
-// Four consecutive columns n .. n + 3 of a row with N of them, as far as they are there.
-__device__ __forceinline__ void store4(float* row, int n, int N, f32x4 v) {
-    if (n + 3 < N) {
-        *reinterpret_cast<f32x4_any*>(row + n) = v;
-    } else {
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-            if (n + t < N) row[n + t] = v[t];
-    }
-}
-
-// The parts of kRows rows of kRowBytes each from a staging area, rows `stride` bytes apart and the parts of a row kRowBytes, to C
-// from (row, column) on, multiples of kRows and 32; rows at and beyond n_rows are not written.
-template <int kRows, int kRowBytes>
-__device__ __forceinline__ void copy_thirds_out(const char* st, int stride, const Thirds& C, int64_t row, int64_t column, int n_rows, int lane) {
-    constexpr int kLanesPerRow = kRowBytes / 16, kRowsPerPass = 64 / kLanesPerRow;
-    static_assert(kRowsPerPass % 2 == 0 && kThirdsUnit % kRows == 0, "both rows of a line in a pass, all rows in a block");
-    const int r = lane / kLanesPerRow, c = lane % kLanesPerRow;
-    bf16* const out = C.p + Thirds::at(row + r, column + c * 8, C.ld);
-    const char* const src = st + r * stride + c * 16;
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-#pragma unroll
-        for (int pass = 0; pass < kRows / kRowsPerPass; ++pass)
-            if (pass * kRowsPerPass < n_rows)            // wave-uniform: n_rows is a multiple of a pass's rows
-                *reinterpret_cast<u32x4*>(out + t * kThirdsPart + pass * kRowsPerPass * 32) =
-                    *reinterpret_cast<const u32x4*>(src + t * kRowBytes + pass * kRowsPerPass * stride);
-}
-
-// ---- epilogues: results go through the wavefront's staging area, as those of the bf16 path do -------------------------
-
-// C = acc as thirds.  Columns up to C.ld (a multiple of a wavefront's), rows below `rows`.
-struct EpiThirds {
-    Thirds C;
-    int rows;
-    __device__ __forceinline__ void operator()(const ThirdsCoord& tc, const ThirdsSums& acc, char* lds) const {
-        constexpr int RW = kWaveRows<kW>, kRow = RW * 2, kStride = 3 * kRow + 16;
-        const int col_base = tc.col0();
-        if (col_base >= C.ld) return;
-        char* const st = wave_stage(tc, lds);
-#pragma unroll
-        for (int i = 0; i < RW / 32; ++i) {                // 32 rows per pass
-#pragma unroll
-            for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-                for (int j = 0; j < kW; ++j) {
-                    bf16x4 part[3];
-                    split4(acc[2 * i + ii][j], part);
-                    char* const at = st + (ii * 16 + (tc.lane & 15)) * kStride + (j * 16 + 4 * (tc.lane >> 4)) * 2;
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(at + t * kRow) = part[t];
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            __builtin_amdgcn_wave_barrier();
-            const int row_base = tc.row0() + i * 32;
-            copy_thirds_out<32, kRow>(st, kStride, C, row_base, col_base, rows - row_base, tc.lane);
-            __builtin_amdgcn_wave_barrier();
-        }
-    }
-};
-
-// C = acc in fp32, M x N with rows ldc apart, of any alignment; part s of a split reduction goes to C + s * split_stride.
-struct EpiFloats {
-    float* C;
-    int64_t ldc, split_stride;
-    int M, N;
-    __device__ __forceinline__ void operator()(const ThirdsCoord& tc, const ThirdsSums& acc, char* lds) const {
-        constexpr int RW = kWaveRows<kW>, kStride = RW * 4 + 16, kLanesPerRow = RW / 4, kRowsPerPass = 64 / kLanesPerRow;
-        char* const st = wave_stage(tc, lds);
-        float* const out = C + tc.split * split_stride;
-        const int n = tc.col0() + tc.lane % kLanesPerRow * 4;
-#pragma unroll
-        for (int i = 0; i < RW / 32; ++i) {                // 32 rows per pass
-#pragma unroll
-            for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-                for (int j = 0; j < kW; ++j)
-                    *reinterpret_cast<f32x4*>(st + (ii * 16 + (tc.lane & 15)) * kStride + (j * 16 + 4 * (tc.lane >> 4)) * 4) = acc[2 * i + ii][j];
-            __builtin_amdgcn_wave_barrier();
-            const int row0 = tc.row0() + i * 32 + tc.lane / kLanesPerRow;
-#pragma unroll 8
-            for (int q = 0; q < 32 / kRowsPerPass; ++q) {
-                const int row = row0 + q * kRowsPerPass;
-                const f32x4 v = *reinterpret_cast<const f32x4*>(st + (q * kRowsPerPass + tc.lane / kLanesPerRow) * kStride + tc.lane % kLanesPerRow * 16);
-                if (row < M) store4(out + (int64_t)row * ldc, n, N, v);
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-    }
-};
-
-// The same where the product's columns are 32 of one matrix and the same 32 of another in turn (each M x N, rows N apart).
-struct EpiFloatsPair {
-    float* C[2];
-    int64_t split_stride;
-    int M, N;
-    __device__ __forceinline__ void operator()(const ThirdsCoord& tc, const ThirdsSums& acc, char* lds) const {
-        constexpr int RW = kWaveRows<kW>, kStride = RW * 4 + 16, kLanesPerRow = RW / 4, kRowsPerPass = 64 / kLanesPerRow;
-        char* const st = wave_stage(tc, lds);
-        const int packed = tc.col0() + tc.lane % kLanesPerRow * 4, n = packed / 64 * 32 + packed % 32;
-        float* const out = (packed & 32 ? C[1] : C[0]) + tc.split * split_stride;
-#pragma unroll
-        for (int i = 0; i < RW / 32; ++i) {                // 32 rows per pass
-#pragma unroll
-            for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-                for (int j = 0; j < kW; ++j)
-                    *reinterpret_cast<f32x4*>(st + (ii * 16 + (tc.lane & 15)) * kStride + (j * 16 + 4 * (tc.lane >> 4)) * 4) = acc[2 * i + ii][j];
-            __builtin_amdgcn_wave_barrier();
-            const int row0 = tc.row0() + i * 32 + tc.lane / kLanesPerRow;
-#pragma unroll 8
-            for (int q = 0; q < 32 / kRowsPerPass; ++q) {
-                const int row = row0 + q * kRowsPerPass;
-                const f32x4 v = *reinterpret_cast<const f32x4*>(st + (q * kRowsPerPass + tc.lane / kLanesPerRow) * kStride + tc.lane % kLanesPerRow * 16);
-                if (row < M) store4(out + (int64_t)row * N, n, N, v);
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-    }
-};
-
-// acc = da.  du = da v silu'(u) and dv = da silu(u) as thirds, in blocks of 32 columns of each in turn, as u and v are.
-struct EpiGateUpBackward {
-    const float* uv;         // [rows, duv.ld]
-    Thirds duv;
-    __device__ __forceinline__ void operator()(const ThirdsCoord& tc, const ThirdsSums& acc, char* lds) const {
-        constexpr int RW = kWaveRows<kW>, kRow = 2 * RW * 2, kStride = 3 * kRow + 16;
-        const int col_base = 2 * tc.col0();                // packed column of this wavefront's block of 2 RW
-        if (col_base >= duv.ld) return;
-        char* const st = wave_stage(tc, lds);
-        constexpr int kTogether = 4;                       // tiles whose u and v are on their way together
-#pragma unroll
-        for (int i = 0; i < kW; ++i) {                     // 16 rows per pass
-            const int64_t row_base = tc.row0() + i * 16;
-            const float* const from = uv + (row_base + (tc.lane & 15)) * duv.ld + col_base + 4 * (tc.lane >> 4);
-            char* const to = st + (tc.lane & 15) * kStride + 4 * (tc.lane >> 4) * 2;
-#pragma unroll
-            for (int j0 = 0; j0 < kW; j0 += kTogether) {
-                f32x4 u[kTogether], v[kTogether];
-#pragma unroll
-                for (int q = 0; q < kTogether; ++q) {
-                    const int at = (j0 + q) / 2 * 64 + (j0 + q) % 2 * 16;
-                    u[q] = *reinterpret_cast<const f32x4*>(from + at);
-                    v[q] = *reinterpret_cast<const f32x4*>(from + at + 32);
-                }
-#pragma unroll
-                for (int q = 0; q < kTogether; ++q) {
-                    const int at = (j0 + q) / 2 * 64 + (j0 + q) % 2 * 16;
-                    f32x4 du, dv;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const float x = u[q][t], g = acc[i][j0 + q][t], s = 1.f / (1.f + expf(-x));
-                        du[t] = g * v[q][t] * (s * (1.f + x * (1.f - s)));
-                        dv[t] = g * (x * s);
-                    }
-                    bf16x4 pu[3], pv[3];
-                    split4(du, pu);
-                    split4(dv, pv);
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) {
-                        *reinterpret_cast<bf16x4*>(to + t * kRow + at * 2) = pu[t];
-                        *reinterpret_cast<bf16x4*>(to + t * kRow + (at + 32) * 2) = pv[t];
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            copy_thirds_out<16, kRow>(st, kStride, duv, row_base, col_base, 16, tc.lane);
-            __builtin_amdgcn_wave_barrier();
-        }
-    }
-};
-
-// ---- forward ------------------------------------------------------------------------------------
-
-// 32 rows x 32 columns of a wavefront of gemm_floats, v[g] columns 8 g + 4 (lane >> 5) .. + 3 of row (lane & 31), to C and, if it is
-// there, to C3, from (row, column) on.
-__device__ __forceinline__ void put_square(char* st, int lane, const f32x4 (&v)[4], const FloatBlocks& C, const Thirds& C3, int64_t row,
-                                           int64_t column) {
-    constexpr int kStride = 128 + 16, kStride3 = 3 * 64 + 16;
-    const int r = lane & 31, half = lane >> 5;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {                          // the even columns of eight, then the odd ones
-        *reinterpret_cast<float2*>(st + r * kStride + g * 32 + half * 8) = make_float2(v[g][0], v[g][2]);
-        *reinterpret_cast<float2*>(st + r * kStride + g * 32 + 16 + half * 8) = make_float2(v[g][1], v[g][3]);
-    }
-    __builtin_amdgcn_wave_barrier();
-    copy_rows_out<32, 128>(st, kStride, reinterpret_cast<char*>(C.p + FloatBlocks::at(row, column, C.ld)), 128, 32, lane);
-    __builtin_amdgcn_wave_barrier();
-    if (C3.p == nullptr) return;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        bf16x4 part[3];
-        split4(v[g], part);
-#pragma unroll
-        for (int t = 0; t < 3; ++t) *reinterpret_cast<bf16x4*>(st + r * kStride3 + t * 64 + (8 * g + 4 * half) * 2) = part[t];
-    }
-    __builtin_amdgcn_wave_barrier();
-    copy_thirds_out<32, 64>(st, kStride3, C3, row, column, 32, lane);
-    __builtin_amdgcn_wave_barrier();
-}
-template <int kJ>
-__device__ __forceinline__ void put_rows(char* st, int lane, const f32x16 (&acc)[kJ], float* C, int64_t ldc) {   // 32 rows, row-major
-    constexpr int kStride = 32 * kJ * 4 + 16;
-#pragma unroll
-    for (int j = 0; j < kJ; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<f32x4*>(st + (lane & 31) * kStride + (j * 32 + 8 * g + 4 * (lane >> 5)) * 4) =
-                f32x4{acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]};
-    __builtin_amdgcn_wave_barrier();
-    copy_rows_out<32, 32 * kJ * 4>(st, kStride, reinterpret_cast<char*>(C), ldc * 4, 32, lane);
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Gate and up projection, columns in blocks of 32 of each in turn: a = silu(u) v, and for a backward pass u and v as they are in
-// the product.
-struct EpiGateUp {
-    float* uv;               // [rows, 2 a.ld] or null
-    FloatBlocks a;
-    Thirds a3;
-    template <int kI, int kJ>
-    __device__ __forceinline__ void operator()(const FloatsCoord<kI, kJ>& tc, const f32x16 (&acc)[kI][kJ], char* st) const {
-        static_assert(kJ == 2, "a gate block and its up block");
-#pragma unroll
-        for (int i = 0; i < kI; ++i) {
-            const int64_t row = tc.row0 + 32 * i;
-            if (uv != nullptr) put_rows(st, tc.lane, acc[i], uv + row * 2 * a.ld + tc.col0, 2 * a.ld);
-            f32x4 r[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float x = acc[i][0][4 * g + t], y = acc[i][1][4 * g + t];
-                    r[g][t] = x / (1.f + expf(-x)) * y;
-                }
-            put_square(st, tc.lane, r, a, a3, row, tc.col0 / 2);
-        }
-    }
-};
-// A product that is an operand of others.
-struct EpiOperand {
-    FloatBlocks C;
-    Thirds C3;
-    template <int kI, int kJ>
-    __device__ __forceinline__ void operator()(const FloatsCoord<kI, kJ>& tc, const f32x16 (&acc)[kI][kJ], char* st) const {
-#pragma unroll
-        for (int i = 0; i < kI; ++i)
-#pragma unroll
-            for (int j = 0; j < kJ; ++j) {
-                f32x4 v[4];
-#pragma unroll
-                for (int e = 0; e < 16; ++e) v[e / 4][e % 4] = acc[i][j][e];
-                put_square(st, tc.lane, v, C, C3, tc.row0 + 32 * i, tc.col0 + 32 * j);
-            }
-    }
-};
-// C row-major.
-struct EpiRows {
-    float* C;
-    int64_t ldc;
-    template <int kI, int kJ>
-    __device__ __forceinline__ void operator()(const FloatsCoord<kI, kJ>& tc, const f32x16 (&acc)[kI][kJ], char* st) const {
-#pragma unroll
-        for (int i = 0; i < kI; ++i) put_rows(st, tc.lane, acc[i], C + (int64_t)(tc.row0 + 32 * i) * ldc + tc.col0, ldc);
-    }
-};
-
 // The tile whose workgroups, shared out over the 256 CUs, have the least to do: the matrix pipes are shared by the workgroups of
 // a CU, so a CU's time is the number of its tiles times their size; the smaller tile counts 1.08 times its size.  By themselves
 // 128 x 128, 64 x 128 and 64 x 64 take at 8192 x 5632 x 1024 802 / 731 / 717 us, at 8192 x 1024 x 2816 332 / 336 / 341, at 8192 x 1024 x
@@ -327,19 +51,6 @@ void launch_floats(const FloatsProblem& p, const Epilogue& epi, hipStream_t s) {
 
 // ---- backward products -----------------------------------------------------------------------------------
 
-// A product of thirds among others of its launch.
-template <int kLayA, int kLayB, class Epilogue>
-struct ThirdsProduct {
-    GemmProblem p;
-    Epilogue epi;
-    int first;                   // its first workgroup, a multiple of eight (see tile_of_workgroup)
-    int workgroups(int tile) {   // operands are padded, so a tile may reach beyond the matrix
-        p.M = ceil_div(p.M, tile) * tile;
-        p.N = ceil_div(p.N, tile) * tile;
-        return p.M / tile * (p.N / tile) * p.splits;
-    }
-    __device__ __forceinline__ void run(int block, ThirdsRing& smem) const { thirds_tile<kLayA, kLayB>(p, epi, block - first, smem); }
-};
 template <int kLayA, int kLayB, class Epilogue>
 ThirdsProduct<kLayA, kLayB, Epilogue> job(const GemmProblem& p, const Epilogue& epi) { return {p, epi, 0}; }
 
@@ -389,28 +100,13 @@ __device__ inline float wave_sum(float x) {
     return x;
 }
 
-// One wavefront per row, a column per lane and 64: log-softmax at the target bin, entropy, ratio, clipped surrogate, and dz =
-// coef * (onehot - softmax) + entropy part as thirds.  With a per-chunk ratio the factor is not known yet: z <- onehot - softmax
-// and the entropy part goes to `extra`; scale_rows makes dz of them once the chunk ratios are known.
-constexpr int kMaxV = 1024;
-struct LossArgs {
-    float* z;                // [rows, ld]
-    int V, ld;
-    float* extra;            // [rows, V]
-    Thirds dz;               // p null: no backward pass
-    RowMeta meta;
-    const int32_t* n_kept;
-    int max_chunks, A;
-    LossOptions opt;
-    float* logp_out;
-    RowOut out;
-};
+// (see LossArgs; kQ * 64 columns at most: 43,008 rows of 256 take 4 us longer with the checks of 1024)
+template <int kQ>
 __global__ __launch_bounds__(kThreads) void loss_rows(LossArgs p) {
-    constexpr int kQ = kMaxV / kWave;
     const int lane = threadIdx.x % kWave;
     const int64_t r = (int64_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
     const int64_t rows = live_rows(p.n_kept, p.max_chunks, p.A);
-    if (r >= (rows + kTileM - 1) / kTileM * kTileM) return;     // later rows: skipped tiles, read by nothing
+    if (r >= p.rows || r >= (rows + p.row_tile - 1) / p.row_tile * p.row_tile) return;     // later rows: skipped tiles, read by nothing
     const bool live = r < rows;
     const float scale = objective_scale(p.opt, rows);
     float* const zr = p.z + r * p.ld;
@@ -450,7 +146,7 @@ __global__ __launch_bounds__(kThreads) void loss_rows(LossArgs p) {
         }
         if (p.logp_out && live) p.logp_out[r] = lp;
     }
-    if (p.dz.p == nullptr) return;
+    if (p.dz.p == nullptr && !p.in_place) return;
     const float coef = p.opt.chunk_ratio ? (live ? 1.f : 0.f) : (live ? lr.coef : 0.f);
     const float ec = live ? p.opt.entropy_coef * scale : 0.f;
 #pragma unroll
@@ -466,6 +162,8 @@ __global__ __launch_bounds__(kThreads) void loss_rows(LossArgs p) {
         if (p.opt.chunk_ratio) {
             zr[j] = pg;
             if (live && j < p.V) p.extra[r * p.V + j] = ent;
+        } else if (p.in_place) {
+            zr[j] = pg + ent;
         } else {
             const float x[2] = {pg + ent, 0.f};
             uint32_t part[3][1];
@@ -570,7 +268,6 @@ F32Plan plan_step(const ActorShape& sh, int64_t Mp, bool composed) {
     }
     // dX in two parts at most: one goes to dX itself, which the other is added to
     two(shape(Mp, d, gu, 2), shape(d, gu, Mp, kMaxParts), p.dX, p.dWgu);
-    if (d <= 64 && ff <= 64) p.dWgu = ceil_div((int)sh.rows_max(), 64);       // a small weight gradient in slices of 64 rows
     return p;
 }
 
@@ -590,24 +287,28 @@ struct F32Workspace {
     size_t bytes;
 };
 
-// One layout for calls with and without gradients: those without hold the buffers of the backward products too, and those with
-// have three more at the end.
-F32Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool composed) {
+F32Workspace carve(void* ws, const ActorShape& sh, bool bwd, const LossOptions& opt, bool composed) {
     Carver c(ws);
     F32Workspace w{};
     const int64_t Mp = w.Mp = tiles256(sh.rows_max());
     const auto thirds = [&](int64_t rows, int64_t columns) { return Thirds{c.take<bf16>((size_t)(3 * padded(rows) * padded(columns))), padded(columns)}; };
     const auto floats = [&](int64_t rows, int64_t columns) { return FloatBlocks{c.take<float>((size_t)(padded(rows) * padded(columns))), padded(columns)}; };
-    w.plan = plan_step(sh, Mp, composed);
-    const F32Plan& plan = w.plan;
+    const F32Plan& plan = w.plan = plan_step(sh, Mp, composed);
     const int64_t ffp = padded(sh.ff), Vp = padded(sh.V);
+    const size_t M = (size_t)sh.rows_max(), d = sh.d, ff = sh.ff, V = sh.V;
+    // du and dv come when X, a and y as floats are no longer needed, and lie in their place
     w.X = floats(Mp, sh.d);
     w.a = floats(Mp, sh.ff);
+    if (!composed) w.y = floats(Mp, sh.d);
+    if (bwd) {
+        w.duv = Thirds{reinterpret_cast<bf16*>(w.X.p), 2 * ffp};
+        const size_t bytes = (size_t)Mp * 2 * ffp * 3 * sizeof(bf16);
+        if (bytes > c.used()) c.take<uint8_t>(bytes - c.used());
+    }
     w.WguT = floats(2 * ffp, sh.d);
     w.WdT = composed ? floats(sh.ff, sh.d) : floats(sh.d, sh.ff);
     w.WoT = floats(sh.V, sh.d);
     if (composed) w.WdoT = floats(sh.V, sh.ff);
-    else w.y = floats(Mp, sh.d);
     w.z = c.take<float>((size_t)Mp * Vp);
     w.meta.token = c.take<uint8_t>(Mp);
     w.meta.logp_old = c.take<float>(Mp);
@@ -618,48 +319,83 @@ F32Workspace carve(void* ws, const ActorShape& sh, bool bwd, bool composed) {
     w.out.clipped = c.take<uint8_t>(Mp);
     w.out.entropy = c.take<float>(Mp);
     w.out.coef = c.take<float>(Mp);
-    const size_t M = (size_t)sh.rows_max(), d = sh.d, ff = sh.ff, V = sh.V;
-    F32Workspace b{};                     // of the backward pass
-    b.uv = c.take<float>((size_t)Mp * 2 * ffp);
-    b.Wgu = thirds(d, 2 * ffp);
-    b.Wd = thirds(ff, d);
-    b.Wo = thirds(d, V);
-    b.X3 = thirds(Mp, d);
-    b.a3 = thirds(Mp, ff);
-    b.dz = thirds(Mp, V);
-    b.duv = thirds(Mp, 2 * ffp);
+    if (!bwd) {
+        w.bytes = c.used();
+        return w;
+    }
+    w.uv = c.take<float>((size_t)Mp * 2 * ffp);
+    w.Wgu = thirds(sh.d, 2 * ffp);
+    w.Wd = thirds(sh.ff, sh.d);
+    w.Wo = thirds(sh.d, sh.V);
+    w.X3 = thirds(Mp, sh.d);
+    w.a3 = thirds(Mp, sh.ff);
+    w.dz = thirds(Mp, sh.V);
     if (composed) {
-        b.WdoT3 = thirds(V, ff);
-        b.G = thirds(ff, V);
-        b.parts_G = c.take<float>((size_t)plan.G * ffp * Vp);
+        w.WdoT3 = thirds(sh.V, sh.ff);
+        w.G = thirds(sh.ff, sh.V);
+        w.parts_G = c.take<float>((size_t)plan.G * ffp * Vp);
     } else {
-        b.y3 = thirds(Mp, d);
-        b.dy = thirds(Mp, d);
+        w.y3 = thirds(Mp, sh.d);
+        w.dy = thirds(Mp, sh.d);
     }
-    const int o = plan.dWo, dd = plan.dWd, gu = plan.dWgu;
-    if (o > 1) b.parts_o = c.take<float>(o * d * V);
-    if (dd > 1) b.parts_d = c.take<float>(dd * ff * d);
-    if (bwd) {
-        w.uv = b.uv; w.Wgu = b.Wgu; w.Wd = b.Wd; w.Wo = b.Wo; w.X3 = b.X3; w.a3 = b.a3; w.y3 = b.y3; w.dz = b.dz; w.dy = b.dy; w.duv = b.duv;
-        w.WdoT3 = b.WdoT3; w.G = b.G; w.parts_G = b.parts_G; w.parts_o = b.parts_o; w.parts_d = b.parts_d;
-        w.z_extra = c.take<float>(M * V);
-        w.dX_part = c.take<float>(M * d);
-        if (gu > 1) w.parts_g = c.take<float>(2 * gu * d * ff);
-        w.parts_u = w.parts_g + gu * d * ff;
-    }
+    const size_t o = plan.dWo, dd = plan.dWd, gu = plan.dWgu;
+    if (o > 1) w.parts_o = c.take<float>(o * d * V);
+    if (dd > 1) w.parts_d = c.take<float>(dd * ff * d);
+    if (gu > 1) w.parts_g = c.take<float>(2 * gu * d * ff);
+    w.parts_u = w.parts_g + gu * d * ff;
+    if (plan.dX > 1) w.dX_part = c.take<float>(M * d);
+    if (opt.chunk_ratio) w.z_extra = c.take<float>(M * V);
     w.bytes = c.used();
     return w;
 }
 
-}  // namespace
-
-size_t actor_f32_workspace_bytes(const ActorShape& sh, bool bwd, bool composed) {
-    return carve(nullptr, sh, bwd, composed).bytes;
+// Whether operands go into blocks first, or a step takes them as they are (the direct route).  Blocks cost a pass over the weights
+// before the first product, padding to 128 and, for the composed head with gradients, a launch more; what they give grows with rows x
+// head.  Measured, direct / blocks, us a call (f: forward, s: step, c: composed; V = 256), by the lines below:
+//   few rows, wide head
+//     4096 -> 11008  56 rows s 1695 / 1725, c f 830 / 937, c s 1840 / 1951 (f 877 / 820); 168 rows s 2216 / 1793, c f 1072 / 940
+//     3072 -> 8192   56 rows s 1241 / 1068, c f 580 / 539, c s 1290 / 1234
+//   many rows, head narrower than a block: the products wait for memory, and what is padded to 128 is twice as long
+//     64 -> 300      43,008 rows f 157 / 171, s 393 / 531, c s 477 / 560; 10,752 rows f 64.6 / 65.1, s 170 / 160, c s 192 / 179
+//     64 -> 1024     43,008 rows f 321 / 312, s 846 / 1017; c f 432 / 374, c s 1173 / 1151; 10,752 rows f 107 / 105, s 282 / 307
+//     1024 -> 64     43,008 rows f 493 / 549, s 1380 / 1393, c s 724 / 808; 10,752 rows f 170 / 178, s 436 / 404, c s 276 / 276
+//     128 -> 128     43,008 rows f 147.6 / 146.8, s 355 / 365, c s 316 / 342; 86,016 rows f 264 / 259, s 662 / 638, c s 571 / 578
+//   small heads
+//     64 -> 64       56 rows f 26.3 / 28.2, s 62.5 / 71.6; 10,752 rows f 49.4 / 54.6, s 116.5 / 116.8, c s 117 / 134
+//     64 -> 128      2688 rows f 33.2 / 32.5, s 84.7 / 89.4, c s 98.9 / 107.9; 5376 rows f 39.7 / 38.0, s 101.4 / 96.6, c s 110 / 118;
+//                    21,504 rows f 70 / 77, s 184 / 162, c s 189 / 178
+//     128 -> 128     1344 rows f 35.5 / 34.2, s 86.9 / 86.5, c s 93.6 / 101.7; 2688 rows c s 105.7 / 110.9; 5376 rows c s 118 / 120
+//     100 -> 300     1344 rows f 41.8 / 38.3, s 106 / 97, c s 115 / 116; 2688 rows c s 125.0 / 124.7
+//     256 -> 256     56 rows c s 95 / 99, 168 rows 104.8 / 103.8
+// Elsewhere blocks are ahead, up to 1.8 times.
+bool uses_blocks(const ActorShape& sh, bool bwd, bool composed) {
+    const int64_t rows = sh.rows_max(), head = (int64_t)sh.d * sh.ff, M = 1 << 20;
+    if (rows <= 64 && head > 32 * M && (bwd || composed)) return false;
+    if (std::min(sh.d, sh.ff) <= 64 && rows > 32768 && (!composed || sh.ff <= 512)) return false;
+    if (head <= 4 * 1024) return false;
+    if (head <= 8 * 1024) return bwd && rows * head > (composed ? 44 : 22) * M;
+    return !(composed && bwd && head <= 36 * 1024 && rows * head <= 44 * M);
 }
 
-int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t s) {
+}  // namespace
+
+void launch_loss_rows(const LossArgs& p, hipStream_t s) {
+    const unsigned grid = (unsigned)ceil_div(p.rows, kThreads / kWave);
+    if (p.ld <= 256) loss_rows<4><<<grid, kThreads, 0, s>>>(p);
+    else loss_rows<kMaxV / kWave><<<grid, kThreads, 0, s>>>(p);
+}
+
+size_t actor_f32_least_bytes(const ActorShape& sh, bool bwd) { return direct_workspace_bytes(sh, bwd); }
+size_t actor_f32_workspace_bytes(const ActorShape& sh, bool bwd, const LossOptions& opt, bool composed) {
+    const size_t least = direct_workspace_bytes(sh, bwd);      // enough for any other options of the shape, too
+    return uses_blocks(sh, bwd, composed) ? std::max(least, carve(nullptr, sh, bwd, opt, composed).bytes) : least;
+}
+
+int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, size_t ws_bytes, hipStream_t s) {
     const bool grads = io.want_grads(), bwd = grads || io.dX != nullptr;
-    const F32Workspace w = carve(ws, sh, bwd, io.composed);
+    if (!uses_blocks(sh, bwd, io.composed)) return direct_run(sh, io, ws, s);
+    const F32Workspace w = carve(ws, sh, bwd, io.opt, io.composed);
+    if (w.bytes > ws_bytes) return direct_run(sh, io, ws, s);
     const F32Plan& plan = w.plan;
     const int Mp = (int)w.Mp, M = (int)sh.rows_max(), d = sh.d, ff = sh.ff, V = sh.V;
     const int ffp = (int)padded(ff), Vp = (int)padded(V), dp = (int)padded(d);
@@ -715,8 +451,7 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t
     }
     {
         StageTimer t(ST_F32_LOSS, s);
-        loss_rows<<<(unsigned)(Mp / (kThreads / kWave)), kThreads, 0, s>>>(
-            LossArgs{w.z, V, Vp, w.z_extra, w.dz, w.meta, io.n_kept, sh.max_chunks, sh.A, io.opt, io.logp_out, w.out});
+        launch_loss_rows(LossArgs{w.z, V, Vp, w.z_extra, w.dz, false, w.meta, io.n_kept, sh.max_chunks, sh.A, Mp, kTileM, io.opt, io.logp_out, w.out}, s);
     }
     if (io.opt.chunk_ratio) {
         rc = launch_chunk_ratio(sh, io, w.meta, w.out, 0, M, s);
@@ -757,7 +492,7 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t
         }
         float* const out_X = static_cast<float*>(io.dX);
         const int x = plan.dX;                                                         // dX = du Wg^T + dv Wu^T
-        const auto dX = job<kRowsByK, kRowsByK>(product(w.duv, w.Wgu, Mp, d, 2 * ffp, kRowsAreM, x), EpiFloats{out_X, d, w.dX_part - out_X, M, d});
+        const auto dX = job<kRowsByK, kRowsByK>(product(w.duv, w.Wgu, Mp, d, 2 * ffp, kRowsAreM, x), EpiFloats{out_X, d, x > 1 ? w.dX_part - out_X : 0, M, d});
         if (out_X && x > 1) sums.add(w.dX_part, 1, (size_t)M * d, (size_t)M * d, out_X, true, nullptr, d);
         if (grads) {
             const int gu = plan.dWgu;                                                    // dWg = X^T du, dWu = X^T dv

@@ -22,19 +22,9 @@ __device__ inline Vec zero_vec();
 template <>
 __device__ inline uint4 zero_vec<uint4>() { return make_uint4(0, 0, 0, 0); }
 template <>
+__device__ inline uint32_t zero_vec<uint32_t>() { return 0u; }
+template <>
 __device__ inline uint16_t zero_vec<uint16_t>() { return 0; }
-
-template <typename Vec>
-struct GatherArgs {
-    const Vec* hidden;
-    const uint8_t* tokens;
-    const float *logp_old, *adv;
-    const int32_t *kept_idx, *n_kept;
-    int max_chunks, T, N, A, V, vec_per_row;
-    int64_t row_offset, rows_pad;   // rows are those of a panel that starts at batch row row_offset;
-    Vec* X;                         // X and the metadata arrays are the panel's
-    RowMeta meta;
-};
 
 // The metadata of rows [r0, r0 + kRowsPerBlock) of the panel, and where they come from (row of hidden, or -1 for a row of zeros).
 template <typename Vec>
@@ -184,14 +174,6 @@ __device__ __forceinline__ void store_floats(const float (&x)[8], float* at) {
 }
 // The fp32 path's counterpart of prepare_step (see launch_prepare_f32).  Bound by memory: four bytes read and four or six written
 // per value; every thread has four groups of eight values under way.
-struct PrepareF32 {
-    GatherArgs<float> gather;    // X unused
-    FloatBlocks X;
-    Thirds X3;
-    WeightJobs weights;
-    float* dX;
-    int gather_blocks;
-};
 __device__ inline void gather_rows_f32(const PrepareF32& p, int block) {
     __shared__ int64_t src_row[kRowsPerBlock];
     const GatherArgs<float>& g = p.gather;
@@ -344,15 +326,16 @@ __global__ __launch_bounds__(kFinishThreads) void finish_loss(LossReduceArgs los
 // parts are read eight at a time, so that their loads are under way together (the five sums and the loss of a step of 5376 fp32 rows of
 // 256 -> 1024 -> 256: six launches of 46 us -> two of 20).
 template <class Vec>
-__device__ inline double sum_parts(const PartsSum& job, int block, size_t n) {
+__device__ inline double sum_parts(const PartsSum& job, int block, size_t n, size_t limit) {
     constexpr int kPer = sizeof(Vec) / sizeof(float), kTogether = 8;
     if ((int)threadIdx.x >= job.threads) return 0.0;
     const size_t stride = (size_t)job.blocks * job.threads * kPer;
     double sq = 0.0;
     for (size_t i = ((size_t)block * job.threads + threadIdx.x) * kPer; i < n; i += stride) {
         auto part = [&](int s) { return *reinterpret_cast<const Vec*>(job.parts + (size_t)s * job.stride + i); };
-        Vec acc = job.add ? *reinterpret_cast<const Vec*>(job.out + i) + part(0) : part(0);
-        for (int s0 = 1; s0 < job.n_parts; s0 += kTogether) {
+        Vec acc = {};
+        if (i < limit) acc = job.add ? *reinterpret_cast<const Vec*>(job.out + i) + part(0) : part(0);
+        for (int s0 = 1; i < limit && s0 < job.n_parts; s0 += kTogether) {
             Vec v[kTogether];
 #pragma unroll
             for (int u = 0; u < kTogether; ++u) v[u] = part(min(s0 + u, job.n_parts - 1));
@@ -376,9 +359,13 @@ __global__ __launch_bounds__(kFinishThreads) void finish_step(PartsSums sums, Fi
     for (int q = 1; q < PartsSums::kMax; ++q) which += q < sums.n && block >= sums.job[q].first ? 1 : 0;
     const PartsSum job = sums.job[which];
     block -= job.first;
-    size_t n = job.n;
-    if (job.live_row > 0) n = min(n, (size_t)((live_rows(loss.n_kept, loss.max_chunks, loss.A) + 255) / 256 * 256) * job.live_row);
-    double sq = job.vec ? sum_parts<f32x4>(job, block, n) : sum_parts<float>(job, block, n);
+    size_t n = job.n, limit = job.n;              // with live_row a multiple of four, or n
+    if (job.live_row > 0) {
+        const int64_t tile = job.live_tile, live = live_rows(loss.n_kept, loss.max_chunks, loss.A);
+        limit = min(n, (size_t)((live + tile - 1) / tile * tile) * job.live_row);
+        if (job.add) n = limit;
+    }
+    double sq = job.vec ? sum_parts<f32x4>(job, block, n, limit) : sum_parts<float>(job, block, n, limit);
     if (job.sumsq == nullptr || !panel()) return;
     __shared__ double wave_part[kFinishThreads / kWave];
 #pragma unroll
@@ -419,6 +406,21 @@ __global__ __launch_bounds__(kRatioThreads) void chunk_ratio_rows(const float* _
         ratio[r] = lr.ratio;
         clipped[r] = lr.clipped;
         coef[r] = lr.coef;
+    }
+}
+
+// Rows [0, live rows) only: rows beyond them hold zeros (or, in row tiles that the logit product
+// skipped, nothing) and are not read by anything downstream.
+__global__ __launch_bounds__(256) void scale_rows_f32(float* __restrict__ dz, const float* __restrict__ extra,
+                                                      const float* __restrict__ coef, const int32_t* __restrict__ n_kept,
+                                                      int max_chunks, int A, int64_t rows_max, int V) {
+    const int64_t live = live_rows(n_kept, max_chunks, A), rows = live < rows_max ? live : rows_max;
+    const int64_t n = rows * V;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        float x = coef[i / V] * dz[i];
+        if (extra) x += extra[i];
+        dz[i] = x;
     }
 }
 
@@ -583,10 +585,10 @@ int launch_prepare_f32(const ActorShape& sh, const ActorIO& io, const FloatBlock
     return launch_status();
 }
 
-int launch_gather(const ActorShape& sh, const ActorIO& io, void* X, int64_t row_offset, int64_t rows_pad,
+int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void* X, int64_t row_offset, int64_t rows_pad,
                   RowMeta meta, const TransposeList& layouts, double* zero, int n_zero, hipStream_t s) {
     StageTimer t(ST_GATHER, s);
-    const int64_t row_bytes = (int64_t)sh.d * 2;
+    const int64_t row_bytes = (int64_t)sh.d * elem_bytes;
     const unsigned blocks = (unsigned)ceil_div64(rows_pad, kRowsPerBlock);
     const unsigned grid = (unsigned)layouts.blocks + blocks + (unsigned)ceil_div(n_zero, kThreads);
     const bool aligned16 = row_bytes % 16 == 0 && (reinterpret_cast<uintptr_t>(io.hidden) & 15u) == 0 &&
@@ -600,6 +602,7 @@ int launch_gather(const ActorShape& sh, const ActorIO& io, void* X, int64_t row_
         else prepare_step<Vec, false><<<grid, kThreads, 0, s>>>(args, (int)blocks, layouts, ZeroSlots{zero, n_zero});
     };
     if (aligned16) launch(uint4{}, row_bytes / 16);
+    else if (elem_bytes == 4) launch(uint32_t{}, sh.d);
     else launch(uint16_t{}, sh.d);
     return launch_status();
 }
@@ -628,9 +631,10 @@ static SumShape sum_shape(size_t n_floats, bool may_vec, int n_parts) {
     }
     return best;
 }
-void PartsSums::add(const float* parts, int n_parts, size_t n_floats, size_t stride, float* out, bool add_to, double* sumsq, int live_row) {
+void PartsSums::add(const float* parts, int n_parts, size_t n_floats, size_t stride, float* out, bool add_to, double* sumsq, int live_row,
+                    int live_tile) {
     PartsSum& p = job[n++];
-    p = PartsSum{parts, n_parts, add_to ? 1 : 0, n_floats, stride, out, sumsq, live_row, blocks, 0, 0, 0};
+    p = PartsSum{parts, n_parts, add_to ? 1 : 0, n_floats, stride, out, sumsq, live_row, live_tile, blocks, 0, 0, 0};
     const bool may_vec = n_floats % 4 == 0 && stride % 4 == 0 && ((reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(parts)) & 15u) == 0;
     const SumShape shape = sum_shape(n_floats, may_vec, n_parts);
     p.blocks = shape.blocks;
@@ -661,6 +665,14 @@ int launch_chunk_ratio(const ActorShape& sh, const ActorIO& io, RowMeta meta, Ro
     chunk_ratio_rows<<<(unsigned)ceil_div64(slots, kRatioSlots), kRatioThreads, 0, s>>>(out.dlogp, meta.adv, io.n_kept, sh.max_chunks,
                                                                       sh.A, row_offset, rows_pad, io.opt, out.term,
                                                                       out.ratio, out.clipped, out.coef);
+    return launch_status();
+}
+
+int launch_scale_rows_f32(const ActorShape& sh, const ActorIO& io, float* dz, const float* extra, const float* coef,
+                          int64_t rows, hipStream_t s) {
+    StageTimer t(ST_REDUCE, s);
+    const int64_t blocks = ceil_div64(rows * sh.V, 256);
+    scale_rows_f32<<<(unsigned)(blocks < 4096 ? blocks : 4096), 256, 0, s>>>(dz, extra, coef, io.n_kept, sh.max_chunks, sh.A, rows, sh.V);
     return launch_status();
 }
 

@@ -81,6 +81,15 @@ struct WeightJobs {
     }
     static int64_t padded(int64_t n) { return ceil_div64(n, kThirdsUnit) * kThirdsUnit; }
 };
+// Its argument.
+struct PrepareF32 {
+    GatherArgs<float> gather;    // X unused
+    FloatBlocks X;
+    Thirds X3;
+    WeightJobs weights;
+    float* dX;
+    int gather_blocks;
+};
 [[nodiscard]] int launch_prepare_f32(const ActorShape& sh, const ActorIO& io, const FloatBlocks& X, const Thirds& X3, int64_t rows_pad,
                                      RowMeta meta, const WeightJobs& weights, float* dX, hipStream_t s);
 

@@ -1,9 +1,10 @@
 """The fp32 actor step where its operands in blocks and as three bf16 matrices can go wrong: sizes at the edges of the padding and of the
-tiles, magnitudes at the ends of the fp32 range, and values that are no numbers."""
+tiles, the lines between its two routes, magnitudes at the ends of the fp32 range and values that are no numbers."""
 import numpy as np
 import pytest
 import torch
 
+from paper_2605_16154_amd import binding
 from test_gpu_actor import CONFIGS, check, condition_logp_old, make_problem, pcm, run_both  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -88,3 +89,49 @@ def test_f32_rows_that_are_no_numbers_stay_alone(pcm, value):   # noqa: F811
     _, got = run_both(pcm, dict(pr, hidden=bad), want_grads=False, want_dX=False)
     others = np.arange(len(want["logp"])) != 17
     assert np.isnan(got["logp"][17]) and np.array_equal(got["logp"][others], want["logp"][others])
+
+
+@pytest.mark.parametrize("composed", [False, True])
+@pytest.mark.parametrize("d,ff,A,n_kept,max_kept", [
+    (64, 128, 16, 176, 176),          # 2816 rows: the last as they are, 22 x 2^20 values of a row and the head
+    (64, 128, 16, 177, 177),          # and the first in blocks (composed: as they are)
+    (64, 80, 16, 2048, 2048),         # 32,768 rows: the last of a narrow head in blocks
+    (64, 80, 16, 2049, 2049),         # and the first as they are
+    (128, 288, 4, 312, 312),          # 1248 rows: composed as they are, 44 x 2^20 values of a row and the head at most
+    (128, 288, 4, 313, 313),          # and in blocks
+    (128, 289, 4, 20, 40),            # a head of more than 36 x 1024 values: in blocks whatever the rows
+    (64, 129, 4, 20, 40),             # more than 8 x 1024
+    (64, 64, 4, 20, 40),              # 4 x 1024: as they are
+    (65, 64, 4, 20, 40),              # a few more, and few rows: as they are
+])
+def test_f32_routes(pcm, d, ff, A, n_kept, max_kept, composed):   # noqa: F811
+    pr = problem(d, ff, 64, A, n_kept)
+    for variants in ({}, dict(chunk_ratio=True, entropy_coef=1e-3)):
+        # per-chunk ratio: the log-ratio of a chunk is a sum over its rows
+        ref, got = run_both(pcm, pr, max_kept=max_kept, composed_head=composed, variants=variants)
+        check(ref, got, 5 * TOL if variants else TOL, len(ref["rows"]), n_stats=5 if variants else 4)
+        assert not got["dX"][len(ref["rows"]):].any()
+
+
+@pytest.mark.parametrize("composed", [False, True])
+@pytest.mark.parametrize("grads,least", [(True, 11409920), (False, 4590080)])
+def test_f32_least_workspace(pcm, monkeypatch, grads, least, composed):   # noqa: F811
+    """An fp32 call takes the bytes that every call of its shape took before operands went into blocks (720 rows of 192 -> 320 -> 128): the
+    operands then stay as they are.  The forward pass has the same bits either way."""
+    pr = problem(192, 320, 128, 8, 85)
+    kw = dict(max_kept=90, composed_head=composed, want_grads=grads, want_dX=grads)
+    _, whole = run_both(pcm, pr, **kw)
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+    taken = []
+    monkeypatch.setattr(binding, "_take_workspace", lambda need, dev, stream: taken.append(need) or ws)
+    monkeypatch.setattr(binding, "_give_workspace", lambda *a: None)
+    ref, got = run_both(pcm, pr, **kw)
+    n = len(ref["rows"])
+    assert taken[0] > least if grads else taken[0] >= least
+    assert np.array_equal(got["loss"], whole["loss"]) and np.array_equal(got["logp"][:n], whole["logp"][:n])
+    if grads:
+        check(ref, got, TOL, n)
+        assert not got["dX"][n:].any()
+    ws = torch.empty(least - 256, dtype=torch.uint8, device="cuda")
+    with pytest.raises(binding.PcmError, match="workspace"):
+        run_both(pcm, pr, **kw)

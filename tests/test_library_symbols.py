@@ -117,10 +117,25 @@ def test_binding_fails_loudly_without_the_library(monkeypatch, tmp_path):
         b.lib()
 
 
+def test_fp32_workspace_holds_what_a_call_uses(cdll):
+    """Without gradients: the rows of X, a and y in tiles of 256, the logits, a few values per row and the weights in blocks, or the buffers of
+    the route that takes them as they are.  With gradients little more than twice what a call accepts."""
+    q = cdll.grpo_masked_actor_step_workspace_bytes
+    q.restype = ctypes.c_size_t
+    for chunks, d, ff, V in ((192, 1024, 2816, 256), (4096, 1024, 2816, 256), (3, 4096, 11008, 256), (18750, 64, 64, 256)):
+        rows, pad = chunks * 56, lambda n: -(-n // 128) * 128
+        blocks = 4 * (-(-rows // 256) * 256 * (2 * pad(d) + pad(ff) + pad(V) + 8) + 3 * pad(d) * pad(ff) + pad(d) * pad(V))
+        as_they_are = 4 * (rows * (2 * d + 3 * ff + V + 8) + 2 * ff * V)
+        assert q(chunks, 56, d, ff, V, 0, 0) <= max(blocks, as_they_are) + 40 * 256, (chunks, d, ff)
+    assert q(4096, 56, 1024, 2816, 256, 0, 1) < 2.2 * 11098193920
+    assert q(1, 56, 4096, 11008, 256, 0, 1) < 50e6
+
+
 @pytest.mark.parametrize("rows,slices", [(2000, 32), (125, 2), (564, 9), (64, 1), (65, 2)])
 def test_fp32_weight_gradient_sums_stay_short(cdll, rows, slices):
-    """A small weight gradient of the fp32 path is summed in slices of at most 64 rows (longer sums lose accuracy).  The
-    slices' buffer is what a call with gradients asks for beyond one without and its dz and dy buffers."""
+    """Where operands of the fp32 path stay as they are, a small weight gradient is summed in slices of at most 64 rows (longer sums lose
+    accuracy).  The slices' buffer is what a call with gradients asks
+    for beyond one without and its dz and dy buffers."""
     d = ff = V = 64
     q = cdll.grpo_masked_actor_step_workspace_bytes
     q.restype = ctypes.c_size_t
