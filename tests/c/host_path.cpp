@@ -1,10 +1,13 @@
 // Runs the host side of the actor step, as built in libpcm.so, on a HIP runtime of its own that launches nothing: the
-// functions below take the place of the runtime's, so no GPU is needed or touched.  Every launch of a matrix product and of
-// a sum of parts is looked at as the library issues it: each matrix that it reads or writes has to lie inside one of the
-// buffers that the call was given, the workspace being as long as the library's own query says.
+// functions below take the place of the runtime's, so no GPU is needed or touched.  Every launch of a matrix product, of
+// a sum of parts and, on the fp32 path, of everything else is looked at as the library issues it: each matrix that it reads or
+// writes has to lie inside one of the buffers that the call was given, apart from what the launch writes; the workspace is as
+// long as the library's own query says, or as short as a call accepts.  A kernel that is neither known here nor listed as left
+// out is a failure.
 //
 //   host_path bounds   sweeps sizes and options and checks every launch
 //   host_path errors   lets each launch of a call fail in turn: the call has to return PCM_EHIP
+//   host_path least    the fp32 calls again, with the shortest workspace that they accept
 #include <cxxabi.h>
 
 #include <cstdio>
@@ -14,7 +17,10 @@
 #include <string>
 #include <vector>
 
+#include "actor_f32.h"
+#include "epilogues_f32.h"
 #include "gemm_bf16.h"
+#include "gemm_direct.h"
 #include "pcm.h"
 
 using namespace pcm;
@@ -42,10 +48,29 @@ T* buffer(const char* what, size_t count) {
     regions.push_back(Region{what, begin, begin + count * sizeof(T)});
     return reinterpret_cast<T*>(begin);
 }
+// What a launch touches: two matrices of which one is written, the epilogue's or the launch's result, may not share memory, unless they
+// are the same one (in place).
+struct Span {
+    const char* what;
+    uintptr_t begin, end;
+    bool written;
+};
+std::vector<Span> spans;
+bool writing = false;
+void check_overlaps(const char* kernel) {
+    for (size_t a = 0; a < spans.size(); ++a)
+        for (size_t b = 0; b < a; ++b) {
+            const Span &p = spans[a], &q = spans[b];
+            if (!(p.written || q.written) || p.begin == q.begin || p.end <= q.begin || q.end <= p.begin) continue;
+            if (++failures <= 20) printf("%s\n  %s: %s and %s share memory\n", call.c_str(), kernel, p.what, q.what);
+        }
+    spans.clear();
+}
 // `rows` rows of `columns` values, ld apart
 void touches(const char* kernel, const char* what, const void* p, int64_t rows, int64_t columns, int64_t ld, size_t size) {
     if (rows <= 0) return;
     const uintptr_t begin = (uintptr_t)p, end = begin + (uintptr_t)((rows - 1) * ld + columns) * size;
+    spans.push_back(Span{what, begin, end, writing});
     for (const Region& r : regions)
         if (begin >= r.begin && end <= r.end) return;
     if (++failures > 20) return;
@@ -94,7 +119,9 @@ void reads(const char* k, const GemmProblem& p) {
 template <int kLayA, int kLayB, class Epilogue>
 void look(const char* k, const GemmProblem& p, const Epilogue& e) {
     reads<kLayA, kLayB>(k, p);
+    writing = true;
     writes(k, p, e);
+    writing = false;
     ++products;
 }
 template <int kLayA, int kLayB, class Epilogue>
@@ -109,6 +136,156 @@ void look_at_pair(const char* k, const void* arg) {
         j.p.B = j.p.B2 = j.B[q];
         look<kLayA, kLayB>(k, j.p, j.epi[q]);
     }
+}
+
+void unknown(const std::string& what) {
+    if (++failures <= 20) printf("%s\n  a launch that this program does not know: %s\n", call.c_str(), what.c_str());
+}
+void require(bool ok, const char* kernel, const char* what) {
+    if (!ok && ++failures <= 20) printf("%s\n  %s: %s\n", call.c_str(), kernel, what);
+}
+
+// ---- fp32: operands in blocks of 128 rows x 32 columns, whole blocks; columns up to `columns` are used
+int64_t padded(int64_t n) { return (n + kThirdsUnit - 1) / kThirdsUnit * kThirdsUnit; }
+void touches_blocks(const char* k, const char* what, const void* p, int64_t rows, int64_t columns, int64_t ld, size_t size) {
+    require(columns <= ld && ld % kThirdsUnit == 0, k, "columns beyond the blocks");
+    touches(k, what, p, padded(rows), ld, ld, size);
+}
+void touches(const char* k, const char* what, const FloatBlocks& m, int64_t rows, int64_t columns) { touches_blocks(k, what, m.p, rows, columns, m.ld, 4); }
+void touches(const char* k, const char* what, const Thirds& m, int64_t rows, int64_t columns) { touches_blocks(k, what, m.p, rows, columns, m.ld, 6); }
+
+void writes(const char* k, const FloatsProblem& p, const EpiGateUp& e) {
+    if (e.uv != nullptr) touches(k, "u and v", e.uv, p.M, 2 * e.a.ld, 2 * e.a.ld, 4);
+    touches(k, "a", e.a, p.M, p.N / 2);
+    if (e.a3.p != nullptr) touches(k, "a as thirds", e.a3, p.M, p.N / 2);
+}
+void writes(const char* k, const FloatsProblem& p, const EpiOperand& e) {
+    touches(k, "result", e.C, p.M, p.N);
+    if (e.C3.p != nullptr) touches(k, "result as thirds", e.C3, p.M, p.N);
+}
+void writes(const char* k, const FloatsProblem& p, const EpiRows& e) { touches(k, "rows", e.C, p.M, p.N, e.ldc, 4); }
+template <class Epilogue>
+void look_at_floats(const char* k, void** args) {
+    const FloatsProblem& p = *static_cast<FloatsProblem*>(args[0]);
+    require(p.M % 64 == 0 && p.N % 64 == 0 && p.K % 32 == 0 && p.K > 0, k, "sizes that are no multiples of the tile");
+    touches(k, "A", FloatBlocks{const_cast<float*>(p.A), p.lda}, p.M, p.K);
+    touches(k, "B", FloatBlocks{const_cast<float*>(p.B), p.ldb}, p.N, p.K);
+    writing = true;
+    writes(k, p, *static_cast<Epilogue*>(args[1]));
+    writing = false;
+    ++products;
+}
+
+void writes(const char* k, const GemmProblem&, const EpiThirds& e) { touches(k, "thirds", e.C, e.rows, e.C.ld); }
+void writes(const char* k, const GemmProblem& p, const EpiFloats& e) {
+    for (int s = 0; s < p.splits; ++s) touches(k, "fp32 result", e.C + s * e.split_stride, e.M, e.N, e.ldc, 4);
+    require(e.M <= p.M && e.N <= p.N, k, "a result wider than the product");
+}
+void writes(const char* k, const GemmProblem& p, const EpiFloatsPair& e) {
+    for (int s = 0; s < p.splits; ++s)
+        for (float* C : e.C) touches(k, "one of two fp32 results", C + s * e.split_stride, e.M, e.N, e.N, 4);
+    require(e.M <= p.M && 2 * e.N <= p.N, k, "a result wider than the product");
+}
+void writes(const char* k, const GemmProblem& p, const EpiGateUpBackward& e) {
+    touches(k, "u and v", e.uv, p.M, e.duv.ld, e.duv.ld, 4);
+    touches(k, "du and dv", e.duv, p.M, e.duv.ld);
+    require(e.duv.ld <= 2 * (int64_t)p.N, k, "du and dv wider than the product");
+}
+template <int kLayA, int kLayB, class Epilogue>
+void look_at_thirds(const char* k, const void* arg) {
+    const auto& j = *static_cast<const ThirdsProduct<kLayA, kLayB, Epilogue>*>(arg);
+    GemmProblem p = j.p;
+    require(p.M % kThirdsUnit == 0 && p.N % kThirdsUnit == 0 && p.K1 % kTileK == 0 && p.K1 > 0, k, "sizes that are no multiples of the tile");
+    require(p.splits >= 1 && p.splits <= 64 && j.first % 8 == 0, k, "parts");
+    const Thirds A{const_cast<bf16*>(p.A), p.lda}, B{const_cast<bf16*>(p.B), p.ldb};
+    touches(k, "A", A, kLayA == kRowsByK ? p.M : p.K1, kLayA == kRowsByK ? p.K1 : p.M);
+    touches(k, "B", B, kLayB == kRowsByK ? p.N : p.K1, kLayB == kRowsByK ? p.K1 : p.N);
+    writing = true;
+    writes(k, p, j.epi);
+    writing = false;
+    ++products;
+}
+
+// ---- fp32, direct route
+template <int kLayA, int kLayB>
+void reads_direct(const char* k, const F32Problem& p, int second) {
+    const float* const operand[2][2] = {{p.A, p.A2}, {p.B, p.B2}};
+    for (int q = 0; q < (second == kNone ? 1 : 2); ++q) {
+        const float* const A = operand[0][second == kSum ? q : 0];
+        if (kLayA == kRowsByK) touches(k, "A", A, p.M, p.K, p.lda, 4);
+        else touches(k, "A", A, p.K, p.M, p.lda, 4);
+        if (kLayB == kRowsByK) touches(k, "B", operand[1][q], p.N, p.K, p.ldb, 4);
+        else touches(k, "B", operand[1][q], p.K, p.N, p.ldb, 4);
+    }
+}
+void writes(const char* k, const F32Problem& p, int second, int slices, const F32Store& e) {
+    for (int z = 0; z < slices; ++z)
+        for (float* C : {e.C, second == kPair ? e.C2 : e.C}) touches(k, "result", C + z * e.split_stride, p.M, p.N, e.ldc, 4);
+}
+void writes(const char* k, const F32Problem& p, int, int, const F32SwigluForward& e) {
+    for (float* C : {e.u, e.v, e.a}) touches(k, "u, v or a", C, p.M, p.N, p.N, 4);
+}
+void writes(const char* k, const F32Problem& p, int, int, const F32SwigluBackward& e) {
+    for (float* C : {e.u, e.v}) touches(k, "u or v", C, p.M, p.N, p.N, 4);
+}
+template <class Epilogue>
+void look_at_direct(const char* k, int lay_a, int lay_b, int second, int slices, void** args) {
+    const F32Problem& p = *static_cast<F32Problem*>(args[0]);
+    if (lay_a == kRowsByK && lay_b == kRowsByK) reads_direct<kRowsByK, kRowsByK>(k, p, second);
+    else if (lay_a == kRowsByK) reads_direct<kRowsByK, kKByRows>(k, p, second);
+    else reads_direct<kKByRows, kKByRows>(k, p, second);
+    require((int64_t)slices * p.k_per_split >= p.K || second == kSum, k, "slices that leave out some of the reduction");
+    writing = true;
+    writes(k, p, second, slices, *static_cast<Epilogue*>(args[1]));
+    writing = false;
+    ++products;
+}
+
+// ---- fp32, the other launches
+template <class Vec>
+void reads(const char* k, const GatherArgs<Vec>& g) {
+    const int64_t all = (int64_t)g.T * g.N * g.A;
+    touches(k, "hidden", g.hidden, all, g.vec_per_row, g.vec_per_row, sizeof(Vec));
+    touches(k, "tokens", g.tokens, 1, all, all, 1);
+    touches(k, "logp_old", g.logp_old, 1, all, all, 4);
+    touches(k, "adv", g.adv, 1, g.T, g.T, 4);
+    touches(k, "row tokens", g.meta.token, 1, g.rows_pad, g.rows_pad, 1);
+    for (const float* q : {g.meta.logp_old, g.meta.adv}) touches(k, "row metadata", q, 1, g.rows_pad, g.rows_pad, 4);
+}
+void look_at_prepare(const char* k, const PrepareF32& p) {
+    const GatherArgs<float>& g = p.gather;
+    const int64_t d = g.vec_per_row;
+    reads(k, g);
+    require(g.rows_pad % 256 == 0 && p.X.ld == padded(d), k, "X");
+    writing = true;
+    touches(k, "X", p.X, g.rows_pad, p.X.ld);
+    if (p.X3.p != nullptr) touches(k, "X as thirds", p.X3, g.rows_pad, p.X.ld);
+    if (p.dX != nullptr) touches(k, "dX", p.dX, (int64_t)g.max_chunks * g.A, d, d, 4);
+    for (int q = 0; q < p.weights.n; ++q) {
+        const WeightJob& j = p.weights.job[q];
+        writing = false;
+        touches(k, "a weight", j.src, j.R, j.C, j.C, 4);
+        writing = true;
+        const int64_t columns = padded(j.C) * (j.mode == kPackNone ? 1 : 2), rows = padded(j.R);
+        if (j.transposed) touches(k, "a weight as floats", j.to, columns, rows);
+        else if (j.to.p != nullptr) touches(k, "a weight as floats", j.to, rows, columns);
+        else touches(k, "a weight as thirds", j.to3, rows, columns);
+    }
+    writing = false;
+}
+void look_at_loss(const char* k, const LossArgs& p) {
+    writing = true;
+    touches(k, "z", p.z, p.rows, p.ld, p.ld, 4);
+    if (p.opt.chunk_ratio && (p.dz.p != nullptr || p.in_place)) {
+        const int64_t live = (int64_t)p.max_chunks * p.A;
+        touches(k, "extra", p.extra, p.rows < live ? p.rows : live, p.V, p.V, 4);
+    }
+    if (p.dz.p != nullptr) touches(k, "dz", p.dz, p.rows, p.ld);
+    touches(k, "row tokens", p.meta.token, 1, p.rows, p.rows, 1);
+    for (const float* q : {p.meta.logp_old, p.meta.adv, p.out.dlogp, p.out.entropy, p.out.term, p.out.ratio})
+        touches(k, "a value per row", q, 1, p.rows, p.rows, 4);
+    touches(k, "clip flags", p.out.clipped, 1, p.rows, p.rows, 1);
+    writing = false;
 }
 
 // The parts of a template argument list "A<..>, B, ..": split at the commas of the outermost level.
@@ -151,17 +328,49 @@ const std::map<std::string, Look>& known_jobs() {
         add_jobs<EpiSwigluBackward<false>>(jobs, "pcm::EpiSwigluBackward<false>");
         add_jobs<EpiSwigluBackward<true>>(jobs, "pcm::EpiSwigluBackward<true>");
         jobs["pcm::GemmPairJob<1,1,pcm::EpiStoreF32>"] = look_at_pair<1, 1, EpiStoreF32>;
+        jobs["pcm::ThirdsProduct<0,0,pcm::EpiThirds>"] = look_at_thirds<0, 0, EpiThirds>;
+        jobs["pcm::ThirdsProduct<0,0,pcm::EpiFloats>"] = look_at_thirds<0, 0, EpiFloats>;
+        jobs["pcm::ThirdsProduct<1,1,pcm::EpiFloats>"] = look_at_thirds<1, 1, EpiFloats>;
+        jobs["pcm::ThirdsProduct<1,1,pcm::EpiFloatsPair>"] = look_at_thirds<1, 1, EpiFloatsPair>;
+        jobs["pcm::ThirdsProduct<0,0,pcm::EpiGateUpBackward>"] = look_at_thirds<0, 0, EpiGateUpBackward>;
+        jobs["pcm::ThirdsProduct<0,1,pcm::EpiGateUpBackward>"] = look_at_thirds<0, 1, EpiGateUpBackward>;
     }
     return jobs;
-}
-void unknown(const std::string& what) {
-    if (++failures <= 20) printf("%s\n  a launch that this program does not know: %s\n", call.c_str(), what.c_str());
 }
 // A product by itself has the arguments (GemmProblem, epilogue); a job holds the two side by side.
 void look_at_product(const char* k, const std::string& layouts_and_epilogue, void** args);
 
-void look_at_launch(const std::string& name, void** args) {
-    size_t at = name.find("gemm_group<");
+void look_at_launch(const std::string& name, void** args, dim3 grid) {
+    size_t at = name.find("gemm_f32<");
+    if (at != std::string::npos) {
+        const auto parts = arguments(name, at + strlen("gemm_f32<") - 1);
+        for (size_t q = 0; q < parts.size(); ++q) {
+            const auto job = known_jobs().find(parts[q]);
+            if (job == known_jobs().end()) unknown(parts[q]);
+            else job->second(parts[q].c_str(), args[q]);
+        }
+        return;
+    }
+    at = name.find("gemm_floats<");
+    if (at != std::string::npos) {
+        const std::string epilogue = arguments(name, at + strlen("gemm_floats<") - 1)[2];
+        if (epilogue == "pcm::EpiGateUp") look_at_floats<EpiGateUp>("gemm_floats, gate and up", args);
+        else if (epilogue == "pcm::EpiOperand") look_at_floats<EpiOperand>("gemm_floats to an operand", args);
+        else if (epilogue == "pcm::EpiRows") look_at_floats<EpiRows>("gemm_floats to rows", args);
+        else unknown(name);
+        return;
+    }
+    at = name.find("gemm_direct<");
+    if (at != std::string::npos) {                      // tile, tile, layout, layout, second product, vectors, epilogue
+        const auto parts = arguments(name, at + strlen("gemm_direct<") - 1);
+        const int lay_a = atoi(parts[2].c_str()), lay_b = atoi(parts[3].c_str()), second = atoi(parts[4].c_str()), slices = (int)grid.z;
+        if (parts[6] == "pcm::F32Store") look_at_direct<F32Store>("gemm_direct", lay_a, lay_b, second, slices, args);
+        else if (parts[6] == "pcm::F32SwigluForward") look_at_direct<F32SwigluForward>("gemm_direct, gate and up", lay_a, lay_b, second, slices, args);
+        else if (parts[6] == "pcm::F32SwigluBackward") look_at_direct<F32SwigluBackward>("gemm_direct, da", lay_a, lay_b, second, slices, args);
+        else unknown(name);
+        return;
+    }
+    at = name.find("gemm_group<");
     if (at != std::string::npos) {
         const auto parts = arguments(name, at + strlen("gemm_group<") - 1);
         for (size_t q = 2; q < parts.size(); ++q) {
@@ -183,16 +392,67 @@ void look_at_launch(const std::string& name, void** args) {
         touches("sum_parts_bf16", "parts", *static_cast<void**>(args[0]), n_parts, (int64_t)n, (int64_t)n, 4);
         touches("sum_parts_bf16", "result", *static_cast<void**>(args[3]), 1, (int64_t)n, (int64_t)n, 2);
         ++sums;
+        return;
+    }
+    const auto is = [&](const char* kernel) { return name.find(std::string("::") + kernel + "(") != std::string::npos; };
+    if (is("sum_parts_thirds")) {
+        const int n_parts = *static_cast<int*>(args[1]);
+        const int64_t n = (int64_t)*static_cast<size_t*>(args[2]);
+        const Thirds C = *static_cast<Thirds*>(args[3]);
+        touches("sum_parts_thirds", "parts", *static_cast<void**>(args[0]), n_parts, n, n, 4);
+        require(n % C.ld == 0, "sum_parts_thirds", "rows in part");
+        writing = true;
+        touches("sum_parts_thirds", "result", C, n / C.ld, C.ld);
+        writing = false;
+        ++sums;
+        return;
+    }
+    if (is("prepare_step_f32")) return look_at_prepare("prepare_step_f32", *static_cast<PrepareF32*>(args[0]));
+    if (name.find("::loss_rows<") != std::string::npos) return look_at_loss("loss_rows", *static_cast<LossArgs*>(args[0]));
+    if (is("scale_rows")) {                             // z, extra or null, V, coef, n_kept, max_chunks, A, dz
+        const int64_t V = *static_cast<int*>(args[2]), rows = (int64_t)*static_cast<int*>(args[5]) * *static_cast<int*>(args[6]);
+        const Thirds dz = *static_cast<Thirds*>(args[7]);
+        touches("scale_rows", "z", *static_cast<float**>(args[0]), rows, dz.ld, dz.ld, 4);
+        if (float* const extra = *static_cast<float**>(args[1])) touches("scale_rows", "extra", extra, rows, V, V, 4);
+        touches("scale_rows", "coefficients", *static_cast<float**>(args[3]), 1, rows, rows, 4);
+        writing = true;
+        touches("scale_rows", "dz", dz, (rows + 255) / 256 * 256, dz.ld);
+        writing = false;
+        return;
+    }
+    if (is("scale_rows_f32")) {                         // dz, extra or null, coef, n_kept, max_chunks, A, rows, V
+        const int64_t rows = *static_cast<int64_t*>(args[6]), V = *static_cast<int*>(args[7]);
+        touches("scale_rows_f32", "dz", *static_cast<float**>(args[0]), rows, V, V, 4);
+        if (float* const extra = *static_cast<float**>(args[1])) touches("scale_rows_f32", "extra", extra, rows, V, V, 4);
+        touches("scale_rows_f32", "coefficients", *static_cast<float**>(args[2]), 1, rows, rows, 4);
+        return;
+    }
+    at = name.find("prepare_step<");
+    if (at != std::string::npos) {
+        const std::string vec = arguments(name, at + strlen("prepare_step<") - 1)[0];
+        if (vec != "unsignedint") return;               // fp32, unaligned
+        const auto& g = *static_cast<GatherArgs<uint32_t>*>(args[0]);
+        reads("prepare_step", g);
+        touches("prepare_step", "X", g.X, g.rows_pad, g.vec_per_row, g.vec_per_row, 4);
+        return;
     }
     if (name.find("finish_step") != std::string::npos) {
         const PartsSums& s = *static_cast<PartsSums*>(args[0]);
         for (int q = 0; q < s.n; ++q) {
             touches("finish_step", "parts", s.job[q].parts, s.job[q].n_parts, (int64_t)s.job[q].n, (int64_t)s.job[q].stride, 4);
+            writing = true;
             touches("finish_step", "result", s.job[q].out, 1, (int64_t)s.job[q].n, (int64_t)s.job[q].n, 4);
+            writing = false;
             if (s.job[q].sumsq) touches("finish_step", "squares", s.job[q].sumsq, 1, s.job[q].blocks, s.job[q].blocks, 8);
             ++sums;
         }
+        return;
     }
+    // left out: a value or two per row, and the bf16 path's copies of rows and weights
+    for (const char* kernel : {"finish_loss", "chunk_ratio_rows", "list_live_rows", "loss_rows_bf16", "scale_rows_bf16", "transpose_weights",
+                               "sum_of_squares"})
+        if (name.find(kernel) != std::string::npos) return;
+    unknown(name);
 }
 template <class Epilogue, int kLayA, int kLayB>
 void look_at_args(const char* k, void** args) {
@@ -247,7 +507,9 @@ hipError_t hipLaunchKernel(const void* stub, dim3 grid, dim3 block, void** args,
     if (fails) return last_error = hipErrorLaunchFailure;
     if (check_bounds) {
         if (grid.x == 0 || grid.y == 0 || grid.z == 0 || block.x * block.y * block.z > 1024) unknown("an empty or too large grid");
-        look_at_launch(kernel_names()[stub], args);
+        spans.clear();
+        look_at_launch(kernel_names()[stub], args, grid);
+        check_overlaps(kernel_names()[stub].substr(0, 200).c_str());
     }
     return hipSuccess;
 }
@@ -272,7 +534,8 @@ struct Step {
     float entropy;
     int panel_rows;
 };
-int run(const Step& c) {
+size_t query = 0;                                 // what the last call's query said
+int run(const Step& c, size_t workspace_bytes = 0) {
     char text[256];
     snprintf(text, sizeof text, "dtype %d, %d chunks of %d rows, %d -> %d -> %d, weights %d dX %d composed %d chunk ratio %d squares %d "
              "packed %d dense %d entropy %g panels %d", c.dtype, c.chunks, c.A, c.d, c.ff, c.V, c.weights, c.dX, c.composed, c.chunk_ratio,
@@ -305,8 +568,10 @@ int run(const Step& c) {
         for (int q = 0; q < 4; ++q) dW[q] = buffer<float>("a weight gradient", n[q]);
     }
     char* const dX = c.dX ? buffer<char>("dX", rows * d * size) : nullptr;
-    const size_t bytes = grpo_masked_actor_step_ex_workspace_bytes(c.chunks, c.A, c.d, c.ff, c.V, c.dtype, c.weights || c.dX, &o);
+    size_t bytes = grpo_masked_actor_step_ex_workspace_bytes(c.chunks, c.A, c.d, c.ff, c.V, c.dtype, c.weights || c.dX, &o);
     if (bytes == 0) { unknown("the workspace query refuses the shape"); return PCM_EINVAL; }
+    query = bytes;
+    if (workspace_bytes != 0) bytes = workspace_bytes;
     char* const ws = buffer<char>("the workspace", bytes);
     launches = 0;
     last_error = hipSuccess;
@@ -336,6 +601,21 @@ void bf16_calls(int chunks, int A, int d, int ff, int panel_rows, F f) {
                 f(c);
             }
 }
+// f over the fp32 calls
+template <class F>
+void f32_calls(F f) {
+    auto calls = [&](int chunks, int A, int d, int ff, int V) {
+        for (int q = 0; q < 16; ++q)
+            f(Step{PCM_F32, chunks, A, d, ff, V, (q & 1) != 0, (q & 2) != 0, (q & 4) != 0, (q & 8) != 0, false, false, false, q % 3 == 0 ? 1e-3f : 0.f, 0});
+    };
+    for (int d : {1, 33, 64, 65, 128, 129, 256, 1024})
+        for (int ff : {1, 64, 65, 127, 300, 2816})
+            for (int V : {1, 17, 256, 1024})
+                for (int chunks : {1, 9, 46, 500}) calls(chunks, 56, d, ff, V);
+    for (int chunks : {1, 2, 64, 65, 256, 257, 300}) calls(chunks, 1, 4096, 11008, 256);     // few rows under a wide head
+    calls(20000, 56, 64, 64, 256);                                                           // and many under a narrow one
+    calls(20000, 56, 65, 64, 64);
+}
 void bounds() {
     check_bounds = true;
     const int heads[][2] = {{256, 256}, {512, 768}, {256, 5120}, {3072, 768}, {768, 2304}, {1024, 11008}, {4096, 11008}, {8192, 28672},
@@ -347,16 +627,27 @@ void bounds() {
                 bf16_calls(r[0], r[1], h[0], h[1], panel, [&](const Step& c) { expect(run(c), PCM_OK); });
     for (const auto& h : heads)                   // rows beyond the tiles of the widest of those heads
         bf16_calls(1 << 20, 16, h[0], h[1], 0, [&](const Step& c) { expect(run(c), PCM_OK); });
-    for (int d : {1, 33, 64, 256, 1024})
-        for (int ff : {1, 65, 300, 2816})
-            for (int V : {1, 17, 256, 1024})
-                for (int chunks : {1, 9, 46, 500})
-                    for (int q = 0; q < 16; ++q) {
-                        const Step c{PCM_F32, chunks, 56, d, ff, V, (q & 1) != 0, (q & 2) != 0, (q & 4) != 0, (q & 8) != 0, false, false, false,
-                                     q % 3 == 0 ? 1e-3f : 0.f, 0};
-                        expect(run(c), PCM_OK);
-                    }
+    f32_calls([](const Step& c) { expect(run(c), PCM_OK); });
     if (products < 10000 || sums < 1000) unknown("too few launches were looked at");
+}
+// The shortest workspace that a call accepts is that of the direct route: whatever the query says, it is enough for every option of the
+// shape, and nothing reaches beyond it.
+void least() {
+    check_bounds = true;
+    f32_calls([](const Step& c) {
+        check_bounds = false;
+        Step plain = c;
+        plain.composed = plain.chunk_ratio = false;
+        expect(run(plain), PCM_OK);
+        size_t enough = query, little = 0;
+        while (enough - little > 1) {
+            const size_t middle = little + (enough - little) / 2;
+            (run(plain, middle) == PCM_OK ? enough : little) = middle;
+        }
+        check_bounds = true;
+        expect(run(c, enough), PCM_OK);
+        expect(run(c, enough - 1), PCM_EWORKSPACE);
+    });
 }
 void errors() {
     auto each_launch = [&](const Step& c) {
@@ -381,6 +672,7 @@ int main(int argc, char** argv) {
     if (argc != 2) return 2;
     if (!strcmp(argv[1], "bounds")) bounds();
     else if (!strcmp(argv[1], "errors")) errors();
+    else if (!strcmp(argv[1], "least")) least();
     else return 2;
     printf("%d products, %d sums, %d failures\n", products, sums, failures);
     return failures != 0;

@@ -37,3 +37,8 @@ def test_every_product_stays_inside_the_buffers_of_the_call(host_path):
 def test_a_launch_that_fails_is_reported(host_path):
     """Each launch of a call fails in turn, in the stub runtime: the call returns PCM_EHIP, whichever launch it was."""
     _run(host_path, "errors")
+
+
+def test_fp32_calls_accept_the_workspace_of_the_direct_route(host_path):
+    """An fp32 call takes the least workspace that any call of its shape takes, whatever its options: nothing reaches beyond it."""
+    _run(host_path, "least")
