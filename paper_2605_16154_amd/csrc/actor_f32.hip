@@ -4,15 +4,16 @@
 // log-probabilities have the bits of the definition's order of additions whatever the tile.
 //
 // Backward: products on the bf16 matrix cores.  Every operand is held as three bf16 matrices whose sum it is exactly (thirds.h),
-// and a product of two is six products of such parts (gemm_thirds.h; the three left out are below 2^-23 of the whole).  The
-// matrix cores add up 32 products at a time in fp32, so a sum has a thirty-second of the roundings that one by fp32
-// multiply-adds has, and they do 16 times the multiply-adds of the fp32 ones: six products take 3/8 of the time at the same share
-// of their rates.
+// and a product of two is six products of such parts (gemm_thirds.h; the three left out come to less than 2^-24 of the whole, the
+// rounding of one fp32 operation).  The matrix cores round a sum a few times per 32 products, where multiply-adds in fp32 do so 32
+// times, and sums over many rows are in chains that are added up.  They do 16 times the multiply-adds of the fp32 ones: six
+// products take 3/8 of the time at the same share of their rates.
 // Measured against fp32 matrix instructions throughout, steps: 10,752 rows of 1024 -> 2816 -> 1024 -> 256, a quarter of them not kept,
-// 3.74 -> 2.54 ms; 5376 of 256 -> 1024 -> 256 -> 256 362 -> 262 to 287 us, by the box; 360 of 473 -> 333 -> 473 -> 512 185 -> 124, 1440 of 619 -> 1302 -> 619 ->
-// 256 413 -> 201, 8960 of 103 -> 149 -> 103 -> 256, composed, where most of the padded tiles is padding, 171 -> 149; faster at 16 of 16
-// sizes, 1.15 to 2.06 times.  Loss, log-probabilities and statistics have the same bits; errors of the gradients against 64 bits,
-// root mean square over six inputs each: dX 4.85e-6 -> 4.74e-6 and 2.78e-6 -> 2.71e-6 at the first two, no larger at any of ten sizes.
+// 3.74 -> 2.54 ms; 5376 of 256 -> 1024 -> 256 -> 256 362 -> 262 to 287 us, by the box; 360 of 473 -> 333 -> 473 -> 512 185 -> 124, 1440
+// of 619 -> 1302 -> 619 -> 256 413 -> 201, 8960 of 103 -> 149 -> 103 -> 256, composed, where most of the padded tiles is padding,
+// 171 -> 149; faster at 16 of 16 sizes, 1.15 to 2.06 times.  Loss, log-probabilities and statistics have the same bits; errors of the
+// gradients against 64 bits, root mean square over six inputs each: dX 4.85e-6 -> 4.74e-6 and 2.78e-6 -> 2.71e-6 at the first two, no
+// larger at any of ten sizes; with sums of one sign dWg 1.24e-7 -> 1.02e-7 at the second, no larger for any gradient of 14 sizes.
 // (The forward products as thirds too: 2.08 ms and 232 us, and a third of the error; but the loss may be a sum of terms of both
 // signs that nearly cancel, and any other rounding of the logits moves it by more than a part in 10^4 then.)
 //
@@ -471,11 +472,12 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, size_t ws_b
             launch_products(s, job<kRowsByK, kKByRows>(product(w.dz, w.WdoT3, Mp, ffp, V, kRowsAreM), swiglu));   // da = dz (Wd Wo)^T
             if (grads) {
                 const size_t n = (size_t)ffp * Vp;                                                     // G = a^T dz
-                launch_products(s, job<kKByRows, kKByRows>(product(w.a3, w.dz, ffp, Vp, Mp, kRowsAreK, plan.G), EpiFloats{w.parts_G, Vp, (int64_t)n, ffp, Vp}));
+                launch_products(s, job<kKByRows, kKByRows>(product(w.a3, w.dz, ffp, Vp, Mp, kRowsAreK, plan.G), EpiFloatsInChains{{w.parts_G, Vp, (int64_t)n, ffp, Vp}}));
                 sum_parts_thirds<<<(unsigned)std::min<size_t>((n / 4 + kThreads - 1) / kThreads, 2048), kThreads, 0, s>>>(w.parts_G, plan.G, n, w.G);
-                const auto dWd = job<kRowsByK, kRowsByK>(product(w.G, w.Wo, ff, d, V, kRowsUnused), EpiFloats{io.dWd, d, 0, ff, d});   // G Wo^T
+                const auto dWd = job<kRowsByK, kRowsByK>(product(w.G, w.Wo, ff, d, V, kRowsUnused), EpiFloatsInChains{{io.dWd, d, 0, ff, d}});   // G Wo^T
                 const int o = plan.dWo;
-                const auto dWo = job<kKByRows, kKByRows>(product(w.Wd, w.G, d, V, ff, kRowsUnused, o), floats(o, w.parts_o, io.dWo, d, V));   // Wd^T G
+                const auto dWo = job<kKByRows, kKByRows>(product(w.Wd, w.G, d, V, ff, kRowsUnused, o),                                     // Wd^T G
+                                                         EpiFloatsInChains{floats(o, w.parts_o, io.dWo, d, V)});
                 launch_products(s, dWo, dWd);
             }
         } else {

@@ -23,6 +23,16 @@ constexpr int kThirdsSlots = 3, kThirdsLoads = 12;                    // steps i
 using ThirdsRing = OperandRing<kSmallTile, kDeepRingSlots>;
 static_assert(kThirdsSlots * kThirdsSlot == sizeof(ThirdsRing), "three steps");
 
+// The compiler does not know how long an MFMA in inline assembly takes to write its results: whatever reads these accumulators
+// afterwards goes through the assembly here and comes behind the wait.
+__device__ __forceinline__ void wait_mfma_results(Accumulators<kSmallTile>& acc) {
+    static_assert(kSmallTile == 4);
+    asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[0][0]), "+a"(acc[0][1]), "+a"(acc[0][2]), "+a"(acc[0][3]), "+a"(acc[1][0]), "+a"(acc[1][1]),
+                 "+a"(acc[1][2]), "+a"(acc[1][3]));
+    asm volatile("" : "+a"(acc[2][0]), "+a"(acc[2][1]), "+a"(acc[2][2]), "+a"(acc[2][3]), "+a"(acc[3][0]), "+a"(acc[3][1]), "+a"(acc[3][2]),
+                 "+a"(acc[3][3]));
+}
+
 template <int kLayA, int kLayB, class Epilogue>
 __device__ __forceinline__ void thirds_tile(const GemmProblem& p, const Epilogue& epi, int block, ThirdsRing& smem) {
     constexpr int kW = kSmallTile, T = kTile<kW>;
@@ -91,12 +101,14 @@ __device__ __forceinline__ void thirds_tile(const GemmProblem& p, const Epilogue
     const uint32_t base_a = fragment_base(kLayA, wm * 64), base_b = fragment_base(kLayB, wn * 64) + 3 * kPartBytes;
 
     // Sums of the products of first parts, and of the five small ones: the matrix cores cut off what they add, and of what is
-    // 2^-8 of the whole that does not count.
-    Accumulators<kW> high, low;
+    // 2^-8 of the whole that does not count.  With kChainSteps the first are one chain of additions over that many steps (an even
+    // number), and the chains are added up: over the rows of a batch a single chain rounds more often than the parts of a sum on the
+    // fp32 matrix instructions do.  (A flush per chain in a loop around the steps: as a branch among them it costs 2.6 % of a step.)
+    Accumulators<kW> high, low, whole;
 #pragma unroll
     for (int i = 0; i < kW; ++i)
 #pragma unroll
-        for (int j = 0; j < kW; ++j) high[i][j] = low[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < kW; ++j) high[i][j] = low[i][j] = whole[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     if (step_begin < step_end) {
         const int last = step_end - 1;
@@ -176,20 +188,36 @@ __device__ __forceinline__ void thirds_tile(const GemmProblem& p, const Epilogue
             next = far;
             far = was;
         };
-        for (int s = step_begin; s < step_end; s += 2) {
-            step(Index<0>{}, s);
-            if (s + 1 >= step_end) break;
-            step(Index<1>{}, s + 1);
+        for (int s = step_begin;;) {
+            const int chain_end = Epilogue::kChainSteps > 0 ? min(step_end, s + Epilogue::kChainSteps) : step_end;
+            for (; s < chain_end; s += 2) {
+                step(Index<0>{}, s);
+                if (s + 1 >= step_end) continue;
+                step(Index<1>{}, s + 1);
+            }
+            if (Epilogue::kChainSteps == 0 || s >= step_end) break;
+            wait_mfma_results(high);
+#pragma unroll
+            for (int i = 0; i < kW; ++i)
+#pragma unroll
+                for (int j = 0; j < kW; ++j) {
+                    whole[i][j] += high[i][j];
+                    high[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    asm volatile("s_nop 1" : "+a"(high[i][j]));             // an MFMA may follow
+                }
         }
         wait_direct_loads<0>();
-        // the last MFMAs' results: the compiler does not know how long inline assembly takes to write them
-        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+        wait_mfma_results(high);
+        wait_mfma_results(low);
         __syncthreads();
     }
 #pragma unroll
     for (int i = 0; i < kW; ++i)
 #pragma unroll
-        for (int j = 0; j < kW; ++j) high[i][j] += low[i][j];
+        for (int j = 0; j < kW; ++j) {
+            if (Epilogue::kChainSteps > 0) high[i][j] += whole[i][j];
+            high[i][j] += low[i][j];
+        }
     const TileCoord<kW> tc{m0, n0, wm, wn, lane, split};
     epi(tc, high, reinterpret_cast<char*>(smem.data));
 }

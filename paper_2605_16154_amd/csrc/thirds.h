@@ -37,23 +37,27 @@ struct FloatBlocks {
     }
 };
 
-// x as the sum of three bf16 values, exactly (but for what lies below the smallest bf16 value): the leading eight bits of the
-// significand by truncation, which cannot overflow, and twice the bf16 value nearest to the rest, the second of which leaves
-// none.  out[t]: the t-th parts of kN values, two to a word.
+// x as the sum of three bf16 values, exactly (but for what lies below the smallest bf16 value): the bf16 value nearest to x (or the
+// largest finite one), and twice the one nearest to the rest, the second of which leaves none.  The second and third part are at
+// most 2^-8 and 2^-17 of x, so the three products of parts that a product of two leaves out (second by third, third by second, third by
+// third) come to less than 2^-24 of it, the rounding of one fp32 operation.  (With the first part cut off instead of rounded 2^-22.)
+// out[t]: the t-th parts of kN values, two to a word.
 template <int kN>
 __device__ __forceinline__ void split_in_three(const float (&x)[kN], uint32_t (&out)[3][kN / 2]) {
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    const float largest = __builtin_bit_cast(float, 0x7F7F0000u);
 #pragma unroll
     for (int q = 0; q < kN / 2; ++q) {
-        const uint32_t x0 = __builtin_bit_cast(uint32_t, x[2 * q]), x1 = __builtin_bit_cast(uint32_t, x[2 * q + 1]);
-        out[0][q] = __builtin_amdgcn_perm(x1, x0, 0x07060302);          // the upper halves
-        float r0 = x[2 * q] - __builtin_bit_cast(float, x0 & 0xFFFF0000u), r1 = x[2 * q + 1] - __builtin_bit_cast(float, x1 & 0xFFFF0000u);
-        const bf16x2 middle = {(__bf16)r0, (__bf16)r1};
-        out[1][q] = __builtin_bit_cast(uint32_t, middle);
-        r0 -= __builtin_bit_cast(float, out[1][q] << 16);
-        r1 -= __builtin_bit_cast(float, out[1][q] & 0xFFFF0000u);
-        const bf16x2 low = {(__bf16)r0, (__bf16)r1};
-        out[2][q] = __builtin_bit_cast(uint32_t, low);
+        float r[2] = {x[2 * q], x[2 * q + 1]};
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const float r0 = t == 0 ? __builtin_amdgcn_fmed3f(r[0], -largest, largest) : r[0];
+            const float r1 = t == 0 ? __builtin_amdgcn_fmed3f(r[1], -largest, largest) : r[1];
+            const bf16x2 part = {(__bf16)r0, (__bf16)r1};
+            out[t][q] = __builtin_bit_cast(uint32_t, part);
+            r[0] -= __builtin_bit_cast(float, out[t][q] << 16);
+            r[1] -= __builtin_bit_cast(float, out[t][q] & 0xFFFF0000u);
+        }
     }
 }
 

@@ -331,6 +331,8 @@ const std::map<std::string, Look>& known_jobs() {
         jobs["pcm::ThirdsProduct<0,0,pcm::EpiThirds>"] = look_at_thirds<0, 0, EpiThirds>;
         jobs["pcm::ThirdsProduct<0,0,pcm::EpiFloats>"] = look_at_thirds<0, 0, EpiFloats>;
         jobs["pcm::ThirdsProduct<1,1,pcm::EpiFloats>"] = look_at_thirds<1, 1, EpiFloats>;
+        jobs["pcm::ThirdsProduct<0,0,pcm::EpiFloatsInChains>"] = look_at_thirds<0, 0, EpiFloatsInChains>;
+        jobs["pcm::ThirdsProduct<1,1,pcm::EpiFloatsInChains>"] = look_at_thirds<1, 1, EpiFloatsInChains>;
         jobs["pcm::ThirdsProduct<1,1,pcm::EpiFloatsPair>"] = look_at_thirds<1, 1, EpiFloatsPair>;
         jobs["pcm::ThirdsProduct<0,0,pcm::EpiGateUpBackward>"] = look_at_thirds<0, 0, EpiGateUpBackward>;
         jobs["pcm::ThirdsProduct<0,1,pcm::EpiGateUpBackward>"] = look_at_thirds<0, 1, EpiGateUpBackward>;

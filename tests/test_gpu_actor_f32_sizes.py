@@ -1,11 +1,11 @@
 """The fp32 actor step where its operands in blocks and as three bf16 matrices can go wrong: sizes at the edges of the padding and of the
-tiles, the lines between its two routes, magnitudes at the ends of the fp32 range and values that are no numbers."""
+tiles, the lines between its two routes, magnitudes at the ends of the fp32 range, values that are no numbers, and sums of one sign."""
 import numpy as np
 import pytest
 import torch
 
 from paper_2605_16154_amd import binding
-from test_gpu_actor import CONFIGS, check, condition_logp_old, make_problem, pcm, run_both  # noqa: F401
+from test_gpu_actor import CONFIGS, GRADS, check, condition_logp_old, make_problem, pcm, run_both  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-5     # the accuracy that the fp32 path states
@@ -135,3 +135,45 @@ def test_f32_least_workspace(pcm, monkeypatch, grads, least, composed):   # noqa
     ws = torch.empty(least - 256, dtype=torch.uint8, device="cuda")
     with pytest.raises(binding.PcmError, match="workspace"):
         run_both(pcm, pr, **kw)
+
+
+def one_sign_problem(d, ff, V, A, n_kept, seed):
+    """Weight gradients whose terms nearly all have one sign."""
+    rng = np.random.default_rng(seed)
+    f32 = lambda x: x.astype(np.float32).astype(np.float64)
+    cfg = CONFIGS["cfg1"].with_(n_groups=1, G=4, N=n_kept, K=2, B=4, d=d, ff=ff, V=V, L=1, D=A, seed=seed)
+    rows = cfg.T * cfg.N * A
+    positive = lambda n, m, scale: f32((np.abs(rng.normal(size=(n, m))) + 0.5) * scale)
+    hidden = positive(rows, d, 1.0)
+    W = dict(Wg=positive(d, ff, 1.0 / d), Wu=positive(d, ff, 1.0 / d), Wd=positive(ff, d, 1.0 / ff), Wo=f32(rng.normal(size=(d, V)) * 0.2 / np.sqrt(d)))
+    W["Wo"][:, 0] = f32(np.abs(rng.normal(size=d)) / d + 2.0 / d)             # every token is bin 0, whose logit every row raises
+    x = hidden[:n_kept * A]
+    u, v = x @ W["Wg"], x @ W["Wu"]
+    z = (u / (1 + np.exp(-u)) * v) @ W["Wd"] @ W["Wo"]
+    logp_old = np.full(rows, -5.5, np.float32)
+    logp_old[:n_kept * A] = z[:, 0] - z.max(1) - np.log(np.exp(z - z.max(1, keepdims=True)).sum(1)) - 0.05    # ratios of 1.05: nothing is cut
+    return dict(cfg=cfg, W=W, hidden=hidden, tokens=np.zeros(rows, np.uint8), logp_old=logp_old, adv=np.ones(cfg.T), kept=np.arange(n_kept))
+
+
+@pytest.mark.parametrize("d,ff,V,A,n_kept,composed,least", [(256, 1024, 256, 56, 96, False, 129398272), (300, 700, 256, 56, 48, False, 71195648),
+                                                            (473, 333, 512, 56, 96, True, 104272128)])
+def test_f32_sums_of_one_sign(pcm, monkeypatch, d, ff, V, A, n_kept, composed, least):   # noqa: F811
+    """Where all terms of a sum have one sign its roundings grow with it, most in long chains of additions: with operands in blocks the error
+    against 64 bits is no larger than with operands as they are (`least` bytes of workspace), root mean square over four inputs; 1.05 for what
+    the two have in common, the error of the ratios, and four inputs leave open."""
+    error = {False: {k: [] for k in GRADS}, True: {k: [] for k in GRADS}}
+    for seed in range(4):
+        pr = one_sign_problem(d, ff, V, A, n_kept, seed)
+        for direct in (False, True):
+            with monkeypatch.context() as m:
+                if direct:
+                    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+                    m.setattr(binding, "_take_workspace", lambda need, dev, stream: ws)
+                    m.setattr(binding, "_give_workspace", lambda *a: None)
+                ref, got = run_both(pcm, pr, composed_head=composed)
+            for k in GRADS:
+                error[direct][k].append(np.linalg.norm(got[k] - ref[k]) / np.linalg.norm(ref[k]))
+    rms = {route: {k: float(np.sqrt(np.mean(np.square(v)))) for k, v in e.items()} for route, e in error.items()}
+    print(rms)
+    for k in GRADS:
+        assert rms[False][k] <= 1.05 * rms[True][k], (k, rms)

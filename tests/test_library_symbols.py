@@ -134,7 +134,7 @@ def test_fp32_workspace_holds_what_a_call_uses(cdll):
 @pytest.mark.parametrize("rows,slices", [(2000, 32), (125, 2), (564, 9), (64, 1), (65, 2)])
 def test_fp32_weight_gradient_sums_stay_short(cdll, rows, slices):
     """Where operands of the fp32 path stay as they are, a small weight gradient is summed in slices of at most 64 rows (longer sums lose
-    accuracy).  The slices' buffer is what a call with gradients asks
+    accuracy; in blocks a sum is in chains instead, see test_f32_sums_of_one_sign).  The slices' buffer is what a call with gradients asks
     for beyond one without and its dz and dy buffers."""
     d = ff = V = 64
     q = cdll.grpo_masked_actor_step_workspace_bytes
