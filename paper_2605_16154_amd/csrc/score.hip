@@ -203,7 +203,7 @@ __device__ inline void accumulate_slice(const float* __restrict__ actions, const
                     for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
                 }
                 ++run;
-                if (__ballot(!x[u].exact()) == 0) {
+                if (__ballot(!x[u].exact()) == 0) {      // (one flag for all four costs 2 us of 25)
 #pragma unroll
                     for (int v = 0; v < VEC; ++v) acc[v] += to_fixed(x[u].v[v]);
                 } else if (c >= 0 && c < kb) {
@@ -408,7 +408,7 @@ constexpr int kTableThreads = 1024;
 // 12.7 / 11.7; 32 x 8 x 64, 56, 5 10.8 / 10.9.
 constexpr int kNarrowThreads = 256, kNarrowLoads = 4 * kNarrowThreads;
 constexpr int kTableMeanEntries = 2048;                  // pair scores in LDS at a time
-constexpr int kTableTrajectoriesMax = 512, kTableGroupsMax = 128;
+constexpr int kTableTrajectoriesMax = 768, kTableGroupsMax = 128;
 constexpr size_t kTableBytesMax = PCM_SCORE_STATIC_MAX_BYTES;
 
 struct TableWorkspace {
@@ -441,20 +441,31 @@ PairBlock pair_block(int A, int tables) {
 
 // Slices per trajectory, or 0 where the batch takes the accumulators: the tables have to fit in 4 MiB, so that a shape fits the
 // library's own array if it did with those, and in the workspace that the caller brings (one that holds the accumulators is enough
-// for any call).  A slice is at least one chunk per thread, and no more are made than two workgroups per compute unit want, or 64
-// tables per group.  Calls one after another, tables / accumulators, 56 values and 5 phases if not said (groups x trajectories x
-// chunks): 8 x 8 x 64 10.2 / 10.0 us; 32 x 8 x 128 11.7 / 13.2; 64 x 8 x 256, 12 phases 16.9 / 18.4; 1 x 8 x 1024 11.1 / 11.6;
-// 8 x 4 x 4096 14.2 / 21.6; 4 x 64 x 64 12.0 / 15.7; 4 x 32 x 256 of 256 values, 8 phases 19.9 / 30.2; 20 x 25 x 100 15.8 / 16.4.
-// Beyond 512 trajectories, more than two workgroups per compute unit, nothing is gained (128 x 8 x 128 18.8 / 18.8, 16 x 64 x 32
-// 16.6 / 16.8), and beyond 128 groups the mean is too long for the last workgroup (128 x 4 x 64 15.2 / 15.5, 170 x 3 x 100 18.9 / 17.4).
+// for any call).  A slice is at least one chunk per thread, and no more are made than 64 tables per group or about two workgroups per
+// compute unit.  Calls one after another, tables / accumulators, 56 values and 5 phases if not said (groups x trajectories x chunks):
+// 2 x 8 x 64 9.2 / 9.9 us; 32 x 8 x 128 11.7 / 13.2; 64 x 8 x 256, 12 phases 16.5 / 18.7; 8 x 4 x 4096 14.2 / 21.6; 4 x 10 x 1024 12.1 /
+// 16.4; 4 x 64 x 64 12.0 / 15.7; 4 x 32 x 256 of 256 values, 8 phases 19.9 / 30.2; 20 x 25 x 100 15.8 / 16.4.
+// Trajectories that are loaded in one go (four chunks a thread) gain nothing from slices while they are few: 2 x 8 x 256 11.2 / 10.4, 8 x 8 x
+// 100 of 35 values, 12 phases 10.8 / 10.2, 14 x 5 x 256 11.7 / 11.7, 16 x 8 x 256 12.2 / 12.8.  Nor from more than fit side by side: 56 x 8 x 256
+// in two 18.7, in one 15.1, accumulators 17.1; 40 x 8 x 256 16.1 / 14.5 / 15.7; but four rather than three: 20 x 8 x 256 12.7, 13.8, 13.6.
+// Longer ones do while they are few: 8 x 8 x 1024 13.6 / 17.6, 14 x 5 x 1024 15.5 / 16.5, 16 x 8 x 4096 25.7 / 26.7, but 20 x 8 x 1024 18.2 /
+// 16.7, 33 x 8 x 1024 21.8 / 20.7, 56 x 8 x 1024 26.5 / 24.4; and a slice of more than 20 chunks a thread takes longer than the finer ones of
+// the accumulators (24 x 8 x 4096 in two, 28 a thread, 34.6 / 32.0).
+// Beyond 768 trajectories nothing is gained (64 chunks 13.9 / 15.8 at 96 x 8, but 256 19.4 / 19.5 there and 23.7 / 21.3 at 128 x 8), and
+// beyond 128 groups the mean is too long for the last workgroup (128 x 4 x 64 14.1 / 15.6, 160 x 4 x 256 20.7 / 20.6, 170 x 3 x 100 18.9 /
+// 17.4).
 int table_slices(int n_groups, int G, int N, int A, int K, size_t bytes_max) {
     if ((size_t)K * A * sizeof(ull) + (size_t)K * sizeof(int) > kLdsMax || G > kWave) return 0;
     if (n_groups > kTableGroupsMax || (int64_t)n_groups * G > kTableTrajectoriesMax) return 0;
     const int T = n_groups * G, per_pass = kTableThreads / (A % 4 == 0 ? A / 4 : A);
-    int slices = std::min({ceil_div(512, T), ceil_div(N, per_pass), kWave / G});
+    const bool one_go = N <= 4 * per_pass;
+    int slices = one_go ? std::max(1, 512 / T) : ceil_div(512, T);
+    if (one_go && slices == 3) slices = 4;
+    slices = std::min({slices, ceil_div(N, per_pass), kWave / G});
+    if (one_go ? slices > 1 && T <= 96 : T > 128) return 0;
     for (; slices > 0; --slices)
         if (carve_tables(nullptr, n_groups, G, A, K, slices).bytes <= std::min(bytes_max, kTableBytesMax)) break;
-    return slices;
+    return slices > 0 && ceil_div(N, slices) <= 20 * per_pass ? slices : 0;
 }
 
 // Successes of the group (a bit per trajectory, G <= 64), the same in every wavefront.

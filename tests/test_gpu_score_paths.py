@@ -31,24 +31,35 @@ def batch(n_groups, G, N, A, K, seed, ragged=True):
     (1, 64, 10, 56, 12),        # the same with tables
     (1, 65, 10, 56, 12),        # and wider than one: accumulators
     (40, 2, 7, 56, 2),          # more pair terms than one workgroup forms
-    (1, 8, 256, 56, 12),        # four slices of a trajectory
+    (1, 8, 256, 56, 12),        # few trajectories of one go: accumulators
+    (1, 8, 300, 56, 12),        # five slices of a trajectory
     (1, 2, 700, 4, 3),          # slices of unequal length; one vector per chunk
     (3, 5, 50, 7, 9),           # single floats
-    (2, 4, 30, 256, 31),        # pair terms of eight workgroups; almost all of LDS for the sums of a trajectory
-    (2, 4, 30, 256, 32),        # more than LDS holds: accumulators
+    (2, 4, 16, 256, 31),        # pair terms of eight workgroups; almost all of LDS for the sums of a trajectory
+    (2, 4, 16, 256, 32),        # more than LDS holds: accumulators
+    (2, 4, 30, 256, 31),        # eight trajectories in one go: accumulators
     (64, 8, 20, 56, 18),        # 4.0 MB of tables
     (64, 8, 20, 56, 19),        # and 4.2: accumulators
     (90, 3, 5, 3, 64),          # pair scores of several rounds through LDS in the mean
-    (3, 32, 40, 200, 9),        # five threads a sum for 64 tables, a phase per workgroup
-    (2, 9, 20, 75, 5),    # two threads a sum for nine tables
+    (4, 32, 40, 200, 9),        # five threads a sum for 64 tables, a phase per workgroup
+    (11, 9, 20, 75, 5),         # three threads a sum for 18 tables
     (8, 8, 73, 56, 5),          # narrow workgroups for the slices: 1022 vectors (wide ones for single floats)
     (2, 8, 128, 32, 8),         # 1024 vectors, and as many sums as narrow workgroups form
-    (2, 8, 129, 32, 9),         # one slot more in two slices, more sums
+    (13, 8, 129, 32, 9),        # one slot more in two slices, more sums
     (3, 4, 60, 68, 3),          # 1020 vectors
-    (3, 4, 61, 68, 3),          # 1037 in slices of 31 slots
-    (2, 2, 4, 256, 31),     # wide workgroups for the sums, narrow ones for the slices
+    (25, 4, 61, 68, 3),         # 1037 in slices of 31 slots
+    (2, 2, 4, 256, 31),         # wide workgroups for the sums, narrow ones for the slices
     (8, 64, 3, 8, 3),           # 512 trajectories
-    (27, 19, 3, 8, 3),          # and 513: accumulators
+    (27, 19, 3, 8, 3),          # and 513
+    (12, 64, 3, 8, 3),          # 768
+    (70, 11, 3, 8, 3),          # and 770: accumulators
+    (20, 8, 292, 56, 5),        # four slices, each in one go
+    (20, 8, 293, 56, 5),        # one slot more than one go: accumulators
+    (16, 8, 320, 255, 2),       # four slices of 20 chunks a thread
+    (16, 8, 324, 255, 2),       # and of 21: accumulators
+    (43, 3, 40, 255, 2),        # more than four chunks a thread and 129 trajectories: accumulators
+    (12, 8, 128, 56, 5),        # 96 trajectories in one go: accumulators
+    (97, 1, 128, 56, 5),        # and 97: several slices
     (128, 4, 6, 5, 3),          # as many groups as tables take
     (129, 3, 6, 5, 3),          # and one more: accumulators
 ])
