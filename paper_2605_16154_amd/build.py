@@ -54,13 +54,14 @@ def _build_pointers() -> None:
     import torch
     from torch.utils.cpp_extension import include_paths
     torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", sysconfig.get_paths()["include"],
            *(x for path in include_paths() for x in ("-isystem", path)), os.path.join(CSRC, "pointers.cpp"), "-o", POINTERS,
            "-L", torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{torch_lib}"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("building pointers.cpp failed:\n" + r.stderr)
+    sys.stderr.write(r.stderr)
 
 
 def build_library(jobs: int = 8) -> str:

@@ -104,13 +104,16 @@ struct GatherArgs {
     RowMeta meta;
 };
 // Copies the kept chunks' hidden rows into X [rows_pad, d] (rows from n_kept*A to the end of
-// their tile of 256 are zero-filled, later ones left as they are: nothing reads them) and fills the row metadata.  elem_bytes is 2 (bf16) or 4 (fp32).
+// their tile of 256 are zero-filled, later ones left as they are: nothing reads them) and fills the row metadata (bf16).
 // With row_offset > 0 the rows are those of a panel of the batch that starts at that row: X and the metadata
 // arrays are the panel's own, `rows_pad` its height.  The same holds for the two per-chunk-ratio launches below
 // (row_offset a multiple of A, so no chunk straddles two panels).
 // In the same launch: the transposes of `layouts`, and zeros in zero[0 .. n_zero).
-[[nodiscard]] int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void* X, int64_t row_offset, int64_t rows_pad,
+[[nodiscard]] int launch_gather(const ActorShape& sh, const ActorIO& io, void* X, int64_t row_offset, int64_t rows_pad,
                   RowMeta meta, const TransposeList& layouts, double* zero, int n_zero, hipStream_t s);
+
+// The same of fp32 rows, as they are, of the whole batch.
+[[nodiscard]] int launch_gather_f32(const ActorShape& sh, const ActorIO& io, float* X, int64_t rows_pad, RowMeta meta, hipStream_t s);
 
 // Partial sums of squares of the four weight gradients, left by the launches that wrote their final values.
 struct SumsqLists {

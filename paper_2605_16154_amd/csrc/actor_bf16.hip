@@ -673,7 +673,7 @@ int actor_bf16_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_
         const RowMeta meta{w.meta.token + row0, w.meta.logp_old + row0, w.meta.adv + row0};
         const RowOut out{w.out.term + row0, w.out.ratio + row0, w.out.dlogp + row0, w.out.clipped + row0,
                          w.out.entropy + row0, w.out.coef + row0};
-        rc = launch_gather(sh, io, 2, w.X, row0, Mp, meta, first ? layouts : TransposeList{}, w.sumsq[0], first ? n_zero : 0, s);
+        rc = launch_gather(sh, io, w.X, row0, Mp, meta, first ? layouts : TransposeList{}, w.sumsq[0], first ? n_zero : 0, s);
         if (rc != PCM_OK) return rc;
         {
             StageTimer t(ST_GEMM_GATE_UP, s);

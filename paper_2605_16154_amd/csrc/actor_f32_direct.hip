@@ -173,7 +173,7 @@ int direct_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t s)
     const float* Wo = static_cast<const float*>(io.Wo);
     const BatchRows rows{io.n_kept, sh.max_chunks, sh.A}, none{nullptr, 0, 0};
 
-    int rc = launch_gather(sh, io, 4, w.X, 0, M, w.meta, TransposeList{}, nullptr, 0, s);
+    int rc = launch_gather_f32(sh, io, w.X, M, w.meta, s);
     if (rc != PCM_OK) return rc;
     {
         StageTimer t(ST_F32_FORWARD, s);

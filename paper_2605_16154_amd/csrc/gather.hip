@@ -585,7 +585,8 @@ int launch_prepare_f32(const ActorShape& sh, const ActorIO& io, const FloatBlock
     return launch_status();
 }
 
-int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void* X, int64_t row_offset, int64_t rows_pad,
+namespace {
+int gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void* X, int64_t row_offset, int64_t rows_pad,
                   RowMeta meta, const TransposeList& layouts, double* zero, int n_zero, hipStream_t s) {
     StageTimer t(ST_GATHER, s);
     const int64_t row_bytes = (int64_t)sh.d * elem_bytes;
@@ -605,6 +606,14 @@ int launch_gather(const ActorShape& sh, const ActorIO& io, int elem_bytes, void*
     else if (elem_bytes == 4) launch(uint32_t{}, sh.d);
     else launch(uint16_t{}, sh.d);
     return launch_status();
+}
+}  // namespace
+int launch_gather(const ActorShape& sh, const ActorIO& io, void* X, int64_t row_offset, int64_t rows_pad, RowMeta meta,
+                  const TransposeList& layouts, double* zero, int n_zero, hipStream_t s) {
+    return gather(sh, io, 2, X, row_offset, rows_pad, meta, layouts, zero, n_zero, s);
+}
+int launch_gather_f32(const ActorShape& sh, const ActorIO& io, float* X, int64_t rows_pad, RowMeta meta, hipStream_t s) {
+    return gather(sh, io, 4, X, 0, rows_pad, meta, TransposeList{}, nullptr, 0, s);
 }
 
 void launch_transposes(const TransposeList& list, bool stream, hipStream_t s) {

@@ -432,10 +432,17 @@ void look_at_launch(const std::string& name, void** args, dim3 grid) {
     at = name.find("prepare_step<");
     if (at != std::string::npos) {
         const std::string vec = arguments(name, at + strlen("prepare_step<") - 1)[0];
-        if (vec != "unsignedint") return;               // fp32, unaligned
-        const auto& g = *static_cast<GatherArgs<uint32_t>*>(args[0]);
-        reads("prepare_step", g);
-        touches("prepare_step", "X", g.X, g.rows_pad, g.vec_per_row, g.vec_per_row, 4);
+        const auto look = [&](auto unit) {
+            const auto& g = *static_cast<GatherArgs<decltype(unit)>*>(args[0]);
+            reads("prepare_step", g);
+            writing = true;
+            touches("prepare_step", "X", g.X, g.rows_pad, g.vec_per_row, g.vec_per_row, sizeof unit);
+            writing = false;
+        };
+        if (vec.find("4") != std::string::npos) look(uint4{});
+        else if (vec == "unsignedint") look(uint32_t{});
+        else if (vec == "unsignedshort") look(uint16_t{});
+        else unknown(name);
         return;
     }
     if (name.find("finish_step") != std::string::npos) {
@@ -450,7 +457,7 @@ void look_at_launch(const std::string& name, void** args, dim3 grid) {
         }
         return;
     }
-    // left out: a value or two per row, and the bf16 path's copies of rows and weights
+    // left out: a value or two per row, and the bf16 path's copies of listed rows and of weights
     for (const char* kernel : {"finish_loss", "chunk_ratio_rows", "list_live_rows", "loss_rows_bf16", "scale_rows_bf16", "transpose_weights",
                                "sum_of_squares"})
         if (name.find(kernel) != std::string::npos) return;
