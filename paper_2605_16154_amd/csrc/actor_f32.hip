@@ -9,7 +9,7 @@
 // times, and sums over many rows are in chains that are added up.  They do 16 times the multiply-adds of the fp32 ones: six
 // products take 3/8 of the time at the same share of their rates.
 // Measured against fp32 matrix instructions throughout, steps: 10,752 rows of 1024 -> 2816 -> 1024 -> 256, a quarter of them not kept,
-// 3.74 -> 2.54 ms; 5376 of 256 -> 1024 -> 256 -> 256 362 -> 262 to 287 us, by the box; 360 of 473 -> 333 -> 473 -> 512 185 -> 124, 1440
+// 3.74 -> 2.54 ms; 5376 of 256 -> 1024 -> 256 -> 256 362 -> 259 to 287 us, by the box; 360 of 473 -> 333 -> 473 -> 512 185 -> 124, 1440
 // of 619 -> 1302 -> 619 -> 256 413 -> 201, 8960 of 103 -> 149 -> 103 -> 256, composed, where most of the padded tiles is padding,
 // 171 -> 149; faster at 16 of 16 sizes, 1.15 to 2.06 times.  Loss, log-probabilities and statistics have the same bits; errors of the
 // gradients against 64 bits, root mean square over six inputs each: dX 4.85e-6 -> 4.74e-6 and 2.78e-6 -> 2.71e-6 at the first two, no
@@ -101,8 +101,8 @@ __device__ inline float wave_sum(float x) {
     return x;
 }
 
-// (see LossArgs; kQ * 64 columns at most: 43,008 rows of 256 take 4 us longer with the checks of 1024)
-template <int kQ>
+// (see LossArgs; kQ * 64 columns at most: with the checks of 1024, 43,008 rows of 256 take 4 us longer, 2688 of 512 0.9)
+template <int kQ, bool kInPlace>
 __global__ __launch_bounds__(kThreads) void loss_rows(LossArgs p) {
     const int lane = threadIdx.x % kWave;
     const int64_t r = (int64_t)blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kThreads) void loss_rows(LossArgs p) {
         }
         if (p.logp_out && live) p.logp_out[r] = lp;
     }
-    if (p.dz.p == nullptr && !p.in_place) return;
+    if (!kInPlace && p.dz.p == nullptr) return;
     const float coef = p.opt.chunk_ratio ? (live ? 1.f : 0.f) : (live ? lr.coef : 0.f);
     const float ec = live ? p.opt.entropy_coef * scale : 0.f;
 #pragma unroll
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kThreads) void loss_rows(LossArgs p) {
         if (p.opt.chunk_ratio) {
             zr[j] = pg;
             if (live && j < p.V) p.extra[r * p.V + j] = ent;
-        } else if (p.in_place) {
+        } else if (kInPlace) {
             zr[j] = pg + ent;
         } else {
             const float x[2] = {pg + ent, 0.f};
@@ -288,6 +288,10 @@ struct F32Workspace {
     size_t bytes;
 };
 
+// (Where all of a step stays in the caches, what the next one reads first is better not the place that was written last: 2688 rows of
+// 93 -> 250 with du and dv of 9 MB 98.4 us in the place of X, a and y, 96.4 apart; 5376 of 256 -> 1024, 66 MB, 272.8 and 274.3.)
+constexpr size_t kOverlayBytes = (size_t)32 << 20;
+
 F32Workspace carve(void* ws, const ActorShape& sh, bool bwd, const LossOptions& opt, bool composed) {
     Carver c(ws);
     F32Workspace w{};
@@ -297,14 +301,18 @@ F32Workspace carve(void* ws, const ActorShape& sh, bool bwd, const LossOptions& 
     const F32Plan& plan = w.plan = plan_step(sh, Mp, composed);
     const int64_t ffp = padded(sh.ff), Vp = padded(sh.V);
     const size_t M = (size_t)sh.rows_max(), d = sh.d, ff = sh.ff, V = sh.V;
-    // du and dv come when X, a and y as floats are no longer needed, and lie in their place
+    // du and dv come when X, a and y as floats are no longer needed, and lie in their place if they are large
     w.X = floats(Mp, sh.d);
     w.a = floats(Mp, sh.ff);
     if (!composed) w.y = floats(Mp, sh.d);
     if (bwd) {
-        w.duv = Thirds{reinterpret_cast<bf16*>(w.X.p), 2 * ffp};
         const size_t bytes = (size_t)Mp * 2 * ffp * 3 * sizeof(bf16);
-        if (bytes > c.used()) c.take<uint8_t>(bytes - c.used());
+        if (bytes > kOverlayBytes) {
+            w.duv = Thirds{reinterpret_cast<bf16*>(w.X.p), 2 * ffp};
+            if (bytes > c.used()) c.take<uint8_t>(bytes - c.used());
+        } else {
+            w.duv = thirds(Mp, 2 * ffp);
+        }
     }
     w.WguT = floats(2 * ffp, sh.d);
     w.WdT = composed ? floats(sh.ff, sh.d) : floats(sh.d, sh.ff);
@@ -382,8 +390,13 @@ bool uses_blocks(const ActorShape& sh, bool bwd, bool composed) {
 
 void launch_loss_rows(const LossArgs& p, hipStream_t s) {
     const unsigned grid = (unsigned)ceil_div(p.rows, kThreads / kWave);
-    if (p.ld <= 256) loss_rows<4><<<grid, kThreads, 0, s>>>(p);
-    else loss_rows<kMaxV / kWave><<<grid, kThreads, 0, s>>>(p);
+    const auto launch = [&](auto columns) {
+        if (p.in_place) loss_rows<decltype(columns)::value, true><<<grid, kThreads, 0, s>>>(p);
+        else loss_rows<decltype(columns)::value, false><<<grid, kThreads, 0, s>>>(p);
+    };
+    if (p.ld <= 4 * kWave) launch(Index<4>{});
+    else if (p.ld <= 8 * kWave) launch(Index<8>{});
+    else launch(Index<kMaxV / kWave>{});
 }
 
 size_t actor_f32_least_bytes(const ActorShape& sh, bool bwd) { return direct_workspace_bytes(sh, bwd); }

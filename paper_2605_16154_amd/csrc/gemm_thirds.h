@@ -104,11 +104,12 @@ __device__ __forceinline__ void thirds_tile(const GemmProblem& p, const Epilogue
     // 2^-8 of the whole that does not count.  With kChainSteps the first are one chain of additions over that many steps (an even
     // number), and the chains are added up: over the rows of a batch a single chain rounds more often than the parts of a sum on the
     // fp32 matrix instructions do.  (A flush per chain in a loop around the steps: as a branch among them it costs 2.6 % of a step.)
-    Accumulators<kW> high, low, whole;
+    Accumulators<kW> high, low, whole;                          // whole: of the chains before this one, if there are any
+    bool chained = false;
 #pragma unroll
     for (int i = 0; i < kW; ++i)
 #pragma unroll
-        for (int j = 0; j < kW; ++j) high[i][j] = low[i][j] = whole[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < kW; ++j) high[i][j] = low[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     if (step_begin < step_end) {
         const int last = step_end - 1;
@@ -201,10 +202,11 @@ __device__ __forceinline__ void thirds_tile(const GemmProblem& p, const Epilogue
             for (int i = 0; i < kW; ++i)
 #pragma unroll
                 for (int j = 0; j < kW; ++j) {
-                    whole[i][j] += high[i][j];
+                    whole[i][j] = chained ? whole[i][j] + high[i][j] : high[i][j];
                     high[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
                     asm volatile("s_nop 1" : "+a"(high[i][j]));             // an MFMA may follow
                 }
+            chained = true;
         }
         wait_direct_loads<0>();
         wait_mfma_results(high);
@@ -215,7 +217,7 @@ __device__ __forceinline__ void thirds_tile(const GemmProblem& p, const Epilogue
     for (int i = 0; i < kW; ++i)
 #pragma unroll
         for (int j = 0; j < kW; ++j) {
-            if (Epilogue::kChainSteps > 0) high[i][j] += whole[i][j];
+            if (chained) high[i][j] += whole[i][j];
             high[i][j] += low[i][j];
         }
     const TileCoord<kW> tc{m0, n0, wm, wn, lane, split};

@@ -55,6 +55,7 @@ __device__ __forceinline__ void split_in_three(const float (&x)[kN], uint32_t (&
             const float r1 = t == 0 ? __builtin_amdgcn_fmed3f(r[1], -largest, largest) : r[1];
             const bf16x2 part = {(__bf16)r0, (__bf16)r1};
             out[t][q] = __builtin_bit_cast(uint32_t, part);
+            asm("" : "+v"(out[t][q]));              // (else the compiler converts the first of the two again, by itself)
             r[0] -= __builtin_bit_cast(float, out[t][q] << 16);
             r[1] -= __builtin_bit_cast(float, out[t][q] & 0xFFFF0000u);
         }
