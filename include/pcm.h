@@ -281,10 +281,10 @@ PCM_API int pcm_kept_phase_counts(const uint8_t* phase, const int32_t* n_chunks,
  * dtype PCM_BF16: bf16 storage, MFMA with fp32 accumulation, bf16 intermediates;
  *             requires d % 256 == 0, ff % 256 == 0, V == 256.
  * ------------------------------------------------------------------------------------------ */
-/* fp32: the query names the bytes with which the call is fastest.  A call takes any workspace that holds its
- * matrices as they are, about rows * (12 d + 12 ff + 8 V) + 8 ff V bytes and the parts of the weight gradients
- * (rows * (8 d + 12 ff + 4 V) + 8 ff V without gradients); loss and log-probabilities have the same bits either way,
- * gradients differ by the rounding of their sums. */
+/* fp32: the query names the bytes with which the call is fastest.  A call of up to 4,194,240 rows takes any
+ * workspace that holds its matrices as they are, about rows * (12 d + 12 ff + 8 V) + 8 ff V bytes and the parts
+ * of the weight gradients (rows * (8 d + 12 ff + 4 V) + 8 ff V without gradients).  Loss and log-probabilities
+ * have the same bits either way, gradients differ by the rounding of their sums. */
 PCM_API size_t grpo_masked_actor_step_workspace_bytes(int max_kept_chunks, int A, int d, int ff, int V,
                                               int dtype, int want_grads);
 PCM_API int grpo_masked_actor_step(const void* hidden, const uint8_t* tokens, const float* logp_old,

@@ -25,7 +25,8 @@ struct LossArgs {
 };
 void launch_loss_rows(const LossArgs& p, hipStream_t s);
 
-// The direct route (actor_f32_direct.hip).
+// The direct route (actor_f32_direct.hip).  A launch has a row of workgroups per 64 rows, and at most 65,535 of them.
+constexpr int64_t kDirectRowsMax = 65535 * 64;
 size_t direct_workspace_bytes(const ActorShape& sh, bool bwd);
 int direct_run(const ActorShape& sh, const ActorIO& io, void* ws, hipStream_t s);
 

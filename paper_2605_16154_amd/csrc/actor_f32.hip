@@ -379,6 +379,7 @@ F32Workspace carve(void* ws, const ActorShape& sh, bool bwd, const LossOptions& 
 // Elsewhere blocks are ahead, up to 1.8 times.
 bool uses_blocks(const ActorShape& sh, bool bwd, bool composed) {
     const int64_t rows = sh.rows_max(), head = (int64_t)sh.d * sh.ff, M = 1 << 20;
+    if (rows > kDirectRowsMax) return true;
     if (rows <= 64 && head > 32 * M && (bwd || composed)) return false;
     if (std::min(sh.d, sh.ff) <= 64 && rows > 32768 && (!composed || sh.ff <= 512)) return false;
     if (head <= 4 * 1024) return false;
@@ -409,7 +410,7 @@ int actor_f32_run(const ActorShape& sh, const ActorIO& io, void* ws, size_t ws_b
     const bool grads = io.want_grads(), bwd = grads || io.dX != nullptr;
     if (!uses_blocks(sh, bwd, io.composed)) return direct_run(sh, io, ws, s);
     const F32Workspace w = carve(ws, sh, bwd, io.opt, io.composed);
-    if (w.bytes > ws_bytes) return direct_run(sh, io, ws, s);
+    if (w.bytes > ws_bytes) return sh.rows_max() > kDirectRowsMax ? (int)PCM_EWORKSPACE : direct_run(sh, io, ws, s);
     const F32Plan& plan = w.plan;
     const int Mp = (int)w.Mp, M = (int)sh.rows_max(), d = sh.d, ff = sh.ff, V = sh.V;
     const int ffp = (int)padded(ff), Vp = (int)padded(V), dp = (int)padded(d);

@@ -515,7 +515,7 @@ hipError_t hipLaunchKernel(const void* stub, dim3 grid, dim3 block, void** args,
     const bool fails = launches++ == fail_at;
     if (fails) return last_error = hipErrorLaunchFailure;
     if (check_bounds) {
-        if (grid.x == 0 || grid.y == 0 || grid.z == 0 || block.x * block.y * block.z > 1024) unknown("an empty or too large grid");
+        if (grid.x == 0 || grid.y == 0 || grid.z == 0 || grid.y > 65535 || grid.z > 65535 || block.x * block.y * block.z > 1024) unknown("an empty or too large grid");
         spans.clear();
         look_at_launch(kernel_names()[stub], args, grid);
         check_overlaps(kernel_names()[stub].substr(0, 200).c_str());
@@ -624,6 +624,7 @@ void f32_calls(F f) {
     for (int chunks : {1, 2, 64, 65, 256, 257, 300}) calls(chunks, 1, 4096, 11008, 256);     // few rows under a wide head
     calls(20000, 56, 64, 64, 256);                                                           // and many under a narrow one
     calls(20000, 56, 65, 64, 64);
+    calls(74897, 56, 64, 64, 64);                                                            // the most rows of the direct route
 }
 void bounds() {
     check_bounds = true;
@@ -657,6 +658,9 @@ void least() {
         expect(run(c, enough), PCM_OK);
         expect(run(c, enough - 1), PCM_EWORKSPACE);
     });
+    const Step large{PCM_F32, 74898, 56, 64, 64, 64, true, true, false, false, false, false, false, 0.f, 0};     // beyond that route
+    expect(run(large), PCM_OK);
+    expect(run(large, query - 1), PCM_EWORKSPACE);
 }
 void errors() {
     auto each_launch = [&](const Step& c) {
